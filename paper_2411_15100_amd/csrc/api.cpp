@@ -811,14 +811,14 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
     if (max_levels == 0 || max_levels > kCtxLevels) max_levels = kCtxLevels;
     for (int l = 1; l < max_levels; ++l) {
       uint64_t next = 0;
-      for (uint16_t r : key_node) next += n_ctx(A.node_rule[r]);
+      for (uint16_t r : key_node) next += n_ctx(A.end_rule(A.node_rule[r]));
       if (next * (uint64_t)n_seg > ((uint64_t)1 << 26)) break;
       std::vector<uint16_t> next_node;
       next_node.reserve((size_t)next);
       c->k_base_host[l].resize(key_node.size());
       for (size_t q = 0; q < key_node.size(); ++q) {
         c->k_base_host[l][q] = (uint32_t)next_node.size();
-        for (int32_t r2 : A.contexts[A.node_rule[key_node[q]]]) next_node.push_back((uint16_t)r2);
+        for (int32_t r2 : A.contexts[A.end_rule(A.node_rule[key_node[q]])]) next_node.push_back((uint16_t)r2);
       }
       key_node.swap(next_node);
       n_k[l] = key_node.size();
@@ -897,6 +897,18 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
     }
     args.ctx_off = d_ctx_off;
     args.ctx_node = d_ctx_node;
+    {
+      std::vector<uint4> rule_info(A.rule_names.size());
+      std::vector<uint16_t> forced_node;
+      for (size_t r = 0; r < A.rule_names.size(); ++r) {
+        const auto& f = A.forced[r];
+        rule_info[r] = make_uint4((uint32_t)forced_node.size(), (uint32_t)f.size(), (uint32_t)A.end_rule((int32_t)r), 0u);
+        for (size_t k = f.size(); k-- > 0;) forced_node.push_back((uint16_t)f[k]);
+      }
+      if (forced_node.empty()) forced_node.push_back(0);
+      args.rule_info = arena.upload(rule_info, stream);
+      args.forced_node = arena.upload(forced_node, stream);
+    }
     args.counts = d_counts;
     // the counting pass of level 1 keeps what it found for every (pair, context), 2 bytes each, unless that
     // would take more than 1 GiB (then the writing pass walks again)
@@ -1181,8 +1193,10 @@ static void stack_keys(const Automaton& A, const xgm_cache& c, const Stack& s, u
   h[kStackHdrTop] = (uint32_t)top | ((uint32_t)c.acc_row_host[top] << 16);
   h[kStackHdrDepth] = (uint32_t)s.size();
   h[kStackHdrFrames] = frame_offset;
-  h[3] = 0u;
-  // the keys of the stack's lists: the top node's own; then one per frame below the top that a kept level reaches
+  const uint32_t depth = (uint32_t)s.size();
+  const uint32_t drops = stack_drops(depth, [&](uint32_t k) { return 1u + (uint32_t)A.forced[A.node_rule[s[depth - 1 - k]]].size(); });
+  h[kStackHdrDrops] = drops;
+  // the keys of the stack's lists: the top node's own; then one per level that the stack reaches and the cache keeps
   auto context_index = [&](int32_t frame_node, int32_t below) {
     const auto& ctx = A.contexts[A.node_rule[frame_node]];
     auto it = std::lower_bound(ctx.begin(), ctx.end(), below);
@@ -1194,8 +1208,9 @@ static void stack_keys(const Automaton& A, const xgm_cache& c, const Stack& s, u
   bool more = true;
   for (int l = 1; l <= kCtxLevels; ++l) {
     key[l] = kNoKey;
-    if (more && l <= c.levels && (int)s.size() >= l + 1 && c.k_base_host[l - 1][local] != kNoKey) {
-      local = c.k_base_host[l - 1][local] + context_index(s[s.size() - l], s[s.size() - l - 1]);
+    const uint32_t at = stack_drop(drops, (uint32_t)l);
+    if (more && l <= c.levels && at < depth && c.k_base_host[l - 1][local] != kNoKey) {
+      local = c.k_base_host[l - 1][local] + context_index(s[depth - at], s[depth - 1 - at]);
       key[l] = key0 + local;
     }
     more = key[l] != kNoKey;

@@ -711,6 +711,29 @@ Automaton compile_grammar(const std::string& text, const std::string& root) {
     for (int r = 0; r < NR; ++r) A.contexts[r].assign(ctx[r].begin(), ctx[r].end());
   }
 
+  // forced frames: at the bottom of a stack are the root rule and what it (or such a rule) enters by a tail call
+  {
+    std::vector<char> at_bottom(NR, 0);
+    at_bottom[A.root_rule] = 1;
+    for (bool changed = true; changed;) {
+      changed = false;
+      for (int n = 0; n < total; ++n)
+        if (at_bottom[A.node_rule[n]])
+          for (auto& e : A.redges[n])
+            if (A.node_dead_end[e.to] && !at_bottom[e.rule]) { at_bottom[e.rule] = 1; changed = true; }
+    }
+    A.forced.assign(NR, {});
+    for (int r = 0; r < NR; ++r) {
+      int cur = r;
+      while (A.contexts[cur].size() == 1 && !at_bottom[cur] && (int)A.forced[r].size() < kMaxForced) {
+        A.forced[r].push_back(A.contexts[cur][0]);
+        cur = A.node_rule[A.contexts[cur][0]];
+      }
+      // a short way down to the bottom is what the levels of a mask cache reach frame by frame
+      if (A.contexts[cur].empty() && (int)A.forced[r].size() <= kShortWayDown) A.forced[r].clear();
+    }
+  }
+
   // Alternatives of node n on byte c, in the order the walk tries them:
   //  * the byte edge;
   //  * for every reference whose callee can start with c: enter the callee.
@@ -796,7 +819,8 @@ Automaton compile_grammar(const std::string& text, const std::string& root) {
     A.targets.insert(A.targets.end(), outcomes.begin(), outcomes.end());
   }
   A.n_shapes = (int32_t)shape_ids.size();
-  for (int n = 0; n < total; ++n) A.hdr[n].flags |= (uint32_t)A.node_rule[n] << 16;
+  for (int n = 0; n < total; ++n)
+    A.hdr[n].flags |= (uint32_t)A.node_rule[n] << 16 | (uint32_t)(1 + A.forced[A.node_rule[n]].size()) << kChainShift;
   A.follow_words.assign((size_t)NR * 8, 0u);
   for (int r = 0; r < NR; ++r)
     for (int c = 0; c < 256; ++c) A.follow_words[(size_t)r * 8 + (c >> 5)] |= (uint32_t)A.follow[r].test(c) << (c & 31);

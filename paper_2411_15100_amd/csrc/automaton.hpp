@@ -28,13 +28,16 @@ struct RefEdge { int32_t rule; int32_t to; };
 struct NodeHdr {
   uint8_t lo, hi;
   uint16_t target;
-  uint32_t flags;  // kFlagFinal | kFlagBranching | kFlagDeadEnd | rule index << 16
+  uint32_t flags;  // kFlagFinal | kFlagBranching | kFlagDeadEnd | frames of the chain << kChainShift | rule index << 16
 };
 static_assert(sizeof(NodeHdr) == 8, "NodeHdr must be 8 bytes");
 
 constexpr uint32_t kFlagFinal = 1;      // the rule may end at this node
 constexpr uint32_t kFlagBranching = 2;
 constexpr uint32_t kFlagDeadEnd = 4;    // accepting and without outgoing edges: all it can do is return
+constexpr uint32_t kChainShift = 8;     // 8 bits: 1 + the forced frames below a frame of the node's rule
+constexpr int kMaxForced = 48;          // forced frames followed per rule (three levels of them stay below 256 frames)
+constexpr int kShortWayDown = 2;        // (the levels of a mask cache below the first)
 constexpr uint8_t kDeadShape = 0xFF;    // shape entry: nothing to do for this byte class
 constexpr uint16_t kAltFlag = 0x8000;   // outcome: index into the alternatives pool (else: move to that node)
 constexpr uint32_t kMoveTag = 0xFFFF;   // alternative (tag << 16 | node): consume the byte, go to node
@@ -58,6 +61,11 @@ struct Automaton {
   // per rule: the nodes that can sit right below a frame of that rule (return nodes of the references to it;
   // a reference in tail position hands on the contexts of the referring rule), sorted
   std::vector<std::vector<int32_t>> contexts;
+  // Per rule: the frames that are certain to lie below a frame of that rule, nearest first.  A rule with a single
+  // context that can never be at the bottom of a stack has that context below it; if the context's rule is of the
+  // same kind, so is its own context, and so on (the precedence levels of an expression grammar).
+  std::vector<std::vector<int32_t>> forced;
+  int32_t end_rule(int32_t rule) const { return forced[rule].empty() ? rule : node_rule[forced[rule].back()]; }
   int32_t root_rule = 0;
   std::vector<std::vector<int32_t>> node_path;  // witness path from the rule start
 

@@ -442,11 +442,16 @@ __device__ __forceinline__ TokenRef load_token(const DevVocab& voc, int32_t id) 
 //   exit_positions_kernel  one thread per pair: the token is walked once more from the node to find the
 //                          positions at which it leaves the node's frame;
 //   context_level1_kernel  one thread per (pair, a few contexts of the node's rule): the rest of the token is
-//                          walked from the context node with nothing known below.  Accepted there: an entry
-//                          of the (node, context) list.  Leaves that frame too: a record for the next level;
+//                          walked from the context node with nothing known below but the frames that this
+//                          context forces.  Accepted there: an entry of the (node, context) list.  Leaves all
+//                          those frames: a record for the next level;
 //   context_deeper_kernel  for level 2, 3, ...: one thread per (record of the level above, a few contexts of
-//                          the rule of that record's context node): the same one frame further down; what
-//                          leaves a frame beyond the last level becomes a walk entry.
+//                          the rule of the last frame left): the same one level further down; what leaves the
+//                          frames of the last level becomes a walk entry.
+// A frame with a single possible frame below it takes no level of its own: the precedence levels of an
+// expression grammar (a dozen frames with one context each between an identifier and the call or bracket it
+// stands in) are one level.  With levels of one frame the fill had to walk 48 K tokens over those frames where
+// an identifier ends in the C/SQL-like grammar (128256 tokens, one row: 950 us).
 // Most (pair, context) combinations end at the first byte of the rest, which the context node cannot
 // take.  All but the first kernel run twice: first they count the entries of every (key, segment), then,
 // with the offsets made from the counts, they write them.
@@ -535,17 +540,17 @@ struct ContextWork {
   __device__ __forceinline__ void step(uint32_t level, uint32_t r, uint32_t key_local, uint32_t ex, bool single,
                                        uint32_t* outcome = nullptr, uint32_t* lds_counts = nullptr) const {
     const uint32_t key = a.key0[level - 1u] + key_local;
-    // how a token that needs the live stack after all is listed here: from the frame of r on, if the way there is unique
-    const uint32_t walk_kind = single ? kEntryWalkTop + level : kEntryWalkTop;
-    const uint32_t walk_pos = single ? (uint32_t)__ffs(ex) - 1u : 0u;
     if (ex & 0x80000000u) { emit(key, kEntryWalkTop, 0u, outcome, lds_counts); return; }
-    bool accepted = false, over = false;
+    bool accepted = false, over = false, known = false;
+    uint4 info = make_uint4(0u, 0u, 0u, 0u);  // the frames that r forces below itself
     uint32_t ex_next = 0u, n_res = 0u;
     for (uint32_t m = ex; m != 0u && !accepted; m &= m - 1u) {
       const uint32_t k = __ffs(m) - 1u;
       if (!plausible(r, k)) continue;
+      if (!known) { info = a.rule_info[T.header(r).y >> 16]; known = true; }
       uint32_t x = 0u;
-      const int res = walk_token<true>(T, t.tk, t.ext, t.len, r, (const uint16_t*)nullptr, 1u, nullptr, T.follow_of(r), (int)k, &x);
+      const int res = walk_token<true, true>(T, t.tk, t.ext, t.len, r, (const XGM_GLOBAL uint16_t*)(a.forced_node + info.x), info.y + 1u,
+                                             nullptr, info.z, (int)k, &x);
       if (res == kAccept) accepted = true;
       else if (res == kOverflow) over = true;
       else if (res == kUncertain) { ex_next |= x; ++n_res; }
@@ -553,16 +558,20 @@ struct ContextWork {
     if (accepted) { emit(key, kEntryAccepted, 0u, outcome, lds_counts); return; }
     if (over) { emit(key, kEntryWalkTop, 0u, outcome, lds_counts); return; }
     if (ex_next == 0u) return;  // rejected in this context
-    if (level == (uint32_t)kCtxLevels || a.k_base[level] == nullptr || (ex_next & 0x80000000u)) {
-      emit(key, walk_kind, walk_pos, outcome, lds_counts);
-      return;
-    }
-    // It leaves this frame as well: records for the next level, one per chunk of kContextsPerThread contexts
-    // of this context node's rule (a rule without contexts has nothing below it: the token ends there).
+    // It leaves these frames as well: records for the next level, one per chunk of kContextsPerThread contexts
+    // of the last frame's rule (a rule without contexts has nothing below it: the token ends there).
     // The lanes that get here together are taken rule by rule, each group with one atomic.
-    const uint32_t rule = T.header(r).y >> 16;
+    const uint32_t rule = info.z;
     const uint32_t n_ch = (a.ctx_off[rule + 1] - a.ctx_off[rule] + kContextsPerThread - 1u) / kContextsPerThread;
     const bool single_next = single && n_res == 1u && (ex_next & (ex_next - 1u)) == 0u;
+    if (level == (uint32_t)kCtxLevels || a.k_base[level] == nullptr || (ex_next & 0x80000000u)) {
+      // the live stack decides: the walk starts where the way so far is unique
+      if (n_ch == 0u) return;
+      if (single_next && !(ex_next & 0x80000000u)) emit(key, kEntryWalkTop + level + 1u, (uint32_t)__ffs(ex_next) - 1u, outcome, lds_counts);
+      else if (single) emit(key, kEntryWalkTop + level, (uint32_t)__ffs(ex) - 1u, outcome, lds_counts);
+      else emit(key, kEntryWalkTop, 0u, outcome, lds_counts);
+      return;
+    }
     const uint32_t lane = threadIdx.x & 63u;
     for (bool pending = true; pending;) {
       const uint32_t lead = __builtin_amdgcn_readfirstlane(rule);
@@ -962,7 +971,7 @@ __device__ __forceinline__ void fill_walks(const Tab& T, FillShared& sm, const R
     const XGM_GLOBAL v4u* off = (const XGM_GLOBAL v4u*)(sh + stack_hdr_off((uint32_t)seg, 0u));
     const v4u scalars = *(const XGM_GLOBAL v4u*)sh, o0 = off[0], o1 = off[1];
     const uint32_t top = scalars.x & 0xFFFFu, depth = scalars.y, f_off = scalars.z;
-    static_assert(kStackHdrTop == 0 && kStackHdrDepth == 1 && kStackHdrFrames == 2 && kStackHdrWords == 4 && kStackLists == 4,
+    static_assert(kStackHdrTop == 0 && kStackHdrDepth == 1 && kStackHdrFrames == 2 && kStackHdrDrops == 3 && kStackHdrWords == 4 && kStackLists == 4,
                   "a stack's scalars are one 16-byte load, a segment's list offsets another");
     LiveView live;
     live.lds = (const XGM_LDS uint16_t*)sm.live + (f_off - frame0);
@@ -978,7 +987,7 @@ __device__ __forceinline__ void fill_walks(const Tab& T, FillShared& sm, const R
         if (kind == kEntryAccepted) continue;
         const uint32_t rel = id - (uint32_t)id0;
         if ((sm.words[rel >> 5] >> (rel & 31u)) & 1u) continue;  // already allowed
-        const uint32_t drop = kind == kEntryWalkTop ? 0u : kind - 1u;  // frames above the one the walk starts in
+        const uint32_t drop = stack_drop(scalars.w, kind - kEntryWalkTop);  // frames above the one the walk starts in
         int res = kReject;
         uint32_t n_steps = 0;
         if (depth > drop) {
@@ -1225,7 +1234,8 @@ __global__ __launch_bounds__(kAcceptThreads) void batch_accept_kernel(DevBatch b
   __shared__ uint32_t foff[kBatchMaxStacks + 1];
   __shared__ uint32_t slot_of[kBatchMaxStacks];    // candidate index per rank
   __shared__ uint32_t keys[kBatchMaxStacks][kStackLists];  // the three lists of every new stack
-  __shared__ uint32_t cidx[kBatchMaxStacks][kCtxLevels];   // which context of its rule each of the top frames sits on
+  __shared__ uint32_t cidx[kBatchMaxStacks][kCtxLevels];   // which context of its rule the frame above each level sits on
+  __shared__ uint32_t drops[kBatchMaxStacks];
   __shared__ uint32_t ccount, coverflow, n_new, can_end, bad_context, not_final;
   const uint32_t tid = threadIdx.x;
   const int32_t b = blockIdx.x;
@@ -1325,14 +1335,18 @@ __global__ __launch_bounds__(kAcceptThreads) void batch_accept_kernel(DevBatch b
       const uint32_t ci = slot_of[r], d = cdepth[ci];
       for (uint32_t k = tid; k < d; k += kAcceptThreads) bt.frames[fb + foff[r] + k] = cand[ci * kBatchMaxDepth + k];
     }
-    // which context of its rule each of the top frames sits on (one thread per stack and level)
+    // where the levels begin in every stack, and which context of its rule the frame above each of them sits on (one
+    // thread per stack and level)
     if (tid < ns * (uint32_t)kCtxLevels) {
       const uint32_t r = tid / (uint32_t)kCtxLevels, l = tid % (uint32_t)kCtxLevels + 1u;
       const uint32_t ci = slot_of[r], d = cdepth[ci];
       const uint16_t* st = cand + ci * kBatchMaxDepth;
       uint32_t idx = kNoKey;
-      if (d >= l + 1u) {
-        const uint32_t rule = T.header(st[d - l]).y >> 16, below = st[d - l - 1u];
+      const uint32_t dr = stack_drops(d, [&](uint32_t k) { return (T.header(st[d - 1u - k]).y >> kHdrChainShift) & kHdrChainMask; });
+      if (l == 1u) drops[r] = dr;
+      const uint32_t at = stack_drop(dr, l);
+      if (at < d) {
+        const uint32_t rule = T.header(st[d - at]).y >> 16, below = st[d - 1u - at];
         for (uint32_t k = dc.node_ctx_off[below]; k < dc.node_ctx_off[below + 1u]; ++k) {
           const uint32_t x = dc.node_ctx[k];
           if ((x >> 16) == rule) idx = x & 0xFFFFu;
@@ -1358,7 +1372,7 @@ __global__ __launch_bounds__(kAcceptThreads) void batch_accept_kernel(DevBatch b
       h[kStackHdrTop] = top | ((uint32_t)dc.acc_row[top] << 16);
       h[kStackHdrDepth] = d;
       h[kStackHdrFrames] = fb + foff[tid];
-      h[3] = 0u;
+      h[kStackHdrDrops] = drops[tid];
       // the keys: the top node's own list, then one per frame below that a kept level reaches
       keys[tid][0] = top;
       uint32_t local = top, key0 = (uint32_t)dc.n_nodes;

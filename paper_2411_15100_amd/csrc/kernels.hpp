@@ -104,11 +104,14 @@ struct DevVocab {
 //                                  them; the others keep a bitset row in `acc`);
 //   level 1, key = (n, i):         the context-dependent tokens of n that are accepted when the frame below
 //                                  is the i-th context node of n's rule (the nodes that can sit right below
-//                                  a frame of that rule: Automaton::contexts);
-//   level 2, key = (n, i, j):      those that leave that frame as well and are accepted when the next frame
-//                                  down is the j-th context node of the rule of context i;
-//   ... and so on, kCtxLevels frames deep.
-// Tokens that leave one more frame than that, or whose walk at build time hit a limit, are listed as "walk"
+//                                  a frame of that rule: Automaton::contexts), or in one of the frames that are
+//                                  then certain to follow below (Automaton::forced: they need no key);
+//   level 2, key = (n, i, j):      those that leave these frames as well and are accepted when the next frame
+//                                  down is the j-th context node of the rule of the last of them (or in the
+//                                  frames forced by that one);
+//   ... and so on, kCtxLevels levels deep.  Where a level begins in a stack: level 1 one frame below the top, level
+//   l + 1 as many frames below level l as the header of level l's node says (kHdrChain*).
+// Tokens that leave all frames of the last level, or whose walk at build time hit a limit, are listed as "walk"
 // entries: the fill kernel decides them against the live stack.
 // A key of level l >= 1 has a number among its level's keys; the keys of all levels share one numbering:
 // node n | n_nodes + (level-1 number) | n_nodes + n_k[0] + (level-2 number) | ...  The children of a key are
@@ -136,8 +139,8 @@ constexpr uint32_t kNoAccRow = 0xFFFFu;
 // A list entry: bits 0..19 token id, bits 20..27 position, bits 28..31 kind:
 //   kEntryAccepted       the token is allowed;
 //   kEntryWalkTop        walk the whole token from the top of the stack;
-//   kEntryWalkTop + d    walk it from byte `position` on, starting at the node d frames below the top (the
-//                        only position at which it leaves the frames above), d = 1 .. kCtxLevels.
+//   kEntryWalkTop + d    walk it from byte `position` on, starting at the first frame of level d (the only
+//                        position at which it leaves the frames above), d = 1 .. kCtxLevels + 1.
 constexpr uint32_t kEntryIdBits = 20, kEntryIdMask = (1u << kEntryIdBits) - 1u, kEntryPosShift = 20, kEntryKindShift = 28;
 constexpr uint32_t kEntryAccepted = 0, kEntryWalkTop = 1;
 constexpr uint32_t kNoKey = 0xFFFFFFFFu;
@@ -156,13 +159,31 @@ struct RowDesc {
 };
 // A stack header is kStackHdrWords + (n_seg + 1) * kStackLists uint32 words (a multiple of 16 bytes):
 //   [kStackHdrTop] top node | its row of DevCache::acc (or kNoAccRow) << 16, [kStackHdrDepth] number of frames,
-//   [kStackHdrFrames] offset of its frames (bottom first) in the uint16 frame array, [3] unused,
+//   [kStackHdrFrames] offset of its frames (bottom first) in the uint16 frame array, [kStackHdrDrops] how many
+//   frames below the top level 2, 3 and 4 begin (8 bits each; stack_drop()),
 //   [stack_hdr_off(s, l)] where the entries of segment s of the stack's level-l list start (s = n_seg: where
 //   the last segment's end); a stack without that list (too shallow, or a level that is not kept) has all of
 //   them equal.  The lists' offsets of one segment lie side by side, so that the workgroup of (row, segment)
 //   finds the begin and the end of all its lists of a stack in 32 consecutive bytes.
-constexpr uint32_t kStackHdrTop = 0, kStackHdrDepth = 1, kStackHdrFrames = 2, kStackHdrWords = 4;
+constexpr uint32_t kStackHdrTop = 0, kStackHdrDepth = 1, kStackHdrFrames = 2, kStackHdrDrops = 3, kStackHdrWords = 4;
 constexpr uint32_t kStackLists = 1 + kCtxLevels;
+// header word y of a node: bits 8..15 = 1 + the frames forced below a frame of the node's rule
+constexpr uint32_t kHdrChainShift = 8, kHdrChainMask = 0xFFu;
+// kStackHdrDrops of a stack; steps(k) = the chain field of the header of the node k frames below the top
+template <class Steps>
+#if defined(__HIPCC__) || defined(__HIP__)
+__host__ __device__
+#endif
+inline uint32_t stack_drops(uint32_t depth, const Steps& steps) {
+  uint32_t drops = 0u, at = 1u;
+  for (uint32_t l = 0; l < (uint32_t)kCtxLevels; ++l) {
+    at = at < depth ? at + steps(at) : 255u;  // (a level that the stack does not reach: no list refers to it)
+    drops |= (at < 255u ? at : 255u) << (8u * l);
+  }
+  return drops;
+}
+// where level d >= 1 begins: frames below the top
+constexpr uint32_t stack_drop(uint32_t drops, uint32_t d) { return d <= 1u ? d : (drops >> (8u * (d - 2u))) & 0xFFu; }
 constexpr uint32_t stack_hdr_stride(int32_t n_seg) { return kStackHdrWords + kStackLists * ((uint32_t)n_seg + 1u); }
 constexpr uint32_t stack_hdr_off(uint32_t seg, uint32_t l) { return kStackHdrWords + seg * kStackLists + l; }
 
@@ -270,6 +291,9 @@ struct ContextListArgs {
   uint32_t key0[kCtxLevels];   // the first key of level 1, 2, ... in the shared numbering
   const uint32_t* ctx_off;
   const uint16_t* ctx_node;
+  const uint4* rule_info;      // [n_rules] frames forced below a frame of the rule: x = first of them in forced_node, y = how
+                               // many, z = the rule of the last one (the rule itself if there is none)
+  const uint16_t* forced_node; // rule after rule, bottom frame first
   uint32_t* counts;            // [n_keys * n_seg]   write = false
   uint32_t* front;             // [n_keys * n_seg]   write = true
   uint32_t* back;              // [n_keys * n_seg]   write = true

@@ -86,22 +86,25 @@ XGM_HD uint32_t token_byte(const uint4& tk, const uint8_t* ext, int i) { return 
 // parent links, so that backing up to a pending alternative never copies a
 // stack (the persistent stack of section 3.3, in miniature).
 //
-// BUILD = true:  nothing is known below the start frame (depth must be 1);
+// BUILD = true:  nothing is known below the bottom frame (the start frame, or
+//                `depth` - 1 frames that are certain to lie below it);
 //                result kAccept / kUncertain / kReject as in section 3.1,
 //                refined by one byte of context (section 3.2 in miniature):
-//                leaving the start frame while bytes remain only counts if
+//                leaving the bottom frame while bytes remain only counts if
 //                the next byte is in the FOLLOW set of rule `follow` (the bytes
-//                that can come right after an instance of the start node's rule
-//                in any context; `T.follow_of(start_node)`); a token that left the frame only in front of other
+//                that can come right after an instance of the bottom node's rule
+//                in any context; `T.follow_of(bottom_node)`); a token that left the frame only in front of other
 //                bytes is kUncertainPlain: context-dependent by section 3.1
 //                alone, rejected in every context by the refinement.
 // BUILD = false: frames below are live[0 .. depth-2]; result kAccept (token
 //                allowed) or kReject.
+// PRUNE:         returns in front of a byte that can never follow the rule are left out (always when BUILD = false;
+//                with BUILD = true kUncertainPlain is then not told from kReject).
 // kOverflow: a limit was hit; the caller records the pair.
 // `steps_out` (may be null) receives the number of automaton steps taken.
 // `i0`: index of the first byte to consume (the walk may start inside the token).
 // `exits_out` (BUILD only, may be null): bit min(k, 31) is set for every
-// position k at which the start frame is left in front of a byte of `follow`.
+// position k at which the bottom frame is left in front of a byte of `follow`.
 // `Live` is anything indexable that yields the live frames (a plain pointer,
 // or a view that knows which of them sit in LDS).
 // `End` decides what the end of the token means.  The default returns kAccept
@@ -114,7 +117,7 @@ struct FirstPathEnds {
   template <class Live>
   XGM_HD void operator()(uint32_t, uint32_t, const uint32_t*, const Live&) const {}
 };
-template <bool BUILD, class Tab, class Live, class End = FirstPathEnds>
+template <bool BUILD, bool PRUNE = !BUILD, class Tab, class Live, class End = FirstPathEnds>
 XGM_HD int walk_token(const Tab& T, const uint4 tk, const uint8_t* ext, const int len,
                       const uint32_t start_node, const Live& live, const uint32_t depth,
                       uint32_t* steps_out = nullptr, const uint32_t follow = 0u, const int i0 = 0,
@@ -125,7 +128,7 @@ XGM_HD int walk_token(const Tab& T, const uint4 tk, const uint8_t* ext, const in
   uint2 choice[kChoicePoints];   // x = node | sp << 16 ; y = i | alt << 8 | top << 16 | f << 24
   uint32_t n = start_node, sp = kLiveBase + depth - 1, f = 1, alt = 0, top = 0, csp = 0;
   int i = i0;
-  uint32_t left_frame = 0u;  // bit 0: the start frame was left with bytes remaining, bit 1: in front of a byte of `follow`
+  uint32_t left_frame = 0u;  // bit 0: the bottom frame was left with bytes remaining, bit 1: in front of a byte of `follow`
   for (int steps = 0;; ++steps) {
     if (steps_out) *steps_out = (uint32_t)steps;
     if (i == len && !End::kEnumerate) return kAccept;
@@ -140,7 +143,7 @@ XGM_HD int walk_token(const Tab& T, const uint4 tk, const uint8_t* ext, const in
       T.lookup(n, c, k, single, base, pooled, fin, after);
       uint32_t can_pop = fin & f;
       if (BUILD && can_pop && sp == kLiveBase) {
-        // The start frame may end here (nothing is known below it): noted at once instead of kept as a
+        // The bottom frame may end here (nothing is known below it): noted at once instead of kept as a
         // pending alternative, so that a run through a rule that may end after every byte (the inside of
         // a string, a number) leaves nothing to come back to.
         const uint32_t fo = T.follows(follow, c);
@@ -148,7 +151,7 @@ XGM_HD int walk_token(const Tab& T, const uint4 tk, const uint8_t* ext, const in
         if (exits_out && fo) *exits_out |= 1u << (i < 31 ? i : 31);
         can_pop = 0u;
       }
-      if (!BUILD) can_pop &= after;  // a return in front of a byte that can never follow the rule leads nowhere
+      if (PRUNE) can_pop &= after;  // a return in front of a byte that can never follow the rule leads nowhere
       const uint32_t total = k + can_pop;
       // nothing but a move along a byte edge (most steps inside a string, a number, a name): taken at once
       if (alt == 0u && total == 1u && k == 1u && !pooled) {
