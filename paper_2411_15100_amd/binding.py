@@ -192,10 +192,14 @@ def schema_to_grammar(schema_json: str) -> str:
     lib = load_library()
     raw = schema_json.encode("utf-8")
     n = ctypes.c_size_t(0)
-    _check(lib.xgm_schema_to_grammar(raw, len(raw), None, 0, ctypes.byref(n)))
-    buf = ctypes.create_string_buffer(n.value + 1)
-    _check(lib.xgm_schema_to_grammar(raw, len(raw), buf, n.value + 1, ctypes.byref(n)))
-    return buf.raw[: n.value].decode("utf-8")
+    size = 4096 + 4 * len(raw)  # most grammars fit; one that does not is converted once more
+    buf = ctypes.create_string_buffer(size)
+    rc = lib.xgm_schema_to_grammar(raw, len(raw), buf, size, ctypes.byref(n))
+    if rc < 0 and n.value + 1 > size:
+        buf = ctypes.create_string_buffer(n.value + 1)
+        rc = lib.xgm_schema_to_grammar(raw, len(raw), buf, n.value + 1, ctypes.byref(n))
+    _check(rc)
+    return ctypes.string_at(buf, n.value).decode("utf-8")
 
 
 class Grammar:

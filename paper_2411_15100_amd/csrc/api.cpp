@@ -455,7 +455,7 @@ int32_t xgm_grammar_node_rule(const xgm_grammar* g, int32_t node) {
 }
 int32_t xgm_grammar_node_path(const xgm_grammar* g, int32_t node, int32_t* h_out, int32_t cap) {
   if (!g || node < 0 || node >= g->A.n_nodes || cap < 0 || (cap > 0 && !h_out)) return fail(XGM_ERR_BAD_ARG, "node_path: bad argument");
-  const auto& p = g->A.node_path[node];
+  const auto p = g->A.node_path(node);
   for (int32_t k = 0; k < std::min<int32_t>(cap, (int32_t)p.size()); ++k) h_out[k] = p[k];
   return (int32_t)p.size();
 }
@@ -509,7 +509,7 @@ int xgm_debug_walk_host(const xgm_grammar* g, const int32_t* h_stack, int32_t de
   if (n == 0) return kReject;
   const CompactTab T{TabView{reinterpret_cast<const uint2*>(A.hdr.data()), A.n_nodes,
                              reinterpret_cast<const uint2*>(A.hdr.data()), A.cls.data(), A.shapes.data(),
-                             A.targets.data(), A.alts.data(), A.follow_words.data(), A.n_cls}};
+                             A.targets.data(), A.alts.data(), A.follow[0].w, A.n_cls}};
   unsigned char row[16] = {0};
   std::memcpy(row, h_bytes, std::min<int32_t>(n, 15));
   row[15] = (unsigned char)std::min<int32_t>(n, 255);
@@ -551,7 +551,7 @@ int xgm_debug_matcher_accept_token_walk(xgm_matcher* m, int32_t token_id) {
   const uint8_t* bytes = v.bytes.data() + v.off[token_id];
   const CompactTab T{TabView{reinterpret_cast<const uint2*>(A.hdr.data()), A.n_nodes,
                              reinterpret_cast<const uint2*>(A.hdr.data()), A.cls.data(), A.shapes.data(),
-                             A.targets.data(), A.alts.data(), A.follow_words.data(), A.n_cls}};
+                             A.targets.data(), A.alts.data(), A.follow[0].w, A.n_cls}};
   unsigned char row[16] = {0};
   std::memcpy(row, bytes, std::min<int32_t>(n, 15));
   row[15] = (unsigned char)std::min<int32_t>(n, 255);
@@ -621,15 +621,15 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
         img.insert(img.end(), (const unsigned char*)src, (const unsigned char*)src + bytes);
         return (uint32_t)at;
       };
-      if (A.cls.size() != 256 || A.follow_words.size() != A.rule_names.size() * 8)
+      if (A.cls.size() != 256 || A.follow.size() != A.rule_names.size())
         throw Failure(XGM_ERR_INTERNAL, "cache_build: inconsistent automaton tables");
       put(A.cls.data(), 256, 4);
       tab.off_shapes = put(A.shapes.data(), A.shapes.size(), 4);
       tab.off_targets = put(A.targets.data(), A.targets.size() * 2, 4);
-      tab.off_follow = put(A.follow_words.data(), A.follow_words.size() * 4, 4);
+      tab.off_follow = put(A.follow.data(), A.follow.size() * sizeof(ByteSet), 4);
       tab.off_alts = put(A.alts.data(), A.alts.size() * 4, 4);
       tab.off_hdr = put(A.hdr.data(), (size_t)N * sizeof(uint2), 16);
-      tab.off_first = put(A.node_first_words.data(), A.node_first_words.size() * 4, 16);
+      tab.off_first = put(A.node_first.data(), (size_t)N * sizeof(ByteSet), 16);
       img.resize((img.size() + 15) / 16 * 16, 0);
       image_bytes = img.size();
       std::vector<uint4> image(img.size() / 16);

@@ -2,7 +2,6 @@
 // automaton (arxiv 2411.15100, section 2.2 and Appendix A: one finite
 // automaton per rule, character edges and rule-reference edges).
 #pragma once
-#include <bitset>
 #include <cstdint>
 #include <stdexcept>
 #include <string>
@@ -44,20 +43,54 @@ constexpr uint32_t kMoveTag = 0xFFFF;   // alternative (tag << 16 | node): consu
 constexpr uint32_t kTailTag = 0xFFFE;   // alternative: enter the callee at `node` without pushing a frame
                                         // (any other tag is the return node to push)
 
+// a set of byte values
+struct ByteSet {
+  uint32_t w[8] = {};
+  bool test(int c) const { return (w[c >> 5] >> (c & 31)) & 1u; }
+  void set_range(int lo, int hi) {
+    for (int k = lo >> 5; k <= hi >> 5; ++k) {
+      const int a = lo > k * 32 ? lo - k * 32 : 0, b = hi < k * 32 + 31 ? hi - k * 32 : 31;
+      w[k] |= (0xFFFFFFFFu >> (31 - (b - a))) << a;
+    }
+  }
+  // whether the set has grown
+  bool add(const ByteSet& o) {
+    uint32_t grown = 0;
+    for (int k = 0; k < 8; ++k) { grown |= o.w[k] & ~w[k]; w[k] |= o.w[k]; }
+    return grown != 0;
+  }
+};
+
+// rows of different lengths, one after the other
+template <class T>
+struct Rows {
+  struct Row {
+    const T *first, *last;
+    const T* begin() const { return first; }
+    const T* end() const { return last; }
+    size_t size() const { return (size_t)(last - first); }
+    bool empty() const { return first == last; }
+    const T& operator[](size_t k) const { return first[k]; }
+  };
+  std::vector<T> items;
+  std::vector<uint32_t> off{0};  // row k is items[off[k] .. off[k + 1])
+  void end_row() { off.push_back((uint32_t)items.size()); }
+  Row operator[](size_t k) const { return {items.data() + off[k], items.data() + off[k + 1]}; }
+};
+
 struct Automaton {
   // structured form (host engine)
   int32_t n_nodes = 0;
   std::vector<int32_t> node_rule;
   std::vector<uint8_t> node_final;
   std::vector<uint8_t> node_dead_end;         // accepting and without outgoing edges: all it can do is return
-  std::vector<std::vector<ByteEdge>> bedges;  // sorted, disjoint
-  std::vector<std::vector<RefEdge>> redges;
+  Rows<ByteEdge> bedges;                      // per node: sorted, disjoint
+  Rows<RefEdge> redges;                       // per node
   std::vector<int32_t> rule_start;            // per rule: global node id
   std::vector<std::string> rule_names;
-  std::vector<std::bitset<256>> first;        // per rule: bytes an instance can start with
-  std::vector<std::bitset<256>> node_first;   // per node: bytes that can be consumed at the node inside its frame
-  std::vector<uint32_t> node_first_words;     // [n_nodes][8] the same sets as machine words
-  std::vector<std::bitset<256>> follow;       // per rule: bytes that can come right after an instance, in any context
+  std::vector<ByteSet> first;                 // per rule: bytes an instance can start with
+  std::vector<ByteSet> node_first;            // per node: bytes that can be consumed at the node inside its frame
+  std::vector<ByteSet> follow;                // per rule: bytes that can come right after an instance, in any context
   // per rule: the nodes that can sit right below a frame of that rule (return nodes of the references to it;
   // a reference in tail position hands on the contexts of the referring rule), sorted
   std::vector<std::vector<int32_t>> contexts;
@@ -67,7 +100,8 @@ struct Automaton {
   std::vector<std::vector<int32_t>> forced;
   int32_t end_rule(int32_t rule) const { return forced[rule].empty() ? rule : node_rule[forced[rule].back()]; }
   int32_t root_rule = 0;
-  std::vector<std::vector<int32_t>> node_path;  // witness path from the rule start
+  std::vector<int32_t> path_parent, path_symbol;  // last step of a witness path from the rule start (-1: the start)
+  std::vector<int32_t> node_path(int32_t node) const;
 
   // flattened form (device tables)
   std::vector<NodeHdr> hdr;        // [n_nodes]
@@ -76,7 +110,6 @@ struct Automaton {
   std::vector<uint8_t> shapes;     // [n_shapes * n_cls]
   int32_t n_shapes = 0;
   std::vector<uint16_t> targets;   // outcomes of the branching nodes, node after node
-  std::vector<uint32_t> follow_words;  // [n_rules][8]: `follow` as 256-bit sets
   std::vector<uint32_t> alts;      // pool: count, then count entries (tag << 16 | node)
   int32_t max_alts = 0;
 };

@@ -7,6 +7,7 @@
 
 #include <cstdint>
 #include <set>
+#include <string_view>
 #include <utility>
 #include <vector>
 
@@ -23,7 +24,7 @@ struct Json {
   std::string text;  // string value (UTF-8), or the number as it was written
   std::vector<Json> items;
   std::vector<std::pair<std::string, Json>> members;
-  const Json* find(const std::string& key) const {
+  const Json* find(std::string_view key) const {
     for (auto& m : members)
       if (m.first == key) return &m.second;
     return nullptr;
@@ -356,14 +357,14 @@ class Converter {
       bad("the schema `false` allows nothing");
     }
     if (s.kind != Json::kObject) bad("a schema must be an object (or true)");
-    static const char* kUnsupported[] = {"$ref", "allOf", "not", "if", "then", "else", "pattern", "format", "minLength",
+    static const std::string_view kUnsupported[] = {"$ref", "allOf", "not", "if", "then", "else", "pattern", "format", "minLength",
                                          "maxLength", "minimum", "maximum", "exclusiveMinimum", "exclusiveMaximum",
                                          "multipleOf", "patternProperties", "propertyNames", "minProperties",
                                          "maxProperties", "dependencies", "dependentRequired", "dependentSchemas",
                                          "prefixItems", "contains", "uniqueItems", "additionalItems",
                                          "unevaluatedProperties", "unevaluatedItems"};
-    for (const char* k : kUnsupported)
-      if (s.find(k)) bad(std::string("keyword \"") + k + "\" is not supported");
+    for (std::string_view k : kUnsupported)
+      if (s.find(k)) bad("keyword \"" + std::string(k) + "\" is not supported");
     if (const Json* c = s.find("const")) return named_alternatives("const", {value_literal(*c)});
     if (const Json* e = s.find("enum")) {
       if (e->kind != Json::kArray || e->items.empty()) bad("\"enum\" must be a non-empty array");
