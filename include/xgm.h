@@ -315,8 +315,9 @@ int xgm_fill_and_apply(xgm_matcher* const* ms, int32_t B, int32_t* d_bitmask, vo
  * under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc): xgm_fill_next_token_bitmask with its per-call staging in fixed
  * memory.  Same arguments, same result in d_bitmask, same handling of walks
- * over the on-chip limits.  The packed stacks are
- * written into a fixed host array and copied, in stream order, into a fixed
+ * over the on-chip limits.  The packed stacks of a
+ * small batch go along with the launch as kernel arguments (not under graph
+ * capture); those of a larger one are written into a fixed host array and copied, in stream order, into a fixed
  * array of XGM_STATIC_STAGING_BYTES (1 MiB) that every device holds from the
  * moment the library is loaded until the process ends, where a kernel writes
  * them out in the form the fill kernel reads (both forms lie in the array);

@@ -224,7 +224,7 @@ struct xgm_matcher {
   xgm_cache* c = nullptr;
   xgm_grammar* g = nullptr;
   xgm_vocab* v = nullptr;
-  std::vector<Stack> stacks;
+  std::vector<Stack> stacks, spare;  // (spare: where the next state is made; its memory is kept)
   bool terminated = false;
 };
 
@@ -306,6 +306,7 @@ struct PendingFill {
   int32_t B = 0;
   int32_t* d_bitmask = nullptr;
   const void* blob = nullptr;
+  bool inline_states = false;      // blob is an InlineStates, else [RowDesc | stacks | frames]
   std::vector<xgm_cache*> caches;  // referenced
 };
 struct FillSlot {
@@ -316,6 +317,7 @@ struct FillSlot {
   hipEvent_t done = nullptr;
   bool used = false;
   PendingFill fill;
+  uint32_t states[kInlineWordsLarge];  // the states of a fill that took them along with its launch
 };
 struct Context {
   std::mutex mu;
@@ -325,7 +327,8 @@ struct Context {
   static constexpr int kSlots = 8;
   FillSlot slot[kSlots];
   int next_slot = 0;
-  PendingFill static_fill;  // the last fill staged in the static arrays
+  PendingFill static_fill;  // the last fill of the entry point that allocates nothing
+  uint32_t static_states[kInlineWordsLarge];
   // records of logs that no longer exist (cache builds, destroyed batches), and the batches that do
   int64_t retired_records = 0;
   std::set<xgm_batch*> batches;
@@ -350,9 +353,10 @@ uint32_t read_overflow_count(const OverflowLog* log) {
   HIP_OK(hipMemcpy(&n, &log->count, sizeof(n), hipMemcpyDeviceToHost));
   return n;
 }
-void set_pending(PendingFill& f, uint32_t seq, int32_t B, int32_t* d_bitmask, const void* blob, xgm_matcher* const* ms) {
+void set_pending(PendingFill& f, uint32_t seq, int32_t B, int32_t* d_bitmask, const void* blob, bool inline_states, xgm_matcher* const* ms) {
   for (xgm_cache* c : f.caches) release(c);
   f.caches.clear();
+  f.inline_states = inline_states;
   f.seq = seq;
   f.B = B;
   f.d_bitmask = d_bitmask;
@@ -632,12 +636,16 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
       tab.off_first = put(A.node_first.data(), (size_t)N * sizeof(ByteSet), 16);
       img.resize((img.size() + 15) / 16 * 16, 0);
       image_bytes = img.size();
-      std::vector<uint4> image(img.size() / 16);
-      std::memcpy(image.data(), img.data(), img.size());
-      tab.image = keep(slab_upload(image));
+      // (behind the image: the description of the tables as the fill kernel stages them)
+      unsigned char* d_img = keep(slab_alloc<unsigned char>(image_bytes + sizeof(DevTables)));
+      tab.image = reinterpret_cast<const uint4*>(d_img);
       tab.n_rules = (int32_t)A.rule_names.size();
       tab.n_cls = A.n_cls;
       tab.n_nodes = N;
+      c->host.tab = staged_for(tab, kFillLdsBudget);
+      put(&c->host.tab, sizeof(DevTables), 16);
+      c->host.dev_tab = reinterpret_cast<const DevTables*>(d_img + image_bytes);
+      HIP_OK(hipMemcpy(d_img, img.data(), img.size(), hipMemcpyHostToDevice));
     }
 
     const int32_t n_seg = dv.n_seg;
@@ -1004,7 +1012,6 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
     HIP_OK(hipGetLastError());
     cleanup_temps();  // (synchronises the stream)
 
-    c->host.tab = staged_for(tab, kFillLdsBudget);
     c->host.acc = acc_rows;
     c->host.acc_row = d_acc_row;
     c->host.key_off = d_key_off;
@@ -1126,7 +1133,8 @@ void xgm_matcher_destroy(xgm_matcher* m) {
 }
 int xgm_matcher_reset(xgm_matcher* m) {
   if (!m) return fail(XGM_ERR_BAD_ARG, "matcher_reset: null matcher");
-  m->stacks = {Stack{m->g->A.rule_start[m->g->A.root_rule]}};
+  m->stacks.resize(1);
+  m->stacks[0].assign(1, m->g->A.rule_start[m->g->A.root_rule]);
   m->terminated = false;
   return XGM_OK;
 }
@@ -1136,12 +1144,11 @@ int xgm_matcher_accept_bytes(xgm_matcher* m, const uint8_t* h_bytes, int32_t n) 
   if (m->terminated) return fail(XGM_ERR_TERMINATED, "accept: the matcher has terminated");
   if (n == 0) return XGM_OK;
   Engine e(&m->g->A);
-  std::vector<Stack> next;
-  int rc = e.advance(m->stacks, h_bytes, n, &next, nullptr, XGM_MAX_STACKS);
+  int rc = e.advance(m->stacks, h_bytes, n, &m->spare, nullptr, XGM_MAX_STACKS);
   if (rc == XGM_ERR_TOKEN_REJECTED) return fail(rc, "accept: the bytes are not allowed here");
   if (rc == XGM_ERR_TOO_MANY_STACKS) return fail(rc, "accept: more than 64 parallel stacks");
   if (rc != XGM_OK) return fail(rc, "accept: stack depth or configuration limit exceeded");
-  m->stacks.swap(next);
+  m->stacks.swap(m->spare);
   return XGM_OK;
   API_END
 }
@@ -1234,6 +1241,53 @@ static void pack_stack_header(const Automaton& A, const xgm_cache& c, const Stac
 // being pageable).  Guarded by the context's mutex.
 alignas(64) static unsigned char g_static_host[kStaticScratchBytes];
 
+static bool is_capturing(hipStream_t stream) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  HIP_OK(hipStreamIsCapturing(stream, &st));
+  return st != hipStreamCaptureStatusNone;
+}
+
+// The states of a small batch as they go along with the launch (see InlineStates).  Returns the words used, 0 if
+// they do not fit (many different caches).
+static size_t pack_inline(xgm_matcher* const* ms, int32_t B, size_t n_stacks, size_t n_frames, uint32_t* w) {
+  const size_t stacks0 = (size_t)B * 2, frames0 = stacks0 + n_stacks * kInlineStackWords;
+  size_t used = frames0 + (n_frames + 1) / 2;  // the caches come last
+  uint16_t* halves = reinterpret_cast<uint16_t*>(w);
+  size_t sw = stacks0, fi = frames0 * 2;
+  for (int32_t b = 0; b < B; ++b) {
+    const xgm_matcher* m = ms[b];
+    uint32_t* row = w + 2 * b;
+    if (m->terminated) { row[0] = (uint32_t)stacks0 | (1u << 24); row[1] = (uint32_t)stacks0; continue; }
+    const xgm_cache& c = *m->c;
+    // the cache of an earlier row with the same one, or put down behind the others
+    size_t at = 0;
+    for (int32_t k = b; k-- > 0 && at == 0;)
+      if (ms[k]->c == m->c && !ms[k]->terminated) at = w[2 * k + 1] & 0xFFFFu;
+    if (at == 0) {
+      if (used + kInlineCacheWords > kInlineWordsLarge) return 0;
+      at = used;
+      used += kInlineCacheWords;
+      const void* ptrs[4] = {c.host.acc, c.host.entries, c.host.key_off, c.host.dev_tab};
+      static_assert(sizeof(ptrs) == kInlineCacheWords * 4, "the words of a cache");
+      std::memcpy(w + at, ptrs, sizeof(ptrs));
+    }
+    const Automaton& A = m->g->A;
+    row[0] = (uint32_t)sw | ((uint32_t)m->stacks.size() << 16) | (Engine(&A).can_terminate(m->stacks) ? 1u << 24 : 0u);
+    const size_t f_begin = fi;
+    for (const Stack& s : m->stacks) {
+      uint32_t h[kStackHdrWords];
+      stack_keys(A, c, s, (uint32_t)fi, h, w + sw + 1);
+      w[sw] = h[kStackHdrTop];
+      w[sw + 5] = h[kStackHdrDepth] | (h[kStackHdrFrames] << 16);
+      w[sw + 6] = h[kStackHdrDrops];
+      sw += kInlineStackWords;
+      for (int32_t n : s) halves[fi++] = (uint16_t)n;
+    }
+    row[1] = (uint32_t)at | ((uint32_t)(fi - f_begin) << 16);
+  }
+  return used;
+}
+
 // `use_static`: stage in g_static_host and the device's static scratch array instead of the ring of
 // allocated slots; nothing is allocated on this path.
 static int fill_impl(xgm_matcher* const* ms, int32_t B, int32_t* d_bitmask, void* hip_stream,
@@ -1271,6 +1325,26 @@ static int fill_impl(xgm_matcher* const* ms, int32_t B, int32_t* d_bitmask, void
 
   Context& C = ctx();
   std::lock_guard<std::mutex> lock(C.mu);
+  // A small batch goes along with the launch (see InlineStates), unless the two kernels are to be looked at one by
+  // one or the launch is being captured into a graph (whose replays take what is staged when they run).
+  const size_t inline_most = (size_t)B * 2 + n_stacks * kInlineStackWords + (n_frames + 1) / 2;
+  if (inline_most + kInlineCacheWords <= kInlineWordsLarge && !timing && !d_step_counter && !(use_static && is_capturing(stream))) {
+    FillSlot& slot = C.slot[C.next_slot];
+    uint32_t* states = use_static ? C.static_states : slot.states;
+    const size_t words = pack_inline(ms, B, n_stacks, n_frames, states);
+    if (words != 0) {
+      if (use_static && !C.d_log) return fail(XGM_ERR_INTERNAL, "fill (static staging): the library's device context does not exist yet");
+      OverflowLog* log = overflow_log();
+      const uint32_t seq = ++C.seq;
+      launch_fill_inline(states, (uint32_t)words, B, v->dv, reinterpret_cast<uint32_t*>(d_bitmask), log, seq, stream,
+                         fused ? fused->d_logits : nullptr, fused ? fused->esize : 0, fused ? fused->neg_inf : 0u,
+                         fused ? fused->V_logits : 0, fused ? fused->row_stride : 0);
+      HIP_OK(hipGetLastError());
+      if (!use_static) C.next_slot = (C.next_slot + 1) % Context::kSlots;
+      set_pending(use_static ? C.static_fill : slot.fill, seq, B, d_bitmask, states, true, ms);
+      return XGM_OK;
+    }
+  }
   // (the fills' record of walks over the limits is allocated when a mask cache is built: this path allocates nothing)
   if (use_static && !C.d_log) return fail(XGM_ERR_INTERNAL, "fill (static staging): the library's device context does not exist yet");
   OverflowLog* log = overflow_log();
@@ -1354,7 +1428,7 @@ static int fill_impl(xgm_matcher* const* ms, int32_t B, int32_t* d_bitmask, void
     ring->used = true;
     C.next_slot = (C.next_slot + 1) % Context::kSlots;
   }
-  set_pending(ring ? ring->fill : C.static_fill, seq, B, d_bitmask, h_buf, ms);
+  set_pending(ring ? ring->fill : C.static_fill, seq, B, d_bitmask, h_buf, false, ms);
   return XGM_OK;
   API_END
 }
@@ -1546,6 +1620,18 @@ int xgm_fill_overflow_fixup(void* hip_stream) {
     const xgm_cache& c = *f->caches[b];
     const xgm_vocab& v = *c.v;
     // the row's stacks as that fill packed them
+    if (f->inline_states) {
+      const auto* w = static_cast<const uint32_t*>(f->blob);
+      const auto* halves = static_cast<const uint16_t*>(f->blob);
+      std::vector<Stack> stacks;
+      for (uint32_t s = 0; s < ((w[2 * b] >> 16) & 0xFFu); ++s) {
+        const uint32_t where = w[(w[2 * b] & 0xFFFFu) + s * kInlineStackWords + 5];
+        stacks.emplace_back(halves + (where >> 16), halves + (where >> 16) + (where & 0xFFFFu));
+      }
+      patch_bit(f->d_bitmask, v.dv.W, b, id, host_decides(c.g->A, v, stacks, id));
+      ++handled;
+      continue;
+    }
     const auto* rows = reinterpret_cast<const RowDesc*>(f->blob);
     const size_t hdr_words = kStackKeysWords;  // (the staging memory holds the stacks as the host packed them)
     const auto* hdrs = reinterpret_cast<const uint32_t*>((const char*)f->blob + (size_t)f->B * sizeof(RowDesc));

@@ -38,6 +38,7 @@ __device__ __forceinline__ void stage_tables(const DevTables& tab, unsigned char
 // branch of a walk step with its latency).
 #define XGM_LDS __attribute__((address_space(3)))
 #define XGM_GLOBAL __attribute__((address_space(1)))
+#define XGM_CONST __attribute__((address_space(4)))
 template <bool kSmallInLds>
 struct LdsTabT {
   const XGM_LDS unsigned char* lds;     // the staged part of the image
@@ -955,27 +956,50 @@ struct FillShared {
 };
 
 
+// What the walks need to know about a row, wherever its state came from.
+struct WalkRow {
+  const XGM_GLOBAL uint32_t* entries;
+  const XGM_GLOBAL uint32_t* stacks;   // first stack: a header, or kInlineStackWords
+  const XGM_GLOBAL uint32_t* key_off;  // states that came with the launch; null: the offsets are in the headers
+  const XGM_GLOBAL uint16_t* frames;
+  uint32_t n_stacks, stride, frame0, n_frames, epoch;
+  int32_t n_seg;
+};
+
 // Decides the walk entries of the workgroup's lists (all threads call this).
 template <bool COUNT, bool KEEP_UNDECIDED, class Tab>
-__device__ __forceinline__ void fill_walks(const Tab& T, FillShared& sm, const RowDesc& rd, const int32_t b, const int32_t seg,
-                                           const uint32_t n_stacks, const uint32_t frame0, const bool frames_in_lds,
-                                           const XGM_GLOBAL uint32_t* __restrict__ stack_hdrs, const uint32_t hdr_stride,
-                                           const XGM_GLOBAL uint16_t* __restrict__ frames, const DevVocab& voc,
-                                           OverflowLog* log, uint32_t seq, unsigned long long& my_steps) {
-  const XGM_GLOBAL uint32_t* entries = (const XGM_GLOBAL uint32_t*)rd.entries;
+__device__ __forceinline__ void fill_walks(const Tab& T, FillShared& sm, const WalkRow& row, const int32_t b, const int32_t seg,
+                                           const bool frames_in_lds, const DevVocab& voc, OverflowLog* log, uint32_t seq,
+                                           unsigned long long& my_steps) {
+  const XGM_GLOBAL uint32_t* entries = row.entries;
   const int32_t id0 = seg * kSegTokens;
-  for (uint32_t st = 0; st < n_stacks; ++st) {
+  for (uint32_t st = 0; st < row.n_stacks; ++st) {
     // one round of loads per stack: its scalars and where its four lists begin in this segment and in the next
-    const XGM_GLOBAL uint32_t* sh = stack_hdrs + (size_t)(rd.stack_begin + st) * hdr_stride;
+    const XGM_GLOBAL uint32_t* sh = row.stacks + (size_t)st * row.stride;
     typedef uint32_t v4u __attribute__((ext_vector_type(4)));
-    const XGM_GLOBAL v4u* off = (const XGM_GLOBAL v4u*)(sh + stack_hdr_off((uint32_t)seg, 0u));
-    const v4u scalars = *(const XGM_GLOBAL v4u*)sh, o0 = off[0], o1 = off[1];
+    v4u scalars, o0, o1;
+    if (row.key_off) {
+      scalars = {sh[0], sh[5] & 0xFFFFu, sh[5] >> 16, sh[6]};
+      o0 = o1 = {0u, 0u, 0u, 0u};
+#pragma unroll
+      for (uint32_t l = 0; l < kStackLists; ++l)
+        if (sh[1 + l] != kNoKey) {
+          const XGM_GLOBAL uint32_t* ko = row.key_off + (size_t)sh[1 + l] * (uint32_t)row.n_seg + (uint32_t)seg;
+          o0[l] = ko[0];
+          o1[l] = ko[1];
+        }
+    } else {
+      const XGM_GLOBAL v4u* off = (const XGM_GLOBAL v4u*)(sh + stack_hdr_off((uint32_t)seg, 0u));
+      scalars = *(const XGM_GLOBAL v4u*)sh;
+      o0 = off[0];
+      o1 = off[1];
+    }
     const uint32_t top = scalars.x & 0xFFFFu, depth = scalars.y, f_off = scalars.z;
     static_assert(kStackHdrTop == 0 && kStackHdrDepth == 1 && kStackHdrFrames == 2 && kStackHdrDrops == 3 && kStackHdrWords == 4 && kStackLists == 4,
                   "a stack's scalars are one 16-byte load, a segment's list offsets another");
     LiveView live;
-    live.lds = (const XGM_LDS uint16_t*)sm.live + (f_off - frame0);
-    live.glob = frames + f_off;
+    live.lds = (const XGM_LDS uint16_t*)sm.live + (f_off - row.frame0);
+    live.glob = row.frames + f_off;
     live.lo = frames_in_lds ? 0u : 0xFFFFFFFFu;
     for (uint32_t l = 0; l < kStackLists; ++l) {  // (not unrolled: one copy of the walk)
       // the list's entries of this segment; the accepted ones are done
@@ -997,7 +1021,7 @@ __device__ __forceinline__ void fill_walks(const Tab& T, FillShared& sm, const R
                                   0u, drop == 0u ? 0 : (int)pos);
         }
         if (COUNT) my_steps += n_steps;
-        if (res == kOverflow) record_overflow(log, seq, (uint32_t)b, id, rd.epoch);  // decided on the host
+        if (res == kOverflow) record_overflow(log, seq, (uint32_t)b, id, row.epoch);  // decided on the host
         if (res == kAccept || (KEEP_UNDECIDED && res == kOverflow)) atomicOr(&sm.words[rel >> 5], 1u << (rel & 31u));
       }
     }
@@ -1007,12 +1031,13 @@ __device__ __forceinline__ void fill_walks(const Tab& T, FillShared& sm, const R
 // The whole of step 3, kept out of line: the request's tables and live frames into LDS, then the walks.  Nearly
 // no workgroup comes here, and inlined the walk's registers and code would weigh on every workgroup's path
 // (the kernel ran out of scalar registers and kept them in lanes of a vector register).  What it needs it
-// reads again: the row descriptor, and of the vocabulary the three arrays a token is fetched from.  The call
+// reads again: the row's state, and of the vocabulary the three arrays a token is fetched from.  The call
 // itself costs a workgroup that walks about a microsecond (registers saved and restored through memory).
 struct FillWalkArgs {
   const RowDesc* row;
   const uint32_t* stack_hdrs;
   const uint16_t* frames;
+  const XGM_GLOBAL uint32_t* states;  // states that came with the launch (the three above are then not used); else null
   const uint4* tok_by_id;
   const uint32_t* off_by_id;
   const uint8_t* bytes;
@@ -1021,31 +1046,54 @@ struct FillWalkArgs {
   int32_t b, seg, n_seg;
   uint32_t seq;
 };
+__device__ __forceinline__ uint64_t word_pair(const XGM_GLOBAL uint32_t* w) { return (uint64_t)w[0] | ((uint64_t)w[1] << 32); }
 template <bool COUNT, bool KEEP_UNDECIDED>
 __device__ __noinline__ void fill_walk_path(const FillWalkArgs a, FillShared XGM_LDS* shared, unsigned char XGM_LDS* staged) {
   FillShared& sm = *(FillShared*)shared;
   unsigned char* smem = (unsigned char*)staged;
-  const RowDesc rd = *a.row;
-  const XGM_GLOBAL uint32_t* stack_hdrs = (const XGM_GLOBAL uint32_t*)a.stack_hdrs;
-  const XGM_GLOBAL uint16_t* frames = (const XGM_GLOBAL uint16_t*)a.frames;
+  WalkRow row;
+  DevTables tab;
+  row.n_seg = a.n_seg;
+  if (a.states) {
+    const uint32_t r0 = a.states[2 * a.b], r1 = a.states[2 * a.b + 1];
+    const XGM_GLOBAL uint32_t* cache = a.states + (r1 & 0xFFFFu);
+    row.entries = (const XGM_GLOBAL uint32_t*)word_pair(cache + 2);
+    row.key_off = (const XGM_GLOBAL uint32_t*)word_pair(cache + 4);
+    tab = *(const DevTables*)word_pair(cache + 6);
+    row.stacks = a.states + (r0 & 0xFFFFu);
+    row.n_stacks = (r0 >> 16) & 0xFFu;
+    row.stride = kInlineStackWords;
+    row.frames = (const XGM_GLOBAL uint16_t*)a.states;
+    row.frame0 = row.stacks[5] >> 16;
+    row.n_frames = r1 >> 16;
+    row.epoch = 0u;
+  } else {
+    const RowDesc rd = *a.row;
+    tab = rd.tab;
+    row.entries = (const XGM_GLOBAL uint32_t*)rd.entries;
+    row.key_off = nullptr;
+    row.stride = stack_hdr_stride(a.n_seg);
+    row.stacks = (const XGM_GLOBAL uint32_t*)a.stack_hdrs + (size_t)rd.stack_begin * row.stride;
+    row.n_stacks = rd.n_stacks;
+    row.frames = (const XGM_GLOBAL uint16_t*)a.frames;
+    row.frame0 = rd.frame_begin;
+    row.n_frames = rd.n_frames;
+    row.epoch = rd.epoch;
+  }
   DevVocab voc{};
   voc.tok_by_id = a.tok_by_id;
   voc.off_by_id = a.off_by_id;
   voc.bytes = a.bytes;
   unsigned long long my_steps = 0;
-  const uint32_t frame0 = rd.frame_begin, n_frames = rd.n_frames;
-  const uint32_t hdr_stride = stack_hdr_stride(a.n_seg);
-  const bool frames_in_lds = n_frames <= kFillFramesLds;
-  stage_tables(rd.tab, smem, kFillThreads);
+  const bool frames_in_lds = row.n_frames <= kFillFramesLds;
+  stage_tables(tab, smem, kFillThreads);
   if (frames_in_lds)
-    for (uint32_t k = threadIdx.x; k < n_frames; k += kFillThreads) sm.live[k] = frames[frame0 + k];
+    for (uint32_t k = threadIdx.x; k < row.n_frames; k += kFillThreads) sm.live[k] = row.frames[row.frame0 + k];
   __syncthreads();
-  if (small_sections_staged(rd.tab))
-    fill_walks<COUNT, KEEP_UNDECIDED>(LdsTabT<true>(rd.tab, smem), sm, rd, a.b, a.seg, rd.n_stacks, frame0, frames_in_lds, stack_hdrs,
-                                      hdr_stride, frames, voc, a.log, a.seq, my_steps);
+  if (small_sections_staged(tab))
+    fill_walks<COUNT, KEEP_UNDECIDED>(LdsTabT<true>(tab, smem), sm, row, a.b, a.seg, frames_in_lds, voc, a.log, a.seq, my_steps);
   else
-    fill_walks<COUNT, KEEP_UNDECIDED>(LdsTab(rd.tab, smem), sm, rd, a.b, a.seg, rd.n_stacks, frame0, frames_in_lds, stack_hdrs,
-                                      hdr_stride, frames, voc, a.log, a.seq, my_steps);
+    fill_walks<COUNT, KEEP_UNDECIDED>(LdsTab(tab, smem), sm, row, a.b, a.seg, frames_in_lds, voc, a.log, a.seq, my_steps);
   __syncthreads();
   if (COUNT && my_steps) atomicAdd(a.step_counter, my_steps);
 }
@@ -1064,8 +1112,10 @@ struct FusedApply {
   uint32_t neg_inf;
 };
 
-template <bool COUNT, int APPLY>
-__global__ __launch_bounds__(kFillThreads, 8) void fill_kernel(const RowDesc* __restrict__ rows,
+// INLINE != 0: the states came with the launch (InlineStates, the first argument: read where the arguments lie);
+// rows, stack_hdrs_ and frames_ are then not used.
+template <bool COUNT, int APPLY, uint32_t INLINE>
+__global__ __launch_bounds__(kFillThreads, 8) void fill_kernel(const InlineStates<INLINE> states_, const RowDesc* __restrict__ rows,
                                                             const uint32_t* __restrict__ stack_hdrs_,
                                                             const uint16_t* __restrict__ frames_, DevVocab voc,
                                                             uint32_t* __restrict__ out, OverflowLog* log, uint32_t seq,
@@ -1082,13 +1132,32 @@ __global__ __launch_bounds__(kFillThreads, 8) void fill_kernel(const RowDesc* __
   for (int32_t w = tid; w < kSegWords; w += kFillThreads) sm.words[w] = 0u;
   if (tid == 0) sm.any_walk = 0u;
   __syncthreads();
-  const RowDesc rd = rows[b];
+  // (in the address space of kernel arguments: what is read from there is known to be the same for all threads)
+  const XGM_CONST uint32_t* states = INLINE ? (const XGM_CONST uint32_t*)__builtin_amdgcn_kernarg_segment_ptr() : nullptr;
+  const XGM_CONST uint32_t* key_off = nullptr;
+  const XGM_GLOBAL uint32_t *acc, *entries;
+  uint32_t n_stacks, flags, stack_begin;
+  if constexpr (INLINE != 0) {
+    const uint32_t r0 = states[2 * b], r1 = states[2 * b + 1];
+    const XGM_CONST uint32_t* cache = states + (r1 & 0xFFFFu);
+    stack_begin = r0 & 0xFFFFu;
+    n_stacks = (r0 >> 16) & 0xFFu;
+    flags = r0 >> 24;
+    acc = (const XGM_GLOBAL uint32_t*)((uint64_t)cache[0] | ((uint64_t)cache[1] << 32));
+    entries = (const XGM_GLOBAL uint32_t*)((uint64_t)cache[2] | ((uint64_t)cache[3] << 32));
+    key_off = (const XGM_CONST uint32_t*)((uint64_t)cache[4] | ((uint64_t)cache[5] << 32));
+  } else {
+    const RowDesc rd = rows[b];
+    stack_begin = rd.stack_begin;
+    n_stacks = rd.n_stacks;
+    flags = rd.flags;
+    acc = (const XGM_GLOBAL uint32_t*)rd.acc;
+    entries = (const XGM_GLOBAL uint32_t*)rd.entries;
+  }
   const uint32_t hdr_stride = stack_hdr_stride(voc.n_seg);
   // may the request end here?  then its stop tokens are allowed (the first kFillThreads of them are fetched now)
-  const bool may_end = rd.flags & 1u;
+  const bool may_end = flags & 1u;
   const int32_t my_stop = may_end && (int32_t)tid < voc.n_stop ? voc.stop_ids[tid] : -1;
-  const XGM_GLOBAL uint32_t* acc = (const XGM_GLOBAL uint32_t*)rd.acc;
-  const XGM_GLOBAL uint32_t* entries = (const XGM_GLOBAL uint32_t*)rd.entries;
   auto take = [&](uint32_t e) {
     if ((e >> kEntryKindShift) == kEntryAccepted) {
       const uint32_t rel = (e & kEntryIdMask) - (uint32_t)id0;
@@ -1101,7 +1170,7 @@ __global__ __launch_bounds__(kFillThreads, 8) void fill_kernel(const RowDesc* __
   // thread's words of their bitset rows (Algorithm 1: the union over the parallel stacks) and the first
   // kFillThreads entries of their lists (most lists are shorter than that); then what is left of the lists.
   constexpr int kWordsPerThread = kSegWords / kFillThreads;
-  for (uint32_t s0 = 0; s0 < rd.n_stacks; s0 += 2u) {
+  for (uint32_t s0 = 0; s0 < n_stacks; s0 += 2u) {
     uint32_t acc_row[2];
     uint2 lst[2][kStackLists];
 #pragma unroll
@@ -1109,17 +1178,30 @@ __global__ __launch_bounds__(kFillThreads, 8) void fill_kernel(const RowDesc* __
       acc_row[q] = kNoAccRow;
 #pragma unroll
       for (uint32_t l = 0; l < kStackLists; ++l) lst[q][l] = make_uint2(0u, 0u);
-      if (s0 + q < rd.n_stacks) {
-        const XGM_GLOBAL uint32_t* sh = stack_hdrs + (size_t)(rd.stack_begin + s0 + q) * hdr_stride;
-        acc_row[q] = sh[kStackHdrTop] >> 16;
-        static_assert(kStackLists == 4, "the offsets of a segment's four lists are one 16-byte load");
-        const uint4* off = reinterpret_cast<const uint4*>(stack_hdrs_ + (size_t)(rd.stack_begin + s0 + q) * hdr_stride +
-                                                          stack_hdr_off((uint32_t)seg, 0u));
-        const uint4 o0 = off[0], o1 = off[1];  // where the lists begin in this segment, and in the next
-        lst[q][0] = make_uint2(o0.x, o1.x);
-        lst[q][1] = make_uint2(o0.y, o1.y);
-        lst[q][2] = make_uint2(o0.z, o1.z);
-        lst[q][3] = make_uint2(o0.w, o1.w);
+      if (s0 + q < n_stacks) {
+        if constexpr (INLINE != 0) {
+          const XGM_CONST uint32_t* sw = states + stack_begin + (s0 + q) * kInlineStackWords;
+          acc_row[q] = sw[0] >> 16;
+#pragma unroll
+          for (uint32_t l = 0; l < kStackLists; ++l) {
+            const uint32_t key = sw[1 + l];
+            if (key != kNoKey) {
+              const XGM_CONST uint32_t* ko = key_off + ((size_t)key * (uint32_t)voc.n_seg + (uint32_t)seg);
+              lst[q][l] = make_uint2(ko[0], ko[1]);
+            }
+          }
+        } else {
+          const XGM_GLOBAL uint32_t* sh = stack_hdrs + (size_t)(stack_begin + s0 + q) * hdr_stride;
+          acc_row[q] = sh[kStackHdrTop] >> 16;
+          static_assert(kStackLists == 4, "the offsets of a segment's four lists are one 16-byte load");
+          const uint4* off = reinterpret_cast<const uint4*>(stack_hdrs_ + (size_t)(stack_begin + s0 + q) * hdr_stride +
+                                                            stack_hdr_off((uint32_t)seg, 0u));
+          const uint4 o0 = off[0], o1 = off[1];  // where the lists begin in this segment, and in the next
+          lst[q][0] = make_uint2(o0.x, o1.x);
+          lst[q][1] = make_uint2(o0.y, o1.y);
+          lst[q][2] = make_uint2(o0.z, o1.z);
+          lst[q][3] = make_uint2(o0.w, o1.w);
+        }
       }
     }
     uint32_t aw[2][kWordsPerThread], first[2][kStackLists];
@@ -1168,6 +1250,7 @@ __global__ __launch_bounds__(kFillThreads, 8) void fill_kernel(const RowDesc* __
     wa.row = rows + b;
     wa.stack_hdrs = stack_hdrs_;
     wa.frames = frames_;
+    wa.states = (const XGM_GLOBAL uint32_t*)(uint64_t)states;
     wa.tok_by_id = voc.tok_by_id;
     wa.off_by_id = voc.off_by_id;
     wa.bytes = voc.bytes;
@@ -1721,18 +1804,28 @@ void launch_fill(const RowDesc* rows, const uint32_t* stack_hdrs, const uint16_t
   if (B <= 0) return;
   const dim3 grid(voc.n_seg, B);
   const FusedApply fa{static_cast<unsigned char*>(logits), row_stride, V_logits, neg_inf};
-  if (logits && elem_size == 2)
-    hipLaunchKernelGGL((fill_kernel<false, 2>), grid, dim3(kFillThreads), kFillLdsBudget, stream, rows, stack_hdrs, frames,
-                       voc, out, log, seq, step_counter, fa);
-  else if (logits)
-    hipLaunchKernelGGL((fill_kernel<false, 4>), grid, dim3(kFillThreads), kFillLdsBudget, stream, rows, stack_hdrs, frames,
-                       voc, out, log, seq, step_counter, fa);
-  else if (step_counter)
-    hipLaunchKernelGGL((fill_kernel<true, 0>), grid, dim3(kFillThreads), kFillLdsBudget, stream, rows, stack_hdrs, frames,
-                       voc, out, log, seq, step_counter, fa);
-  else
-    hipLaunchKernelGGL((fill_kernel<false, 0>), grid, dim3(kFillThreads), kFillLdsBudget, stream, rows, stack_hdrs, frames,
-                       voc, out, log, seq, step_counter, fa);
+  auto kernel = logits ? (elem_size == 2 ? fill_kernel<false, 2, 0> : fill_kernel<false, 4, 0>)
+                       : (step_counter ? fill_kernel<true, 0, 0> : fill_kernel<false, 0, 0>);
+  hipLaunchKernelGGL(kernel, grid, dim3(kFillThreads), kFillLdsBudget, stream, InlineStates<0>{}, rows, stack_hdrs, frames, voc, out,
+                     log, seq, step_counter, fa);
+}
+
+template <uint32_t WORDS>
+static void launch_fill_inline_of(const uint32_t* states, uint32_t words, const dim3 grid, const DevVocab& voc, uint32_t* out,
+                                  OverflowLog* log, uint32_t seq, hipStream_t stream, int elem_size, const FusedApply& fa) {
+  InlineStates<WORDS> st;
+  std::copy(states, states + words, st.w);
+  auto kernel = fa.logits ? (elem_size == 2 ? fill_kernel<false, 2, WORDS> : fill_kernel<false, 4, WORDS>) : fill_kernel<false, 0, WORDS>;
+  hipLaunchKernelGGL(kernel, grid, dim3(kFillThreads), kFillLdsBudget, stream, st, (const RowDesc*)nullptr, (const uint32_t*)nullptr,
+                     (const uint16_t*)nullptr, voc, out, log, seq, (unsigned long long*)nullptr, fa);
+}
+void launch_fill_inline(const uint32_t* states, uint32_t words, int32_t B, const DevVocab& voc, uint32_t* out, OverflowLog* log,
+                        uint32_t seq, hipStream_t stream, void* logits, int elem_size, uint32_t neg_inf, int32_t V_logits, int64_t row_stride) {
+  if (B <= 0) return;
+  const dim3 grid(voc.n_seg, B);
+  const FusedApply fa{static_cast<unsigned char*>(logits), row_stride, V_logits, neg_inf};
+  if (words <= kInlineWordsSmall) launch_fill_inline_of<kInlineWordsSmall>(states, words, grid, voc, out, log, seq, stream, elem_size, fa);
+  else launch_fill_inline_of<kInlineWordsLarge>(states, words, grid, voc, out, log, seq, stream, elem_size, fa);
 }
 
 void launch_lds_lookups(int32_t n_blocks, uint32_t hops, uint32_t* sink, hipStream_t stream) {

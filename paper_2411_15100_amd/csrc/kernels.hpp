@@ -121,6 +121,7 @@ struct DevVocab {
 constexpr int kCtxLevels = 3;
 struct DevCache {
   DevTables tab;             // staging split for the fill kernel
+  const DevTables* dev_tab;  // `tab` in device memory
   const uint32_t* acc;       // [n_acc_rows][W] accepted tokens, id space: the distinct bitset rows
   const uint16_t* acc_row;   // [n_nodes] which row of `acc` is the node's, or kNoAccRow (listed under its level-0 key)
   const uint32_t* key_off;   // [n_keys * n_seg + 1]
@@ -186,6 +187,19 @@ inline uint32_t stack_drops(uint32_t depth, const Steps& steps) {
 constexpr uint32_t stack_drop(uint32_t drops, uint32_t d) { return d <= 1u ? d : (drops >> (8u * (d - 2u))) & 0xFFu; }
 constexpr uint32_t stack_hdr_stride(int32_t n_seg) { return kStackHdrWords + kStackLists * ((uint32_t)n_seg + 1u); }
 constexpr uint32_t stack_hdr_off(uint32_t seg, uint32_t l) { return kStackHdrWords + seg * kStackLists + l; }
+
+// ---- host-side states that come with the launch.  What a fill from host-side states has to know about a small
+// batch fits the kernel's arguments: one launch then does the whole step, with no staging memory, no kernel that
+// copies it and no event that guards it.  In 32-bit words:
+//   [2 b], [2 b + 1]    row b: first word of its stacks | stacks << 16 | flags << 24;  word of its cache | frames << 16
+//   caches              kInlineCacheWords each, every distinct one once: acc, entries, key_off, DevCache::dev_tab
+//   stacks              kInlineStackWords each: kStackHdrTop, the keys of the four lists (kNoKey: none),
+//                       depth | where its frames start << 16 (in 16-bit units from word 0), kStackHdrDrops
+//   frames              uint16, a row's stacks one after the other
+constexpr uint32_t kInlineCacheWords = 8, kInlineStackWords = 7;
+constexpr uint32_t kInlineWordsSmall = 64, kInlineWordsLarge = 896;  // (a launch's arguments are kept under 4 KiB)
+template <uint32_t WORDS>
+struct InlineStates { uint32_t w[WORDS]; };
 
 // ---- matcher states that live on the device (section 3.3 on the GPU: the
 // sampled tokens move the stacks on without a round trip to the host).
@@ -334,6 +348,9 @@ void launch_fill(const RowDesc* rows, const uint32_t* stack_hdrs, const uint16_t
                  const DevVocab& voc, uint32_t* out, OverflowLog* log, uint32_t seq,
                  unsigned long long* step_counter, hipStream_t stream, void* logits = nullptr,
                  int elem_size = 0, uint32_t neg_inf = 0, int32_t V_logits = 0, int64_t row_stride = 0);
+// the same with the states in the launch (InlineStates: `words` of them, at most kInlineWordsLarge); step_counter is not supported
+void launch_fill_inline(const uint32_t* states, uint32_t words, int32_t B, const DevVocab& voc, uint32_t* out, OverflowLog* log,
+                        uint32_t seq, hipStream_t stream, void* logits, int elem_size, uint32_t neg_inf, int32_t V_logits, int64_t row_stride);
 // device-resident states: move every row on by its token (ids < 0 leave a row alone)
 void launch_batch_accept(const DevBatch& bt, const DevVocab& voc, const int32_t* d_tokens, hipStream_t stream);
 // go back d_steps[b] tokens in every row (<= 0 leaves a row alone)

@@ -73,3 +73,56 @@ def test_forced_frames(xgm, wl, levels):
                 assert oms[b].advance(toks[int(picks[b])])
             if not walker.history[b] or status[b]:
                 resident.set_row(b, walker.matchers[b], _stream())
+
+
+# Host-side states go along with the launch while they fit: 64 words (one row, a few frames), 896 words (a few dozen
+# rows, or a deep stack); beyond that they are staged.  Rows with several stacks, ended rows, several grammars.
+@pytest.mark.parametrize("rows,depth", [(1, 1), (1, 20), (1, 40), (1, 90), (1, 1700), (1, 1780), (2, 3), (9, 8), (28, 6), (33, 6), (45, 6), (70, 3), (130, 2)])
+def test_states_in_the_launch(xgm, wl, rows, depth):
+    vocab = si.make_vocab("bpe", 1500, 5)
+    xv = wl.make_xgm_vocab(vocab)
+    texts = [si.JSON_GRAMMAR, si.PYDSL_GRAMMAR, si.make_schema_grammar(1)]
+    starts = [b"[" * depth, b"v" + b"[v" * min(depth, 3), b""]
+    n = 1 if rows == 1 else 3
+    caches = [xgm.Cache(xgm.Grammar(t, "root"), xv) for t in texts[:n]]
+    ogs = [oracle.Grammar(t, "root") for t in texts[:n]]
+    rng = np.random.Generator(np.random.PCG64(rows * 1000 + depth))
+    toks = vocab.tokens()
+    ms, oms = [], []
+    for b in range(rows):
+        k = b % n
+        m, om = xgm.Matcher(cache=caches[k]), oracle.EarleyMatcher(ogs[k])
+        if starts[k]:
+            m.accept_bytes(starts[k])
+            assert om.advance(starts[k])
+        for _ in range(int(rng.integers(0, 4))):
+            ids = np.flatnonzero(om.mask(vocab))
+            ids = ids[ids != vocab.stop_ids[0]]
+            t = int(rng.choice(ids)) if ids.size else None
+            if t is not None:
+                m.accept_token(t)
+                assert om.advance(toks[t])
+        ms.append(m)
+        oms.append(om)
+    want = np.stack([om.mask(vocab) for om in oms])
+    if rows > 2:   # an ended row
+        ms[2] = xgm.Matcher(cache=caches[0])
+        ms[2].accept_bytes(b"null")
+        ms[2].accept_token(int(vocab.stop_ids[0]))
+        want[2] = False
+        want[2, vocab.stop_ids] = True
+    bits = oracle.pack_bitmask(want)
+    masks = [torch.full((rows, xgm.bitmask_words(vocab.size)), -1, dtype=torch.int32, device="cuda") for _ in range(4)]
+    logits = [torch.randn((rows, 1504), device="cuda").to(dt) for dt in (torch.bfloat16, torch.float32)]
+    before = [t.cpu() for t in logits]
+    xgm.fill_next_token_bitmask(ms, masks[0].data_ptr(), _stream())
+    xgm.fill_next_token_bitmask_static(ms, masks[1].data_ptr(), _stream())
+    xgm.fill_and_apply(ms, masks[2].data_ptr(), logits[0].data_ptr(), xgm.DTYPE_BF16, 1504, 1504, stream=_stream())
+    xgm.fill_and_apply(ms, masks[3].data_ptr(), logits[1].data_ptr(), xgm.DTYPE_F32, 1504, 1504, stream=_stream())
+    xgm.fill_overflow_fixup(_stream())
+    torch.cuda.synchronize()
+    for k in range(4):
+        assert np.array_equal(masks[k].cpu().numpy(), bits), f"call {k}"
+    allowed = torch.from_numpy(np.pad(want, ((0, 0), (0, 4))))
+    for t, was in zip(logits, before):
+        assert torch.equal(t.cpu(), torch.where(allowed, was, torch.full_like(was, float("-inf"))))
