@@ -1,4 +1,6 @@
-"""ctypes binding of libxgm.so: argument marshalling only.
+"""Python binding of libxgm.so: argument marshalling only, through ctypes and,
+for the calls of a decode step, through the extension `_native`
+(csrc/pybinding.cpp), which costs a tenth of it per call.
 
 Every function here has the name of the C entry point it calls (minus the
 ``xgm_`` prefix).  Device buffers are passed as integer addresses
@@ -18,6 +20,17 @@ import numpy as np
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libxgm.so")
 _lib = None
+
+
+class _NotLoaded:
+    """Stands in for the extension until the library is loaded."""
+
+    def __getattr__(self, name):
+        load_library()
+        return getattr(_fast, name)
+
+
+_fast = _NotLoaded()
 
 DTYPE_F32, DTYPE_BF16, DTYPE_F16 = 0, 1, 2
 
@@ -127,7 +140,7 @@ def _preload_hip_runtime():
 
 
 def load_library():
-    global _lib
+    global _lib, _fast
     if _lib is not None:
         return _lib
     if not os.path.exists(_LIB_PATH):
@@ -140,6 +153,12 @@ def load_library():
         fn = getattr(lib, name)
         fn.restype = res
         fn.argtypes = args
+    try:
+        from . import _native
+    except ImportError as e:
+        raise ImportError("the extension _native is missing: build it with `python -m paper_2411_15100_amd.build`") from e
+    _native.install({name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in SIGNATURES}, XgmError, Matcher, DeviceBatch)
+    _fast = _native
     _lib = lib
     _handles["lib"] = lib
     return lib
@@ -336,6 +355,8 @@ class Cache:
 
 
 class Matcher:
+    # accept_token(token_id), accept_bytes(data) and reset() are put here by load_library() (csrc/pybinding.cpp)
+
     def __init__(self, cache: Cache = None, grammar: Grammar = None, vocab: Vocab = None):
         lib = load_library()
         h = ctypes.c_void_p()
@@ -345,19 +366,10 @@ class Matcher:
         else:
             _check(lib.xgm_matcher_create_host(grammar._h, vocab._h if vocab is not None else None, ctypes.byref(h)))
             self._keep = (grammar, vocab)
-        self._h = h
+        self._h = h.value
 
     def __del__(self, _destroy=_destroy):
         _destroy("xgm_matcher_destroy", self)
-
-    def reset(self):
-        _check(load_library().xgm_matcher_reset(self._h))
-
-    def accept_token(self, token_id: int):
-        _check(load_library().xgm_matcher_accept_token(self._h, int(token_id)))
-
-    def accept_bytes(self, data: bytes):
-        _check(load_library().xgm_matcher_accept_bytes(self._h, data, len(data)))
 
     def debug_fill_work(self) -> np.ndarray:
         """[stacks with a bitset row, entries of the level-0 / level-1 / level-2 lists] a fill reads for this state."""
@@ -394,16 +406,12 @@ class Matcher:
 
 def fill_next_token_bitmask(matchers, d_bitmask: int, stream: int = 0):
     """d_bitmask: device address of int32 [len(matchers), bitmask_words(V)]."""
-    arr = (ctypes.c_void_p * len(matchers))(*[m._h for m in matchers])
-    _check(load_library().xgm_fill_next_token_bitmask(arr, len(matchers), ctypes.c_void_p(d_bitmask),
-                                                      ctypes.c_void_p(stream)))
+    _fast.fill(matchers, d_bitmask, stream, False)
 
 
 def fill_next_token_bitmask_static(matchers, d_bitmask: int, stream: int = 0):
     """As fill_next_token_bitmask, staged in fixed memory (the call allocates nothing)."""
-    arr = (ctypes.c_void_p * len(matchers))(*[m._h for m in matchers])
-    _check(load_library().xgm_fill_next_token_bitmask_static(arr, len(matchers), ctypes.c_void_p(d_bitmask),
-                                                             ctypes.c_void_p(stream)))
+    _fast.fill(matchers, d_bitmask, stream, True)
 
 
 STATIC_STAGING_BYTES = 1 << 20
@@ -415,37 +423,32 @@ class MatcherBatch:
     def __init__(self, matchers):
         self.matchers = list(matchers)
         self._arr = (ctypes.c_void_p * len(self.matchers))(*[m._h for m in self.matchers])
+        self._addr = ctypes.addressof(self._arr)
 
     def fill_next_token_bitmask(self, d_bitmask: int, stream: int = 0):
-        _check(load_library().xgm_fill_next_token_bitmask(self._arr, len(self.matchers), ctypes.c_void_p(d_bitmask),
-                                                          ctypes.c_void_p(stream)))
+        _fast.fill(self, d_bitmask, stream, False)
 
 
 class DeviceBatch:
     """Matcher states of a fixed batch kept in device memory (xgm_batch_*).
 
     All pointer arguments are device addresses (ints); token ids and rollback
-    steps are int32 [B] device arrays."""
+    steps are int32 [B] device arrays.  accept_tokens(d_token_ids, stream=0),
+    rollback(d_steps, stream=0), fork(d_src_rows, stream=0),
+    fill_next_token_bitmask(d_bitmask, stream=0) and fill_and_apply(d_bitmask,
+    d_logits, dtype, v_logits, row_stride, stream=0) are put here by
+    load_library() (csrc/pybinding.cpp)."""
 
     def __init__(self, matchers, history: int = 8, stream: int = 0):
         lib = load_library()
         arr = (ctypes.c_void_p * len(matchers))(*[m._h for m in matchers])
         h = ctypes.c_void_p()
         _check(lib.xgm_batch_create(arr, len(matchers), int(history), ctypes.c_void_p(stream), ctypes.byref(h)))
-        self._h = h
+        self._h = h.value
         self.size = len(matchers)
 
     def __del__(self, _destroy=_destroy):
         _destroy("xgm_batch_destroy", self)
-
-    def accept_tokens(self, d_token_ids: int, stream: int = 0):
-        _check(load_library().xgm_batch_accept_tokens(self._h, ctypes.c_void_p(d_token_ids), ctypes.c_void_p(stream)))
-
-    def rollback(self, d_steps: int, stream: int = 0):
-        _check(load_library().xgm_batch_rollback(self._h, ctypes.c_void_p(d_steps), ctypes.c_void_p(stream)))
-
-    def fork(self, d_src_rows: int, stream: int = 0):
-        _check(load_library().xgm_batch_fork(self._h, ctypes.c_void_p(d_src_rows), ctypes.c_void_p(stream)))
 
     def status(self, stream: int = 0) -> np.ndarray:
         out = np.zeros(self.size, dtype=np.int32)
@@ -465,24 +468,11 @@ class DeviceBatch:
         """Device address of the batch's counter of walks over the limits."""
         return int(load_library().xgm_batch_overflow_count_device(self._h) or 0)
 
-    def fill_next_token_bitmask(self, d_bitmask: int, stream: int = 0):
-        _check(load_library().xgm_batch_fill_next_token_bitmask(self._h, ctypes.c_void_p(d_bitmask),
-                                                                ctypes.c_void_p(stream)))
-
-    def fill_and_apply(self, d_bitmask: int, d_logits: int, dtype: int, v_logits: int, row_stride: int,
-                       stream: int = 0):
-        _check(load_library().xgm_batch_fill_and_apply(self._h, ctypes.c_void_p(d_bitmask), ctypes.c_void_p(d_logits),
-                                                       int(dtype), int(v_logits), int(row_stride),
-                                                       ctypes.c_void_p(stream)))
-
 
 def fill_and_apply(matchers, d_bitmask: int, d_logits: int, dtype: int, v_logits: int, row_stride: int,
                    stream: int = 0):
     """Fill the bitmask and mask the logits in one launch (rows 16-byte aligned)."""
-    batch = matchers if isinstance(matchers, MatcherBatch) else MatcherBatch(matchers)
-    _check(load_library().xgm_fill_and_apply(batch._arr, len(batch.matchers), ctypes.c_void_p(d_bitmask),
-                                             ctypes.c_void_p(d_logits), int(dtype), int(v_logits), int(row_stride),
-                                             ctypes.c_void_p(stream)))
+    _fast.fill_and_apply(matchers, d_bitmask, d_logits, dtype, v_logits, row_stride, stream)
 
 
 def debug_fill_count_steps(batch: "MatcherBatch", d_bitmask: int, stream: int = 0) -> int:
@@ -528,8 +518,4 @@ def overflow_total() -> int:
 
 def apply_token_bitmask_inplace(d_logits: int, dtype: int, B: int, V_logits: int, row_stride: int, d_bitmask: int,
                                 V_mask: int, d_row_index: int = 0, n_rows: int = None, stream: int = 0):
-    if n_rows is None:
-        n_rows = B
-    _check(load_library().xgm_apply_token_bitmask_inplace(
-        ctypes.c_void_p(d_logits), dtype, B, V_logits, row_stride, ctypes.c_void_p(d_bitmask), V_mask,
-        ctypes.c_void_p(d_row_index) if d_row_index else None, n_rows, ctypes.c_void_p(stream)))
+    _fast.apply(d_logits, dtype, B, V_logits, row_stride, d_bitmask, V_mask, d_row_index, B if n_rows is None else n_rows, stream)

@@ -1,14 +1,18 @@
-"""Build libxgm.so (host C++ + HIP kernels for gfx950) in-tree with hipcc."""
+"""Build libxgm.so (host C++ + HIP kernels for gfx950) with hipcc and the extension _native.so of the Python binding
+with the host compiler, both in-tree."""
 
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libxgm.so")
+EXT = os.path.join(HERE, "_native.so")
+EXT_SOURCE = os.path.join(CSRC, "pybinding.cpp")
 SOURCES = ["automaton.cpp", "engine.cpp", "schema.cpp", "api.cpp", "kernels.hip"]
 HEADERS = ["automaton.hpp", "engine.hpp", "schema.hpp", "kernels.hpp", "walk.hpp", os.path.join("..", "..", "include", "xgm.h")]
 
@@ -20,21 +24,28 @@ FLAGS = [
 ]
 
 
-def build(force: bool = True, verbose: bool = False) -> str:
-    """Compile every source; returns the path of the shared library."""
-    srcs = [os.path.join(CSRC, s) for s in SOURCES]
-    deps = srcs + [os.path.join(CSRC, h) for h in HEADERS]
-    if not force and os.path.exists(LIB) and os.path.getmtime(LIB) >= max(os.path.getmtime(d) for d in deps):
-        return LIB
-    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    cmd = [hipcc] + FLAGS + srcs + ["-o", LIB]
+def _stale(out: str, deps) -> bool:
+    return not os.path.exists(out) or os.path.getmtime(out) < max(os.path.getmtime(d) for d in deps)
+
+
+def _run(cmd, verbose: bool) -> None:
     if verbose:
         print(" ".join(cmd), file=sys.stderr)
     proc = subprocess.run(cmd, capture_output=True, text=True)
     if proc.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + proc.stdout + proc.stderr)
+        raise RuntimeError(f"{cmd[0]} failed:\n" + proc.stdout + proc.stderr)
     if verbose and proc.stderr:
         print(proc.stderr, file=sys.stderr)
+
+
+def build(force: bool = True, verbose: bool = False) -> str:
+    """Compile every source; returns the path of the shared library."""
+    srcs = [os.path.join(CSRC, s) for s in SOURCES]
+    if force or _stale(LIB, srcs + [os.path.join(CSRC, h) for h in HEADERS]):
+        _run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")] + FLAGS + srcs + ["-o", LIB], verbose)
+    if force or _stale(EXT, [EXT_SOURCE]):
+        _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-fvisibility=hidden",
+              "-I" + sysconfig.get_paths()["include"], EXT_SOURCE, "-o", EXT], verbose)
     return LIB
 
 
