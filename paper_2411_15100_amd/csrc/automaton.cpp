@@ -1132,18 +1132,9 @@ Automaton compile_grammar(const std::string& text, const std::string& root) {
     if (is_new) lists.push_back({list, alt, lists[list].length + 1, -1});
     return id;
   };
-  A.hdr.assign(total, NodeHdr{1, 0, 0, 0});
-  SequenceTable shape_ids;
-  shape_ids.clear(256);
-  std::vector<int> list_of(A.n_cls, 0), classes, shape, rev;  // shape: (class, outcome) pairs of the classes that lead anywhere
-  std::vector<uint16_t> outcomes;
-  for (int n = 0; n < total; ++n) {
-    NodeHdr& h = A.hdr[n];
-    h.flags = (A.node_final[n] ? kFlagFinal : 0) | (A.node_dead_end[n] ? kFlagDeadEnd : 0);
-    if (plain(n)) {
-      if (A.bedges[n].size() == 1) { h.lo = A.bedges[n][0].lo; h.hi = A.bedges[n][0].hi; h.target = (uint16_t)A.bedges[n][0].to; }
-      continue;
-    }
+  // what node n does with the byte classes that lead anywhere: (class, list) pairs by class
+  std::vector<int> list_of(A.n_cls, 0), classes;
+  auto lists_at = [&](int n, std::vector<std::pair<int, int>>* out) {
     classes.clear();
     auto add = [&](int k, uint32_t alt) {
       if (list_of[k] == 0) classes.push_back(k);
@@ -1160,21 +1151,80 @@ Automaton compile_grammar(const std::string& text, const std::string& root) {
         else alt = ((uint32_t)e.to << 16) | (uint32_t)A.rule_start[e.rule];
         add(st.first, alt);
       }
+    std::sort(classes.begin(), classes.end());
+    out->clear();
+    for (int k : classes) { out->push_back({k, list_of[k]}); list_of[k] = 0; }
+  };
+  std::vector<std::pair<int, int>> at_node;
+  std::vector<int> start_lists((size_t)NR * A.n_cls, 0);  // per rule and class: the list at the rule's start
+  for (int r = 0; r < NR; ++r) {
+    lists_at(A.rule_start[r], &at_node);
+    for (auto& kl : at_node) start_lists[(size_t)r * A.n_cls + kl.first] = kl.second;
+  }
+  auto pool_room = [&] {
+    if (A.alts.size() >= 0x7FFF) throw Failure(XGM_ERR_TOO_LARGE, "grammar: alternatives pool is full");
+    return (int)A.alts.size();
+  };
+  // The only alternative at a rule's start for class k is a call: the run of calls that starts with it, in the pool; -1 if it
+  // is too short to be worth its place there or if runs are not wanted.  (At other nodes the first call is a step of its
+  // own: its return node would make the run another one for every place that refers to the rule, and what the tables
+  // grow by is missing on chip.)
+  SequenceTable run_ids, run_frames;
+  std::vector<int> run_at, frames_at, run;
+  bool with_runs = true;
+  auto run_of = [&](uint32_t alt, int k) {
+    run.clear();  // the frames
+    int node = 0, calls = 0;
+    bool consumes = false;
+    for (;; ++calls) {
+      if ((alt >> 16) == kMoveTag) { consumes = true; node = (int)(alt & 0xFFFF); break; }
+      if ((alt >> 16) != kTailTag) run.push_back((int)(alt >> 16));
+      node = (int)(alt & 0xFFFF);  // the start of the rule that is entered
+      const AltList& next = lists[start_lists[(size_t)A.node_rule[node] * A.n_cls + k]];
+      if (next.length != 1 || (int)run.size() >= kMaxRun) { ++calls; break; }
+      alt = next.alt;
+    }
+    if (calls < kShortestRun || !with_runs) return -1;
+    bool is_new = false;
+    const int frames = run_frames.intern(run.data(), run.size(), &is_new);
+    if (is_new) {
+      frames_at.push_back(pool_room());
+      for (size_t j = 0; j < run.size(); j += 2) A.alts.push_back((uint32_t)run[j] | (j + 1 < run.size() ? (uint32_t)run[j + 1] << 16 : 0u));
+    }
+    const int key[3] = {frames, consumes, node};
+    const int id = run_ids.intern(key, 3, &is_new);
+    if (is_new) {
+      run_at.push_back(pool_room());
+      A.alts.push_back(kRunFlag | (consumes ? kRunConsumes : 0u) | (uint32_t)run.size() << kRunFramesShift | (uint32_t)frames_at[frames]);
+      A.alts.push_back((uint32_t)node);
+    }
+    return run_at[id];
+  };
+  SequenceTable shape_ids;
+  std::vector<int> shape, rev;  // shape: (class, outcome) pairs of the classes that lead anywhere
+  std::vector<uint16_t> outcomes;
+  auto flatten = [&](int n) {
+    NodeHdr& h = A.hdr[n];
+    h.flags = (A.node_final[n] ? kFlagFinal : 0) | (A.node_dead_end[n] ? kFlagDeadEnd : 0);
+    if (plain(n)) {
+      if (A.bedges[n].size() == 1) { h.lo = A.bedges[n][0].lo; h.hi = A.bedges[n][0].hi; h.target = (uint16_t)A.bedges[n][0].to; }
+      return;
+    }
+    lists_at(n, &at_node);
     outcomes.clear();
     shape.clear();
-    std::sort(classes.begin(), classes.end());
-    for (int k : classes) {
-      AltList& list = lists[list_of[k]];
+    for (auto& kl : at_node) {
+      AltList& list = lists[kl.second];
       uint16_t entry;
       if (list.length == 1 && (list.alt >> 16) == kMoveTag) entry = (uint16_t)(list.alt & 0xFFFF);
+      else if (const int at = list.length == 1 && n == A.rule_start[A.node_rule[n]] ? run_of(list.alt, kl.first) : -1; at >= 0) entry = (uint16_t)(kAltFlag | at);
       else {
         if (list.length > 250) throw Failure(XGM_ERR_TOO_LARGE, "grammar: too many alternatives at one node");
         if (list.pool_at < 0) {
-          list.pool_at = (int)A.alts.size();
-          if (list.pool_at >= 0x7FFF) throw Failure(XGM_ERR_TOO_LARGE, "grammar: alternatives pool is full");
+          list.pool_at = pool_room();
           A.alts.push_back((uint32_t)list.length);
           rev.clear();
-          for (int j = list_of[k]; j > 0; j = lists[j].before) rev.push_back((int)lists[j].alt);
+          for (int j = kl.second; j > 0; j = lists[j].before) rev.push_back((int)lists[j].alt);
           for (size_t j = rev.size(); j-- > 0;) A.alts.push_back((uint32_t)rev[j]);
         }
         entry = (uint16_t)(kAltFlag | list.pool_at);
@@ -1183,9 +1233,8 @@ Automaton compile_grammar(const std::string& text, const std::string& root) {
       size_t idx = std::find(outcomes.begin(), outcomes.end(), entry) - outcomes.begin();
       if (idx == outcomes.size()) outcomes.push_back(entry);
       if (idx >= kDeadShape) throw Failure(XGM_ERR_TOO_LARGE, "grammar: too many distinct outcomes at one node");
-      shape.push_back(k);
+      shape.push_back(kl.first);
       shape.push_back((int)idx);
-      list_of[k] = 0;
     }
     bool is_new = false;
     const uint32_t id = (uint32_t)shape_ids.intern(shape.data(), shape.size(), &is_new);
@@ -1201,6 +1250,26 @@ Automaton compile_grammar(const std::string& text, const std::string& root) {
     h.hi = (uint8_t)(id >> 8);
     h.target = (uint16_t)A.targets.size();        // start of this node's outcomes
     A.targets.insert(A.targets.end(), outcomes.begin(), outcomes.end());
+  };
+  // (a grammar whose pool has no room for the runs does without them)
+  for (bool done = false; !done;) {
+    A.hdr.assign(total, NodeHdr{1, 0, 0, 0});
+    A.alts.clear();
+    A.shapes.clear();
+    A.targets.clear();
+    shape_ids.clear(256);
+    run_ids.clear(256);
+    run_frames.clear(64);
+    run_at.clear();
+    frames_at.clear();
+    for (auto& l : lists) l.pool_at = -1;
+    try {
+      for (int n = 0; n < total; ++n) flatten(n);
+      done = true;
+    } catch (const Failure&) {
+      if (!with_runs) throw;
+      with_runs = false;
+    }
   }
   A.n_shapes = (int32_t)shape_ids.size();
   for (int n = 0; n < total; ++n)

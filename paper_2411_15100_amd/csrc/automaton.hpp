@@ -42,6 +42,13 @@ constexpr uint16_t kAltFlag = 0x8000;   // outcome: index into the alternatives 
 constexpr uint32_t kMoveTag = 0xFFFF;   // alternative (tag << 16 | node): consume the byte, go to node
 constexpr uint32_t kTailTag = 0xFFFE;   // alternative: enter the callee at `node` without pushing a frame
                                         // (any other tag is the return node to push)
+// A run of calls without a choice - entering an expression goes through a dozen precedence levels before the first
+// byte of the operand is consumed - is one entry of the alternatives pool instead of a list, of two words: kRunFlag |
+// (kRunConsumes if the byte is consumed at its end) | frames to push << kRunFramesShift | where in the pool they are
+// (16 bits each, in the order in which they are pushed), and the node it leads to.
+constexpr uint32_t kRunFlag = 0x80000000u, kRunConsumes = 0x40000000u, kRunFramesShift = 16, kRunFramesMask = 0x3Fu, kRunAtMask = 0x7FFFu;
+constexpr int kShortestRun = 3;         // calls
+constexpr int kMaxRun = 32;             // frames pushed by one run
 
 // a set of byte values
 struct ByteSet {
@@ -110,7 +117,7 @@ struct Automaton {
   std::vector<uint8_t> shapes;     // [n_shapes * n_cls]
   int32_t n_shapes = 0;
   std::vector<uint16_t> targets;   // outcomes of the branching nodes, node after node
-  std::vector<uint32_t> alts;      // pool: count, then count entries (tag << 16 | node)
+  std::vector<uint32_t> alts;      // pool: count, then count entries (tag << 16 | node); or a run (kRunFlag)
   int32_t max_alts = 0;
 };
 

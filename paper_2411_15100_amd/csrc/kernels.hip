@@ -69,9 +69,9 @@ struct LdsTabT {
     return make_uint2((uint32_t)h, (uint32_t)(h >> 32));
   }
   __device__ __forceinline__ void lookup(uint32_t n, uint32_t c, uint32_t& k, uint32_t& single, uint32_t& base_out,
-                                         bool& pooled, uint32_t& fin, uint32_t& after) const {
+                                         uint32_t& run, bool& pooled, uint32_t& fin, uint32_t& after) const {
     const uint2 h = header(n);
-    k = 0; single = 0; base_out = 0; pooled = false;
+    k = 0; single = 0; base_out = 0; run = 0; pooled = false;
     fin = h.y & 1u;
     after = (rd32(off_follow + ((h.y >> 16) * 8u + (c >> 5)) * 4u, follow_lds) >> (c & 31)) & 1u;
     if (h.y & 2u) {
@@ -80,7 +80,12 @@ struct LdsTabT {
       if (si != 0xFFu) {
         const uint32_t a = rd16(off_targets + ((h.x >> 16) + si) * 2u, targets_lds);
         if (a < 0x8000u) { k = 1; single = (0xFFFFu << 16) | a; }
-        else { base_out = a & 0x7FFFu; k = alt(base_out); pooled = true; }
+        else {
+          base_out = a & 0x7FFFu;
+          k = alt(base_out);
+          pooled = true;
+          if (k & kRunFlagD) { run = k; k = 1; }
+        }
       }
     } else {
       const uint32_t lo = h.x & 0xFFu, hi = (h.x >> 8) & 0xFFu;
@@ -123,7 +128,7 @@ struct LiveView {
 // one that needs most of the LDS budget runs with 768, so that two workgroups
 // per compute unit still give 6 waves per SIMD.
 constexpr int kClassifyThreadsSmall = 256, kClassifyThreadsLarge = 768;
-constexpr uint32_t kClassifySmallStage = 24 * 1024;
+constexpr uint32_t kClassifySmallStage = 32 * 1024;
 // nodes a thread classifies its token at, one after the other: few for small tables (more, shorter-lived
 // workgroups: the slowest walks weigh less), more where every workgroup has a large table image to stage
 constexpr int kNodesPerBlockSmall = 4, kNodesPerBlockMany = 16, kNodesPerBlockLarge = 64;

@@ -20,18 +20,22 @@ namespace xgm {
 constexpr uint32_t kAltFlagD = 0x8000;
 constexpr uint32_t kMoveTagD = 0xFFFF;
 constexpr uint32_t kTailTagD = 0xFFFE;
+constexpr uint32_t kRunFlagD = 0x80000000u, kRunConsumesD = 0x40000000u;  // a run of calls (see automaton.hpp)
+XGM_HD uint32_t run_frames(uint32_t word) { return (word >> 16) & 0x3Fu; }
+XGM_HD uint32_t run_frames_at(uint32_t word) { return word & 0x7FFFu; }
 constexpr uint32_t kLiveBase = 0x8000;  // stack handles >= this refer to the request's live frames
 
 // Table access for the walk: at node n on byte c, how many move / call
 // alternatives are there (k), which (a single packed one, or k entries in the
-// alternatives pool from `base`), may the rule end at n (fin), and can c come
-// right after an instance of n's rule at all (after).
+// alternatives pool from `base`; a run of calls counts as one and has its first
+// word in `run`), may the rule end at n (fin), and can c come right after an
+// instance of n's rule at all (after).
 struct CompactTab {
   TabView v;
-  XGM_HD void lookup(uint32_t n, uint32_t c, uint32_t& k, uint32_t& single, uint32_t& base, bool& pooled,
+  XGM_HD void lookup(uint32_t n, uint32_t c, uint32_t& k, uint32_t& single, uint32_t& base, uint32_t& run, bool& pooled,
                      uint32_t& fin, uint32_t& after) const {
     const uint2 h = (n < (uint32_t)v.n_near) ? v.hdr_near[n] : v.hdr_far[n];
-    k = 0; single = 0; base = 0; pooled = false;
+    k = 0; single = 0; base = 0; run = 0; pooled = false;
     fin = h.y & 1u;
     after = (v.follow_rules[(h.y >> 16) * 8 + (c >> 5)] >> (c & 31)) & 1u;
     if (h.y & 2u) {
@@ -39,7 +43,12 @@ struct CompactTab {
       if (si != 0xFFu) {
         const uint32_t a = v.targets[(h.x >> 16) + si];
         if (a < 0x8000u) { k = 1; single = (0xFFFFu << 16) | a; }
-        else { base = a & 0x7FFFu; k = v.alts[base]; pooled = true; }
+        else {
+          base = a & 0x7FFFu;
+          k = v.alts[base];
+          pooled = true;
+          if (k & kRunFlagD) { run = k; k = 1; }
+        }
       }
     } else {
       const uint32_t lo = h.x & 0xFFu, hi = (h.x >> 8) & 0xFFu;
@@ -127,28 +136,30 @@ XGM_HD int walk_token(const Tab& T, const uint4 tk, const uint8_t* ext, const in
   uint32_t arena[kArenaFrames];  // ret | parent handle << 16
   uint2 choice[kChoicePoints];   // x = node | sp << 16 ; y = i | alt << 8 | top << 16 | f << 24
   uint32_t n = start_node, sp = kLiveBase + depth - 1, f = 1, alt = 0, top = 0, csp = 0;
+  uint32_t needed = 0;           // frames below this are needed by the most recent pending alternative
   int i = i0;
+  uint32_t c = i < len ? token_byte(tw, ext, i) : 0u;
   uint32_t left_frame = 0u;  // bit 0: the bottom frame was left with bytes remaining, bit 1: in front of a byte of `follow`
   for (int steps = 0;; ++steps) {
     if (steps_out) *steps_out = (uint32_t)steps;
     if (i == len && !End::kEnumerate) return kAccept;
     if (steps >= kMaxSteps) return kOverflow;
-    bool advanced = false;
     if (i == len) {
       at_end(n, sp, arena, live);      // then on to the next path
     } else {
-      const uint32_t c = token_byte(tw, ext, i);
-      uint32_t k, single, base, fin, after;
+      uint32_t k, single, base, run, fin, after;
       bool pooled;
-      T.lookup(n, c, k, single, base, pooled, fin, after);
+      T.lookup(n, c, k, single, base, run, pooled, fin, after);
       uint32_t can_pop = fin & f;
-      if (BUILD && can_pop && sp == kLiveBase) {
+      if (sp == kLiveBase) {
         // The bottom frame may end here (nothing is known below it): noted at once instead of kept as a
         // pending alternative, so that a run through a rule that may end after every byte (the inside of
-        // a string, a number) leaves nothing to come back to.
-        const uint32_t fo = T.follows(follow, c);
-        left_frame |= 1u | (fo << 1);
-        if (exits_out && fo) *exits_out |= 1u << (i < 31 ? i : 31);
+        // a string, a number) leaves nothing to come back to.  (BUILD = false: the end of the root rule.)
+        if (BUILD && can_pop) {
+          const uint32_t fo = T.follows(follow, c);
+          left_frame |= 1u | (fo << 1);
+          if (exits_out && fo) *exits_out |= 1u << (i < 31 ? i : 31);
+        }
         can_pop = 0u;
       }
       if (PRUNE) can_pop &= after;  // a return in front of a byte that can never follow the rule leads nowhere
@@ -156,56 +167,70 @@ XGM_HD int walk_token(const Tab& T, const uint4 tk, const uint8_t* ext, const in
       // nothing but a move along a byte edge (most steps inside a string, a number, a name): taken at once
       if (alt == 0u && total == 1u && k == 1u && !pooled) {
         n = single & 0xFFFFu;
-        ++i;
         f = 1;
+        if (++i < len) c = token_byte(tw, ext, i);
         continue;
       }
       if (alt < total) {
-        bool ok = true;
         if (alt + 1 < total) {
           if (csp == kChoicePoints) return kOverflow;
           choice[csp++] = make_uint2(n | (sp << 16), (uint32_t)i | ((alt + 1) << 8) | (top << 16) | (f << 24));
+          needed = top;
         }
+        bool consumes = false;
         if (alt < k) {
-          const uint32_t e = pooled ? T.alt(base + 1 + alt) : single;
-          const uint32_t tag = e >> 16, dst = e & 0xFFFFu;
-          if (tag == kMoveTagD) { n = dst; ++i; f = 1; }
-          else if (tag == kTailTagD) { n = dst; f = 0; }  // enter the callee, it returns to our parent
-          else {
-            if (top == kArenaFrames) return kOverflow;
-            arena[top] = tag | (sp << 16);
-            sp = top++;
-            n = dst;
+          if (run) {  // several calls, one after the other
+            const uint32_t m = run_frames(run);
+            if (top + m > kArenaFrames) return kOverflow;
+            for (uint32_t j = 0; j < m; ++j) {
+              arena[top] = ((T.alt(run_frames_at(run) + (j >> 1)) >> ((j & 1u) * 16u)) & 0xFFFFu) | (sp << 16);
+              sp = top++;
+            }
+            n = T.alt(base + 1);
             f = 0;
+            consumes = (run & kRunConsumesD) != 0u;
+          } else {
+            const uint32_t e = pooled ? T.alt(base + 1 + alt) : single;
+            const uint32_t tag = e >> 16;
+            n = e & 0xFFFFu;
+            f = 0;
+            if (tag == kMoveTagD) consumes = true;
+            else if (tag != kTailTagD) {  // (a tail call: enter the callee, it returns to our parent)
+              if (top == kArenaFrames) return kOverflow;
+              arena[top] = tag | (sp << 16);
+              sp = top++;
+            }
+          }
+          if (consumes) {
+            f = 1;
+            if (++i < len) c = token_byte(tw, ext, i);
           }
         } else if (sp < kLiveBase) {   // return into a frame pushed during this walk
           const uint32_t fr = arena[sp], old = sp;
           n = fr & 0xFFFFu;
           sp = fr >> 16;
           // frames from `old` upwards are garbage unless a pending alternative still needs them
-          if (csp == 0 || ((choice[csp - 1].y >> 16) & 0xFFu) <= old) top = old;
+          if (needed <= old) top = old;
         } else {                       // return into a live frame
           const uint32_t d = sp - kLiveBase;
-          if (d == 0) {                // nothing below: the end of the root rule (BUILD notes this case above)
-            ok = false;
-          } else {
-            n = live[d - 1];
-            sp = kLiveBase + d - 1;
-          }
+          n = live[d - 1];
+          sp = kLiveBase + d - 1;
         }
-        if (ok) { alt = 0; advanced = true; }
+        alt = 0;
+        continue;
       }
     }
-    if (!advanced) {                 // back up to the most recent pending alternative
-      if (csp == 0) break;
-      const uint2 ch = choice[--csp];
-      n = ch.x & 0xFFFFu;
-      sp = ch.x >> 16;
-      i = (int)(ch.y & 0xFFu);
-      alt = (ch.y >> 8) & 0xFFu;
-      top = (ch.y >> 16) & 0xFFu;
-      f = (ch.y >> 24) & 1u;
-    }
+    // back up to the most recent pending alternative
+    if (csp == 0) break;
+    const uint2 ch = choice[--csp];
+    n = ch.x & 0xFFFFu;
+    sp = ch.x >> 16;
+    i = (int)(ch.y & 0xFFu);
+    alt = (ch.y >> 8) & 0xFFu;
+    top = (ch.y >> 16) & 0xFFu;
+    f = (ch.y >> 24) & 1u;
+    c = token_byte(tw, ext, i);
+    needed = csp ? (choice[csp - 1].y >> 16) & 0xFFu : 0u;
   }
   if (BUILD && left_frame) return (left_frame & 2u) ? kUncertain : kUncertainPlain;
   return kReject;
