@@ -233,6 +233,7 @@ struct xgm_batch {
   int32_t B = 0, H = 0;
   xgm_vocab* v = nullptr;
   std::vector<xgm_cache*> caches;  // one per row (referenced)
+  bool walks = false;              // some of them have walk entries
   DevBatch dev{};
   std::vector<void*> dev_ptrs;
   // walks over the on-chip limits: the batch's own log, how much of it has been examined, and where the last
@@ -894,7 +895,7 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
     // grammars, 0.8 for a C-like one; the pass is run again with more room if this is not enough)
     args.res_cap = (uint32_t)std::min<uint64_t>(std::max<uint64_t>(n_base, 1u << 16), 1u << 25);
     for (int l = 0; l + 1 < c->levels; ++l) args.res[l] = arena.array<uint4>(args.res_cap);
-    args.res_count = arena.array<uint32_t>(kCtxLevels);
+    args.res_count = arena.array<uint32_t>(kCtxLevels + 1);
     {
       uint32_t key0 = (uint32_t)N;
       for (int l = 0; l < kCtxLevels; ++l) {
@@ -938,9 +939,10 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
     HIP_OK(hipGetLastError());
     HIP_OK(hipStreamSynchronize(stream));
     for (;;) {  // records that did not fit were dropped: count again with room for all of them (rare)
-      uint32_t made[kCtxLevels] = {};
+      uint32_t made[kCtxLevels + 1] = {};
       HIP_OK(hipMemcpy(made, args.res_count, sizeof(made), hipMemcpyDeviceToHost));
       const uint32_t most = *std::max_element(made, made + kCtxLevels);
+      c->host.walks = made[kCtxLevels];
       if (most <= args.res_cap) break;
       args.res_cap = most;
       for (int l = 0; l + 1 < c->levels; ++l) args.res[l] = arena.array<uint4>(args.res_cap);
@@ -1298,12 +1300,14 @@ static int fill_impl(xgm_matcher* const* ms, int32_t B, int32_t* d_bitmask, void
   if (B > 65535) return fail(XGM_ERR_TOO_LARGE, "fill: more than 65535 rows in one call");
   xgm_vocab* v = nullptr;
   size_t n_stacks = 0, n_frames = 0;
+  bool walks = false;
   for (int32_t b = 0; b < B; ++b) {
     const xgm_matcher* m = ms[b];
     if (!m || !m->c) return fail(XGM_ERR_BAD_ARG, "fill: matcher is null or has no cache");
     if (v && m->v != v) return fail(XGM_ERR_BAD_ARG, "fill: all matchers must share one vocabulary");
     v = m->v;
     if (m->terminated) continue;
+    walks = walks || m->c->host.walks != 0;
     n_stacks += m->stacks.size();
     for (auto& s : m->stacks) {
       if (s.size() > XGM_MAX_STACK_DEPTH) return fail(XGM_ERR_TOO_LARGE, "fill: stack deeper than 4096 frames");
@@ -1336,7 +1340,7 @@ static int fill_impl(xgm_matcher* const* ms, int32_t B, int32_t* d_bitmask, void
       if (use_static && !C.d_log) return fail(XGM_ERR_INTERNAL, "fill (static staging): the library's device context does not exist yet");
       OverflowLog* log = overflow_log();
       const uint32_t seq = ++C.seq;
-      launch_fill_inline(states, (uint32_t)words, B, v->dv, reinterpret_cast<uint32_t*>(d_bitmask), log, seq, stream,
+      launch_fill_inline(states, (uint32_t)words, B, v->dv, walks, reinterpret_cast<uint32_t*>(d_bitmask), log, seq, stream,
                          fused ? fused->d_logits : nullptr, fused ? fused->esize : 0, fused ? fused->neg_inf : 0u,
                          fused ? fused->V_logits : 0, fused ? fused->row_stride : 0);
       HIP_OK(hipGetLastError());
@@ -1418,7 +1422,7 @@ static int fill_impl(xgm_matcher* const* ms, int32_t B, int32_t* d_bitmask, void
   if (timing) HIP_OK(hipEventRecord(timing[1], stream));
   const uint32_t seq = ++C.seq;
   launch_fill(reinterpret_cast<const RowDesc*>(d_buf), reinterpret_cast<const uint32_t*>((char*)d_buf + off_stacks),
-              reinterpret_cast<const uint16_t*>((char*)d_buf + off_frames), B, v->dv, reinterpret_cast<uint32_t*>(d_bitmask),
+              reinterpret_cast<const uint16_t*>((char*)d_buf + off_frames), B, v->dv, walks, reinterpret_cast<uint32_t*>(d_bitmask),
               log, seq, d_step_counter, stream, fused ? fused->d_logits : nullptr, fused ? fused->esize : 0,
               fused ? fused->neg_inf : 0u, fused ? fused->V_logits : 0, fused ? fused->row_stride : 0);
   HIP_OK(hipGetLastError());
@@ -1736,7 +1740,11 @@ int xgm_batch_create(xgm_matcher* const* ms, int32_t B, int32_t history, void* h
     bt->H = history + 1;
     bt->v = v;
     ++v->refs;
-    for (int32_t b = 0; b < B; ++b) { bt->caches.push_back(ms[b]->c); ++ms[b]->c->refs; }
+    for (int32_t b = 0; b < B; ++b) {
+      bt->caches.push_back(ms[b]->c);
+      ++ms[b]->c->refs;
+      bt->walks = bt->walks || ms[b]->c->host.walks != 0;
+    }
     auto keep = [&](auto* p) { bt->dev_ptrs.push_back((void*)p); return p; };
     const size_t hdr_words = stack_hdr_stride(v->dv.n_seg);
     const size_t slots = (size_t)B * bt->H;
@@ -1912,7 +1920,7 @@ static int batch_fill_impl(xgm_batch* bt, int32_t* d_bitmask, void* hip_stream, 
     seq = ++C.seq;
   }
   const DevBatch& d = bt->dev;
-  launch_fill(d.rows, d.hdrs, d.frames, d.B, bt->v->dv, reinterpret_cast<uint32_t*>(d_bitmask), d.log, seq, nullptr,
+  launch_fill(d.rows, d.hdrs, d.frames, d.B, bt->v->dv, bt->walks, reinterpret_cast<uint32_t*>(d_bitmask), d.log, seq, nullptr,
               static_cast<hipStream_t>(hip_stream), fused ? fused->d_logits : nullptr, fused ? fused->esize : 0,
               fused ? fused->neg_inf : 0u, fused ? fused->V_logits : 0, fused ? fused->row_stride : 0);
   HIP_OK(hipGetLastError());

@@ -529,6 +529,7 @@ struct ContextWork {
   // workgroup's own counters per segment for this list: the entry is then only counted there)
   __device__ __forceinline__ void emit(uint32_t key, uint32_t kind, uint32_t pos, uint32_t* outcome,
                                        uint32_t* lds_counts) const {
+    if (!WRITE && kind != kEntryAccepted) a.res_count[kCtxLevels] = 1u;  // (the cache has walk entries)
     if (!WRITE && lds_counts) atomicAdd(&lds_counts[id / (uint32_t)kSegTokens], 1u);
     else ListSink<WRITE>{voc, a}.emit(id, key, kind, pos);
     if (outcome) *outcome = outcome_code(kind, pos);
@@ -941,11 +942,10 @@ constexpr int kFillFramesLds = 1024;            // live frames kept in LDS (deep
 //      top node's own accepted tokens if it keeps a list instead of a bitset,
 //      the tokens accepted given the node below the top frame, those accepted
 //      given the two and the three nodes below) are streamed once, coalesced;
-//      an accepted entry sets its bit with an LDS atomic, a walk entry is only
-//      noted (one flag for the workgroup);
-//   3. if there was a walk entry, the lists are gone through again and theirs
-//      are decided against the live stack: only then are the request's automaton
-//      tables and frames copied into LDS.  Most launches walk nothing;
+//      an accepted entry sets its bit with an LDS atomic, a walk entry is put
+//      into a queue in LDS;
+//   3. if there are walk entries, they are decided against the live stack: only
+//      then are the request's automaton tables and frames copied into LDS;
 //   4. the words are stored once, coalesced, and - in the fused instantiation -
 //      the logits of the segment are masked straight from them.
 // No global atomics, no second pass over the mask.  The launch is bound by
@@ -954,157 +954,85 @@ constexpr int kFillFramesLds = 1024;            // live frames kept in LDS (deep
 // the same for the whole workgroup (an empty list costs a scalar compare).
 // COUNT = true additionally sums the automaton steps of all walks into
 // *step_counter (instrumentation for the benchmark; never used on the hot path).
+// WALKS = false: no mask cache of the batch has a walk entry (a cache knows:
+// schema grammars have none) and step 3 is left out; the kernel then fits eight
+// workgroups per compute unit (registers, LDS) and needs no scratch memory.
+// WALKS = true: four workgroups per compute unit, with room for the walk's
+// registers and for the tables of all but the largest grammars.  With one
+// kernel for both the walk was a function of its own, which spilled in its
+// inner loop and cost 5 us before its first step: the fill of a
+// row that walks a handful of tokens (C/SQL-like grammar, 128256 tokens, one row)
+// went from 13.7 to 8.7 us, one that walks 500 steps from 53 to 36.
+template <bool WALKS>
 struct FillShared {
   uint32_t words[kSegWords];
-  uint16_t live[kFillFramesLds];
-  uint32_t any_walk;
 };
-
+constexpr uint32_t kWalkQueue = 256;  // entries; where there are more the lists are gone through again
+template <>
+struct FillShared<true> {
+  uint32_t words[kSegWords];
+  uint16_t live[kFillFramesLds];
+  uint2 queue[kWalkQueue];            // (entry, stack)
+  uint32_t n_queued;                  // counts on beyond the queue's room
+};
 
 // What the walks need to know about a row, wherever its state came from.
 struct WalkRow {
-  const XGM_GLOBAL uint32_t* entries;
   const XGM_GLOBAL uint32_t* stacks;   // first stack: a header, or kInlineStackWords
-  const XGM_GLOBAL uint32_t* key_off;  // states that came with the launch; null: the offsets are in the headers
   const XGM_GLOBAL uint16_t* frames;
-  uint32_t n_stacks, stride, frame0, n_frames, epoch;
-  int32_t n_seg;
+  uint32_t stride, frame0, n_frames, epoch;
 };
 
-// Decides the walk entries of the workgroup's lists (all threads call this).
-template <bool COUNT, bool KEEP_UNDECIDED, class Tab>
-__device__ __forceinline__ void fill_walks(const Tab& T, FillShared& sm, const WalkRow& row, const int32_t b, const int32_t seg,
-                                           const bool frames_in_lds, const DevVocab& voc, OverflowLog* log, uint32_t seq,
-                                           unsigned long long& my_steps) {
-  const XGM_GLOBAL uint32_t* entries = row.entries;
-  const int32_t id0 = seg * kSegTokens;
-  for (uint32_t st = 0; st < row.n_stacks; ++st) {
-    // one round of loads per stack: its scalars and where its four lists begin in this segment and in the next
-    const XGM_GLOBAL uint32_t* sh = row.stacks + (size_t)st * row.stride;
-    typedef uint32_t v4u __attribute__((ext_vector_type(4)));
-    v4u scalars, o0, o1;
-    if (row.key_off) {
-      scalars = {sh[0], sh[5] & 0xFFFFu, sh[5] >> 16, sh[6]};
-      o0 = o1 = {0u, 0u, 0u, 0u};
-#pragma unroll
-      for (uint32_t l = 0; l < kStackLists; ++l)
-        if (sh[1 + l] != kNoKey) {
-          const XGM_GLOBAL uint32_t* ko = row.key_off + (size_t)sh[1 + l] * (uint32_t)row.n_seg + (uint32_t)seg;
-          o0[l] = ko[0];
-          o1[l] = ko[1];
-        }
+// Decides walk entries, thread t the entries t, t + kFillThreads, ... of the queue (list null) or of a list of stack
+// `list_stack` (all threads call this).
+template <bool COUNT, bool KEEP_UNDECIDED, bool INLINE, class Tab>
+__device__ __forceinline__ void fill_walks(const Tab& T, FillShared<true>& sm, const WalkRow& row, const int32_t b, const int32_t id0,
+                                           const XGM_GLOBAL uint32_t* list, const uint32_t list_stack, const uint32_t n,
+                                           const DevVocab& voc, OverflowLog* log, uint32_t seq, unsigned long long& my_steps) {
+  const bool frames_in_lds = row.n_frames <= kFillFramesLds;
+#pragma unroll 1
+  for (uint32_t q = threadIdx.x; q < n; q += kFillThreads) {
+    uint32_t e, stack = list_stack;
+    if (list) {
+      e = list[q];
+      if ((e >> kEntryKindShift) == kEntryAccepted) continue;
     } else {
-      const XGM_GLOBAL v4u* off = (const XGM_GLOBAL v4u*)(sh + stack_hdr_off((uint32_t)seg, 0u));
-      scalars = *(const XGM_GLOBAL v4u*)sh;
-      o0 = off[0];
-      o1 = off[1];
+      e = sm.queue[q].x;
+      stack = sm.queue[q].y;
     }
-    const uint32_t top = scalars.x & 0xFFFFu, depth = scalars.y, f_off = scalars.z;
-    static_assert(kStackHdrTop == 0 && kStackHdrDepth == 1 && kStackHdrFrames == 2 && kStackHdrDrops == 3 && kStackHdrWords == 4 && kStackLists == 4,
-                  "a stack's scalars are one 16-byte load, a segment's list offsets another");
+    const XGM_GLOBAL uint32_t* sh = row.stacks + (size_t)stack * row.stride;
+    const uint32_t id = e & kEntryIdMask, kind = e >> kEntryKindShift, pos = (e >> kEntryPosShift) & 0xFFu;
+    const uint32_t rel = id - (uint32_t)id0;
+    if ((sm.words[rel >> 5] >> (rel & 31u)) & 1u) continue;  // already allowed
+    const TokenRef t = load_token(voc, (int32_t)id);
+    uint32_t top, depth, f_off, drops;
+    if (INLINE) {
+      top = sh[0] & 0xFFFFu;
+      depth = sh[5] & 0xFFFFu;
+      f_off = sh[5] >> 16;
+      drops = sh[6];
+    } else {
+      top = sh[kStackHdrTop] & 0xFFFFu;
+      depth = sh[kStackHdrDepth];
+      f_off = sh[kStackHdrFrames];
+      drops = sh[kStackHdrDrops];
+    }
     LiveView live;
     live.lds = (const XGM_LDS uint16_t*)sm.live + (f_off - row.frame0);
     live.glob = row.frames + f_off;
     live.lo = frames_in_lds ? 0u : 0xFFFFFFFFu;
-    for (uint32_t l = 0; l < kStackLists; ++l) {  // (not unrolled: one copy of the walk)
-      // the list's entries of this segment; the accepted ones are done
-      const uint32_t begin = l == 0u ? o0.x : l == 1u ? o0.y : l == 2u ? o0.z : o0.w;
-      const uint32_t end = l == 0u ? o1.x : l == 1u ? o1.y : l == 2u ? o1.z : o1.w;
-      for (uint32_t j = begin + threadIdx.x; j < end; j += kFillThreads) {
-        const uint32_t e = entries[j];
-        const uint32_t id = e & kEntryIdMask, kind = e >> kEntryKindShift, pos = (e >> kEntryPosShift) & 0xFFu;
-        if (kind == kEntryAccepted) continue;
-        const uint32_t rel = id - (uint32_t)id0;
-        if ((sm.words[rel >> 5] >> (rel & 31u)) & 1u) continue;  // already allowed
-        const uint32_t drop = stack_drop(scalars.w, kind - kEntryWalkTop);  // frames above the one the walk starts in
-        int res = kReject;
-        uint32_t n_steps = 0;
-        if (depth > drop) {
-          const TokenRef t = load_token(voc, (int32_t)id);
-          const uint32_t start = drop == 0u ? top : live[depth - 1u - drop];
-          res = walk_token<false>(T, t.tk, t.ext, t.len, start, live, depth - drop, COUNT ? &n_steps : nullptr,
-                                  0u, drop == 0u ? 0 : (int)pos);
-        }
-        if (COUNT) my_steps += n_steps;
-        if (res == kOverflow) record_overflow(log, seq, (uint32_t)b, id, row.epoch);  // decided on the host
-        if (res == kAccept || (KEEP_UNDECIDED && res == kOverflow)) atomicOr(&sm.words[rel >> 5], 1u << (rel & 31u));
-      }
-    }
+    const uint32_t drop = stack_drop(drops, kind - kEntryWalkTop);  // frames above the one the walk starts in
+    if (depth <= drop) continue;
+    uint32_t n_steps = 0;
+    const uint32_t start = drop == 0u ? top : live[depth - 1u - drop];
+    const int res = walk_token<false>(T, t.tk, t.ext, t.len, start, live, depth - drop, COUNT ? &n_steps : nullptr, 0u, drop == 0u ? 0 : (int)pos);
+    if (COUNT) my_steps += n_steps;
+    if (res == kOverflow) record_overflow(log, seq, (uint32_t)b, id, row.epoch);  // decided on the host
+    if (res == kAccept || (KEEP_UNDECIDED && res == kOverflow)) atomicOr(&sm.words[rel >> 5], 1u << (rel & 31u));
   }
 }
 
-// The whole of step 3, kept out of line: the request's tables and live frames into LDS, then the walks.  Nearly
-// no workgroup comes here, and inlined the walk's registers and code would weigh on every workgroup's path
-// (the kernel ran out of scalar registers and kept them in lanes of a vector register).  What it needs it
-// reads again: the row's state, and of the vocabulary the three arrays a token is fetched from.  The call
-// itself costs a workgroup that walks about a microsecond (registers saved and restored through memory).
-struct FillWalkArgs {
-  const RowDesc* row;
-  const uint32_t* stack_hdrs;
-  const uint16_t* frames;
-  const XGM_GLOBAL uint32_t* states;  // states that came with the launch (the three above are then not used); else null
-  const uint4* tok_by_id;
-  const uint32_t* off_by_id;
-  const uint8_t* bytes;
-  OverflowLog* log;
-  unsigned long long* step_counter;
-  int32_t b, seg, n_seg;
-  uint32_t seq;
-};
-__device__ __forceinline__ uint64_t word_pair(const XGM_GLOBAL uint32_t* w) { return (uint64_t)w[0] | ((uint64_t)w[1] << 32); }
-template <bool COUNT, bool KEEP_UNDECIDED>
-__device__ __noinline__ void fill_walk_path(const FillWalkArgs a, FillShared XGM_LDS* shared, unsigned char XGM_LDS* staged) {
-  FillShared& sm = *(FillShared*)shared;
-  unsigned char* smem = (unsigned char*)staged;
-  WalkRow row;
-  DevTables tab;
-  row.n_seg = a.n_seg;
-  if (a.states) {
-    const uint32_t r0 = a.states[2 * a.b], r1 = a.states[2 * a.b + 1];
-    const XGM_GLOBAL uint32_t* cache = a.states + (r1 & 0xFFFFu);
-    row.entries = (const XGM_GLOBAL uint32_t*)word_pair(cache + 2);
-    row.key_off = (const XGM_GLOBAL uint32_t*)word_pair(cache + 4);
-    tab = *(const DevTables*)word_pair(cache + 6);
-    row.stacks = a.states + (r0 & 0xFFFFu);
-    row.n_stacks = (r0 >> 16) & 0xFFu;
-    row.stride = kInlineStackWords;
-    row.frames = (const XGM_GLOBAL uint16_t*)a.states;
-    row.frame0 = row.stacks[5] >> 16;
-    row.n_frames = r1 >> 16;
-    row.epoch = 0u;
-  } else {
-    const RowDesc rd = *a.row;
-    tab = rd.tab;
-    row.entries = (const XGM_GLOBAL uint32_t*)rd.entries;
-    row.key_off = nullptr;
-    row.stride = stack_hdr_stride(a.n_seg);
-    row.stacks = (const XGM_GLOBAL uint32_t*)a.stack_hdrs + (size_t)rd.stack_begin * row.stride;
-    row.n_stacks = rd.n_stacks;
-    row.frames = (const XGM_GLOBAL uint16_t*)a.frames;
-    row.frame0 = rd.frame_begin;
-    row.n_frames = rd.n_frames;
-    row.epoch = rd.epoch;
-  }
-  DevVocab voc{};
-  voc.tok_by_id = a.tok_by_id;
-  voc.off_by_id = a.off_by_id;
-  voc.bytes = a.bytes;
-  unsigned long long my_steps = 0;
-  const bool frames_in_lds = row.n_frames <= kFillFramesLds;
-  stage_tables(tab, smem, kFillThreads);
-  if (frames_in_lds)
-    for (uint32_t k = threadIdx.x; k < row.n_frames; k += kFillThreads) sm.live[k] = row.frames[row.frame0 + k];
-  __syncthreads();
-  if (small_sections_staged(tab))
-    fill_walks<COUNT, KEEP_UNDECIDED>(LdsTabT<true>(tab, smem), sm, row, a.b, a.seg, frames_in_lds, voc, a.log, a.seq, my_steps);
-  else
-    fill_walks<COUNT, KEEP_UNDECIDED>(LdsTab(tab, smem), sm, row, a.b, a.seg, frames_in_lds, voc, a.log, a.seq, my_steps);
-  __syncthreads();
-  if (COUNT && my_steps) atomicAdd(a.step_counter, my_steps);
-}
-
-// Eight workgroups of 4 waves per compute unit need 8 waves per SIMD: the second
-// launch bound keeps the kernel within the registers that this takes.
+// The second launch bound keeps the kernel within the registers that eight (four) workgroups per compute unit leave.
 // APPLY = 0: the mask only.  APPLY = 2 / 4 (bytes per logit): the workgroup
 // also writes -inf into the logits of its (row, segment) straight from its
 // LDS words (section 2.1), which saves a launch and the re-read of the mask.
@@ -1119,14 +1047,14 @@ struct FusedApply {
 
 // INLINE != 0: the states came with the launch (InlineStates, the first argument: read where the arguments lie);
 // rows, stack_hdrs_ and frames_ are then not used.
-template <bool COUNT, int APPLY, uint32_t INLINE>
-__global__ __launch_bounds__(kFillThreads, 8) void fill_kernel(const InlineStates<INLINE> states_, const RowDesc* __restrict__ rows,
+template <bool COUNT, int APPLY, uint32_t INLINE, bool WALKS>
+__global__ __launch_bounds__(kFillThreads, WALKS ? 4 : 8) void fill_kernel(const InlineStates<INLINE> states_, const RowDesc* __restrict__ rows,
                                                             const uint32_t* __restrict__ stack_hdrs_,
                                                             const uint16_t* __restrict__ frames_, DevVocab voc,
                                                             uint32_t* __restrict__ out, OverflowLog* log, uint32_t seq,
                                                             unsigned long long* step_counter, FusedApply fa) {
   extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ FillShared sm;
+  __shared__ FillShared<WALKS> sm;
   const XGM_GLOBAL uint32_t* stack_hdrs = (const XGM_GLOBAL uint32_t*)stack_hdrs_;
   const uint32_t tid = threadIdx.x;
   const int32_t b = (int32_t)blockIdx.y, seg = (int32_t)blockIdx.x;
@@ -1135,7 +1063,8 @@ __global__ __launch_bounds__(kFillThreads, 8) void fill_kernel(const InlineState
   const int32_t id0 = w_begin * 32;
   // LDS is cleared before anything is fetched (a barrier waits for what its threads have in flight)
   for (int32_t w = tid; w < kSegWords; w += kFillThreads) sm.words[w] = 0u;
-  if (tid == 0) sm.any_walk = 0u;
+  if constexpr (WALKS)
+    if (tid == 0) sm.n_queued = 0u;
   __syncthreads();
   // (in the address space of kernel arguments: what is read from there is known to be the same for all threads)
   const XGM_CONST uint32_t* states = INLINE ? (const XGM_CONST uint32_t*)__builtin_amdgcn_kernarg_segment_ptr() : nullptr;
@@ -1163,12 +1092,40 @@ __global__ __launch_bounds__(kFillThreads, 8) void fill_kernel(const InlineState
   // may the request end here?  then its stop tokens are allowed (the first kFillThreads of them are fetched now)
   const bool may_end = flags & 1u;
   const int32_t my_stop = may_end && (int32_t)tid < voc.n_stop ? voc.stop_ids[tid] : -1;
-  auto take = [&](uint32_t e) {
-    if ((e >> kEntryKindShift) == kEntryAccepted) {
-      const uint32_t rel = (e & kEntryIdMask) - (uint32_t)id0;
-      atomicOr(&sm.words[rel >> 5], 1u << (rel & 31u));
+  auto take = [&](uint32_t e, uint32_t stack) {
+    if constexpr (WALKS)
+      if ((e >> kEntryKindShift) != kEntryAccepted) {
+        const uint32_t at = atomicAdd(&sm.n_queued, 1u);
+        if (at < kWalkQueue) sm.queue[at] = make_uint2(e, stack);
+        return;
+      }
+    const uint32_t rel = (e & kEntryIdMask) - (uint32_t)id0;
+    atomicOr(&sm.words[rel >> 5], 1u << (rel & 31u));
+  };
+  // where the lists of a stack begin in this segment, and in the next (the same for every thread)
+  auto lists_of = [&](uint32_t stack, uint32_t* acc_row, uint2 (&lst)[kStackLists]) {
+    if constexpr (INLINE != 0) {
+      const XGM_CONST uint32_t* sw = states + stack_begin + stack * kInlineStackWords;
+      *acc_row = sw[0] >> 16;
+#pragma unroll
+      for (uint32_t l = 0; l < kStackLists; ++l) {
+        const uint32_t key = sw[1 + l];
+        if (key != kNoKey) {
+          const XGM_CONST uint32_t* ko = key_off + ((size_t)key * (uint32_t)voc.n_seg + (uint32_t)seg);
+          lst[l] = make_uint2(ko[0], ko[1]);
+        }
+      }
     } else {
-      sm.any_walk = 1u;
+      const XGM_GLOBAL uint32_t* sh = stack_hdrs + (size_t)(stack_begin + stack) * hdr_stride;
+      *acc_row = sh[kStackHdrTop] >> 16;
+      static_assert(kStackLists == 4, "the offsets of a segment's four lists are one 16-byte load");
+      const uint4* off = reinterpret_cast<const uint4*>(stack_hdrs_ + (size_t)(stack_begin + stack) * hdr_stride +
+                                                        stack_hdr_off((uint32_t)seg, 0u));
+      const uint4 o0 = off[0], o1 = off[1];
+      lst[0] = make_uint2(o0.x, o1.x);
+      lst[1] = make_uint2(o0.y, o1.y);
+      lst[2] = make_uint2(o0.z, o1.z);
+      lst[3] = make_uint2(o0.w, o1.w);
     }
   };
   // 1 + 2. Two stacks at a time: their headers (the same words for every thread), then, in one go, this
@@ -1183,31 +1140,7 @@ __global__ __launch_bounds__(kFillThreads, 8) void fill_kernel(const InlineState
       acc_row[q] = kNoAccRow;
 #pragma unroll
       for (uint32_t l = 0; l < kStackLists; ++l) lst[q][l] = make_uint2(0u, 0u);
-      if (s0 + q < n_stacks) {
-        if constexpr (INLINE != 0) {
-          const XGM_CONST uint32_t* sw = states + stack_begin + (s0 + q) * kInlineStackWords;
-          acc_row[q] = sw[0] >> 16;
-#pragma unroll
-          for (uint32_t l = 0; l < kStackLists; ++l) {
-            const uint32_t key = sw[1 + l];
-            if (key != kNoKey) {
-              const XGM_CONST uint32_t* ko = key_off + ((size_t)key * (uint32_t)voc.n_seg + (uint32_t)seg);
-              lst[q][l] = make_uint2(ko[0], ko[1]);
-            }
-          }
-        } else {
-          const XGM_GLOBAL uint32_t* sh = stack_hdrs + (size_t)(stack_begin + s0 + q) * hdr_stride;
-          acc_row[q] = sh[kStackHdrTop] >> 16;
-          static_assert(kStackLists == 4, "the offsets of a segment's four lists are one 16-byte load");
-          const uint4* off = reinterpret_cast<const uint4*>(stack_hdrs_ + (size_t)(stack_begin + s0 + q) * hdr_stride +
-                                                            stack_hdr_off((uint32_t)seg, 0u));
-          const uint4 o0 = off[0], o1 = off[1];  // where the lists begin in this segment, and in the next
-          lst[q][0] = make_uint2(o0.x, o1.x);
-          lst[q][1] = make_uint2(o0.y, o1.y);
-          lst[q][2] = make_uint2(o0.z, o1.z);
-          lst[q][3] = make_uint2(o0.w, o1.w);
-        }
-      }
+      if (s0 + q < n_stacks) lists_of(s0 + q, &acc_row[q], lst[q]);
     }
     uint32_t aw[2][kWordsPerThread], first[2][kStackLists];
     bool have[2][kStackLists];
@@ -1236,9 +1169,9 @@ __global__ __launch_bounds__(kFillThreads, 8) void fill_kernel(const InlineState
 #pragma unroll
       for (uint32_t l = 0; l < kStackLists; ++l) {
         if (lst[q][l].x < lst[q][l].y) {
-          if (have[q][l]) take(first[q][l]);
+          if (have[q][l]) take(first[q][l], s0 + q);
           if (lst[q][l].y - lst[q][l].x > (uint32_t)kFillThreads)
-            for (uint32_t j = lst[q][l].x + kFillThreads + tid; j < lst[q][l].y; j += kFillThreads) take(entries[j]);
+            for (uint32_t j = lst[q][l].x + kFillThreads + tid; j < lst[q][l].y; j += kFillThreads) take(entries[j], s0 + q);
         }
       }
     }
@@ -1250,22 +1183,56 @@ __global__ __launch_bounds__(kFillThreads, 8) void fill_kernel(const InlineState
     }
   __syncthreads();
   // 3. walk entries, if any
-  if (sm.any_walk) {
-    FillWalkArgs wa;
-    wa.row = rows + b;
-    wa.stack_hdrs = stack_hdrs_;
-    wa.frames = frames_;
-    wa.states = (const XGM_GLOBAL uint32_t*)(uint64_t)states;
-    wa.tok_by_id = voc.tok_by_id;
-    wa.off_by_id = voc.off_by_id;
-    wa.bytes = voc.bytes;
-    wa.log = log;
-    wa.step_counter = step_counter;
-    wa.b = b;
-    wa.seg = seg;
-    wa.n_seg = voc.n_seg;
-    wa.seq = seq;
-    fill_walk_path<COUNT, APPLY != 0>(wa, (FillShared XGM_LDS*)&sm, (unsigned char XGM_LDS*)smem);
+  if constexpr (WALKS) {
+    if (sm.n_queued != 0u) {
+      WalkRow row;
+      DevTables tab;
+      if constexpr (INLINE != 0) {
+        const XGM_CONST uint32_t* cache = states + (states[2 * b + 1] & 0xFFFFu);
+        tab = *(const DevTables*)((uint64_t)cache[6] | ((uint64_t)cache[7] << 32));
+        row.stacks = (const XGM_GLOBAL uint32_t*)(uint64_t)(states + stack_begin);
+        row.frames = (const XGM_GLOBAL uint16_t*)(uint64_t)states;
+        row.stride = kInlineStackWords;
+        row.frame0 = states[stack_begin + 5u] >> 16;
+        row.n_frames = states[2 * b + 1] >> 16;
+        row.epoch = 0u;
+      } else {
+        tab = rows[b].tab;
+        row.stacks = stack_hdrs + (size_t)stack_begin * hdr_stride;
+        row.frames = (const XGM_GLOBAL uint16_t*)frames_;
+        row.stride = hdr_stride;
+        row.frame0 = rows[b].frame_begin;
+        row.n_frames = rows[b].n_frames;
+        row.epoch = rows[b].epoch;
+      }
+      unsigned long long my_steps = 0;
+      stage_tables(tab, smem, kFillThreads);
+      if (row.n_frames <= kFillFramesLds) {
+#pragma unroll 1
+        for (uint32_t k = tid; k < row.n_frames; k += kFillThreads) sm.live[k] = row.frames[row.frame0 + k];
+      }
+      __syncthreads();
+      // the queue, or, if it overflowed, list after list
+      const uint32_t n_queued = sm.n_queued;
+      const bool again = n_queued > kWalkQueue;
+#pragma unroll 1
+      for (uint32_t k = 0; k < (again ? n_stacks * kStackLists : 1u); ++k) {
+        uint2 list = make_uint2(0u, n_queued);
+        if (again) {
+          uint32_t acc_row;
+          uint2 lst[kStackLists] = {};
+          lists_of(k / kStackLists, &acc_row, lst);
+          list = k % kStackLists == 0u ? lst[0] : k % kStackLists == 1u ? lst[1] : k % kStackLists == 2u ? lst[2] : lst[3];
+        }
+        const XGM_GLOBAL uint32_t* from = again ? entries + list.x : nullptr;
+        if (small_sections_staged(tab))
+          fill_walks<COUNT, APPLY != 0, INLINE != 0>(LdsTabT<true>(tab, smem), sm, row, b, id0, from, k / kStackLists, list.y - list.x, voc, log, seq, my_steps);
+        else
+          fill_walks<COUNT, APPLY != 0, INLINE != 0>(LdsTab(tab, smem), sm, row, b, id0, from, k / kStackLists, list.y - list.x, voc, log, seq, my_steps);
+      }
+      __syncthreads();
+      if (COUNT && my_steps) atomicAdd(step_counter, my_steps);
+    }
   }
   // 4. the words, and the logits of the segment; the last segment also takes the columns beyond the vocabulary
   for (int32_t w = tid; w < n_words; w += kFillThreads) out[(size_t)b * voc.W + w_begin + w] = sm.words[w];
@@ -1771,7 +1738,7 @@ void launch_context_lists(const DevTables& tab, const DevVocab& voc, const Conte
     }
     return;
   }
-  (void)hipMemsetAsync(args.res_count, 0, 4 * kCtxLevels, stream);
+  (void)hipMemsetAsync(args.res_count, 0, 4 * (kCtxLevels + 1), stream);
   if (write) hipLaunchKernelGGL(context_level1_kernel<true>, g1, dim3(kContextThreads), st.stage_bytes, stream, st, voc, args);
   else hipLaunchKernelGGL(context_level1_kernel<false>, g1, dim3(kContextThreads), st.stage_bytes, stream, st, voc, args);
   for (uint32_t level = 2; level <= (uint32_t)kCtxLevels && args.k_base[level - 1] != nullptr; ++level) {
@@ -1803,34 +1770,41 @@ void launch_upload_stacks(const void* src, void* dst, size_t plain_bytes, const 
                      reinterpret_cast<const uint4*>(src_stacks), n_stacks, (uint32_t)n_seg, reinterpret_cast<uint32_t*>(dst_hdrs));
 }
 
-void launch_fill(const RowDesc* rows, const uint32_t* stack_hdrs, const uint16_t* frames, int32_t B, const DevVocab& voc,
+template <bool COUNT, int APPLY, uint32_t INLINE>
+static void launch_fill_of(const InlineStates<INLINE>& st, const RowDesc* rows, const uint32_t* stack_hdrs, const uint16_t* frames, int32_t B,
+                           const DevVocab& voc, bool walks, uint32_t* out, OverflowLog* log, uint32_t seq, unsigned long long* step_counter,
+                           hipStream_t stream, const FusedApply& fa) {
+  const dim3 grid(voc.n_seg, B);
+  if (walks)
+    hipLaunchKernelGGL((fill_kernel<COUNT, APPLY, INLINE, true>), grid, dim3(kFillThreads), kFillLdsBudget, stream, st, rows, stack_hdrs,
+                       frames, voc, out, log, seq, step_counter, fa);
+  else
+    hipLaunchKernelGGL((fill_kernel<false, APPLY, INLINE, false>), grid, dim3(kFillThreads), 0, stream, st, rows, stack_hdrs, frames, voc,
+                       out, log, seq, step_counter, fa);
+}
+void launch_fill(const RowDesc* rows, const uint32_t* stack_hdrs, const uint16_t* frames, int32_t B, const DevVocab& voc, bool walks,
                  uint32_t* out, OverflowLog* log, uint32_t seq, unsigned long long* step_counter, hipStream_t stream,
                  void* logits, int elem_size, uint32_t neg_inf, int32_t V_logits, int64_t row_stride) {
   if (B <= 0) return;
-  const dim3 grid(voc.n_seg, B);
   const FusedApply fa{static_cast<unsigned char*>(logits), row_stride, V_logits, neg_inf};
-  auto kernel = logits ? (elem_size == 2 ? fill_kernel<false, 2, 0> : fill_kernel<false, 4, 0>)
-                       : (step_counter ? fill_kernel<true, 0, 0> : fill_kernel<false, 0, 0>);
-  hipLaunchKernelGGL(kernel, grid, dim3(kFillThreads), kFillLdsBudget, stream, InlineStates<0>{}, rows, stack_hdrs, frames, voc, out,
-                     log, seq, step_counter, fa);
+  auto launch = logits ? (elem_size == 2 ? launch_fill_of<false, 2, 0> : launch_fill_of<false, 4, 0>)
+                       : (step_counter ? launch_fill_of<true, 0, 0> : launch_fill_of<false, 0, 0>);
+  launch(InlineStates<0>{}, rows, stack_hdrs, frames, B, voc, walks, out, log, seq, step_counter, stream, fa);
 }
-
 template <uint32_t WORDS>
-static void launch_fill_inline_of(const uint32_t* states, uint32_t words, const dim3 grid, const DevVocab& voc, uint32_t* out,
+static void launch_fill_inline_of(const uint32_t* states, uint32_t words, int32_t B, const DevVocab& voc, bool walks, uint32_t* out,
                                   OverflowLog* log, uint32_t seq, hipStream_t stream, int elem_size, const FusedApply& fa) {
   InlineStates<WORDS> st;
   std::copy(states, states + words, st.w);
-  auto kernel = fa.logits ? (elem_size == 2 ? fill_kernel<false, 2, WORDS> : fill_kernel<false, 4, WORDS>) : fill_kernel<false, 0, WORDS>;
-  hipLaunchKernelGGL(kernel, grid, dim3(kFillThreads), kFillLdsBudget, stream, st, (const RowDesc*)nullptr, (const uint32_t*)nullptr,
-                     (const uint16_t*)nullptr, voc, out, log, seq, (unsigned long long*)nullptr, fa);
+  auto launch = fa.logits ? (elem_size == 2 ? launch_fill_of<false, 2, WORDS> : launch_fill_of<false, 4, WORDS>) : launch_fill_of<false, 0, WORDS>;
+  launch(st, nullptr, nullptr, nullptr, B, voc, walks, out, log, seq, nullptr, stream, fa);
 }
-void launch_fill_inline(const uint32_t* states, uint32_t words, int32_t B, const DevVocab& voc, uint32_t* out, OverflowLog* log,
+void launch_fill_inline(const uint32_t* states, uint32_t words, int32_t B, const DevVocab& voc, bool walks, uint32_t* out, OverflowLog* log,
                         uint32_t seq, hipStream_t stream, void* logits, int elem_size, uint32_t neg_inf, int32_t V_logits, int64_t row_stride) {
   if (B <= 0) return;
-  const dim3 grid(voc.n_seg, B);
   const FusedApply fa{static_cast<unsigned char*>(logits), row_stride, V_logits, neg_inf};
-  if (words <= kInlineWordsSmall) launch_fill_inline_of<kInlineWordsSmall>(states, words, grid, voc, out, log, seq, stream, elem_size, fa);
-  else launch_fill_inline_of<kInlineWordsLarge>(states, words, grid, voc, out, log, seq, stream, elem_size, fa);
+  if (words <= kInlineWordsSmall) launch_fill_inline_of<kInlineWordsSmall>(states, words, B, voc, walks, out, log, seq, stream, elem_size, fa);
+  else launch_fill_inline_of<kInlineWordsLarge>(states, words, B, voc, walks, out, log, seq, stream, elem_size, fa);
 }
 
 void launch_lds_lookups(int32_t n_blocks, uint32_t hops, uint32_t* sink, hipStream_t stream) {

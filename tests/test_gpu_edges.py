@@ -126,3 +126,31 @@ def test_states_in_the_launch(xgm, wl, rows, depth):
     allowed = torch.from_numpy(np.pad(want, ((0, 0), (0, 4))))
     for t, was in zip(logits, before):
         assert torch.equal(t.cpu(), torch.where(allowed, was, torch.full_like(was, float("-inf"))))
+
+
+# A number that ends an expression leaves hundreds of tokens to the walk: few, as many as the queue of a workgroup
+# holds (256), more; in one segment and in several.
+@pytest.mark.parametrize("V", [300, 900, 1000, 1100, 1300, 8191, 8193, 24000])
+def test_walk_entries(xgm, wl, V):
+    vocab = si.make_vocab("bpe", V, 7)
+    cache = xgm.Cache(xgm.Grammar(si.PYDSL_GRAMMAR, "root"), wl.make_xgm_vocab(vocab))
+    og = oracle.Grammar(si.PYDSL_GRAMMAR, "root")
+    texts = [b"x=1", b"if v==1:x=(1", b"while x:v[1", b"x=\"a", b"def v(x):return v[1]+1"]
+    ms, oms = [], []
+    for t in texts:
+        m, om = xgm.Matcher(cache=cache), oracle.EarleyMatcher(og)
+        m.accept_bytes(t)
+        assert om.advance(t)
+        ms.append(m)
+        oms.append(om)
+    want = oracle.pack_bitmask(np.stack([om.mask(vocab) for om in oms]))
+    before = xgm.overflow_total()
+    for rows in ([0], [1, 3, 4], [0, 1, 2, 3, 4], [k % 5 for k in range(100)]):
+        d_mask = torch.full((len(rows), xgm.bitmask_words(V)), -1, dtype=torch.int32, device="cuda")
+        xgm.fill_next_token_bitmask([ms[k] for k in rows], d_mask.data_ptr(), _stream())
+        assert np.array_equal(d_mask.cpu().numpy(), want[rows]), f"host-side states, {len(rows)} rows"
+        resident = xgm.DeviceBatch([ms[k] for k in rows], history=0, stream=_stream())
+        d_mask.fill_(-1)
+        resident.fill_next_token_bitmask(d_mask.data_ptr(), _stream())
+        assert np.array_equal(d_mask.cpu().numpy(), want[rows]), f"resident states, {len(rows)} rows"
+    assert xgm.overflow_total() == before
