@@ -39,41 +39,58 @@ __device__ __forceinline__ void stage_tables(const DevTables& tab, unsigned char
 #define XGM_LDS __attribute__((address_space(3)))
 #define XGM_GLOBAL __attribute__((address_space(1)))
 #define XGM_CONST __attribute__((address_space(4)))
-template <bool kSmallInLds>
+// kUniform = true: the whole wave asks for the same thing, and what comes back is
+// known to be the same for all lanes (see WaveMem): what is not staged is then read
+// through the scalar cache.
+__device__ __forceinline__ uint32_t uniform(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
+template <bool kSmallInLds, bool kUniform = false>
 struct LdsTabT {
   const XGM_LDS unsigned char* lds;     // the staged part of the image
   const XGM_GLOBAL unsigned char* img;  // the whole image
-  uint32_t n_near, n_cls, off_shapes, off_targets, off_follow, off_alts, off_hdr, off_first;
+  uint32_t n_near, n_nodes, n_cls, off_shapes, off_targets, off_follow, off_alts, off_hdr, off_first;
   bool cls_lds, shapes_lds, targets_lds, follow_lds, alts_lds;
   __device__ __forceinline__ LdsTabT(const DevTables& t, unsigned char* smem)
       : lds((const XGM_LDS unsigned char*)smem),
         img((const XGM_GLOBAL unsigned char*)reinterpret_cast<const unsigned char*>(t.image)),
-        n_near(t.n_near), n_cls((uint32_t)t.n_cls), off_shapes(t.off_shapes), off_targets(t.off_targets),
+        n_near(t.n_near), n_nodes((uint32_t)t.n_nodes), n_cls((uint32_t)t.n_cls), off_shapes(t.off_shapes), off_targets(t.off_targets),
         off_follow(t.off_follow), off_alts(t.off_alts), off_hdr(t.off_hdr), off_first(t.off_first),
         cls_lds(t.lds_end >= 256u), shapes_lds(t.lds_end >= t.off_targets), targets_lds(t.lds_end >= t.off_follow),
         follow_lds(t.lds_end >= t.off_alts), alts_lds(t.lds_end >= t.off_hdr) {}
+  // the 32-bit word that holds the bytes at `off`, through the scalar cache
+  __device__ __forceinline__ uint32_t scalar_word(uint32_t off) const {
+    return *(const XGM_CONST uint32_t*)((const XGM_CONST unsigned char*)(uint64_t)img + (off & ~3u));
+  }
   __device__ __forceinline__ uint32_t rd8(uint32_t off, bool in_lds) const {
+    if constexpr (kUniform) return (kSmallInLds || in_lds) ? uniform(lds[off]) : (scalar_word(off) >> ((off & 3u) * 8u)) & 0xFFu;
     return (kSmallInLds || in_lds) ? (uint32_t)lds[off] : (uint32_t)img[off];
   }
   __device__ __forceinline__ uint32_t rd16(uint32_t off, bool in_lds) const {
+    if constexpr (kUniform)
+      return (kSmallInLds || in_lds) ? uniform(*(const XGM_LDS uint16_t*)(lds + off)) : (scalar_word(off) >> ((off & 2u) * 8u)) & 0xFFFFu;
     return (kSmallInLds || in_lds) ? (uint32_t)*(const XGM_LDS uint16_t*)(lds + off)
                                    : (uint32_t)*(const XGM_GLOBAL uint16_t*)(img + off);
   }
   __device__ __forceinline__ uint32_t rd32(uint32_t off, bool in_lds) const {
+    if constexpr (kUniform) return (kSmallInLds || in_lds) ? uniform(*(const XGM_LDS uint32_t*)(lds + off)) : scalar_word(off);
     return (kSmallInLds || in_lds) ? *(const XGM_LDS uint32_t*)(lds + off) : *(const XGM_GLOBAL uint32_t*)(img + off);
   }
   __device__ __forceinline__ uint2 header(uint32_t n) const {
     unsigned long long h;  // one 8-byte read
+    if constexpr (kUniform) {
+      if (n >= n_near) return make_uint2(scalar_word(off_hdr + n * 8u), scalar_word(off_hdr + n * 8u + 4u));
+      h = *(const XGM_LDS unsigned long long*)(lds + off_hdr + n * 8u);
+      return make_uint2(uniform((uint32_t)h), uniform((uint32_t)(h >> 32)));
+    }
     if (n < n_near) h = *(const XGM_LDS unsigned long long*)(lds + off_hdr + n * 8u);
     else h = *(const XGM_GLOBAL unsigned long long*)(img + off_hdr + (size_t)n * 8u);
     return make_uint2((uint32_t)h, (uint32_t)(h >> 32));
   }
   __device__ __forceinline__ void lookup(uint32_t n, uint32_t c, uint32_t& k, uint32_t& single, uint32_t& base_out,
-                                         uint32_t& run, bool& pooled, uint32_t& fin, uint32_t& after) const {
+                                         uint32_t& run, bool& pooled, uint32_t& fin, uint32_t& rule) const {
     const uint2 h = header(n);
     k = 0; single = 0; base_out = 0; run = 0; pooled = false;
     fin = h.y & 1u;
-    after = (rd32(off_follow + ((h.y >> 16) * 8u + (c >> 5)) * 4u, follow_lds) >> (c & 31)) & 1u;
+    rule = h.y >> 16;
     if (h.y & 2u) {
       const uint32_t cl = rd8(c, cls_lds);
       const uint32_t si = rd8(off_shapes + (h.x & 0xFFFFu) * n_cls + cl, shapes_lds);
@@ -1252,62 +1269,274 @@ __global__ __launch_bounds__(kFillThreads, WALKS ? 4 : 8) void fill_kernel(const
 
 
 // ------------------------------------------------- device-resident states
-// Candidate stacks of one row in LDS (see CollectStacks).
-struct LdsStackSink {
-  uint16_t* frames;
-  uint32_t* depth;
-  uint32_t* count;
-  uint32_t* overflow;
-  uint32_t capacity, max_depth;
-  __device__ __forceinline__ uint32_t claim() { return atomicAdd(count, 1u); }
-};
-
 constexpr int kAcceptThreads = 256;
 constexpr int kErrTokenRejected = -6, kErrTerminated = -7, kErrTooManyStacks = -8, kErrTooLarge = -9, kErrBadArg = -1, kErrInternal = -11;
 
-// is stack a (depth da) ordered before stack b?  element by element, the shorter first (the host's order of stacks)
-__device__ __forceinline__ int compare_stacks(const uint16_t* a, uint32_t da, const uint16_t* b, uint32_t db) {
-  const uint32_t m = da < db ? da : db;
-  for (uint32_t k = 0; k < m; ++k)
-    if (a[k] != b[k]) return a[k] < b[k] ? -1 : 1;
-  return da == db ? 0 : (da < db ? -1 : 1);
+// What the walks of an accept leave behind: for every stack that the token can end in, which of the row's stacks it
+// comes from, how many of that one's frames it keeps, and the frames above them (bottom first, the current node
+// last).  The frames it keeps are not copied by the lane that walks - it would fetch and store a deep stack frame
+// by frame - but by the whole workgroup when the next state is written.
+constexpr uint32_t kAcceptHeaders = 1024;  // node headers staged at most
+constexpr uint32_t kNewFrames = kArenaFrames + 1;
+constexpr uint32_t kWaveMemWords = kArenaFrames + 2 * kChoicePoints;  // (see WaveMem)
+struct AcceptShared {
+  uint16_t live[kBatchRowFrames];                    // the row's frames
+  uint16_t fresh[kBatchMaxCandidates][kNewFrames + 1];
+  uint32_t from[kBatchMaxCandidates];                // stack it comes from | frames kept << 8 | new frames << 16
+  uint32_t less[kBatchMaxCandidates];                // the candidates that come before it, as a bit set
+  uint32_t stack[kBatchMaxStacks];                   // the row's stacks: first frame in `live` | frames << 16
+  uint32_t common[kBatchMaxStacks][kBatchMaxStacks]; // frames that two of them have in common, from the bottom
+  uint32_t slot_of[kBatchMaxStacks], first[kBatchMaxStacks + 1];  // the new stacks in order: candidate, first frame
+  uint32_t keys[kBatchMaxStacks][kStackLists];       // the lists of every new stack
+  uint32_t cidx[kBatchMaxStacks][kCtxLevels];        // which context of its rule the frame above each level sits on
+  uint32_t drops[kBatchMaxStacks];
+  uint32_t mem[kAcceptThreads / 64][kWaveMemWords];
+  uint32_t count, overflow, duplicates, not_final, bad_context;
+  __device__ __forceinline__ uint32_t kept(uint32_t i) const { return (from[i] >> 8) & 0xFFu; }
+  __device__ __forceinline__ uint32_t depth(uint32_t i) const { return kept(i) + (from[i] >> 16); }
+  __device__ __forceinline__ uint32_t frame(uint32_t i, uint32_t k) const {  // frame k of candidate i, from the bottom
+    const uint32_t f = from[i], d = (f >> 8) & 0xFFu;
+    return k < d ? live[(stack[f & 0xFFu] & 0xFFFFu) + k] : fresh[i][k - d];
+  }
+};
+// A walk by a whole wave (all lanes do the same): its memory is in LDS, and everything it reads is declared the same
+// for all lanes, so that the walk runs in scalar registers with scalar branches.  A lone lane waits for every
+// instruction just as long, and needs more of them (each branch turns lanes off and on again; frames and
+// alternatives go through scratch memory).
+struct WaveMem {
+  XGM_LDS uint32_t* arena;    // [kArenaFrames]
+  XGM_LDS uint32_t* choices;  // [2 * kChoicePoints]
+  __device__ __forceinline__ uint32_t frame(uint32_t k) const { return uniform(arena[k]); }
+  __device__ __forceinline__ void set_frame(uint32_t k, uint32_t v) { arena[k] = v; }
+  __device__ __forceinline__ uint2 choice(uint32_t k) const { return make_uint2(uniform(choices[2u * k]), uniform(choices[2u * k + 1u])); }
+  __device__ __forceinline__ void set_choice(uint32_t k, uint2 v) { choices[2u * k] = v.x; choices[2u * k + 1u] = v.y; }
+};
+struct UniformFrames {
+  const XGM_LDS uint16_t* p;
+  __device__ __forceinline__ uint32_t operator[](uint32_t k) const { return uniform(p[k]); }
+};
+// The end policy of the walk (see walk_token): notes where the token can end.  A top node that can only return is
+// returned from first, so that equal states get equal stacks.
+template <class Tab>
+struct NoteStacks {
+  static constexpr bool kEnumerate = true;
+  const Tab* T;
+  AcceptShared* sm;
+  uint32_t stack;
+  template <class Mem, class Live>
+  __device__ __forceinline__ void operator()(uint32_t n, uint32_t sp, const Mem& mem, const Live& live) const {
+    while (T->is_dead_end(n)) {
+      if (sp < kLiveBase) {
+        const uint32_t fr = mem.frame(sp);
+        n = fr & 0xFFFFu;
+        sp = fr >> 16;
+      } else {
+        const uint32_t d = sp - kLiveBase;
+        if (d == 0) break;
+        n = live[d - 1];
+        sp = kLiveBase + d - 1;
+      }
+    }
+    uint32_t m = 1, h = sp;
+    for (; h < kLiveBase; h = mem.frame(h) >> 16) ++m;
+    const uint32_t d = h - kLiveBase;  // frames kept
+    uint32_t i = kBatchMaxCandidates;
+    if (d + m <= kBatchMaxDepth) {
+      if ((threadIdx.x & 63u) == 0u) i = atomicAdd(&sm->count, 1u);
+      i = uniform(i);
+    }
+    if (i >= kBatchMaxCandidates) { sm->overflow = 1u; return; }
+    sm->from[i] = stack | (d << 8) | (m << 16);
+    uint32_t k = m - 1u;
+    sm->fresh[i][k] = (uint16_t)n;
+    for (h = sp; h < kLiveBase; ) {
+      const uint32_t fr = mem.frame(h);
+      sm->fresh[i][--k] = (uint16_t)(fr & 0xFFFFu);
+      h = fr >> 16;
+    }
+  }
+};
+// walk_token's enumerating walk for a wave whose tables (the sections in front of the headers) are in LDS: the same
+// paths in the same order, fewer steps.  A step looks many bytes ahead: lane j at node n on byte i + j (the inside of
+// a string stays where it is), lane 32 + j at node n + j on byte i + j (a literal's nodes are numbered one after the
+// other).  While there is nothing to do but a move along a byte edge, all of a run is taken at once, and the move
+// behind it; what the lane in front of which the run ended has read is what the alternatives there are made from.
+// The lookup has no branches: to a wave that is alone with its walk a taken branch costs as much as a dozen
+// instructions.  A nine-byte piece of a string takes 1.2 us this way, 6 with a lane's walk byte by byte.
+template <class Note>
+__device__ __forceinline__ int walk_wave(const LdsTabT<true, true>& T, WaveMem& mem, const uint4 tk, const uint8_t* ext, const int len,
+                                         const uint32_t start_node, const UniformFrames& live, const uint32_t depth, const Note& note) {
+  if (len > kMaxTokenLen) return kOverflow;
+  const TokenWords tw(tk);
+  const uint32_t lane = threadIdx.x & 63u, ahead = lane & 31u;
+  const uint32_t last_alt = (T.off_hdr - T.off_alts) / 4u - 1u;
+  uint32_t n = start_node, sp = kLiveBase + depth - 1, f = 1, alt = 0, top = 0, csp = 0, needed = 0;
+  int i = 0;
+  for (int steps = 0;; ++steps) {
+    if (steps >= kMaxSteps) return kOverflow;
+    bool back = true;
+    if (i == len) {
+      note(n, sp, mem, live);  // then on to the next path
+    } else {
+      const bool mine = (int)ahead < len - i;
+      const uint32_t c = token_byte(tw, ext, mine ? i + (int)ahead : i);
+      const uint32_t node = lane < 32u || !mine ? n : min(n + ahead, T.n_nodes - 1u);
+      const unsigned long long hdr = node < T.n_near ? *(const XGM_LDS unsigned long long*)(T.lds + T.off_hdr + node * 8u)
+                                                     : *(const XGM_GLOBAL unsigned long long*)(T.img + T.off_hdr + (size_t)node * 8u);
+      const uint32_t hx = (uint32_t)hdr, hy = (uint32_t)(hdr >> 32);
+      const uint32_t cl = T.lds[c];
+      const uint32_t follow = *(const XGM_LDS uint32_t*)(T.lds + T.off_follow + ((hy >> 16) * 8u + (c >> 5)) * 4u) >> (c & 31u);
+      const bool branching = (hy & 2u) != 0u;
+      const uint32_t si = T.lds[T.off_shapes + (branching ? (hx & 0xFFFFu) * T.n_cls : 0u) + cl];
+      const uint32_t at = branching && si != 0xFFu ? (hx >> 16) + si : 0u;
+      const uint32_t target = *(const XGM_LDS uint16_t*)(T.lds + T.off_targets + at * 2u);
+      const bool some = branching ? si != 0xFFu : c >= (hx & 0xFFu) && c <= ((hx >> 8) & 0xFFu);  // a move or calls
+      const uint32_t to = branching ? target : hx >> 16;
+      const bool may_return = ((hy & (ahead == 0u ? f : 1u) & follow) & 1u) != 0u;
+      const bool moves_on = mine && some && to < 0x8000u && !may_return && alt == 0u;
+      const unsigned long long can = __ballot(moves_on), stays = __ballot(moves_on && to == (lane < 32u ? n : node + 1u));
+      const uint32_t same = (uint32_t)__ffs((int)(~(uint32_t)stays | 0x80000000u)) - 1u;
+      const uint32_t chain = (uint32_t)__ffs((int)(~(uint32_t)(stays >> 32) | 0x80000000u)) - 1u;
+      const uint32_t run = max(same, chain), last = same >= chain ? same : 32u + chain;
+      auto of_last = [&](uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)last); };
+      const uint32_t dst = of_last(to);
+      if (chain > same) n += chain;
+      i += (int)run;
+      steps += (int)run;
+      f = run ? 1u : f;
+      if ((can >> last) & 1ull) {
+        n = dst;
+        ++i;
+        f = 1;
+        continue;
+      }
+      if (i == len) { --steps; continue; }
+      const uint32_t y = of_last(hy), k_some = of_last(some ? 1u : 0u);
+      const uint32_t can_pop = sp == kLiveBase ? 0u : y & f & of_last(follow) & 1u;
+      const bool pooled = k_some && dst >= 0x8000u;
+      // the pool entry: lane j has its word j (a count and the alternatives, or a run of calls)
+      const uint32_t base = dst & 0x7FFFu;
+      const uint32_t word = pooled ? *(const XGM_LDS uint32_t*)(T.lds + T.off_alts + min(base + lane, last_alt) * 4u) : 0u;
+      const uint32_t word0 = uniform(word);
+      const bool calls = (word0 & kRunFlagD) != 0u;
+      const uint32_t k = pooled && !calls ? word0 : k_some, total = k + can_pop;
+      if (alt < total) {
+        back = false;
+        if (alt + 1 < total) {
+          if (csp == kChoicePoints) return kOverflow;
+          mem.set_choice(csp++, make_uint2(n | (sp << 16), (uint32_t)i | ((alt + 1) << 8) | (top << 16) | (f << 24)));
+          needed = top;
+        }
+        if (alt < k) {
+          bool consumes;
+          if (calls) {
+            const uint32_t m = run_frames(word0);
+            if (top + m > kArenaFrames) return kOverflow;
+            for (uint32_t j = 0; j < m; ++j) {
+              mem.set_frame(top, ((T.alt(run_frames_at(word0) + (j >> 1)) >> ((j & 1u) * 16u)) & 0xFFFFu) | (sp << 16));
+              sp = top++;
+            }
+            n = (uint32_t)__builtin_amdgcn_readlane((int)word, 1);
+            consumes = (word0 & kRunConsumesD) != 0u;
+          } else {
+            const uint32_t e = !pooled ? (kMoveTagD << 16) | dst : alt < 63u ? (uint32_t)__builtin_amdgcn_readlane((int)word, (int)(1u + alt)) : T.alt(base + 1u + alt);
+            const uint32_t tag = e >> 16;
+            n = e & 0xFFFFu;
+            consumes = tag == kMoveTagD;
+            if (!consumes && tag != kTailTagD) {
+              if (top == kArenaFrames) return kOverflow;
+              mem.set_frame(top, tag | (sp << 16));
+              sp = top++;
+            }
+          }
+          f = consumes ? 1u : 0u;
+          i += consumes ? 1 : 0;
+        } else if (sp < kLiveBase) {   // return into a frame pushed during this walk
+          const uint32_t fr = mem.frame(sp), old = sp;
+          n = fr & 0xFFFFu;
+          sp = fr >> 16;
+          if (needed <= old) top = old;
+        } else {                       // return into a live frame
+          n = live[sp - kLiveBase - 1u];
+          --sp;
+        }
+        alt = 0;
+      }
+    }
+    if (back) {  // to the most recent pending alternative
+      if (csp == 0) break;
+      const uint2 ch = mem.choice(--csp);
+      n = ch.x & 0xFFFFu;
+      sp = ch.x >> 16;
+      i = (int)(ch.y & 0xFFu);
+      alt = (ch.y >> 8) & 0xFFu;
+      top = (ch.y >> 16) & 0xFFu;
+      f = (ch.y >> 24) & 1u;
+      needed = csp ? (mem.choice(csp - 1).y >> 16) & 0xFFu : 0u;
+    }
+  }
+  return kReject;
+}
+// the order of candidates: element by element from the bottom, the shorter first (the host's order of stacks)
+__device__ __forceinline__ int compare_candidates(const AcceptShared& sm, uint32_t i, uint32_t j) {
+  const uint32_t si = sm.from[i] & 0xFFu, sj = sm.from[j] & 0xFFu, di = sm.depth(i), dj = sm.depth(j);
+  uint32_t k = min(sm.kept(i), sm.kept(j));
+  if (si != sj) k = min(k, sm.common[si][sj]);
+  for (const uint32_t m = min(di, dj); k < m; ++k) {
+    const uint32_t a = sm.frame(i, k), b = sm.frame(j, k);
+    if (a != b) return a < b ? -1 : 1;
+  }
+  return di == dj ? 0 : (di < dj ? -1 : 1);
 }
 
 // Section 3.3 on the device: one workgroup per row moves the row's stacks on
-// by the row's token.  Lane s of the first wave walks the token from stack s
-// and writes out every stack it can end in; duplicates are removed, the rest
+// by the row's token.  A wave walks the token from one stack after the other
+// and notes every stack it can end in; duplicates are removed, the rest
 // is put in the host's order and packed as the next state of the row's ring,
-// in the layout the fill kernel reads (stack headers with their first-byte
-// list offsets; frames).  A row whose token is not
-// allowed, or whose new state does not fit the device limits, keeps its state
-// and gets an error code in `status`.
-__global__ __launch_bounds__(kAcceptThreads) void batch_accept_kernel(DevBatch bt, DevVocab voc,
+// in the layout the fill kernel reads (stack headers with their lists' segment
+// offsets; frames).  A row whose token is not allowed, or whose new state does
+// not fit the device limits, keeps its state and gets an error code in `status`.
+// Bound by latency: a row is one workgroup, and what it does is one chain - state,
+// walk, order, contexts, keys, offsets.  So everything that does not depend on
+// the walk is fetched at once in front of it (frames and tables into LDS), and
+// whatever concerns many frames is done by many threads.  In-kernel clocks, mean
+// of 128 schema rows: 2.3 us until state and tables are there, walk 1.7, order
+// and contexts 1.4, keys 0.9, offsets and the rest 0.9; the launch lasts as long
+// as its slowest row (a twelve-byte token through several frames: 20 steps of
+// 0.6 us).  With one lane per stack, tables in global memory and stacks copied
+// by that lane: 17.9 us for the launch, now 16; one JSON row 8.2 us, now 6;
+// rows of the C/SQL-like grammar, 90 frames deep, 46 us in the mean, now 10.
+__global__ __launch_bounds__(kAcceptThreads) void batch_accept_kernel(DevBatch bt, DevVocab voc, uint32_t lds_budget,
                                                                       const int32_t* __restrict__ tokens) {
-  __shared__ uint16_t cand[kBatchMaxCandidates * kBatchMaxDepth];
-  __shared__ uint32_t cdepth[kBatchMaxCandidates];
-  __shared__ uint32_t order[kBatchMaxCandidates];  // rank among the distinct stacks, or kNoKey for a duplicate
-  __shared__ uint32_t foff[kBatchMaxStacks + 1];
-  __shared__ uint32_t slot_of[kBatchMaxStacks];    // candidate index per rank
-  __shared__ uint32_t keys[kBatchMaxStacks][kStackLists];  // the three lists of every new stack
-  __shared__ uint32_t cidx[kBatchMaxStacks][kCtxLevels];   // which context of its rule the frame above each level sits on
-  __shared__ uint32_t drops[kBatchMaxStacks];
-  __shared__ uint32_t ccount, coverflow, n_new, can_end, bad_context, not_final;
+  extern __shared__ __align__(16) unsigned char smem[];
+  __shared__ AcceptShared sm;
   const uint32_t tid = threadIdx.x;
   const int32_t b = blockIdx.x;
-  // what the row needs is fetched before anything is decided: one round trip for the token id and the slot,
-  // one for the token's bytes and the state's size (a branch in between would make each of them wait)
+  // what the row needs is fetched before anything is decided (a branch in between would make each round wait)
   const int32_t tok = tokens[b];
   const int32_t head = bt.head[b];
   const DevCache& dc = bt.cache[b];
+  // (of a large grammar only the first headers: its literals are walked through a few lines of the others)
+  const DevTables tab = staged_for(dc.tab, (int32_t)min(lds_budget, dc.tab.off_hdr + kAcceptHeaders * 8u));
   const int32_t first_stop = voc.n_stop > 0 ? voc.stop_ids[0] : -1;
   const uint4 tk = voc.tok_by_id[tok >= 0 && tok < voc.V ? tok : 0];
-  const SlotMeta cur = bt.meta[(size_t)b * bt.H + head];
-  if (tok < 0) return;  // this row is left alone (its status too)
-  const uint32_t n_off = (uint32_t)bt.n_seg + 1u;
   const uint32_t hdr_stride = stack_hdr_stride(bt.n_seg);
-  const int32_t next = (head + 1) % bt.H;
-  const uint32_t sb = ((uint32_t)b * bt.H + next) * kBatchMaxStacks;
-  const uint32_t fb = ((uint32_t)b * bt.H + next) * kBatchRowFrames;
+  const uint32_t at = (uint32_t)b * bt.H + head;
+  const SlotMeta cur = bt.meta[at];
+  if (tok < 0) return;  // this row is left alone (its status too)
+  {
+    uint4 h = make_uint4(0u, 0u, 0u, 0u);
+    if (tid < kBatchMaxStacks) h = *reinterpret_cast<const uint4*>(bt.hdrs + (size_t)(at * kBatchMaxStacks + tid) * hdr_stride);
+    const uint32_t* frames = reinterpret_cast<const uint32_t*>(bt.frames + (size_t)at * kBatchRowFrames);
+    const uint32_t two = frames[tid];  // (most rows have fewer frames than this brings)
+    stage_tables(tab, smem, kAcceptThreads);
+    reinterpret_cast<uint32_t*>(sm.live)[tid] = two;
+    for (uint32_t k = tid + kAcceptThreads; k * 2u < cur.n_frames; k += kAcceptThreads) reinterpret_cast<uint32_t*>(sm.live)[k] = frames[k];
+    static_assert(kStackHdrTop == 0 && kStackHdrDepth == 1 && kStackHdrFrames == 2, "a stack's scalars are one 16-byte load");
+    if (tid < kBatchMaxStacks) sm.stack[tid] = (h.z - at * kBatchRowFrames) | (h.y << 16);
+  }
+  if (tid == 0) { sm.count = 0u; sm.overflow = 0u; sm.duplicates = 0u; sm.not_final = 0u; sm.bad_context = 0u; }
+  if (tid < kBatchMaxCandidates) sm.less[tid] = 0u;
   int32_t status = 0;
   bool stop = false;
   if (tok >= voc.V) status = kErrBadArg;
@@ -1317,154 +1546,164 @@ __global__ __launch_bounds__(kAcceptThreads) void batch_accept_kernel(DevBatch b
     for (int32_t k = 1; k < voc.n_stop; ++k) stop = stop || voc.stop_ids[k] == tok;
     if (stop && !(cur.flags & 1u)) status = kErrTokenRejected;
   }
+  int len = (int)(tk.w >> 24);
+  if (status == 0 && !stop && len == 0) status = kErrTokenRejected;
   if (status != 0) {
     if (tid == 0) bt.status[b] = status;
     return;
   }
-  if (tid == 0) { ccount = 0u; coverflow = 0u; n_new = 0u; can_end = 0u; bad_context = 0u; not_final = 0u; }
   __syncthreads();
-  DevTables tab = dc.tab;
-  tab.lds_end = tab.stage_bytes = tab.n_near = 0u;  // the walks read the tables where they are
-  const LdsTab T(tab, nullptr);
+  const uint32_t n_off = (uint32_t)bt.n_seg + 1u;
+  const int32_t next = (head + 1) % bt.H;
+  const uint32_t sb = ((uint32_t)b * bt.H + next) * kBatchMaxStacks;
+  const uint32_t fb = ((uint32_t)b * bt.H + next) * kBatchRowFrames;
+  uint32_t ns = 0u, n_frames = 0u, can_end = 0u;
+  const LdsTab T(tab, smem);
   if (!stop) {
-    int len = (int)(tk.w >> 24);
-    const uint8_t* ext = voc.bytes;
-    if (len >= 15) {
-      ext = voc.bytes + voc.off_by_id[tok];
-      if (len == 255) len = (int)(voc.off_by_id[tok + 1] - voc.off_by_id[tok]);
+    const uint32_t wave = uniform(tid >> 6), lane = tid & 63u;
+    {
+      const uint8_t* ext = voc.bytes;
+      if (len >= 15) {
+        ext = voc.bytes + voc.off_by_id[tok];
+        if (len == 255) len = (int)(voc.off_by_id[tok + 1] - voc.off_by_id[tok]);
+      }
+      const LdsTabT<false, true> U(tab, smem);
+      const LdsTabT<true, true> S(tab, smem);
+      WaveMem mem{(XGM_LDS uint32_t*)sm.mem[wave], (XGM_LDS uint32_t*)sm.mem[wave] + kArenaFrames};
+      for (uint32_t st = wave; st < cur.n_stacks; st += kAcceptThreads / 64) {
+        const uint32_t where = uniform(sm.stack[st]), depth = where >> 16;
+        const UniformFrames live{(const XGM_LDS uint16_t*)sm.live + (where & 0xFFFFu)};
+        int res;
+        if (small_sections_staged(tab)) {
+          const NoteStacks<LdsTabT<true, true>> note{&S, &sm, st};
+          res = walk_wave(S, mem, tk, ext, len, live[depth - 1u], live, depth, note);
+        } else {  // (a grammar whose tables are too large)
+          const NoteStacks<LdsTabT<false, true>> note{&U, &sm, st};
+          res = walk_token_in<false, true>(mem, U, tk, ext, len, live[depth - 1u], live, depth, (uint32_t*)nullptr, 0u, 0, (uint32_t*)nullptr, note);
+        }
+        if (res == kOverflow) sm.overflow = 1u;
+      }
     }
-    if (len == 0) {
-      if (tid == 0) bt.status[b] = kErrTokenRejected;
-      return;
-    }
-    if (tid < cur.n_stacks) {
-      const uint32_t* h = bt.hdrs + (size_t)(((uint32_t)b * bt.H + head) * kBatchMaxStacks + tid) * hdr_stride;
-      const uint16_t* fr = bt.frames + h[kStackHdrFrames];
-      LdsStackSink sink{cand, cdepth, &ccount, &coverflow, kBatchMaxCandidates, kBatchMaxDepth};
-      const CollectStacks<LdsTab, LdsStackSink> collect{&T, &sink};
-      const int res = walk_token<false>(T, tk, ext, len, h[kStackHdrTop] & 0xFFFFu, fr, h[kStackHdrDepth], (uint32_t*)nullptr,
-                                        0u, 0, (uint32_t*)nullptr, collect);
-      if (res == kOverflow) coverflow = 1u;
-    }
+    // what the row's stacks have in common (the last waves get here first)
+    if (cur.n_stacks > 1u)
+      for (uint32_t p = kAcceptThreads / 64 - 1u - wave; p < cur.n_stacks * cur.n_stacks; p += kAcceptThreads / 64) {
+        const uint32_t x = p / cur.n_stacks, y = p % cur.n_stacks;
+        if (x >= y) continue;
+        const uint32_t sx = sm.stack[x], sy = sm.stack[y], m = min(sx >> 16, sy >> 16);
+        uint32_t same = m;
+        for (uint32_t k0 = 0; k0 < m; k0 += 64u) {
+          const uint32_t k = k0 + lane;
+          const unsigned long long differ = __ballot(k < m && sm.live[(sx & 0xFFFFu) + k] != sm.live[(sy & 0xFFFFu) + k]);
+          if (differ) { same = k0 + (uint32_t)__ffsll((long long)differ) - 1u; break; }
+        }
+        if (lane == 0u) sm.common[x][y] = sm.common[y][x] = same;
+      }
     __syncthreads();
-    if (coverflow || ccount > kBatchMaxCandidates) status = kErrTooLarge;
-    else if (ccount == 0u) status = kErrTokenRejected;
+    const uint32_t nc = sm.count;
+    if (sm.overflow) status = kErrTooLarge;
+    else if (nc == 0u) status = kErrTokenRejected;
     if (status != 0) {
       if (tid == 0) bt.status[b] = status;
       return;
     }
-    const uint32_t nc = ccount;
-    // duplicates out, the rest in order
-    if (tid < nc) {
-      bool dup = false;
-      for (uint32_t j = 0; j < tid; ++j)
-        dup = dup || compare_stacks(cand + j * kBatchMaxDepth, cdepth[j], cand + tid * kBatchMaxDepth, cdepth[tid]) == 0;
-      order[tid] = dup ? kNoKey : 0u;
-      if (!dup) atomicAdd(&n_new, 1u);
+    // duplicates out, the rest in order: all pairs at once
+    if (nc > 1u) {
+      for (uint32_t p = tid; p < nc * nc; p += kAcceptThreads) {
+        const uint32_t i = p / nc, j = p % nc;
+        if (j >= i) continue;
+        const int c = compare_candidates(sm, j, i);
+        if (c == 0) atomicOr(&sm.duplicates, 1u << i);
+        else if (c < 0) atomicOr(&sm.less[i], 1u << j);
+        else atomicOr(&sm.less[j], 1u << i);
+      }
+      __syncthreads();
     }
-    __syncthreads();
-    uint32_t before = 0u;
-    if (tid < nc && order[tid] != kNoKey)
-      for (uint32_t j = 0; j < nc; ++j)
-        if (j != tid && order[j] != kNoKey &&
-            compare_stacks(cand + j * kBatchMaxDepth, cdepth[j], cand + tid * kBatchMaxDepth, cdepth[tid]) < 0)
-          ++before;
-    __syncthreads();
-    if (tid < nc && order[tid] != kNoKey) order[tid] = before;
-    __syncthreads();
-    if (n_new > kBatchMaxStacks) {
+    const uint32_t dup = sm.duplicates;
+    ns = nc - (uint32_t)__popc(dup);
+    if (ns > kBatchMaxStacks) {
       if (tid == 0) bt.status[b] = kErrTooManyStacks;
       return;
     }
-    if (tid < nc && order[tid] != kNoKey) slot_of[order[tid]] = tid;
+    if (tid < nc && !((dup >> tid) & 1u)) sm.slot_of[__popc(sm.less[tid] & ~dup)] = tid;
     __syncthreads();
-    if (tid == 0) {
-      uint32_t run = 0;
-      for (uint32_t r = 0; r < n_new; ++r) { foff[r] = run; run += cdepth[slot_of[r]]; }
-      foff[n_new] = run;
-    }
-    __syncthreads();
-    const uint32_t ns = n_new;
-    // frames
-    for (uint32_t r = 0; r < ns; ++r) {
-      const uint32_t ci = slot_of[r], d = cdepth[ci];
-      for (uint32_t k = tid; k < d; k += kAcceptThreads) bt.frames[fb + foff[r] + k] = cand[ci * kBatchMaxDepth + k];
+    if (tid <= ns) {
+      uint32_t run = 0u;
+      for (uint32_t r = 0; r < tid; ++r) run += sm.depth(sm.slot_of[r]);
+      sm.first[tid] = run;
     }
     // where the levels begin in every stack, and which context of its rule the frame above each of them sits on (one
     // thread per stack and level)
-    if (tid < ns * (uint32_t)kCtxLevels) {
-      const uint32_t r = tid / (uint32_t)kCtxLevels, l = tid % (uint32_t)kCtxLevels + 1u;
-      const uint32_t ci = slot_of[r], d = cdepth[ci];
-      const uint16_t* st = cand + ci * kBatchMaxDepth;
+    if (tid >= 64u && tid < 64u + ns * (uint32_t)kCtxLevels) {
+      const uint32_t r = (tid - 64u) / (uint32_t)kCtxLevels, l = (tid - 64u) % (uint32_t)kCtxLevels + 1u;
+      const uint32_t ci = sm.slot_of[r], d = sm.depth(ci);
       uint32_t idx = kNoKey;
-      const uint32_t dr = stack_drops(d, [&](uint32_t k) { return (T.header(st[d - 1u - k]).y >> kHdrChainShift) & kHdrChainMask; });
-      if (l == 1u) drops[r] = dr;
-      const uint32_t at = stack_drop(dr, l);
-      if (at < d) {
-        const uint32_t rule = T.header(st[d - at]).y >> 16, below = st[d - 1u - at];
+      const uint32_t dr = stack_drops(d, [&](uint32_t k) { return (T.header(sm.frame(ci, d - 1u - k)).y >> kHdrChainShift) & kHdrChainMask; });
+      if (l == 1u) sm.drops[r] = dr;
+      const uint32_t from = stack_drop(dr, l);
+      if (from < d) {
+        const uint32_t rule = T.header(sm.frame(ci, d - from)).y >> 16, below = sm.frame(ci, d - 1u - from);
         for (uint32_t k = dc.node_ctx_off[below]; k < dc.node_ctx_off[below + 1u]; ++k) {
           const uint32_t x = dc.node_ctx[k];
           if ((x >> 16) == rule) idx = x & 0xFFFFu;
         }
-        if (idx == kNoKey) bad_context = 1u;
+        if (idx == kNoKey) sm.bad_context = 1u;
       }
-      cidx[r][l - 1u] = idx;
-    }
-    // whether some stack can end the text: every frame of it may end its rule
-    for (uint32_t item = tid; item < ns * kBatchMaxDepth; item += kAcceptThreads) {
-      const uint32_t r = item / kBatchMaxDepth, k = item % kBatchMaxDepth;
-      const uint32_t ci = slot_of[r];
-      if (k < cdepth[ci] && !T.is_final(cand[ci * kBatchMaxDepth + k])) atomicOr(&not_final, 1u << r);
+      sm.cidx[r][l - 1u] = idx;
     }
     __syncthreads();
-    if (tid == 0 && (not_final & ((1u << ns) - 1u)) != ((1u << ns) - 1u)) can_end = 1u;
-    // headers: scalars, the keys of the stack's lists
+    n_frames = sm.first[ns];
+    // the keys: the top node's own list, then one per level that the stack reaches and the cache keeps
     if (tid < ns) {
-      const uint32_t ci = slot_of[tid], d = cdepth[ci];
-      const uint16_t* st = cand + ci * kBatchMaxDepth;
+      const uint32_t ci = sm.slot_of[tid], d = sm.depth(ci);
       uint32_t* h = bt.hdrs + (size_t)(sb + tid) * hdr_stride;
-      const uint32_t top = st[d - 1];
-      h[kStackHdrTop] = top | ((uint32_t)dc.acc_row[top] << 16);
-      h[kStackHdrDepth] = d;
-      h[kStackHdrFrames] = fb + foff[tid];
-      h[kStackHdrDrops] = drops[tid];
-      // the keys: the top node's own list, then one per frame below that a kept level reaches
-      keys[tid][0] = top;
+      const uint32_t top = sm.frame(ci, d - 1u);
+      sm.keys[tid][0] = top;
       uint32_t local = top, key0 = (uint32_t)dc.n_nodes;
       bool more = true;
 #pragma unroll
       for (uint32_t l = 1; l <= (uint32_t)kCtxLevels; ++l) {
         uint32_t key = kNoKey;
-        if (more && cidx[tid][l - 1u] != kNoKey && dc.k_base[l - 1u] != nullptr) {
+        if (more && sm.cidx[tid][l - 1u] != kNoKey && dc.k_base[l - 1u] != nullptr) {
           const uint32_t kb = dc.k_base[l - 1u][local];
           if (kb != kNoKey) {
-            local = kb + cidx[tid][l - 1u];
+            local = kb + sm.cidx[tid][l - 1u];
             key = key0 + local;
           }
         }
         more = key != kNoKey;
-        keys[tid][l] = key;
+        sm.keys[tid][l] = key;
         key0 += dc.n_k[l - 1u];
+      }
+      *reinterpret_cast<uint4*>(h) = make_uint4(top | ((uint32_t)dc.acc_row[top] << 16), d, fb + sm.first[tid], sm.drops[tid]);
+    } else if (tid >= 64u) {
+      // frames, and whether some stack can end the text: every frame of it may end its rule
+      for (uint32_t item = tid - 64u; item < ns * kBatchMaxDepth; item += kAcceptThreads - 64) {
+        const uint32_t r = item / kBatchMaxDepth, k = item % kBatchMaxDepth, ci = sm.slot_of[r];
+        if (k < sm.depth(ci)) {
+          const uint32_t n = sm.frame(ci, k);
+          bt.frames[fb + sm.first[r] + k] = (uint16_t)n;
+          if (!T.is_final(n)) atomicOr(&sm.not_final, 1u << r);
+        }
       }
     }
     __syncthreads();
-    if (bad_context) {  // a frame sits on a node that is no context of its rule: never the case for stacks the walk makes
+    can_end = (sm.not_final & ((1u << ns) - 1u)) != ((1u << ns) - 1u) ? 1u : 0u;
+    if (sm.bad_context) {  // a frame sits on a node that is no context of its rule: never the case for stacks the walk makes
       if (tid == 0) bt.status[b] = kErrInternal;
       return;
     }
     // headers: where the lists' segments start
     for (uint32_t item = tid; item < ns * kStackLists * n_off; item += kAcceptThreads) {
       const uint32_t r = item / (kStackLists * n_off), sgm = item / kStackLists % n_off, l = item % kStackLists;
-      const uint32_t key = keys[r][l];
+      const uint32_t key = sm.keys[r][l];
       bt.hdrs[(size_t)(sb + r) * hdr_stride + stack_hdr_off(sgm, l)] =
           key == kNoKey ? 0u : dc.key_off[(size_t)key * (uint32_t)bt.n_seg + sgm];
     }
-    __syncthreads();
   }
   if (tid == 0) {
     SlotMeta m;
-    m.n_stacks = stop ? 0u : n_new;
-    m.n_frames = stop ? 0u : foff[n_new];
+    m.n_stacks = ns;
+    m.n_frames = n_frames;
     m.flags = stop ? 3u : can_end;
     m.pad = 0u;
     bt.meta[(size_t)b * bt.H + next] = m;
@@ -1812,7 +2051,7 @@ void launch_lds_lookups(int32_t n_blocks, uint32_t hops, uint32_t* sink, hipStre
 }
 
 void launch_batch_accept(const DevBatch& bt, const DevVocab& voc, const int32_t* d_tokens, hipStream_t stream) {
-  hipLaunchKernelGGL(batch_accept_kernel, dim3(bt.B), dim3(kAcceptThreads), 0, stream, bt, voc, d_tokens);
+  hipLaunchKernelGGL(batch_accept_kernel, dim3(bt.B), dim3(kAcceptThreads), kAcceptLdsBudget, stream, bt, voc, (uint32_t)kAcceptLdsBudget, d_tokens);
 }
 
 void launch_batch_fork(const DevBatch& bt, const int32_t* d_src_rows, hipStream_t stream) {

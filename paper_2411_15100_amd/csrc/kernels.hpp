@@ -62,8 +62,12 @@ struct TabView {
 constexpr int32_t kClassifyLdsBudget = 76 * 1024;
 constexpr int32_t kContextLdsBudget = 68 * 1024;  // the list kernels keep 8 KB of counters beside the tables
 constexpr int32_t kFillLdsBudget = 31 * 1024;     // of the fill kernel that walks (it runs four workgroups per compute unit)
+constexpr int32_t kAcceptLdsBudget = 64 * 1024;   // (a row is one workgroup: there is room for one or two per compute unit)
 // The staging split for a kernel that has `budget` bytes of LDS for the tables:
 // as many whole sections as fit, then as many headers as fit.
+#if defined(__HIPCC__) || defined(__HIP__)
+__host__ __device__
+#endif
 inline DevTables staged_for(DevTables t, int32_t budget) {
   const uint32_t ends[5] = {256u, t.off_targets, t.off_follow, t.off_alts, t.off_hdr};  // section ends in image order
   t.lds_end = t.stage_bytes = t.n_near = 0;

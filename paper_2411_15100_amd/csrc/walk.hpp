@@ -28,16 +28,16 @@ constexpr uint32_t kLiveBase = 0x8000;  // stack handles >= this refer to the re
 // Table access for the walk: at node n on byte c, how many move / call
 // alternatives are there (k), which (a single packed one, or k entries in the
 // alternatives pool from `base`; a run of calls counts as one and has its first
-// word in `run`), may the rule end at n (fin), and can c come right after an
-// instance of n's rule at all (after).
+// word in `run`), may the rule end at n (fin), and n's rule (for `follows`: can
+// c come right after an instance of it at all).
 struct CompactTab {
   TabView v;
   XGM_HD void lookup(uint32_t n, uint32_t c, uint32_t& k, uint32_t& single, uint32_t& base, uint32_t& run, bool& pooled,
-                     uint32_t& fin, uint32_t& after) const {
+                     uint32_t& fin, uint32_t& rule) const {
     const uint2 h = (n < (uint32_t)v.n_near) ? v.hdr_near[n] : v.hdr_far[n];
     k = 0; single = 0; base = 0; run = 0; pooled = false;
     fin = h.y & 1u;
-    after = (v.follow_rules[(h.y >> 16) * 8 + (c >> 5)] >> (c & 31)) & 1u;
+    rule = h.y >> 16;
     if (h.y & 2u) {
       const uint32_t si = v.shapes[(h.x & 0xFFFFu) * v.n_cls + v.cls[c]];
       if (si != 0xFFu) {
@@ -121,20 +121,27 @@ XGM_HD uint32_t token_byte(const uint4& tk, const uint8_t* ext, int i) { return 
 // called with every configuration (node, stack handle, arena, live frames) in
 // which the token can end, and the walk goes on to the next path; the result
 // is then kReject (or kOverflow).
+// `Mem` keeps the frames pushed by the walk (ret | parent handle << 16) and the
+// pending alternatives (x = node | sp << 16 ; y = i | alt << 8 | top << 16 | f << 24).
 struct FirstPathEnds {
   static constexpr bool kEnumerate = false;
-  template <class Live>
-  XGM_HD void operator()(uint32_t, uint32_t, const uint32_t*, const Live&) const {}
+  template <class Mem, class Live>
+  XGM_HD void operator()(uint32_t, uint32_t, const Mem&, const Live&) const {}
 };
-template <bool BUILD, bool PRUNE = !BUILD, class Tab, class Live, class End = FirstPathEnds>
-XGM_HD int walk_token(const Tab& T, const uint4 tk, const uint8_t* ext, const int len,
-                      const uint32_t start_node, const Live& live, const uint32_t depth,
-                      uint32_t* steps_out = nullptr, const uint32_t follow = 0u, const int i0 = 0,
-                      uint32_t* exits_out = nullptr, const End& at_end = End()) {
+struct PrivateMem {
+  uint32_t arena[kArenaFrames];
+  uint2 choices[kChoicePoints];
+  XGM_HD uint32_t frame(uint32_t k) const { return arena[k]; }
+  XGM_HD void set_frame(uint32_t k, uint32_t v) { arena[k] = v; }
+  XGM_HD uint2 choice(uint32_t k) const { return choices[k]; }
+  XGM_HD void set_choice(uint32_t k, uint2 v) { choices[k] = v; }
+};
+template <bool BUILD, bool PRUNE, class Mem, class Tab, class Live, class End>
+XGM_HD int walk_token_in(Mem& mem, const Tab& T, const uint4 tk, const uint8_t* ext, const int len,
+                         const uint32_t start_node, const Live& live, const uint32_t depth,
+                         uint32_t* steps_out, const uint32_t follow, const int i0, uint32_t* exits_out, const End& at_end) {
   if (len > kMaxTokenLen) return kOverflow;
   const TokenWords tw(tk);
-  uint32_t arena[kArenaFrames];  // ret | parent handle << 16
-  uint2 choice[kChoicePoints];   // x = node | sp << 16 ; y = i | alt << 8 | top << 16 | f << 24
   uint32_t n = start_node, sp = kLiveBase + depth - 1, f = 1, alt = 0, top = 0, csp = 0;
   uint32_t needed = 0;           // frames below this are needed by the most recent pending alternative
   int i = i0;
@@ -145,11 +152,11 @@ XGM_HD int walk_token(const Tab& T, const uint4 tk, const uint8_t* ext, const in
     if (i == len && !End::kEnumerate) return kAccept;
     if (steps >= kMaxSteps) return kOverflow;
     if (i == len) {
-      at_end(n, sp, arena, live);      // then on to the next path
+      at_end(n, sp, mem, live);      // then on to the next path
     } else {
-      uint32_t k, single, base, run, fin, after;
+      uint32_t k, single, base, run, fin, rule;
       bool pooled;
-      T.lookup(n, c, k, single, base, run, pooled, fin, after);
+      T.lookup(n, c, k, single, base, run, pooled, fin, rule);
       uint32_t can_pop = fin & f;
       if (sp == kLiveBase) {
         // The bottom frame may end here (nothing is known below it): noted at once instead of kept as a
@@ -162,7 +169,7 @@ XGM_HD int walk_token(const Tab& T, const uint4 tk, const uint8_t* ext, const in
         }
         can_pop = 0u;
       }
-      if (PRUNE) can_pop &= after;  // a return in front of a byte that can never follow the rule leads nowhere
+      if (PRUNE && can_pop) can_pop = T.follows(rule, c);  // (a return in front of a byte that can never follow the rule leads nowhere)
       const uint32_t total = k + can_pop;
       // nothing but a move along a byte edge (most steps inside a string, a number, a name): taken at once
       if (alt == 0u && total == 1u && k == 1u && !pooled) {
@@ -174,7 +181,7 @@ XGM_HD int walk_token(const Tab& T, const uint4 tk, const uint8_t* ext, const in
       if (alt < total) {
         if (alt + 1 < total) {
           if (csp == kChoicePoints) return kOverflow;
-          choice[csp++] = make_uint2(n | (sp << 16), (uint32_t)i | ((alt + 1) << 8) | (top << 16) | (f << 24));
+          mem.set_choice(csp++, make_uint2(n | (sp << 16), (uint32_t)i | ((alt + 1) << 8) | (top << 16) | (f << 24)));
           needed = top;
         }
         bool consumes = false;
@@ -183,7 +190,7 @@ XGM_HD int walk_token(const Tab& T, const uint4 tk, const uint8_t* ext, const in
             const uint32_t m = run_frames(run);
             if (top + m > kArenaFrames) return kOverflow;
             for (uint32_t j = 0; j < m; ++j) {
-              arena[top] = ((T.alt(run_frames_at(run) + (j >> 1)) >> ((j & 1u) * 16u)) & 0xFFFFu) | (sp << 16);
+              mem.set_frame(top, ((T.alt(run_frames_at(run) + (j >> 1)) >> ((j & 1u) * 16u)) & 0xFFFFu) | (sp << 16));
               sp = top++;
             }
             n = T.alt(base + 1);
@@ -197,7 +204,7 @@ XGM_HD int walk_token(const Tab& T, const uint4 tk, const uint8_t* ext, const in
             if (tag == kMoveTagD) consumes = true;
             else if (tag != kTailTagD) {  // (a tail call: enter the callee, it returns to our parent)
               if (top == kArenaFrames) return kOverflow;
-              arena[top] = tag | (sp << 16);
+              mem.set_frame(top, tag | (sp << 16));
               sp = top++;
             }
           }
@@ -206,7 +213,7 @@ XGM_HD int walk_token(const Tab& T, const uint4 tk, const uint8_t* ext, const in
             if (++i < len) c = token_byte(tw, ext, i);
           }
         } else if (sp < kLiveBase) {   // return into a frame pushed during this walk
-          const uint32_t fr = arena[sp], old = sp;
+          const uint32_t fr = mem.frame(sp), old = sp;
           n = fr & 0xFFFFu;
           sp = fr >> 16;
           // frames from `old` upwards are garbage unless a pending alternative still needs them
@@ -222,7 +229,7 @@ XGM_HD int walk_token(const Tab& T, const uint4 tk, const uint8_t* ext, const in
     }
     // back up to the most recent pending alternative
     if (csp == 0) break;
-    const uint2 ch = choice[--csp];
+    const uint2 ch = mem.choice(--csp);
     n = ch.x & 0xFFFFu;
     sp = ch.x >> 16;
     i = (int)(ch.y & 0xFFu);
@@ -230,10 +237,18 @@ XGM_HD int walk_token(const Tab& T, const uint4 tk, const uint8_t* ext, const in
     top = (ch.y >> 16) & 0xFFu;
     f = (ch.y >> 24) & 1u;
     c = token_byte(tw, ext, i);
-    needed = csp ? (choice[csp - 1].y >> 16) & 0xFFu : 0u;
+    needed = csp ? (mem.choice(csp - 1).y >> 16) & 0xFFu : 0u;
   }
   if (BUILD && left_frame) return (left_frame & 2u) ? kUncertain : kUncertainPlain;
   return kReject;
+}
+template <bool BUILD, bool PRUNE = !BUILD, class Tab, class Live, class End = FirstPathEnds>
+XGM_HD int walk_token(const Tab& T, const uint4 tk, const uint8_t* ext, const int len,
+                      const uint32_t start_node, const Live& live, const uint32_t depth,
+                      uint32_t* steps_out = nullptr, const uint32_t follow = 0u, const int i0 = 0,
+                      uint32_t* exits_out = nullptr, const End& at_end = End()) {
+  PrivateMem mem;
+  return walk_token_in<BUILD, PRUNE>(mem, T, tk, ext, len, start_node, live, depth, steps_out, follow, i0, exits_out, at_end);
 }
 
 // End policy that writes out the stack of every configuration a token can end
@@ -250,11 +265,11 @@ struct CollectStacks {
   static constexpr bool kEnumerate = true;
   const Tab* T;
   Sink* sink;
-  template <class Live>
-  XGM_HD void operator()(uint32_t n, uint32_t sp, const uint32_t* arena, const Live& live) const {
+  template <class Mem, class Live>
+  XGM_HD void operator()(uint32_t n, uint32_t sp, const Mem& mem, const Live& live) const {
     while (T->is_dead_end(n)) {
       if (sp < kLiveBase) {
-        const uint32_t fr = arena[sp];
+        const uint32_t fr = mem.frame(sp);
         n = fr & 0xFFFFu;
         sp = fr >> 16;
       } else {
@@ -265,7 +280,7 @@ struct CollectStacks {
       }
     }
     uint32_t depth = 1, h = sp;
-    for (; h < kLiveBase; h = arena[h] >> 16) ++depth;
+    for (; h < kLiveBase; h = mem.frame(h) >> 16) ++depth;
     const uint32_t d = h - kLiveBase;  // live frames kept
     depth += d;
     if (depth > sink->max_depth) { *sink->overflow = 1u; return; }
@@ -274,7 +289,7 @@ struct CollectStacks {
     auto* out = sink->frames + (size_t)idx * sink->max_depth;
     out[depth - 1] = (uint16_t)n;
     uint32_t k = depth - 1;
-    for (h = sp; h < kLiveBase; h = arena[h] >> 16) out[--k] = (uint16_t)(arena[h] & 0xFFFFu);
+    for (h = sp; h < kLiveBase; h = mem.frame(h) >> 16) out[--k] = (uint16_t)(mem.frame(h) & 0xFFFFu);
     for (uint32_t j = 0; j < d; ++j) out[j] = (uint16_t)live[j];
     sink->depth[idx] = depth;
   }
