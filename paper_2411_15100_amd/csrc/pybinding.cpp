@@ -76,25 +76,28 @@ bool arguments(const char* fn, PyObject* const* args, Py_ssize_t n, PyObject* kw
     if (!out[k]) { PyErr_Format(PyExc_TypeError, "%s() missing required argument '%s'", fn, names[k]); return false; }
   return true;
 }
-bool integer(PyObject* o, int64_t* out) {
-  if (!o || o == Py_None) { *out = 0; return true; }
-  if (PyLong_Check(o)) {
-    int over = 0;
-    *out = PyLong_AsLongLongAndOverflow(o, &over);
-    if (over == 0) return *out != -1 || !PyErr_Occurred();
-    *out = (int64_t)PyLong_AsUnsignedLongLongMask(o);
-    return !PyErr_Occurred();
-  }
-  PyObject* v = PyNumber_Long(o);
-  if (!v) return false;
-  *out = (int64_t)PyLong_AsUnsignedLongLongMask(v);
-  Py_DECREF(v);
-  return !PyErr_Occurred();
+bool low_bits(PyObject* o, int64_t* out) {
+  *out = (int64_t)PyLong_AsUnsignedLongLongMask(o);
+  return *out != -1 || !PyErr_Occurred();
 }
+bool converted(PyObject* v, int64_t* out) {  // (takes over v)
+  const bool ok = v && low_bits(v, out);
+  Py_XDECREF(v);
+  return ok;
+}
+// an address: an integer, or None (or absent) for null
+bool address(PyObject* o, int64_t* out) {
+  if (!o || o == Py_None) { *out = 0; return true; }
+  return PyLong_Check(o) ? low_bits(o, out) : converted(PyNumber_Index(o), out);
+}
+bool integer(PyObject* o, int64_t* out) { return PyLong_Check(o) ? low_bits(o, out) : converted(PyNumber_Index(o), out); }
+// a number, as int() takes it
+bool number(PyObject* o, int64_t* out) { return PyLong_Check(o) ? low_bits(o, out) : converted(PyNumber_Long(o), out); }
+// kinds[k]: 'a' for an address, 'n' for a number, 'i' for an integer
 template <int N>
-bool integers(PyObject* (&in)[N], int64_t (&out)[N], int from = 0) {
-  for (int k = from; k < N; ++k)
-    if (!integer(in[k], &out[k])) return false;
+bool values(PyObject* const* in, int64_t (&out)[N], const char (&kinds)[N + 1]) {
+  for (int k = 0; k < N; ++k)
+    if (!(kinds[k] == 'a' ? address(in[k], &out[k]) : kinds[k] == 'n' ? number(in[k], &out[k]) : integer(in[k], &out[k]))) return false;
   return true;
 }
 void* pointer(int64_t v) { return reinterpret_cast<void*>((uintptr_t)v); }
@@ -102,7 +105,7 @@ bool attribute(PyObject* self, PyObject* name, void** out) {
   PyObject* h = PyObject_GetAttr(self, name);
   if (!h) return false;
   int64_t v = 0;
-  const bool ok = integer(h, &v);
+  const bool ok = address(h, &v);
   Py_DECREF(h);
   *out = pointer(v);
   return ok;
@@ -114,7 +117,7 @@ PyObject* matcher_accept_token(PyObject* self, PyObject* const* args, Py_ssize_t
   PyObject* a[1];
   int64_t v[1];
   void* h;
-  if (!arguments("accept_token", args, n, kwnames, names, 1, a) || !integers(a, v) || !attribute(self, s_h, &h)) return nullptr;
+  if (!arguments("accept_token", args, n, kwnames, names, 1, a) || !values(a, v, "n") || !attribute(self, s_h, &h)) return nullptr;
   return result(api.matcher_accept_token(h, (int32_t)v[0]));
 }
 PyObject* matcher_accept_bytes(PyObject* self, PyObject* const* args, Py_ssize_t n, PyObject* kwnames) {
@@ -125,7 +128,12 @@ PyObject* matcher_accept_bytes(PyObject* self, PyObject* const* args, Py_ssize_t
   void* h;
   if (!arguments("accept_bytes", args, n, kwnames, names, 1, a) || PyBytes_AsStringAndSize(a[0], &bytes, &len) < 0 || !attribute(self, s_h, &h))
     return nullptr;
-  return result(api.matcher_accept_bytes(h, (const uint8_t*)bytes, (int32_t)len));
+  if (len <= 64) return result(api.matcher_accept_bytes(h, (const uint8_t*)bytes, (int32_t)len));
+  int rc;  // (a long text takes longer than letting other threads run)
+  Py_BEGIN_ALLOW_THREADS
+  rc = api.matcher_accept_bytes(h, (const uint8_t*)bytes, (int32_t)len);
+  Py_END_ALLOW_THREADS
+  return result(rc);
 }
 PyObject* matcher_reset(PyObject* self, PyObject*) {
   void* h;
@@ -138,7 +146,7 @@ PyObject* batch_step(PyObject* self, int (*step)(void*, const void*, void*), con
   PyObject* a[2];
   int64_t v[2];
   void* h;
-  if (!arguments(fn, args, n, kwnames, names, 1, a) || !integers(a, v) || !attribute(self, s_h, &h)) return nullptr;
+  if (!arguments(fn, args, n, kwnames, names, 1, a) || !values(a, v, "aa") || !attribute(self, s_h, &h)) return nullptr;
   int rc;
   Py_BEGIN_ALLOW_THREADS
   rc = step(h, pointer(v[0]), pointer(v[1]));
@@ -162,7 +170,7 @@ PyObject* batch_fill(PyObject* self, PyObject* const* args, Py_ssize_t n, PyObje
   PyObject* a[2];
   int64_t v[2];
   void* h;
-  if (!arguments("fill_next_token_bitmask", args, n, kwnames, names, 1, a) || !integers(a, v) || !attribute(self, s_h, &h)) return nullptr;
+  if (!arguments("fill_next_token_bitmask", args, n, kwnames, names, 1, a) || !values(a, v, "aa") || !attribute(self, s_h, &h)) return nullptr;
   int rc;
   Py_BEGIN_ALLOW_THREADS
   rc = api.batch_fill_next_token_bitmask(h, pointer(v[0]), pointer(v[1]));
@@ -174,7 +182,7 @@ PyObject* batch_fill_and_apply(PyObject* self, PyObject* const* args, Py_ssize_t
   PyObject* a[6];
   int64_t v[6];
   void* h;
-  if (!arguments("fill_and_apply", args, n, kwnames, names, 5, a) || !integers(a, v) || !attribute(self, s_h, &h)) return nullptr;
+  if (!arguments("fill_and_apply", args, n, kwnames, names, 5, a) || !values(a, v, "aannna") || !attribute(self, s_h, &h)) return nullptr;
   int rc;
   Py_BEGIN_ALLOW_THREADS
   rc = api.batch_fill_and_apply(h, pointer(v[0]), pointer(v[1]), (int)v[2], (int32_t)v[3], v[4], pointer(v[5]));
@@ -183,7 +191,8 @@ PyObject* batch_fill_and_apply(PyObject* self, PyObject* const* args, Py_ssize_t
 }
 
 // ---- functions over matchers
-// The handles of a MatcherBatch (prepared once) or of a sequence of matchers.
+// The handles of a MatcherBatch (prepared once) or of a sequence of matchers, which are kept alive for the call: other
+// threads run meanwhile, and a sequence may be the only one that has them.
 class Handles {
  public:
   bool get(PyObject* matchers) {
@@ -196,25 +205,29 @@ class Handles {
       data_ = (void**)p;
       return true;
     }
+    if (!PyErr_ExceptionMatches(PyExc_AttributeError)) return false;
     PyErr_Clear();
-    PyObject* seq = PySequence_Fast(matchers, "a sequence of matchers is wanted");
-    if (!seq) return false;
-    n_ = PySequence_Fast_GET_SIZE(seq);
+    kept_ = PySequence_Tuple(matchers);
+    if (!kept_) return false;
+    n_ = PyTuple_GET_SIZE(kept_);
     void** p = few_;
     if (n_ > kFew) p = own_ = (void**)PyMem_Malloc(sizeof(void*) * (size_t)n_);
     bool ok = p != nullptr;
     if (!ok) PyErr_NoMemory();
-    for (Py_ssize_t k = 0; ok && k < n_; ++k) ok = attribute(PySequence_Fast_GET_ITEM(seq, k), s_h, &p[k]);
-    Py_DECREF(seq);
+    for (Py_ssize_t k = 0; ok && k < n_; ++k) ok = attribute(PyTuple_GET_ITEM(kept_, k), s_h, &p[k]);
     data_ = p;
     return ok;
   }
-  ~Handles() { PyMem_Free(own_); }
+  ~Handles() {
+    PyMem_Free(own_);
+    Py_XDECREF(kept_);
+  }
   void* const* data() const { return data_; }
   int32_t size() const { return (int32_t)n_; }
 
  private:
   static constexpr Py_ssize_t kFew = 256;
+  PyObject* kept_ = nullptr;
   void* few_[kFew];
   void** own_ = nullptr;
   void** data_ = nullptr;
@@ -223,27 +236,25 @@ class Handles {
 // fill_next_token_bitmask(matchers, d_bitmask, stream, static)
 PyObject* fill(PyObject*, PyObject* const* args, Py_ssize_t n) {
   if (n != 4) return PyErr_Format(PyExc_TypeError, "fill takes 4 arguments");
-  int64_t bitmask, stream;
+  int64_t v[2];
   Handles h;
-  if (!h.get(args[0]) || !integer(args[1], &bitmask) || !integer(args[2], &stream)) return nullptr;
+  if (!h.get(args[0]) || !values(args + 1, v, "aa")) return nullptr;
   auto fn = args[3] == Py_True ? api.fill_next_token_bitmask_static : api.fill_next_token_bitmask;
   int rc;
   Py_BEGIN_ALLOW_THREADS
-  rc = fn(h.data(), h.size(), pointer(bitmask), pointer(stream));
+  rc = fn(h.data(), h.size(), pointer(v[0]), pointer(v[1]));
   Py_END_ALLOW_THREADS
   return result(rc);
 }
 // fill_and_apply(matchers, d_bitmask, d_logits, dtype, v_logits, row_stride, stream)
 PyObject* fill_and_apply(PyObject*, PyObject* const* args, Py_ssize_t n) {
   if (n != 7) return PyErr_Format(PyExc_TypeError, "fill_and_apply takes 7 arguments");
-  int64_t v[7];
+  int64_t v[6];
   Handles h;
-  if (!h.get(args[0])) return nullptr;
-  for (int k = 1; k < 7; ++k)
-    if (!integer(args[k], &v[k])) return nullptr;
+  if (!h.get(args[0]) || !values(args + 1, v, "aannna")) return nullptr;
   int rc;
   Py_BEGIN_ALLOW_THREADS
-  rc = api.fill_and_apply(h.data(), h.size(), pointer(v[1]), pointer(v[2]), (int)v[3], (int32_t)v[4], v[5], pointer(v[6]));
+  rc = api.fill_and_apply(h.data(), h.size(), pointer(v[0]), pointer(v[1]), (int)v[2], (int32_t)v[3], v[4], pointer(v[5]));
   Py_END_ALLOW_THREADS
   return result(rc);
 }
@@ -251,8 +262,7 @@ PyObject* fill_and_apply(PyObject*, PyObject* const* args, Py_ssize_t n) {
 PyObject* apply(PyObject*, PyObject* const* args, Py_ssize_t n) {
   if (n != 10) return PyErr_Format(PyExc_TypeError, "apply takes 10 arguments");
   int64_t v[10];
-  for (int k = 0; k < 10; ++k)
-    if (!integer(args[k], &v[k])) return nullptr;
+  if (!values(args, v, "aiiiiaiaia")) return nullptr;
   int rc;
   Py_BEGIN_ALLOW_THREADS
   rc = api.apply_token_bitmask_inplace(pointer(v[0]), (int)v[1], (int32_t)v[2], (int32_t)v[3], v[4], pointer(v[5]), (int32_t)v[6], pointer(v[7]),

@@ -512,3 +512,29 @@ def test_depth_first_accept_on_random_grammars():
                 if not moved:
                     break
     assert n_grammars > 100 and n_steps > 3000 and n_multi > 100, (n_grammars, n_steps, n_multi)
+
+
+def test_binding_refuses_what_is_no_number_and_keeps_a_sequence_alive():
+    """The calls that csrc/pybinding.cpp marshals take what ctypes and int() take, and no more."""
+    v = xgm.Vocab(np.frombuffer(b"123", dtype=np.uint8), np.arange(4, dtype=np.int64), [])
+    g = xgm.Grammar('root ::= [0-9]*', "root")
+    m = xgm.Matcher(grammar=g, vocab=v)
+    for wrong in (None, [], "x1"):
+        with pytest.raises((TypeError, ValueError)):
+            m.accept_token(wrong)
+    m.accept_token(np.int64(1))
+    m.accept_token(token_id=2)
+    m.accept_bytes(b"7" * 1000)
+    with pytest.raises(TypeError):
+        m.accept_bytes("7")
+    with pytest.raises(TypeError):
+        xgm.apply_token_bitmask_inplace(0, None, 1, 1, 1, 0, 1)
+    with pytest.raises(TypeError):
+        xgm.apply_token_bitmask_inplace(1.5, xgm.DTYPE_F32, 1, 1, 1, 0, 1)
+    with pytest.raises(TypeError):
+        xgm.fill_and_apply([m], 0, 0, xgm.DTYPE_F32, None, 1)
+    # matchers without a cache are refused by the library, also those that only the generator has
+    for matchers in ([m], (m,), (xgm.Matcher(grammar=g, vocab=v) for _ in range(300))):
+        with pytest.raises(xgm.XgmError) as e:
+            xgm.fill_next_token_bitmask(matchers, 64)
+        assert e.value.status == -1
