@@ -1795,45 +1795,61 @@ __global__ void batch_fork_commit_kernel(DevBatch bt, const int32_t* __restrict_
 // ---------------------------------------------------------------- kernel (c)
 constexpr int kApplyThreads = 256;
 
-// Section 2.1: logits of disallowed tokens become -inf.  One workgroup per
-// (segment of kSegTokens elements, row), as in the one-launch kernel, and with
-// its code (LogitsRange): a thread takes 16-byte groups (8 bf16/fp16 or 4 fp32
-// elements), the 64 groups of a wave are contiguous (1 KiB); the mask bits come
-// straight from the bitmask in global memory.  ESIZE = bytes per element.
+// Section 2.1: logits of disallowed tokens become -inf.  One workgroup per (segment of kSegTokens elements, row); a
+// wave takes 2048 elements of it, lane l the mask word of elements 32 l .. 32 l + 31.  Segments begin on 16 bytes, up
+// to a group less one element in front of a row that does not: the words are then put together from two words of the
+// mask, and elements outside the row count as allowed.  A stretch of 64 groups of 16 bytes with nothing allowed is one
+// streaming store per lane; any other is stored element by element, 64 elements at a time, under their mask bits, which
+// lie in the order of the lanes.  Bound by the stores: 128 rows x 151937 bf16 (no row but every eighth is aligned) with
+// three words of ten mixed take 9.6 us, with one of fifty 8.5; one element per thread, as such rows went before, took
+// 28.4.  Aligned rows of 151936: 8.8 and 7.3 us; with a loop over the disallowed elements of a lane's group, which runs as
+// often as the wave's busiest lane needs, 11.4 and 7.9.  16 x 100003: 3.6, before 4.3 (most of it the launch).
+// ESIZE = bytes per element.
 template <int ESIZE>
 __global__ __launch_bounds__(kApplyThreads) void apply_kernel(unsigned char* __restrict__ logits, int64_t row_stride,
                                                               const uint32_t* __restrict__ bitmask, int32_t W_mask,
                                                               int32_t V_logits, int32_t V_mask,
                                                               const int32_t* __restrict__ row_index, uint32_t neg_inf) {
-  const int32_t j = blockIdx.y, seg = blockIdx.x;
+  typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+  constexpr int kStretch = 64 * 16 / ESIZE, kStretchWords = kStretch / 32, kWaveWords = 64;
+  const int32_t j = blockIdx.y, lane = (int32_t)(threadIdx.x & 63u), wave = (int32_t)uniform(threadIdx.x >> 6);
   const int64_t lrow = row_index ? row_index[j] : j;
-  LogitsRange<ESIZE> r;
-  r.row = logits + (size_t)lrow * row_stride * ESIZE;
-  r.words = bitmask + (size_t)j * W_mask + (size_t)seg * kSegWords;
-  r.e_begin = seg * kSegTokens;
-  r.e_end = min(r.e_begin + kSegTokens, V_logits);
-  r.V = V_mask;
-  r.V_logits = V_logits;
-  r.neg_inf = neg_inf;
-  if (r.e_begin + kSegTokens <= min(V_mask, V_logits)) r.template whole_segment<kApplyThreads>(threadIdx.x);
-  else r.groups(threadIdx.x, kApplyThreads);
-}
-
-// any alignment, any stride: one element per thread
-template <int ESIZE>
-__global__ void apply_elementwise_kernel(unsigned char* __restrict__ logits, int64_t row_stride,
-                                         const uint32_t* __restrict__ bitmask, int32_t W_mask, int32_t V_logits,
-                                         int32_t V_mask, const int32_t* __restrict__ row_index, uint32_t neg_inf) {
-  const int32_t j = blockIdx.y;
-  const int64_t lrow = row_index ? row_index[j] : j;
-  const int32_t e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= V_logits) return;
-  bool allowed = false;
-  if (e < V_mask) allowed = (bitmask[(size_t)j * W_mask + (e >> 5)] >> (e & 31)) & 1u;
-  if (allowed) return;
-  unsigned char* p = logits + ((size_t)lrow * row_stride + e) * ESIZE;
-  if (ESIZE == 2) *reinterpret_cast<uint16_t*>(p) = (uint16_t)neg_inf;
-  else *reinterpret_cast<uint32_t*>(p) = neg_inf;
+  unsigned char* row = logits + (size_t)lrow * row_stride * ESIZE;
+  const uint32_t* words = bitmask + (size_t)j * W_mask;
+  const int32_t ahead = (int32_t)((uint32_t)reinterpret_cast<uintptr_t>(row) % 16u) / ESIZE;
+  const int32_t e_wave = (int32_t)blockIdx.x * kSegTokens + wave * kWaveWords * 32 - ahead;  // the wave's first element
+  if (e_wave >= V_logits) return;
+  const int32_t e = e_wave + lane * 32;  // the lane's first
+  const int32_t at = e >> 5;
+  const uint32_t lo = at >= 0 && at < W_mask ? words[at] : 0u;
+  const uint32_t hi = ahead != 0 && at + 1 < W_mask ? words[at + 1] : 0u;
+  uint32_t allowed = __builtin_amdgcn_alignbit(hi, lo, (uint32_t)e & 31u);
+  if (e + 32 > V_mask) allowed &= e < V_mask ? (1u << (V_mask - e)) - 1u : 0u;
+  if (e < 0) allowed |= (1u << -e) - 1u;
+  if (e + 32 > V_logits) allowed |= e < V_logits ? ~0u << (V_logits - e) : ~0u;
+  const unsigned long long none = __ballot(allowed == 0u), all = __ballot(allowed == ~0u);
+  const uint32_t fill = ESIZE == 2 ? (neg_inf | (neg_inf << 16)) : neg_inf;
+  const v4u val = {fill, fill, fill, fill};
+  unsigned char* const p = row + (ptrdiff_t)e_wave * ESIZE;
+#pragma unroll
+  for (int k = 0; k < kWaveWords / kStretchWords; ++k) {
+    constexpr unsigned long long kOnes = (1ull << kStretchWords) - 1ull;
+    if (((all >> (k * kStretchWords)) & kOnes) == kOnes) continue;
+    unsigned char* const q = p + k * 1024;
+    if (((none >> (k * kStretchWords)) & kOnes) == kOnes) {
+      __builtin_nontemporal_store(val, reinterpret_cast<v4u*>(q + lane * 16));
+    } else {
+#pragma unroll
+      for (int h = 0; h < kStretchWords / 2; ++h) {
+        const unsigned long long bits = (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)allowed, k * kStretchWords + 2 * h) |
+                                        ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)allowed, k * kStretchWords + 2 * h + 1) << 32);
+        if (!__builtin_amdgcn_inverse_ballot_w64(bits)) {
+          if (ESIZE == 2) reinterpret_cast<uint16_t*>(q)[h * 64 + lane] = (uint16_t)neg_inf;
+          else reinterpret_cast<uint32_t*>(q)[h * 64 + lane] = neg_inf;
+        }
+      }
+    }
+  }
 }
 
 // ------------------------------------------------------------ measurement aid
@@ -2068,25 +2084,12 @@ void launch_apply(void* logits, int elem_size, uint32_t neg_inf, int32_t V_logit
                   hipStream_t stream) {
   if (n_rows <= 0 || V_logits <= 0) return;
   const int32_t W_mask = (V_mask + 31) / 32;
-  const bool aligned = (reinterpret_cast<uintptr_t>(logits) % 16 == 0) && ((row_stride * elem_size) % 16 == 0);
   unsigned char* p = static_cast<unsigned char*>(logits);
-  if (aligned) {
-    dim3 grid((V_logits + kSegTokens - 1) / kSegTokens, n_rows);
-    if (elem_size == 2)
-      hipLaunchKernelGGL(apply_kernel<2>, grid, dim3(kApplyThreads), 0, stream, p, row_stride, bitmask, W_mask,
-                         V_logits, V_mask, row_index, neg_inf);
-    else
-      hipLaunchKernelGGL(apply_kernel<4>, grid, dim3(kApplyThreads), 0, stream, p, row_stride, bitmask, W_mask,
-                         V_logits, V_mask, row_index, neg_inf);
-  } else {
-    dim3 grid((V_logits + 255) / 256, n_rows);
-    if (elem_size == 2)
-      hipLaunchKernelGGL(apply_elementwise_kernel<2>, grid, dim3(256), 0, stream, p, row_stride, bitmask, W_mask,
-                         V_logits, V_mask, row_index, neg_inf);
-    else
-      hipLaunchKernelGGL(apply_elementwise_kernel<4>, grid, dim3(256), 0, stream, p, row_stride, bitmask, W_mask,
-                         V_logits, V_mask, row_index, neg_inf);
-  }
+  // (a row begins up to a group less one element behind 16 bytes)
+  const int32_t ahead = reinterpret_cast<uintptr_t>(logits) % 16 == 0 && row_stride * elem_size % 16 == 0 ? 0 : 16 / elem_size - 1;
+  const dim3 grid((V_logits + ahead + kSegTokens - 1) / kSegTokens, n_rows);
+  auto launch = elem_size == 2 ? apply_kernel<2> : apply_kernel<4>;
+  hipLaunchKernelGGL(launch, grid, dim3(kApplyThreads), 0, stream, p, row_stride, bitmask, W_mask, V_logits, V_mask, row_index, neg_inf);
 }
 
 }  // namespace xgm

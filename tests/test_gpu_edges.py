@@ -154,3 +154,31 @@ def test_walk_entries(xgm, wl, V):
         resident.fill_next_token_bitmask(d_mask.data_ptr(), _stream())
         assert np.array_equal(d_mask.cpu().numpy(), want[rows]), f"resident states, {len(rows)} rows"
     assert xgm.overflow_total() == before
+
+
+# Logits rows that begin anywhere: groups of 16 bytes in front of the row, behind it, and where the mask's words or a
+# workgroup's 8192 elements end; rows narrower and wider than the mask.
+@pytest.mark.parametrize("dtype_name", ["f32", "bf16"])
+@pytest.mark.parametrize("V,Vl", [(1, 1), (3, 9), (32, 32), (33, 31), (8184, 8184), (8185, 8191), (8192, 8192), (8200, 8193), (16384, 16389), (24577, 24570)])
+def test_apply_rows_that_begin_anywhere(xgm, dtype_name, V, Vl):
+    code, ninf, udt, view = {"f32": (xgm.DTYPE_F32, 0xFF800000, np.uint32, np.int32), "bf16": (xgm.DTYPE_BF16, 0xFF80, np.uint16, np.int16)}[dtype_name]
+    esize = np.dtype(udt).itemsize
+    rng = np.random.Generator(np.random.PCG64(V + Vl))
+    rows, total = 4, 6
+    allowed = rng.random((rows, V)) < np.array([[0.5], [0.001], [0.999], [0.03]])
+    d_mask = torch.from_numpy(oracle.pack_bitmask(allowed)).cuda()
+    index = rng.permutation(total)[:rows].astype(np.int32)
+    d_index = torch.from_numpy(index).cuda()
+    want = np.zeros((rows, Vl), dtype=bool)
+    want[:, :V] = allowed[:, :Vl] if Vl < V else allowed
+    for offset in range(16 // esize):
+        for stride in (Vl, Vl + 1, Vl + 6):
+            before = rng.integers(0, 2 ** (8 * esize), size=offset + total * stride + 16, dtype=np.uint64).astype(udt)
+            buf = torch.from_numpy(before.view(view)).cuda()
+            xgm.apply_token_bitmask_inplace(buf.data_ptr() + offset * esize, code, total, Vl, stride, d_mask.data_ptr(), V, d_index.data_ptr(), rows,
+                                            stream=_stream())
+            expect = before.copy()
+            for j, r in enumerate(index):
+                row = expect[offset + r * stride:offset + r * stride + Vl]
+                row[~want[j]] = ninf
+            assert np.array_equal(buf.cpu().numpy().view(udt), expect), (offset, stride)
