@@ -803,102 +803,55 @@ __global__ void patch_classes_kernel(DevVocab voc, const uint32_t* __restrict__ 
   }
 }
 
-// One 16-byte group of a logits row (section 2.1): `mk` holds the mask bits of
-// its EPT = 16 / ESIZE elements, e0 is the index of its first element.  All
-// allowed: nothing is touched.  None allowed: one 16-byte streaming store of the
-// -inf pattern.  Both kinds: every disallowed element is stored by itself.  The
-// logits are never read: a group that is fetched, blended and stored whole makes
-// its wave wait for the fetch, while stores are issued and forgotten (measured
-// on the serving masks, where four rows in ten allow nearly every token and the
-// others nearly none: 15.6 -> 13.5 us for the one-launch step and 7.9 -> 7.5 us
-// for the stand-alone kernel against blending; merging neighbouring elements
-// into 4-byte stores, or streaming stores for single elements, were slower).
+// What a wave stores of 2048 elements of a logits row (section 2.1): -inf where the element's bit is not set.  Lane l
+// has the bits of elements 32 l .. 32 l + 31; `p` is the address of element 0, on 16 bytes.  A stretch of 64 groups of
+// 16 bytes with nothing allowed is one streaming store per lane (the lines are written whole and not read again here,
+// so they need not stay in the caches); any other is stored element by element, 64 at a time, under their bits, which
+// lie in the order of the lanes.  The logits are never read: a group that is fetched, blended and stored whole makes
+// its wave wait for the fetch, while stores are issued and forgotten.
+// Where no lane has more than kApplyFew disallowed elements each stores its own, one after the other (inside a string
+// nearly every token is allowed: serving masks have 3 to 7 in the fullest word of such a wave).  One-launch step of 128
+// rows, 8.27 us with 8 or 12 of them, 8.9 with 4 and 9.1 with 3, where most of these waves go the other way; a loop over
+// the disallowed elements of a lane's group of 16 bytes, for all masks, took 8.81.
+constexpr int32_t kApplyWaveWords = 64, kApplyWaveElems = kApplyWaveWords * 32;
+constexpr int kApplyFew = 8;
 template <int ESIZE>
-__device__ __forceinline__ void apply_group(unsigned char* p, uint32_t mk, int32_t e0, int32_t V_logits, uint32_t neg_inf) {
-  constexpr int EPT = 16 / ESIZE;
-  constexpr uint32_t kAll = (1u << EPT) - 1u;
-  if (mk == kAll) return;
-  if (mk == 0u && e0 + EPT <= V_logits) {
-    // a streaming store: the line is written whole and not read again here, so it need not stay in the caches
-    typedef uint32_t v4u __attribute__((ext_vector_type(4)));
-    const uint32_t w = ESIZE == 2 ? (neg_inf | (neg_inf << 16)) : neg_inf;
-    const v4u val = {w, w, w, w};
-    __builtin_nontemporal_store(val, reinterpret_cast<v4u*>(p));
-  } else {
+__device__ __forceinline__ void apply_wave(unsigned char* p, uint32_t allowed, uint32_t neg_inf) {
+  typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+  constexpr int kStretchWords = 64 * 16 / ESIZE / 32;
+  constexpr unsigned long long kOnes = (1ull << kStretchWords) - 1ull;
+  const uint32_t lane = threadIdx.x & 63u;
+  const unsigned long long none = __ballot(allowed == 0u), all = __ballot(allowed == ~0u);
+  const uint32_t fill = ESIZE == 2 ? (neg_inf | (neg_inf << 16)) : neg_inf;
+  const v4u val = {fill, fill, fill, fill};
+  if (__ballot(__popc(~allowed) > kApplyFew) == 0ull) {
+    unsigned char* const q = p + lane * (32u * ESIZE);
+    for (uint32_t x = ~allowed; x; x &= x - 1u) {
+      const uint32_t h = (uint32_t)__ffs((int)x) - 1u;
+      if (ESIZE == 2) reinterpret_cast<uint16_t*>(q)[h] = (uint16_t)neg_inf;
+      else reinterpret_cast<uint32_t*>(q)[h] = neg_inf;
+    }
+    return;
+  }
 #pragma unroll
-    for (int h = 0; h < EPT; ++h)
-      if (e0 + h < V_logits && !((mk >> h) & 1u)) {
-        if (ESIZE == 2) reinterpret_cast<uint16_t*>(p)[h] = (uint16_t)neg_inf;
-        else reinterpret_cast<uint32_t*>(p)[h] = neg_inf;
+  for (int k = 0; k < kApplyWaveWords / kStretchWords; ++k) {
+    if (((all >> (k * kStretchWords)) & kOnes) == kOnes) continue;
+    unsigned char* const q = p + k * 1024;
+    if (((none >> (k * kStretchWords)) & kOnes) == kOnes) {
+      __builtin_nontemporal_store(val, reinterpret_cast<v4u*>(q + lane * 16u));
+    } else {
+#pragma unroll
+      for (int h = 0; h < kStretchWords / 2; ++h) {
+        const unsigned long long bits = (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)allowed, k * kStretchWords + 2 * h) |
+                                        ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)allowed, k * kStretchWords + 2 * h + 1) << 32);
+        if (!__builtin_amdgcn_inverse_ballot_w64(bits)) {
+          if (ESIZE == 2) reinterpret_cast<uint16_t*>(q)[h * 64 + lane] = (uint16_t)neg_inf;
+          else reinterpret_cast<uint32_t*>(q)[h * 64 + lane] = neg_inf;
+        }
       }
+    }
   }
 }
-
-// The logits of one workgroup of the fused kernel: its request's row, the
-// elements [e_begin, e_end) that its mask words in LDS cover (section 2.1).
-// APPLY = bytes per logit; 0 = the kernel leaves the logits alone.
-template <int APPLY>
-struct LogitsRange {
-  unsigned char* row;
-  const uint32_t* words;  // the workgroup's mask words; bit 0 of words[0] is element e_begin
-  int32_t e_begin, e_end, V, V_logits;
-  uint32_t neg_inf;
-  // thread t of nt: the range's groups t, t + nt, ...
-  __device__ __forceinline__ void groups(uint32_t t, uint32_t nt) const {
-    if constexpr (APPLY != 0) {
-      constexpr int EPT = 16 / APPLY;
-      constexpr uint32_t kAll = (1u << EPT) - 1u;
-      for (int32_t e0 = e_begin + (int32_t)t * EPT; e0 < e_end; e0 += (int32_t)nt * EPT) {
-        uint32_t mk = 0u;  // (columns beyond the vocabulary are masked)
-        if (e0 < V) {
-          mk = (words[(e0 - e_begin) >> 5] >> (e0 & 31)) & kAll;
-          if (e0 + EPT > V) mk &= (1u << (V - e0)) - 1u;
-        }
-        apply_group<APPLY>(row + (size_t)e0 * APPLY, mk, e0, V_logits, neg_inf);
-      }
-    }
-  }
-  // The same for a range of kSegTokens elements that lies inside both the vocabulary and the row (every
-  // segment but a row's last), written for the fewest instructions: with 2432 workgroups of four waves on
-  // 1024 SIMDs the launch is bound by instruction issue, and each 60 instructions per thread cost a
-  // microsecond.  Thread t of NT takes the groups t, t + NT, ...: their mask bits are fetched from LDS
-  // first (one byte each for 2-byte logits), then a group with nothing allowed is one streaming store and a
-  // group with both kinds one 2- or 4-byte store per disallowed element, in a loop that runs as often as
-  // the lane of the wave with the most of them needs.
-  template <int NT>
-  __device__ __forceinline__ void whole_segment(uint32_t t) const {
-    if constexpr (APPLY != 0) {
-      constexpr int EPT = 16 / APPLY;
-      constexpr uint32_t kAll = (1u << EPT) - 1u;
-      constexpr int kGroups = kSegTokens / EPT / NT;  // per thread
-      static_assert(kSegTokens % (EPT * NT) == 0, "every thread takes the same number of groups");
-      typedef uint32_t v4u __attribute__((ext_vector_type(4)));
-      const uint32_t fill = APPLY == 2 ? (neg_inf | (neg_inf << 16)) : neg_inf;
-      const v4u val = {fill, fill, fill, fill};
-      unsigned char* p = row + ((size_t)e_begin * APPLY + (size_t)t * 16u);
-      uint32_t mk[kGroups];
-#pragma unroll
-      for (int k = 0; k < kGroups; ++k) {
-        const uint32_t g = (uint32_t)k * NT + t;
-        if (APPLY == 2) mk[k] = reinterpret_cast<const unsigned char*>(words)[g];
-        else mk[k] = (words[g >> 3] >> ((g & 7u) * 4u)) & kAll;
-      }
-#pragma unroll
-      for (int k = 0; k < kGroups; ++k) {
-        unsigned char* q = p + (size_t)k * NT * 16u;
-        if (mk[k] == 0u) {
-          __builtin_nontemporal_store(val, reinterpret_cast<v4u*>(q));
-        } else {
-          for (uint32_t x = ~mk[k] & kAll; x; x &= x - 1u) {
-            const uint32_t h = (uint32_t)__ffs(x) - 1u;
-            if (APPLY == 2) reinterpret_cast<uint16_t*>(q)[h] = (uint16_t)neg_inf;
-            else reinterpret_cast<uint32_t*>(q)[h] = neg_inf;
-          }
-        }
-      }
-    }
-  }
-};
 
 // ---------------------------------------------------------------- kernel (b)
 // The per-step stack upload, as a kernel on the caller's stream that reads pinned host memory over the bus
@@ -1253,17 +1206,15 @@ __global__ __launch_bounds__(kFillThreads, WALKS ? 4 : 8) void fill_kernel(const
   }
   // 4. the words, and the logits of the segment; the last segment also takes the columns beyond the vocabulary
   for (int32_t w = tid; w < n_words; w += kFillThreads) out[(size_t)b * voc.W + w_begin + w] = sm.words[w];
-  if (APPLY != 0) {
-    LogitsRange<APPLY> logits;
-    logits.row = fa.logits + (size_t)b * fa.row_stride * APPLY;
-    logits.words = sm.words;
-    logits.e_begin = id0;
-    logits.e_end = seg + 1 == voc.n_seg ? fa.V_logits : min(id0 + kSegTokens, fa.V_logits);
-    logits.V = voc.V;
-    logits.V_logits = fa.V_logits;
-    logits.neg_inf = fa.neg_inf;
-    if (logits.e_end == id0 + kSegTokens && logits.e_end <= voc.V) logits.template whole_segment<kFillThreads>(tid);
-    else logits.groups(tid, kFillThreads);
+  if constexpr (APPLY != 0) {
+    const int32_t e_end = seg + 1 == voc.n_seg ? fa.V_logits : min(id0 + kSegTokens, fa.V_logits), lane = (int32_t)(tid & 63u);
+    unsigned char* const logits = fa.logits + (size_t)b * fa.row_stride * APPLY;
+    for (int32_t e0 = id0 + (int32_t)uniform(tid >> 6) * kApplyWaveElems; e0 < e_end; e0 += kSegTokens) {
+      const int32_t e = e0 + lane * 32;  // (words beyond the vocabulary's are zero, and so are the bits of its last one)
+      uint32_t allowed = e < id0 + kSegTokens ? sm.words[(e - id0) >> 5] : 0u;
+      if (e + 32 > e_end) allowed |= e < e_end ? ~0u << (e_end - e) : ~0u;
+      apply_wave<APPLY>(logits + (size_t)e0 * APPLY, allowed, fa.neg_inf);
+    }
   }
 }
 
@@ -1795,61 +1746,34 @@ __global__ void batch_fork_commit_kernel(DevBatch bt, const int32_t* __restrict_
 // ---------------------------------------------------------------- kernel (c)
 constexpr int kApplyThreads = 256;
 
-// Section 2.1: logits of disallowed tokens become -inf.  One workgroup per (segment of kSegTokens elements, row); a
-// wave takes 2048 elements of it, lane l the mask word of elements 32 l .. 32 l + 31.  Segments begin on 16 bytes, up
-// to a group less one element in front of a row that does not: the words are then put together from two words of the
-// mask, and elements outside the row count as allowed.  A stretch of 64 groups of 16 bytes with nothing allowed is one
-// streaming store per lane; any other is stored element by element, 64 elements at a time, under their mask bits, which
-// lie in the order of the lanes.  Bound by the stores: 128 rows x 151937 bf16 (no row but every eighth is aligned) with
-// three words of ten mixed take 9.6 us, with one of fifty 8.5; one element per thread, as such rows went before, took
-// 28.4.  Aligned rows of 151936: 8.8 and 7.3 us; with a loop over the disallowed elements of a lane's group, which runs as
-// often as the wave's busiest lane needs, 11.4 and 7.9.  16 x 100003: 3.6, before 4.3 (most of it the launch).
+// Section 2.1: logits of disallowed tokens become -inf.  One workgroup per (segment of kSegTokens elements, row), a
+// quarter of it each wave.  Segments begin on 16 bytes, up to a group less one element in front of a row that does not:
+// the bits are then put together from two words of the mask, and elements outside the row count as allowed.
+// Bound by the stores: serving masks on 128 rows x 151936 bf16 take 6.9 us, fp32 11.1 (with a loop over the disallowed
+// elements of a lane's group of 16 bytes 7.6 and 12.0); rows of 151937, of which every eighth is aligned, 7.6 (one
+// element per thread, as such rows went before: 27.8).  16 x 100003: 3.6, before 4.3 (most of it the launch).
 // ESIZE = bytes per element.
 template <int ESIZE>
 __global__ __launch_bounds__(kApplyThreads) void apply_kernel(unsigned char* __restrict__ logits, int64_t row_stride,
                                                               const uint32_t* __restrict__ bitmask, int32_t W_mask,
                                                               int32_t V_logits, int32_t V_mask,
                                                               const int32_t* __restrict__ row_index, uint32_t neg_inf) {
-  typedef uint32_t v4u __attribute__((ext_vector_type(4)));
-  constexpr int kStretch = 64 * 16 / ESIZE, kStretchWords = kStretch / 32, kWaveWords = 64;
-  const int32_t j = blockIdx.y, lane = (int32_t)(threadIdx.x & 63u), wave = (int32_t)uniform(threadIdx.x >> 6);
+  static_assert(kApplyThreads / 64 * kApplyWaveElems == kSegTokens, "four waves take a segment");
+  const int32_t j = blockIdx.y, lane = (int32_t)(threadIdx.x & 63u);
   const int64_t lrow = row_index ? row_index[j] : j;
   unsigned char* row = logits + (size_t)lrow * row_stride * ESIZE;
   const uint32_t* words = bitmask + (size_t)j * W_mask;
   const int32_t ahead = (int32_t)((uint32_t)reinterpret_cast<uintptr_t>(row) % 16u) / ESIZE;
-  const int32_t e_wave = (int32_t)blockIdx.x * kSegTokens + wave * kWaveWords * 32 - ahead;  // the wave's first element
-  if (e_wave >= V_logits) return;
-  const int32_t e = e_wave + lane * 32;  // the lane's first
-  const int32_t at = e >> 5;
+  const int32_t e0 = (int32_t)blockIdx.x * kSegTokens + (int32_t)uniform(threadIdx.x >> 6) * kApplyWaveElems - ahead;
+  if (e0 >= V_logits) return;
+  const int32_t e = e0 + lane * 32, at = e >> 5;  // the lane's first element
   const uint32_t lo = at >= 0 && at < W_mask ? words[at] : 0u;
   const uint32_t hi = ahead != 0 && at + 1 < W_mask ? words[at + 1] : 0u;
   uint32_t allowed = __builtin_amdgcn_alignbit(hi, lo, (uint32_t)e & 31u);
   if (e + 32 > V_mask) allowed &= e < V_mask ? (1u << (V_mask - e)) - 1u : 0u;
   if (e < 0) allowed |= (1u << -e) - 1u;
   if (e + 32 > V_logits) allowed |= e < V_logits ? ~0u << (V_logits - e) : ~0u;
-  const unsigned long long none = __ballot(allowed == 0u), all = __ballot(allowed == ~0u);
-  const uint32_t fill = ESIZE == 2 ? (neg_inf | (neg_inf << 16)) : neg_inf;
-  const v4u val = {fill, fill, fill, fill};
-  unsigned char* const p = row + (ptrdiff_t)e_wave * ESIZE;
-#pragma unroll
-  for (int k = 0; k < kWaveWords / kStretchWords; ++k) {
-    constexpr unsigned long long kOnes = (1ull << kStretchWords) - 1ull;
-    if (((all >> (k * kStretchWords)) & kOnes) == kOnes) continue;
-    unsigned char* const q = p + k * 1024;
-    if (((none >> (k * kStretchWords)) & kOnes) == kOnes) {
-      __builtin_nontemporal_store(val, reinterpret_cast<v4u*>(q + lane * 16));
-    } else {
-#pragma unroll
-      for (int h = 0; h < kStretchWords / 2; ++h) {
-        const unsigned long long bits = (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)allowed, k * kStretchWords + 2 * h) |
-                                        ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)allowed, k * kStretchWords + 2 * h + 1) << 32);
-        if (!__builtin_amdgcn_inverse_ballot_w64(bits)) {
-          if (ESIZE == 2) reinterpret_cast<uint16_t*>(q)[h * 64 + lane] = (uint16_t)neg_inf;
-          else reinterpret_cast<uint32_t*>(q)[h * 64 + lane] = neg_inf;
-        }
-      }
-    }
-  }
+  apply_wave<ESIZE>(row + (ptrdiff_t)e0 * ESIZE, allowed, neg_inf);
 }
 
 // ------------------------------------------------------------ measurement aid
