@@ -900,6 +900,177 @@ __global__ __launch_bounds__(kUploadThreads) void upload_stacks_kernel(const uin
   }
 }
 
+// A walk by a whole wave (all lanes do the same): its memory is in LDS, and everything it reads is declared the same
+// for all lanes, so that the walk runs in scalar registers with scalar branches.  A lone lane waits for every
+// instruction just as long, and needs more of them (each branch turns lanes off and on again; frames and
+// alternatives go through scratch memory).
+constexpr uint32_t kWaveMemWords = kArenaFrames + 2 * kChoicePoints;
+struct WaveMem {
+  XGM_LDS uint32_t* arena;    // [kArenaFrames]
+  XGM_LDS uint32_t* choices;  // [2 * kChoicePoints]
+  __device__ __forceinline__ uint32_t frame(uint32_t k) const { return uniform(arena[k]); }
+  __device__ __forceinline__ void set_frame(uint32_t k, uint32_t v) { arena[k] = v; }
+  __device__ __forceinline__ uint2 choice(uint32_t k) const { return make_uint2(uniform(choices[2u * k]), uniform(choices[2u * k + 1u])); }
+  __device__ __forceinline__ void set_choice(uint32_t k, uint2 v) { choices[2u * k] = v.x; choices[2u * k + 1u] = v.y; }
+};
+struct UniformFrames {
+  const XGM_LDS uint16_t* p;
+  __device__ __forceinline__ uint32_t operator[](uint32_t k) const { return uniform(p[k]); }
+  __device__ __forceinline__ uint32_t of_lane(uint32_t k) const { return p[k]; }
+};
+// walk_token (of a live stack) for a wave whose tables (the sections in front of the headers) are in LDS: the same
+// paths in the same order, fewer steps.  A step looks many bytes ahead: lane j at node n on byte i + j (the inside of
+// a string stays where it is), lane 32 + j at node n + j on byte i + j (a literal's nodes are numbered one after the
+// other).  While there is nothing to do but a move along a byte edge, all of a run is taken at once, and the move
+// behind it; what the lane in front of which the run ended has read is what the alternatives there are made from.
+// Where there is nothing but a return, lane j looks at the frame j below the one returned into, and all frames are
+// returned through that can do nothing else with the byte (an operand in an expression grammar sits a dozen precedence
+// levels deep).
+// The lookup has no branches: to a wave that is alone with its walk a taken branch costs as much as a dozen
+// instructions.  A nine-byte piece of a string takes 1.2 us this way, 6 with a lane's walk byte by byte.
+template <class Note>
+__device__ __forceinline__ int walk_wave(const LdsTabT<true, true>& T, WaveMem& mem, const uint4 tk, const uint8_t* ext, const int len,
+                                         const uint32_t start_node, const UniformFrames& live, const uint32_t depth, const Note& note,
+                                         const int i0 = 0) {
+  if (len > kMaxTokenLen) return kOverflow;
+  const TokenWords tw(tk);
+  const uint32_t lane = threadIdx.x & 63u, ahead = lane & 31u;
+  const uint32_t last_alt = (T.off_hdr - T.off_alts) / 4u - 1u;
+  uint32_t n = start_node, sp = kLiveBase + depth - 1, f = 1, alt = 0, top = 0, csp = 0, needed = 0;
+  int i = i0;
+  // node `node` on byte `c`, each lane its own: the header's flags, whether c can follow the node's rule, whether there
+  // is a move or calls, and where to
+  struct Found { uint32_t flags, follow, to; bool some; };
+  auto look = [&](uint32_t node, uint32_t c) {
+    Found r;
+    const unsigned long long hdr = node < T.n_near ? *(const XGM_LDS unsigned long long*)(T.lds + T.off_hdr + node * 8u)
+                                                   : *(const XGM_GLOBAL unsigned long long*)(T.img + T.off_hdr + (size_t)node * 8u);
+    const uint32_t hx = (uint32_t)hdr;
+    r.flags = (uint32_t)(hdr >> 32);
+    const uint32_t cl = T.lds[c];
+    r.follow = *(const XGM_LDS uint32_t*)(T.lds + T.off_follow + ((r.flags >> 16) * 8u + (c >> 5)) * 4u) >> (c & 31u);
+    const bool branching = (r.flags & 2u) != 0u;
+    const uint32_t si = T.lds[T.off_shapes + (branching ? (hx & 0xFFFFu) * T.n_cls : 0u) + cl];
+    const uint32_t at = branching && si != 0xFFu ? (hx >> 16) + si : 0u;
+    const uint32_t target = *(const XGM_LDS uint16_t*)(T.lds + T.off_targets + at * 2u);
+    r.some = branching ? si != 0xFFu : c >= (hx & 0xFFu) && c <= ((hx >> 8) & 0xFFu);
+    r.to = branching ? target : hx >> 16;
+    return r;
+  };
+  for (int steps = 0;; ++steps) {
+    if (steps >= kMaxSteps) return kOverflow;
+    bool back = true;
+    if (i == len) {
+      if constexpr (!Note::kEnumerate) return kAccept;
+      note(n, sp, mem, live);  // then on to the next path
+    } else {
+      const bool mine = (int)ahead < len - i;
+      const uint32_t c = token_byte(tw, ext, mine ? i + (int)ahead : i);
+      const uint32_t node = lane < 32u || !mine ? n : min(n + ahead, T.n_nodes - 1u);
+      const Found at_node = look(node, c);
+      const bool may_return = ((at_node.flags & (ahead == 0u ? f : 1u) & at_node.follow) & 1u) != 0u;
+      const bool moves_on = mine && at_node.some && at_node.to < 0x8000u && !may_return && alt == 0u;
+      const unsigned long long can = __ballot(moves_on), stays = __ballot(moves_on && at_node.to == (lane < 32u ? n : node + 1u));
+      const uint32_t same = (uint32_t)__ffs((int)(~(uint32_t)stays | 0x80000000u)) - 1u;
+      const uint32_t chain = (uint32_t)__ffs((int)(~(uint32_t)(stays >> 32) | 0x80000000u)) - 1u;
+      const uint32_t run = max(same, chain), last = same >= chain ? same : 32u + chain;
+      auto of_last = [&](uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)last); };
+      uint32_t dst = of_last(at_node.to);
+      if (chain > same) n += chain;
+      i += (int)run;
+      steps += (int)run;
+      f = run ? 1u : f;
+      if ((can >> last) & 1ull) {
+        n = dst;
+        ++i;
+        f = 1;
+        continue;
+      }
+      if (i == len) { --steps; continue; }
+      uint32_t k_some = of_last(at_node.some ? 1u : 0u);
+      uint32_t can_pop = sp == kLiveBase ? 0u : of_last(at_node.flags & at_node.follow) & f & 1u;
+      if (can_pop && !k_some && alt == 0u) {
+        // (frames pushed one after the other lie one after the other, each with the number of the one below)
+        const bool pushed = sp < kLiveBase;
+        const uint32_t below = pushed ? sp + 1u : sp - kLiveBase;
+        const uint32_t word = lane >= below ? n : pushed ? mem.arena[sp - lane] : live.of_lane(below - 1u - lane);
+        const Found there = look(word & 0xFFFFu, of_last(c));
+        const bool next = pushed ? (word >> 16) + 1u == sp - lane : lane + 1u < below;  // (frame 0 of the stack is not returned from)
+        const unsigned long long other = ~__ballot(lane < below && next && !there.some && (there.flags & there.follow & 1u));
+        const uint32_t through = min((uint32_t)__ffsll((long long)other) - 1u, 63u);  // (none: 0xFFFFFFFF)
+        auto of_frame = [&](uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)through); };
+        n = of_frame(word) & 0xFFFFu;
+        if (pushed && needed <= sp) top = max(sp - through, needed);  // (frames that a pending alternative needs stay)
+        sp = pushed ? of_frame(word) >> 16 : sp - through - 1u;
+        steps += (int)through + 1;
+        dst = of_frame(there.to);
+        k_some = of_frame(there.some ? 1u : 0u);
+        can_pop = sp == kLiveBase ? 0u : of_frame(there.flags & there.follow) & 1u;
+      }
+      const bool pooled = k_some && dst >= 0x8000u;
+      // the pool entry: lane j has its word j (a count and the alternatives, or a run of calls)
+      const uint32_t base = dst & 0x7FFFu;
+      const uint32_t word = pooled ? *(const XGM_LDS uint32_t*)(T.lds + T.off_alts + min(base + lane, last_alt) * 4u) : 0u;
+      const uint32_t word0 = uniform(word);
+      const bool calls = (word0 & kRunFlagD) != 0u;
+      const uint32_t k = pooled && !calls ? word0 : k_some, total = k + can_pop;
+      if (alt < total) {
+        back = false;
+        if (alt + 1 < total) {
+          if (csp == kChoicePoints) return kOverflow;
+          mem.set_choice(csp++, make_uint2(n | (sp << 16), (uint32_t)i | ((alt + 1) << 8) | (top << 16) | (f << 24)));
+          needed = top;
+        }
+        if (alt < k) {
+          bool consumes;
+          if (calls) {
+            const uint32_t m = run_frames(word0);
+            if (top + m > kArenaFrames) return kOverflow;
+            for (uint32_t j = 0; j < m; ++j) {
+              mem.set_frame(top, ((T.alt(run_frames_at(word0) + (j >> 1)) >> ((j & 1u) * 16u)) & 0xFFFFu) | (sp << 16));
+              sp = top++;
+            }
+            n = (uint32_t)__builtin_amdgcn_readlane((int)word, 1);
+            consumes = (word0 & kRunConsumesD) != 0u;
+          } else {
+            const uint32_t e = !pooled ? (kMoveTagD << 16) | dst : alt < 63u ? (uint32_t)__builtin_amdgcn_readlane((int)word, (int)(1u + alt)) : T.alt(base + 1u + alt);
+            const uint32_t tag = e >> 16;
+            n = e & 0xFFFFu;
+            consumes = tag == kMoveTagD;
+            if (!consumes && tag != kTailTagD) {
+              if (top == kArenaFrames) return kOverflow;
+              mem.set_frame(top, tag | (sp << 16));
+              sp = top++;
+            }
+          }
+          f = consumes ? 1u : 0u;
+          i += consumes ? 1 : 0;
+        } else if (sp < kLiveBase) {   // return into a frame pushed during this walk
+          const uint32_t fr = mem.frame(sp), old = sp;
+          n = fr & 0xFFFFu;
+          sp = fr >> 16;
+          if (needed <= old) top = old;
+        } else {                       // return into a live frame
+          n = live[sp - kLiveBase - 1u];
+          --sp;
+        }
+        alt = 0;
+      }
+    }
+    if (back) {  // to the most recent pending alternative
+      if (csp == 0) break;
+      const uint2 ch = mem.choice(--csp);
+      n = ch.x & 0xFFFFu;
+      sp = ch.x >> 16;
+      i = (int)(ch.y & 0xFFu);
+      alt = (ch.y >> 8) & 0xFFu;
+      top = (ch.y >> 16) & 0xFFu;
+      f = (ch.y >> 24) & 1u;
+      needed = csp ? (mem.choice(csp - 1).y >> 16) & 0xFFu : 0u;
+    }
+  }
+  return kReject;
+}
 constexpr int kFillThreads = 256;
 constexpr int kFillFramesLds = 1024;            // live frames kept in LDS (deeper stacks: global memory)
 
@@ -932,18 +1103,25 @@ constexpr int kFillFramesLds = 1024;            // live frames kept in LDS (deep
 // kernel for both the walk was a function of its own, which spilled in its
 // inner loop and cost 5 us before its first step: the fill of a
 // row that walks a handful of tokens (C/SQL-like grammar, 128256 tokens, one row)
-// went from 13.7 to 8.7 us, one that walks 500 steps from 53 to 36.
+// went from 13.7 to 8.7 us, one that walks 500 steps from 53 to 36, and to 31 with a
+// wave for each entry of a short queue; a row of the scripting grammar that walks 50
+// steps from 7.8 to 4.8.
 template <bool WALKS>
 struct FillShared {
   uint32_t words[kSegWords];
 };
 constexpr uint32_t kWalkQueue = 256;  // entries; where there are more the lists are gone through again
+// Up to this many entries go to a wave each (walk_wave): six one after the other cost what a lane's longest walk does in
+// a grammar of deep walks (C/SQL-like: 23 -> 17 us for a row with a walk of 79 steps; with up to 64 a row of 4358 steps
+// took 137 us instead of 55, with up to 256 as long).
+constexpr uint32_t kWaveWalks = 24;
 template <>
 struct FillShared<true> {
   uint32_t words[kSegWords];
   uint16_t live[kFillFramesLds];
   uint2 queue[kWalkQueue];            // (entry, stack)
   uint32_t n_queued;                  // counts on beyond the queue's room
+  uint32_t mem[kFillThreads / 64][kWaveMemWords];
 };
 
 // What the walks need to know about a row, wherever its state came from.
@@ -953,15 +1131,34 @@ struct WalkRow {
   uint32_t stride, frame0, n_frames, epoch;
 };
 
-// Decides walk entries, thread t the entries t, t + kFillThreads, ... of the queue (list null) or of a list of stack
-// `list_stack` (all threads call this).
+// One walk entry of a list of a stack: what to walk.  Returns false if the stack does not reach the entry's level.
+struct WalkStart { uint32_t f_off, depth, drop; };  // the stack's frames; frames above the one the walk starts in
+template <bool INLINE>
+__device__ __forceinline__ bool walk_start(const WalkRow& row, uint32_t stack, uint32_t entry, WalkStart& w) {
+  const XGM_GLOBAL uint32_t* sh = row.stacks + (size_t)stack * row.stride;
+  uint32_t drops;
+  if (INLINE) {
+    w.depth = sh[5] & 0xFFFFu;
+    w.f_off = sh[5] >> 16;
+    drops = sh[6];
+  } else {
+    w.depth = sh[kStackHdrDepth];
+    w.f_off = sh[kStackHdrFrames];
+    drops = sh[kStackHdrDrops];
+  }
+  w.drop = stack_drop(drops, (entry >> kEntryKindShift) - kEntryWalkTop);
+  return w.depth > w.drop;
+}
+
+// Decides walk entries, thread t the entries t, t + kFillThreads, ... of the queue (list null; neighbours in it go to
+// different waves) or of a list of stack `list_stack` (all threads call this).
 template <bool COUNT, bool KEEP_UNDECIDED, bool INLINE, class Tab>
 __device__ __forceinline__ void fill_walks(const Tab& T, FillShared<true>& sm, const WalkRow& row, const int32_t b, const int32_t id0,
                                            const XGM_GLOBAL uint32_t* list, const uint32_t list_stack, const uint32_t n,
                                            const DevVocab& voc, OverflowLog* log, uint32_t seq, unsigned long long& my_steps) {
   const bool frames_in_lds = row.n_frames <= kFillFramesLds;
 #pragma unroll 1
-  for (uint32_t q = threadIdx.x; q < n; q += kFillThreads) {
+  for (uint32_t q = list ? threadIdx.x : (threadIdx.x & 63u) * (kFillThreads / 64) + (threadIdx.x >> 6); q < n; q += kFillThreads) {
     uint32_t e, stack = list_stack;
     if (list) {
       e = list[q];
@@ -970,35 +1167,46 @@ __device__ __forceinline__ void fill_walks(const Tab& T, FillShared<true>& sm, c
       e = sm.queue[q].x;
       stack = sm.queue[q].y;
     }
-    const XGM_GLOBAL uint32_t* sh = row.stacks + (size_t)stack * row.stride;
-    const uint32_t id = e & kEntryIdMask, kind = e >> kEntryKindShift, pos = (e >> kEntryPosShift) & 0xFFu;
+    const uint32_t id = e & kEntryIdMask, pos = (e >> kEntryPosShift) & 0xFFu;
     const uint32_t rel = id - (uint32_t)id0;
     if ((sm.words[rel >> 5] >> (rel & 31u)) & 1u) continue;  // already allowed
     const TokenRef t = load_token(voc, (int32_t)id);
-    uint32_t top, depth, f_off, drops;
-    if (INLINE) {
-      top = sh[0] & 0xFFFFu;
-      depth = sh[5] & 0xFFFFu;
-      f_off = sh[5] >> 16;
-      drops = sh[6];
-    } else {
-      top = sh[kStackHdrTop] & 0xFFFFu;
-      depth = sh[kStackHdrDepth];
-      f_off = sh[kStackHdrFrames];
-      drops = sh[kStackHdrDrops];
-    }
+    WalkStart w;
+    if (!walk_start<INLINE>(row, stack, e, w)) continue;
     LiveView live;
-    live.lds = (const XGM_LDS uint16_t*)sm.live + (f_off - row.frame0);
-    live.glob = row.frames + f_off;
+    live.lds = (const XGM_LDS uint16_t*)sm.live + (w.f_off - row.frame0);
+    live.glob = row.frames + w.f_off;
     live.lo = frames_in_lds ? 0u : 0xFFFFFFFFu;
-    const uint32_t drop = stack_drop(drops, kind - kEntryWalkTop);  // frames above the one the walk starts in
-    if (depth <= drop) continue;
     uint32_t n_steps = 0;
-    const uint32_t start = drop == 0u ? top : live[depth - 1u - drop];
-    const int res = walk_token<false>(T, t.tk, t.ext, t.len, start, live, depth - drop, COUNT ? &n_steps : nullptr, 0u, drop == 0u ? 0 : (int)pos);
+    const int res = walk_token<false>(T, t.tk, t.ext, t.len, live[w.depth - 1u - w.drop], live, w.depth - w.drop, COUNT ? &n_steps : nullptr, 0u,
+                                      w.drop == 0u ? 0 : (int)pos);
     if (COUNT) my_steps += n_steps;
     if (res == kOverflow) record_overflow(log, seq, (uint32_t)b, id, row.epoch);  // decided on the host
     if (res == kAccept || (KEEP_UNDECIDED && res == kOverflow)) atomicOr(&sm.words[rel >> 5], 1u << (rel & 31u));
+  }
+}
+// The same for a short queue, a wave per entry (tables and frames are in LDS).
+template <bool KEEP_UNDECIDED, bool INLINE>
+__device__ __forceinline__ void fill_walks_by_wave(const LdsTabT<true, true>& T, FillShared<true>& sm, const WalkRow& row, const int32_t b,
+                                                   const int32_t id0, const uint32_t n, const DevVocab& voc, OverflowLog* log, uint32_t seq) {
+  const uint32_t wave = uniform(threadIdx.x >> 6);
+  WaveMem mem{(XGM_LDS uint32_t*)sm.mem[wave], (XGM_LDS uint32_t*)sm.mem[wave] + kArenaFrames};
+#pragma unroll 1
+  for (uint32_t q = wave; q < n; q += kFillThreads / 64) {
+    const uint32_t e = uniform(sm.queue[q].x), stack = uniform(sm.queue[q].y);
+    const uint32_t id = e & kEntryIdMask, pos = (e >> kEntryPosShift) & 0xFFu;
+    const uint32_t rel = id - (uint32_t)id0;
+    if ((uniform(sm.words[rel >> 5]) >> (rel & 31u)) & 1u) continue;  // already allowed
+    const TokenRef t = load_token(voc, (int32_t)id);
+    WalkStart w;
+    if (!walk_start<INLINE>(row, stack, e, w)) continue;
+    const uint32_t depth = uniform(w.depth), drop = uniform(w.drop);
+    const UniformFrames live{(const XGM_LDS uint16_t*)sm.live + (uniform(w.f_off) - row.frame0)};
+    const int res = walk_wave(T, mem, t.tk, t.ext, (int)uniform((uint32_t)t.len), live[depth - 1u - drop], live, depth - drop, FirstPathEnds(), drop == 0u ? 0 : (int)pos);
+    if ((threadIdx.x & 63u) == 0u) {
+      if (res == kOverflow) record_overflow(log, seq, (uint32_t)b, id, row.epoch);  // decided on the host
+      if (res == kAccept || (KEEP_UNDECIDED && res == kOverflow)) atomicOr(&sm.words[rel >> 5], 1u << (rel & 31u));
+    }
   }
 }
 
@@ -1185,6 +1393,9 @@ __global__ __launch_bounds__(kFillThreads, WALKS ? 4 : 8) void fill_kernel(const
       // the queue, or, if it overflowed, list after list
       const uint32_t n_queued = sm.n_queued;
       const bool again = n_queued > kWalkQueue;
+      if (!COUNT && n_queued <= kWaveWalks && small_sections_staged(tab) && row.n_frames <= kFillFramesLds)
+        fill_walks_by_wave<APPLY != 0, INLINE != 0>(LdsTabT<true, true>(tab, smem), sm, row, b, id0, n_queued, voc, log, seq);
+      else
 #pragma unroll 1
       for (uint32_t k = 0; k < (again ? n_stacks * kStackLists : 1u); ++k) {
         uint2 list = make_uint2(0u, n_queued);
@@ -1229,7 +1440,6 @@ constexpr int kErrTokenRejected = -6, kErrTerminated = -7, kErrTooManyStacks = -
 // by frame - but by the whole workgroup when the next state is written.
 constexpr uint32_t kAcceptHeaders = 1024;  // node headers staged at most
 constexpr uint32_t kNewFrames = kArenaFrames + 1;
-constexpr uint32_t kWaveMemWords = kArenaFrames + 2 * kChoicePoints;  // (see WaveMem)
 struct AcceptShared {
   uint16_t live[kBatchRowFrames];                    // the row's frames
   uint16_t fresh[kBatchMaxCandidates][kNewFrames + 1];
@@ -1249,22 +1459,6 @@ struct AcceptShared {
     const uint32_t f = from[i], d = (f >> 8) & 0xFFu;
     return k < d ? live[(stack[f & 0xFFu] & 0xFFFFu) + k] : fresh[i][k - d];
   }
-};
-// A walk by a whole wave (all lanes do the same): its memory is in LDS, and everything it reads is declared the same
-// for all lanes, so that the walk runs in scalar registers with scalar branches.  A lone lane waits for every
-// instruction just as long, and needs more of them (each branch turns lanes off and on again; frames and
-// alternatives go through scratch memory).
-struct WaveMem {
-  XGM_LDS uint32_t* arena;    // [kArenaFrames]
-  XGM_LDS uint32_t* choices;  // [2 * kChoicePoints]
-  __device__ __forceinline__ uint32_t frame(uint32_t k) const { return uniform(arena[k]); }
-  __device__ __forceinline__ void set_frame(uint32_t k, uint32_t v) { arena[k] = v; }
-  __device__ __forceinline__ uint2 choice(uint32_t k) const { return make_uint2(uniform(choices[2u * k]), uniform(choices[2u * k + 1u])); }
-  __device__ __forceinline__ void set_choice(uint32_t k, uint2 v) { choices[2u * k] = v.x; choices[2u * k + 1u] = v.y; }
-};
-struct UniformFrames {
-  const XGM_LDS uint16_t* p;
-  __device__ __forceinline__ uint32_t operator[](uint32_t k) const { return uniform(p[k]); }
 };
 // The end policy of the walk (see walk_token): notes where the token can end.  A top node that can only return is
 // returned from first, so that equal states get equal stacks.
@@ -1307,127 +1501,6 @@ struct NoteStacks {
     }
   }
 };
-// walk_token's enumerating walk for a wave whose tables (the sections in front of the headers) are in LDS: the same
-// paths in the same order, fewer steps.  A step looks many bytes ahead: lane j at node n on byte i + j (the inside of
-// a string stays where it is), lane 32 + j at node n + j on byte i + j (a literal's nodes are numbered one after the
-// other).  While there is nothing to do but a move along a byte edge, all of a run is taken at once, and the move
-// behind it; what the lane in front of which the run ended has read is what the alternatives there are made from.
-// The lookup has no branches: to a wave that is alone with its walk a taken branch costs as much as a dozen
-// instructions.  A nine-byte piece of a string takes 1.2 us this way, 6 with a lane's walk byte by byte.
-template <class Note>
-__device__ __forceinline__ int walk_wave(const LdsTabT<true, true>& T, WaveMem& mem, const uint4 tk, const uint8_t* ext, const int len,
-                                         const uint32_t start_node, const UniformFrames& live, const uint32_t depth, const Note& note) {
-  if (len > kMaxTokenLen) return kOverflow;
-  const TokenWords tw(tk);
-  const uint32_t lane = threadIdx.x & 63u, ahead = lane & 31u;
-  const uint32_t last_alt = (T.off_hdr - T.off_alts) / 4u - 1u;
-  uint32_t n = start_node, sp = kLiveBase + depth - 1, f = 1, alt = 0, top = 0, csp = 0, needed = 0;
-  int i = 0;
-  for (int steps = 0;; ++steps) {
-    if (steps >= kMaxSteps) return kOverflow;
-    bool back = true;
-    if (i == len) {
-      note(n, sp, mem, live);  // then on to the next path
-    } else {
-      const bool mine = (int)ahead < len - i;
-      const uint32_t c = token_byte(tw, ext, mine ? i + (int)ahead : i);
-      const uint32_t node = lane < 32u || !mine ? n : min(n + ahead, T.n_nodes - 1u);
-      const unsigned long long hdr = node < T.n_near ? *(const XGM_LDS unsigned long long*)(T.lds + T.off_hdr + node * 8u)
-                                                     : *(const XGM_GLOBAL unsigned long long*)(T.img + T.off_hdr + (size_t)node * 8u);
-      const uint32_t hx = (uint32_t)hdr, hy = (uint32_t)(hdr >> 32);
-      const uint32_t cl = T.lds[c];
-      const uint32_t follow = *(const XGM_LDS uint32_t*)(T.lds + T.off_follow + ((hy >> 16) * 8u + (c >> 5)) * 4u) >> (c & 31u);
-      const bool branching = (hy & 2u) != 0u;
-      const uint32_t si = T.lds[T.off_shapes + (branching ? (hx & 0xFFFFu) * T.n_cls : 0u) + cl];
-      const uint32_t at = branching && si != 0xFFu ? (hx >> 16) + si : 0u;
-      const uint32_t target = *(const XGM_LDS uint16_t*)(T.lds + T.off_targets + at * 2u);
-      const bool some = branching ? si != 0xFFu : c >= (hx & 0xFFu) && c <= ((hx >> 8) & 0xFFu);  // a move or calls
-      const uint32_t to = branching ? target : hx >> 16;
-      const bool may_return = ((hy & (ahead == 0u ? f : 1u) & follow) & 1u) != 0u;
-      const bool moves_on = mine && some && to < 0x8000u && !may_return && alt == 0u;
-      const unsigned long long can = __ballot(moves_on), stays = __ballot(moves_on && to == (lane < 32u ? n : node + 1u));
-      const uint32_t same = (uint32_t)__ffs((int)(~(uint32_t)stays | 0x80000000u)) - 1u;
-      const uint32_t chain = (uint32_t)__ffs((int)(~(uint32_t)(stays >> 32) | 0x80000000u)) - 1u;
-      const uint32_t run = max(same, chain), last = same >= chain ? same : 32u + chain;
-      auto of_last = [&](uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)last); };
-      const uint32_t dst = of_last(to);
-      if (chain > same) n += chain;
-      i += (int)run;
-      steps += (int)run;
-      f = run ? 1u : f;
-      if ((can >> last) & 1ull) {
-        n = dst;
-        ++i;
-        f = 1;
-        continue;
-      }
-      if (i == len) { --steps; continue; }
-      const uint32_t y = of_last(hy), k_some = of_last(some ? 1u : 0u);
-      const uint32_t can_pop = sp == kLiveBase ? 0u : y & f & of_last(follow) & 1u;
-      const bool pooled = k_some && dst >= 0x8000u;
-      // the pool entry: lane j has its word j (a count and the alternatives, or a run of calls)
-      const uint32_t base = dst & 0x7FFFu;
-      const uint32_t word = pooled ? *(const XGM_LDS uint32_t*)(T.lds + T.off_alts + min(base + lane, last_alt) * 4u) : 0u;
-      const uint32_t word0 = uniform(word);
-      const bool calls = (word0 & kRunFlagD) != 0u;
-      const uint32_t k = pooled && !calls ? word0 : k_some, total = k + can_pop;
-      if (alt < total) {
-        back = false;
-        if (alt + 1 < total) {
-          if (csp == kChoicePoints) return kOverflow;
-          mem.set_choice(csp++, make_uint2(n | (sp << 16), (uint32_t)i | ((alt + 1) << 8) | (top << 16) | (f << 24)));
-          needed = top;
-        }
-        if (alt < k) {
-          bool consumes;
-          if (calls) {
-            const uint32_t m = run_frames(word0);
-            if (top + m > kArenaFrames) return kOverflow;
-            for (uint32_t j = 0; j < m; ++j) {
-              mem.set_frame(top, ((T.alt(run_frames_at(word0) + (j >> 1)) >> ((j & 1u) * 16u)) & 0xFFFFu) | (sp << 16));
-              sp = top++;
-            }
-            n = (uint32_t)__builtin_amdgcn_readlane((int)word, 1);
-            consumes = (word0 & kRunConsumesD) != 0u;
-          } else {
-            const uint32_t e = !pooled ? (kMoveTagD << 16) | dst : alt < 63u ? (uint32_t)__builtin_amdgcn_readlane((int)word, (int)(1u + alt)) : T.alt(base + 1u + alt);
-            const uint32_t tag = e >> 16;
-            n = e & 0xFFFFu;
-            consumes = tag == kMoveTagD;
-            if (!consumes && tag != kTailTagD) {
-              if (top == kArenaFrames) return kOverflow;
-              mem.set_frame(top, tag | (sp << 16));
-              sp = top++;
-            }
-          }
-          f = consumes ? 1u : 0u;
-          i += consumes ? 1 : 0;
-        } else if (sp < kLiveBase) {   // return into a frame pushed during this walk
-          const uint32_t fr = mem.frame(sp), old = sp;
-          n = fr & 0xFFFFu;
-          sp = fr >> 16;
-          if (needed <= old) top = old;
-        } else {                       // return into a live frame
-          n = live[sp - kLiveBase - 1u];
-          --sp;
-        }
-        alt = 0;
-      }
-    }
-    if (back) {  // to the most recent pending alternative
-      if (csp == 0) break;
-      const uint2 ch = mem.choice(--csp);
-      n = ch.x & 0xFFFFu;
-      sp = ch.x >> 16;
-      i = (int)(ch.y & 0xFFu);
-      alt = (ch.y >> 8) & 0xFFu;
-      top = (ch.y >> 16) & 0xFFu;
-      f = (ch.y >> 24) & 1u;
-      needed = csp ? (mem.choice(csp - 1).y >> 16) & 0xFFu : 0u;
-    }
-  }
-  return kReject;
-}
 // the order of candidates: element by element from the bottom, the shorter first (the host's order of stacks)
 __device__ __forceinline__ int compare_candidates(const AcceptShared& sm, uint32_t i, uint32_t j) {
   const uint32_t si = sm.from[i] & 0xFFu, sj = sm.from[j] & 0xFFu, di = sm.depth(i), dj = sm.depth(j);
