@@ -233,7 +233,7 @@ struct xgm_batch {
   int32_t B = 0, H = 0;
   xgm_vocab* v = nullptr;
   std::vector<xgm_cache*> caches;  // one per row (referenced)
-  bool walks = false;              // some of them have walk entries
+  uint32_t walks = 0;              // the most walk entries that one of them has (DevCache::walks)
   DevBatch dev{};
   std::vector<void*> dev_ptrs;
   // walks over the on-chip limits: the batch's own log, how much of it has been examined, and where the last
@@ -1300,14 +1300,14 @@ static int fill_impl(xgm_matcher* const* ms, int32_t B, int32_t* d_bitmask, void
   if (B > 65535) return fail(XGM_ERR_TOO_LARGE, "fill: more than 65535 rows in one call");
   xgm_vocab* v = nullptr;
   size_t n_stacks = 0, n_frames = 0;
-  bool walks = false;
+  uint32_t walks = 0;
   for (int32_t b = 0; b < B; ++b) {
     const xgm_matcher* m = ms[b];
     if (!m || !m->c) return fail(XGM_ERR_BAD_ARG, "fill: matcher is null or has no cache");
     if (v && m->v != v) return fail(XGM_ERR_BAD_ARG, "fill: all matchers must share one vocabulary");
     v = m->v;
     if (m->terminated) continue;
-    walks = walks || m->c->host.walks != 0;
+    walks = std::max(walks, m->c->host.walks);
     n_stacks += m->stacks.size();
     for (auto& s : m->stacks) {
       if (s.size() > XGM_MAX_STACK_DEPTH) return fail(XGM_ERR_TOO_LARGE, "fill: stack deeper than 4096 frames");
@@ -1743,7 +1743,7 @@ int xgm_batch_create(xgm_matcher* const* ms, int32_t B, int32_t history, void* h
     for (int32_t b = 0; b < B; ++b) {
       bt->caches.push_back(ms[b]->c);
       ++ms[b]->c->refs;
-      bt->walks = bt->walks || ms[b]->c->host.walks != 0;
+      bt->walks = std::max(bt->walks, ms[b]->c->host.walks);
     }
     auto keep = [&](auto* p) { bt->dev_ptrs.push_back((void*)p); return p; };
     const size_t hdr_words = stack_hdr_stride(v->dv.n_seg);

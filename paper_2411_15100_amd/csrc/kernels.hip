@@ -546,7 +546,12 @@ struct ContextWork {
   // workgroup's own counters per segment for this list: the entry is then only counted there)
   __device__ __forceinline__ void emit(uint32_t key, uint32_t kind, uint32_t pos, uint32_t* outcome,
                                        uint32_t* lds_counts) const {
-    if (!WRITE && kind != kEntryAccepted) a.res_count[kCtxLevels] = 1u;  // (the cache has walk entries)
+    if (!WRITE && kind != kEntryAccepted) {  // (how many walk entries the cache has, up to kManyWalks)
+      const unsigned long long peers = __ballot(true);
+      uint32_t* const total = a.res_count + kCtxLevels;
+      if ((uint32_t)__ffsll((long long)peers) - 1u == (threadIdx.x & 63u) && *(volatile uint32_t*)total < kManyWalks)
+        atomicAdd(total, (uint32_t)__popcll(peers));
+    }
     if (!WRITE && lds_counts) atomicAdd(&lds_counts[id / (uint32_t)kSegTokens], 1u);
     else ListSink<WRITE>{voc, a}.emit(id, key, kind, pos);
     if (outcome) *outcome = outcome_code(kind, pos);
@@ -1110,7 +1115,15 @@ template <bool WALKS>
 struct FillShared {
   uint32_t words[kSegWords];
 };
-constexpr uint32_t kWalkQueue = 256;  // entries; where there are more the lists are gone through again
+constexpr uint32_t kWalkQueue = 1024;  // entries; where there are more the lists are gone through again
+// a queued entry: its id within the segment, position << 13, kind << 21, stack << 24
+__device__ __forceinline__ uint32_t queue_entry(uint32_t e, uint32_t stack, uint32_t seg_id0) {
+  static_assert(kSegTokens == 1 << 13 && kEntryWalkTop + kCtxLevels + 1 < 8, "the fields of a queued entry");
+  return ((e & kEntryIdMask) - seg_id0) | ((e >> kEntryPosShift) & 0xFFu) << 13 | (e >> kEntryKindShift) << 21 | stack << 24;
+}
+__device__ __forceinline__ uint32_t list_entry(uint32_t q, uint32_t seg_id0) {
+  return ((q & 0x1FFFu) + seg_id0) | ((q >> 13) & 0xFFu) << kEntryPosShift | ((q >> 21) & 7u) << kEntryKindShift;
+}
 // Up to this many entries go to a wave each (walk_wave): six one after the other cost what a lane's longest walk does in
 // a grammar of deep walks (C/SQL-like: 23 -> 17 us for a row with a walk of 79 steps; with up to 64 a row of 4358 steps
 // took 137 us instead of 55, with up to 256 as long).
@@ -1119,7 +1132,7 @@ template <>
 struct FillShared<true> {
   uint32_t words[kSegWords];
   uint16_t live[kFillFramesLds];
-  uint2 queue[kWalkQueue];            // (entry, stack)
+  uint32_t queue[kWalkQueue];
   uint32_t n_queued;                  // counts on beyond the queue's room
   uint32_t mem[kFillThreads / 64][kWaveMemWords];
 };
@@ -1154,7 +1167,7 @@ __device__ __forceinline__ bool walk_start(const WalkRow& row, uint32_t stack, u
 // different waves) or of a list of stack `list_stack` (all threads call this).
 template <bool COUNT, bool KEEP_UNDECIDED, bool INLINE, class Tab>
 __device__ __forceinline__ void fill_walks(const Tab& T, FillShared<true>& sm, const WalkRow& row, const int32_t b, const int32_t id0,
-                                           const XGM_GLOBAL uint32_t* list, const uint32_t list_stack, const uint32_t n,
+                                           const uint32_t n_ids, const XGM_GLOBAL uint32_t* list, const uint32_t list_stack, const uint32_t n,
                                            const DevVocab& voc, OverflowLog* log, uint32_t seq, unsigned long long& my_steps) {
   const bool frames_in_lds = row.n_frames <= kFillFramesLds;
 #pragma unroll 1
@@ -1164,11 +1177,12 @@ __device__ __forceinline__ void fill_walks(const Tab& T, FillShared<true>& sm, c
       e = list[q];
       if ((e >> kEntryKindShift) == kEntryAccepted) continue;
     } else {
-      e = sm.queue[q].x;
-      stack = sm.queue[q].y;
+      e = list_entry(sm.queue[q], (uint32_t)id0 & ~(kSegTokens - 1u));
+      stack = sm.queue[q] >> 24;
     }
     const uint32_t id = e & kEntryIdMask, pos = (e >> kEntryPosShift) & 0xFFu;
     const uint32_t rel = id - (uint32_t)id0;
+    if (list && rel >= n_ids) continue;                      // another part's
     if ((sm.words[rel >> 5] >> (rel & 31u)) & 1u) continue;  // already allowed
     const TokenRef t = load_token(voc, (int32_t)id);
     WalkStart w;
@@ -1193,7 +1207,7 @@ __device__ __forceinline__ void fill_walks_by_wave(const LdsTabT<true, true>& T,
   WaveMem mem{(XGM_LDS uint32_t*)sm.mem[wave], (XGM_LDS uint32_t*)sm.mem[wave] + kArenaFrames};
 #pragma unroll 1
   for (uint32_t q = wave; q < n; q += kFillThreads / 64) {
-    const uint32_t e = uniform(sm.queue[q].x), stack = uniform(sm.queue[q].y);
+    const uint32_t entry = uniform(sm.queue[q]), e = list_entry(entry, (uint32_t)id0 & ~(kSegTokens - 1u)), stack = entry >> 24;
     const uint32_t id = e & kEntryIdMask, pos = (e >> kEntryPosShift) & 0xFFu;
     const uint32_t rel = id - (uint32_t)id0;
     if ((uniform(sm.words[rel >> 5]) >> (rel & 31u)) & 1u) continue;  // already allowed
@@ -1225,20 +1239,23 @@ struct FusedApply {
 
 // INLINE != 0: the states came with the launch (InlineStates, the first argument: read where the arguments lie);
 // rows, stack_hdrs_ and frames_ are then not used.
-template <bool COUNT, int APPLY, uint32_t INLINE, bool WALKS>
+template <bool COUNT, int APPLY, uint32_t INLINE, bool WALKS, bool PARTS = false>
 __global__ __launch_bounds__(kFillThreads, WALKS ? 4 : 8) void fill_kernel(const InlineStates<INLINE> states_, const RowDesc* __restrict__ rows,
                                                             const uint32_t* __restrict__ stack_hdrs_,
                                                             const uint16_t* __restrict__ frames_, DevVocab voc,
                                                             uint32_t* __restrict__ out, OverflowLog* log, uint32_t seq,
-                                                            unsigned long long* step_counter, FusedApply fa) {
+                                                            unsigned long long* step_counter, FusedApply fa, uint32_t part_shift) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ FillShared<WALKS> sm;
   const XGM_GLOBAL uint32_t* stack_hdrs = (const XGM_GLOBAL uint32_t*)stack_hdrs_;
   const uint32_t tid = threadIdx.x;
   const int32_t b = (int32_t)blockIdx.y, seg = (int32_t)blockIdx.x;
-  const int32_t w_begin = seg * kSegWords;
-  const int32_t n_words = min(kSegWords, voc.W - w_begin);
+  // PARTS: 1 << part_shift workgroups share the segment, each with its part of the words (the lists are read by all of them)
+  const int32_t part_words = PARTS ? kSegWords >> part_shift : kSegWords;
+  const int32_t w_begin = seg * kSegWords + (PARTS ? (int32_t)blockIdx.z * part_words : 0);
+  const int32_t n_words = min(part_words, voc.W - w_begin);
   const int32_t id0 = w_begin * 32;
+  const uint32_t n_ids = (uint32_t)part_words * 32u;
   // LDS is cleared before anything is fetched (a barrier waits for what its threads have in flight)
   for (int32_t w = tid; w < kSegWords; w += kFillThreads) sm.words[w] = 0u;
   if constexpr (WALKS)
@@ -1271,13 +1288,15 @@ __global__ __launch_bounds__(kFillThreads, WALKS ? 4 : 8) void fill_kernel(const
   const bool may_end = flags & 1u;
   const int32_t my_stop = may_end && (int32_t)tid < voc.n_stop ? voc.stop_ids[tid] : -1;
   auto take = [&](uint32_t e, uint32_t stack) {
-    if constexpr (WALKS)
+    const uint32_t rel = (e & kEntryIdMask) - (uint32_t)id0;
+    if (PARTS && rel >= n_ids) return;
+    if constexpr (WALKS) {
       if ((e >> kEntryKindShift) != kEntryAccepted) {
         const uint32_t at = atomicAdd(&sm.n_queued, 1u);
-        if (at < kWalkQueue) sm.queue[at] = make_uint2(e, stack);
+        if (at < kWalkQueue) sm.queue[at] = queue_entry(e, stack, (uint32_t)(seg * kSegTokens));
         return;
       }
-    const uint32_t rel = (e & kEntryIdMask) - (uint32_t)id0;
+    }
     atomicOr(&sm.words[rel >> 5], 1u << (rel & 31u));
   };
   // where the lists of a stack begin in this segment, and in the next (the same for every thread)
@@ -1407,9 +1426,9 @@ __global__ __launch_bounds__(kFillThreads, WALKS ? 4 : 8) void fill_kernel(const
         }
         const XGM_GLOBAL uint32_t* from = again ? entries + list.x : nullptr;
         if (small_sections_staged(tab))
-          fill_walks<COUNT, APPLY != 0, INLINE != 0>(LdsTabT<true>(tab, smem), sm, row, b, id0, from, k / kStackLists, list.y - list.x, voc, log, seq, my_steps);
+          fill_walks<COUNT, APPLY != 0, INLINE != 0>(LdsTabT<true>(tab, smem), sm, row, b, id0, n_ids, from, k / kStackLists, list.y - list.x, voc, log, seq, my_steps);
         else
-          fill_walks<COUNT, APPLY != 0, INLINE != 0>(LdsTab(tab, smem), sm, row, b, id0, from, k / kStackLists, list.y - list.x, voc, log, seq, my_steps);
+          fill_walks<COUNT, APPLY != 0, INLINE != 0>(LdsTab(tab, smem), sm, row, b, id0, n_ids, from, k / kStackLists, list.y - list.x, voc, log, seq, my_steps);
       }
       __syncthreads();
       if (COUNT && my_steps) atomicAdd(step_counter, my_steps);
@@ -1418,11 +1437,12 @@ __global__ __launch_bounds__(kFillThreads, WALKS ? 4 : 8) void fill_kernel(const
   // 4. the words, and the logits of the segment; the last segment also takes the columns beyond the vocabulary
   for (int32_t w = tid; w < n_words; w += kFillThreads) out[(size_t)b * voc.W + w_begin + w] = sm.words[w];
   if constexpr (APPLY != 0) {
-    const int32_t e_end = seg + 1 == voc.n_seg ? fa.V_logits : min(id0 + kSegTokens, fa.V_logits), lane = (int32_t)(tid & 63u);
+    const bool last = seg + 1 == voc.n_seg && (!PARTS || blockIdx.z + 1u == 1u << part_shift);
+    const int32_t e_end = last ? fa.V_logits : min(id0 + (int32_t)n_ids, fa.V_logits), lane = (int32_t)(tid & 63u);
     unsigned char* const logits = fa.logits + (size_t)b * fa.row_stride * APPLY;
     for (int32_t e0 = id0 + (int32_t)uniform(tid >> 6) * kApplyWaveElems; e0 < e_end; e0 += kSegTokens) {
       const int32_t e = e0 + lane * 32;  // (words beyond the vocabulary's are zero, and so are the bits of its last one)
-      uint32_t allowed = e < id0 + kSegTokens ? sm.words[(e - id0) >> 5] : 0u;
+      uint32_t allowed = e < id0 + (int32_t)n_ids ? sm.words[(e - id0) >> 5] : 0u;
       if (e + 32 > e_end) allowed |= e < e_end ? ~0u << (e_end - e) : ~0u;
       apply_wave<APPLY>(logits + (size_t)e0 * APPLY, allowed, fa.neg_inf);
     }
@@ -2022,19 +2042,23 @@ void launch_upload_stacks(const void* src, void* dst, size_t plain_bytes, const 
                      reinterpret_cast<const uint4*>(src_stacks), n_stacks, (uint32_t)n_seg, reinterpret_cast<uint32_t*>(dst_hdrs));
 }
 
+// Walks take long, and few rows of a batch have many: where the segments alone do not fill the chip four workgroups share
+// each, if a cache of the batch has many walk entries (C/SQL-like and scripting grammars have 1e4 to 1e6, JSON has
+// 23 at 128256 tokens).  Fill of 32 rows of the scripting grammar, 128256 tokens: 51 -> 27 us; 64 rows of the C/SQL-like
+// one, three draws: 41, 52, 121 -> 32, 34, 53 us; rows that walk little pay 1 us for reading the lists in every part.
+constexpr uint32_t kFillWalkSlots = 4 * 256;  // workgroups that the chip has room for
 template <bool COUNT, int APPLY, uint32_t INLINE>
 static void launch_fill_of(const InlineStates<INLINE>& st, const RowDesc* rows, const uint32_t* stack_hdrs, const uint16_t* frames, int32_t B,
-                           const DevVocab& voc, bool walks, uint32_t* out, OverflowLog* log, uint32_t seq, unsigned long long* step_counter,
+                           const DevVocab& voc, uint32_t walks, uint32_t* out, OverflowLog* log, uint32_t seq, unsigned long long* step_counter,
                            hipStream_t stream, const FusedApply& fa) {
-  const dim3 grid(voc.n_seg, B);
-  if (walks)
-    hipLaunchKernelGGL((fill_kernel<COUNT, APPLY, INLINE, true>), grid, dim3(kFillThreads), kFillLdsBudget, stream, st, rows, stack_hdrs,
-                       frames, voc, out, log, seq, step_counter, fa);
-  else
-    hipLaunchKernelGGL((fill_kernel<false, APPLY, INLINE, false>), grid, dim3(kFillThreads), 0, stream, st, rows, stack_hdrs, frames, voc,
-                       out, log, seq, step_counter, fa);
+  dim3 grid(voc.n_seg, B);
+  const uint32_t n = grid.x * grid.y, part_shift = walks >= kManyWalks && n <= kFillWalkSlots ? 2u : 0u;
+  grid.z = 1u << part_shift;
+  auto kernel = walks == 0u ? fill_kernel<false, APPLY, INLINE, false> : part_shift ? fill_kernel<COUNT, APPLY, INLINE, true, true> : fill_kernel<COUNT, APPLY, INLINE, true>;
+  hipLaunchKernelGGL(kernel, grid, dim3(kFillThreads), walks ? kFillLdsBudget : 0, stream, st, rows, stack_hdrs, frames, voc, out, log, seq,
+                     step_counter, fa, part_shift);
 }
-void launch_fill(const RowDesc* rows, const uint32_t* stack_hdrs, const uint16_t* frames, int32_t B, const DevVocab& voc, bool walks,
+void launch_fill(const RowDesc* rows, const uint32_t* stack_hdrs, const uint16_t* frames, int32_t B, const DevVocab& voc, uint32_t walks,
                  uint32_t* out, OverflowLog* log, uint32_t seq, unsigned long long* step_counter, hipStream_t stream,
                  void* logits, int elem_size, uint32_t neg_inf, int32_t V_logits, int64_t row_stride) {
   if (B <= 0) return;
@@ -2044,14 +2068,14 @@ void launch_fill(const RowDesc* rows, const uint32_t* stack_hdrs, const uint16_t
   launch(InlineStates<0>{}, rows, stack_hdrs, frames, B, voc, walks, out, log, seq, step_counter, stream, fa);
 }
 template <uint32_t WORDS>
-static void launch_fill_inline_of(const uint32_t* states, uint32_t words, int32_t B, const DevVocab& voc, bool walks, uint32_t* out,
+static void launch_fill_inline_of(const uint32_t* states, uint32_t words, int32_t B, const DevVocab& voc, uint32_t walks, uint32_t* out,
                                   OverflowLog* log, uint32_t seq, hipStream_t stream, int elem_size, const FusedApply& fa) {
   InlineStates<WORDS> st;
   std::copy(states, states + words, st.w);
   auto launch = fa.logits ? (elem_size == 2 ? launch_fill_of<false, 2, WORDS> : launch_fill_of<false, 4, WORDS>) : launch_fill_of<false, 0, WORDS>;
   launch(st, nullptr, nullptr, nullptr, B, voc, walks, out, log, seq, nullptr, stream, fa);
 }
-void launch_fill_inline(const uint32_t* states, uint32_t words, int32_t B, const DevVocab& voc, bool walks, uint32_t* out, OverflowLog* log,
+void launch_fill_inline(const uint32_t* states, uint32_t words, int32_t B, const DevVocab& voc, uint32_t walks, uint32_t* out, OverflowLog* log,
                         uint32_t seq, hipStream_t stream, void* logits, int elem_size, uint32_t neg_inf, int32_t V_logits, int64_t row_stride) {
   if (B <= 0) return;
   const FusedApply fa{static_cast<unsigned char*>(logits), row_stride, V_logits, neg_inf};

@@ -139,8 +139,9 @@ struct DevCache {
   const uint32_t* node_ctx_off;  // [n_nodes + 1]
   const uint32_t* node_ctx;
   int32_t n_nodes;
-  uint32_t walks;            // not 0: some list has walk entries
+  uint32_t walks;            // the lists' walk entries, counted up to about kManyWalks
 };
+constexpr uint32_t kManyWalks = 1024;
 constexpr uint32_t kNoAccRow = 0xFFFFu;
 // A list entry: bits 0..19 token id, bits 20..27 position, bits 28..31 kind:
 //   kEntryAccepted       the token is allowed;
@@ -305,7 +306,7 @@ struct ContextListArgs {
   uint32_t n_tiles;
   uint4* res[kCtxLevels];      // (the last one is not used)
   uint32_t res_cap;
-  uint32_t* res_count;         // [kCtxLevels + 1]; the last one: not 0 if some entry is a walk entry
+  uint32_t* res_count;         // [kCtxLevels + 1]; the last one: walk entries, counted up to about kManyWalks
   const uint32_t* k_base[kCtxLevels];
   uint32_t key0[kCtxLevels];   // the first key of level 1, 2, ... in the shared numbering
   const uint32_t* ctx_off;
@@ -346,16 +347,16 @@ void launch_upload_stacks(const void* src, void* dst, size_t plain_bytes, const 
                           int32_t n_seg, void* dst_hdrs, const void* src_frames, void* dst_frames, size_t frames_bytes,
                           hipStream_t stream);
 // (b) batched mask fill: one workgroup per (segment, row)
-// walks: whether some cache of the batch has walk entries.
+// walks: the most walk entries that a cache of the batch has (DevCache::walks).
 // step_counter: null on the hot path; otherwise the counting instantiation is launched.
 // logits != null: the fused instantiation also applies each row's mask to its logits row
 // (elem_size 2 or 4, rows 16-byte aligned; a walk over the limits leaves its token allowed).
 void launch_fill(const RowDesc* rows, const uint32_t* stack_hdrs, const uint16_t* frames, int32_t B,
-                 const DevVocab& voc, bool walks, uint32_t* out, OverflowLog* log, uint32_t seq,
+                 const DevVocab& voc, uint32_t walks, uint32_t* out, OverflowLog* log, uint32_t seq,
                  unsigned long long* step_counter, hipStream_t stream, void* logits = nullptr,
                  int elem_size = 0, uint32_t neg_inf = 0, int32_t V_logits = 0, int64_t row_stride = 0);
 // the same with the states in the launch (InlineStates: `words` of them, at most kInlineWordsLarge); step_counter is not supported
-void launch_fill_inline(const uint32_t* states, uint32_t words, int32_t B, const DevVocab& voc, bool walks, uint32_t* out,
+void launch_fill_inline(const uint32_t* states, uint32_t words, int32_t B, const DevVocab& voc, uint32_t walks, uint32_t* out,
                         OverflowLog* log, uint32_t seq, hipStream_t stream, void* logits, int elem_size, uint32_t neg_inf, int32_t V_logits, int64_t row_stride);
 // device-resident states: move every row on by its token (ids < 0 leave a row alone)
 void launch_batch_accept(const DevBatch& bt, const DevVocab& voc, const int32_t* d_tokens, hipStream_t stream);

@@ -129,8 +129,8 @@ def test_states_in_the_launch(xgm, wl, rows, depth):
 
 
 # A number that ends an expression leaves hundreds of tokens to the walk: few, as many as the queue of a workgroup
-# holds (256), more; in one segment and in several.
-@pytest.mark.parametrize("V", [300, 900, 1000, 1100, 1300, 8191, 8193, 24000])
+# of a workgroup holds (1024), more; in one segment and in several, whole or shared by workgroups (few rows).
+@pytest.mark.parametrize("V", [300, 900, 1000, 1100, 1300, 2047, 2049, 6145, 8191, 8193, 24000, 90000])
 def test_walk_entries(xgm, wl, V):
     vocab = si.make_vocab("bpe", V, 7)
     cache = xgm.Cache(xgm.Grammar(si.PYDSL_GRAMMAR, "root"), wl.make_xgm_vocab(vocab))
