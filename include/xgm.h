@@ -288,10 +288,10 @@ int32_t xgm_matcher_stack(const xgm_matcher* m, int32_t s, int32_t* h_nodes, int
  * gets a row with only the stop tokens.  All matchers must share one
  * vocabulary; their grammars may differ.  B <= 65535.  The call packs the
  * stacks (per stack: its frames and which token lists of the cache are its)
- * into pinned staging owned by the library (a ring of 8 slots), enqueues a
- * small kernel that copies them and looks up where those lists lie, and the
- * fill kernel (one workgroup per row and 8192
- * token ids) on hip_stream, and returns.
+ * and enqueues the fill kernel (a workgroup per row and 8192 token ids, or four)
+ * on hip_stream, and returns.  The stacks of a small batch go along as kernel
+ * arguments; those of a larger one into pinned staging owned by the library (a
+ * ring of 8 slots), from which a small kernel copies them in front of the fill.
  * A walk that exceeds the on-chip bounds (64 frames pushed inside one token,
  * 24 pending alternatives, 4096 steps, tokens longer than 255 bytes) is never
  * guessed: the pair is recorded on the device, its bit is left 0, and
