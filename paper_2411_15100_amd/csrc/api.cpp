@@ -1327,12 +1327,17 @@ static int fill_impl(xgm_matcher* const* ms, int32_t B, int32_t* d_bitmask, void
   const size_t d_bytes = ((off_frames + n_frames * 2 + 63) / 64) * 64;
   const size_t bytes = use_static ? d_bytes + h_bytes : std::max(d_bytes, h_bytes);
 
+  // A replay of a captured launch takes what is staged when it runs, which may be states of other caches: those may have
+  // walk entries where these have none, so that the kernel without walks is out.
+  const bool capturing = use_static && is_capturing(stream);
+  if (capturing) walks = std::max(walks, 1u);
+
   Context& C = ctx();
   std::lock_guard<std::mutex> lock(C.mu);
   // A small batch goes along with the launch (see InlineStates), unless the two kernels are to be looked at one by
   // one or the launch is being captured into a graph (whose replays take what is staged when they run).
   const size_t inline_most = (size_t)B * 2 + n_stacks * kInlineStackWords + (n_frames + 1) / 2;
-  if (inline_most + kInlineCacheWords <= kInlineWordsLarge && !timing && !d_step_counter && !(use_static && is_capturing(stream))) {
+  if (inline_most + kInlineCacheWords <= kInlineWordsLarge && !timing && !d_step_counter && !capturing) {
     FillSlot& slot = C.slot[C.next_slot];
     uint32_t* states = use_static ? C.static_states : slot.states;
     const size_t words = pack_inline(ms, B, n_stacks, n_frames, states);
