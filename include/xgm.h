@@ -315,20 +315,24 @@ int xgm_fill_and_apply(xgm_matcher* const* ms, int32_t B, int32_t* d_bitmask, vo
  * under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc): xgm_fill_next_token_bitmask with its per-call staging in fixed
  * memory.  Same arguments, same result in d_bitmask, same handling of walks
- * over the on-chip limits.  The packed stacks of a
- * small batch go along with the launch as kernel arguments (not under graph
- * capture); those of a larger one are written into a fixed host array and copied, in stream order, into a fixed
+ * over the on-chip limits.  The packed stacks are written into a fixed host
+ * array, which keeps the last call's contents.  A small batch goes along with
+ * the launch as kernel arguments beside that; a larger one, and any batch under
+ * graph capture, is copied from there, in stream order, into a fixed
  * array of XGM_STATIC_STAGING_BYTES (1 MiB) that every device holds from the
  * moment the library is loaded until the process ends, where a kernel writes
- * them out in the form the fill kernel reads (both forms lie in the array);
+ * it out in the form the fill kernel reads (both forms lie in the array);
  * the call makes no hipMalloc / hipHostMalloc / hipFree and uses no event.  A
  * batch whose stacks need more than that returns XGM_ERR_TOO_LARGE (nothing is
  * enqueued); batch 128 at a vocabulary of 151936 needs about 110 KiB.  The
  * mask caches of the matchers must have been built before (they were, or the
- * matchers would not exist).  All calls on one device share the array, which
- * keeps the last call's contents: calls whose work overlaps on one device
- * (different streams, or several host threads) race and must be ordered by
- * the caller; calls on one stream are ordered by the stream. */
+ * matchers would not exist).  All calls share the arrays: calls whose work
+ * overlaps on one device (different streams, or several host threads) race and
+ * must be ordered by the caller; calls on one stream are ordered by the stream.
+ * A captured call copies the host array whenever its graph runs: a replay fills
+ * the masks of the states that the last call before it has staged, which must
+ * be as many rows, stacks and frames as the captured ones, over the same
+ * vocabulary (of any grammars), and the next call must come after the replay. */
 #define XGM_STATIC_STAGING_BYTES (1 << 20)
 int xgm_fill_next_token_bitmask_static(xgm_matcher* const* ms, int32_t B, int32_t* d_bitmask,
                                        void* hip_stream);

@@ -1290,6 +1290,46 @@ static size_t pack_inline(xgm_matcher* const* ms, int32_t B, size_t n_stacks, si
   return used;
 }
 
+// The states of a batch as they are staged: row descriptors | per stack its scalar words and list keys | frames.
+static void pack_staged(xgm_matcher* const* ms, int32_t B, size_t n_stacks, void* h_buf) {
+  auto* rows = reinterpret_cast<RowDesc*>(h_buf);
+  auto* hdrs = reinterpret_cast<uint32_t*>(rows + B);
+  auto* frames = reinterpret_cast<uint16_t*>(hdrs + n_stacks * kStackKeysWords);
+  uint32_t si = 0, fi = 0;
+  for (int32_t b = 0; b < B; ++b) {
+    const xgm_matcher* m = ms[b];
+    RowDesc& r = rows[b];
+    r.epoch = 0;
+    r.stack_begin = si;
+    r.frame_begin = fi;
+    r.n_frames = 0;
+    if (m->terminated) {
+      r.tab = DevTables{};
+      r.acc = r.entries = nullptr;
+      r.n_stacks = 0;
+      r.flags = 1;
+      continue;
+    }
+    const Automaton& A = m->g->A;
+    r.tab = m->c->host.tab;
+    r.acc = m->c->host.acc;
+    r.entries = m->c->host.entries;
+    r.n_stacks = (uint32_t)m->stacks.size();
+    r.flags = Engine(&A).can_terminate(m->stacks) ? 1u : 0u;
+    for (auto& s : m->stacks) {
+      uint32_t* h = hdrs + (size_t)si * kStackKeysWords;
+      stack_keys(A, *m->c, s, fi, h, h + kStackHdrWords);
+      const uintptr_t key_off = reinterpret_cast<uintptr_t>(m->c->host.key_off);
+      h[kStackHdrWords + kStackLists] = (uint32_t)key_off;
+      h[kStackHdrWords + kStackLists + 1] = (uint32_t)((uint64_t)key_off >> 32);
+      for (uint32_t w = kStackHdrWords + kStackLists + 2; w < kStackKeysWords; ++w) h[w] = 0u;
+      ++si;
+      for (int32_t n : s) frames[fi++] = (uint16_t)n;
+      r.n_frames += (uint32_t)s.size();
+    }
+  }
+}
+
 // `use_static`: stage in g_static_host and the device's static scratch array instead of the ring of
 // allocated slots; nothing is allocated on this path.
 static int fill_impl(xgm_matcher* const* ms, int32_t B, int32_t* d_bitmask, void* hip_stream,
@@ -1327,6 +1367,9 @@ static int fill_impl(xgm_matcher* const* ms, int32_t B, int32_t* d_bitmask, void
   const size_t d_bytes = ((off_frames + n_frames * 2 + 63) / 64) * 64;
   const size_t bytes = use_static ? d_bytes + h_bytes : std::max(d_bytes, h_bytes);
 
+  if (use_static && bytes > kStaticScratchBytes)
+    return fail(XGM_ERR_TOO_LARGE, "fill (static staging): the batch's stacks need " + std::to_string(bytes) +
+                                       " bytes of staging, the static array holds " + std::to_string(kStaticScratchBytes));
   // A replay of a captured launch takes what is staged when it runs, which may be states of other caches: those may have
   // walk entries where these have none, so that the kernel without walks is out.
   const bool capturing = use_static && is_capturing(stream);
@@ -1335,7 +1378,8 @@ static int fill_impl(xgm_matcher* const* ms, int32_t B, int32_t* d_bitmask, void
   Context& C = ctx();
   std::lock_guard<std::mutex> lock(C.mu);
   // A small batch goes along with the launch (see InlineStates), unless the two kernels are to be looked at one by
-  // one or the launch is being captured into a graph (whose replays take what is staged when they run).
+  // one or the launch is being captured into a graph.  The entry point that allocates nothing stages it all the same:
+  // replays of a captured call take what the last call has staged.
   const size_t inline_most = (size_t)B * 2 + n_stacks * kInlineStackWords + (n_frames + 1) / 2;
   if (inline_most + kInlineCacheWords <= kInlineWordsLarge && !timing && !d_step_counter && !capturing) {
     FillSlot& slot = C.slot[C.next_slot];
@@ -1344,6 +1388,7 @@ static int fill_impl(xgm_matcher* const* ms, int32_t B, int32_t* d_bitmask, void
     if (words != 0) {
       if (use_static && !C.d_log) return fail(XGM_ERR_INTERNAL, "fill (static staging): the library's device context does not exist yet");
       OverflowLog* log = overflow_log();
+      if (use_static) pack_staged(ms, B, n_stacks, g_static_host);
       const uint32_t seq = ++C.seq;
       launch_fill_inline(states, (uint32_t)words, B, v->dv, walks, reinterpret_cast<uint32_t*>(d_bitmask), log, seq, stream,
                          fused ? fused->d_logits : nullptr, fused ? fused->esize : 0, fused ? fused->neg_inf : 0u,
@@ -1361,9 +1406,6 @@ static int fill_impl(xgm_matcher* const* ms, int32_t B, int32_t* d_bitmask, void
   void* d_buf = nullptr;
   FillSlot* ring = nullptr;
   if (use_static) {
-    if (bytes > kStaticScratchBytes)
-      return fail(XGM_ERR_TOO_LARGE, "fill (static staging): the batch's stacks need " + std::to_string(bytes) +
-                                         " bytes of staging, the static array holds " + std::to_string(kStaticScratchBytes));
     HIP_OK(static_scratch(&d_buf));
     h_buf = g_static_host;
   } else {
@@ -1383,42 +1425,7 @@ static int fill_impl(xgm_matcher* const* ms, int32_t B, int32_t* d_bitmask, void
     h_buf = slot.h_buf;
     d_buf = slot.d_buf;
   }
-  auto* rows = reinterpret_cast<RowDesc*>(h_buf);
-  auto* hdrs = reinterpret_cast<uint32_t*>((char*)h_buf + off_stacks);
-  auto* frames = reinterpret_cast<uint16_t*>((char*)h_buf + h_off_frames);
-  uint32_t si = 0, fi = 0;
-  for (int32_t b = 0; b < B; ++b) {
-    const xgm_matcher* m = ms[b];
-    RowDesc& r = rows[b];
-    r.epoch = 0;
-    r.stack_begin = si;
-    r.frame_begin = fi;
-    r.n_frames = 0;
-    if (m->terminated) {
-      r.tab = DevTables{};
-      r.acc = r.entries = nullptr;
-      r.n_stacks = 0;
-      r.flags = 1;
-      continue;
-    }
-    const Automaton& A = m->g->A;
-    r.tab = m->c->host.tab;
-    r.acc = m->c->host.acc;
-    r.entries = m->c->host.entries;
-    r.n_stacks = (uint32_t)m->stacks.size();
-    r.flags = Engine(&A).can_terminate(m->stacks) ? 1u : 0u;
-    for (auto& s : m->stacks) {
-      uint32_t* h = hdrs + (size_t)si * kStackKeysWords;
-      stack_keys(A, *m->c, s, fi, h, h + kStackHdrWords);
-      const uintptr_t key_off = reinterpret_cast<uintptr_t>(m->c->host.key_off);
-      h[kStackHdrWords + kStackLists] = (uint32_t)key_off;
-      h[kStackHdrWords + kStackLists + 1] = (uint32_t)((uint64_t)key_off >> 32);
-      for (uint32_t w = kStackHdrWords + kStackLists + 2; w < kStackKeysWords; ++w) h[w] = 0u;
-      ++si;
-      for (int32_t n : s) frames[fi++] = (uint16_t)n;
-      r.n_frames += (uint32_t)s.size();
-    }
-  }
+  pack_staged(ms, B, n_stacks, h_buf);
   if (timing) HIP_OK(hipEventRecord(timing[0], stream));
   const void* src = ring ? ring->h_dev : (const void*)((char*)d_buf + d_bytes);
   if (use_static) HIP_OK(hipMemcpyAsync((char*)d_buf + d_bytes, h_buf, h_bytes, hipMemcpyHostToDevice, stream));

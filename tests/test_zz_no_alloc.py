@@ -93,8 +93,9 @@ def test_static_staging_fill_rejects_what_does_not_fit():
 
 
 # A replay of a captured call fills the masks of the states staged last (of the same rows, stacks and frames), also
-# where those walk tokens at run time and the captured ones did not.
-@pytest.mark.parametrize("rows", [130])
+# where those walk tokens at run time and the captured ones did not: 130 rows, and 1 and 3, whose own calls take their
+# states along with the launch.
+@pytest.mark.parametrize("rows", [1, 3, 130])
 def test_replays_of_a_captured_fill_take_the_states_staged_last(rows):
     import paper_2411_15100_amd as xgm
     from paper_2411_15100_amd import workloads as wl
