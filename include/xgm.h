@@ -231,6 +231,9 @@ int64_t xgm_cache_device_bytes(const xgm_cache* c);
  * in all, [4] of them accepted tokens of nodes that keep a list, [5] context-dependent (node, token) pairs
  * the lists were made from, [6] (pair, context) combinations examined at build time, [7] bitset rows. */
 int xgm_cache_stats(const xgm_cache* c, int64_t* h_out8);
+/* For tests: entries of the lists that a fill has to walk, counted up to about 1024 (0: fills of such caches run a
+ * kernel that cannot walk). */
+int32_t xgm_debug_cache_walk_entries(const xgm_cache* c);
 
 /* The exact host routine that decides a (node, token) pair whose GPU walk
  * exceeded its limits during xgm_cache_build: 0 rejected, 1 context-dependent,

@@ -71,6 +71,7 @@ SIGNATURES = {
     "xgm_cache_num_accept_rows": (_i32, [_vp]),
     "xgm_cache_device_bytes": (ctypes.c_int64, [_vp]),
     "xgm_cache_stats": (_i32, [_vp, _vp]),
+    "xgm_debug_cache_walk_entries": (_i32, [_vp]),
     "xgm_matcher_create": (_i32, [_vp, _pp]),
     "xgm_matcher_create_host": (_i32, [_vp, _vp, _pp]),
     "xgm_matcher_destroy": (None, [_vp]),
@@ -333,6 +334,10 @@ class Cache:
     def device_bytes(self) -> int:
         """Bytes of device memory the cache holds."""
         return int(load_library().xgm_cache_device_bytes(self._h))
+
+    def debug_walk_entries(self) -> int:
+        """Entries of the cache's lists that a fill walks, counted up to about 1024."""
+        return _check(load_library().xgm_debug_cache_walk_entries(self._h))
 
     def copy_node_bits(self, node: int, with_uncertain: bool = True):
         """(accepted, context-dependent) bitsets of a node; the second needs keep_plain=True at build time

@@ -1078,6 +1078,10 @@ int xgm_cache_stats(const xgm_cache* c, int64_t* h_out8) {
   return XGM_OK;
 }
 
+int32_t xgm_debug_cache_walk_entries(const xgm_cache* c) {
+  return c ? (int32_t)std::min<uint32_t>(c->host.walks, INT32_MAX) : fail(XGM_ERR_BAD_ARG, "cache_walk_entries: null cache");
+}
+
 int xgm_cache_copy_node_bits(const xgm_cache* c, int32_t node, int32_t* h_acc, int32_t* h_unc) {
   API_BEGIN
   if (!c || node < 0 || node >= c->host.n_nodes) return fail(XGM_ERR_BAD_ARG, "copy_node_bits: bad cache or node");

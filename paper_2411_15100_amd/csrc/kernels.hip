@@ -1992,6 +1992,8 @@ void launch_exit_positions(const DevTables& tab, const DevVocab& voc, const Cont
 }
 
 void launch_context_lists(const DevTables& tab, const DevVocab& voc, const ContextListArgs& args, bool write, hipStream_t stream) {
+  // (the caller reads the counters also where there is nothing to count)
+  if (!(write && args.outcomes)) (void)hipMemsetAsync(args.res_count, 0, 4 * (kCtxLevels + 1), stream);
   if (args.total == 0 || args.n_tiles == 0) return;
   const DevTables st = staged_for(tab, kContextLdsBudget);
   const dim3 g1(args.n_tiles), g2(1024);
@@ -2010,7 +2012,6 @@ void launch_context_lists(const DevTables& tab, const DevVocab& voc, const Conte
     }
     return;
   }
-  (void)hipMemsetAsync(args.res_count, 0, 4 * (kCtxLevels + 1), stream);
   if (write) hipLaunchKernelGGL(context_level1_kernel<true>, g1, dim3(kContextThreads), st.stage_bytes, stream, st, voc, args);
   else hipLaunchKernelGGL(context_level1_kernel<false>, g1, dim3(kContextThreads), st.stage_bytes, stream, st, voc, args);
   for (uint32_t level = 2; level <= (uint32_t)kCtxLevels && args.k_base[level - 1] != nullptr; ++level) {

@@ -182,3 +182,26 @@ def test_apply_rows_that_begin_anywhere(xgm, dtype_name, V, Vl):
                 row = expect[offset + r * stride:offset + r * stride + Vl]
                 row[~want[j]] = ninf
             assert np.array_equal(buf.cpu().numpy().view(udt), expect), (offset, stride)
+
+
+# The number of walk entries decides which kernel fills.  Builds share their temporary memory: these two, both of at most
+# 32 nodes, 64 tokens and 64 list keys, lay it out alike, so that the second finds the first one's counters there.
+def test_a_grammar_without_contexts_has_no_walk_entries(xgm, wl):
+    toks = [b"[", b"]", b"x", b"y"] + [b"]" * k for k in range(2, 10)] + [b"q" * k for k in range(1, 52)] + [b""]
+    assert len(toks) == 64
+
+    class V_:
+        data = np.frombuffer(b"".join(toks), dtype=np.uint8).copy()
+        offsets = np.concatenate([[0], np.cumsum([len(t) for t in toks])]).astype(np.int64)
+        stop_ids = np.array([63], dtype=np.int32)
+
+    xv = wl.make_xgm_vocab(V_)
+    nested = xgm.Grammar('root ::= "[" root "]" | "x"', "root")
+    flat = xgm.Grammar('root ::= [xy]* "]"', "root")
+    for _ in range(2):
+        first = xgm.Cache(nested, xv)
+    assert first.num_nodes <= 32 and first.stats["keys"] <= 64 and 0 < first.stats["context_dependent_pairs"] <= 64, first.stats
+    assert first.debug_walk_entries() > 0
+    second = xgm.Cache(flat, xv)
+    assert second.num_nodes <= 32 and second.stats["context_dependent_pairs"] == 0
+    assert second.debug_walk_entries() == 0
