@@ -118,7 +118,11 @@ PyObject* matcher_accept_token(PyObject* self, PyObject* const* args, Py_ssize_t
   int64_t v[1];
   void* h;
   if (!arguments("accept_token", args, n, kwnames, names, 1, a) || !values(a, v, "n") || !attribute(self, s_h, &h)) return nullptr;
-  return result(api.matcher_accept_token(h, (int32_t)v[0]));
+  int rc;  // (a token of an ambiguous grammar, or a long one, may take milliseconds)
+  Py_BEGIN_ALLOW_THREADS
+  rc = api.matcher_accept_token(h, (int32_t)v[0]);
+  Py_END_ALLOW_THREADS
+  return result(rc);
 }
 PyObject* matcher_accept_bytes(PyObject* self, PyObject* const* args, Py_ssize_t n, PyObject* kwnames) {
   static const char* const names[] = {"data"};
@@ -128,8 +132,7 @@ PyObject* matcher_accept_bytes(PyObject* self, PyObject* const* args, Py_ssize_t
   void* h;
   if (!arguments("accept_bytes", args, n, kwnames, names, 1, a) || PyBytes_AsStringAndSize(a[0], &bytes, &len) < 0 || !attribute(self, s_h, &h))
     return nullptr;
-  if (len <= 64) return result(api.matcher_accept_bytes(h, (const uint8_t*)bytes, (int32_t)len));
-  int rc;  // (a long text takes longer than letting other threads run)
+  int rc;
   Py_BEGIN_ALLOW_THREADS
   rc = api.matcher_accept_bytes(h, (const uint8_t*)bytes, (int32_t)len);
   Py_END_ALLOW_THREADS
@@ -138,7 +141,11 @@ PyObject* matcher_accept_bytes(PyObject* self, PyObject* const* args, Py_ssize_t
 PyObject* matcher_reset(PyObject* self, PyObject*) {
   void* h;
   if (!attribute(self, s_h, &h)) return nullptr;
-  return result(api.matcher_reset(h));
+  int rc;
+  Py_BEGIN_ALLOW_THREADS
+  rc = api.matcher_reset(h);
+  Py_END_ALLOW_THREADS
+  return result(rc);
 }
 
 // ---- methods of DeviceBatch

@@ -6,6 +6,9 @@ a node is named by its rule and a symbol path from the rule's start)."""
 import ctypes
 import os
 import re
+import sys
+import threading
+import time
 import zlib
 
 import numpy as np
@@ -538,3 +541,39 @@ def test_binding_refuses_what_is_no_number_and_keeps_a_sequence_alive():
         with pytest.raises(xgm.XgmError) as e:
             xgm.fill_next_token_bitmask(matchers, 64)
         assert e.value.status == -1
+
+
+@pytest.mark.parametrize("call", ["accept_token", "accept_bytes"])
+def test_other_threads_run_while_a_token_is_accepted(call):
+    """A token of a megabyte, and a few bytes that each double the number of parallel stacks: another thread goes on
+    meanwhile."""
+    long_token, doubling = b'"' + b"a" * (1 << 20), b"x" * 15
+    v = xgm.Vocab(np.frombuffer(long_token, dtype=np.uint8), np.array([0, len(long_token)], dtype=np.int64), [])
+    text = si.JSON_GRAMMAR if call == "accept_token" else 'root ::= a | b\na ::= "x" root? "p"\nb ::= "x" root? "q"'
+    m = xgm.Matcher(grammar=xgm.Grammar(text, "root"), vocab=v)
+    turns, stop = [0], threading.Event()
+
+    def other():
+        while not stop.is_set():
+            turns[0] += 1
+            time.sleep(1e-4)
+
+    interval = sys.getswitchinterval()
+    thread = threading.Thread(target=other)
+    try:
+        sys.setswitchinterval(100.0)   # the lock changes hands only where it is let go
+        thread.start()
+        time.sleep(0.01)
+        before = turns[0]
+        if call == "accept_token":
+            m.accept_token(0)
+        else:
+            with pytest.raises(xgm.XgmError) as e:
+                m.accept_bytes(doubling)
+            assert e.value.status == -8
+        during = turns[0] - before
+    finally:
+        sys.setswitchinterval(interval)
+        stop.set()
+        thread.join()
+    assert during > 0
