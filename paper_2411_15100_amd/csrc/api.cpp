@@ -233,7 +233,7 @@ struct xgm_batch {
   int32_t B = 0, H = 0;
   xgm_vocab* v = nullptr;
   std::vector<xgm_cache*> caches;  // one per row (referenced)
-  uint32_t walks = 0;              // the most walk entries that one of them has (DevCache::walks)
+  FillWalks walks;                 // what their walks need
   DevBatch dev{};
   std::vector<void*> dev_ptrs;
   // walks over the on-chip limits: the batch's own log, how much of it has been examined, and where the last
@@ -1344,14 +1344,14 @@ static int fill_impl(xgm_matcher* const* ms, int32_t B, int32_t* d_bitmask, void
   if (B > 65535) return fail(XGM_ERR_TOO_LARGE, "fill: more than 65535 rows in one call");
   xgm_vocab* v = nullptr;
   size_t n_stacks = 0, n_frames = 0;
-  uint32_t walks = 0;
+  FillWalks walks;
   for (int32_t b = 0; b < B; ++b) {
     const xgm_matcher* m = ms[b];
     if (!m || !m->c) return fail(XGM_ERR_BAD_ARG, "fill: matcher is null or has no cache");
     if (v && m->v != v) return fail(XGM_ERR_BAD_ARG, "fill: all matchers must share one vocabulary");
     v = m->v;
     if (m->terminated) continue;
-    walks = std::max(walks, m->c->host.walks);
+    walks.add(m->c->host);
     n_stacks += m->stacks.size();
     for (auto& s : m->stacks) {
       if (s.size() > XGM_MAX_STACK_DEPTH) return fail(XGM_ERR_TOO_LARGE, "fill: stack deeper than 4096 frames");
@@ -1375,9 +1375,9 @@ static int fill_impl(xgm_matcher* const* ms, int32_t B, int32_t* d_bitmask, void
     return fail(XGM_ERR_TOO_LARGE, "fill (static staging): the batch's stacks need " + std::to_string(bytes) +
                                        " bytes of staging, the static array holds " + std::to_string(kStaticScratchBytes));
   // A replay of a captured launch takes what is staged when it runs, which may be states of other caches: those may have
-  // walk entries where these have none, so that the kernel without walks is out.
+  // walk entries where these have none, or larger tables.
   const bool capturing = use_static && is_capturing(stream);
-  if (capturing) walks = std::max(walks, 1u);
+  if (capturing) walks = FillWalks{std::max(walks.entries, 1u), kFillLdsBudget};
 
   Context& C = ctx();
   std::lock_guard<std::mutex> lock(C.mu);
@@ -1759,7 +1759,7 @@ int xgm_batch_create(xgm_matcher* const* ms, int32_t B, int32_t history, void* h
     for (int32_t b = 0; b < B; ++b) {
       bt->caches.push_back(ms[b]->c);
       ++ms[b]->c->refs;
-      bt->walks = std::max(bt->walks, ms[b]->c->host.walks);
+      bt->walks.add(ms[b]->c->host);
     }
     auto keep = [&](auto* p) { bt->dev_ptrs.push_back((void*)p); return p; };
     const size_t hdr_words = stack_hdr_stride(v->dv.n_seg);

@@ -1103,8 +1103,8 @@ constexpr int kFillFramesLds = 1024;            // live frames kept in LDS (deep
 // WALKS = false: no mask cache of the batch has a walk entry (a cache knows:
 // schema grammars have none) and step 3 is left out; the kernel then fits eight
 // workgroups per compute unit (registers, LDS) and needs no scratch memory.
-// WALKS = true: four workgroups per compute unit, with room for the walk's
-// registers and for the tables of all but the largest grammars.  With one
+// WALKS = true: up to seven workgroups per compute unit (scalar registers), as many
+// as have room for the batch's tables in LDS (four at 31 KB).  With one
 // kernel for both the walk was a function of its own, which spilled in its
 // inner loop and cost 5 us before its first step: the fill of a
 // row that walks a handful of tokens (C/SQL-like grammar, 128256 tokens, one row)
@@ -2047,19 +2047,23 @@ void launch_upload_stacks(const void* src, void* dst, size_t plain_bytes, const 
 // each, if a cache of the batch has many walk entries (C/SQL-like and scripting grammars have 1e4 to 1e6, JSON has
 // 23 at 128256 tokens).  Fill of 32 rows of the scripting grammar, 128256 tokens: 51 -> 27 us; 64 rows of the C/SQL-like
 // one, three draws: 41, 52, 121 -> 32, 34, 53 us; rows that walk little pay 1 us for reading the lists in every part.
-constexpr uint32_t kFillWalkSlots = 4 * 256;  // workgroups that the chip has room for
+// A workgroup's LDS is what the tables of the batch's caches with walk entries need, so that a full batch whose rows hardly
+// ever walk does not run four workgroups per compute unit for it: one launch of 128 JSON rows x 151936, mask and bf16
+// logits, 10.83 us with 31 KB for all of them, 9.84 so; 127 schema rows and one JSON row, or one of the scripting
+// grammar, 9.3 and 8.46 (8.25 without that row); batches of rows that walk a lot take as long either way.
+constexpr uint32_t kFillWalkSlots = 4 * 256;  // workgroups that the chip has room for if each has 31 KB of tables
 template <bool COUNT, int APPLY, uint32_t INLINE>
 static void launch_fill_of(const InlineStates<INLINE>& st, const RowDesc* rows, const uint32_t* stack_hdrs, const uint16_t* frames, int32_t B,
-                           const DevVocab& voc, uint32_t walks, uint32_t* out, OverflowLog* log, uint32_t seq, unsigned long long* step_counter,
+                           const DevVocab& voc, const FillWalks& walks, uint32_t* out, OverflowLog* log, uint32_t seq, unsigned long long* step_counter,
                            hipStream_t stream, const FusedApply& fa) {
   dim3 grid(voc.n_seg, B);
-  const uint32_t n = grid.x * grid.y, part_shift = walks >= kManyWalks && n <= kFillWalkSlots ? 2u : 0u;
+  const uint32_t n = grid.x * grid.y, part_shift = walks.entries >= kManyWalks && n <= kFillWalkSlots ? 2u : 0u;
   grid.z = 1u << part_shift;
-  auto kernel = walks == 0u ? fill_kernel<false, APPLY, INLINE, false> : part_shift ? fill_kernel<COUNT, APPLY, INLINE, true, true> : fill_kernel<COUNT, APPLY, INLINE, true>;
-  hipLaunchKernelGGL(kernel, grid, dim3(kFillThreads), walks ? kFillLdsBudget : 0, stream, st, rows, stack_hdrs, frames, voc, out, log, seq,
+  auto kernel = walks.entries == 0u ? fill_kernel<false, APPLY, INLINE, false> : part_shift ? fill_kernel<COUNT, APPLY, INLINE, true, true> : fill_kernel<COUNT, APPLY, INLINE, true>;
+  hipLaunchKernelGGL(kernel, grid, dim3(kFillThreads), walks.table_bytes, stream, st, rows, stack_hdrs, frames, voc, out, log, seq,
                      step_counter, fa, part_shift);
 }
-void launch_fill(const RowDesc* rows, const uint32_t* stack_hdrs, const uint16_t* frames, int32_t B, const DevVocab& voc, uint32_t walks,
+void launch_fill(const RowDesc* rows, const uint32_t* stack_hdrs, const uint16_t* frames, int32_t B, const DevVocab& voc, const FillWalks& walks,
                  uint32_t* out, OverflowLog* log, uint32_t seq, unsigned long long* step_counter, hipStream_t stream,
                  void* logits, int elem_size, uint32_t neg_inf, int32_t V_logits, int64_t row_stride) {
   if (B <= 0) return;
@@ -2069,14 +2073,14 @@ void launch_fill(const RowDesc* rows, const uint32_t* stack_hdrs, const uint16_t
   launch(InlineStates<0>{}, rows, stack_hdrs, frames, B, voc, walks, out, log, seq, step_counter, stream, fa);
 }
 template <uint32_t WORDS>
-static void launch_fill_inline_of(const uint32_t* states, uint32_t words, int32_t B, const DevVocab& voc, uint32_t walks, uint32_t* out,
+static void launch_fill_inline_of(const uint32_t* states, uint32_t words, int32_t B, const DevVocab& voc, const FillWalks& walks, uint32_t* out,
                                   OverflowLog* log, uint32_t seq, hipStream_t stream, int elem_size, const FusedApply& fa) {
   InlineStates<WORDS> st;
   std::copy(states, states + words, st.w);
   auto launch = fa.logits ? (elem_size == 2 ? launch_fill_of<false, 2, WORDS> : launch_fill_of<false, 4, WORDS>) : launch_fill_of<false, 0, WORDS>;
   launch(st, nullptr, nullptr, nullptr, B, voc, walks, out, log, seq, nullptr, stream, fa);
 }
-void launch_fill_inline(const uint32_t* states, uint32_t words, int32_t B, const DevVocab& voc, uint32_t walks, uint32_t* out, OverflowLog* log,
+void launch_fill_inline(const uint32_t* states, uint32_t words, int32_t B, const DevVocab& voc, const FillWalks& walks, uint32_t* out, OverflowLog* log,
                         uint32_t seq, hipStream_t stream, void* logits, int elem_size, uint32_t neg_inf, int32_t V_logits, int64_t row_stride) {
   if (B <= 0) return;
   const FusedApply fa{static_cast<unsigned char*>(logits), row_stride, V_logits, neg_inf};

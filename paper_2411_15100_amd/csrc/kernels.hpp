@@ -61,7 +61,7 @@ struct TabView {
 // LDS budgets (bytes of dynamic shared memory) for the staged tables
 constexpr int32_t kClassifyLdsBudget = 76 * 1024;
 constexpr int32_t kContextLdsBudget = 68 * 1024;  // the list kernels keep 8 KB of counters beside the tables
-constexpr int32_t kFillLdsBudget = 31 * 1024;     // of the fill kernel that walks (it runs four workgroups per compute unit)
+constexpr int32_t kFillLdsBudget = 31 * 1024;     // of the fill kernel that walks, at most (four workgroups per compute unit then)
 constexpr int32_t kAcceptLdsBudget = 64 * 1024;   // (a row is one workgroup: there is room for one or two per compute unit)
 // The staging split for a kernel that has `budget` bytes of LDS for the tables:
 // as many whole sections as fit, then as many headers as fit.
@@ -347,16 +347,25 @@ void launch_upload_stacks(const void* src, void* dst, size_t plain_bytes, const 
                           int32_t n_seg, void* dst_hdrs, const void* src_frames, void* dst_frames, size_t frames_bytes,
                           hipStream_t stream);
 // (b) batched mask fill: one workgroup per (segment, row)
-// walks: the most walk entries that a cache of the batch has (DevCache::walks).
+// walks: what the walks of the batch's caches need.
 // step_counter: null on the hot path; otherwise the counting instantiation is launched.
 // logits != null: the fused instantiation also applies each row's mask to its logits row
 // (elem_size 2 or 4, rows 16-byte aligned; a walk over the limits leaves its token allowed).
+struct FillWalks {
+  uint32_t entries = 0;      // the most walk entries that one of them has (DevCache::walks)
+  uint32_t table_bytes = 0;  // the most LDS that one with walk entries wants for its tables
+  void add(const DevCache& c) {
+    if (c.walks == 0u) return;
+    entries = entries > c.walks ? entries : c.walks;
+    table_bytes = table_bytes > c.tab.stage_bytes ? table_bytes : c.tab.stage_bytes;
+  }
+};
 void launch_fill(const RowDesc* rows, const uint32_t* stack_hdrs, const uint16_t* frames, int32_t B,
-                 const DevVocab& voc, uint32_t walks, uint32_t* out, OverflowLog* log, uint32_t seq,
+                 const DevVocab& voc, const FillWalks& walks, uint32_t* out, OverflowLog* log, uint32_t seq,
                  unsigned long long* step_counter, hipStream_t stream, void* logits = nullptr,
                  int elem_size = 0, uint32_t neg_inf = 0, int32_t V_logits = 0, int64_t row_stride = 0);
 // the same with the states in the launch (InlineStates: `words` of them, at most kInlineWordsLarge); step_counter is not supported
-void launch_fill_inline(const uint32_t* states, uint32_t words, int32_t B, const DevVocab& voc, uint32_t walks, uint32_t* out,
+void launch_fill_inline(const uint32_t* states, uint32_t words, int32_t B, const DevVocab& voc, const FillWalks& walks, uint32_t* out,
                         OverflowLog* log, uint32_t seq, hipStream_t stream, void* logits, int elem_size, uint32_t neg_inf, int32_t V_logits, int64_t row_stride);
 // device-resident states: move every row on by its token (ids < 0 leave a row alone)
 void launch_batch_accept(const DevBatch& bt, const DevVocab& voc, const int32_t* d_tokens, hipStream_t stream);

@@ -205,3 +205,55 @@ def test_a_grammar_without_contexts_has_no_walk_entries(xgm, wl):
     second = xgm.Cache(flat, xv)
     assert second.num_nodes <= 32 and second.stats["context_dependent_pairs"] == 0
     assert second.debug_walk_entries() == 0
+
+
+# A fill that walks stages the tables of the caches that have walk entries as far as they fit 31 KB: all of them, without
+# the last headers, without the sections in front of those (1000 rules have 32 KB of FOLLOW sets); beside a row with
+# small tables.
+@pytest.mark.parametrize("rules", [1, 60, 500, 800, 900, 1000, 1400])
+def test_walks_by_tables_of_all_sizes(xgm, wl, rules):
+    name = lambda k: "".join(chr(ord("a") + k // 26 ** j % 26) for j in range(3))
+    text = ['root ::= item ("," item)*', 'item ::= "[" root "]" | "{" root "}" | ' + " | ".join(f"k{k}" for k in range(rules))]
+    text += [f'k{k} ::= "{name(k)}" ("(" k{k * 7 % rules} ")" | k{k * 5 % rules} "." )?' for k in range(rules)]
+    text = "\n".join(text)
+    toks = [bytes([c]) for c in b"[]{}(),.abcdefghijklmnopqrstuvwxyz"] + [b"]" * k for k in range(2, 40)] + [b"]}" * k for k in range(1, 20)]
+    toks += [b"]]}]]," + name(k).encode() for k in range(0, rules, 1 + rules // 30)] + [b"]]]]]][[", b"]]]]]],aaa", b""]
+
+    class V_:
+        data = np.frombuffer(b"".join(toks), dtype=np.uint8).copy()
+        offsets = np.concatenate([[0], np.cumsum([len(t) for t in toks])]).astype(np.int64)
+        stop_ids = np.array([len(toks) - 1], dtype=np.int32)
+
+    xv = wl.make_xgm_vocab(V_)
+    texts = [text, si.JSON_GRAMMAR]
+    caches = [xgm.Cache(xgm.Grammar(t, "root"), xv) for t in texts]
+    ogs = [oracle.Grammar(t, "root") for t in texts]
+    assert all(c.debug_walk_entries() > 0 for c in caches)
+    starts = [(0, b"[[[[[[aaa"), (1, b"[[[[[[1"), (0, b"[[{[[[[{[[aaa"), (0, b"aaa"), (1, b'{"a":[[[[[[{"b":1'), (0, b"[" * 30 + b"aaa")]
+    ms, want = [], []
+    for k, start in starts:
+        m, om = xgm.Matcher(cache=caches[k]), oracle.EarleyMatcher(ogs[k])
+        m.accept_bytes(start)
+        assert om.advance(start)
+        ms.append(m)
+        want.append(om.mask(V_))
+    want = np.stack(want)
+    bits = oracle.pack_bitmask(want)
+    columns = (len(toks) + 7) // 8 * 8
+    for rows in ([0, 1, 2, 3, 4, 5], [0], [1, 4], [b % 6 for b in range(300)]):
+        some = [ms[b] for b in rows]
+        resident = xgm.DeviceBatch(some, history=0, stream=_stream())
+        d_mask = torch.full((len(rows), bits.shape[1]), -1, dtype=torch.int32, device="cuda")
+        calls = [lambda lg: xgm.fill_next_token_bitmask(some, d_mask.data_ptr(), _stream()),
+                 lambda lg: resident.fill_next_token_bitmask(d_mask.data_ptr(), _stream()),
+                 lambda lg: xgm.fill_and_apply(some, d_mask.data_ptr(), lg.data_ptr(), xgm.DTYPE_F32, columns, columns, _stream()),
+                 lambda lg: resident.fill_and_apply(d_mask.data_ptr(), lg.data_ptr(), xgm.DTYPE_F32, columns, columns, _stream())]
+        for k, call in enumerate(calls):
+            d_mask.fill_(-1)
+            logits = torch.ones((len(rows), columns), device="cuda")
+            call(logits)
+            assert np.array_equal(d_mask.cpu().numpy(), bits[rows]), (rows[:8], k)
+            if k >= 2:
+                assert np.array_equal(logits.cpu().numpy()[:, :len(toks)] == 1.0, want[rows]), (rows[:8], k)
+        assert xgm.debug_fill_count_steps(xgm.MatcherBatch(some), d_mask.data_ptr(), _stream()) > 0
+        assert np.array_equal(d_mask.cpu().numpy(), bits[rows])
