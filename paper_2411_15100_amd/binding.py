@@ -157,7 +157,7 @@ def load_library():
     try:
         from . import _native
     except ImportError as e:
-        raise ImportError("the extension _native is missing: build it with `python -m paper_2411_15100_amd.build`") from e
+        raise ImportError("the extension _native is missing for this Python: build it with `python -m paper_2411_15100_amd.build`") from e
     _native.install({name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in SIGNATURES}, XgmError, Matcher, DeviceBatch)
     _fast = _native
     _lib = lib

@@ -7,6 +7,7 @@ import ctypes
 import os
 import re
 import sys
+import sysconfig
 import threading
 import time
 import zlib
@@ -577,3 +578,11 @@ def test_other_threads_run_while_a_token_is_accepted(call):
         stop.set()
         thread.join()
     assert during > 0
+
+
+def test_the_extension_is_the_one_of_this_python():
+    """Its file carries this Python's tag; one without a tag, which any Python would load, is not there."""
+    from paper_2411_15100_amd import _native, build
+    assert os.path.samefile(_native.__file__, build.EXT)
+    assert os.path.basename(build.EXT) == "_native" + sysconfig.get_config_var("EXT_SUFFIX") != "_native.so"
+    assert not os.path.exists(build.EXT_UNTAGGED)
