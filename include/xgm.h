@@ -461,11 +461,12 @@ const uint32_t* xgm_batch_overflow_count_device(const xgm_batch* bt);
  * lookups of the token walks (section 3.1, 3.3) are reads of this kind, each
  * depending on the one before. */
 int xgm_debug_lds_lookup_rate(void* hip_stream, double* h_lookups_per_second);
-/* For tests without a device: accept a token with the routine the device uses
- * (a depth-first walk over the flattened tables that writes out every stack
- * the token can end in) instead of the host engine.  Same results and errors
- * as xgm_matcher_accept_token, plus XGM_ERR_TOO_LARGE when the walk's limits
- * are hit. */
+/* For tests without a device: accept a token with the kernels' depth-first walk
+ * over the flattened tables, as a lane does it, writing out every stack the token
+ * can end in, instead of the host engine.  (xgm_batch_accept_tokens walks the same
+ * paths with a whole wave and orders the stacks by comparing all pairs; both forms
+ * are compared with the host engine.)  Same results and errors as
+ * xgm_matcher_accept_token, plus XGM_ERR_TOO_LARGE when the walk's limits are hit. */
 int xgm_debug_matcher_accept_token_walk(xgm_matcher* m, int32_t token_id);
 
 /* --------------------------------------------------------------------- apply

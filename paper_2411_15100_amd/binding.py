@@ -389,7 +389,7 @@ class Matcher:
         return load_library().xgm_matcher_accept_token(self._h, int(token_id))
 
     def debug_try_accept_token_walk(self, token_id: int) -> int:
-        """accept_token through the depth-first walk the device uses (status code)."""
+        """accept_token through the kernels' depth-first walk, compiled for the host (status code)."""
         return load_library().xgm_debug_matcher_accept_token_walk(self._h, int(token_id))
 
     def is_terminated(self) -> bool:

@@ -251,8 +251,9 @@ XGM_HD int walk_token(const Tab& T, const uint4 tk, const uint8_t* ext, const in
   return walk_token_in<BUILD, PRUNE>(mem, T, tk, ext, len, start_node, live, depth, steps_out, follow, i0, exits_out, at_end);
 }
 
-// End policy that writes out the stack of every configuration a token can end
-// in (section 3.3: the sampled token moves every parallel stack on).  A top
+// End policy of the walk on the host that writes out the stack of every configuration a
+// token can end in (section 3.3: the sampled token moves every parallel stack on; the accept
+// kernel has one of its own, which notes only the frames above those a stack keeps).  A top
 // node that can only return is returned from first, so that equal states get
 // equal stacks.  A stack goes to the slot that `sink.claim()` hands out:
 //   sink.frames  [capacity][max_depth] uint16, bottom frame first, the current node last

@@ -207,15 +207,22 @@ def test_a_grammar_without_contexts_has_no_walk_entries(xgm, wl):
     assert second.debug_walk_entries() == 0
 
 
+def rule_word(k: int) -> str:
+    return "".join(chr(ord("a") + k // 26 ** j % 26) for j in range(3))
+
+
+def many_rules_grammar(rules: int) -> str:
+    """Brackets around words, each a rule of its own that may go on with others: tables of any size, tokens that are walked."""
+    text = ['root ::= item ("," item)*', 'item ::= "[" root "]" | "{" root "}" | ' + " | ".join(f"k{k}" for k in range(rules))]
+    return "\n".join(text + [f'k{k} ::= "{rule_word(k)}" ("(" k{k * 7 % rules} ")" | k{k * 5 % rules} "." )?' for k in range(rules)])
+
+
 # A fill that walks stages the tables of the caches that have walk entries as far as they fit 31 KB: all of them, without
 # the last headers, without the sections in front of those (1000 rules have 32 KB of FOLLOW sets); beside a row with
 # small tables.
 @pytest.mark.parametrize("rules", [1, 60, 500, 800, 900, 1000, 1400])
 def test_walks_by_tables_of_all_sizes(xgm, wl, rules):
-    name = lambda k: "".join(chr(ord("a") + k // 26 ** j % 26) for j in range(3))
-    text = ['root ::= item ("," item)*', 'item ::= "[" root "]" | "{" root "}" | ' + " | ".join(f"k{k}" for k in range(rules))]
-    text += [f'k{k} ::= "{name(k)}" ("(" k{k * 7 % rules} ")" | k{k * 5 % rules} "." )?' for k in range(rules)]
-    text = "\n".join(text)
+    text, name = many_rules_grammar(rules), rule_word
     toks = [bytes([c]) for c in b"[]{}(),.abcdefghijklmnopqrstuvwxyz"] + [b"]" * k for k in range(2, 40)] + [b"]}" * k for k in range(1, 20)]
     toks += [b"]]}]]," + name(k).encode() for k in range(0, rules, 1 + rules // 30)] + [b"]]]]]][[", b"]]]]]],aaa", b""]
 
@@ -257,3 +264,110 @@ def test_walks_by_tables_of_all_sizes(xgm, wl, rules):
                 assert np.array_equal(logits.cpu().numpy()[:, :len(toks)] == 1.0, want[rows]), (rows[:8], k)
         assert xgm.debug_fill_count_steps(xgm.MatcherBatch(some), d_mask.data_ptr(), _stream()) > 0
         assert np.array_equal(d_mask.cpu().numpy(), bits[rows])
+
+
+# Walks over the limits in fills whose states went along with the launch (2 rows) and whose states were staged (200),
+# in the ring and in the static array, decided by one fixup.
+@pytest.mark.parametrize("rows", [2, 200])
+def test_records_of_launched_and_staged_states_are_fixed_up(xgm, wl, rows):
+    deep = b")+" + b"(" * 30          # closes one level, then opens 30: more than 64 frames in one token
+    toks = [b"1", b"(", b")", b"+", deep, deep + b"+", b"1" * 20, b")" * 40, b""]
+
+    class V_:
+        data = np.frombuffer(b"".join(toks), dtype=np.uint8).copy()
+        offsets = np.concatenate([[0], np.cumsum([len(t) for t in toks])]).astype(np.int64)
+        stop_ids = np.array([8], dtype=np.int32)
+
+    cache = xgm.Cache(xgm.Grammar(si.ARITH_GRAMMAR, "expr"), wl.make_xgm_vocab(V_))
+    og = oracle.Grammar(si.ARITH_GRAMMAR, "expr")
+    states = []
+    for text in (b"(" * 41 + b"1", b"1+", b"(" * 37 + b"1"):
+        m, om = xgm.Matcher(cache=cache), oracle.EarleyMatcher(og)
+        m.accept_bytes(text)
+        assert om.advance(text)
+        states.append((m, om.mask(V_)))
+    which = [[(b + k) % 3 for b in range(rows)] for k in range(3)]
+    d = [torch.full((rows, 1), -1, dtype=torch.int32, device="cuda") for _ in range(3)]
+    logits = torch.ones((rows, 16), device="cuda")
+    ms = [[states[k][0] for k in w] for w in which]
+    xgm.fill_overflow_fixup(_stream())
+    xgm.fill_next_token_bitmask(ms[0], d[0].data_ptr(), _stream())
+    xgm.fill_next_token_bitmask_static(ms[1], d[1].data_ptr(), _stream())
+    xgm.fill_and_apply(ms[2], d[2].data_ptr(), logits.data_ptr(), xgm.DTYPE_F32, 16, 16, stream=_stream())
+    torch.cuda.synchronize()
+    undecided = sum(k != 1 for w in which for k in w) * 2   # tokens 4 and 5, where a parenthesis is open
+    want = [np.stack([states[k][1] for k in w]) for w in which]
+    assert all(w[4] and not w[5] for k, (_, w) in enumerate(states) if k != 1)
+    for k in range(3):                                      # left out, or in the one launch left allowed, until they are decided
+        got = d[k].cpu().numpy()[:, 0].astype(np.uint32)
+        for b, s in enumerate(which[k]):
+            assert (got[b] >> 4) & 3 == (0 if s == 1 or k < 2 else 3), (k, b)
+    assert xgm.fill_overflow_fixup(_stream()) == undecided
+    for k in range(3):
+        assert np.array_equal(d[k].cpu().numpy(), oracle.pack_bitmask(want[k])), k
+
+
+# The accept kernel walks by whole waves and puts candidates in order all pairs at once; its tables are staged as far as
+# they fit 64 KB (the last grammar's FOLLOW sets alone take 70).  Random grammars, tokens allowed and not: the host
+# engine's verdicts and its stacks in its order.
+@pytest.mark.parametrize("seed", [1, 2])
+def test_device_accept_gives_the_engines_stacks(xgm, wl, seed):
+    from test_host_library import AMBIGUOUS_GRAMMAR, _random_grammar_text
+    rng = np.random.Generator(np.random.PCG64(seed))
+    toks = [b"a", b"b", b"c", b"d", b"(", b")", b"ab", b"ba", b"a(", b")b", b"cd)", b"((", b"))", b"abc", b"dcba", b"(a)", b"aa", b"aaa", b"x", b"y",
+            b"z", b"ax", b"aay(", b"y(a", b"az", b"[", b"]", b"{", b"}", b"[[[{", b"}]", b"]]],", b"]]]],[", b"aaa(", b"e", b"f", b",", b".", b"bcd"]
+    toks += [rule_word(k).encode() for k in range(0, 2200, 40)] + [b"[" + rule_word(k).encode() + b"]," for k in range(0, 2200, 300)] + [b""]
+
+    class V_:
+        data = np.frombuffer(b"".join(toks), dtype=np.uint8).copy()
+        offsets = np.concatenate([[0], np.cumsum([len(t) for t in toks])]).astype(np.int64)
+        stop_ids = np.array([len(toks) - 1], dtype=np.int32)
+
+    xv = wl.make_xgm_vocab(V_)
+    texts = [AMBIGUOUS_GRAMMAR, many_rules_grammar(2200)]
+    while len(texts) < 60:
+        text = _random_grammar_text(rng)
+        try:
+            xgm.Grammar(text, "root")
+        except xgm.XgmError:
+            continue
+        texts.append(text)
+    caches = [xgm.Cache(xgm.Grammar(t, "root"), xv) for t in texts]
+    n_ok = n_rejected = n_multi = n_host = 0
+    for walk in range(3):
+        ms = [xgm.Matcher(cache=c) for c in caches]
+        read = [xgm.Matcher(cache=c) for c in caches]
+        batch = xgm.DeviceBatch(ms, history=1, stream=_stream())
+        mask = torch.zeros((len(ms), xgm.bitmask_words(len(toks))), dtype=torch.int32, device="cuda")
+        done = [False] * len(ms)
+        for step in range(14):
+            batch.fill_next_token_bitmask(mask.data_ptr(), _stream())
+            batch.fill_overflow_fixup(_stream())
+            allowed = wl.unpack_rows(mask.cpu().numpy(), len(toks))
+            ids = np.full(len(ms), -1, dtype=np.int32)
+            for b in range(len(ms)):
+                some = np.flatnonzero(allowed[b])
+                if not done[b]:
+                    ids[b] = rng.integers(0, len(toks)) if some.size == 0 or rng.random() < 0.2 else some[rng.integers(0, some.size)]
+            batch.accept_tokens(torch.from_numpy(ids).cuda().data_ptr(), _stream())
+            status = batch.status(_stream())
+            for b in range(len(ms)):
+                if ids[b] < 0:
+                    continue
+                rc = ms[b].try_accept_token(int(ids[b]))
+                if rc == -8 or (rc == 0 and status[b] in (-8, -9)):   # beyond the host's, or the device's, limits
+                    n_host += 1
+                    done[b] = True
+                    continue
+                assert status[b] == rc, (texts[b], toks[ids[b]], status[b], rc)
+                n_ok += rc == 0
+                n_rejected += rc == -6
+                batch.get_row(b, read[b], _stream())
+                assert read[b].is_terminated() == ms[b].is_terminated()
+                if ms[b].is_terminated():
+                    done[b] = True
+                    continue
+                stacks = [ms[b].stack(s) for s in range(ms[b].num_stacks())]
+                assert [read[b].stack(s) for s in range(read[b].num_stacks())] == stacks, (texts[b], toks[ids[b]])
+                n_multi += len(stacks) > 1
+    assert n_ok > 500 and n_rejected > 200 and n_multi > 50, (n_ok, n_rejected, n_multi, n_host)

@@ -382,11 +382,11 @@ def _same_state(m1, m2):
 
 @pytest.mark.parametrize("name", ["arith", "json", "csql", "schema", "xml", "ambiguous"])
 def test_depth_first_accept_gives_the_engines_stacks(name):
-    """The routine the device uses to move stacks on by a token (an enumerating
-    depth-first walk over the flattened tables) against the host engine (a
-    breadth-first run of the structured automaton): same verdict for every
-    token tried and the same set of stacks, in the same order, after every
-    accepted one."""
+    """The kernels' enumerating depth-first walk over the flattened tables, as a lane does
+    it (compiled for the host; the whole-wave form of the accept kernel is compared in
+    test_gpu_edges and test_gpu_batch), against the host engine (a breadth-first run of
+    the structured automaton): same verdict for every token tried and the same set of
+    stacks, in the same order, after every accepted one."""
     if name == "ambiguous":
         text, root = AMBIGUOUS_GRAMMAR, "root"
         vocab = TinyVocab([b"a", b"aa", b"aaa", b"x", b"y", b"z", b"ax", b"aay(", b"(", b")", b"y(a", b"))", b"az", b""], [13])
@@ -467,7 +467,7 @@ def _random_grammar_text(rng) -> str:
 
 def test_depth_first_accept_on_random_grammars():
     """Seeded random grammars (those the library accepts: no left recursion, productive root): for random
-    byte strings fed a few bytes at a time as tokens, the depth-first accept (what the device runs), the
+    byte strings fed a few bytes at a time as tokens, the depth-first accept (the kernels' walk on the host), the
     host engine and the oracle's recogniser agree on every verdict, and the two library routes on the stacks."""
     rng = np.random.Generator(np.random.PCG64(424242))
     pieces = [bytes(p) for p in (b"a", b"b", b"c", b"d", b"(", b")", b"ab", b"ba", b"a(", b")b", b"cd)", b"((", b"))", b"abc", b"dcba", b"(a)")]
