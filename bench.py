@@ -17,7 +17,6 @@ and the CPU oracle on a bounded sample.  Prints ONE JSON line on stdout.
 from __future__ import annotations
 
 import argparse
-import hashlib
 import json
 import os
 import sys
@@ -27,21 +26,14 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
+from paper_2411_15100_amd import profile_summary
+
 HBM_PEAK_GBS = 8000.0                      # MI355X HBM3E, published
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic.json")
-KERNEL_SOURCES = ["kernels.hip", "kernels.hpp", "walk.hpp"]
 
 
 def log(*a):
     print("[bench]", *a, file=sys.stderr, flush=True)
-
-
-def kernel_source_hash() -> str:
-    h = hashlib.sha256()
-    for name in KERNEL_SOURCES:
-        with open(os.path.join(ROOT, "paper_2411_15100_amd", "csrc", name), "rb") as f:
-            h.update(f.read())
-    return h.hexdigest()[:16]
 
 
 def counter_traffic():
@@ -52,7 +44,7 @@ def counter_traffic():
             t = json.load(f)
     except (OSError, ValueError):
         return {}
-    if t.get("kernel_source_hash") != kernel_source_hash():
+    if t.get("kernel_source_hash") != profile_summary.kernel_source_hash():
         return {}
     return t.get("bytes_per_launch", {})
 
@@ -285,8 +277,9 @@ def main():
     ceiling = {"plain_fill_of_the_same_buffers_GB/s": plain_fill_gbs, "plain_copy_between_them_GB/s": plain_copy_gbs,
                "note": "what this box reaches with a plain torch fill / copy of the rotating logits buffers: the attainable "
                        "ceiling for a kernel that writes them, against the published 8 TB/s"}
-    roof_fused = roofline("fill_kernel<false, 2> (mask fill and -inf apply in one launch, device-resident states)",
-                          fused_bytes, fused_kernel_us, "fill_kernel<false, 2>",
+    names = profile_summary.STEP_KERNELS
+    roof_fused = roofline(f"{names['one launch']} (mask fill and -inf apply in one launch, device-resident states)",
+                          fused_bytes, fused_kernel_us, names["one launch"],
                           bytes_per_launch_in_64_byte_pieces=fill_bytes + piece_bytes,
                           frac_of_measured_fill_rate=fused_bytes / (fused_kernel_us * 1e-6) / 1e9 / plain_fill_gbs,
                           pieces_frac_of_measured_fill_rate=(fill_bytes + piece_bytes) / (fused_kernel_us * 1e-6) / 1e9 / plain_fill_gbs,
@@ -297,19 +290,19 @@ def main():
                                "that holds a rejected logit once, and pieces_frac_of_measured_fill_rate prices that count against "
                                "the plain fill of the same buffers; kernel_us = HIP "
                                "events on the launch stream around the K back-to-back launches of a pass, divided by K")
-    roof_fill = roofline("fill_kernel<false, 0> (device-resident states)", fill_bytes, fill_kernel_us, "fill_kernel<false, 0>",
+    roof_fill = roofline(f"{names['fill']} (device-resident states)", fill_bytes, fill_kernel_us, names["fill"],
                          stacks_with_bitset_row=float(fwork[0]), list_entries_per_launch=float(fwork[1:].sum()),
                          automaton_steps_per_launch=float(np.mean(steps_count)),
                          note="a few dependent memory rounds per workgroup (row descriptor, stack headers, bitset row and list "
                               "entries, store): latency, not bytes; the accepted rows of the 16 state sets fit the last-level "
                               "cache, so part of these reads never reaches HBM")
-    roof_apply = roofline("apply_kernel<2>", apply_bytes, apply_kernel_us, "apply_kernel<2>",
+    roof_apply = roofline(names["apply"], apply_bytes, apply_kernel_us, names["apply"],
                           read_modify_write_bytes_per_launch=2.0 * 2.0 * B * V + 4.0 * B * W,
                           bytes_per_launch_in_64_byte_pieces=4.0 * B * W + piece_bytes,
                           frac_of_measured_fill_rate=apply_bytes / (apply_kernel_us * 1e-6) / 1e9 / plain_fill_gbs,
                           pieces_frac_of_measured_fill_rate=(4.0 * B * W + piece_bytes) / (apply_kernel_us * 1e-6) / 1e9 / plain_fill_gbs,
                           attainable=ceiling)
-    roof_step = roofline("fill_kernel<false, 0> + apply_kernel<2>", fill_bytes + apply_bytes, two_call_us, None,
+    roof_step = roofline(f"{names['fill']} + {names['apply']}", fill_bytes + apply_bytes, two_call_us, None,
                          note="the two-call step: fill, then apply (wall clock per step)")
 
     # ------------------------------------------------------------------ configs 1-3: the smaller workloads

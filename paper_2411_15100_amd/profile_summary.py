@@ -24,6 +24,9 @@ import sys
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 KERNEL_SOURCES = ["kernels.hip", "kernels.hpp", "walk.hpp"]
+# the kernels of the serving step of bench.py (no cache of its batch has walk entries), by their names in a trace
+STEP_KERNELS = {"one launch": "fill_kernel<false, 2, 0u, false, false>", "fill": "fill_kernel<false, 0, 0u, false, false>",
+                "apply": "apply_kernel<2>"}
 COPY_KERNEL = "bfloat16_copy_kernel"         # torch's fp32 -> bf16 copy of one logits buffer
 
 
@@ -78,7 +81,8 @@ def counters(out: str, traffic_json: str, note: str, runs):
         text.append(f"# run {label}: {db}")
         for counter, per_kernel in sorted(counter_averages(db).items()):
             text.append(f"{counter}:")
-            for kernel, (n, mean) in sorted(per_kernel.items(), key=lambda kv: -kv[1][1])[:14]:
+            ranked = sorted(per_kernel.items(), key=lambda kv: -kv[1][1])
+            for kernel, (n, mean) in [kv for k, kv in enumerate(ranked) if k < 14 or "xgm::" in kv[0]]:
                 text.append(f"  {n:7d} dispatches  mean {mean:14.1f}  {short(kernel)}")
             if counter == "FETCH_SIZE":
                 fetch = per_kernel
@@ -98,10 +102,12 @@ def counters(out: str, traffic_json: str, note: str, runs):
                             "copy_kernel_KiB": {"FETCH_SIZE": copy_f[0][1], "WRITE_SIZE": copy_w[0][1]}}
         text.append(f"# scale: WRITE_SIZE taken at 1.0 (the copy writes {copy_w[0][1]:.0f} KiB); FETCH_SIZE x {f_scale:.3f} "
                     f"(the copy reads twice what it writes, the counter shows {copy_f[0][1]:.0f} KiB)")
-        for key, part in (("fill_kernel<false, 2>", "fill_kernel<false, 2>"), ("fill_kernel<false, 0>", "fill_kernel<false, 0>"),
-                          ("apply_kernel<2>", "apply_kernel<2>")):
-            f_, w_ = find(fetch, part), find(write, part)
-            if f_ and w_:
+        for key in STEP_KERNELS.values():
+            f_, w_ = find(fetch, key + "("), find(write, key + "(")
+            if not (f_ and w_):
+                if traffic_json != "-":
+                    raise SystemExit(f"no dispatch of {key} in the runs: STEP_KERNELS is not what the step runs")
+            else:
                 traffic["bytes_per_launch"][key] = (f_[0][1] * f_scale + w_[0][1]) * 1024.0
                 traffic.setdefault("fetched_written", {})[key] = [f_[0][1] * f_scale * 1024.0, w_[0][1] * 1024.0]
                 text.append(f"# {key}: fetched {f_[0][1] * f_scale * 1024 / 1e6:.2f} MB + written {w_[0][1] * 1024 / 1e6:.2f} MB per launch")
