@@ -1025,6 +1025,7 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
     c->host.ctx_off = d_ctx_off;
     c->host.ctx_node = d_ctx_node;
     c->host.n_nodes = N;
+    c->host.long_walks = c->host_classified > 0 ? 1u : 0u;
     c->device_bytes += (int64_t)(n_slots + 1) * 4 + (int64_t)total * 4 + (int64_t)image_bytes + (int64_t)(n_keys - n_k[c->levels - 1]) * 4 +
                        (int64_t)ctx_off.size() * 4 + (int64_t)ctx_node.size() * 2;
     if (keep_plain) c->device_bytes += (int64_t)N * dv.W * 8;
@@ -1377,7 +1378,7 @@ static int fill_impl(xgm_matcher* const* ms, int32_t B, int32_t* d_bitmask, void
   // A replay of a captured launch takes what is staged when it runs, which may be states of other caches: those may have
   // walk entries where these have none, or larger tables.
   const bool capturing = use_static && is_capturing(stream);
-  if (capturing) walks = FillWalks{std::max(walks.entries, 1u), kFillLdsBudget};
+  if (capturing) walks = FillWalks{std::max(walks.entries, 1u), kFillLdsBudget, walks.long_walks};
 
   Context& C = ctx();
   std::lock_guard<std::mutex> lock(C.mu);

@@ -1126,8 +1126,12 @@ __device__ __forceinline__ uint32_t list_entry(uint32_t q, uint32_t seg_id0) {
 }
 // Up to this many entries go to a wave each (walk_wave): six one after the other cost what a lane's longest walk does in
 // a grammar of deep walks (C/SQL-like: 23 -> 17 us for a row with a walk of 79 steps; with up to 64 a row of 4358 steps
-// took 137 us instead of 55, with up to 256 as long).
+// took 137 us instead of 55, with up to 256 as long).  None go to waves in a batch with a cache whose build had walks over
+// the limits: such a fill waits for walks of thousands of steps, of which a wave takes longer than a lane each (what a
+// wave looks ahead for is not there) and only four at a time.  Markup grammar, fills of 3 rows x 128256 and of 8 x 151936
+// by waves 4.75 and 4.86 ms, by lanes 3.97 and 4.0.
 constexpr uint32_t kWaveWalks = 24;
+constexpr uint32_t kPartShift = 2;  // workgroups that share a segment, as a power of two (PARTS)
 template <>
 struct FillShared<true> {
   uint32_t words[kSegWords];
@@ -1244,14 +1248,14 @@ __global__ __launch_bounds__(kFillThreads, WALKS ? 4 : 8) void fill_kernel(const
                                                             const uint32_t* __restrict__ stack_hdrs_,
                                                             const uint16_t* __restrict__ frames_, DevVocab voc,
                                                             uint32_t* __restrict__ out, OverflowLog* log, uint32_t seq,
-                                                            unsigned long long* step_counter, FusedApply fa, uint32_t part_shift) {
+                                                            unsigned long long* step_counter, FusedApply fa, uint32_t wave_walks) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ FillShared<WALKS> sm;
   const XGM_GLOBAL uint32_t* stack_hdrs = (const XGM_GLOBAL uint32_t*)stack_hdrs_;
   const uint32_t tid = threadIdx.x;
   const int32_t b = (int32_t)blockIdx.y, seg = (int32_t)blockIdx.x;
-  // PARTS: 1 << part_shift workgroups share the segment, each with its part of the words (the lists are read by all of them)
-  const int32_t part_words = PARTS ? kSegWords >> part_shift : kSegWords;
+  // PARTS: 1 << kPartShift workgroups share the segment, each with its part of the words (the lists are read by all of them)
+  const int32_t part_words = PARTS ? kSegWords >> kPartShift : kSegWords;
   const int32_t w_begin = seg * kSegWords + (PARTS ? (int32_t)blockIdx.z * part_words : 0);
   const int32_t n_words = min(part_words, voc.W - w_begin);
   const int32_t id0 = w_begin * 32;
@@ -1412,7 +1416,8 @@ __global__ __launch_bounds__(kFillThreads, WALKS ? 4 : 8) void fill_kernel(const
       // the queue, or, if it overflowed, list after list
       const uint32_t n_queued = sm.n_queued;
       const bool again = n_queued > kWalkQueue;
-      if (!COUNT && n_queued <= kWaveWalks && small_sections_staged(tab) && row.n_frames <= kFillFramesLds)
+      // (the waves' walk lies right behind: where the lanes' comes in between, a launch of few rows takes 0.2 us longer)
+      if (!COUNT && __builtin_expect(n_queued <= wave_walks && small_sections_staged(tab) && row.n_frames <= kFillFramesLds, 1))
         fill_walks_by_wave<APPLY != 0, INLINE != 0>(LdsTabT<true, true>(tab, smem), sm, row, b, id0, n_queued, voc, log, seq);
       else
 #pragma unroll 1
@@ -1437,7 +1442,7 @@ __global__ __launch_bounds__(kFillThreads, WALKS ? 4 : 8) void fill_kernel(const
   // 4. the words, and the logits of the segment; the last segment also takes the columns beyond the vocabulary
   for (int32_t w = tid; w < n_words; w += kFillThreads) out[(size_t)b * voc.W + w_begin + w] = sm.words[w];
   if constexpr (APPLY != 0) {
-    const bool last = seg + 1 == voc.n_seg && (!PARTS || blockIdx.z + 1u == 1u << part_shift);
+    const bool last = seg + 1 == voc.n_seg && (!PARTS || blockIdx.z + 1u == 1u << kPartShift);
     const int32_t e_end = last ? fa.V_logits : min(id0 + (int32_t)n_ids, fa.V_logits), lane = (int32_t)(tid & 63u);
     unsigned char* const logits = fa.logits + (size_t)b * fa.row_stride * APPLY;
     for (int32_t e0 = id0 + (int32_t)uniform(tid >> 6) * kApplyWaveElems; e0 < e_end; e0 += kSegTokens) {
@@ -2057,11 +2062,11 @@ static void launch_fill_of(const InlineStates<INLINE>& st, const RowDesc* rows, 
                            const DevVocab& voc, const FillWalks& walks, uint32_t* out, OverflowLog* log, uint32_t seq, unsigned long long* step_counter,
                            hipStream_t stream, const FusedApply& fa) {
   dim3 grid(voc.n_seg, B);
-  const uint32_t n = grid.x * grid.y, part_shift = walks.entries >= kManyWalks && n <= kFillWalkSlots ? 2u : 0u;
-  grid.z = 1u << part_shift;
-  auto kernel = walks.entries == 0u ? fill_kernel<false, APPLY, INLINE, false> : part_shift ? fill_kernel<COUNT, APPLY, INLINE, true, true> : fill_kernel<COUNT, APPLY, INLINE, true>;
+  const bool parts = walks.entries >= kManyWalks && grid.x * grid.y <= kFillWalkSlots;
+  if (parts) grid.z = 1u << kPartShift;
+  auto kernel = walks.entries == 0u ? fill_kernel<false, APPLY, INLINE, false> : parts ? fill_kernel<COUNT, APPLY, INLINE, true, true> : fill_kernel<COUNT, APPLY, INLINE, true>;
   hipLaunchKernelGGL(kernel, grid, dim3(kFillThreads), walks.table_bytes, stream, st, rows, stack_hdrs, frames, voc, out, log, seq,
-                     step_counter, fa, part_shift);
+                     step_counter, fa, walks.long_walks ? 0u : kWaveWalks);
 }
 void launch_fill(const RowDesc* rows, const uint32_t* stack_hdrs, const uint16_t* frames, int32_t B, const DevVocab& voc, const FillWalks& walks,
                  uint32_t* out, OverflowLog* log, uint32_t seq, unsigned long long* step_counter, hipStream_t stream,

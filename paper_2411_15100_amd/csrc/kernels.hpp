@@ -140,6 +140,7 @@ struct DevCache {
   const uint32_t* node_ctx;
   int32_t n_nodes;
   uint32_t walks;            // the lists' walk entries, counted up to about kManyWalks
+  uint32_t long_walks;       // walks of the build exceeded the limits (a text that may be read in many ways): so will a fill's
 };
 constexpr uint32_t kManyWalks = 1024;
 constexpr uint32_t kNoAccRow = 0xFFFFu;
@@ -354,10 +355,12 @@ void launch_upload_stacks(const void* src, void* dst, size_t plain_bytes, const 
 struct FillWalks {
   uint32_t entries = 0;      // the most walk entries that one of them has (DevCache::walks)
   uint32_t table_bytes = 0;  // the most LDS that one with walk entries wants for its tables
+  bool long_walks = false;   // some have long walks
   void add(const DevCache& c) {
     if (c.walks == 0u) return;
     entries = entries > c.walks ? entries : c.walks;
     table_bytes = table_bytes > c.tab.stage_bytes ? table_bytes : c.tab.stage_bytes;
+    long_walks = long_walks || c.long_walks != 0u;
   }
 };
 void launch_fill(const RowDesc* rows, const uint32_t* stack_hdrs, const uint16_t* frames, int32_t B,

@@ -371,3 +371,36 @@ def test_device_accept_gives_the_engines_stacks(xgm, wl, seed):
                 assert [read[b].stack(s) for s in range(read[b].num_stacks())] == stacks, (texts[b], toks[ids[b]])
                 n_multi += len(stacks) > 1
     assert n_ok > 500 and n_rejected > 200 and n_multi > 50, (n_ok, n_rejected, n_multi, n_host)
+
+
+# Few walks of a row go to waves, unless a cache of the batch (the markup grammar's) is known to walk to the limits.
+@pytest.mark.parametrize("V", [4096, 32000])
+def test_walks_by_waves_and_by_lanes(xgm, wl, V):
+    vocab = si.make_vocab("bpe", V, 0)
+    xv = wl.make_xgm_vocab(vocab)
+    texts = [si.PYDSL_GRAMMAR, si.XML_GRAMMAR, si.CSQL_GRAMMAR]
+    caches = [xgm.Cache(xgm.Grammar(t, "root"), xv) for t in texts]
+    assert [c.host_classified > 0 for c in caches] == [False, True, False]
+    starts = [(0, b"x=1"), (1, b"<a"), (2, b"int x"), (1, b"<a>x"), (0, b"if v==1:x=(1"), (1, b"<a><b"), (1, b"<a b=\"c")]
+    ms, want = [], []
+    for k, start in starts:
+        m, om = xgm.Matcher(cache=caches[k]), oracle.EarleyMatcher(oracle.Grammar(texts[k], "root"))
+        if m.try_accept_bytes(start) != 0:
+            continue
+        assert om.advance(start)
+        ms.append((k, m))
+        want.append(oracle.pack_bitmask(om.mask(vocab)))
+    assert {k for k, _ in ms} == {0, 1, 2}
+    everything = list(range(len(ms)))
+    for rows in (everything, [b for b in everything if ms[b][0] != 1], [b for b in everything if ms[b][0] == 1]):
+        some = [ms[b][1] for b in rows]
+        resident = xgm.DeviceBatch(some, history=0, stream=_stream())
+        for k in range(2):
+            d_mask = torch.full((len(rows), xgm.bitmask_words(V)), -1, dtype=torch.int32, device="cuda")
+            if k:
+                resident.fill_next_token_bitmask(d_mask.data_ptr(), _stream())
+                resident.fill_overflow_fixup(_stream())
+            else:
+                xgm.fill_next_token_bitmask(some, d_mask.data_ptr(), _stream())
+                xgm.fill_overflow_fixup(_stream())
+            assert np.array_equal(d_mask.cpu().numpy(), np.stack([want[b] for b in rows])), (rows, k)
