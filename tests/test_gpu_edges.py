@@ -128,7 +128,7 @@ def test_states_in_the_launch(xgm, wl, rows, depth):
         assert torch.equal(t.cpu(), torch.where(allowed, was, torch.full_like(was, float("-inf"))))
 
 
-# A number that ends an expression leaves hundreds of tokens to the walk: few, as many as the queue of a workgroup
+# A number that ends an expression leaves hundreds of tokens to the walk: few, as many as the queue
 # of a workgroup holds (1024), more; in one segment and in several, whole or shared by workgroups (few rows).
 @pytest.mark.parametrize("V", [300, 900, 1000, 1100, 1300, 2047, 2049, 6145, 8191, 8193, 24000, 90000])
 def test_walk_entries(xgm, wl, V):
