@@ -295,6 +295,11 @@ int32_t xgm_matcher_stack(const xgm_matcher* m, int32_t s, int32_t* h_nodes, int
  * on hip_stream, and returns.  The stacks of a small batch go along as kernel
  * arguments; those of a larger one into pinned staging owned by the library (a
  * ring of 8 slots), from which a small kernel copies them in front of the fill.
+ * What a fill reads is kept until it is done, also if the caller drops the
+ * matchers and their caches right after the call: the library remembers the last
+ * 8 fills or more (up to 32 small ones per stream) and waits for those that later
+ * calls take the place of.  (The caches of a call under graph capture are kept by
+ * whoever keeps the graph.)
  * A walk that exceeds the on-chip bounds (64 frames pushed inside one token,
  * 24 pending alternatives, 4096 steps, tokens longer than 255 bytes) is never
  * guessed: the pair is recorded on the device, its bit is left 0, and
@@ -325,7 +330,7 @@ int xgm_fill_and_apply(xgm_matcher* const* ms, int32_t B, int32_t* d_bitmask, vo
  * array of XGM_STATIC_STAGING_BYTES (1 MiB) that every device holds from the
  * moment the library is loaded until the process ends, where a kernel writes
  * it out in the form the fill kernel reads (both forms lie in the array);
- * the call makes no hipMalloc / hipHostMalloc / hipFree and uses no event.  A
+ * the call makes no hipMalloc / hipHostMalloc / hipFree and creates no event.  A
  * batch whose stacks need more than that returns XGM_ERR_TOO_LARGE (nothing is
  * enqueued); batch 128 at a vocabulary of 151936 needs about 110 KiB.  The
  * mask caches of the matchers must have been built before (they were, or the

@@ -304,6 +304,7 @@ void vocab_to_device(xgm_vocab* v) {
 // staging memory is used again).
 struct PendingFill {
   uint32_t seq = 0;          // 0: none
+  uint64_t number = 0;       // among the fills of its kind (see Context::fills)
   int32_t B = 0;
   int32_t* d_bitmask = nullptr;
   const void* blob = nullptr;
@@ -318,7 +319,22 @@ struct FillSlot {
   hipEvent_t done = nullptr;
   bool used = false;
   PendingFill fill;
-  uint32_t states[kInlineWordsLarge];  // the states of a fill that took them along with its launch
+};
+// The fills of one stream whose states went along with the launch.  What they read has to be kept until they are done,
+// and an event costs a launch 3.7 us (4.3 without); launches of one stream end one after the other, so that one event at
+// the end of a group speaks for all of it (4.35 us per fill of one row; 4.5 with groups of 8).  A group is entered again
+// when the other one is full, and waits for its event then: the last kGroup fills at least are kept, twice as many at most.
+struct LaunchRing {
+  static constexpr int kGroup = 16;
+  hipStream_t stream = nullptr;
+  uint64_t last_use = 0;  // 0: the ring is nobody's
+  int next = 0;
+  hipEvent_t done[2] = {nullptr, nullptr};
+  bool recorded[2] = {false, false};
+  struct Slot {
+    PendingFill fill;
+    uint32_t states[kInlineWordsLarge];  // for the fixup
+  } slot[2 * kGroup];
 };
 struct Context {
   std::mutex mu;
@@ -328,8 +344,11 @@ struct Context {
   static constexpr int kSlots = 8;
   FillSlot slot[kSlots];
   int next_slot = 0;
-  PendingFill static_fill;  // the last fill of the entry point that allocates nothing
-  uint32_t static_states[kInlineWordsLarge];
+  static constexpr int kRings = 4;
+  LaunchRing ring[2][kRings];  // (the entry point that allocates nothing has its own)
+  uint64_t ring_uses = 0;
+  uint64_t fills[2] = {0, 0};  // so far, but for captured ones; [1]: of the entry point that allocates nothing
+  PendingFill static_fill;     // the last staged fill of the entry point that allocates nothing
   // records of logs that no longer exist (cache builds, destroyed batches), and the batches that do
   int64_t retired_records = 0;
   std::set<xgm_batch*> batches;
@@ -346,7 +365,13 @@ OverflowLog* new_log() {
 }
 OverflowLog* overflow_log() {
   Context& c = ctx();
-  if (!c.d_log) c.d_log = new_log();
+  if (!c.d_log) {
+    for (auto& rings : c.ring)
+      for (LaunchRing& ring : rings)
+        for (hipEvent_t& e : ring.done)
+          if (!e) HIP_OK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+    c.d_log = new_log();
+  }
   return c.d_log;
 }
 uint32_t read_overflow_count(const OverflowLog* log) {
@@ -354,15 +379,43 @@ uint32_t read_overflow_count(const OverflowLog* log) {
   HIP_OK(hipMemcpy(&n, &log->count, sizeof(n), hipMemcpyDeviceToHost));
   return n;
 }
-void set_pending(PendingFill& f, uint32_t seq, int32_t B, int32_t* d_bitmask, const void* blob, bool inline_states, xgm_matcher* const* ms) {
+void forget(PendingFill& f) {
   for (xgm_cache* c : f.caches) release(c);
   f.caches.clear();
+  f.seq = 0;
+}
+void set_pending(PendingFill& f, uint32_t seq, uint64_t number, int32_t B, int32_t* d_bitmask, const void* blob, bool inline_states, xgm_matcher* const* ms) {
+  forget(f);
   f.inline_states = inline_states;
   f.seq = seq;
+  f.number = number;
   f.B = B;
   f.d_bitmask = d_bitmask;
   f.blob = blob;
   for (int32_t b = 0; b < B; ++b) { ++ms[b]->c->refs; f.caches.push_back(ms[b]->c); }
+}
+
+// The ring of a stream, or null: the fill is staged then.  A stream takes over the ring of one that has not been heard of
+// for a thousand fills, when the device has come to rest; more streams than rings at the same time are staged.
+LaunchRing* launch_ring(Context& c, bool of_static, hipStream_t stream) {
+  if (stream == hipStreamPerThread) return nullptr;  // (one handle for the streams of all threads)
+  const uint64_t now = ++c.ring_uses;
+  LaunchRing* oldest = nullptr;
+  for (LaunchRing& r : c.ring[of_static ? 1 : 0]) {
+    if (r.last_use != 0 && r.stream == stream) { r.last_use = now; return &r; }
+    if (!oldest || r.last_use < oldest->last_use) oldest = &r;
+  }
+  LaunchRing& r = *oldest;
+  if (r.last_use != 0) {
+    if (now - r.last_use < 1024) return nullptr;
+    HIP_OK(hipDeviceSynchronize());
+    for (LaunchRing::Slot& s : r.slot) forget(s.fill);
+    r.recorded[0] = r.recorded[1] = false;
+    r.next = 0;
+  }
+  r.stream = stream;
+  r.last_use = now;
+  return &r;
 }
 
 int fail(const Failure& f) {
@@ -1250,7 +1303,10 @@ alignas(64) static unsigned char g_static_host[kStaticScratchBytes];
 
 static bool is_capturing(hipStream_t stream) {
   hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-  HIP_OK(hipStreamIsCapturing(stream, &st));
+  if (hipStreamIsCapturing(stream, &st) != hipSuccess) {  // (the legacy stream while another one is being captured)
+    (void)hipGetLastError();
+    return false;
+  }
   return st != hipStreamCaptureStatusNone;
 }
 
@@ -1377,30 +1433,48 @@ static int fill_impl(xgm_matcher* const* ms, int32_t B, int32_t* d_bitmask, void
                                        " bytes of staging, the static array holds " + std::to_string(kStaticScratchBytes));
   // A replay of a captured launch takes what is staged when it runs, which may be states of other caches: those may have
   // walk entries where these have none, or larger tables.
-  const bool capturing = use_static && is_capturing(stream);
-  if (capturing) walks = FillWalks{std::max(walks.entries, 1u), kFillLdsBudget, walks.long_walks};
+  const bool capturing = is_capturing(stream);
+  if (use_static && capturing) walks = FillWalks{std::max(walks.entries, 1u), kFillLdsBudget, walks.long_walks};
 
   Context& C = ctx();
   std::lock_guard<std::mutex> lock(C.mu);
   // A small batch goes along with the launch (see InlineStates), unless the two kernels are to be looked at one by
-  // one or the launch is being captured into a graph.  The entry point that allocates nothing stages it all the same:
-  // replays of a captured call take what the last call has staged.
+  // one or a call of the entry point that allocates nothing is being captured into a graph.  That one stages it all
+  // the same: replays of a captured call take what the last call has staged.
+  // What the launch reads is kept until it is done (the caches may be dropped right after the call); a captured launch takes
+  // no slot: whoever keeps its graph keeps the caches.
   const size_t inline_most = (size_t)B * 2 + n_stacks * kInlineStackWords + (n_frames + 1) / 2;
-  if (inline_most + kInlineCacheWords <= kInlineWordsLarge && !timing && !d_step_counter && !capturing) {
-    FillSlot& slot = C.slot[C.next_slot];
-    uint32_t* states = use_static ? C.static_states : slot.states;
-    const size_t words = pack_inline(ms, B, n_stacks, n_frames, states);
+  if (inline_most + kInlineCacheWords <= kInlineWordsLarge && !timing && !d_step_counter && !(use_static && capturing)) {
+    if (use_static && !C.d_log) return fail(XGM_ERR_INTERNAL, "fill (static staging): the library's device context does not exist yet");
+    OverflowLog* log = overflow_log();
+    uint32_t captured_states[kInlineWordsLarge];
+    LaunchRing* ring = capturing ? nullptr : launch_ring(C, use_static, stream);
+    uint32_t* states = captured_states;
+    int group = 0;
+    bool closes = false;
+    if (ring) {
+      group = ring->next / LaunchRing::kGroup;
+      closes = ring->next % LaunchRing::kGroup == LaunchRing::kGroup - 1;
+      if (ring->next % LaunchRing::kGroup == 0 && ring->recorded[group]) {
+        HIP_OK(hipEventSynchronize(ring->done[group]));
+        ring->recorded[group] = false;
+        for (int k = 0; k < LaunchRing::kGroup; ++k) forget(ring->slot[ring->next + k].fill);
+      }
+      states = ring->slot[ring->next].states;
+    }
+    const size_t words = ring || capturing ? pack_inline(ms, B, n_stacks, n_frames, states) : 0;
     if (words != 0) {
-      if (use_static && !C.d_log) return fail(XGM_ERR_INTERNAL, "fill (static staging): the library's device context does not exist yet");
-      OverflowLog* log = overflow_log();
       if (use_static) pack_staged(ms, B, n_stacks, g_static_host);
       const uint32_t seq = ++C.seq;
       launch_fill_inline(states, (uint32_t)words, B, v->dv, walks, reinterpret_cast<uint32_t*>(d_bitmask), log, seq, stream,
-                         fused ? fused->d_logits : nullptr, fused ? fused->esize : 0, fused ? fused->neg_inf : 0u,
-                         fused ? fused->V_logits : 0, fused ? fused->row_stride : 0);
+                         closes ? ring->done[group] : nullptr, fused ? fused->d_logits : nullptr, fused ? fused->esize : 0,
+                         fused ? fused->neg_inf : 0u, fused ? fused->V_logits : 0, fused ? fused->row_stride : 0);
       HIP_OK(hipGetLastError());
-      if (!use_static) C.next_slot = (C.next_slot + 1) % Context::kSlots;
-      set_pending(use_static ? C.static_fill : slot.fill, seq, B, d_bitmask, states, true, ms);
+      if (ring) {
+        set_pending(ring->slot[ring->next].fill, seq, ++C.fills[use_static], B, d_bitmask, states, true, ms);
+        if (closes) ring->recorded[group] = true;
+        ring->next = (ring->next + 1) % (2 * LaunchRing::kGroup);
+      }
       return XGM_OK;
     }
   }
@@ -1449,7 +1523,7 @@ static int fill_impl(xgm_matcher* const* ms, int32_t B, int32_t* d_bitmask, void
     ring->used = true;
     C.next_slot = (C.next_slot + 1) % Context::kSlots;
   }
-  set_pending(ring ? ring->fill : C.static_fill, seq, B, d_bitmask, h_buf, false, ms);
+  set_pending(ring ? ring->fill : C.static_fill, seq, ++C.fills[use_static], B, d_bitmask, h_buf, false, ms);
   return XGM_OK;
   API_END
 }
@@ -1633,9 +1707,15 @@ int xgm_fill_overflow_fixup(void* hip_stream) {
   int handled = 0, lost = 0;
   for (const auto& e : records) {
     // the fill that recorded it: one of the last fills from the ring of staging slots, or the last one staged statically
-    const PendingFill* f = C.static_fill.seq == e[0] && e[0] != 0 ? &C.static_fill : nullptr;
-    for (const FillSlot& slot : C.slot)
-      if (slot.fill.seq == e[0] && e[0] != 0) f = &slot.fill;
+    const PendingFill* f = nullptr;
+    auto look = [&](const PendingFill& p, int kind) {
+      if (e[0] != 0 && p.seq == e[0] && C.fills[kind] - p.number < (kind ? 1u : (uint64_t)Context::kSlots)) f = &p;
+    };
+    look(C.static_fill, 1);
+    for (const FillSlot& slot : C.slot) look(slot.fill, 0);
+    for (int kind = 0; kind < 2; ++kind)
+      for (const LaunchRing& ring : C.ring[kind])
+        for (const LaunchRing::Slot& slot : ring.slot) look(slot.fill, kind);
     const int32_t b = (int32_t)e[1], id = (int32_t)e[2];
     if (!f || b >= f->B) { ++lost; continue; }
     const xgm_cache& c = *f->caches[b];

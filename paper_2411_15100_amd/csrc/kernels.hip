@@ -1,5 +1,6 @@
 // HIP kernels for gfx950 (wave64): token walk / classify, rank->id permute,
 // context-dependent lists, batched mask fill, -inf apply.
+#include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -2060,13 +2061,18 @@ constexpr uint32_t kFillWalkSlots = 4 * 256;  // workgroups that the chip has ro
 template <bool COUNT, int APPLY, uint32_t INLINE>
 static void launch_fill_of(const InlineStates<INLINE>& st, const RowDesc* rows, const uint32_t* stack_hdrs, const uint16_t* frames, int32_t B,
                            const DevVocab& voc, const FillWalks& walks, uint32_t* out, OverflowLog* log, uint32_t seq, unsigned long long* step_counter,
-                           hipStream_t stream, const FusedApply& fa) {
+                           hipStream_t stream, const FusedApply& fa, hipEvent_t done = nullptr) {
   dim3 grid(voc.n_seg, B);
   const bool parts = walks.entries >= kManyWalks && grid.x * grid.y <= kFillWalkSlots;
   if (parts) grid.z = 1u << kPartShift;
   auto kernel = walks.entries == 0u ? fill_kernel<false, APPLY, INLINE, false> : parts ? fill_kernel<COUNT, APPLY, INLINE, true, true> : fill_kernel<COUNT, APPLY, INLINE, true>;
-  hipLaunchKernelGGL(kernel, grid, dim3(kFillThreads), walks.table_bytes, stream, st, rows, stack_hdrs, frames, voc, out, log, seq,
-                     step_counter, fa, walks.long_walks ? 0u : kWaveWalks);
+  const uint32_t wave_walks = walks.long_walks ? 0u : kWaveWalks;
+  if (done)
+    hipExtLaunchKernelGGL(kernel, grid, dim3(kFillThreads), walks.table_bytes, stream, nullptr, done, 0, st, rows, stack_hdrs, frames, voc, out, log,
+                          seq, step_counter, fa, wave_walks);
+  else
+    hipLaunchKernelGGL(kernel, grid, dim3(kFillThreads), walks.table_bytes, stream, st, rows, stack_hdrs, frames, voc, out, log, seq, step_counter, fa,
+                       wave_walks);
 }
 void launch_fill(const RowDesc* rows, const uint32_t* stack_hdrs, const uint16_t* frames, int32_t B, const DevVocab& voc, const FillWalks& walks,
                  uint32_t* out, OverflowLog* log, uint32_t seq, unsigned long long* step_counter, hipStream_t stream,
@@ -2075,22 +2081,23 @@ void launch_fill(const RowDesc* rows, const uint32_t* stack_hdrs, const uint16_t
   const FusedApply fa{static_cast<unsigned char*>(logits), row_stride, V_logits, neg_inf};
   auto launch = logits ? (elem_size == 2 ? launch_fill_of<false, 2, 0> : launch_fill_of<false, 4, 0>)
                        : (step_counter ? launch_fill_of<true, 0, 0> : launch_fill_of<false, 0, 0>);
-  launch(InlineStates<0>{}, rows, stack_hdrs, frames, B, voc, walks, out, log, seq, step_counter, stream, fa);
+  launch(InlineStates<0>{}, rows, stack_hdrs, frames, B, voc, walks, out, log, seq, step_counter, stream, fa, nullptr);
 }
 template <uint32_t WORDS>
 static void launch_fill_inline_of(const uint32_t* states, uint32_t words, int32_t B, const DevVocab& voc, const FillWalks& walks, uint32_t* out,
-                                  OverflowLog* log, uint32_t seq, hipStream_t stream, int elem_size, const FusedApply& fa) {
+                                  OverflowLog* log, uint32_t seq, hipStream_t stream, hipEvent_t done, int elem_size, const FusedApply& fa) {
   InlineStates<WORDS> st;
   std::copy(states, states + words, st.w);
   auto launch = fa.logits ? (elem_size == 2 ? launch_fill_of<false, 2, WORDS> : launch_fill_of<false, 4, WORDS>) : launch_fill_of<false, 0, WORDS>;
-  launch(st, nullptr, nullptr, nullptr, B, voc, walks, out, log, seq, nullptr, stream, fa);
+  launch(st, nullptr, nullptr, nullptr, B, voc, walks, out, log, seq, nullptr, stream, fa, done);
 }
 void launch_fill_inline(const uint32_t* states, uint32_t words, int32_t B, const DevVocab& voc, const FillWalks& walks, uint32_t* out, OverflowLog* log,
-                        uint32_t seq, hipStream_t stream, void* logits, int elem_size, uint32_t neg_inf, int32_t V_logits, int64_t row_stride) {
+                        uint32_t seq, hipStream_t stream, hipEvent_t done, void* logits, int elem_size, uint32_t neg_inf, int32_t V_logits,
+                        int64_t row_stride) {
   if (B <= 0) return;
   const FusedApply fa{static_cast<unsigned char*>(logits), row_stride, V_logits, neg_inf};
-  if (words <= kInlineWordsSmall) launch_fill_inline_of<kInlineWordsSmall>(states, words, B, voc, walks, out, log, seq, stream, elem_size, fa);
-  else launch_fill_inline_of<kInlineWordsLarge>(states, words, B, voc, walks, out, log, seq, stream, elem_size, fa);
+  if (words <= kInlineWordsSmall) launch_fill_inline_of<kInlineWordsSmall>(states, words, B, voc, walks, out, log, seq, stream, done, elem_size, fa);
+  else launch_fill_inline_of<kInlineWordsLarge>(states, words, B, voc, walks, out, log, seq, stream, done, elem_size, fa);
 }
 
 void launch_lds_lookups(int32_t n_blocks, uint32_t hops, uint32_t* sink, hipStream_t stream) {

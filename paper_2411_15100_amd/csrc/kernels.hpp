@@ -367,9 +367,11 @@ void launch_fill(const RowDesc* rows, const uint32_t* stack_hdrs, const uint16_t
                  const DevVocab& voc, const FillWalks& walks, uint32_t* out, OverflowLog* log, uint32_t seq,
                  unsigned long long* step_counter, hipStream_t stream, void* logits = nullptr,
                  int elem_size = 0, uint32_t neg_inf = 0, int32_t V_logits = 0, int64_t row_stride = 0);
-// the same with the states in the launch (InlineStates: `words` of them, at most kInlineWordsLarge); step_counter is not supported
+// the same with the states in the launch (InlineStates: `words` of them, at most kInlineWordsLarge); step_counter is not
+// supported; `done` (may be null) is recorded with the launch
 void launch_fill_inline(const uint32_t* states, uint32_t words, int32_t B, const DevVocab& voc, const FillWalks& walks, uint32_t* out,
-                        OverflowLog* log, uint32_t seq, hipStream_t stream, void* logits, int elem_size, uint32_t neg_inf, int32_t V_logits, int64_t row_stride);
+                        OverflowLog* log, uint32_t seq, hipStream_t stream, hipEvent_t done, void* logits, int elem_size, uint32_t neg_inf,
+                        int32_t V_logits, int64_t row_stride);
 // device-resident states: move every row on by its token (ids < 0 leave a row alone)
 void launch_batch_accept(const DevBatch& bt, const DevVocab& voc, const int32_t* d_tokens, hipStream_t stream);
 // go back d_steps[b] tokens in every row (<= 0 leaves a row alone)

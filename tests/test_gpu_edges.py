@@ -295,7 +295,8 @@ def test_records_of_launched_and_staged_states_are_fixed_up(xgm, wl, rows):
     xgm.fill_next_token_bitmask_static(ms[1], d[1].data_ptr(), _stream())
     xgm.fill_and_apply(ms[2], d[2].data_ptr(), logits.data_ptr(), xgm.DTYPE_F32, 16, 16, stream=_stream())
     torch.cuda.synchronize()
-    undecided = sum(k != 1 for w in which for k in w) * 2   # tokens 4 and 5, where a parenthesis is open
+    undecided_of = [sum(k != 1 for k in w) * 2 for w in which]   # tokens 4 and 5, where a parenthesis is open
+    undecided = sum(undecided_of)
     want = [np.stack([states[k][1] for k in w]) for w in which]
     assert all(w[4] and not w[5] for k, (_, w) in enumerate(states) if k != 1)
     for k in range(3):                                      # left out, or in the one launch left allowed, until they are decided
@@ -305,6 +306,23 @@ def test_records_of_launched_and_staged_states_are_fixed_up(xgm, wl, rows):
     assert xgm.fill_overflow_fixup(_stream()) == undecided
     for k in range(3):
         assert np.array_equal(d[k].cpu().numpy(), oracle.pack_bitmask(want[k])), k
+    # records of the last eight fills are decided, those of the ninth and of an earlier static one are reported
+    for more in (7, 8):
+        xgm.fill_next_token_bitmask(ms[0], d[0].data_ptr(), _stream())
+        for _ in range(more):
+            xgm.fill_next_token_bitmask([states[1][0]], d[1].data_ptr(), _stream())
+        if more == 7:
+            assert xgm.fill_overflow_fixup(_stream()) == undecided_of[0]
+            assert np.array_equal(d[0].cpu().numpy(), oracle.pack_bitmask(want[0]))
+        else:
+            with pytest.raises(xgm.XgmError) as e:
+                xgm.fill_overflow_fixup(_stream())
+            assert e.value.status == -9
+    xgm.fill_next_token_bitmask_static(ms[1], d[1].data_ptr(), _stream())
+    xgm.fill_next_token_bitmask_static([states[1][0]], d[0].data_ptr(), _stream())
+    with pytest.raises(xgm.XgmError):
+        xgm.fill_overflow_fixup(_stream())
+    assert xgm.fill_overflow_fixup(_stream()) == 0
 
 
 # The accept kernel walks by whole waves and puts candidates in order all pairs at once; its tables are staged as far as
@@ -404,3 +422,70 @@ def test_walks_by_waves_and_by_lanes(xgm, wl, V):
                 xgm.fill_next_token_bitmask(some, d_mask.data_ptr(), _stream())
                 xgm.fill_overflow_fixup(_stream())
             assert np.array_equal(d_mask.cpu().numpy(), np.stack([want[b] for b in rows])), (rows, k)
+
+
+# What a fill reads is kept until it is done, also where a program drops its matchers and caches right after the call: the
+# library remembers 16 to 32 fills whose states went along with the launch (1 row) and 8 that were staged (200), and waits
+# for those before it forgets them.
+@pytest.mark.parametrize("form,rows", [("fill", 1), ("fill", 200), ("fused", 1), ("fused", 200), ("static", 1)])
+def test_fills_are_forgotten_only_when_they_are_done(xgm, wl, form, rows):
+    vocab = si.make_vocab("bpe", 2048, 3)
+    m = xgm.Matcher(cache=xgm.Cache(xgm.Grammar(si.JSON_GRAMMAR, "root"), wl.make_xgm_vocab(vocab)))
+    ms = [m] * rows
+    d_mask = torch.zeros((rows, xgm.bitmask_words(2048)), dtype=torch.int32, device="cuda")
+    logits = torch.zeros((rows, 2048), device="cuda")
+
+    def call():
+        if form == "fill":
+            xgm.fill_next_token_bitmask(ms, d_mask.data_ptr(), _stream())
+        elif form == "static":
+            xgm.fill_next_token_bitmask_static(ms, d_mask.data_ptr(), _stream())
+        else:
+            xgm.fill_and_apply(ms, d_mask.data_ptr(), logits.data_ptr(), xgm.DTYPE_F32, 2048, 2048, _stream())
+
+    for _ in range(9):
+        call()
+    big = torch.empty(1 << 30, dtype=torch.int32, device="cuda")   # 4 GiB: about a millisecond to fill
+    torch.cuda.synchronize()
+    for k in range(60):
+        big.fill_(k)
+    before = torch.cuda.Event()
+    before.record()
+    for _ in range(8):
+        call()
+    assert not before.query()
+    for _ in range(25 if rows == 1 else 1):
+        call()
+    assert before.query()
+    want = oracle.EarleyMatcher(oracle.Grammar(si.JSON_GRAMMAR, "root")).mask(vocab)
+    assert np.array_equal(d_mask.cpu().numpy(), np.tile(oracle.pack_bitmask(want), (rows, 1)))
+
+
+# Fills on more streams than the library remembers launches of (4), in turn: those of the others are staged; after a thousand
+# fills on one stream the others' places are taken over.
+def test_fills_on_many_streams(xgm, wl):
+    vocab = si.make_vocab("bpe", 2048, 3)
+    caches = [xgm.Cache(xgm.Grammar(t, "root"), wl.make_xgm_vocab(vocab)) for t in (si.JSON_GRAMMAR,)]
+    og = oracle.Grammar(si.JSON_GRAMMAR, "root")
+    streams = [torch.cuda.Stream() for _ in range(7)]
+    for lap in range(25):
+        if lap in (8, 16):
+            m = xgm.Matcher(cache=caches[0])
+            some = torch.zeros((1, xgm.bitmask_words(2048)), dtype=torch.int32, device="cuda")
+            for _ in range(1100):
+                xgm.fill_next_token_bitmask([m], some.data_ptr(), int(streams[lap % 7].cuda_stream))
+        texts = [b"[" * (1 + (lap + k) % 5) for k in range(7)]
+        masks = [torch.full((2, xgm.bitmask_words(2048)), -1, dtype=torch.int32, device="cuda") for _ in streams]
+        torch.cuda.synchronize()
+        for form in (xgm.fill_next_token_bitmask, xgm.fill_next_token_bitmask_static):
+            for s, t, d in zip(streams, texts, masks):
+                m = xgm.Matcher(cache=caches[0])
+                m.accept_bytes(t)
+                if form is xgm.fill_next_token_bitmask_static:
+                    torch.cuda.synchronize()   # (its calls share their staging: ordered by the caller)
+                form([m], d[1 if form is xgm.fill_next_token_bitmask_static else 0:].data_ptr(), int(s.cuda_stream))
+        torch.cuda.synchronize()
+        for t, d in zip(texts, masks):
+            om = oracle.EarleyMatcher(og)
+            assert om.advance(t)
+            assert np.array_equal(d.cpu().numpy(), np.tile(oracle.pack_bitmask(om.mask(vocab)), (2, 1)))
