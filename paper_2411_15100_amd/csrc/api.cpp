@@ -320,7 +320,8 @@ struct FillSlot {
   bool used = false;
   PendingFill fill;
 };
-// The fills of one stream whose states went along with the launch.  What they read has to be kept until they are done,
+// The fills of one stream that have no event of their own: those whose states went along with the launch, and all of the
+// entry point that allocates nothing.  What they read has to be kept until they are done,
 // and an event costs a launch 3.7 us (4.3 without); launches of one stream end one after the other, so that one event at
 // the end of a group speaks for all of it (4.35 us per fill of one row; 4.5 with groups of 8).  A group is entered again
 // when the other one is full, and waits for its event then: the last kGroup fills at least are kept, twice as many at most.
@@ -335,6 +336,9 @@ struct LaunchRing {
     PendingFill fill;
     uint32_t states[kInlineWordsLarge];  // for the fixup
   } slot[2 * kGroup];
+  Slot& enter();         // the next fill's slot
+  hipEvent_t closing();  // the event that the next fill is to record, or null
+  void launched();       // it has been enqueued, and has recorded it
 };
 struct Context {
   std::mutex mu;
@@ -395,7 +399,21 @@ void set_pending(PendingFill& f, uint32_t seq, uint64_t number, int32_t B, int32
   for (int32_t b = 0; b < B; ++b) { ++ms[b]->c->refs; f.caches.push_back(ms[b]->c); }
 }
 
-// The ring of a stream, or null: the fill is staged then.  A stream takes over the ring of one that has not been heard of
+LaunchRing::Slot& LaunchRing::enter() {
+  const int group = next / kGroup;
+  if (next % kGroup == 0 && recorded[group]) {
+    HIP_OK(hipEventSynchronize(done[group]));
+    recorded[group] = false;
+    for (int k = 0; k < kGroup; ++k) forget(slot[next + k].fill);
+  }
+  return slot[next];
+}
+hipEvent_t LaunchRing::closing() { return next % kGroup == kGroup - 1 ? done[next / kGroup] : nullptr; }
+void LaunchRing::launched() {
+  if (closing()) recorded[next / kGroup] = true;
+  next = (next + 1) % (2 * kGroup);
+}
+// The ring of a stream, or null: the fill is staged then, and followed by an event or waited for.  A stream takes over the ring of one that has not been heard of
 // for a thousand fills, when the device has come to rest; more streams than rings at the same time are staged.
 LaunchRing* launch_ring(Context& c, bool of_static, hipStream_t stream) {
   if (stream == hipStreamPerThread) return nullptr;  // (one handle for the streams of all threads)
@@ -1449,31 +1467,19 @@ static int fill_impl(xgm_matcher* const* ms, int32_t B, int32_t* d_bitmask, void
     OverflowLog* log = overflow_log();
     uint32_t captured_states[kInlineWordsLarge];
     LaunchRing* ring = capturing ? nullptr : launch_ring(C, use_static, stream);
-    uint32_t* states = captured_states;
-    int group = 0;
-    bool closes = false;
-    if (ring) {
-      group = ring->next / LaunchRing::kGroup;
-      closes = ring->next % LaunchRing::kGroup == LaunchRing::kGroup - 1;
-      if (ring->next % LaunchRing::kGroup == 0 && ring->recorded[group]) {
-        HIP_OK(hipEventSynchronize(ring->done[group]));
-        ring->recorded[group] = false;
-        for (int k = 0; k < LaunchRing::kGroup; ++k) forget(ring->slot[ring->next + k].fill);
-      }
-      states = ring->slot[ring->next].states;
-    }
+    LaunchRing::Slot* slot = ring ? &ring->enter() : nullptr;
+    uint32_t* states = slot ? slot->states : captured_states;
     const size_t words = ring || capturing ? pack_inline(ms, B, n_stacks, n_frames, states) : 0;
     if (words != 0) {
       if (use_static) pack_staged(ms, B, n_stacks, g_static_host);
       const uint32_t seq = ++C.seq;
       launch_fill_inline(states, (uint32_t)words, B, v->dv, walks, reinterpret_cast<uint32_t*>(d_bitmask), log, seq, stream,
-                         closes ? ring->done[group] : nullptr, fused ? fused->d_logits : nullptr, fused ? fused->esize : 0,
+                         ring ? ring->closing() : nullptr, fused ? fused->d_logits : nullptr, fused ? fused->esize : 0,
                          fused ? fused->neg_inf : 0u, fused ? fused->V_logits : 0, fused ? fused->row_stride : 0);
       HIP_OK(hipGetLastError());
       if (ring) {
-        set_pending(ring->slot[ring->next].fill, seq, ++C.fills[use_static], B, d_bitmask, states, true, ms);
-        if (closes) ring->recorded[group] = true;
-        ring->next = (ring->next + 1) % (2 * LaunchRing::kGroup);
+        set_pending(slot->fill, seq, ++C.fills[use_static], B, d_bitmask, states, true, ms);
+        ring->launched();
       }
       return XGM_OK;
     }
@@ -1484,7 +1490,9 @@ static int fill_impl(xgm_matcher* const* ms, int32_t B, int32_t* d_bitmask, void
   void* h_buf = nullptr;
   void* d_buf = nullptr;
   FillSlot* ring = nullptr;
+  LaunchRing* kept = nullptr;  // (of the static staging: keeps the caches)
   if (use_static) {
+    if (!capturing && (kept = launch_ring(C, true, stream))) kept->enter();
     HIP_OK(static_scratch(&d_buf));
     h_buf = g_static_host;
   } else {
@@ -1522,6 +1530,12 @@ static int fill_impl(xgm_matcher* const* ms, int32_t B, int32_t* d_bitmask, void
     HIP_OK(hipEventRecord(ring->done, stream));
     ring->used = true;
     C.next_slot = (C.next_slot + 1) % Context::kSlots;
+  } else if (kept) {
+    if (kept->closing()) HIP_OK(hipEventRecord(kept->closing(), stream));
+    set_pending(kept->slot[kept->next].fill, 0u, 0u, B, d_bitmask, h_buf, false, ms);
+    kept->launched();
+  } else if (!capturing) {
+    HIP_OK(hipStreamSynchronize(stream));
   }
   set_pending(ring ? ring->fill : C.static_fill, seq, ++C.fills[use_static], B, d_bitmask, h_buf, false, ms);
   return XGM_OK;
