@@ -855,7 +855,10 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
     launch_rows_equal(acc_id, N, dv.W, d_rep, d_equal, stream);
 
     // ---- keys: level 1 = (node with context-dependent tokens, context of its rule), level 2 = (level-1
-    // key, context of that context node's rule)
+    // key, context of that context node's rule).  Only nodes that can be on top of a stack with a frame below it have
+    // any: nothing asks for those of the others, which hold most of the context-dependent tokens (a node where a rule
+    // has just ended leaves its frame in front of every byte that may follow the rule: 9.8 of the 10.1 M pairs of the
+    // largest schema grammar at 151936 tokens, 6.0 of the 6.8 M of the C/SQL-like one at 128256).
     std::vector<uint32_t> ctx_off(A.rule_names.size() + 1, 0);
     std::vector<uint16_t> ctx_node;
     for (size_t r = 0; r < A.rule_names.size(); ++r) {
@@ -874,6 +877,7 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
     for (int32_t n = 0; n < N; ++n) {
       node_off[n] = (uint32_t)n_base;
       const uint64_t m = n_ctx(A.node_rule[n]);
+      if (!A.node_on_top[n]) continue;
       if (c->unc_count[n] > 0 && m > 0) {
         c->k_base_host[0][n] = (uint32_t)key_node.size();
         for (int32_t r1 : A.contexts[A.node_rule[n]]) key_node.push_back((uint16_t)r1);
@@ -932,14 +936,14 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
     uint16_t* d_base_node = arena.array<uint16_t>((size_t)n_base);
     uint32_t* d_exits = arena.array<uint32_t>((size_t)n_base);
     {
-      std::vector<uint32_t> identity((size_t)N);
-      std::iota(identity.begin(), identity.end(), 0u);
-      uint32_t* d_identity = arena.upload(identity, stream);
+      std::vector<uint32_t> row_of((size_t)N);
+      for (int32_t n = 0; n < N; ++n) row_of[n] = A.node_on_top[n] ? (uint32_t)n : kNoKey;
+      uint32_t* d_row_of = arena.upload(row_of, stream);
       uint32_t* d_cursor = arena.upload(node_off, stream);
       // In byte-sorted order where the rank-space rows of all nodes are still there (one batch): the walks of
       // neighbouring lanes then share prefixes, as in the classify kernel.
-      if (one_batch) launch_rows_to_lists(unc_rank, dv.WR, dv.id_of_rank, N, d_identity, 1, d_cursor, d_base_ids, d_base_node, stream);
-      else launch_rows_to_lists(unc_id, dv.W, nullptr, N, d_identity, 1, d_cursor, d_base_ids, d_base_node, stream);
+      if (one_batch) launch_rows_to_lists(unc_rank, dv.WR, dv.id_of_rank, N, d_row_of, 1, d_cursor, d_base_ids, d_base_node, stream);
+      else launch_rows_to_lists(unc_id, dv.W, nullptr, N, d_row_of, 1, d_cursor, d_base_ids, d_base_node, stream);
     }
     uint32_t* d_counts = arena.array<uint32_t>(n_slots);
     HIP_OK(hipMemsetAsync(d_counts, 0, n_slots * 4, stream));
@@ -962,9 +966,9 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
     args.exits = d_exits;
     args.tiles = arena.upload(tiles, stream);
     args.n_tiles = (uint32_t)tiles.size();
-    // (a pair leaves at most about one record per level on the grammars measured: 0.08 per pair for schema
-    // grammars, 0.8 for a C-like one; the pass is run again with more room if this is not enough)
-    args.res_cap = (uint32_t)std::min<uint64_t>(std::max<uint64_t>(n_base, 1u << 16), 1u << 25);
+    // (a pair leaves at most about two records per level on the grammars measured: 0.3 to 1.9 for schema grammars, 0.7 for
+    // a C-like one, 1.1 for a scripting one; the pass is run again with more room if this is not enough)
+    args.res_cap = (uint32_t)std::min<uint64_t>(std::max<uint64_t>(2 * n_base, 1u << 17), 1u << 25);
     for (int l = 0; l + 1 < c->levels; ++l) args.res[l] = arena.array<uint4>(args.res_cap);
     args.res_count = arena.array<uint32_t>(kCtxLevels + 1);
     {

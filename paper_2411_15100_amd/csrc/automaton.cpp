@@ -895,6 +895,9 @@ Automaton compile_grammar(const std::string& text, const std::string& root) {
     }
   }
   const int NR = (int)order.size();
+  A.node_on_top.assign(total, 0);
+  for (auto& e : A.bedges.items) A.node_on_top[e.to] = !A.node_dead_end[e.to];
+  for (auto& e : A.redges.items) A.node_on_top[e.to] = !A.node_dead_end[e.to];
 
   // left recursion: a chain of references taken at rule starts that returns to its origin
   std::vector<int> callees_first;  // the rules, those entered at a rule's start before the rule

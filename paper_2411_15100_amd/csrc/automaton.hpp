@@ -91,6 +91,9 @@ struct Automaton {
   std::vector<int32_t> node_rule;
   std::vector<uint8_t> node_final;
   std::vector<uint8_t> node_dead_end;         // accepting and without outgoing edges: all it can do is return
+  // The node can be on top of a stack that has other frames: a byte or an instance of a rule leads to it, and it has
+  // something of its own to do (a top that can only return is returned from at once).
+  std::vector<uint8_t> node_on_top;
   Rows<ByteEdge> bedges;                      // per node: sorted, disjoint
   Rows<RefEdge> redges;                       // per node
   std::vector<int32_t> rule_start;            // per rule: global node id

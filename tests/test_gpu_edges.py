@@ -2,11 +2,14 @@
 level, a tile or a segment begins, ends or is just full.  Expected masks come
 from the CPU oracle."""
 
+import itertools
+
 import numpy as np
 import pytest
 
 import oracle
 import synth_inputs as si
+from synth_inputs.vocab import Vocab
 
 pytestmark = pytest.mark.gpu
 
@@ -389,6 +392,37 @@ def test_device_accept_gives_the_engines_stacks(xgm, wl, seed):
                 assert [read[b].stack(s) for s in range(read[b].num_stacks())] == stacks, (texts[b], toks[ids[b]])
                 n_multi += len(stacks) > 1
     assert n_ok > 500 and n_rejected > 200 and n_multi > 50, (n_ok, n_rejected, n_multi, n_host)
+
+
+# Only nodes that can be on top of a stack have per-context lists: inside a rule whose start is entered again, behind calls
+# in tail position, at a rule's end (also at the bottom of the stack).  Every state of up to five bytes.
+@pytest.mark.parametrize("text", ['root ::= "(" a ")" "."\na ::= ("x" "y")* "z"', 'root ::= "(" b\nb ::= "x" b | "[" root "]" | ")"',
+                                  'root ::= a "," a | "(" root ")"\na ::= "x" a | "x" | "[" a "]"', 'root ::= "(" c c ")"\nc ::= "x"* "y" | "[" root "]"'])
+def test_every_top_has_its_lists(xgm, wl, text):
+    alphabet = b"()[]xyz.,"
+    toks = [bytes(t) for n in (1, 2, 3) for t in itertools.product(alphabet, repeat=n)] + [b"))))", b"]]]]", b")])])", b""]
+
+    vocab = Vocab(np.frombuffer(b"".join(toks), dtype=np.uint8).copy(), np.cumsum([0] + [len(t) for t in toks]).astype(np.int64),
+                  np.array([len(toks) - 1], dtype=np.int32))
+    cache, og = xgm.Cache(xgm.Grammar(text, "root"), wl.make_xgm_vocab(vocab)), oracle.Grammar(text, "root")
+    ms, want, texts = [], [], [b""]
+    for t in texts:
+        om = oracle.EarleyMatcher(og)
+        if t and not om.advance(t):
+            continue
+        m = xgm.Matcher(cache=cache)
+        if t:
+            m.accept_bytes(t)
+        ms.append(m)
+        want.append(om.mask(vocab))
+        if len(t) < 5:
+            texts += [t + bytes([c]) for c in alphabet]
+    want = oracle.pack_bitmask(np.stack(want))
+    resident = xgm.DeviceBatch(ms, history=0, stream=_stream())
+    for fill in (lambda d: xgm.fill_next_token_bitmask(ms, d, _stream()), lambda d: resident.fill_next_token_bitmask(d, _stream())):
+        d_mask = torch.full((len(ms), xgm.bitmask_words(len(toks))), -1, dtype=torch.int32, device="cuda")
+        fill(d_mask.data_ptr())
+        assert np.array_equal(d_mask.cpu().numpy(), want)
 
 
 # Few walks of a row go to waves, unless a cache of the batch (the markup grammar's) is known to walk to the limits.
