@@ -728,7 +728,6 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
     const size_t row_bytes = (size_t)dv.WR * 4;
     int32_t batch = (int32_t)std::max<size_t>(32, std::min<size_t>((size_t)N, ((size_t)512 << 20) / row_bytes));
     if (g_build_batch_nodes > 0) batch = std::max(32, std::min(N, g_build_batch_nodes.load()));
-    if (batch < N) batch &= ~31;  // (the classify kernel wants batches of nodes to begin at multiples of 32)
     uint32_t* acc_rank = arena.array<uint32_t>((size_t)batch * dv.WR);
     uint32_t* unc_rank = arena.array<uint32_t>((size_t)batch * dv.WR);
     uint32_t* plain_rank = keep_plain ? arena.array<uint32_t>((size_t)batch * dv.WR) : nullptr;
@@ -790,11 +789,14 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
     // over the limits only afterwards; if there are any, the patched rows are permuted again.
     const bool one_batch = batch >= N;
     uint4* d_first_byte = arena.array<uint4>((size_t)256 * first_byte_words(N));
+    uint32_t* d_pairs = arena.array<uint32_t>((size_t)batch * (dv.WR / 2));
+    uint32_t* d_n_pairs = arena.array<uint32_t>(1);
     launch_first_byte(tab, d_first_byte, stream);
     for (int32_t node0 = 0; node0 < N; node0 += batch) {
       const int32_t nb = std::min(batch, N - node0);
       HIP_OK(hipEventRecord(ev0, stream));
-      launch_classify(tab, dv, node0, nb, d_first_byte, acc_rank, unc_rank, plain_rank, d_plain_count, log, seq, stream);
+      launch_classify(tab, dv, ClassifyArgs{node0, nb, d_first_byte, first_byte_words(N), acc_rank, unc_rank, plain_rank, d_plain_count,
+                                            d_pairs, d_n_pairs, log, seq}, stream);
       HIP_OK(hipEventRecord(ev1, stream));
       HIP_OK(hipGetLastError());
       if (!one_batch) {

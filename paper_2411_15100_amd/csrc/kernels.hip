@@ -141,23 +141,25 @@ struct LiveView {
 };
 
 // ---------------------------------------------------------------- kernel (a)
-// Workgroup size of the classify kernel.  A grammar whose staged tables are
+// Workgroup size of the classify kernels.  A grammar whose staged tables are
 // small runs with 256 threads (many workgroups per compute unit, short tails);
 // one that needs most of the LDS budget runs with 768, so that two workgroups
 // per compute unit still give 6 waves per SIMD.
 constexpr int kClassifyThreadsSmall = 256, kClassifyThreadsLarge = 768;
 constexpr uint32_t kClassifySmallStage = 32 * 1024;
-// nodes a thread classifies its token at, one after the other: few for small tables (more, shorter-lived
-// workgroups: the slowest walks weigh less), more where every workgroup has a large table image to stage
-constexpr int kNodesPerBlockSmall = 4, kNodesPerBlockMany = 16, kNodesPerBlockLarge = 64;
-constexpr int kManyNodes = 1024;  // small tables but this many nodes: plenty of workgroups anyway
+// Tokens are classified in byte-sorted order, 64 of them (an item) at a time: neighbours mostly share prefixes and
+// control flow.  A workgroup of classify_kernel owns up to kClassifyItems items, which its waves draw from a counter in
+// LDS, and kClassifyNodes nodes, one for each lane.
+constexpr int kClassifyNodes = 64, kClassifyItems = 64;
+// items per wave of a workgroup, on average: with large tables four, which are staged for fewer workgroups then (11867-node
+// schema grammar, 151936 tokens: 533 us with one, 463 with two, 381 with four or five); with small ones two (C/SQL-like
+// grammar, 128256 tokens: 99 us with one, 77 with two, 68 with four; JSON 38, 40, 41)
+constexpr int kItemsPerWaveSmall = 2, kItemsPerWaveLarge = 4;
+// A run of fewer tokens is not looked at by its prefix: an item of many runs (the tokens that begin with the rarer bytes)
+// would take a walk for each of them, one after the other.
+constexpr int kPrefixTokens = 16;
+constexpr uint32_t kPairNodeBits = 15;  // (XGM_MAX_NODES; the item number takes the bits above)
 
-// One thread owns one token (byte-sorted order, so a wave's 64 tokens are
-// neighbours in the sorted vocabulary and mostly share prefixes and control
-// flow) and classifies it at several nodes, the token staying in
-// registers.  Each wave packs its 64 results per node with a ballot into two
-// mask words of the rank-space bitsets.  The automaton tables (as many node
-// headers as `n_near`) are first copied into shared memory.
 // What the first byte of a token settles at every node, as bitsets over the nodes: for byte c and the 32 nodes
 // of word w, `x` = the node can consume c inside its frame (a walk decides), `y` = it cannot, may end its rule
 // here and c can follow that rule in some context (the token leaves the frame at position 0:
@@ -186,120 +188,172 @@ __global__ __launch_bounds__(kFirstByteThreads) void first_byte_kernel(DevTables
   out[t] = q;
 }
 
-template <int kClassifyThreads, class Tab>
-__device__ __forceinline__ void classify_body(const Tab& T, const DevVocab& voc, int32_t node0, int32_t n_nodes,
-                                              const uint4* __restrict__ first_byte, uint32_t n_words,
-                                              uint32_t* __restrict__ acc_rank, uint32_t* __restrict__ unc_rank,
-                                              uint32_t* __restrict__ plain_rank, uint32_t* __restrict__ plain_count,
-                                              OverflowLog* log, uint32_t seq, int32_t nodes_per_block,
-                                              int32_t items_per_wave, uint32_t* next_item) {
-  // A workgroup owns a run of kClassifyThreads * items_per_wave tokens, cut into items of 64; its waves draw
-  // items from a counter in LDS, so that none of them waits for the slowest walks of another (a workgroup keeps
-  // its LDS, and so its place on the compute unit, until its last wave is done).
-  const int32_t chunk0 = blockIdx.x * kClassifyThreads * items_per_wave;
-  const int32_t n_items = min((kClassifyThreads / 64) * items_per_wave, (voc.V - chunk0 + 63) / 64);
-  for (;;) {
-  int32_t item = 0;
-  if ((threadIdx.x & 63u) == 0u) item = (int32_t)atomicAdd(next_item, 1u);
-  item = __builtin_amdgcn_readfirstlane(item);
-  if (item >= n_items) break;
-  const int32_t r = chunk0 + item * 64 + (int32_t)(threadIdx.x & 63u);
-  const bool live_lane = r < voc.V;
-  uint4 tk = make_uint4(0, 0, 0, 0);
-  const uint8_t* ext = voc.bytes;
-  int len = 0;
-  if (live_lane) {
-    tk = voc.tok_by_rank[r];
-    len = (int)(tk.w >> 24);
-    if (len >= 15) {
+// The token of byte-sorted rank r.
+struct RankedToken {
+  uint4 tk;
+  const uint8_t* ext;
+  int len;  // 0: no such rank
+};
+__device__ __forceinline__ RankedToken load_ranked(const DevVocab& voc, int32_t r) {
+  RankedToken t{make_uint4(0u, 0u, 0u, 0u), voc.bytes, 0};
+  if (r < voc.V) {
+    t.tk = voc.tok_by_rank[r];
+    t.len = (int)(t.tk.w >> 24);
+    if (t.len >= 15) {
       const int32_t id = voc.id_of_rank[r];
-      ext = voc.bytes + voc.off_by_id[id];
-      if (len == 255) len = (int)(voc.off_by_id[id + 1] - voc.off_by_id[id]);
+      t.ext = voc.bytes + voc.off_by_id[id];
+      if (t.len == 255) t.len = (int)(voc.off_by_id[id + 1] - voc.off_by_id[id]);
     }
   }
-  const int32_t word = (chunk0 + item * 64) >> 5;  // even
-  // Do all tokens of the wave begin with the same byte?  (In byte-sorted order most waves' do.)  Then what the
-  // first byte settles at a node is the same for every lane, and the nodes that need no walk need no loop.
-  const bool has = live_lane && len > 0;
-  const unsigned long long has_mask = __ballot(has);
-  const uint32_t c0 = tk.x & 0xFFu;
-  const uint32_t c_wave = has_mask ? (uint32_t)__shfl((int)c0, __ffsll((long long)has_mask) - 1, 64) : 0u;
-  const bool one_first_byte = has_mask != 0ull && __ballot(has && c0 == c_wave) == has_mask;
-  const int32_t n_begin = blockIdx.y * nodes_per_block;
-  const int32_t n_end = min(n_begin + nodes_per_block, n_nodes);
-  // Most pairs are settled by the token's first byte: if the node cannot
-  // consume it inside its frame, the token is rejected - or, at a node where
-  // the rule may end, leaves the frame at position 0.  The nodes of a block lie in whole 32-node words of
-  // the first-byte bitsets, or inside one (node0 and nodes_per_block are aligned for that).
-  for (int32_t k0 = n_begin; k0 < n_end; k0 += 32) {
-    uint4 fb = make_uint4(0u, 0u, 0u, 0u);
-    if (live_lane && len > 0) fb = first_byte[(size_t)(tk.x & 0xFFu) * n_words + ((uint32_t)(node0 + k0) >> 5)];
-    const uint32_t shift = (uint32_t)(node0 + k0) & 31u;
-    const uint32_t needs_walk = fb.x >> shift, exits_follow = fb.y >> shift, exits_plain = fb.z >> shift;
-    const int32_t k1 = min(k0 + 32 - (int32_t)shift, n_end);
-    // Lane j of the wave keeps the wave's result words for the j-th of these nodes; the lanes then write
-    // them out together (a handful of store instructions per 32 nodes instead of several per node).
-    const uint32_t lane = threadIdx.x & 63u;
-    unsigned long long keep_a = 0ull, keep_u = 0ull, keep_p = 0ull;
-    if (one_first_byte) {
-      // the lane's own node, settled by the first byte unless it is walked below
-      const uint4 fbw = first_byte[(size_t)c_wave * n_words + ((uint32_t)(node0 + k0) >> 5)];  // (the same for the wave)
-      const uint32_t span = k1 - k0 >= 32 ? 0xFFFFFFFFu : (1u << (k1 - k0)) - 1u;
-      if (lane < 32u && (((fbw.y >> shift) >> lane) & 1u)) keep_u = has_mask;
-      if (lane < 32u && (((fbw.z >> shift) >> lane) & 1u)) keep_p = has_mask;
-      for (uint32_t todo = (fbw.x >> shift) & span; todo; todo &= todo - 1u) {
-        const int32_t k = k0 + __ffs(todo) - 1;
-        int res = kReject;
-        if (has) {
-          res = walk_token<true>(T, tk, ext, len, (uint32_t)(node0 + k), (const uint16_t*)nullptr, 1u, nullptr, T.follow_of(node0 + k));
-          if (res == kOverflow) { record_overflow(log, seq, (uint32_t)k, (uint32_t)r); res = kReject; }
+  return t;
+}
+
+// What a workgroup of the classify kernel keeps beside the tables.
+struct ClassifyShared {
+  uint32_t next_item, first_pair;
+  unsigned long long open[kClassifyItems];  // per item: the nodes at which its tokens have to be walked
+};
+
+// Kernel (a), first part: what can be said about an item as a whole.  Lane j of a wave looks at node j.  The first byte
+// settles most (item, node) pairs (first_byte_kernel).  Where it does not, the prefix that the item's tokens have in
+// common often does: the lane walks the prefix alone, and if no path can consume all of it, every path of every token ends
+// where it does, with the same exits from the start frame.  (Where white space may come first - two nodes in ten of a schema
+// grammar, and a quarter of the tokens begin with a space - the second byte decides nearly always.)  What is left is
+// listed for classify_walks_kernel: 338 K pairs of an 11867-node schema grammar and 151936 tokens, where the first byte
+// alone leaves 1.56 M of the 28 M.
+// Both kernels write whole words of the rank-space bitsets, 64 tokens of one node.  Bound by these stores, one line per
+// node: 381 us for that grammar (451 MB), and 365 us for the walks, where one kernel that walked all pairs that the first
+// byte leaves took 1663 us; JSON (128256 tokens) 41 + 36 us, before 163, where a few waves with the walks of whole
+// strings were the last to finish; 32000 tokens 20 + 30, before 65; a scripting grammar 51 + 175, before 394; the
+// C/SQL-like grammar, whose identifiers are walked to their ends at a hundred nodes, 77 + 1032, before 1283.
+template <class Tab>
+__device__ __forceinline__ void classify_body(const Tab& T, ClassifyShared& sm, const DevVocab& voc, const ClassifyArgs& a, int32_t n_items_max) {
+  // A workgroup owns a run of up to kClassifyItems items of 64 tokens, and kClassifyNodes nodes; lane j of a wave looks at
+  // node j.
+  const int32_t item0 = blockIdx.x * n_items_max;
+  const int32_t n_items = min(n_items_max, (voc.V + 63) / 64 - item0);
+  const int32_t k0 = blockIdx.y * kClassifyNodes, n_own = min(kClassifyNodes, a.n_nodes - k0);
+  const uint32_t lane = threadIdx.x & 63u;
+  const bool own = (int32_t)lane < n_own;
+  const uint32_t own_node = (uint32_t)(a.node0 + k0 + min((int32_t)lane, n_own - 1));
+  for (;;) {
+    int32_t item = 0;
+    if (lane == 0u) item = (int32_t)atomicAdd(&sm.next_item, 1u);
+    item = __builtin_amdgcn_readfirstlane(item);
+    if (item >= n_items) break;
+    const RankedToken t = load_ranked(voc, (item0 + item) * 64 + (int32_t)lane);
+    const uint32_t c0 = t.tk.x & 0xFFu;
+    const bool too_long = __ballot(t.len > kMaxTokenLen) != 0ull;  // (the walk refuses such a token)
+    unsigned long long keep_u = 0ull, keep_p = 0ull, open = 0ull;
+    // The tokens come in byte-sorted order: those that begin with the same byte (all of them, in most items) lie side
+    // by side and share a prefix.
+    for (unsigned long long left = __ballot(t.len > 0); left;) {
+      const int first = __ffsll((long long)left) - 1;
+      const uint32_t c = (uint32_t)__builtin_amdgcn_readlane((int)c0, first);
+      const unsigned long long run = __ballot(t.len > 0 && c0 == c);
+      left &= ~run;
+      // what the first byte settles: if the node cannot consume it inside its frame, the token is rejected - or, at a
+      // node where the rule may end, leaves the frame at position 0
+      const uint4 fb = a.first_byte[(size_t)c * a.n_words + (own_node >> 5)];
+      if ((fb.y >> (own_node & 31u)) & 1u) keep_u |= run;
+      if ((fb.z >> (own_node & 31u)) & 1u) keep_p |= run;
+      bool walk = own && ((fb.x >> (own_node & 31u)) & 1u);
+      const unsigned long long needs = __ballot(walk);
+      // what the common prefix settles: where no path consumes all of it, every token of the run fares as the prefix does
+      if (__popcll(run) >= kPrefixTokens && (needs & (needs - 1ull)) && !too_long) {
+        const int last = 63 - __clzll((long long)run);
+        auto of = [&](uint32_t v, int l) { return (uint32_t)__builtin_amdgcn_readlane((int)v, l); };
+        const uint4 pre = make_uint4(of(t.tk.x, first), of(t.tk.y, first), of(t.tk.z, first), of(t.tk.w, first));
+        const int shortest = (int)min(of((uint32_t)t.len, first), of((uint32_t)t.len, last));
+        const uint32_t d0 = pre.x ^ of(t.tk.x, last), d1 = pre.y ^ of(t.tk.y, last), d2 = pre.z ^ of(t.tk.z, last);
+        const uint32_t d3 = (pre.w ^ of(t.tk.w, last)) | 0xFF000000u;
+        const int same = (d0 ? __ffs((int)d0) - 1 : d1 ? __ffs((int)d1) + 31 : d2 ? __ffs((int)d2) + 63 : __ffs((int)d3) + 95) / 8;
+        const int n = min(same, shortest);
+        if (n >= 2 && walk) {
+          const int res = walk_token<true>(T, pre, voc.bytes, n, own_node, (const uint16_t*)nullptr, 1u, nullptr, T.follow_of(own_node));
+          if (res == kUncertain) keep_u |= run;
+          if (res == kUncertainPlain) keep_p |= run;
+          walk = res == kAccept || res == kOverflow;
         }
-        const unsigned long long a = __ballot(res == kAccept);
-        const unsigned long long u = __ballot(res == kUncertain);
-        const unsigned long long p = __ballot(res == kUncertainPlain);
-        if (lane == (uint32_t)(k - k0)) { keep_a = a; keep_u = u; keep_p = p; }
       }
-    } else
-    for (int32_t k = k0; k < k1; ++k) {
-      const uint32_t bit = 1u << (k - k0);
-      int res = (exits_follow & bit) ? kUncertain : (exits_plain & bit) ? kUncertainPlain : kReject;
-      if (needs_walk & bit) {
-        res = walk_token<true>(T, tk, ext, len, (uint32_t)(node0 + k), (const uint16_t*)nullptr, 1u, nullptr, T.follow_of(node0 + k));
-        if (res == kOverflow) { record_overflow(log, seq, (uint32_t)k, (uint32_t)r); res = kReject; }
-      }
-      const unsigned long long a = __ballot(res == kAccept);
-      const unsigned long long u = __ballot(res == kUncertain);
-      const unsigned long long p = __ballot(res == kUncertainPlain);
-      if (lane == (uint32_t)(k - k0)) { keep_a = a; keep_u = u; keep_p = p; }
+      open |= __ballot(walk);
     }
-    if ((int32_t)lane < k1 - k0 && word < voc.WR) {
-      const size_t at = (size_t)(k0 + (int32_t)lane) * voc.WR + word;  // word is even: 8-byte aligned
-      *reinterpret_cast<uint2*>(acc_rank + at) = make_uint2((uint32_t)keep_a, (uint32_t)(keep_a >> 32));
-      *reinterpret_cast<uint2*>(unc_rank + at) = make_uint2((uint32_t)keep_u, (uint32_t)(keep_u >> 32));
-      if (plain_rank) *reinterpret_cast<uint2*>(plain_rank + at) = make_uint2((uint32_t)keep_p, (uint32_t)(keep_p >> 32));
-      if (keep_p) atomicAdd(&plain_count[node0 + k0 + (int32_t)lane], (uint32_t)__popcll(keep_p));
+    if (lane == 0u) sm.open[item] = open;
+    if (own && !((open >> lane) & 1ull)) {
+      const size_t at = (size_t)(k0 + (int32_t)lane) * voc.WR + (uint32_t)((item0 + item) * 2);  // an even word: 8-byte aligned
+      *reinterpret_cast<uint2*>(a.acc_rank + at) = make_uint2(0u, 0u);
+      *reinterpret_cast<uint2*>(a.unc_rank + at) = make_uint2((uint32_t)keep_u, (uint32_t)(keep_u >> 32));
+      if (a.plain_rank) *reinterpret_cast<uint2*>(a.plain_rank + at) = make_uint2((uint32_t)keep_p, (uint32_t)(keep_p >> 32));
+      if (keep_p) atomicAdd(&a.plain_count[own_node], (uint32_t)__popcll(keep_p));
     }
   }
+  __syncthreads();
+  // the (item, node) pairs that are left are listed for classify_walks_kernel
+  const uint32_t n_open = (int32_t)lane < n_items ? (uint32_t)__popcll(sm.open[lane]) : 0u;
+  uint32_t upto = n_open;  // pairs of the items up to the lane's
+#pragma unroll
+  for (uint32_t d = 1; d < 64u; d <<= 1) {
+    const uint32_t v = __shfl_up(upto, d, 64);
+    if (lane >= d) upto += v;
+  }
+  if (threadIdx.x == 63u) sm.first_pair = upto ? atomicAdd(a.n_pairs, upto) : 0u;
+  __syncthreads();
+  for (int32_t item = (int32_t)uniform(threadIdx.x >> 6); item < n_items; item += (int32_t)(blockDim.x >> 6)) {
+    const unsigned long long open = sm.open[item];
+    const uint32_t before = (uint32_t)__builtin_amdgcn_readlane((int)(upto - n_open), item);
+    if ((open >> lane) & 1ull)
+      a.pairs[sm.first_pair + before + (uint32_t)__popcll(open & ((1ull << lane) - 1ull))] = (uint32_t)(item0 + item) << kPairNodeBits | (uint32_t)(k0 + (int32_t)lane);
   }
 }
 
-
 template <int kClassifyThreads>
-__global__ __launch_bounds__(kClassifyThreads) void classify_kernel(
-    DevTables tab, DevVocab voc, int32_t node0, int32_t n_nodes, const uint4* __restrict__ first_byte, uint32_t n_words,
-    uint32_t* __restrict__ acc_rank, uint32_t* __restrict__ unc_rank, uint32_t* __restrict__ plain_rank,
-    uint32_t* __restrict__ plain_count, OverflowLog* log, uint32_t seq, int32_t nodes_per_block, int32_t items_per_wave) {
+__global__ __launch_bounds__(kClassifyThreads) void classify_kernel(DevTables tab, DevVocab voc, ClassifyArgs a, int32_t n_items) {
   extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ uint32_t next_item;
-  if (threadIdx.x == 0) next_item = 0u;
+  __shared__ ClassifyShared sm;
+  if (threadIdx.x == 0) sm.next_item = 0u;
   stage_tables(tab, smem, kClassifyThreads);
   __syncthreads();
-  if (small_sections_staged(tab))
-    classify_body<kClassifyThreads>(LdsTabT<true>(tab, smem), voc, node0, n_nodes, first_byte, n_words, acc_rank, unc_rank,
-                                    plain_rank, plain_count, log, seq, nodes_per_block, items_per_wave, &next_item);
-  else
-    classify_body<kClassifyThreads>(LdsTab(tab, smem), voc, node0, n_nodes, first_byte, n_words, acc_rank, unc_rank,
-                                    plain_rank, plain_count, log, seq, nodes_per_block, items_per_wave, &next_item);
+  if (small_sections_staged(tab)) classify_body(LdsTabT<true>(tab, smem), sm, voc, a, n_items);
+  else classify_body(LdsTab(tab, smem), sm, voc, a, n_items);
+}
+
+// Second part: the pairs that are left, a wave for each; lane j walks token j of the item.  Neighbours in the list (the
+// nodes of one item) go to different workgroups, and with several workgroups per place on the chip (small tables) the
+// later ones even out what the first ones got: C/SQL-like grammar 1032 us with 4096 workgroups, 1150 with 2048, 1278 with
+// 1024.  Large tables are staged once per place: 365 us for the schema grammar above with 512, 400 with 1024.
+// Bound by instruction issue: a step takes some 160 instructions.
+constexpr uint32_t kWalkBlocksSmall = 4096, kWalkBlocksLarge = 512;
+template <int kClassifyThreads>
+__global__ __launch_bounds__(kClassifyThreads) void classify_walks_kernel(DevTables tab, DevVocab voc, ClassifyArgs a) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const uint32_t n_pairs = *a.n_pairs;
+  if (blockIdx.x >= n_pairs) return;
+  stage_tables(tab, smem, kClassifyThreads);
+  __syncthreads();
+  auto body = [&](const auto& T) {
+    const uint32_t lane = threadIdx.x & 63u;
+    for (uint32_t q = uniform(threadIdx.x >> 6) * gridDim.x + blockIdx.x; q < n_pairs; q += gridDim.x * (kClassifyThreads / 64)) {
+      const uint32_t pair = uniform(a.pairs[q]);
+      const uint32_t item = pair >> kPairNodeBits, k = pair & ((1u << kPairNodeBits) - 1u), node = (uint32_t)a.node0 + k;
+      const int32_t r = (int32_t)(item * 64u + lane);
+      const RankedToken t = load_ranked(voc, r);
+      int res = kReject;
+      if (t.len > 0) {
+        res = walk_token<true>(T, t.tk, t.ext, t.len, node, (const uint16_t*)nullptr, 1u, nullptr, T.follow_of(node));
+        if (res == kOverflow) { record_overflow(a.log, a.seq, k, (uint32_t)r); res = kReject; }
+      }
+      const unsigned long long acc = __ballot(res == kAccept), unc = __ballot(res == kUncertain), plain = __ballot(res == kUncertainPlain);
+      if (lane == 0u) {
+        const size_t at = (size_t)k * voc.WR + item * 2u;
+        *reinterpret_cast<uint2*>(a.acc_rank + at) = make_uint2((uint32_t)acc, (uint32_t)(acc >> 32));
+        *reinterpret_cast<uint2*>(a.unc_rank + at) = make_uint2((uint32_t)unc, (uint32_t)(unc >> 32));
+        if (a.plain_rank) *reinterpret_cast<uint2*>(a.plain_rank + at) = make_uint2((uint32_t)plain, (uint32_t)(plain >> 32));
+        if (plain) atomicAdd(&a.plain_count[node], (uint32_t)__popcll(plain));
+      }
+    }
+  };
+  if (small_sections_staged(tab)) body(LdsTabT<true>(tab, smem));
+  else body(LdsTab(tab, smem));
 }
 
 // Many nodes of a grammar have the same accepted bitset (the inside of a string is
@@ -1929,40 +1983,19 @@ void launch_first_byte(const DevTables& tab, uint4* first_byte, hipStream_t stre
                      dim3(kFirstByteThreads), 0, stream, tab, n_words, first_byte);
 }
 
-// Items of 64 tokens that a wave of the classify kernel takes on average.  Measured at 128256 tokens: the large
-// workgroups (whose LDS holds a compute unit's place until their slowest wave is done) gain from four
-// (11867-node schema grammar 1.68 -> 1.42 ms; eight: the same); the small ones from two when the grid has few
-// node groups (JSON, 19 groups: 0.18 -> 0.14 ms) and from none when it has many (C/SQL, 187 groups: 1.62 ms
-// with one, 1.66 with two, 2.0 with four).
-static int32_t classify_items_per_wave(int threads, int32_t ny) {
-  if (threads == kClassifyThreadsLarge) return 4;
-  return ny < 64 ? 2 : 1;
-}
-
-void launch_classify(const DevTables& tab, const DevVocab& voc, int32_t node0, int32_t n, const uint4* first_byte,
-                     uint32_t* acc_rank, uint32_t* unc_rank, uint32_t* plain_rank, uint32_t* plain_count, OverflowLog* log,
-                     uint32_t seq, hipStream_t stream) {
-  if (n <= 0 || voc.V <= 0) return;
-  static_assert(32 % kNodesPerBlockSmall == 0 && 32 % kNodesPerBlockMany == 0 && kNodesPerBlockLarge % 32 == 0,
-                "a block's nodes lie in whole words, or in one");
-  const uint32_t n_words = first_byte_words(tab.n_nodes);
+void launch_classify(const DevTables& tab, const DevVocab& voc, const ClassifyArgs& args, hipStream_t stream) {
+  if (args.n_nodes <= 0 || voc.V <= 0) return;
+  (void)hipMemsetAsync(args.n_pairs, 0, 4, stream);
   const DevTables st = staged_for(tab, kClassifyLdsBudget);
-  if (st.stage_bytes <= kClassifySmallStage) {
-    const int32_t per_block = n >= kManyNodes ? kNodesPerBlockMany : kNodesPerBlockSmall;
-    const int32_t ny = (n + per_block - 1) / per_block;
-    const int32_t items = classify_items_per_wave(kClassifyThreadsSmall, ny);
-    const int32_t chunk = kClassifyThreadsSmall * items;
-    hipLaunchKernelGGL(classify_kernel<kClassifyThreadsSmall>, dim3((voc.V + chunk - 1) / chunk, ny), dim3(kClassifyThreadsSmall),
-                       st.stage_bytes, stream, st, voc, node0, n, first_byte, n_words, acc_rank, unc_rank, plain_rank,
-                       plain_count, log, seq, per_block, items);
-  } else {
-    const int32_t ny = (n + kNodesPerBlockLarge - 1) / kNodesPerBlockLarge;
-    const int32_t items = classify_items_per_wave(kClassifyThreadsLarge, ny);
-    const int32_t chunk = kClassifyThreadsLarge * items;
-    hipLaunchKernelGGL(classify_kernel<kClassifyThreadsLarge>, dim3((voc.V + chunk - 1) / chunk, ny), dim3(kClassifyThreadsLarge),
-                       st.stage_bytes, stream, st, voc, node0, n, first_byte, n_words, acc_rank, unc_rank, plain_rank,
-                       plain_count, log, seq, kNodesPerBlockLarge, items);
-  }
+  const bool small = st.stage_bytes <= kClassifySmallStage;
+  const int32_t waves = (small ? kClassifyThreadsSmall : kClassifyThreadsLarge) / 64;
+  const int32_t items = std::min(waves * (small ? kItemsPerWaveSmall : kItemsPerWaveLarge), kClassifyItems);
+  const dim3 grid(((voc.V + 63) / 64 + items - 1) / items, (args.n_nodes + kClassifyNodes - 1) / kClassifyNodes);
+  const dim3 grid2(small ? kWalkBlocksSmall : kWalkBlocksLarge);
+  hipLaunchKernelGGL((small ? classify_kernel<kClassifyThreadsSmall> : classify_kernel<kClassifyThreadsLarge>), grid, dim3(waves * 64), st.stage_bytes,
+                     stream, st, voc, args, items);
+  hipLaunchKernelGGL((small ? classify_walks_kernel<kClassifyThreadsSmall> : classify_walks_kernel<kClassifyThreadsLarge>), grid2, dim3(waves * 64),
+                     st.stage_bytes, stream, st, voc, args);
 }
 
 void launch_permute(const DevVocab& voc, int32_t n, const uint32_t* a_rank, const uint32_t* b_rank, uint32_t* a_id,

@@ -253,13 +253,22 @@ constexpr size_t kStaticScratchBytes = (size_t)1 << 20;
 hipError_t static_scratch(void** out);
 
 // ---- launchers (all asynchronous on `stream`)
-// (a) classify tokens [all ranks] x nodes [node0, node0+n) into rank-space bitsets
-// plain_rank (may be null): tokens that are context-dependent by section 3.1 alone
-// but rejected by the one-byte context refinement; plain_count[node0 + k] += their number
-// first_byte: what launch_first_byte() wrote for this grammar; node0 must be a multiple of 32
-void launch_classify(const DevTables& tab, const DevVocab& voc, int32_t node0, int32_t n, const uint4* first_byte,
-                     uint32_t* acc_rank, uint32_t* unc_rank, uint32_t* plain_rank, uint32_t* plain_count,
-                     OverflowLog* log, uint32_t seq, hipStream_t stream);
+// (a) classify tokens [all ranks] x nodes [node0, node0 + n_nodes) into rank-space bitsets
+struct ClassifyArgs {
+  int32_t node0, n_nodes;
+  const uint4* first_byte;     // what launch_first_byte() wrote for this grammar
+  uint32_t n_words;            // first_byte_words() of it
+  uint32_t* acc_rank;          // [n_nodes][WR]
+  uint32_t* unc_rank;
+  uint32_t* plain_rank;        // (may be null) tokens that are context-dependent by section 3.1 alone but rejected by the
+                               // one-byte context refinement
+  uint32_t* plain_count;       // plain_count[node0 + k] += their number
+  uint32_t* pairs;             // [n_nodes * WR / 2] room for every (64 tokens, node) pair
+  uint32_t* n_pairs;           // (cleared by the launcher)
+  OverflowLog* log;
+  uint32_t seq;
+};
+void launch_classify(const DevTables& tab, const DevVocab& voc, const ClassifyArgs& args, hipStream_t stream);
 // What a token's first byte settles at every node: first_byte[c * first_byte_words(N) + w] holds, for byte c and
 // nodes 32 w .. 32 w + 31, the bitsets {walk needed, leaves the frame at once in front of a byte that may follow
 // the rule, leaves it in front of one that may not, 0}.

@@ -425,6 +425,35 @@ def test_every_top_has_its_lists(xgm, wl, text):
         assert np.array_equal(d_mask.cpu().numpy(), want)
 
 
+# The classify kernel looks at 64 tokens and 64 nodes at a time, and at what a run of at least 16 tokens with the same first
+# byte has in common (15 bytes of it at most): runs that begin and end anywhere in an item, grammars of one block of nodes
+# and of several, tokens longer than a walk takes.
+@pytest.mark.parametrize("run", [1, 15, 16, 17, 63, 64, 65, 200])
+@pytest.mark.parametrize("words, nodes", [(11, 62), (12, 65), (40, 151)])
+def test_classes_of_tokens_that_share_prefixes(xgm, wl, run, words, nodes):
+    text = 'root ::= "{" ws item (ws "," ws item)* ws "}"\nws ::= " "*\nname ::= [a-z]+ | "-" name\nitem ::= ' + " | ".join(
+        f'"{rule_word(k)}{rule_word(7 * k)}" ws ":" ws {"name" if k % 2 else "item"}' for k in range(words)) + ' | "." name'
+    toks = [bytes([c]) for c in b"{}(),.:- abz"] + [b""]
+    for p in (b" ", b"  ", b"a", b"aaa", b"  }", b"abcdefghijklmn", b"abcdefghijklmno", b"abcdefghijklmnopq", b" aaaaaa : aaaaaa", b", .", b"---"):
+        toks += [p + rule_word(k).encode() for k in range(run - 1)] + [p]
+    if run == 64:
+        toks += [b"a" * 300, b"-" * 256 + b"a", b" " * 280]  # (each decided on the host, its neighbours by their walks)
+    toks = list(dict.fromkeys(toks))
+    stop = toks.index(b"")
+    vocab = Vocab(np.frombuffer(b"".join(toks), dtype=np.uint8).copy(), np.cumsum([0] + [len(t) for t in toks]).astype(np.int64),
+                  np.array([stop], dtype=np.int32))
+    g, og = xgm.Grammar(text, "root"), oracle.Grammar(text, "root")
+    assert g.num_nodes == nodes
+    cache = xgm.Cache(g, wl.make_xgm_vocab(vocab), keep_plain=True)
+    assert (cache.host_classified > 0) == (run == 64)
+    for node in range(g.num_nodes):
+        want = og.classify(g.rule_name(g.node_rule(node)), g.node_path(node), vocab)
+        acc, unc = cache.copy_node_bits(node)
+        for got, cls in ((acc, 2), (unc, 1), (cache.copy_node_plain(node), 4)):
+            assert np.array_equal(got, oracle.pack_bitmask(want == cls)), (node, cls)
+        assert cache.num_uncertain(node) == int((want == 1).sum()) and cache.num_uncertain_plain(node) == int((want == 4).sum())
+
+
 # Few walks of a row go to waves, unless a cache of the batch (the markup grammar's) is known to walk to the limits.
 @pytest.mark.parametrize("V", [4096, 32000])
 def test_walks_by_waves_and_by_lanes(xgm, wl, V):
