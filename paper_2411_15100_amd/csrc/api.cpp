@@ -723,11 +723,14 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
     const int32_t n_seg = dv.n_seg;
     uint32_t* acc_id = arena.array<uint32_t>((size_t)N * dv.W);  // one row per node
     const bool keep_plain = (flags & XGM_CACHE_KEEP_PLAIN) != 0;
-    uint32_t* unc_id = keep_plain ? (c->d_unc_id = keep(slab_alloc<uint32_t>((size_t)N * dv.W))) : arena.array<uint32_t>((size_t)N * dv.W);
     // rank-space scratch for a batch of nodes (at most 1 GiB for both bitsets)
     const size_t row_bytes = (size_t)dv.WR * 4;
     int32_t batch = (int32_t)std::max<size_t>(32, std::min<size_t>((size_t)N, ((size_t)512 << 20) / row_bytes));
     if (g_build_batch_nodes > 0) batch = std::max(32, std::min(N, g_build_batch_nodes.load()));
+    // A grammar that fits one batch (the rule) keeps of its rank-space rows only the words that are not zero, and of the
+    // rows in id space only those that the cache keeps.
+    const bool one_batch = batch >= N, sparse = one_batch && !keep_plain;
+    uint32_t* unc_id = keep_plain ? (c->d_unc_id = keep(slab_alloc<uint32_t>((size_t)N * dv.W))) : sparse ? nullptr : arena.array<uint32_t>((size_t)N * dv.W);
     uint32_t* acc_rank = arena.array<uint32_t>((size_t)batch * dv.WR);
     uint32_t* unc_rank = arena.array<uint32_t>((size_t)batch * dv.WR);
     uint32_t* plain_rank = keep_plain ? arena.array<uint32_t>((size_t)batch * dv.WR) : nullptr;
@@ -752,8 +755,21 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
     uint32_t* d_seg_counts = arena.array<uint32_t>((size_t)N * n_seg);
     unsigned long long* d_digest = arena.array<unsigned long long>((size_t)N);
     uint32_t* d_unc_counts = arena.array<uint32_t>((size_t)N);
+    RankRows sparse_rows{acc_rank, unc_rank, nullptr, nullptr, nullptr, d_unc_counts, d_seg_counts, nullptr, nullptr};
+    uint8_t *some_acc = nullptr, *some_unc = nullptr;
+    if (sparse) {
+      sparse_rows.some_acc = some_acc = arena.array<uint8_t>((size_t)N * some_stride(dv));
+      sparse_rows.some_unc = some_unc = arena.array<uint8_t>((size_t)N * some_stride(dv));
+      sparse_rows.acc_counts = arena.array<uint32_t>((size_t)N);
+      sparse_rows.bitset_nodes = arena.array<uint32_t>((size_t)N);
+      sparse_rows.n_bitset_nodes = arena.array<uint32_t>(1);
+    }
     // rank -> id space, with the rows' statistics (accepted tokens per segment, digest, context-dependent tokens)
     auto permute = [&](int32_t node0, int32_t nb) {
+      if (sparse) {
+        launch_row_stats(dv, sparse_rows, N, acc_id, d_digest, stream);
+        return;
+      }
       launch_permute(dv, nb, acc_rank, unc_rank, acc_id + (size_t)node0 * dv.W, unc_id + (size_t)node0 * dv.W,
                      d_seg_counts + (size_t)node0 * n_seg, d_digest + node0, d_unc_counts + node0, stream);
       if (keep_plain)
@@ -787,7 +803,6 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
     // Classify, batch after batch of nodes.  A grammar that fits one batch (the rule) runs classify,
     // the rank -> id permutation and the row statistics back to back and looks at the record of walks
     // over the limits only afterwards; if there are any, the patched rows are permuted again.
-    const bool one_batch = batch >= N;
     uint4* d_first_byte = arena.array<uint4>((size_t)256 * first_byte_words(N));
     uint32_t* d_pairs = arena.array<uint32_t>((size_t)batch * (dv.WR / 2));
     uint32_t* d_n_pairs = arena.array<uint32_t>(1);
@@ -796,7 +811,7 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
       const int32_t nb = std::min(batch, N - node0);
       HIP_OK(hipEventRecord(ev0, stream));
       launch_classify(tab, dv, ClassifyArgs{node0, nb, d_first_byte, first_byte_words(N), acc_rank, unc_rank, plain_rank, d_plain_count,
-                                            d_pairs, d_n_pairs, log, seq}, stream);
+                                            some_acc, some_unc, d_pairs, d_n_pairs, log, seq}, stream);
       HIP_OK(hipEventRecord(ev1, stream));
       HIP_OK(hipGetLastError());
       if (!one_batch) {
@@ -845,7 +860,7 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
     for (int32_t n = 0; n < N; ++n) {
       uint64_t total = 0;
       for (int32_t sgm = 0; sgm < n_seg; ++sgm) total += seg_counts[(size_t)n * n_seg + sgm];
-      as_list[n] = total * 2 <= (uint64_t)dv.W;
+      as_list[n] = kept_as_list(total, dv.W);
     }
     std::vector<int32_t> rep((size_t)N);
     {
@@ -938,14 +953,16 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
     uint16_t* d_base_node = arena.array<uint16_t>((size_t)n_base);
     uint32_t* d_exits = arena.array<uint32_t>((size_t)n_base);
     {
-      std::vector<uint32_t> row_of((size_t)N);
-      for (int32_t n = 0; n < N; ++n) row_of[n] = A.node_on_top[n] ? (uint32_t)n : kNoKey;
-      uint32_t* d_row_of = arena.upload(row_of, stream);
-      uint32_t* d_cursor = arena.upload(node_off, stream);
-      // In byte-sorted order where the rank-space rows of all nodes are still there (one batch): the walks of
-      // neighbouring lanes then share prefixes, as in the classify kernel.
-      if (one_batch) launch_rows_to_lists(unc_rank, dv.WR, dv.id_of_rank, N, d_row_of, 1, d_cursor, d_base_ids, d_base_node, stream);
-      else launch_rows_to_lists(unc_id, dv.W, nullptr, N, d_row_of, 1, d_cursor, d_base_ids, d_base_node, stream);
+      if (sparse) {
+        std::vector<uint32_t> first((size_t)N);
+        for (int32_t n = 0; n < N; ++n) first[n] = A.node_on_top[n] && c->unc_count[n] ? node_off[n] : kNoKey;
+        launch_base_lists(dv, sparse_rows, N, arena.upload(first, stream), d_base_ids, d_base_node, stream);
+      } else {
+        std::vector<uint32_t> row_of((size_t)N);
+        for (int32_t n = 0; n < N; ++n) row_of[n] = A.node_on_top[n] ? (uint32_t)n : kNoKey;
+        uint32_t* d_row_of = arena.upload(row_of, stream);
+        launch_rows_to_lists(unc_id, dv.W, N, d_row_of, 1, arena.upload(node_off, stream), d_base_ids, d_base_node, stream);
+      }
     }
     uint32_t* d_counts = arena.array<uint32_t>(n_slots);
     HIP_OK(hipMemsetAsync(d_counts, 0, n_slots * 4, stream));
@@ -1079,10 +1096,12 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
       uint32_t* d_back = arena.array<uint32_t>(n_slots);
       HIP_OK(hipMemcpyAsync(d_front, d_key_off, n_slots * 4, hipMemcpyDeviceToDevice, stream));
       HIP_OK(hipMemcpyAsync(d_back, d_key_off + 1, n_slots * 4, hipMemcpyDeviceToDevice, stream));
-      std::vector<uint32_t> list_key((size_t)N);
-      for (int32_t n = 0; n < N; ++n) list_key[n] = as_list[n] ? (uint32_t)n : kNoKey;
-      uint32_t* d_list_key = arena.upload(list_key, stream);
-      launch_rows_to_lists(acc_id, dv.W, nullptr, N, d_list_key, n_seg, d_front, d_entries, nullptr, stream);
+      if (sparse) launch_level0_lists(dv, sparse_rows, N, d_key_off, d_entries, stream);
+      else {
+        std::vector<uint32_t> list_key((size_t)N);
+        for (int32_t n = 0; n < N; ++n) list_key[n] = as_list[n] ? (uint32_t)n : kNoKey;
+        launch_rows_to_lists(acc_id, dv.W, N, arena.upload(list_key, stream), n_seg, d_front, d_entries, nullptr, stream);
+      }
       args.front = d_front;
       args.back = d_back;
       args.entries = d_entries;

@@ -150,11 +150,10 @@ constexpr uint32_t kClassifySmallStage = 32 * 1024;
 // Tokens are classified in byte-sorted order, 64 of them (an item) at a time: neighbours mostly share prefixes and
 // control flow.  A workgroup of classify_kernel owns up to kClassifyItems items, which its waves draw from a counter in
 // LDS, and kClassifyNodes nodes, one for each lane.
-constexpr int kClassifyNodes = 64, kClassifyItems = 64;
-// items per wave of a workgroup, on average: with large tables four, which are staged for fewer workgroups then (11867-node
-// schema grammar, 151936 tokens: 533 us with one, 463 with two, 381 with four or five); with small ones two (C/SQL-like
-// grammar, 128256 tokens: 99 us with one, 77 with two, 68 with four; JSON 38, 40, 41)
-constexpr int kItemsPerWaveSmall = 2, kItemsPerWaveLarge = 4;
+// With large tables as many as can be, which are staged for fewer workgroups then (11867-node schema grammar, 151936 tokens,
+// with every word written: 533 us with one item per wave, 463 with two, 381 with four or five); with small ones two per
+// wave (C/SQL-like grammar, 128256 tokens: 99 us with one, 77 with two, 68 with four; JSON 38, 40, 41).
+constexpr int kClassifyNodes = 64, kClassifyItems = 64, kClassifyItemsSmall = 8;
 // A run of fewer tokens is not looked at by its prefix: an item of many runs (the tokens that begin with the rarer bytes)
 // would take a walk for each of them, one after the other.
 constexpr int kPrefixTokens = 16;
@@ -212,6 +211,7 @@ __device__ __forceinline__ RankedToken load_ranked(const DevVocab& voc, int32_t 
 struct ClassifyShared {
   uint32_t next_item, first_pair;
   unsigned long long open[kClassifyItems];  // per item: the nodes at which its tokens have to be walked
+  unsigned long long unc[kClassifyItems];   // and those of which it has context-dependent tokens, or may have
 };
 
 // Kernel (a), first part: what can be said about an item as a whole.  Lane j of a wave looks at node j.  The first byte
@@ -221,11 +221,12 @@ struct ClassifyShared {
 // grammar, and a quarter of the tokens begin with a space - the second byte decides nearly always.)  What is left is
 // listed for classify_walks_kernel: 338 K pairs of an 11867-node schema grammar and 151936 tokens, where the first byte
 // alone leaves 1.56 M of the 28 M.
-// Both kernels write whole words of the rank-space bitsets, 64 tokens of one node.  Bound by these stores, one line per
-// node: 381 us for that grammar (451 MB), and 365 us for the walks, where one kernel that walked all pairs that the first
-// byte leaves took 1663 us; JSON (128256 tokens) 41 + 36 us, before 163, where a few waves with the walks of whole
-// strings were the last to finish; 32000 tokens 20 + 30, before 65; a scripting grammar 51 + 175, before 394; the
-// C/SQL-like grammar, whose identifiers are walked to their ends at a hundred nodes, 77 + 1032, before 1283.
+// Both kernels write whole words of the rank-space bitsets, 64 tokens of one node, which are lines of their own: only those
+// that are not zero (ClassifyArgs::some_acc).  264 us for that grammar (381 with every word written, 451 MB), and 365 us
+// for the walks, where one kernel that walked all pairs that the first byte leaves took 1663 us; JSON (128256 tokens) 37 +
+// 37 us, before 163, where a few waves with the walks of whole strings were the last to finish; 32000 tokens 18 + 30, before
+// 65; a scripting grammar 54 + 175, before 394; the C/SQL-like grammar, whose identifiers are walked to their ends at a
+// hundred nodes, 70 + 1032, before 1283.
 template <class Tab>
 __device__ __forceinline__ void classify_body(const Tab& T, ClassifyShared& sm, const DevVocab& voc, const ClassifyArgs& a, int32_t n_items_max) {
   // A workgroup owns a run of up to kClassifyItems items of 64 tokens, and kClassifyNodes nodes; lane j of a wave looks at
@@ -278,16 +279,34 @@ __device__ __forceinline__ void classify_body(const Tab& T, ClassifyShared& sm, 
       }
       open |= __ballot(walk);
     }
-    if (lane == 0u) sm.open[item] = open;
+    const unsigned long long unc = __ballot(own && keep_u != 0ull) | open;
+    if (lane == 0u) { sm.open[item] = open; sm.unc[item] = unc; }
     if (own && !((open >> lane) & 1ull)) {
       const size_t at = (size_t)(k0 + (int32_t)lane) * voc.WR + (uint32_t)((item0 + item) * 2);  // an even word: 8-byte aligned
-      *reinterpret_cast<uint2*>(a.acc_rank + at) = make_uint2(0u, 0u);
-      *reinterpret_cast<uint2*>(a.unc_rank + at) = make_uint2((uint32_t)keep_u, (uint32_t)(keep_u >> 32));
+      if (!a.some_acc) *reinterpret_cast<uint2*>(a.acc_rank + at) = make_uint2(0u, 0u);
+      if (!a.some_unc || keep_u) *reinterpret_cast<uint2*>(a.unc_rank + at) = make_uint2((uint32_t)keep_u, (uint32_t)(keep_u >> 32));
       if (a.plain_rank) *reinterpret_cast<uint2*>(a.plain_rank + at) = make_uint2((uint32_t)keep_p, (uint32_t)(keep_p >> 32));
       if (keep_p) atomicAdd(&a.plain_count[own_node], (uint32_t)__popcll(keep_p));
     }
   }
   __syncthreads();
+  // which words of the nodes' rows there are
+  if (a.some_acc)
+    for (int32_t t = (int32_t)threadIdx.x; t < n_own * (n_items_max / 8); t += (int32_t)blockDim.x) {
+      const int32_t j = t / (n_items_max / 8), eight = t % (n_items_max / 8);
+      uint32_t acc = 0u, unc = 0u;
+#pragma unroll
+      for (int32_t i = 0; i < 8; ++i) {
+        const int32_t item = eight * 8 + i;
+        if (item < n_items) {
+          acc |= (uint32_t)((sm.open[item] >> j) & 1ull) << i;
+          unc |= (uint32_t)((sm.unc[item] >> j) & 1ull) << i;
+        }
+      }
+      const size_t at = (size_t)(k0 + j) * some_stride(voc) + (uint32_t)(item0 / 8 + eight);
+      a.some_acc[at] = (uint8_t)acc;
+      a.some_unc[at] = (uint8_t)unc;
+    }
   // the (item, node) pairs that are left are listed for classify_walks_kernel
   const uint32_t n_open = (int32_t)lane < n_items ? (uint32_t)__popcll(sm.open[lane]) : 0u;
   uint32_t upto = n_open;  // pairs of the items up to the lane's
@@ -369,7 +388,236 @@ __device__ __forceinline__ unsigned long long mix64(unsigned long long x) {
 }
 constexpr int kMaxSegs = 128;  // segments of the largest vocabulary (XGM_MAX_VOCAB / kSegTokens), rounded up
 
-// Rank space -> id space: bit id_of_rank[r] of the output = bit r of the input.  One workgroup per node builds
+// The words of a node's rank-space row (64 tokens each) that are there and not zero, 64 items at a time: each(first item of
+// the 64, the lane's word of them or 0).  All lanes of a wave call this together; wave `part` of `parts` takes every
+// parts-th 64 items.
+typedef unsigned long long u64;
+__device__ __forceinline__ u64 word_of_lane(u64 v, int lane) {
+  return (u64)(uint32_t)__builtin_amdgcn_readlane((int)v, lane) | (u64)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), lane) << 32;
+}
+template <class Each>
+__device__ __forceinline__ void for_each_word(const DevVocab& voc, const uint32_t* __restrict__ rows, const uint8_t* __restrict__ some,
+                                              size_t node, uint32_t part, uint32_t parts, const Each& each) {
+  const uint32_t lane = threadIdx.x & 63u, n_items = (uint32_t)voc.WR / 2u, n_blocks = (n_items + 63u) / 64u;
+  const u64* const row = reinterpret_cast<const u64*>(rows) + node * n_items;
+  const u64* const bits = reinterpret_cast<const u64*>(some + node * some_stride(voc));
+  for (uint32_t b0 = 0; b0 < n_blocks; b0 += 64u) {
+    const uint32_t b = b0 + lane;
+    u64 mine = 0ull;
+    if (b < n_blocks) {
+      mine = bits[b];
+      if (b * 64u + 64u > n_items) mine &= (1ull << (n_items - b * 64u)) - 1ull;
+    }
+    // four at a time, so that their words are fetched together
+    for (u64 left = __ballot(mine != 0ull && b % parts == part); left;) {
+      u64 word[4];
+      uint32_t first[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        word[q] = 0ull;
+        first[q] = 0u;
+        if (left) {
+          const int j = __ffsll((long long)left) - 1;
+          left &= left - 1ull;
+          first[q] = (b0 + (uint32_t)j) * 64u;
+          if ((word_of_lane(mine, j) >> lane) & 1ull) word[q] = row[first[q] + lane];
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (__ballot(word[q] != 0ull)) each(first[q], word[q]);
+    }
+  }
+}
+// The tokens of such words: each(whether the lane has one, its id, how many there are in the wave's lanes before it and in
+// all).  With few tokens per item every lane takes those of its own word, with many all lanes those of one word after the
+// other; either way several ids are fetched at once.  ORDERED: in byte-sorted order.
+template <bool ORDERED, class Each>
+__device__ __forceinline__ void for_each_token(const DevVocab& voc, uint32_t item0, u64 word, const Each& each) {
+  constexpr int kFew = 4, kAtOnce = 8;
+  const uint32_t lane = threadIdx.x & 63u;
+  const u64 below = (1ull << lane) - 1ull;
+  if (__ballot(__popcll(word) > (ORDERED ? 1 : kFew)) == 0ull) {
+    uint32_t id[kFew];
+    bool has[kFew];
+#pragma unroll
+    for (int q = 0; q < (ORDERED ? 1 : kFew); ++q) {
+      has[q] = word != 0ull;
+      id[q] = has[q] ? (uint32_t)voc.id_of_rank[(item0 + lane) * 64u + (uint32_t)__ffsll((long long)word) - 1u] : 0u;
+      word &= word - 1ull;
+    }
+#pragma unroll
+    for (int q = 0; q < (ORDERED ? 1 : kFew); ++q) {
+      const u64 all = __ballot(has[q]);
+      if (all) each(has[q], id[q], (uint32_t)__popcll(all & below), (uint32_t)__popcll(all));
+    }
+    return;
+  }
+  for (u64 left = __ballot(word != 0ull); left;) {
+    u64 x[kAtOnce];
+    uint32_t id[kAtOnce];
+#pragma unroll
+    for (int q = 0; q < kAtOnce; ++q) {
+      x[q] = 0ull;
+      id[q] = 0u;
+      if (left) {
+        const int j = __ffsll((long long)left) - 1;
+        left &= left - 1ull;
+        x[q] = word_of_lane(word, j);
+        id[q] = (uint32_t)voc.id_of_rank[min((int32_t)((item0 + (uint32_t)j) * 64u + lane), voc.V - 1)];
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < kAtOnce; ++q)
+      if (x[q]) each((bool)((x[q] >> lane) & 1ull), id[q], (uint32_t)__popcll(x[q] & below), (uint32_t)__popcll(x[q]));
+  }
+}
+__device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
+#pragma unroll
+  for (uint32_t d = 1; d < 64u; d <<= 1) v += __shfl_xor(v, d, 64);
+  return v;
+}
+
+// The statistics of every node's rows, a workgroup per node: how many tokens it accepts and, if it lists them (a node with
+// few of them has no bitset row), how many in each segment; how many are context-dependent.  Nodes with a bitset row are
+// collected for bitset_rows_kernel.  Together 62 us for the 11867-node schema grammar and 151936 tokens, where a kernel that
+// went through whole rows took 496 (902 MB); 33 for JSON and 128256 tokens, before 53.  (512 threads: 57 us for this kernel
+// instead of 30, there are too many nodes that have hardly anything.)
+constexpr int kNodeThreads = 256;
+__global__ __launch_bounds__(kNodeThreads) void row_stats_kernel(DevVocab voc, RankRows a) {
+  __shared__ uint32_t seg[kMaxSegs];
+  __shared__ uint32_t sums[2];
+  const uint32_t wave = uniform(threadIdx.x >> 6), lane = threadIdx.x & 63u;
+  const size_t node = blockIdx.x;
+  if (threadIdx.x < kMaxSegs) seg[threadIdx.x] = 0u;
+  if (threadIdx.x < 2u) sums[threadIdx.x] = 0u;
+  __syncthreads();
+  uint32_t acc = 0u, unc = 0u;
+  for_each_word(voc, a.acc_rank, a.some_acc, node, wave, kNodeThreads / 64, [&](uint32_t, u64 x) { acc += (uint32_t)__popcll(x); });
+  for_each_word(voc, a.unc_rank, a.some_unc, node, wave, kNodeThreads / 64, [&](uint32_t, u64 x) { unc += (uint32_t)__popcll(x); });
+  acc = wave_sum(acc);
+  unc = wave_sum(unc);
+  if (lane == 0u && acc) atomicAdd(&sums[0], acc);
+  if (lane == 0u && unc) atomicAdd(&sums[1], unc);
+  __syncthreads();
+  const uint32_t total = sums[0];
+  if (threadIdx.x == 0u) {
+    a.acc_counts[node] = total;
+    a.unc_counts[node] = sums[1];
+    if (!kept_as_list(total, voc.W)) a.bitset_nodes[atomicAdd(a.n_bitset_nodes, 1u)] = (uint32_t)node;
+  }
+  if (!kept_as_list(total, voc.W)) return;
+  if (acc)
+    for_each_word(voc, a.acc_rank, a.some_acc, node, wave, kNodeThreads / 64, [&](uint32_t item0, u64 x) {
+      for_each_token<false>(voc, item0, x, [&](bool has, uint32_t id, uint32_t, uint32_t) { if (has) atomicAdd(&seg[id / (uint32_t)kSegTokens], 1u); });
+    });
+  __syncthreads();
+  if ((int32_t)threadIdx.x < voc.n_seg) a.seg_counts[node * voc.n_seg + threadIdx.x] = seg[threadIdx.x];
+}
+
+// The accepted rows of the nodes that keep a bitset, in id space (bit id_of_rank[r] of the output = bit r of the row), and
+// their statistics.  A workgroup builds a row in LDS, of the rarer kind of bit: a row with few set bits starts as zeros
+// and gets its set bits, one with many as ones and gets its zeros.
+constexpr int kBitsetThreads = 512;
+__global__ __launch_bounds__(kBitsetThreads) void bitset_rows_kernel(DevVocab voc, RankRows a, uint32_t* __restrict__ acc_id,
+                                                                  unsigned long long* __restrict__ digest) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  uint32_t* row = reinterpret_cast<uint32_t*>(smem);  // [W]
+  __shared__ unsigned long long part[kBitsetThreads / 64];
+  __shared__ uint32_t seg[kMaxSegs];
+  const uint32_t n = *a.n_bitset_nodes, n_items = (uint32_t)voc.WR / 2u;
+  const uint32_t tail = (voc.V & 31) ? ((1u << (voc.V & 31)) - 1u) : 0xFFFFFFFFu;  // valid bits of the last word
+  for (uint32_t k = blockIdx.x; k < n; k += gridDim.x) {
+    const size_t node = a.bitset_nodes[k];
+    const bool full = a.acc_counts[node] * 2u > (uint32_t)voc.V;
+    __syncthreads();
+    if (threadIdx.x < kMaxSegs) seg[threadIdx.x] = 0u;
+    for (int32_t w = threadIdx.x; w < voc.W; w += kBitsetThreads) row[w] = !full ? 0u : w == voc.W - 1 ? tail : 0xFFFFFFFFu;
+    __syncthreads();
+    for (uint32_t item0 = uniform(threadIdx.x >> 6) * 64u; item0 < n_items; item0 += kBitsetThreads) {
+      const uint32_t item = item0 + (threadIdx.x & 63u);
+      u64 x = 0ull;
+      if (item < n_items) {
+        if ((a.some_acc[node * some_stride(voc) + item / 8u] >> (item & 7u)) & 1u) x = reinterpret_cast<const u64*>(a.acc_rank)[node * n_items + item];
+        if (full) {
+          x = ~x;
+          const int32_t left = voc.V - (int32_t)item * 64;  // ranks from V on do not exist
+          if (left < 64) x &= (1ull << left) - 1ull;
+        }
+      }
+      for_each_token<false>(voc, item0, x, [&](bool has, uint32_t id, uint32_t, uint32_t) {
+        if (!has) return;
+        if (full) atomicAnd(&row[id >> 5], ~(1u << (id & 31)));
+        else atomicOr(&row[id >> 5], 1u << (id & 31));
+      });
+    }
+    __syncthreads();
+    unsigned long long h = 0ull;
+    for (int32_t w = threadIdx.x; w < voc.W; w += kBitsetThreads) {
+      const uint32_t x = row[w];
+      acc_id[node * voc.W + w] = x;
+      if (x) atomicAdd(&seg[w / kSegWords], (uint32_t)__popc(x));
+      h += mix64(((unsigned long long)(uint32_t)w << 32 | x) + 0x9E3779B97F4A7C15ull);
+    }
+#pragma unroll
+    for (uint32_t d = 32; d > 0; d >>= 1) h += __shfl_down(h, d, 64);
+    if ((threadIdx.x & 63u) == 0) part[threadIdx.x >> 6] = h;
+    __syncthreads();
+    if ((int32_t)threadIdx.x < voc.n_seg) a.seg_counts[node * voc.n_seg + threadIdx.x] = seg[threadIdx.x];
+    if (threadIdx.x == 0) {
+      unsigned long long t = 0ull;
+      for (int q = 0; q < kBitsetThreads / 64; ++q) t += part[q];
+      digest[node] = t;
+    }
+  }
+}
+
+// The context-dependent tokens of the nodes with a place in the base lists (first[n] != kNoKey), a workgroup per node; those
+// of 4096 neighbours in byte-sorted order stay in that order (the walks of neighbouring lanes then share prefixes, as in
+// the classify kernels).  Most nodes have none; a workgroup is large for the few with thousands, which the launch waits for:
+// 37 us for the 11867-node schema grammar (151936 tokens), 23 for JSON and 33 for the C/SQL-like grammar (128256), with 256
+// threads 61, 43 and 90; lists of whole rows took 68, 18 and 50.
+constexpr int kBaseListThreads = 1024;
+__global__ __launch_bounds__(kBaseListThreads) void base_lists_kernel(DevVocab voc, RankRows a, const uint32_t* __restrict__ first,
+                                                                  uint32_t* __restrict__ ids, uint16_t* __restrict__ nodes) {
+  __shared__ uint32_t next;
+  const size_t node = blockIdx.x;
+  const uint32_t lane = threadIdx.x & 63u, begin = first[node];
+  if (begin == kNoKey) return;
+  if (threadIdx.x == 0u) next = begin;
+  __syncthreads();
+  for_each_word(voc, a.unc_rank, a.some_unc, node, uniform(threadIdx.x >> 6), kBaseListThreads / 64, [&](uint32_t item0, u64 x) {
+    uint32_t at = 0u;
+    const uint32_t total = wave_sum((uint32_t)__popcll(x));
+    if (lane == 0u) at = atomicAdd(&next, total);
+    at = uniform(at);
+    for_each_token<true>(voc, item0, x, [&](bool has, uint32_t id, uint32_t before, uint32_t n) {
+      if (has) {
+        ids[at + before] = id;
+        nodes[at + before] = (uint16_t)node;
+      }
+      at += n;
+    });
+  });
+}
+// The level-0 lists: the accepted tokens of the nodes that list them, by segment.  A workgroup per node.
+__global__ __launch_bounds__(kNodeThreads) void level0_lists_kernel(DevVocab voc, RankRows a, const uint32_t* __restrict__ key_off,
+                                                                    uint32_t* __restrict__ entries) {
+  __shared__ uint32_t next[kMaxSegs];
+  const size_t node = blockIdx.x;
+  const uint32_t acc = a.acc_counts[node];
+  if (acc == 0u || !kept_as_list(acc, voc.W)) return;
+  if ((int32_t)threadIdx.x < voc.n_seg) next[threadIdx.x] = key_off[node * voc.n_seg + threadIdx.x];
+  __syncthreads();
+  for_each_word(voc, a.acc_rank, a.some_acc, node, uniform(threadIdx.x >> 6), kNodeThreads / 64, [&](uint32_t item0, u64 x) {
+    for_each_token<false>(voc, item0, x, [&](bool has, uint32_t id, uint32_t, uint32_t) {
+      if (has) entries[atomicAdd(&next[id / (uint32_t)kSegTokens], 1u)] = id;
+    });
+  });
+}
+
+// The same from whole rows, for builds that keep what the sparse ones do without (batches of nodes; the context-dependent
+// bitsets): bit id_of_rank[r] of the output = bit r of the input.  One workgroup per node builds
 // the node's two id-space rows in LDS.  Rows are nearly empty (most nodes reject nearly every token) or nearly
 // full (the inside of a string), so only the rarer kind of bit is moved: a row with few set bits starts as zeros
 // and gets its set bits, one with many starts as ones and gets its zeros.  With the rows still in LDS the
@@ -450,11 +698,9 @@ __global__ __launch_bounds__(kRowThreads) void permute_kernel(DevVocab voc, cons
 }
 
 // Bitset rows (row_words words each) -> lists through cursors.  One workgroup per (segment, row); a thread
-// takes four words; a wave reserves room for all its tokens with one atomic.  What is listed for bit v is
-// map[v] if a map is given (rank-space rows: the token ids, in byte-sorted order within a segment), else v.
+// takes four words; a wave reserves room for all its tokens with one atomic.
 constexpr int kListThreads = kSegWords / 4;
 __global__ __launch_bounds__(kListThreads) void rows_to_lists_kernel(const uint32_t* __restrict__ rows, int32_t row_words,
-                                                                     const int32_t* __restrict__ map,
                                                                      const uint32_t* __restrict__ cursor_of, int32_t per_row,
                                                                      uint32_t* __restrict__ cursor, uint32_t* __restrict__ out,
                                                                      uint16_t* __restrict__ out_row, int32_t row0) {
@@ -491,8 +737,7 @@ __global__ __launch_bounds__(kListThreads) void rows_to_lists_kernel(const uint3
       const uint32_t b = __ffs(x) - 1;
       x &= x - 1;
       if (out_row) out_row[pos] = (uint16_t)(row0 + (int32_t)r);
-      const uint32_t v = (uint32_t)(w0 + k) * 32u + b;
-      out[pos++] = map ? (uint32_t)map[v] : v;
+      out[pos++] = (uint32_t)(w0 + k) * 32u + b;
     }
   }
 }
@@ -828,6 +1073,10 @@ __global__ __launch_bounds__(kRowThreads) void rows_equal_kernel(const uint32_t*
                                                                  const int32_t* __restrict__ rep,
                                                                  uint32_t* __restrict__ equal) {
   __shared__ uint32_t differs;
+  if (rep[blockIdx.x] == (int32_t)blockIdx.x) {  // (most nodes are their own)
+    if (threadIdx.x == 0) equal[blockIdx.x] = 1u;
+    return;
+  }
   if (threadIdx.x == 0) differs = 0u;
   __syncthreads();
   const uint32_t* a = rows + (size_t)blockIdx.x * W;
@@ -1989,7 +2238,8 @@ void launch_classify(const DevTables& tab, const DevVocab& voc, const ClassifyAr
   const DevTables st = staged_for(tab, kClassifyLdsBudget);
   const bool small = st.stage_bytes <= kClassifySmallStage;
   const int32_t waves = (small ? kClassifyThreadsSmall : kClassifyThreadsLarge) / 64;
-  const int32_t items = std::min(waves * (small ? kItemsPerWaveSmall : kItemsPerWaveLarge), kClassifyItems);
+  const int32_t items = small ? kClassifyItemsSmall : kClassifyItems;
+  static_assert(kClassifyItems % 8 == 0 && kClassifyItemsSmall % 8 == 0, "whole bytes of ClassifyArgs::some_acc");
   const dim3 grid(((voc.V + 63) / 64 + items - 1) / items, (args.n_nodes + kClassifyNodes - 1) / kClassifyNodes);
   const dim3 grid2(small ? kWalkBlocksSmall : kWalkBlocksLarge);
   hipLaunchKernelGGL((small ? classify_kernel<kClassifyThreadsSmall> : classify_kernel<kClassifyThreadsLarge>), grid, dim3(waves * 64), st.stage_bytes,
@@ -2005,6 +2255,19 @@ void launch_permute(const DevVocab& voc, int32_t n, const uint32_t* a_rank, cons
                      seg_counts, digest, b_counts);
 }
 
+void launch_row_stats(const DevVocab& voc, const RankRows& rows, int32_t n, uint32_t* acc_id, unsigned long long* digest, hipStream_t stream) {
+  if (n <= 0) return;
+  (void)hipMemsetAsync(rows.n_bitset_nodes, 0, 4, stream);
+  hipLaunchKernelGGL(row_stats_kernel, dim3(n), dim3(kNodeThreads), 0, stream, voc, rows);
+  hipLaunchKernelGGL(bitset_rows_kernel, dim3(std::min(n, 1024)), dim3(kBitsetThreads), (size_t)voc.W * 4, stream, voc, rows, acc_id, digest);
+}
+void launch_base_lists(const DevVocab& voc, const RankRows& rows, int32_t n, const uint32_t* first, uint32_t* ids, uint16_t* nodes, hipStream_t stream) {
+  if (n > 0) hipLaunchKernelGGL(base_lists_kernel, dim3(n), dim3(kBaseListThreads), 0, stream, voc, rows, first, ids, nodes);
+}
+void launch_level0_lists(const DevVocab& voc, const RankRows& rows, int32_t n, const uint32_t* key_off, uint32_t* entries, hipStream_t stream) {
+  if (n > 0) hipLaunchKernelGGL(level0_lists_kernel, dim3(n), dim3(kNodeThreads), 0, stream, voc, rows, key_off, entries);
+}
+
 void launch_rows_equal(const uint32_t* rows, int32_t n, int32_t W, const int32_t* rep, uint32_t* equal, hipStream_t stream) {
   if (n > 0) hipLaunchKernelGGL(rows_equal_kernel, dim3(n), dim3(kRowThreads), 0, stream, rows, W, rep, equal);
 }
@@ -2013,13 +2276,13 @@ void launch_gather_rows(const uint32_t* rows, int32_t W, const int32_t* unique, 
   if (n_unique > 0) hipLaunchKernelGGL(gather_rows_kernel, dim3(n_unique), dim3(kRowThreads), 0, stream, rows, W, unique, out);
 }
 
-void launch_rows_to_lists(const uint32_t* rows, int32_t row_words, const int32_t* map, int32_t n, const uint32_t* cursor_of,
+void launch_rows_to_lists(const uint32_t* rows, int32_t row_words, int32_t n, const uint32_t* cursor_of,
                           int32_t per_row, uint32_t* cursor, uint32_t* out, uint16_t* out_row, hipStream_t stream) {
   const int32_t n_seg = (row_words + kSegWords - 1) / kSegWords;
   for (int32_t r0 = 0; r0 < n; r0 += 32768) {  // grid.y limit
     const int32_t nb = std::min(32768, n - r0);
     hipLaunchKernelGGL(rows_to_lists_kernel, dim3(n_seg, nb), dim3(kListThreads), 0, stream, rows + (size_t)r0 * row_words,
-                       row_words, map, cursor_of + r0, per_row, cursor, out, out_row, r0);
+                       row_words, cursor_of + r0, per_row, cursor, out, out_row, r0);
   }
 }
 

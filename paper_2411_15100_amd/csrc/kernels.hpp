@@ -263,6 +263,11 @@ struct ClassifyArgs {
   uint32_t* plain_rank;        // (may be null) tokens that are context-dependent by section 3.1 alone but rejected by the
                                // one-byte context refinement
   uint32_t* plain_count;       // plain_count[node0 + k] += their number
+  // Which words of acc_rank and unc_rank there are (null: all of them): bit i % 8 of byte node * some_stride() + i / 8 says it
+  // of word pair i, tokens 64 i .. 64 i + 63.  Nearly all pairs of a schema grammar are zero: they are not written, and
+  // nothing has to read them.
+  uint8_t* some_acc;
+  uint8_t* some_unc;
   uint32_t* pairs;             // [n_nodes * WR / 2] room for every (64 tokens, node) pair
   uint32_t* n_pairs;           // (cleared by the launcher)
   OverflowLog* log;
@@ -274,9 +279,39 @@ void launch_classify(const DevTables& tab, const DevVocab& voc, const ClassifyAr
 // the rule, leaves it in front of one that may not, 0}.
 inline uint32_t first_byte_words(int32_t n_nodes) { return (uint32_t)((n_nodes + 31) / 32); }
 void launch_first_byte(const DevTables& tab, uint4* first_byte, hipStream_t stream);
+// bytes per node of ClassifyArgs::some_acc
+#if defined(__HIPCC__) || defined(__HIP__)
+__host__ __device__
+#endif
+inline uint32_t some_stride(const DevVocab& voc) { return ((uint32_t)voc.WR / 2u + 63u) / 64u * 8u; }
+// does a node with so many accepted tokens list them (W: words of a bitset row)?
+#if defined(__HIPCC__) || defined(__HIP__)
+__host__ __device__
+#endif
+inline bool kept_as_list(uint64_t accepted, int32_t W) { return accepted * 2u <= (uint64_t)W; }
+// Rows of which only some words are there, and what launch_row_stats() finds out about them: the number of accepted and of
+// context-dependent tokens per node, the accepted ones per segment, and the nodes that keep a bitset row.  Those rows
+// it also writes in id space (acc_id[node * W ..]), with a 64-bit digest (equal rows have equal digests; it only
+// proposes which rows might be equal).
+struct RankRows {
+  const uint32_t* acc_rank;
+  const uint32_t* unc_rank;
+  const uint8_t* some_acc;
+  const uint8_t* some_unc;
+  uint32_t* acc_counts;      // [n]
+  uint32_t* unc_counts;      // [n]
+  uint32_t* seg_counts;      // [n][n_seg]
+  uint32_t* bitset_nodes;    // [n]
+  uint32_t* n_bitset_nodes;
+};
+void launch_row_stats(const DevVocab& voc, const RankRows& rows, int32_t n, uint32_t* acc_id, unsigned long long* digest, hipStream_t stream);
+// the context-dependent tokens of every node with first[node] != kNoKey, from there on: ids, and the node beside each
+void launch_base_lists(const DevVocab& voc, const RankRows& rows, int32_t n, const uint32_t* first, uint32_t* ids, uint16_t* nodes, hipStream_t stream);
+// the entries of the level-0 keys (see DevCache)
+void launch_level0_lists(const DevVocab& voc, const RankRows& rows, int32_t n, const uint32_t* key_off, uint32_t* entries, hipStream_t stream);
 // Rank space -> id space for n node rows (two bitsets per node), and - unless the pointers are null - per node the
-// set bits of the first row per segment (seg_counts[n][n_seg]), a 64-bit digest of the first row (equal rows have
-// equal digests; it only proposes which rows might be equal) and the set bits of the second row (b_counts[n]).
+// set bits of the first row per segment (seg_counts[n][n_seg]), a digest of the first row and the set bits of the
+// second row (b_counts[n]).
 void launch_permute(const DevVocab& voc, int32_t n, const uint32_t* a_rank, const uint32_t* b_rank, uint32_t* a_id,
                     uint32_t* b_id, uint32_t* seg_counts, unsigned long long* digest, uint32_t* b_counts, hipStream_t stream);
 // whether row k equals row rep[k], word for word (k = 0 .. n-1); rows[unique[u]] -> out[u]
@@ -284,12 +319,10 @@ void launch_rows_equal(const uint32_t* rows, int32_t n, int32_t W, const int32_t
 void launch_gather_rows(const uint32_t* rows, int32_t W, const int32_t* unique, int32_t n_unique, uint32_t* out,
                         hipStream_t stream);
 // The set bits of n bitset rows of row_words words as lists, appended through cursors: bit v of row r, in
-// segment s = v / kSegTokens, goes to out[cursor[cursor_of[r] * per_row + (per_row > 1 ? s : 0)]++] as
-// map[v] (map not null: rank-space rows with map = id_of_rank list token ids, neighbours in the list being
-// neighbours in byte-sorted order) or as v; rows with cursor_of[r] == kNoKey are skipped.  per_row = the
-// segments of a row: one list per (row, segment); 1: one per row.  out_row (may be null) receives the row
-// number beside every entry.
-void launch_rows_to_lists(const uint32_t* rows, int32_t row_words, const int32_t* map, int32_t n, const uint32_t* cursor_of,
+// segment s = v / kSegTokens, goes to out[cursor[cursor_of[r] * per_row + (per_row > 1 ? s : 0)]++]; rows with
+// cursor_of[r] == kNoKey are skipped.  per_row = the segments of a row: one list per (row, segment); 1: one per
+// row.  out_row (may be null) receives the row number beside every entry.
+void launch_rows_to_lists(const uint32_t* rows, int32_t row_words, int32_t n, const uint32_t* cursor_of,
                           int32_t per_row, uint32_t* cursor, uint32_t* out, uint16_t* out_row, hipStream_t stream);
 // The level-1 and level-2 lists of a cache (see DevCache) from the base lists: the context-dependent
 // (node, token) pairs, base_node[e] / base_ids[e] for e < total, the pairs of one node side by side.

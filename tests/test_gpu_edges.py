@@ -454,6 +454,46 @@ def test_classes_of_tokens_that_share_prefixes(xgm, wl, run, words, nodes):
         assert cache.num_uncertain(node) == int((want == 1).sum()) and cache.num_uncertain_plain(node) == int((want == 4).sum())
 
 
+# A build keeps only the words of its rank-space rows that are not zero, unless it keeps the context-dependent bitsets too or
+# goes through the nodes in batches: the same caches from all three, and the same masks; vocabularies that end anywhere in an
+# item of 64 tokens, in 64 items and in 64 times 64 of them.
+@pytest.mark.parametrize("V", [37, 64, 65, 511, 4095, 4097, 8193, 262145])
+@pytest.mark.parametrize("family", ["json", "words"])
+def test_builds_of_all_kinds_give_the_same_cache(xgm, wl, family, V):
+    text = si.JSON_GRAMMAR if family == "json" else 'root ::= ([a-z] [a-z]* | [0-9]+ | " ")* "." | "(" root ")" tail\ntail ::= ("," root)*'
+    chars = bytes(range(33, 127)) if V > 50000 else b'{}[]:,"0123456789.E+- ()abcdefgxyz\\'
+    toks = [bytes(t) for n in (1, 2, 3) for t in itertools.islice(itertools.product(chars, repeat=n), V)]
+    toks = (toks[:V - 1] if V < 50000 else toks[:V - 1] + [b"%d" % k for k in range(10 ** 6, 10 ** 6 + max(0, V - 1 - len(toks)))]) + [b""]
+    vocab = Vocab(np.frombuffer(b"".join(toks), dtype=np.uint8).copy(), np.cumsum([0] + [len(t) for t in toks]).astype(np.int64),
+                  np.array([len(toks) - 1], dtype=np.int32))
+    assert vocab.size == V and len(set(toks)) == V
+    g, xv = xgm.Grammar(text, "root"), wl.make_xgm_vocab(vocab)
+    caches = [xgm.Cache(g, xv), xgm.Cache(g, xv, keep_plain=True)]
+    xgm.debug_set_build_batch_nodes(32)
+    try:
+        caches.append(xgm.Cache(g, xv))
+    finally:
+        xgm.debug_set_build_batch_nodes(0)
+    for node in range(g.num_nodes):
+        acc, _ = caches[0].copy_node_bits(node, with_uncertain=False)
+        for c in caches[1:]:
+            assert np.array_equal(c.copy_node_bits(node, with_uncertain=False)[0], acc)
+            assert c.num_uncertain(node) == caches[0].num_uncertain(node)
+            assert c.num_uncertain_plain(node) == caches[0].num_uncertain_plain(node)
+    assert caches[0].stats == caches[1].stats == caches[2].stats
+    masks = []
+    for c in caches:
+        ms = []
+        for start in ([b"", b"[", b'{"a', b'{"a":[1', b"[[[-2.", b'["b",'] if family == "json" else [b"", b"a", b"(12", b"((b ", b"(c.)", b"(c.),d"]):
+            ms.append(xgm.Matcher(cache=c))
+            if start:
+                ms[-1].accept_bytes(start)
+        d_mask = torch.full((len(ms), xgm.bitmask_words(V)), -1, dtype=torch.int32, device="cuda")
+        xgm.fill_next_token_bitmask(ms, d_mask.data_ptr(), _stream())
+        masks.append(d_mask.cpu().numpy())
+    assert np.array_equal(masks[0], masks[1]) and np.array_equal(masks[0], masks[2])
+
+
 # Few walks of a row go to waves, unless a cache of the batch (the markup grammar's) is known to walk to the limits.
 @pytest.mark.parametrize("V", [4096, 32000])
 def test_walks_by_waves_and_by_lanes(xgm, wl, V):
