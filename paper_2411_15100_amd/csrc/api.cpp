@@ -110,7 +110,8 @@ T* slab_upload(const std::vector<T>& v) {
 
 // Temporary device memory of the cache builds: one block that is reused by every build and grows to what
 // the largest build so far needed (allocating and freeing two dozen arrays per build costs more than the
-// kernels of a small grammar take).  Builds are serialised by `mu`.
+// kernels of a small grammar take).  Builds are serialised by `mu`.  The same for the pinned host memory that their
+// copies go through, of which at most kPinned bytes are kept.
 class TempArena {
  public:
   std::mutex mu;
@@ -131,6 +132,9 @@ class TempArena {
   void reset() {
     for (void* p : extra_) (void)hipFree(p);
     extra_.clear();
+    for (void* p : pinned_extra_) (void)hipHostFree(p);
+    pinned_extra_.clear();
+    pinned_used_ = 0;
     host_keep_.clear();
     if (wanted_ > cap_) {
       if (base_) (void)hipFree(base_);
@@ -144,6 +148,20 @@ class TempArena {
   }
   template <class T>
   T* array(size_t n) { return static_cast<T*>(alloc(std::max<size_t>(n, 1) * sizeof(T))); }
+  // pinned host memory, until reset()
+  char* pinned(size_t bytes) {
+    bytes = std::max<size_t>((bytes + 255) & ~(size_t)255, 256);
+    if (!pinned_ && bytes <= kPinned) hip_check(hipHostMalloc(&pinned_, kPinned), "hipHostMalloc");
+    if (pinned_ && pinned_used_ + bytes <= kPinned) {
+      char* p = (char*)pinned_ + pinned_used_;
+      pinned_used_ += bytes;
+      return p;
+    }
+    void* p = nullptr;
+    hip_check(hipHostMalloc(&p, bytes), "hipHostMalloc");
+    pinned_extra_.push_back(p);
+    return (char*)p;
+  }
   // (the host bytes are kept until reset(), so that the copy may run whenever the stream gets to it)
   template <class T>
   T* upload(const std::vector<T>& v, hipStream_t stream) {
@@ -159,12 +177,42 @@ class TempArena {
   char* base_ = nullptr;
   size_t cap_ = 0, used_ = 0, wanted_ = 0;
   std::vector<void*> extra_;
+  static constexpr size_t kPinned = (size_t)8 << 20;
+  void* pinned_ = nullptr;
+  size_t pinned_used_ = 0;
+  std::vector<void*> pinned_extra_;
   std::deque<std::vector<char>> host_keep_;
 };
 TempArena& temp_arena() {
   static TempArena a;
   return a;
 }
+
+// Host arrays that go to the device in one copy, through pinned memory (an array copied by itself from pageable memory
+// keeps the host for 12 us, however small it is, and a build has some twenty of them).  They are read by send().
+class Parts {
+ public:
+  size_t add(const void* src, size_t bytes, size_t align = 256) {
+    bytes_ = (bytes_ + align - 1) / align * align;
+    parts_.push_back({src, bytes, bytes_});
+    bytes_ += bytes;
+    return parts_.back().at;
+  }
+  template <class T>
+  size_t add(const std::vector<T>& v) { return add(v.data(), v.size() * sizeof(T)); }
+  size_t bytes() const { return bytes_; }
+  void send(void* dst, TempArena& arena, hipStream_t stream) const {
+    char* const h = arena.pinned(bytes_);
+    for (const Part& p : parts_)
+      if (p.bytes) std::memcpy(h + p.at, p.src, p.bytes);
+    if (bytes_) hip_check(hipMemcpyAsync(dst, h, bytes_, hipMemcpyHostToDevice, stream), "hipMemcpyAsync");
+  }
+
+ private:
+  struct Part { const void* src; size_t bytes, at; };
+  std::vector<Part> parts_;
+  size_t bytes_ = 0;
+};
 
 void require_device() {
   static std::atomic<bool> found{false};  // (asked once: the per-step calls come through here too)
@@ -205,7 +253,6 @@ struct xgm_cache {
   std::vector<void*> dev_ptrs;
   // host copies of what packing a stack header needs (see DevCache)
   std::vector<uint16_t> acc_row_host;  // [n_nodes]
-  std::vector<uint32_t> key_off_host;  // [n_keys * n_seg + 1]
   std::vector<uint32_t> k_base_host[kCtxLevels];  // [n_nodes] (kNoKey for a node without context-dependent tokens), [n_k[0]], ...
   int levels = 0;                      // levels of per-context lists kept (<= kCtxLevels)
   std::vector<uint32_t> unc_count;     // [n_nodes] context-dependent tokens
@@ -690,24 +737,17 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
     DevTables tab{};
     size_t image_bytes = 0;
     {
-      std::vector<unsigned char> img;
-      auto put = [&](const void* src, size_t bytes, size_t align) {
-        img.resize((img.size() + align - 1) / align * align, 0);
-        const size_t at = img.size();
-        img.insert(img.end(), (const unsigned char*)src, (const unsigned char*)src + bytes);
-        return (uint32_t)at;
-      };
+      Parts img;
       if (A.cls.size() != 256 || A.follow.size() != A.rule_names.size())
         throw Failure(XGM_ERR_INTERNAL, "cache_build: inconsistent automaton tables");
-      put(A.cls.data(), 256, 4);
-      tab.off_shapes = put(A.shapes.data(), A.shapes.size(), 4);
-      tab.off_targets = put(A.targets.data(), A.targets.size() * 2, 4);
-      tab.off_follow = put(A.follow.data(), A.follow.size() * sizeof(ByteSet), 4);
-      tab.off_alts = put(A.alts.data(), A.alts.size() * 4, 4);
-      tab.off_hdr = put(A.hdr.data(), (size_t)N * sizeof(uint2), 16);
-      tab.off_first = put(A.node_first.data(), (size_t)N * sizeof(ByteSet), 16);
-      img.resize((img.size() + 15) / 16 * 16, 0);
-      image_bytes = img.size();
+      img.add(A.cls.data(), 256, 4);
+      tab.off_shapes = (uint32_t)img.add(A.shapes.data(), A.shapes.size(), 4);
+      tab.off_targets = (uint32_t)img.add(A.targets.data(), A.targets.size() * 2, 4);
+      tab.off_follow = (uint32_t)img.add(A.follow.data(), A.follow.size() * sizeof(ByteSet), 4);
+      tab.off_alts = (uint32_t)img.add(A.alts.data(), A.alts.size() * 4, 4);
+      tab.off_hdr = (uint32_t)img.add(A.hdr.data(), (size_t)N * sizeof(uint2), 16);
+      tab.off_first = (uint32_t)img.add(A.node_first.data(), (size_t)N * sizeof(ByteSet), 16);
+      image_bytes = (img.bytes() + 15) / 16 * 16;
       // (behind the image: the description of the tables as the fill kernel stages them)
       unsigned char* d_img = keep(slab_alloc<unsigned char>(image_bytes + sizeof(DevTables)));
       tab.image = reinterpret_cast<const uint4*>(d_img);
@@ -715,9 +755,9 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
       tab.n_cls = A.n_cls;
       tab.n_nodes = N;
       c->host.tab = staged_for(tab, kFillLdsBudget);
-      put(&c->host.tab, sizeof(DevTables), 16);
+      img.add(&c->host.tab, sizeof(DevTables), 16);
       c->host.dev_tab = reinterpret_cast<const DevTables*>(d_img + image_bytes);
-      HIP_OK(hipMemcpy(d_img, img.data(), img.size(), hipMemcpyHostToDevice));
+      img.send(d_img, arena, stream);
     }
 
     const int32_t n_seg = dv.n_seg;
@@ -735,12 +775,21 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
     uint32_t* unc_rank = arena.array<uint32_t>((size_t)batch * dv.WR);
     uint32_t* plain_rank = keep_plain ? arena.array<uint32_t>((size_t)batch * dv.WR) : nullptr;
     if (keep_plain) c->d_plain_id = keep(slab_alloc<uint32_t>((size_t)N * dv.W));
-    uint32_t* d_plain_count = arena.array<uint32_t>((size_t)N);
-    HIP_OK(hipMemsetAsync(d_plain_count, 0, (size_t)N * 4, stream));
-    // walks over the on-chip limits are recorded in a log of this build's own (the one that the fills from
-    // host-side states share is made here too, so that no fill has to allocate it)
-    OverflowLog* log = arena.array<OverflowLog>(1);
-    HIP_OK(hipMemsetAsync(log, 0, 8, stream));
+    // What the first kernels find out about the nodes, side by side, so that one copy brings it to the host: the digests of
+    // the accepted rows, accepted and context-dependent tokens, those that only section 3.1 calls context-dependent; then
+    // counters, and the log of the walks over the on-chip limits (the one that the fills from host-side states share is
+    // made here too, so that no fill has to allocate it).  What is counted up begins at zero.
+    const size_t plain_at = (size_t)N * 16, log_at = ((size_t)N * 20 + 8 + 15) / 16 * 16, stat_bytes = log_at + 8;
+    char* const d_stats = static_cast<char*>(arena.alloc(log_at + sizeof(OverflowLog)));
+    unsigned long long* d_digest = reinterpret_cast<unsigned long long*>(d_stats);
+    uint32_t* d_acc_counts = reinterpret_cast<uint32_t*>(d_stats + (size_t)N * 8);
+    uint32_t* d_unc_counts = d_acc_counts + N;
+    uint32_t* d_plain_count = d_unc_counts + N;
+    uint32_t* d_n_pairs = d_plain_count + N;
+    uint32_t* d_n_bitset_nodes = d_n_pairs + 1;
+    OverflowLog* log = reinterpret_cast<OverflowLog*>(d_stats + log_at);
+    const char* const h_stats = arena.pinned(stat_bytes);
+    HIP_OK(hipMemsetAsync(d_plain_count, 0, stat_bytes - plain_at, stream));
     {
       std::lock_guard<std::mutex> lock(ctx().mu);
       (void)overflow_log();
@@ -753,16 +802,12 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
     Engine engine(&A);
     std::vector<int32_t> host_plain;  // nodes of host-decided pairs that are context-dependent by section 3.1 alone
     uint32_t* d_seg_counts = arena.array<uint32_t>((size_t)N * n_seg);
-    unsigned long long* d_digest = arena.array<unsigned long long>((size_t)N);
-    uint32_t* d_unc_counts = arena.array<uint32_t>((size_t)N);
-    RankRows sparse_rows{acc_rank, unc_rank, nullptr, nullptr, nullptr, d_unc_counts, d_seg_counts, nullptr, nullptr};
+    RankRows sparse_rows{acc_rank, unc_rank, nullptr, nullptr, d_acc_counts, d_unc_counts, d_seg_counts, nullptr, d_n_bitset_nodes};
     uint8_t *some_acc = nullptr, *some_unc = nullptr;
     if (sparse) {
       sparse_rows.some_acc = some_acc = arena.array<uint8_t>((size_t)N * some_stride(dv));
       sparse_rows.some_unc = some_unc = arena.array<uint8_t>((size_t)N * some_stride(dv));
-      sparse_rows.acc_counts = arena.array<uint32_t>((size_t)N);
       sparse_rows.bitset_nodes = arena.array<uint32_t>((size_t)N);
-      sparse_rows.n_bitset_nodes = arena.array<uint32_t>(1);
     }
     // rank -> id space, with the rows' statistics (accepted tokens per segment, digest, context-dependent tokens)
     auto permute = [&](int32_t node0, int32_t nb) {
@@ -771,15 +816,14 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
         return;
       }
       launch_permute(dv, nb, acc_rank, unc_rank, acc_id + (size_t)node0 * dv.W, unc_id + (size_t)node0 * dv.W,
-                     d_seg_counts + (size_t)node0 * n_seg, d_digest + node0, d_unc_counts + node0, stream);
+                     d_seg_counts + (size_t)node0 * n_seg, d_digest + node0, d_acc_counts + node0, d_unc_counts + node0, stream);
       if (keep_plain)
         launch_permute(dv, nb, plain_rank, plain_rank, c->d_plain_id + (size_t)node0 * dv.W,
-                       c->d_plain_id + (size_t)node0 * dv.W, nullptr, nullptr, nullptr, stream);
+                       c->d_plain_id + (size_t)node0 * dv.W, nullptr, nullptr, nullptr, nullptr, stream);
     };
     // Pairs whose walk hit a limit are decided on the host and patched into the rank-space rows of the
-    // current batch of nodes.  Returns whether there were any.
-    auto decide_recorded_pairs = [&](int32_t node0) {
-      const uint32_t count_after = read_overflow_count(log);
+    // current batch of nodes (count_after: the log's count).  Returns whether there were any.
+    auto decide_recorded_pairs = [&](int32_t node0, uint32_t count_after) {
       const uint32_t fresh = count_after - count_before;
       if (fresh == 0) return false;
       if (fresh > OverflowLog::kCap) throw Failure(XGM_ERR_TOO_LARGE, "cache_build: too many walks exceeded the on-chip limits");
@@ -805,10 +849,10 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
     // over the limits only afterwards; if there are any, the patched rows are permuted again.
     uint4* d_first_byte = arena.array<uint4>((size_t)256 * first_byte_words(N));
     uint32_t* d_pairs = arena.array<uint32_t>((size_t)batch * (dv.WR / 2));
-    uint32_t* d_n_pairs = arena.array<uint32_t>(1);
     launch_first_byte(tab, d_first_byte, stream);
     for (int32_t node0 = 0; node0 < N; node0 += batch) {
       const int32_t nb = std::min(batch, N - node0);
+      if (node0 > 0) HIP_OK(hipMemsetAsync(d_n_pairs, 0, 4, stream));
       HIP_OK(hipEventRecord(ev0, stream));
       launch_classify(tab, dv, ClassifyArgs{node0, nb, d_first_byte, first_byte_words(N), acc_rank, unc_rank, plain_rank, d_plain_count,
                                             some_acc, some_unc, d_pairs, d_n_pairs, log, seq}, stream);
@@ -819,19 +863,51 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
         float ms = 0.f;
         HIP_OK(hipEventElapsedTime(&ms, ev0, ev1));
         c->kernel_seconds += ms * 1e-3;
-        decide_recorded_pairs(node0);
+        decide_recorded_pairs(node0, read_overflow_count(log));
       }
       permute(node0, nb);
     }
     HIP_OK(hipGetLastError());
+    auto copy_stats = [&] { HIP_OK(hipMemcpyAsync((void*)h_stats, d_stats, stat_bytes, hipMemcpyDeviceToHost, stream)); };
+    copy_stats();
+
+    // ---- while these kernels run: the contexts of the rules, and the same relation by node (what the accept kernel looks
+    // up: which context of a rule a frame sits on)
+    std::vector<uint32_t> ctx_off(A.rule_names.size() + 1, 0);
+    std::vector<uint16_t> ctx_node;
+    std::vector<uint32_t> node_ctx_off((size_t)N + 1, 0), node_ctx;
+    std::vector<uint4> rule_info(A.rule_names.size());
+    std::vector<uint16_t> forced_node;
+    for (size_t r = 0; r < A.rule_names.size(); ++r) {
+      for (int32_t n : A.contexts[r]) {
+        ctx_node.push_back((uint16_t)n);
+        ++node_ctx_off[(size_t)n + 1];
+      }
+      ctx_off[r + 1] = (uint32_t)ctx_node.size();
+      const auto& f = A.forced[r];
+      rule_info[r] = make_uint4((uint32_t)forced_node.size(), (uint32_t)f.size(), (uint32_t)A.end_rule((int32_t)r), 0u);
+      for (size_t k = f.size(); k-- > 0;) forced_node.push_back((uint16_t)f[k]);
+    }
+    std::partial_sum(node_ctx_off.begin(), node_ctx_off.end(), node_ctx_off.begin());
+    node_ctx.resize(std::max<size_t>(ctx_node.size(), 1));
+    {
+      std::vector<uint32_t> next(node_ctx_off.begin(), node_ctx_off.end() - 1);
+      for (size_t r = 0; r < A.rule_names.size(); ++r)
+        for (uint32_t i = ctx_off[r]; i < ctx_off[r + 1]; ++i) node_ctx[next[ctx_node[i]]++] = (uint32_t)r << 16 | (i - ctx_off[r]);
+    }
+    if (ctx_node.empty()) ctx_node.push_back(0);
+    if (forced_node.empty()) forced_node.push_back(0);
+
     HIP_OK(hipStreamSynchronize(stream));
     if (one_batch) {
       float ms = 0.f;
       HIP_OK(hipEventElapsedTime(&ms, ev0, ev1));
       c->kernel_seconds += ms * 1e-3;
-      if (decide_recorded_pairs(0)) {
+      if (decide_recorded_pairs(0, *reinterpret_cast<const uint32_t*>(h_stats + log_at))) {
+        if (sparse) HIP_OK(hipMemsetAsync(d_n_bitset_nodes, 0, 4, stream));
         permute(0, N);
         HIP_OK(hipGetLastError());
+        copy_stats();
         HIP_OK(hipStreamSynchronize(stream));
       }
     }
@@ -842,47 +918,32 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
       ctx().retired_records += count_before;
     }
 
-    // ---- per node: accepted tokens per segment, digest of the accepted row, context-dependent tokens
-    std::vector<uint32_t> seg_counts((size_t)N * n_seg);
-    std::vector<unsigned long long> digest((size_t)N);
-    c->unc_count.resize(N);
-    c->plain_count.resize(N);
-    HIP_OK(hipMemcpy(seg_counts.data(), d_seg_counts, seg_counts.size() * 4, hipMemcpyDeviceToHost));
-    HIP_OK(hipMemcpy(digest.data(), d_digest, digest.size() * 8, hipMemcpyDeviceToHost));
-    HIP_OK(hipMemcpy(c->unc_count.data(), d_unc_counts, (size_t)N * 4, hipMemcpyDeviceToHost));
-    HIP_OK(hipMemcpy(c->plain_count.data(), d_plain_count, (size_t)N * 4, hipMemcpyDeviceToHost));
+    const unsigned long long* const digest = reinterpret_cast<const unsigned long long*>(h_stats);
+    const uint32_t* const acc_counts = reinterpret_cast<const uint32_t*>(h_stats + (size_t)N * 8);
+    c->unc_count.assign(acc_counts + N, acc_counts + 2 * (size_t)N);
+    c->plain_count.assign(acc_counts + 2 * (size_t)N, acc_counts + 3 * (size_t)N);
     for (int32_t n : host_plain) ++c->plain_count[n];
     c->classify_seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t_build0).count();
 
     // ---- accepted tokens: a node with few of them keeps a list (its level-0 key), the others a bitset row;
     // every distinct row is kept once (rows with equal digests are compared with the first of them)
     std::vector<char> as_list((size_t)N, 0);
+    uint64_t n_level0 = 0;
     for (int32_t n = 0; n < N; ++n) {
-      uint64_t total = 0;
-      for (int32_t sgm = 0; sgm < n_seg; ++sgm) total += seg_counts[(size_t)n * n_seg + sgm];
-      as_list[n] = kept_as_list(total, dv.W);
+      as_list[n] = kept_as_list(acc_counts[n], dv.W);
+      if (as_list[n]) n_level0 += acc_counts[n];
     }
     std::vector<int32_t> rep((size_t)N);
     {
       std::unordered_map<unsigned long long, int32_t> first_with;
       for (int32_t n = 0; n < N; ++n) rep[n] = as_list[n] ? n : first_with.emplace(digest[n], n).first->second;
     }
-    int32_t* d_rep = arena.upload(rep, stream);
-    uint32_t* d_equal = arena.array<uint32_t>((size_t)N);
-    launch_rows_equal(acc_id, N, dv.W, d_rep, d_equal, stream);
 
     // ---- keys: level 1 = (node with context-dependent tokens, context of its rule), level 2 = (level-1
     // key, context of that context node's rule).  Only nodes that can be on top of a stack with a frame below it have
     // any: nothing asks for those of the others, which hold most of the context-dependent tokens (a node where a rule
     // has just ended leaves its frame in front of every byte that may follow the rule: 9.8 of the 10.1 M pairs of the
     // largest schema grammar at 151936 tokens, 6.0 of the 6.8 M of the C/SQL-like one at 128256).
-    std::vector<uint32_t> ctx_off(A.rule_names.size() + 1, 0);
-    std::vector<uint16_t> ctx_node;
-    for (size_t r = 0; r < A.rule_names.size(); ++r) {
-      for (int32_t n : A.contexts[r]) ctx_node.push_back((uint16_t)n);
-      ctx_off[r + 1] = (uint32_t)ctx_node.size();
-    }
-    if (ctx_node.empty()) ctx_node.push_back(0);
     auto n_ctx = [&](int32_t rule) { return (uint64_t)(ctx_off[rule + 1] - ctx_off[rule]); };
     // Level l + 1 has a key for every (key of level l, context of the rule of that key's context node).  A level is
     // kept unless its keys alone would take hundreds of megabytes (grammars whose rules are each used in
@@ -929,43 +990,6 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
     for (int l = 0; l < c->levels; ++l) n_keys += n_k[l];
     const size_t n_slots = (size_t)(n_keys * (uint64_t)n_seg);
 
-    // ---- base lists (every node's context-dependent tokens), then the entries of every (key, segment): counted
-    const uint32_t* d_k_base[kCtxLevels] = {};
-    for (int l = 0; l < c->levels; ++l) d_k_base[l] = keep(slab_upload(c->k_base_host[l]));
-    uint32_t* d_ctx_off = keep(slab_upload(ctx_off));
-    uint16_t* d_ctx_node = keep(slab_upload(ctx_node));
-    // the same relation by node (what the accept kernel looks up: which context of a rule a frame sits on)
-    std::vector<uint32_t> node_ctx_off((size_t)N + 1, 0), node_ctx;
-    {
-      std::vector<std::vector<uint32_t>> by_node((size_t)N);
-      for (size_t r = 0; r < A.rule_names.size(); ++r)
-        for (size_t i = 0; i < A.contexts[r].size(); ++i) by_node[A.contexts[r][i]].push_back((uint32_t)(r << 16 | i));
-      for (int32_t n = 0; n < N; ++n) {
-        node_ctx_off[n] = (uint32_t)node_ctx.size();
-        node_ctx.insert(node_ctx.end(), by_node[n].begin(), by_node[n].end());
-      }
-      node_ctx_off[N] = (uint32_t)node_ctx.size();
-      if (node_ctx.empty()) node_ctx.push_back(0u);
-    }
-    c->host.node_ctx_off = keep(slab_upload(node_ctx_off));
-    c->host.node_ctx = keep(slab_upload(node_ctx));
-    uint32_t* d_base_ids = arena.array<uint32_t>((size_t)n_base);
-    uint16_t* d_base_node = arena.array<uint16_t>((size_t)n_base);
-    uint32_t* d_exits = arena.array<uint32_t>((size_t)n_base);
-    {
-      if (sparse) {
-        std::vector<uint32_t> first((size_t)N);
-        for (int32_t n = 0; n < N; ++n) first[n] = A.node_on_top[n] && c->unc_count[n] ? node_off[n] : kNoKey;
-        launch_base_lists(dv, sparse_rows, N, arena.upload(first, stream), d_base_ids, d_base_node, stream);
-      } else {
-        std::vector<uint32_t> row_of((size_t)N);
-        for (int32_t n = 0; n < N; ++n) row_of[n] = A.node_on_top[n] ? (uint32_t)n : kNoKey;
-        uint32_t* d_row_of = arena.upload(row_of, stream);
-        launch_rows_to_lists(unc_id, dv.W, N, d_row_of, 1, arena.upload(node_off, stream), d_base_ids, d_base_node, stream);
-      }
-    }
-    uint32_t* d_counts = arena.array<uint32_t>(n_slots);
-    HIP_OK(hipMemsetAsync(d_counts, 0, n_slots * 4, stream));
     // the level-1 kernel's tiles: the pairs of a node in blocks, its rule's contexts in blocks
     std::vector<uint4> tiles;
     {
@@ -978,18 +1002,82 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
             tiles.push_back(make_uint4(node_off[n] + eb, std::min(tp, L - eb) | (std::min(tc, m - ib) << 16), ib, (uint32_t)n));
       }
     }
+    // the counting pass of level 1 keeps what it found for every (pair, context), 2 bytes each, unless that
+    // would take more than 1 GiB (then the writing pass walks again)
+    const bool keep_outcomes = n_items > 0 && n_items <= ((uint64_t)1 << 29);
+    std::vector<uint4> node_info;
+    if (keep_outcomes) {
+      node_info.assign((size_t)N, make_uint4(0u, 0u, 0u, 0u));
+      uint64_t at = 0;
+      for (int32_t n = 0; n < N; ++n) {
+        if (c->k_base_host[0][n] == kNoKey) continue;
+        node_info[n] = make_uint4((uint32_t)at, c->unc_count[n], node_off[n], 0u);
+        at += (uint64_t)c->unc_count[n] * n_ctx(A.node_rule[n]);
+      }
+    }
+    // where the base list of every node that has one begins
+    std::vector<uint32_t> first((size_t)N);
+    for (int32_t n = 0; n < N; ++n) first[n] = A.node_on_top[n] && c->unc_count[n] ? node_off[n] : kNoKey;
+
+    // ---- to the device: what the cache keeps, and what only the build needs
+    const uint32_t* d_k_base[kCtxLevels] = {};
     ContextListArgs args{};
+    const int32_t* d_rep;
+    const uint32_t* d_first;
+    {
+      Parts kept, temp;
+      size_t at_k[kCtxLevels] = {};
+      for (int l = 0; l < c->levels; ++l) at_k[l] = kept.add(c->k_base_host[l]);
+      const size_t at_off = kept.add(ctx_off), at_ctx = kept.add(ctx_node), at_noff = kept.add(node_ctx_off), at_nctx = kept.add(node_ctx);
+      char* const k = keep(slab_alloc<char>(kept.bytes()));
+      kept.send(k, arena, stream);
+      for (int l = 0; l < c->levels; ++l) d_k_base[l] = reinterpret_cast<const uint32_t*>(k + at_k[l]);
+      c->host.ctx_off = args.ctx_off = reinterpret_cast<const uint32_t*>(k + at_off);
+      c->host.ctx_node = args.ctx_node = reinterpret_cast<const uint16_t*>(k + at_ctx);
+      c->host.node_ctx_off = reinterpret_cast<const uint32_t*>(k + at_noff);
+      c->host.node_ctx = reinterpret_cast<const uint32_t*>(k + at_nctx);
+      const size_t at_rep = temp.add(rep), at_first = temp.add(first), at_tiles = temp.add(tiles), at_rule = temp.add(rule_info),
+                   at_forced = temp.add(forced_node), at_info = temp.add(node_info);
+      char* const t = arena.array<char>(temp.bytes());
+      temp.send(t, arena, stream);
+      d_rep = reinterpret_cast<const int32_t*>(t + at_rep);
+      d_first = reinterpret_cast<const uint32_t*>(t + at_first);
+      args.tiles = reinterpret_cast<const uint4*>(t + at_tiles);
+      args.rule_info = reinterpret_cast<const uint4*>(t + at_rule);
+      args.forced_node = reinterpret_cast<const uint16_t*>(t + at_forced);
+      if (keep_outcomes) args.node_info = reinterpret_cast<const uint4*>(t + at_info);
+    }
+
+    // ---- base lists (every node's context-dependent tokens), then the entries of every (key, segment): counted.  What
+    // the host has to know of it lies side by side: the length of all lists, the counters of the list kernels, the
+    // equality of the rows; the counters and the counts begin at zero.
+    const size_t made_at = 16, equal_at = made_at + 16, counts_at = (equal_at + (size_t)N * 4 + 15) / 16 * 16;
+    static_assert((kCtxLevels + 1) * 4 <= 16, "the counters of the list kernels");
+    char* const d_found = static_cast<char*>(arena.alloc(counts_at + n_slots * 4));
+    const char* const h_found = arena.pinned(counts_at);
+    uint32_t* d_equal = reinterpret_cast<uint32_t*>(d_found + equal_at);
+    uint32_t* d_counts = reinterpret_cast<uint32_t*>(d_found + counts_at);
+    args.res_count = reinterpret_cast<uint32_t*>(d_found + made_at);
+    HIP_OK(hipMemsetAsync(d_found, 0, counts_at + n_slots * 4, stream));
+    launch_rows_equal(acc_id, N, dv.W, d_rep, d_equal, stream);
+    uint32_t* d_base_ids = arena.array<uint32_t>((size_t)n_base);
+    uint16_t* d_base_node = arena.array<uint16_t>((size_t)n_base);
+    if (sparse) launch_base_lists(dv, sparse_rows, N, d_first, d_base_ids, d_base_node, stream);
+    else {
+      std::vector<uint32_t> row_of((size_t)N);
+      for (int32_t n = 0; n < N; ++n) row_of[n] = A.node_on_top[n] ? (uint32_t)n : kNoKey;
+      uint32_t* d_row_of = arena.upload(row_of, stream);
+      launch_rows_to_lists(unc_id, dv.W, N, d_row_of, 1, arena.upload(node_off, stream), d_base_ids, d_base_node, stream);
+    }
     args.base_node = d_base_node;
     args.base_ids = d_base_ids;
     args.total = (uint32_t)n_base;
-    args.exits = d_exits;
-    args.tiles = arena.upload(tiles, stream);
+    args.exits = arena.array<uint32_t>((size_t)n_base);
     args.n_tiles = (uint32_t)tiles.size();
     // (a pair leaves at most about two records per level on the grammars measured: 0.3 to 1.9 for schema grammars, 0.7 for
     // a C-like one, 1.1 for a scripting one; the pass is run again with more room if this is not enough)
     args.res_cap = (uint32_t)std::min<uint64_t>(std::max<uint64_t>(2 * n_base, 1u << 17), 1u << 25);
     for (int l = 0; l + 1 < c->levels; ++l) args.res[l] = arena.array<uint4>(args.res_cap);
-    args.res_count = arena.array<uint32_t>(kCtxLevels + 1);
     {
       uint32_t key0 = (uint32_t)N;
       for (int l = 0; l < kCtxLevels; ++l) {
@@ -998,62 +1086,47 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
         key0 += (uint32_t)n_k[l];
       }
     }
-    args.ctx_off = d_ctx_off;
-    args.ctx_node = d_ctx_node;
-    {
-      std::vector<uint4> rule_info(A.rule_names.size());
-      std::vector<uint16_t> forced_node;
-      for (size_t r = 0; r < A.rule_names.size(); ++r) {
-        const auto& f = A.forced[r];
-        rule_info[r] = make_uint4((uint32_t)forced_node.size(), (uint32_t)f.size(), (uint32_t)A.end_rule((int32_t)r), 0u);
-        for (size_t k = f.size(); k-- > 0;) forced_node.push_back((uint16_t)f[k]);
-      }
-      if (forced_node.empty()) forced_node.push_back(0);
-      args.rule_info = arena.upload(rule_info, stream);
-      args.forced_node = arena.upload(forced_node, stream);
-    }
     args.counts = d_counts;
-    // the counting pass of level 1 keeps what it found for every (pair, context), 2 bytes each, unless that
-    // would take more than 1 GiB (then the writing pass walks again)
-    if (n_items > 0 && n_items <= ((uint64_t)1 << 29)) {
-      std::vector<uint4> node_info((size_t)N, make_uint4(0u, 0u, 0u, 0u));
-      uint64_t at = 0;
-      for (int32_t n = 0; n < N; ++n) {
-        if (c->k_base_host[0][n] == kNoKey) continue;
-        node_info[n] = make_uint4((uint32_t)at, c->unc_count[n], node_off[n], 0u);
-        at += (uint64_t)c->unc_count[n] * n_ctx(A.node_rule[n]);
-      }
-      args.node_info = arena.upload(node_info, stream);
+    if (keep_outcomes) {
       args.outcomes = arena.array<uint16_t>((size_t)n_items);
       // (the deeper levels keep theirs per record: 16 bytes each)
       for (int l = 1; l < c->levels; ++l) args.deep_outcomes[l] = arena.array<uint4>(args.res_cap);
     }
+    // the offsets of every (key, segment) from the counts; front and back: where its accepted and its walk entries go
+    uint32_t* d_key_off = keep(slab_alloc<uint32_t>(n_slots + 1));
+    args.front = arena.array<uint32_t>(n_slots);
+    args.back = arena.array<uint32_t>(n_slots);
+    uint32_t* d_block_sums = arena.array<uint32_t>(slot_blocks(n_slots) * 2);
+    auto offsets = [&] {
+      launch_slot_offsets(SlotCounts{d_acc_counts, d_seg_counts, d_counts, N, dv.W, n_seg, n_slots}, reinterpret_cast<unsigned long long*>(d_block_sums),
+                          d_key_off, args.front, args.back, reinterpret_cast<unsigned long long*>(d_found), stream);
+      HIP_OK(hipGetLastError());
+      HIP_OK(hipMemcpyAsync((void*)h_found, d_found, counts_at, hipMemcpyDeviceToHost, stream));
+      HIP_OK(hipStreamSynchronize(stream));
+    };
     launch_exit_positions(tab, dv, args, stream);
     launch_context_lists(tab, dv, args, false, stream);
-    HIP_OK(hipGetLastError());
-    HIP_OK(hipStreamSynchronize(stream));
-    for (;;) {  // records that did not fit were dropped: count again with room for all of them (rare)
-      uint32_t made[kCtxLevels + 1] = {};
-      HIP_OK(hipMemcpy(made, args.res_count, sizeof(made), hipMemcpyDeviceToHost));
-      const uint32_t most = *std::max_element(made, made + kCtxLevels);
-      c->host.walks = made[kCtxLevels];
-      if (most <= args.res_cap) break;
-      args.res_cap = most;
+    offsets();
+    const uint32_t* const made = reinterpret_cast<const uint32_t*>(h_found + made_at);
+    while (*std::max_element(made, made + kCtxLevels) > args.res_cap) {  // records that did not fit were dropped: count again with room for all of them (rare)
+      args.res_cap = *std::max_element(made, made + kCtxLevels);
       for (int l = 0; l + 1 < c->levels; ++l) args.res[l] = arena.array<uint4>(args.res_cap);
       if (args.outcomes)
         for (int l = 1; l < c->levels; ++l) args.deep_outcomes[l] = arena.array<uint4>(args.res_cap);
+      HIP_OK(hipMemsetAsync(args.res_count, 0, 16, stream));
       HIP_OK(hipMemsetAsync(d_counts, 0, n_slots * 4, stream));
       launch_context_lists(tab, dv, args, false, stream);
-      HIP_OK(hipGetLastError());
-      HIP_OK(hipStreamSynchronize(stream));
+      offsets();
     }
+    c->host.walks = made[kCtxLevels];
+    const uint64_t total = *reinterpret_cast<const uint64_t*>(h_found);
+    if (total >= ((uint64_t)1 << 32)) throw Failure(XGM_ERR_TOO_LARGE, "cache_build: token lists exceed 2^32 entries");
 
     // ---- the distinct bitset rows
     uint32_t* acc_rows = nullptr;
     uint16_t* d_acc_row = nullptr;
     {
-      std::vector<uint32_t> equal((size_t)N);
-      HIP_OK(hipMemcpy(equal.data(), d_equal, equal.size() * 4, hipMemcpyDeviceToHost));
+      const uint32_t* const equal = reinterpret_cast<const uint32_t*>(h_found + equal_at);
       std::vector<int32_t> unique;
       c->acc_row_host.assign((size_t)N, (uint16_t)kNoAccRow);
       std::vector<int32_t> row_of_rep((size_t)N, -1);
@@ -1069,44 +1142,25 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
       if (unique.size() >= kNoAccRow) throw Failure(XGM_ERR_TOO_LARGE, "cache_build: more than 65534 distinct accepted bitsets");
       c->n_acc_rows = (int32_t)unique.size();
       acc_rows = keep(slab_alloc<uint32_t>(unique.size() * (size_t)dv.W));
-      int32_t* d_unique = arena.upload(unique, stream);
-      launch_gather_rows(acc_id, dv.W, d_unique, c->n_acc_rows, acc_rows, stream);
-      d_acc_row = keep(slab_upload(c->acc_row_host));
+      Parts rows;
+      const size_t at_row = rows.add(c->acc_row_host), at_unique = rows.add(unique);
+      char* const r = keep(slab_alloc<char>(rows.bytes()));
+      rows.send(r, arena, stream);
+      d_acc_row = reinterpret_cast<uint16_t*>(r + at_row);
+      launch_gather_rows(acc_id, dv.W, reinterpret_cast<const int32_t*>(r + at_unique), c->n_acc_rows, acc_rows, stream);
       c->device_bytes += (int64_t)unique.size() * dv.W * 4 + (int64_t)N * 2;
     }
-    // ---- offsets from the counts, then the entries
-    std::vector<uint32_t> counts(n_slots);
-    HIP_OK(hipMemcpy(counts.data(), d_counts, n_slots * 4, hipMemcpyDeviceToHost));
-    uint64_t n_level0 = 0;
-    for (int32_t n = 0; n < N; ++n)
-      if (as_list[n])
-        for (int32_t sgm = 0; sgm < n_seg; ++sgm) n_level0 += counts[(size_t)n * n_seg + sgm] = seg_counts[(size_t)n * n_seg + sgm];
-    c->key_off_host.assign(n_slots + 1, 0u);
-    uint64_t total = 0;
-    for (size_t k = 0; k < n_slots; ++k) {
-      c->key_off_host[k] = (uint32_t)total;
-      total += counts[k];
-      if (total >= ((uint64_t)1 << 32)) throw Failure(XGM_ERR_TOO_LARGE, "cache_build: token lists exceed 2^32 entries");
-    }
-    c->key_off_host[n_slots] = (uint32_t)total;
-    uint32_t* d_key_off = keep(slab_upload(c->key_off_host));
+    // ---- the entries
     uint32_t* d_entries = keep(slab_alloc<uint32_t>((size_t)total));
-    {
-      uint32_t* d_front = arena.array<uint32_t>(n_slots);
-      uint32_t* d_back = arena.array<uint32_t>(n_slots);
-      HIP_OK(hipMemcpyAsync(d_front, d_key_off, n_slots * 4, hipMemcpyDeviceToDevice, stream));
-      HIP_OK(hipMemcpyAsync(d_back, d_key_off + 1, n_slots * 4, hipMemcpyDeviceToDevice, stream));
-      if (sparse) launch_level0_lists(dv, sparse_rows, N, d_key_off, d_entries, stream);
-      else {
-        std::vector<uint32_t> list_key((size_t)N);
-        for (int32_t n = 0; n < N; ++n) list_key[n] = as_list[n] ? (uint32_t)n : kNoKey;
-        launch_rows_to_lists(acc_id, dv.W, N, arena.upload(list_key, stream), n_seg, d_front, d_entries, nullptr, stream);
-      }
-      args.front = d_front;
-      args.back = d_back;
-      args.entries = d_entries;
-      launch_context_lists(tab, dv, args, true, stream);
+    if (sparse) launch_level0_lists(dv, sparse_rows, N, d_key_off, d_entries, stream);
+    else {
+      std::vector<uint32_t> list_key((size_t)N);
+      for (int32_t n = 0; n < N; ++n) list_key[n] = as_list[n] ? (uint32_t)n : kNoKey;
+      launch_rows_to_lists(acc_id, dv.W, N, arena.upload(list_key, stream), n_seg, args.front, d_entries, nullptr, stream);
     }
+    args.entries = d_entries;
+    if (!args.outcomes) HIP_OK(hipMemsetAsync(args.res_count, 0, 16, stream));
+    launch_context_lists(tab, dv, args, true, stream);
     HIP_OK(hipGetLastError());
     cleanup_temps();  // (synchronises the stream)
 
@@ -1118,8 +1172,6 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
       c->host.k_base[l] = d_k_base[l];
       c->host.n_k[l] = (uint32_t)n_k[l];
     }
-    c->host.ctx_off = d_ctx_off;
-    c->host.ctx_node = d_ctx_node;
     c->host.n_nodes = N;
     c->host.long_walks = c->host_classified > 0 ? 1u : 0u;
     c->device_bytes += (int64_t)(n_slots + 1) * 4 + (int64_t)total * 4 + (int64_t)image_bytes + (int64_t)(n_keys - n_k[c->levels - 1]) * 4 +
@@ -1188,7 +1240,9 @@ int xgm_cache_copy_node_bits(const xgm_cache* c, int32_t node, int32_t* h_acc, i
       HIP_OK(hipMemcpy(h_acc, c->host.acc + (size_t)c->acc_row_host[node] * dv.W, (size_t)dv.W * 4, hipMemcpyDeviceToHost));
     } else {  // the node keeps its accepted tokens as a list (its level-0 key)
       std::memset(h_acc, 0, (size_t)dv.W * 4);
-      const uint32_t j0 = c->key_off_host[(size_t)node * dv.n_seg], j1 = c->key_off_host[(size_t)(node + 1) * dv.n_seg];
+      uint32_t j0 = 0u, j1 = 0u;
+      HIP_OK(hipMemcpy(&j0, c->host.key_off + (size_t)node * dv.n_seg, 4, hipMemcpyDeviceToHost));
+      HIP_OK(hipMemcpy(&j1, c->host.key_off + (size_t)(node + 1) * dv.n_seg, 4, hipMemcpyDeviceToHost));
       std::vector<uint32_t> list(j1 - j0);
       if (j1 > j0) HIP_OK(hipMemcpy(list.data(), c->host.entries + j0, (size_t)(j1 - j0) * 4, hipMemcpyDeviceToHost));
       for (uint32_t e : list) {
@@ -1327,16 +1381,11 @@ static void stack_keys(const Automaton& A, const xgm_cache& c, const Stack& s, u
     key0 += c.host.n_k[l - 1];
   }
 }
-// One stack header as the fill kernel reads it, written out on the host (device-resident batches are set up
-// this way; the fills from host-side states send the keys and let the device look the offsets up).
-static void pack_stack_header(const Automaton& A, const xgm_cache& c, const Stack& s, uint32_t frame_offset, uint32_t* h) {
-  const int32_t n_seg = c.v->dv.n_seg;
-  uint32_t key[kStackLists];
-  stack_keys(A, c, s, frame_offset, h, key);
-  for (uint32_t l = 0; l < kStackLists; ++l) {
-    const uint32_t* ko = key[l] == kNoKey ? nullptr : &c.key_off_host[(size_t)key[l] * n_seg];
-    for (int32_t sgm = 0; sgm <= n_seg; ++sgm) h[stack_hdr_off((uint32_t)sgm, l)] = ko ? ko[sgm] : 0u;
-  }
+// What the device makes a stack's header of (kStackKeysWords words).
+static void pack_stack_keys(const Automaton& A, const xgm_cache& c, const Stack& s, uint32_t frame_offset, uint32_t* h) {
+  stack_keys(A, c, s, frame_offset, h, h + kStackHdrWords);
+  const uint64_t key_off = (uint64_t)c.host.key_off;
+  std::memcpy(h + kStackHdrWords + kStackLists, &key_off, 8);
 }
 
 // Host staging of the entry point that allocates nothing: the blob is packed here and copied to the device's
@@ -1572,13 +1621,18 @@ int xgm_debug_matcher_fill_work(const xgm_matcher* m, int64_t* h_out4) {
   if (!m || !m->c || !h_out4) return fail(XGM_ERR_BAD_ARG, "matcher_fill_work: null argument or a matcher without a cache");
   for (int k = 0; k < 4; ++k) h_out4[k] = 0;
   if (m->terminated) return XGM_OK;
-  const int32_t n_seg = m->v->dv.n_seg;
-  std::vector<uint32_t> h(stack_hdr_stride(n_seg));
+  const size_t n_seg = (size_t)m->v->dv.n_seg;
+  uint32_t h[kStackKeysWords];
   for (const Stack& s : m->stacks) {
-    pack_stack_header(m->g->A, *m->c, s, 0u, h.data());
+    pack_stack_keys(m->g->A, *m->c, s, 0u, h);
     if ((h[kStackHdrTop] >> 16) != kNoAccRow) ++h_out4[0];
     for (uint32_t l = 0; l < kStackLists; ++l) {
-      h_out4[1 + std::min<uint32_t>(l, 2u)] += h[stack_hdr_off((uint32_t)n_seg, l)] - h[stack_hdr_off(0u, l)];
+      const uint32_t key = h[kStackHdrWords + l];
+      uint32_t j0 = 0u, j1 = 0u;
+      if (key == kNoKey) continue;
+      HIP_OK(hipMemcpy(&j0, m->c->host.key_off + key * n_seg, 4, hipMemcpyDeviceToHost));
+      HIP_OK(hipMemcpy(&j1, m->c->host.key_off + (key + 1) * n_seg, 4, hipMemcpyDeviceToHost));
+      h_out4[1 + std::min<uint32_t>(l, 2u)] += j1 - j0;
     }
   }
   return XGM_OK;
@@ -1831,7 +1885,7 @@ PackedState pack_state(const xgm_batch& bt, int32_t row, int32_t slot, const xgm
     for (size_t k = 0; k < m.stacks.size(); ++k) {
       const Stack& s = m.stacks[k];
       if (s.size() > kBatchMaxDepth) throw Failure(XGM_ERR_TOO_LARGE, "batch: a stack deeper than 128 frames");
-      pack_stack_header(A, c, s, p.row.frame_begin + fi, &p.hdrs[k * hdr_words]);
+      pack_stack_keys(A, c, s, p.row.frame_begin + fi, &p.hdrs[k * hdr_words]);
       for (int32_t n : s) p.frames.push_back((uint16_t)n);
       fi += (uint32_t)s.size();
     }
@@ -1844,7 +1898,8 @@ PackedState pack_state(const xgm_batch& bt, int32_t row, int32_t slot, const xgm
   p.row.flags = p.meta.flags & 1u;
   return p;
 }
-// `epoch`: the row's count of state changes after this write
+// `epoch`: the row's count of state changes after this write.  The stack headers are written out on the device:
+// launch_batch_headers() has to follow.
 void write_state(const xgm_batch& bt, int32_t row, int32_t slot, PackedState p, uint32_t epoch) {
   const size_t hdr_words = stack_hdr_stride(bt.dev.n_seg);
   const size_t at = (size_t)row * bt.H + slot;
@@ -1904,6 +1959,8 @@ int xgm_batch_create(xgm_matcher* const* ms, int32_t B, int32_t history, void* h
     HIP_OK(hipMemset(d.older, 0, (size_t)B * 4));
     HIP_OK(hipMemset(d.status, 0, (size_t)B * 4));
     for (int32_t b = 0; b < B; ++b) write_state(*bt, b, 0, pack_state(*bt, b, 0, *ms[b]), 0u);
+    launch_batch_headers(d, 0, B, 0, stream);
+    HIP_OK(hipGetLastError());
     HIP_OK(hipStreamSynchronize(stream));
     std::lock_guard<std::mutex> lock(ctx().mu);
     ctx().batches.insert(bt);
@@ -2001,6 +2058,9 @@ int xgm_batch_set_row(xgm_batch* bt, int32_t row, const xgm_matcher* m, void* hi
   HIP_OK(hipMemcpy(&cur, bt->dev.rows + row, sizeof(RowDesc), hipMemcpyDeviceToHost));
   const int32_t next = (head + 1) % bt->H;
   write_state(*bt, row, next, pack_state(*bt, row, next, *m), cur.epoch + 1u);
+  launch_batch_headers(bt->dev, row, 1, next, stream);
+  HIP_OK(hipGetLastError());
+  HIP_OK(hipStreamSynchronize(stream));
   older = std::min(older + 1, bt->H - 1);
   const int32_t ok = XGM_OK;
   HIP_OK(hipMemcpy(bt->dev.head + row, &next, 4, hipMemcpyHostToDevice));

@@ -621,14 +621,14 @@ __global__ __launch_bounds__(kNodeThreads) void level0_lists_kernel(DevVocab voc
 // the node's two id-space rows in LDS.  Rows are nearly empty (most nodes reject nearly every token) or nearly
 // full (the inside of a string), so only the rarer kind of bit is moved: a row with few set bits starts as zeros
 // and gets its set bits, one with many starts as ones and gets its zeros.  With the rows still in LDS the
-// workgroup also takes their statistics (all three outputs may be null): set bits of the first row per segment,
-// its digest, and the number of set bits of the second.
+// workgroup also takes their statistics (the outputs may be null, all together): set bits of the first row per segment,
+// its digest, and the number of set bits of both.
 __global__ __launch_bounds__(kRowThreads) void permute_kernel(DevVocab voc, const uint32_t* __restrict__ a_rank,
                                                               const uint32_t* __restrict__ b_rank,
                                                               uint32_t* a_id, uint32_t* b_id,  // (may be the same row)
                                                               uint32_t* __restrict__ seg_counts,
                                                               unsigned long long* __restrict__ digest,
-                                                              uint32_t* __restrict__ b_counts) {
+                                                              uint32_t* __restrict__ a_counts, uint32_t* __restrict__ b_counts) {
   extern __shared__ __align__(16) unsigned char smem[];
   uint32_t* rows = reinterpret_cast<uint32_t*>(smem);  // [2][W]
   __shared__ uint32_t set_bits[2];
@@ -693,6 +693,7 @@ __global__ __launch_bounds__(kRowThreads) void permute_kernel(DevVocab voc, cons
     unsigned long long t = 0ull;
     for (int k = 0; k < kRowThreads / 64; ++k) t += part[k];
     digest[node] = t;
+    a_counts[node] = set_bits[0];
     b_counts[node] = set_bits[1];
   }
 }
@@ -1069,6 +1070,68 @@ __global__ __launch_bounds__(256) void context_deeper_write_kernel(DevVocab voc,
   }
 }
 
+// The running sum over the slots (see launch_slot_offsets), in two launches: the sum of every block of slots, then the offsets
+// in it (a block adds up the sums of all blocks in front of it by itself: 98 of them for the 11867-node schema grammar).
+// On the host, with the counts copied there and the offsets copied back, this took 350 us of that grammar's build.
+constexpr int kSlotThreads = 256, kSlotsPerThread = 16, kSlotBlock = kSlotThreads * kSlotsPerThread;
+__device__ __forceinline__ uint32_t slot_count(const SlotCounts& c, size_t k) {
+  if (k >= c.n_slots) return 0u;
+  if (k >= (size_t)c.n_nodes * (uint32_t)c.n_seg) return c.counts[k];
+  return kept_as_list(c.acc_counts[(uint32_t)k / (uint32_t)c.n_seg], c.W) ? c.seg_counts[k] : 0u;
+}
+// the sum over the workgroup, in every thread (64 bits: a grammar's lists may be too long for 32)
+__device__ __forceinline__ u64 block_sum(u64 v, u64* part) {
+#pragma unroll
+  for (uint32_t d = 1; d < 64u; d <<= 1) v += __shfl_xor(v, d, 64);
+  if ((threadIdx.x & 63u) == 0u) part[threadIdx.x >> 6] = v;
+  __syncthreads();
+  u64 sum = 0ull;
+  for (int k = 0; k < kSlotThreads / 64; ++k) sum += part[k];
+  __syncthreads();
+  return sum;
+}
+__global__ __launch_bounds__(kSlotThreads) void slot_sums_kernel(SlotCounts c, u64* __restrict__ block_sums) {
+  __shared__ u64 part[kSlotThreads / 64];
+  u64 v = 0ull;
+  for (int j = 0; j < kSlotsPerThread; ++j) v += slot_count(c, (size_t)blockIdx.x * kSlotBlock + (uint32_t)(j * kSlotThreads) + threadIdx.x);
+  const u64 sum = block_sum(v, part);
+  if (threadIdx.x == 0u) block_sums[blockIdx.x] = sum;
+}
+__global__ __launch_bounds__(kSlotThreads) void slot_offsets_kernel(SlotCounts c, const u64* __restrict__ block_sums, uint32_t* __restrict__ key_off,
+                                                                    uint32_t* __restrict__ front, uint32_t* __restrict__ back, u64* __restrict__ total) {
+  __shared__ u64 part[kSlotThreads / 64];
+  u64 before = 0ull;
+  for (uint32_t k = threadIdx.x; k < blockIdx.x; k += kSlotThreads) before += block_sums[k];
+  u64 base = block_sum(before, part);
+  const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+  for (int j = 0; j < kSlotsPerThread; ++j) {
+    const size_t k = (size_t)blockIdx.x * kSlotBlock + (uint32_t)(j * kSlotThreads) + threadIdx.x;
+    const u64 n = slot_count(c, k);
+    u64 incl = n;
+#pragma unroll
+    for (uint32_t d = 1; d < 64u; d <<= 1) {
+      const u64 v = __shfl_up(incl, d, 64);
+      if (lane >= d) incl += v;
+    }
+    if (lane == 63u) part[wave] = incl;
+    __syncthreads();
+    u64 at = base + incl - n;
+    for (uint32_t q = 0; q < (uint32_t)kSlotThreads / 64u; ++q) {
+      if (q < wave) at += part[q];
+      base += part[q];
+    }
+    __syncthreads();
+    if (k < c.n_slots) {
+      key_off[k] = front[k] = (uint32_t)at;
+      back[k] = (uint32_t)(at + n);
+      if (k + 1 == c.n_slots) {
+        key_off[k + 1] = (uint32_t)(at + n);
+        *total = at + n;
+      }
+    }
+  }
+}
+
 __global__ __launch_bounds__(kRowThreads) void rows_equal_kernel(const uint32_t* __restrict__ rows, int32_t W,
                                                                  const int32_t* __restrict__ rep,
                                                                  uint32_t* __restrict__ equal) {
@@ -1206,6 +1269,23 @@ __global__ __launch_bounds__(kUploadThreads) void upload_stacks_kernel(const uin
       out = key == kNoKey ? 0u : key_off[(size_t)key * n_seg + sgm];
     }
     dst_hdrs[(size_t)(s0 + st) * stride + w] = out;
+  }
+}
+
+// The same in place: the stacks of the states in one slot of some rows of a batch, a workgroup per (stack, row).
+__global__ __launch_bounds__(64) void batch_headers_kernel(DevBatch bt, int32_t row0, int32_t slot) {
+  __shared__ uint32_t keys[kStackKeysWords];
+  const size_t at = (size_t)(row0 + (int32_t)blockIdx.y) * bt.H + slot;
+  if (blockIdx.x >= bt.meta[at].n_stacks) return;
+  const uint32_t stride = stack_hdr_stride(bt.n_seg), n_seg = (uint32_t)bt.n_seg;
+  uint32_t* const h = bt.hdrs + (at * kBatchMaxStacks + blockIdx.x) * stride;
+  if (threadIdx.x < kStackKeysWords) keys[threadIdx.x] = h[threadIdx.x];
+  __syncthreads();
+  const uint32_t* key_off = reinterpret_cast<const uint32_t*>((uintptr_t)keys[kStackHdrWords + kStackLists] |
+                                                              ((uintptr_t)keys[kStackHdrWords + kStackLists + 1] << 32));
+  for (uint32_t w = kStackHdrWords + threadIdx.x; w < stride; w += 64u) {
+    const uint32_t sgm = (w - kStackHdrWords) / kStackLists, key = keys[kStackHdrWords + (w - kStackHdrWords) % kStackLists];
+    h[w] = key == kNoKey ? 0u : key_off[(size_t)key * n_seg + sgm];
   }
 }
 
@@ -2234,7 +2314,6 @@ void launch_first_byte(const DevTables& tab, uint4* first_byte, hipStream_t stre
 
 void launch_classify(const DevTables& tab, const DevVocab& voc, const ClassifyArgs& args, hipStream_t stream) {
   if (args.n_nodes <= 0 || voc.V <= 0) return;
-  (void)hipMemsetAsync(args.n_pairs, 0, 4, stream);
   const DevTables st = staged_for(tab, kClassifyLdsBudget);
   const bool small = st.stage_bytes <= kClassifySmallStage;
   const int32_t waves = (small ? kClassifyThreadsSmall : kClassifyThreadsLarge) / 64;
@@ -2249,15 +2328,14 @@ void launch_classify(const DevTables& tab, const DevVocab& voc, const ClassifyAr
 }
 
 void launch_permute(const DevVocab& voc, int32_t n, const uint32_t* a_rank, const uint32_t* b_rank, uint32_t* a_id,
-                    uint32_t* b_id, uint32_t* seg_counts, unsigned long long* digest, uint32_t* b_counts, hipStream_t stream) {
+                    uint32_t* b_id, uint32_t* seg_counts, unsigned long long* digest, uint32_t* a_counts, uint32_t* b_counts, hipStream_t stream) {
   if (n <= 0) return;
   hipLaunchKernelGGL(permute_kernel, dim3(n), dim3(kRowThreads), (size_t)voc.W * 8, stream, voc, a_rank, b_rank, a_id, b_id,
-                     seg_counts, digest, b_counts);
+                     seg_counts, digest, a_counts, b_counts);
 }
 
 void launch_row_stats(const DevVocab& voc, const RankRows& rows, int32_t n, uint32_t* acc_id, unsigned long long* digest, hipStream_t stream) {
   if (n <= 0) return;
-  (void)hipMemsetAsync(rows.n_bitset_nodes, 0, 4, stream);
   hipLaunchKernelGGL(row_stats_kernel, dim3(n), dim3(kNodeThreads), 0, stream, voc, rows);
   hipLaunchKernelGGL(bitset_rows_kernel, dim3(std::min(n, 1024)), dim3(kBitsetThreads), (size_t)voc.W * 4, stream, voc, rows, acc_id, digest);
 }
@@ -2286,6 +2364,14 @@ void launch_rows_to_lists(const uint32_t* rows, int32_t row_words, int32_t n, co
   }
 }
 
+size_t slot_blocks(size_t n_slots) { return (n_slots + kSlotBlock - 1) / kSlotBlock; }
+void launch_slot_offsets(const SlotCounts& counts, unsigned long long* block_sums, uint32_t* key_off, uint32_t* front, uint32_t* back,
+                         unsigned long long* total, hipStream_t stream) {
+  const dim3 grid((uint32_t)slot_blocks(counts.n_slots));  // (a grammar has a node, a vocabulary a segment)
+  hipLaunchKernelGGL(slot_sums_kernel, grid, dim3(kSlotThreads), 0, stream, counts, block_sums);
+  hipLaunchKernelGGL(slot_offsets_kernel, grid, dim3(kSlotThreads), 0, stream, counts, block_sums, key_off, front, back, total);
+}
+
 void launch_exit_positions(const DevTables& tab, const DevVocab& voc, const ContextListArgs& args, hipStream_t stream) {
   if (args.total == 0) return;
   const DevTables st = staged_for(tab, kContextLdsBudget);
@@ -2294,8 +2380,6 @@ void launch_exit_positions(const DevTables& tab, const DevVocab& voc, const Cont
 }
 
 void launch_context_lists(const DevTables& tab, const DevVocab& voc, const ContextListArgs& args, bool write, hipStream_t stream) {
-  // (the caller reads the counters also where there is nothing to count)
-  if (!(write && args.outcomes)) (void)hipMemsetAsync(args.res_count, 0, 4 * (kCtxLevels + 1), stream);
   if (args.total == 0 || args.n_tiles == 0) return;
   const DevTables st = staged_for(tab, kContextLdsBudget);
   const dim3 g1(args.n_tiles), g2(1024);
@@ -2343,6 +2427,11 @@ void launch_upload_stacks(const void* src, void* dst, size_t plain_bytes, const 
                      reinterpret_cast<const uint4*>(src), reinterpret_cast<uint4*>(dst), plain16,
                      reinterpret_cast<const uint4*>(src_frames), reinterpret_cast<uint4*>(dst_frames), frames16, copy_blocks,
                      reinterpret_cast<const uint4*>(src_stacks), n_stacks, (uint32_t)n_seg, reinterpret_cast<uint32_t*>(dst_hdrs));
+}
+
+void launch_batch_headers(const DevBatch& bt, int32_t row0, int32_t n, int32_t slot, hipStream_t stream) {
+  static_assert(kStackKeysWords <= stack_hdr_stride(1), "the key words of a stack lie where its header belongs");
+  hipLaunchKernelGGL(batch_headers_kernel, dim3(kBatchMaxStacks, n), dim3(64), 0, stream, bt, row0, slot);
 }
 
 // Walks take long, and few rows of a batch have many: where the segments alone do not fill the chip four workgroups share

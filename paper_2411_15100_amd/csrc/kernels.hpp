@@ -269,7 +269,7 @@ struct ClassifyArgs {
   uint8_t* some_acc;
   uint8_t* some_unc;
   uint32_t* pairs;             // [n_nodes * WR / 2] room for every (64 tokens, node) pair
-  uint32_t* n_pairs;           // (cleared by the launcher)
+  uint32_t* n_pairs;           // (zero before the launch)
   OverflowLog* log;
   uint32_t seq;
 };
@@ -302,7 +302,7 @@ struct RankRows {
   uint32_t* unc_counts;      // [n]
   uint32_t* seg_counts;      // [n][n_seg]
   uint32_t* bitset_nodes;    // [n]
-  uint32_t* n_bitset_nodes;
+  uint32_t* n_bitset_nodes;  // (zero before the launch)
 };
 void launch_row_stats(const DevVocab& voc, const RankRows& rows, int32_t n, uint32_t* acc_id, unsigned long long* digest, hipStream_t stream);
 // the context-dependent tokens of every node with first[node] != kNoKey, from there on: ids, and the node beside each
@@ -310,10 +310,11 @@ void launch_base_lists(const DevVocab& voc, const RankRows& rows, int32_t n, con
 // the entries of the level-0 keys (see DevCache)
 void launch_level0_lists(const DevVocab& voc, const RankRows& rows, int32_t n, const uint32_t* key_off, uint32_t* entries, hipStream_t stream);
 // Rank space -> id space for n node rows (two bitsets per node), and - unless the pointers are null - per node the
-// set bits of the first row per segment (seg_counts[n][n_seg]), a digest of the first row and the set bits of the
-// second row (b_counts[n]).
+// set bits of the first row per segment (seg_counts[n][n_seg]), a digest of the first row and the set bits of both
+// rows (a_counts[n], b_counts[n]).
 void launch_permute(const DevVocab& voc, int32_t n, const uint32_t* a_rank, const uint32_t* b_rank, uint32_t* a_id,
-                    uint32_t* b_id, uint32_t* seg_counts, unsigned long long* digest, uint32_t* b_counts, hipStream_t stream);
+                    uint32_t* b_id, uint32_t* seg_counts, unsigned long long* digest, uint32_t* a_counts, uint32_t* b_counts,
+                    hipStream_t stream);
 // whether row k equals row rep[k], word for word (k = 0 .. n-1); rows[unique[u]] -> out[u]
 void launch_rows_equal(const uint32_t* rows, int32_t n, int32_t W, const int32_t* rep, uint32_t* equal, hipStream_t stream);
 void launch_gather_rows(const uint32_t* rows, int32_t W, const int32_t* unique, int32_t n_unique, uint32_t* out,
@@ -349,7 +350,8 @@ struct ContextListArgs {
   uint32_t n_tiles;
   uint4* res[kCtxLevels];      // (the last one is not used)
   uint32_t res_cap;
-  uint32_t* res_count;         // [kCtxLevels + 1]; the last one: walk entries, counted up to about kManyWalks
+  uint32_t* res_count;         // [kCtxLevels + 1], zero before the counting pass (and before a writing pass that walks again);
+                               // the last one: walk entries, counted up to about kManyWalks
   const uint32_t* k_base[kCtxLevels];
   uint32_t key0[kCtxLevels];   // the first key of level 1, 2, ... in the shared numbering
   const uint32_t* ctx_off;
@@ -372,6 +374,20 @@ struct ContextListArgs {
   // pass of that level walks again.  Used together with `outcomes` only.
   uint4* deep_outcomes[kCtxLevels];
 };
+// Where the entries of every slot (key, segment) begin: the running sum of the counts, in key_off (n_slots + 1 words) and
+// front; back[k] = key_off[k + 1].  A slot of a node (its level-0 key) holds the accepted tokens that the node lists, one
+// of the other keys what the list kernels counted.  *total: all of them (more than 2^32 do not fit key_off).
+// block_sums: slot_blocks(n_slots) words of 64 bits.
+struct SlotCounts {
+  const uint32_t* acc_counts;  // [n_nodes]
+  const uint32_t* seg_counts;  // [n_nodes][n_seg]
+  const uint32_t* counts;      // [n_slots]
+  int32_t n_nodes, W, n_seg;
+  size_t n_slots;
+};
+size_t slot_blocks(size_t n_slots);
+void launch_slot_offsets(const SlotCounts& counts, unsigned long long* block_sums, uint32_t* key_off, uint32_t* front, uint32_t* back,
+                         unsigned long long* total, hipStream_t stream);
 void launch_exit_positions(const DevTables& tab, const DevVocab& voc, const ContextListArgs& args, hipStream_t stream);
 void launch_context_lists(const DevTables& tab, const DevVocab& voc, const ContextListArgs& args, bool write, hipStream_t stream);
 uint32_t context_tile_pairs();
@@ -389,6 +405,8 @@ constexpr uint32_t kStackKeysWords = 12;
 void launch_upload_stacks(const void* src, void* dst, size_t plain_bytes, const void* src_stacks, uint32_t n_stacks,
                           int32_t n_seg, void* dst_hdrs, const void* src_frames, void* dst_frames, size_t frames_bytes,
                           hipStream_t stream);
+// The same in place for the states in slot `slot` of rows [row0, row0 + n): where a header belongs lie kStackKeysWords words.
+void launch_batch_headers(const DevBatch& bt, int32_t row0, int32_t n, int32_t slot, hipStream_t stream);
 // (b) batched mask fill: one workgroup per (segment, row)
 // walks: what the walks of the batch's caches need.
 // step_counter: null on the hot path; otherwise the counting instantiation is launched.
