@@ -703,7 +703,8 @@ int xgm_debug_matcher_accept_token_walk(xgm_matcher* m, int32_t token_id) {
 
 // --------------------------------------------------------------------- cache
 namespace {
-std::atomic<int32_t> g_build_batch_nodes{0};  // test knob: nodes classified per batch (0: as many as 1 GiB of rows holds)
+constexpr uint64_t kOpenRoom = (uint64_t)1 << 23;  // (tile, context) of the level-1 kernels at a time
+std::atomic<int32_t> g_build_batch_nodes{0};  // test knob: nodes classified per batch (0: as many as 1 GiB of rows holds); level-1 tiles then go one by one
 }
 void xgm_debug_set_build_batch_nodes(int32_t nodes) { g_build_batch_nodes = nodes > 0 ? nodes : 0; }
 
@@ -990,31 +991,33 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
     for (int l = 0; l < c->levels; ++l) n_keys += n_k[l];
     const size_t n_slots = (size_t)(n_keys * (uint64_t)n_seg);
 
-    // the level-1 kernel's tiles: the pairs of a node in blocks, its rule's contexts in blocks
+    // The level-1 kernels' tiles: the pairs of a node in blocks, its rule's contexts in blocks.  The counting pass keeps
+    // what it found for every (up to 64 pairs, context) that it has to look at, 128 bytes each, if that cannot take more
+    // than 1 GiB; else the tiles are taken in parts and the writing pass walks again.
     std::vector<uint4> tiles;
+    std::vector<uint32_t> tile_parts;
+    uint64_t room = 0;  // (tile, context) of the largest part
     {
-      const uint32_t tp = context_tile_pairs(), tc = context_tile_contexts();
+      uint64_t in_part = 0;
+      const uint64_t most = g_build_batch_nodes > 0 ? kTileContexts : kOpenRoom;
       for (int32_t n = 0; n < N; ++n) {
         if (c->k_base_host[0][n] == kNoKey) continue;
         const uint32_t L = c->unc_count[n], m = (uint32_t)n_ctx(A.node_rule[n]);
-        for (uint32_t eb = 0; eb < L; eb += tp)
-          for (uint32_t ib = 0; ib < m; ib += tc)
-            tiles.push_back(make_uint4(node_off[n] + eb, std::min(tp, L - eb) | (std::min(tc, m - ib) << 16), ib, (uint32_t)n));
+        for (uint32_t eb = 0; eb < L; eb += kTilePairs)
+          for (uint32_t ib = 0; ib < m; ib += kTileContexts) {
+            const uint32_t n_tile = std::min(kTileContexts, m - ib);
+            if (in_part + n_tile > most) {
+              tile_parts.push_back((uint32_t)tiles.size());
+              in_part = 0;
+            }
+            in_part += n_tile;
+            room = std::max(room, in_part);
+            tiles.push_back(make_uint4(node_off[n] + eb, std::min(kTilePairs, L - eb) | (n_tile << 16), ib, (uint32_t)n));
+          }
       }
+      tile_parts.push_back((uint32_t)tiles.size());
     }
-    // the counting pass of level 1 keeps what it found for every (pair, context), 2 bytes each, unless that
-    // would take more than 1 GiB (then the writing pass walks again)
-    const bool keep_outcomes = n_items > 0 && n_items <= ((uint64_t)1 << 29);
-    std::vector<uint4> node_info;
-    if (keep_outcomes) {
-      node_info.assign((size_t)N, make_uint4(0u, 0u, 0u, 0u));
-      uint64_t at = 0;
-      for (int32_t n = 0; n < N; ++n) {
-        if (c->k_base_host[0][n] == kNoKey) continue;
-        node_info[n] = make_uint4((uint32_t)at, c->unc_count[n], node_off[n], 0u);
-        at += (uint64_t)c->unc_count[n] * n_ctx(A.node_rule[n]);
-      }
-    }
+    const bool keep_outcomes = !tiles.empty() && tile_parts.size() == 1;
     // where the base list of every node that has one begins
     std::vector<uint32_t> first((size_t)N);
     for (int32_t n = 0; n < N; ++n) first[n] = A.node_on_top[n] && c->unc_count[n] ? node_off[n] : kNoKey;
@@ -1037,7 +1040,7 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
       c->host.node_ctx_off = reinterpret_cast<const uint32_t*>(k + at_noff);
       c->host.node_ctx = reinterpret_cast<const uint32_t*>(k + at_nctx);
       const size_t at_rep = temp.add(rep), at_first = temp.add(first), at_tiles = temp.add(tiles), at_rule = temp.add(rule_info),
-                   at_forced = temp.add(forced_node), at_info = temp.add(node_info);
+                   at_forced = temp.add(forced_node);
       char* const t = arena.array<char>(temp.bytes());
       temp.send(t, arena, stream);
       d_rep = reinterpret_cast<const int32_t*>(t + at_rep);
@@ -1045,18 +1048,18 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
       args.tiles = reinterpret_cast<const uint4*>(t + at_tiles);
       args.rule_info = reinterpret_cast<const uint4*>(t + at_rule);
       args.forced_node = reinterpret_cast<const uint16_t*>(t + at_forced);
-      if (keep_outcomes) args.node_info = reinterpret_cast<const uint4*>(t + at_info);
     }
 
     // ---- base lists (every node's context-dependent tokens), then the entries of every (key, segment): counted.  What
     // the host has to know of it lies side by side: the length of all lists, the counters of the list kernels, the
     // equality of the rows; the counters and the counts begin at zero.
-    const size_t made_at = 16, equal_at = made_at + 16, counts_at = (equal_at + (size_t)N * 4 + 15) / 16 * 16;
+    const size_t open_at = 8, made_at = 16, equal_at = made_at + 16, counts_at = (equal_at + (size_t)N * 4 + 15) / 16 * 16;
     static_assert((kCtxLevels + 1) * 4 <= 16, "the counters of the list kernels");
     char* const d_found = static_cast<char*>(arena.alloc(counts_at + n_slots * 4));
     const char* const h_found = arena.pinned(counts_at);
     uint32_t* d_equal = reinterpret_cast<uint32_t*>(d_found + equal_at);
     uint32_t* d_counts = reinterpret_cast<uint32_t*>(d_found + counts_at);
+    args.n_open = reinterpret_cast<uint32_t*>(d_found + open_at);
     args.res_count = reinterpret_cast<uint32_t*>(d_found + made_at);
     HIP_OK(hipMemsetAsync(d_found, 0, counts_at + n_slots * 4, stream));
     launch_rows_equal(acc_id, N, dv.W, d_rep, d_equal, stream);
@@ -1074,6 +1077,8 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
     args.total = (uint32_t)n_base;
     args.exits = arena.array<uint32_t>((size_t)n_base);
     args.n_tiles = (uint32_t)tiles.size();
+    args.tile_parts = tile_parts.data();
+    args.open = arena.array<uint2>((size_t)room);
     // (a pair leaves at most about two records per level on the grammars measured: 0.3 to 1.9 for schema grammars, 0.7 for
     // a C-like one, 1.1 for a scripting one; the pass is run again with more room if this is not enough)
     args.res_cap = (uint32_t)std::min<uint64_t>(std::max<uint64_t>(2 * n_base, 1u << 17), 1u << 25);
@@ -1088,7 +1093,7 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
     }
     args.counts = d_counts;
     if (keep_outcomes) {
-      args.outcomes = arena.array<uint16_t>((size_t)n_items);
+      args.outcomes = arena.array<uint16_t>((size_t)room * 64);
       // (the deeper levels keep theirs per record: 16 bytes each)
       for (int l = 1; l < c->levels; ++l) args.deep_outcomes[l] = arena.array<uint4>(args.res_cap);
     }
@@ -1113,7 +1118,7 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
       for (int l = 0; l + 1 < c->levels; ++l) args.res[l] = arena.array<uint4>(args.res_cap);
       if (args.outcomes)
         for (int l = 1; l < c->levels; ++l) args.deep_outcomes[l] = arena.array<uint4>(args.res_cap);
-      HIP_OK(hipMemsetAsync(args.res_count, 0, 16, stream));
+      HIP_OK(hipMemsetAsync(args.n_open, 0, made_at + 16 - open_at, stream));
       HIP_OK(hipMemsetAsync(d_counts, 0, n_slots * 4, stream));
       launch_context_lists(tab, dv, args, false, stream);
       offsets();
@@ -1159,7 +1164,7 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
       launch_rows_to_lists(acc_id, dv.W, N, arena.upload(list_key, stream), n_seg, args.front, d_entries, nullptr, stream);
     }
     args.entries = d_entries;
-    if (!args.outcomes) HIP_OK(hipMemsetAsync(args.res_count, 0, 16, stream));
+    if (!args.outcomes) HIP_OK(hipMemsetAsync(args.n_open, 0, made_at + 16 - open_at, stream));
     launch_context_lists(tab, dv, args, true, stream);
     HIP_OK(hipGetLastError());
     cleanup_temps();  // (synchronises the stream)

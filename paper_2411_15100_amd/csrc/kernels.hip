@@ -765,7 +765,8 @@ __device__ __forceinline__ TokenRef load_token(const DevVocab& voc, int32_t id) 
 // context-dependent (node, token) pairs.  Kernels, tables staged as in the classify kernel:
 //   exit_positions_kernel  one thread per pair: the token is walked once more from the node to find the
 //                          positions at which it leaves the node's frame;
-//   context_level1_kernel  one thread per (pair, a few contexts of the node's rule): the rest of the token is
+//   context_open_kernel    which contexts of the node's rule have to be looked at for 64 pairs at all;
+//   context_level1_kernel  one lane per (pair, such a context): the rest of the token is
 //                          walked from the context node with nothing known below but the frames that this
 //                          context forces.  Accepted there: an entry of the (node, context) list.  Leaves all
 //                          those frames: a record for the next level;
@@ -777,7 +778,7 @@ __device__ __forceinline__ TokenRef load_token(const DevVocab& voc, int32_t id) 
 // stands in) are one level.  With levels of one frame the fill had to walk 48 K tokens over those frames where
 // an identifier ends in the C/SQL-like grammar (128256 tokens, one row: 950 us).
 // Most (pair, context) combinations end at the first byte of the rest, which the context node cannot
-// take.  All but the first kernel run twice: first they count the entries of every (key, segment), then,
+// take.  The walking ones but the first run twice: first they count the entries of every (key, segment), then,
 // with the offsets made from the counts, they write them.
 constexpr int kContextThreads = 768;
 constexpr uint32_t kContextsPerThread = 8;
@@ -924,91 +925,205 @@ struct ContextWork {
   }
 };
 
-// One workgroup per tile (see ContextListArgs::tiles): up to kContextThreads pairs of one node, up to
-// kContextsPerThread contexts of its rule.  All entries of a tile go to the lists of those few contexts, so the
-// counting pass counts them per (context, segment) in LDS and adds each counter to the global one once; the
-// writing pass does the same to reserve room in every list and then hands out the places from LDS - the
-// global counters of a list are touched once per workgroup instead of once per wave and segment.
-constexpr uint32_t kTileCounters = kContextsPerThread * kMaxSegs;
-template <bool WRITE, class Tab>
-__device__ __forceinline__ void context_level1_body(const Tab& T, const DevVocab& voc, const ContextListArgs& a, const uint4 tile,
-                                                    uint32_t* tile_counts) {
-  const uint32_t node = tile.w, i0 = tile.z, i1 = tile.z + (tile.y >> 16);
-  const uint32_t k1b = a.k_base[0][node];
-  if (threadIdx.x < (tile.y & 0xFFFFu)) {
-    const uint32_t e = tile.x + threadIdx.x;
-    const uint32_t id = a.base_ids[e], ex0 = a.exits[e];
-    const ContextWork<WRITE, Tab> w{T, voc, a, e, id, load_token(voc, (int32_t)id)};
-    const uint32_t cb = a.ctx_off[T.header(node).y >> 16];
-    const bool single0 = (ex0 & (ex0 - 1u)) == 0u;
-    const bool keep = !WRITE && a.outcomes != nullptr;
-    const uint4 info = keep ? a.node_info[node] : make_uint4(0u, 0u, 0u, 0u);
-    for (uint32_t i = i0; i < i1; ++i) {
-      uint32_t outcome = 0u;
-      w.step(1u, a.ctx_node[cb + i], k1b + i, ex0, single0, keep ? &outcome : nullptr,
-             WRITE ? nullptr : tile_counts + (i - i0) * (uint32_t)voc.n_seg);
-      if (keep) a.outcomes[(size_t)info.x + (size_t)i * info.y + (e - info.z)] = (uint16_t)outcome;
-    }
-  }
-  if (WRITE) return;
+// Level 1, first part: which contexts the pairs of a tile (see ContextListArgs::tiles) have to be walked on in at all.  A
+// wave takes a tile, a pair per lane, and looks at its contexts 64 at a time, a context per lane: pairs that leave the
+// node's frame at the same position, in front of the same byte, fare alike in every context whose frames cannot take that
+// byte, and in those where no path gets through what the rest of their tokens has in common.  The others are listed, an
+// (up to 64 pairs, context) each.
+// White space inside an object of a schema grammar has the context of every place where white space may stand: 17072 pairs
+// times 2188 contexts of the 44.4 M of the 11867-node grammar at 151936 tokens, of which 9.3 M get past the first byte.
+// Both parts and the writing pass: 20 + 111 + 15 us for that grammar, where workgroups of 768 pairs that walked every one
+// of 8 contexts took 381 + 63 (8333 times the staging of the tables, 89 MB of outcomes); JSON and 32000 tokens 8 + 20 + 5,
+// before 76 + 5; a scripting grammar and 128256 tokens 21 + 187 + 11, before 225 + 12; the C/SQL-like grammar, whose
+// pairs get through most contexts, 105 + 897 + 70, before 970 + 62.
+// A tile of few contexts is listed as it is (JSON 37 -> 8 us), and so is one of more than a few runs, which would be looked at
+// one after the other (schema grammar 58 us with any number of runs, 28 with 8, 20 with 4).
+constexpr uint32_t kManyContexts = 8;
+constexpr int kMostRuns = 4;
+__global__ __launch_bounds__(kContextThreads) void context_open_kernel(DevTables tab, DevVocab voc, ContextListArgs a, uint32_t tile0, uint32_t n_tiles) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  constexpr uint32_t kWaves = kContextThreads / 64;
+  constexpr int kChunks = kTileContexts / 64;
+  __shared__ uint32_t listed[kWaves], first_listed;
+  if (blockIdx.x * kWaves >= n_tiles) return;
+  stage_tables(tab, smem, kContextThreads);
   __syncthreads();
-  for (uint32_t t = threadIdx.x; t < (i1 - i0) * (uint32_t)voc.n_seg; t += kContextThreads) {
-    const uint32_t n = tile_counts[t];
-    if (n) atomicAdd(&a.counts[(a.key0[0] + k1b + i0 + t / (uint32_t)voc.n_seg) * (uint32_t)voc.n_seg + t % (uint32_t)voc.n_seg], n);
-  }
+  auto body = [&](const auto& T) {
+    const uint32_t wave = uniform(threadIdx.x >> 6), lane = threadIdx.x & 63u;
+    for (uint32_t t0 = blockIdx.x * kWaves; t0 < n_tiles; t0 += gridDim.x * kWaves) {
+      u64 open[kChunks] = {};
+      uint4 tile = make_uint4(0u, 0u, 0u, 0u);
+      if (t0 + wave < n_tiles) {
+        tile = a.tiles[tile0 + t0 + wave];
+        const uint32_t n_pairs = uniform(tile.y & 0xFFFFu), n_ctx = uniform(tile.y >> 16);
+        const uint32_t cb = a.ctx_off[T.header(tile.w).y >> 16] + tile.z;
+        TokenRef t{make_uint4(0u, 0u, 0u, 0u), voc.bytes, 0};
+        uint32_t ex = 0u;
+        const bool look = n_ctx >= kManyContexts;
+        if (look && lane < n_pairs) {
+          t = load_token(voc, (int32_t)a.base_ids[tile.x + lane]);
+          ex = a.exits[tile.x + lane];
+        }
+        // where the token goes on, if there is only one such place and its byte is among those that the lane holds
+        const bool one_exit = ex != 0u && (ex & (ex - 1u)) == 0u && ex < (1u << 15);
+        const uint32_t k = one_exit ? (uint32_t)__ffs((int)ex) - 1u : 0u;
+        const uint32_t tag = k << 8 | token_byte(t.tk, voc.bytes, (int)k);
+        u64 others = __ballot(lane < n_pairs && !one_exit);
+        int runs = 0;
+        for (u64 left = __ballot(lane < n_pairs && one_exit); left && !others;) {
+          const int lead = __ffsll((long long)left) - 1;
+          auto of = [&](uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)v, lead); };
+          const uint32_t lead_tag = of(tag), c = lead_tag & 0xFFu;
+          const u64 run = __ballot(lane < n_pairs && one_exit && tag == lead_tag);
+          left &= ~run;
+          if (++runs > kMostRuns) { others = 1ull; break; }
+          const uint4 pre = make_uint4(of(t.tk.x), of(t.tk.y), of(t.tk.z), of(t.tk.w));
+          // what the tokens of the run have in common with the first of them
+          uint32_t same = 15u;
+          if ((run >> lane) & 1ull) {
+            const uint32_t d0 = t.tk.x ^ pre.x, d1 = t.tk.y ^ pre.y, d2 = t.tk.z ^ pre.z, d3 = (t.tk.w ^ pre.w) | 0xFF000000u;
+            same = (uint32_t)(d0 ? __ffs((int)d0) - 1 : d1 ? __ffs((int)d1) + 31 : d2 ? __ffs((int)d2) + 63 : __ffs((int)d3) + 95) / 8u;
+            same = min(same, (uint32_t)t.len);
+          }
+#pragma unroll
+          for (uint32_t d = 1; d < 64u; d <<= 1) same = min(same, (uint32_t)__shfl_xor((int)same, d, 64));
+          same = uniform(same);
+#pragma unroll
+          for (int q = 0; q < kChunks; ++q) {
+            if (q * 64u >= n_ctx) break;
+            const uint32_t i = q * 64u + lane;
+            bool walk = false;
+            uint32_t r = 0u;
+            if (i < n_ctx) {
+              r = a.ctx_node[cb + i];
+              const uint2 h = T.header(r);
+              walk = T.can_start(r, c) || ((h.y & 1u) && T.can_follow(h, c));
+            }
+            const u64 needs = __ballot(walk);
+            if ((needs & (needs - 1ull)) && same > (lead_tag >> 8) + 1u && __popcll(run) >= kPrefixTokens) {
+              if (walk) {
+                const uint4 info = a.rule_info[T.header(r).y >> 16];
+                walk = walk_token<true, true>(T, pre, voc.bytes, (int)same, r, (const XGM_GLOBAL uint16_t*)(a.forced_node + info.x), info.y + 1u,
+                                              nullptr, info.z, (int)(lead_tag >> 8)) != kReject;
+              }
+            }
+            open[q] |= __ballot(walk);
+          }
+        }
+        if (others) {
+#pragma unroll
+          for (int q = 0; q < kChunks; ++q)
+            if (q * 64u < n_ctx) open[q] = n_ctx - q * 64u >= 64u ? ~0ull : (1ull << (n_ctx - q * 64u)) - 1ull;
+        }
+      }
+      uint32_t n = 0u;
+#pragma unroll
+      for (int q = 0; q < kChunks; ++q) n += (uint32_t)__popcll(open[q]);
+      if (lane == 0u) listed[wave] = n;
+      __syncthreads();
+      uint32_t at = 0u, all = 0u;
+      for (uint32_t w = 0; w < kWaves; ++w) {
+        if (w < wave) at += listed[w];
+        all += listed[w];
+      }
+      if (threadIdx.x == 0u && all) first_listed = atomicAdd(a.n_open, all);
+      __syncthreads();
+      at += first_listed;
+#pragma unroll
+      for (int q = 0; q < kChunks; ++q) {
+        if ((open[q] >> lane) & 1ull)
+          a.open[at + (uint32_t)__popcll(open[q] & ((1ull << lane) - 1ull))] = make_uint2(tile.x, (tile.y & 0xFFFFu) - 1u | (tile.z + q * 64u + lane) << 6);
+        at += (uint32_t)__popcll(open[q]);
+      }
+      __syncthreads();
+    }
+  };
+  if (small_sections_staged(tab)) body(LdsTabT<true>(tab, smem));
+  else body(LdsTab(tab, smem));
 }
+
+// Second part: the listed (64 pairs, context), a wave for each (for two neighbours in the list, mostly of the same pairs, if
+// there are more than the chip has room for: C/SQL-like grammar 958 us with one, 897 with two, 1064 with four, 1329 with
+// eight).  All entries of a wave go to the lists of one key: they are counted
+// per segment in LDS and added to the global counters once.
+constexpr uint32_t kOpenBlocks = 512;  // the tables are staged once per place on the chip
 template <bool WRITE>
 __global__ __launch_bounds__(kContextThreads) void context_level1_kernel(DevTables tab, DevVocab voc, ContextListArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ uint32_t tile_counts[WRITE ? 1 : kTileCounters];
-  const uint4 tile = a.tiles[blockIdx.x];
-  if (!WRITE)
-    for (uint32_t t = threadIdx.x; t < kTileCounters; t += kContextThreads) tile_counts[t] = 0u;
+  constexpr uint32_t kWaves = kContextThreads / 64;
+  __shared__ uint32_t counts[WRITE ? 1 : kWaves][kMaxSegs];
+  const uint32_t n_open = *a.n_open;
+  if (blockIdx.x >= n_open) return;
   stage_tables(tab, smem, kContextThreads);
+  if (!WRITE)
+    for (uint32_t t = threadIdx.x; t < kWaves * kMaxSegs; t += kContextThreads) counts[t / kMaxSegs][t % kMaxSegs] = 0u;
   __syncthreads();
-  if (small_sections_staged(tab)) context_level1_body<WRITE>(LdsTabT<true>(tab, smem), voc, a, tile, tile_counts);
-  else context_level1_body<WRITE>(LdsTab(tab, smem), voc, a, tile, tile_counts);
+  auto body = [&](const auto& T) {
+    const uint32_t wave = uniform(threadIdx.x >> 6), lane = threadIdx.x & 63u, n_seg = (uint32_t)voc.n_seg;
+    uint32_t* const mine = WRITE ? nullptr : counts[WRITE ? 0 : wave];
+    const uint32_t per = n_open > 2u * kOpenBlocks * kWaves ? 2u : 1u;
+    uint32_t loaded = 0xFFFFFFFFu, id = 0u, ex = 0u, node = 0u;
+    TokenRef t{make_uint4(0u, 0u, 0u, 0u), voc.bytes, 0};
+    for (uint32_t q0 = (wave * gridDim.x + blockIdx.x) * per; q0 < n_open; q0 += gridDim.x * kWaves * per)
+      for (uint32_t q = q0; q < min(q0 + per, n_open); ++q) {
+        const uint2 item = a.open[q];
+        const uint32_t e0 = uniform(item.x), n_pairs = (uniform(item.y) & 63u) + 1u, i = uniform(item.y) >> 6;
+        if (e0 != loaded) {
+          node = uniform(a.base_node[e0]);
+          if (lane < n_pairs) {
+            id = a.base_ids[e0 + lane];
+            ex = a.exits[e0 + lane];
+            t = load_token(voc, (int32_t)id);
+          }
+          loaded = e0;
+        }
+        const uint32_t r = uniform(a.ctx_node[a.ctx_off[T.header(node).y >> 16] + i]), key = a.k_base[0][node] + i;
+        uint32_t outcome = 0u;
+        if (lane < n_pairs) {
+          const ContextWork<WRITE, std::decay_t<decltype(T)>> w{T, voc, a, e0 + lane, id, t};
+          w.step(1u, r, key, ex, (ex & (ex - 1u)) == 0u, &outcome, mine);
+        }
+        if (WRITE) continue;
+        if (a.outcomes) a.outcomes[(size_t)q * 64u + lane] = (uint16_t)outcome;
+        if (__ballot(outcome != 0u))
+          for (uint32_t s = lane; s < n_seg; s += 64u) {
+            const uint32_t n = mine[s];
+            if (n) {
+              atomicAdd(&a.counts[(size_t)(a.key0[0] + key) * n_seg + s], n);
+              mine[s] = 0u;
+            }
+          }
+      }
+  };
+  if (small_sections_staged(tab)) body(LdsTabT<true>(tab, smem));
+  else body(LdsTab(tab, smem));
 }
-// The writing pass of level 1 when the counting pass kept its outcomes: the same tiles, no walks, no tables.
-__global__ __launch_bounds__(kContextThreads) void context_level1_write_kernel(DevVocab voc, ContextListArgs a) {
-  __shared__ uint32_t next[2 * kTileCounters];   // per (context, segment, accepted or walk entry): entries, then places handed out
-  __shared__ uint32_t base[2 * kTileCounters];   // where the workgroup's entries of that kind begin in the list
-  const uint4 tile = a.tiles[blockIdx.x];
-  const uint32_t node = tile.w, i0 = tile.z, n_ctx = tile.y >> 16, n_seg = (uint32_t)voc.n_seg;
-  const uint32_t k1b = a.key0[0] + a.k_base[0][node] + i0;
-  const bool active = threadIdx.x < (tile.y & 0xFFFFu);
-  for (uint32_t t = threadIdx.x; t < 2u * n_ctx * n_seg; t += kContextThreads) next[t] = 0u;
-  __syncthreads();
-  uint32_t code[kContextsPerThread], id = 0u, seg = 0u;
-  if (active) {
-    const uint32_t e = tile.x + threadIdx.x;
-    const uint4 info = a.node_info[node];
-    id = a.base_ids[e];
-    seg = id / (uint32_t)kSegTokens;
-#pragma unroll
-    for (uint32_t q = 0; q < kContextsPerThread; ++q) {
-      code[q] = q < n_ctx ? a.outcomes[(size_t)info.x + (size_t)(i0 + q) * info.y + (e - info.z)] : 0u;
-      if (code[q]) atomicAdd(&next[2u * (q * n_seg + seg) + ((code[q] & 0xFFu) - 1u == kEntryAccepted ? 0u : 1u)], 1u);
+// The writing pass of level 1 when the counting pass kept its outcomes: the same list, no walks, no tables.  A wave
+// reserves room in every list once and hands out the places from LDS.
+constexpr int kOpenWriteThreads = 256;
+__global__ __launch_bounds__(kOpenWriteThreads) void context_level1_write_kernel(DevVocab voc, ContextListArgs a) {
+  constexpr uint32_t kWaves = kOpenWriteThreads / 64;
+  __shared__ uint32_t next[kWaves][2 * kMaxSegs];  // per segment, accepted and walk entries: how many, then where the next one goes
+  const uint32_t wave = uniform(threadIdx.x >> 6), lane = threadIdx.x & 63u, n_seg = (uint32_t)voc.n_seg, n_open = *a.n_open;
+  uint32_t* const mine = next[wave];
+  for (uint32_t q = blockIdx.x * kWaves + wave; q < n_open; q += gridDim.x * kWaves) {
+    const uint32_t code = a.outcomes[(size_t)q * 64u + lane];
+    if (__ballot(code != 0u) == 0ull) continue;
+    const uint2 item = a.open[q];
+    const uint32_t e0 = uniform(item.x), i = uniform(item.y) >> 6;
+    const uint32_t key = a.key0[0] + a.k_base[0][a.base_node[e0]] + i;
+    const uint32_t id = code ? a.base_ids[e0 + lane] : 0u, kind = (code & 0xFFu) - 1u;
+    const uint32_t at = 2u * (id / (uint32_t)kSegTokens) + (kind == kEntryAccepted ? 0u : 1u);
+    for (uint32_t s = lane; s < 2u * n_seg; s += 64u) mine[s] = 0u;
+    if (code) atomicAdd(&mine[at], 1u);
+    for (uint32_t s = lane; s < 2u * n_seg; s += 64u) {
+      const uint32_t n = mine[s];
+      if (n) {
+        const size_t slot = (size_t)key * n_seg + (s >> 1);
+        mine[s] = (s & 1u) ? atomicSub(&a.back[slot], n) - n : atomicAdd(&a.front[slot], n);
+      }
     }
-  }
-  __syncthreads();
-  for (uint32_t t = threadIdx.x; t < 2u * n_ctx * n_seg; t += kContextThreads) {
-    const uint32_t n = next[t];
-    if (n) {
-      const uint32_t slot = (k1b + (t >> 1) / n_seg) * n_seg + (t >> 1) % n_seg;
-      base[t] = (t & 1u) ? atomicSub(&a.back[slot], n) - n : atomicAdd(&a.front[slot], n);
-      next[t] = 0u;
-    }
-  }
-  __syncthreads();
-  if (active) {
-#pragma unroll
-    for (uint32_t q = 0; q < kContextsPerThread; ++q) {
-      if (!code[q]) continue;
-      const uint32_t kind = (code[q] & 0xFFu) - 1u, pos = code[q] >> 8;
-      const uint32_t t = 2u * (q * n_seg + seg) + (kind == kEntryAccepted ? 0u : 1u);
-      a.entries[base[t] + atomicAdd(&next[t], 1u)] = id | (pos << kEntryPosShift) | (kind << kEntryKindShift);
-    }
+    if (code) a.entries[atomicAdd(&mine[at], 1u)] = id | ((code >> 8) << kEntryPosShift) | (kind << kEntryKindShift);
   }
 }
 
@@ -2382,12 +2497,12 @@ void launch_exit_positions(const DevTables& tab, const DevVocab& voc, const Cont
 void launch_context_lists(const DevTables& tab, const DevVocab& voc, const ContextListArgs& args, bool write, hipStream_t stream) {
   if (args.total == 0 || args.n_tiles == 0) return;
   const DevTables st = staged_for(tab, kContextLdsBudget);
-  const dim3 g1(args.n_tiles), g2(1024);
+  const dim3 g2(1024);
   if (write && args.outcomes) {
     // Level 1 from the kept outcomes; its records for level 2 are still there from the counting pass, and so
     // are the deeper levels' records if their outcomes were kept too (levels that walk again make the records
     // of the next level again: those counts start at zero).
-    hipLaunchKernelGGL(context_level1_write_kernel, g1, dim3(kContextThreads), 0, stream, voc, args);
+    hipLaunchKernelGGL(context_level1_write_kernel, dim3(2048), dim3(kOpenWriteThreads), 0, stream, voc, args);
     bool deep = true;  // all deeper levels from kept outcomes, or all of them by walking again
     for (uint32_t level = 2; level <= (uint32_t)kCtxLevels && args.k_base[level - 1] != nullptr; ++level)
       deep = deep && args.deep_outcomes[level - 1] != nullptr;
@@ -2398,15 +2513,21 @@ void launch_context_lists(const DevTables& tab, const DevVocab& voc, const Conte
     }
     return;
   }
-  if (write) hipLaunchKernelGGL(context_level1_kernel<true>, g1, dim3(kContextThreads), st.stage_bytes, stream, st, voc, args);
-  else hipLaunchKernelGGL(context_level1_kernel<false>, g1, dim3(kContextThreads), st.stage_bytes, stream, st, voc, args);
+  // the tiles whose contexts fit the list, if all of them have to be listed, at a time
+  for (uint32_t tile0 = 0, k = 0; tile0 < args.n_tiles; ++k) {
+    const uint32_t tile1 = args.tile_parts[k];
+    if (tile0 > 0) (void)hipMemsetAsync(args.n_open, 0, 4, stream);
+    const uint32_t waves = kContextThreads / 64, blocks = std::min((tile1 - tile0 + waves - 1) / waves, kOpenBlocks);
+    hipLaunchKernelGGL(context_open_kernel, dim3(blocks), dim3(kContextThreads), st.stage_bytes, stream, st, voc, args, tile0, tile1 - tile0);
+    auto kernel = write ? context_level1_kernel<true> : context_level1_kernel<false>;
+    hipLaunchKernelGGL(kernel, dim3(kOpenBlocks), dim3(kContextThreads), st.stage_bytes, stream, st, voc, args);
+    tile0 = tile1;
+  }
   for (uint32_t level = 2; level <= (uint32_t)kCtxLevels && args.k_base[level - 1] != nullptr; ++level) {
     if (write) hipLaunchKernelGGL(context_deeper_kernel<true>, g2, dim3(kContextThreads), st.stage_bytes, stream, st, voc, args, level);
     else hipLaunchKernelGGL(context_deeper_kernel<false>, g2, dim3(kContextThreads), st.stage_bytes, stream, st, voc, args, level);
   }
 }
-uint32_t context_tile_pairs() { return (uint32_t)kContextThreads; }
-uint32_t context_tile_contexts() { return kContextsPerThread; }
 
 void launch_patch_classes(const DevVocab& voc, const uint32_t* items, int32_t n_items, uint32_t* acc_rank,
                           uint32_t* unc_rank, uint32_t* plain_rank, hipStream_t stream) {

@@ -333,14 +333,16 @@ void launch_rows_to_lists(const uint32_t* rows, int32_t row_words, int32_t n, co
 // write = true: the entries are written, accepted ones upwards from front[slot], walk entries downwards from
 // back[slot] (both arrays are advanced).  Levels whose k_base is null are not kept: tokens that would need
 // them become walk entries of the level above.
-// tiles: the work of the level-1 kernel, one workgroup each: x = first pair, y = pairs (at most
-// context_tile_pairs(), all of one node) | contexts << 16 (at most context_tile_contexts()), z = first
-// context, w = the node.  res[l] / res_cap / res_count[l]: records of the (pair, key of level l + 1) that
+// tiles: the work of the level-1 kernels: x = first pair, y = pairs (at most kTilePairs, all of one node) | contexts
+// << 16 (at most kTileContexts), z = first context, w = the node.  What of them has to be walked is listed in `open`:
+// x = first pair, y = pairs - 1 | context << 6; it has room for all (tile, context) of the tiles of one part.
+// res[l] / res_cap / res_count[l]: records of the (pair, key of level l + 1) that
 // leave one more frame, made by the kernel of level l + 1 for the kernel of level l + 2 - one record for
-// every chunk of context_tile_contexts() contexts of the rule whose frame comes next: x = pair, y = number of
+// every chunk of kContextsPerThread contexts of the rule whose frame comes next: x = pair, y = number of
 // the key among its level's keys, z = the positions at which the frame is left, w = that rule | the way so
 // far is unique << 16 | chunk << 17; a record that does not fit is dropped and counted all the same (the
 // caller then runs the pass again with more room).
+constexpr uint32_t kTilePairs = 64, kTileContexts = 256;
 struct ContextListArgs {
   const uint16_t* base_node;
   const uint32_t* base_ids;
@@ -348,6 +350,9 @@ struct ContextListArgs {
   uint32_t* exits;             // [total]
   const uint4* tiles;
   uint32_t n_tiles;
+  const uint32_t* tile_parts;  // (host) where the parts of the tiles end, the last at n_tiles
+  uint2* open;
+  uint32_t* n_open;            // (zero before the counting pass, and before a writing pass that walks again)
   uint4* res[kCtxLevels];      // (the last one is not used)
   uint32_t res_cap;
   uint32_t* res_count;         // [kCtxLevels + 1], zero before the counting pass (and before a writing pass that walks again);
@@ -363,11 +368,9 @@ struct ContextListArgs {
   uint32_t* front;             // [n_keys * n_seg]   write = true
   uint32_t* back;              // [n_keys * n_seg]   write = true
   uint32_t* entries;
-  // What the level-1 kernel found for every (pair, context) when it counted, kept so that the writing pass
-  // need not walk again (null: it walks again).  node_info[n] = {first outcome of node n, its pairs L, its
-  // first pair, 0}; the outcome of pair e and context i of node n is outcomes[info.x + i * L + (e - info.z)]:
-  // 0 = no entry, else (kind + 1) | pos << 8.
-  const uint4* node_info;
+  // What the level-1 kernel found for every pair and context in `open` when it counted, 64 of them each, kept so that the
+  // writing pass need not walk again (null: it walks again; all tiles are one part otherwise): 0 = no entry, else
+  // (kind + 1) | pos << 8.
   uint16_t* outcomes;
   // The same for the deeper levels: deep_outcomes[l][r] holds the outcomes (8 x 16 bits, coded as above) of
   // record r of res[l - 1], that is of level l + 1, for the contexts of the record's chunk; null: the writing
@@ -390,8 +393,6 @@ void launch_slot_offsets(const SlotCounts& counts, unsigned long long* block_sum
                          unsigned long long* total, hipStream_t stream);
 void launch_exit_positions(const DevTables& tab, const DevVocab& voc, const ContextListArgs& args, hipStream_t stream);
 void launch_context_lists(const DevTables& tab, const DevVocab& voc, const ContextListArgs& args, bool write, hipStream_t stream);
-uint32_t context_tile_pairs();
-uint32_t context_tile_contexts();
 // set / clear single bits of rank-space rows: items = (node - node0, rank, class)
 void launch_patch_classes(const DevVocab& voc, const uint32_t* items, int32_t n_items,
                           uint32_t* acc_rank, uint32_t* unc_rank, uint32_t* plain_rank, hipStream_t stream);

@@ -494,6 +494,35 @@ def test_builds_of_all_kinds_give_the_same_cache(xgm, wl, family, V):
     assert np.array_equal(masks[0], masks[1]) and np.array_equal(masks[0], masks[2])
 
 
+# The list kernels take the pairs of a node 64 at a time and the contexts of its rule 64 and 256 at a time: a rule in m places,
+# as many tokens that begin with the same byte and go on to the next, or to the end and to what follows it.
+@pytest.mark.parametrize("m", [1, 7, 8, 9, 63, 64, 65, 257])
+@pytest.mark.parametrize("pairs", [1, 16, 63, 64, 65, 300])
+def test_contexts_and_pairs_of_all_counts(xgm, wl, m, pairs):
+    text = 'root ::= item (";" item)*\nws ::= " "+\nitem ::= ' + " | ".join(f'"{rule_word(k)}" ws "{rule_word(5 * k)}" ws' for k in range(m))
+    text += ' | "(" ws root ")"'
+    toks = [bytes([c]) for c in b"();. abcdefghij"] + [b" " * k for k in (2, 3, 17)] + [b" ;", b" );", b" ) ;"]
+    for k in range(pairs):
+        toks += [p + rule_word(5 * k).encode() for p in (b" ", b"   ", b" ;", b" " * 14)]
+        toks += [b" " + rule_word(5 * k)[:2].encode(), b" " + rule_word(5 * k).encode() + b" ;" + rule_word(k).encode(),
+                 b" )" + rule_word(k).encode()]
+    toks = list(dict.fromkeys(toks)) + [b""]
+    vocab = Vocab(np.frombuffer(b"".join(toks), dtype=np.uint8).copy(), np.cumsum([0] + [len(t) for t in toks]).astype(np.int64),
+                  np.array([len(toks) - 1], dtype=np.int32))
+    cache, og = xgm.Cache(xgm.Grammar(text, "root"), wl.make_xgm_vocab(vocab)), oracle.Grammar(text, "root")
+    ms, want = [], []
+    for k in sorted({0, 1, 7, 8, 62, 63, 64, 65, 255, 256, m - 1} & set(range(m))):
+        for start in (rule_word(k) + " ", rule_word(k) + " " + rule_word(5 * k) + " ", "( (  " + rule_word(k) + " " + rule_word(5 * k) + "  "):
+            ms.append(xgm.Matcher(cache=cache))
+            ms[-1].accept_bytes(start.encode())
+            om = oracle.EarleyMatcher(og)
+            assert om.advance(start.encode())
+            want.append(om.mask(vocab))
+    d_mask = torch.full((len(ms), xgm.bitmask_words(len(toks))), -1, dtype=torch.int32, device="cuda")
+    xgm.fill_next_token_bitmask(ms, d_mask.data_ptr(), _stream())
+    assert np.array_equal(d_mask.cpu().numpy(), oracle.pack_bitmask(np.stack(want)))
+
+
 # Few walks of a row go to waves, unless a cache of the batch (the markup grammar's) is known to walk to the limits.
 @pytest.mark.parametrize("V", [4096, 32000])
 def test_walks_by_waves_and_by_lanes(xgm, wl, V):
