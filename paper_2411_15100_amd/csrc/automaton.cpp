@@ -261,6 +261,7 @@ class Parser {
   const std::vector<Token>& t_;
   Nfa& nfa_;
   size_t p_ = 0;
+  std::pair<std::string_view, int> last_of_length_[16] = {};  // (a name is never empty)
 
   bool at_rule_head() const { return t_[p_].kind == T_IDENT && t_[p_ + 1].kind == T_DEFINE; }
   Frag alternatives() {
@@ -331,10 +332,16 @@ class Parser {
       }
       case T_IDENT: {
         ++p_;
-        auto it = rule_index_.find(lexed_.text_of(tk));
-        if (it == rule_index_.end()) throw Failure(XGM_ERR_UNDEFINED_RULE, "grammar: rule '" + std::string(lexed_.text_of(tk)) + "' is not defined");
+        // (a few names, white space above all, are most of the references: the last one of each length is remembered)
+        const std::string_view name = lexed_.text_of(tk);
+        std::pair<std::string_view, int>& last = last_of_length_[name.size() % 16];
+        if (last.first != name) {
+          auto it = rule_index_.find(name);
+          if (it == rule_index_.end()) throw Failure(XGM_ERR_UNDEFINED_RULE, "grammar: rule '" + std::string(name) + "' is not defined");
+          last = *it;
+        }
         int in = nfa_.add(), out = nfa_.add();
-        nfa_.ref(in, it->second, out);
+        nfa_.ref(in, last.second, out);
         return {in, out};
       }
       case T_LP: {
@@ -395,7 +402,8 @@ class Parser {
 // rule to rule.  A new schema is on the path of a request's first token: the
 // 36 KB grammar of the largest synthetic schema (11867 nodes) took 84 ms to
 // compile with a set or map per state and rounds over all states until nothing
-// changed, and takes 3.9 ms this way (same machine).
+// changed, 2.1 ms this way (another machine), and 1.7 with nothing hashed for states inside a
+// literal and for rules whose states cannot be equivalent.
 
 // Finds equal integer sequences: intern() gives every distinct one a number, in the order of first appearance.
 class SequenceTable {
@@ -420,11 +428,16 @@ class SequenceTable {
         return id;
       }
     }
-    const int id = (int)size();
+    const int id = append(p, n);
     slots_[at] = id + 1;
+    if (is_new) *is_new = true;
+    return id;
+  }
+  // a sequence that intern() will never be asked for
+  int append(const int* p, size_t n) {
+    const int id = (int)size();
     pool_.insert(pool_.end(), p, p + n);
     off_.push_back((uint32_t)pool_.size());
-    if (is_new) *is_new = true;
     return id;
   }
 
@@ -439,7 +452,7 @@ class SequenceTable {
   }
   void grow() {
     slots_.assign(slots_.size() * 2, 0);
-    for (int id = 0; id < (int)size(); ++id) {
+    for (int id = 0; id < (int)size(); ++id) {  // (appended ones too: nothing is equal to them)
       size_t at = hash(begin(id), (size_t)(end(id) - begin(id))) & (slots_.size() - 1);
       while (slots_[at]) at = (at + 1) & (slots_.size() - 1);
       slots_[at] = id + 1;
@@ -527,7 +540,7 @@ std::vector<char> derivable(const Nfa& nfa, const std::vector<int>& start, const
 class Determinizer {
  public:
   Determinizer(const Nfa& nfa, const std::vector<char>& productive, const std::vector<char>& nullable)
-      : nfa_(nfa), productive_(productive), nullable_(nullable), mark_(nfa.size(), 0u), single_(nfa.size(), -1) {}
+      : nfa_(nfa), productive_(productive), nullable_(nullable), mark_(nfa.size(), 0u), single_(nfa.size(), -1), alone_(nfa.size(), -1) {}
   void run(int start, int accept, Dfa& d) {
     d.clear();
     sets_.clear(64);
@@ -574,7 +587,7 @@ class Determinizer {
       s.r1 = (uint32_t)d.r.size();
       d.s.push_back(s);
     }
-    for (int q : touched_) single_[q] = -1;
+    for (int q : touched_) single_[q] = alone_[q] = -1;
   }
 
  private:
@@ -582,33 +595,46 @@ class Determinizer {
   // to nullable rules skipped); only states with something of their own to say are kept.
   int closed(const int* seed, size_t n) {
     if (n == 1 && single_[*seed] >= 0) return single_[*seed];
-    ++stamp_;
     set_.clear();
-    work_.clear();
-    for (size_t k = 0; k < n; ++k)
-      if (mark_[seed[k]] != stamp_) { mark_[seed[k]] = stamp_; work_.push_back(seed[k]); }
-    while (!work_.empty()) {
-      const int q = work_.back();
-      work_.pop_back();
-      bool says = q == accept_;
-      for (auto& e : nfa_.out(q)) {
-        if (e.kind == 0 || (e.kind == 2 && productive_[e.rule] && nullable_[e.rule])) {
-          if (mark_[e.to] != stamp_) { mark_[e.to] = stamp_; work_.push_back(e.to); }
+    if (n == 1 && goes_nowhere(*seed)) set_.push_back(*seed);  // (inside a literal)
+    else {
+      ++stamp_;
+      work_.clear();
+      for (size_t k = 0; k < n; ++k)
+        if (mark_[seed[k]] != stamp_) { mark_[seed[k]] = stamp_; work_.push_back(seed[k]); }
+      while (!work_.empty()) {
+        const int q = work_.back();
+        work_.pop_back();
+        bool says = q == accept_;
+        for (auto& e : nfa_.out(q)) {
+          if (skips(e) && mark_[e.to] != stamp_) { mark_[e.to] = stamp_; work_.push_back(e.to); }
+          says = says || e.kind == 1 || (e.kind == 2 && productive_[e.rule]);
         }
-        says = says || e.kind == 1 || (e.kind == 2 && productive_[e.rule]);
+        if (says) set_.push_back(q);
       }
-      if (says) set_.push_back(q);
+      std::sort(set_.begin(), set_.end());
     }
-    std::sort(set_.begin(), set_.end());
-    const int id = sets_.intern(set_.data(), set_.size());
+    int id;
+    if (set_.size() == 1) {  // most are: found by their state, not by their hash
+      int& a = alone_[set_[0]];
+      if (a < 0) { a = sets_.append(set_.data(), 1); touched_.push_back(set_[0]); }
+      id = a;
+    } else {
+      id = sets_.intern(set_.data(), set_.size());
+    }
     if (n == 1) { single_[*seed] = id; touched_.push_back(*seed); }
     return id;
+  }
+  bool skips(const NEdge& e) const { return e.kind == 0 || (e.kind == 2 && productive_[e.rule] && nullable_[e.rule]); }
+  bool goes_nowhere(int q) const {
+    const auto out = nfa_.out(q);
+    return out.last - out.first == 1 && out.first->kind == 1;
   }
   struct Bytes { int lo, hi, to; };
   const Nfa& nfa_;
   const std::vector<char>&productive_, &nullable_;
   std::vector<uint32_t> mark_;
-  std::vector<int> single_, touched_;  // the closure of a single state of the current rule
+  std::vector<int> single_, alone_, touched_;  // of a single state of the current rule: its closure; the set of it alone
   uint32_t stamp_ = 0;
   int accept_ = -1;
   SequenceTable sets_;
@@ -623,6 +649,7 @@ class Minimizer {
   Dfa run(const Dfa& d) {
     n_ = (int)d.s.size();
     d_ = &d;
+    if (all_heights_differ()) return d;
     // predecessors
     pred_.fill(n_, [&](auto put) {
       for (int q = 0; q < n_; ++q) {
@@ -664,7 +691,39 @@ class Minimizer {
   }
 
  private:
-  // A rule without loops of its own (an object of a schema, as a rule): every state is looked at once, after all
+  // If there are no loops and no two states have the same longest way to an accepting one, all states are alive and no two
+  // are equivalent (an object of a schema: its members come one after the other).
+  bool all_heights_differ() {
+    constexpr int kNew = -2, kOpen = -1;
+    height_.assign(n_, kNew);
+    seen_.assign(n_, 0);
+    std::vector<int>& work = dirty_;
+    work.assign(1, 0);  // (every state is reached from the start)
+    while (!work.empty()) {
+      const int q = work.back();
+      const DState& s = d_->s[q];
+      const bool entered = height_[q] == kOpen;
+      if (height_[q] >= 0) { work.pop_back(); continue; }
+      height_[q] = kOpen;
+      int h = s.final_ ? 0 : -1;
+      bool waits = false, loop = false;
+      auto edge = [&](int to) {
+        if (height_[to] >= 0) h = std::max(h, height_[to] + 1);
+        else if (height_[to] == kOpen) loop = true;
+        else { work.push_back(to); waits = true; }
+      };
+      for (uint32_t k = s.b0; k < s.b1; ++k) edge(d_->b[k].to);
+      for (uint32_t k = s.r0; k < s.r1; ++k) edge(d_->r[k].to);
+      if (loop || (entered && waits)) return false;
+      if (waits) continue;
+      if (h < 0 || seen_[h]) return false;
+      seen_[h] = 1;
+      height_[q] = h;
+      work.pop_back();
+    }
+    return true;
+  }
+  // A rule without loops of its own: every state is looked at once, after all
   // its successors, and states with equal signatures are one block.  False if there is a loop.
   bool hash_upwards() {
     block_.assign(n_, -1);
@@ -807,8 +866,8 @@ class Minimizer {
   int n_ = 0;
   const Dfa* d_ = nullptr;
   Buckets pred_;
-  std::vector<char> alive_, is_dirty_;
-  std::vector<int> block_, sizes_, head_, next_, prev_, dirty_, moved_, sig_, pending_, group_size_, group_of_, number_;
+  std::vector<char> alive_, is_dirty_, seen_;
+  std::vector<int> block_, sizes_, head_, next_, prev_, dirty_, moved_, sig_, pending_, group_size_, group_of_, number_, height_;
   SequenceTable table_;
 };
 
@@ -1126,13 +1185,17 @@ Automaton compile_grammar(const std::string& text, const std::string& root) {
   std::vector<AltList> lists{{-1, 0u, 0, -1}};
   SequenceTable list_ids;
   list_ids.clear(1024);
+  uint32_t last_single = 0u;  // (a reference has the same alternative for all bytes that its callee can start with)
+  int last_single_id = -1;
   auto extend = [&](int list, uint32_t alt) {
+    if (list == 0 && last_single_id >= 0 && alt == last_single) return last_single_id;
     for (int k = list; k > 0; k = lists[k].before)
       if (lists[k].alt == alt) return list;
     const int key[2] = {list, (int)alt};
     bool is_new = false;
     const int id = list_ids.intern(key, 2, &is_new) + 1;
     if (is_new) lists.push_back({list, alt, lists[list].length + 1, -1});
+    if (list == 0) { last_single = alt; last_single_id = id; }
     return id;
   };
   // what node n does with the byte classes that lead anywhere: (class, list) pairs by class
