@@ -876,26 +876,35 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
     // up: which context of a rule a frame sits on)
     std::vector<uint32_t> ctx_off(A.rule_names.size() + 1, 0);
     std::vector<uint16_t> ctx_node;
-    std::vector<uint32_t> node_ctx_off((size_t)N + 1, 0), node_ctx;
+    std::vector<uint2> node_ctx_first((size_t)N, make_uint2(kNoKey, kNoKey));
+    std::vector<uint32_t> node_ctx;
     std::vector<uint4> rule_info(A.rule_names.size());
     std::vector<uint16_t> forced_node;
+    std::vector<std::pair<uint32_t, uint32_t>> others;  // (node, rule << 16 | index)
     for (size_t r = 0; r < A.rule_names.size(); ++r) {
+      const uint32_t begin = (uint32_t)ctx_node.size();
       for (int32_t n : A.contexts[r]) {
+        const uint32_t x = (uint32_t)r << 16 | ((uint32_t)ctx_node.size() - begin);
+        if (node_ctx_first[n].x == kNoKey) node_ctx_first[n].x = x;
+        else others.push_back({(uint32_t)n, x});
         ctx_node.push_back((uint16_t)n);
-        ++node_ctx_off[(size_t)n + 1];
       }
       ctx_off[r + 1] = (uint32_t)ctx_node.size();
       const auto& f = A.forced[r];
       rule_info[r] = make_uint4((uint32_t)forced_node.size(), (uint32_t)f.size(), (uint32_t)A.end_rule((int32_t)r), 0u);
       for (size_t k = f.size(); k-- > 0;) forced_node.push_back((uint16_t)f[k]);
     }
-    std::partial_sum(node_ctx_off.begin(), node_ctx_off.end(), node_ctx_off.begin());
-    node_ctx.resize(std::max<size_t>(ctx_node.size(), 1));
-    {
-      std::vector<uint32_t> next(node_ctx_off.begin(), node_ctx_off.end() - 1);
-      for (size_t r = 0; r < A.rule_names.size(); ++r)
-        for (uint32_t i = ctx_off[r]; i < ctx_off[r + 1]; ++i) node_ctx[next[ctx_node[i]]++] = (uint32_t)r << 16 | (i - ctx_off[r]);
+    std::sort(others.begin(), others.end());
+    for (size_t k = 0; k < others.size();) {
+      const uint32_t n = others[k].first;
+      node_ctx_first[n].y = (uint32_t)node_ctx.size();
+      node_ctx.push_back(0u);
+      for (; k < others.size() && others[k].first == n; ++k) {
+        ++node_ctx[node_ctx_first[n].y];
+        node_ctx.push_back(others[k].second);
+      }
     }
+    if (node_ctx.empty()) node_ctx.push_back(0u);
     if (ctx_node.empty()) ctx_node.push_back(0);
     if (forced_node.empty()) forced_node.push_back(0);
 
@@ -1031,13 +1040,13 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
       Parts kept, temp;
       size_t at_k[kCtxLevels] = {};
       for (int l = 0; l < c->levels; ++l) at_k[l] = kept.add(c->k_base_host[l]);
-      const size_t at_off = kept.add(ctx_off), at_ctx = kept.add(ctx_node), at_noff = kept.add(node_ctx_off), at_nctx = kept.add(node_ctx);
+      const size_t at_off = kept.add(ctx_off), at_ctx = kept.add(ctx_node), at_nfirst = kept.add(node_ctx_first), at_nctx = kept.add(node_ctx);
       char* const k = keep(slab_alloc<char>(kept.bytes()));
       kept.send(k, arena, stream);
       for (int l = 0; l < c->levels; ++l) d_k_base[l] = reinterpret_cast<const uint32_t*>(k + at_k[l]);
       c->host.ctx_off = args.ctx_off = reinterpret_cast<const uint32_t*>(k + at_off);
       c->host.ctx_node = args.ctx_node = reinterpret_cast<const uint16_t*>(k + at_ctx);
-      c->host.node_ctx_off = reinterpret_cast<const uint32_t*>(k + at_noff);
+      c->host.node_ctx_first = reinterpret_cast<const uint2*>(k + at_nfirst);
       c->host.node_ctx = reinterpret_cast<const uint32_t*>(k + at_nctx);
       const size_t at_rep = temp.add(rep), at_first = temp.add(first), at_tiles = temp.add(tiles), at_rule = temp.add(rule_info),
                    at_forced = temp.add(forced_node);

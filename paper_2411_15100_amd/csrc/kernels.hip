@@ -1955,7 +1955,7 @@ __global__ __launch_bounds__(kFillThreads, WALKS ? 4 : 8) void fill_kernel(const
 
 
 // ------------------------------------------------- device-resident states
-constexpr int kAcceptThreads = 256;
+constexpr int kAcceptThreads = 512;
 constexpr int kErrTokenRejected = -6, kErrTerminated = -7, kErrTooManyStacks = -8, kErrTooLarge = -9, kErrBadArg = -1, kErrInternal = -11;
 
 // What the walks of an accept leave behind: for every stack that the token can end in, which of the row's stacks it
@@ -1971,12 +1971,9 @@ struct AcceptShared {
   uint32_t less[kBatchMaxCandidates];                // the candidates that come before it, as a bit set
   uint32_t stack[kBatchMaxStacks];                   // the row's stacks: first frame in `live` | frames << 16
   uint32_t common[kBatchMaxStacks][kBatchMaxStacks]; // frames that two of them have in common, from the bottom
-  uint32_t slot_of[kBatchMaxStacks], first[kBatchMaxStacks + 1];  // the new stacks in order: candidate, first frame
-  uint32_t keys[kBatchMaxStacks][kStackLists];       // the lists of every new stack
-  uint32_t cidx[kBatchMaxStacks][kCtxLevels];        // which context of its rule the frame above each level sits on
-  uint32_t drops[kBatchMaxStacks];
+  uint32_t slot_of[kBatchMaxStacks];                 // the new stacks in order
   uint32_t mem[kAcceptThreads / 64][kWaveMemWords];
-  uint32_t count, overflow, duplicates, not_final, bad_context;
+  uint32_t count, overflow, duplicates, can_end, bad_context, n_frames;
   __device__ __forceinline__ uint32_t kept(uint32_t i) const { return (from[i] >> 8) & 0xFFu; }
   __device__ __forceinline__ uint32_t depth(uint32_t i) const { return kept(i) + (from[i] >> 16); }
   __device__ __forceinline__ uint32_t frame(uint32_t i, uint32_t k) const {  // frame k of candidate i, from the bottom
@@ -2046,13 +2043,18 @@ __device__ __forceinline__ int compare_candidates(const AcceptShared& sm, uint32
 // not fit the device limits, keeps its state and gets an error code in `status`.
 // Bound by latency: a row is one workgroup, and what it does is one chain - state,
 // walk, order, contexts, keys, offsets.  So everything that does not depend on
-// the walk is fetched at once in front of it (frames and tables into LDS), and
-// whatever concerns many frames is done by many threads.  In-kernel clocks, mean
-// of 128 schema rows: 2.3 us until state and tables are there, walk 1.7, order
-// and contexts 1.4, keys 0.9, offsets and the rest 0.9; the launch lasts as long
-// as its slowest row (a twelve-byte token through several frames: 20 steps of
-// 0.6 us).  With one lane per stack, tables in global memory and stacks copied
-// by that lane: 17.9 us for the launch, now 16; one JSON row 8.2 us, now 6;
+// the walk is fetched at once in front of it (frames and tables into LDS, by 512
+// threads: a pass of 128 schema rows takes 1 us less than with 256, one of a JSON row
+// as long), and a wave works out a new stack by itself, its frames and their headers
+// one in each lane: what used to be five barriers with a lookup or two between them is
+// one memory round for the contexts (DevCache::node_ctx_first), one for each level's
+// key and one for the offsets.  In-kernel clocks, mean of 128 schema rows: 2.2 us until
+// state and tables are there (2.6 before), walk 1.9, stacks 2.6 (3.4 before), the
+// rest 0.4 (0.6); the launch, 13.3 us (14.3 before), lasts as long as its slowest row (a twelve-byte token
+// through several frames: 20 steps of 0.6 us).  A pass of four fills and three accepts of
+// 128 schema rows 86.7 -> 83.3 us, of five and four of one JSON row 42.9 -> 41.6.
+// With one lane per stack, tables in global memory and stacks copied
+// by that lane: 17.9 us for the launch; one JSON row 8.2 us, now 5.7;
 // rows of the C/SQL-like grammar, 90 frames deep, 46 us in the mean, now 10.
 __global__ __launch_bounds__(kAcceptThreads) void batch_accept_kernel(DevBatch bt, DevVocab voc, uint32_t lds_budget,
                                                                       const int32_t* __restrict__ tokens) {
@@ -2071,19 +2073,21 @@ __global__ __launch_bounds__(kAcceptThreads) void batch_accept_kernel(DevBatch b
   const uint32_t hdr_stride = stack_hdr_stride(bt.n_seg);
   const uint32_t at = (uint32_t)b * bt.H + head;
   const SlotMeta cur = bt.meta[at];
+  const uint32_t epoch = bt.rows[b].epoch;
+  const int32_t older = bt.older[b];
   if (tok < 0) return;  // this row is left alone (its status too)
   {
     uint4 h = make_uint4(0u, 0u, 0u, 0u);
     if (tid < kBatchMaxStacks) h = *reinterpret_cast<const uint4*>(bt.hdrs + (size_t)(at * kBatchMaxStacks + tid) * hdr_stride);
     const uint32_t* frames = reinterpret_cast<const uint32_t*>(bt.frames + (size_t)at * kBatchRowFrames);
-    const uint32_t two = frames[tid];  // (most rows have fewer frames than this brings)
+    const uint32_t two = frames[tid];
     stage_tables(tab, smem, kAcceptThreads);
     reinterpret_cast<uint32_t*>(sm.live)[tid] = two;
     for (uint32_t k = tid + kAcceptThreads; k * 2u < cur.n_frames; k += kAcceptThreads) reinterpret_cast<uint32_t*>(sm.live)[k] = frames[k];
     static_assert(kStackHdrTop == 0 && kStackHdrDepth == 1 && kStackHdrFrames == 2, "a stack's scalars are one 16-byte load");
     if (tid < kBatchMaxStacks) sm.stack[tid] = (h.z - at * kBatchRowFrames) | (h.y << 16);
   }
-  if (tid == 0) { sm.count = 0u; sm.overflow = 0u; sm.duplicates = 0u; sm.not_final = 0u; sm.bad_context = 0u; }
+  if (tid == 0) { sm.count = 0u; sm.overflow = 0u; sm.duplicates = 0u; sm.can_end = 0u; sm.bad_context = 0u; }
   if (tid < kBatchMaxCandidates) sm.less[tid] = 0u;
   int32_t status = 0;
   bool stop = false;
@@ -2174,78 +2178,80 @@ __global__ __launch_bounds__(kAcceptThreads) void batch_accept_kernel(DevBatch b
     }
     if (tid < nc && !((dup >> tid) & 1u)) sm.slot_of[__popc(sm.less[tid] & ~dup)] = tid;
     __syncthreads();
-    if (tid <= ns) {
-      uint32_t run = 0u;
-      for (uint32_t r = 0; r < tid; ++r) run += sm.depth(sm.slot_of[r]);
-      sm.first[tid] = run;
-    }
-    // where the levels begin in every stack, and which context of its rule the frame above each of them sits on (one
-    // thread per stack and level)
-    if (tid >= 64u && tid < 64u + ns * (uint32_t)kCtxLevels) {
-      const uint32_t r = (tid - 64u) / (uint32_t)kCtxLevels, l = (tid - 64u) % (uint32_t)kCtxLevels + 1u;
-      const uint32_t ci = sm.slot_of[r], d = sm.depth(ci);
+    // A wave writes out a stack, and works out where its lists lie: which context of its rule the frame above each level
+    // sits on (a lane per level), the keys (one after the other), the offsets of their segments (a lane per segment).
+    for (uint32_t r = wave; r < ns; r += kAcceptThreads / 64) {
+      const uint32_t ci = uniform(sm.slot_of[r]), d = uniform(sm.depth(ci));
+      // lane k: the frame k below the top (below the 64th: looked up when they are needed)
+      const uint32_t mine = lane < d ? sm.frame(ci, d - 1u - lane) : 0u;
+      const uint32_t top = uniform(mine);
+      const uint32_t base = dc.k_base[0] != nullptr ? dc.k_base[0][top] : kNoKey, acc_row = dc.acc_row[top];
+      const uint32_t flags = T.header(mine).y;
+      const uint32_t first = fb + wave_sum(lane < r ? sm.depth(sm.slot_of[lane]) : 0u);
+      auto node_at = [&](uint32_t k) { return sm.frame(ci, d - 1u - k); };
+      const uint32_t drops = stack_drops(d, [&](uint32_t k) {
+        const uint32_t y = k < 64u ? (uint32_t)__builtin_amdgcn_readlane((int)flags, (int)k) : T.header(node_at(k)).y;
+        return (uniform(y) >> kHdrChainShift) & kHdrChainMask;
+      });
+      // which context of its rule the frame above level `lane` + 1 sits on
+      const uint32_t from = lane < (uint32_t)kCtxLevels ? stack_drop(drops, lane + 1u) : 255u;
+      uint32_t above = (uint32_t)__shfl((int)flags, (int)(from - 1u) & 63, 64), below = (uint32_t)__shfl((int)mine, (int)from & 63, 64);
       uint32_t idx = kNoKey;
-      const uint32_t dr = stack_drops(d, [&](uint32_t k) { return (T.header(sm.frame(ci, d - 1u - k)).y >> kHdrChainShift) & kHdrChainMask; });
-      if (l == 1u) sm.drops[r] = dr;
-      const uint32_t from = stack_drop(dr, l);
       if (from < d) {
-        const uint32_t rule = T.header(sm.frame(ci, d - from)).y >> 16, below = sm.frame(ci, d - 1u - from);
-        for (uint32_t k = dc.node_ctx_off[below]; k < dc.node_ctx_off[below + 1u]; ++k) {
-          const uint32_t x = dc.node_ctx[k];
-          if ((x >> 16) == rule) idx = x & 0xFFFFu;
-        }
+        if (from > 64u) above = T.header(node_at(from - 1u)).y;
+        if (from > 63u) below = node_at(from);
+        const uint32_t rule = above >> 16;
+        const uint2 of = dc.node_ctx_first[below];
+        if ((of.x >> 16) == rule) idx = of.x & 0xFFFFu;
+        else if (of.y != kNoKey)
+          for (uint32_t k = 1u; k <= dc.node_ctx[of.y]; ++k) {
+            const uint32_t x = dc.node_ctx[of.y + k];
+            if ((x >> 16) == rule) idx = x & 0xFFFFu;
+          }
         if (idx == kNoKey) sm.bad_context = 1u;
       }
-      sm.cidx[r][l - 1u] = idx;
-    }
-    __syncthreads();
-    n_frames = sm.first[ns];
-    // the keys: the top node's own list, then one per level that the stack reaches and the cache keeps
-    if (tid < ns) {
-      const uint32_t ci = sm.slot_of[tid], d = sm.depth(ci);
-      uint32_t* h = bt.hdrs + (size_t)(sb + tid) * hdr_stride;
-      const uint32_t top = sm.frame(ci, d - 1u);
-      sm.keys[tid][0] = top;
-      uint32_t local = top, key0 = (uint32_t)dc.n_nodes;
-      bool more = true;
+      // frames, and whether the stack can end the text: every frame of it may end its rule
+      bool all_final = lane >= d || (flags & 1u) != 0u;
+      if (lane < d) bt.frames[first + d - 1u - lane] = (uint16_t)mine;
+      for (uint32_t k = lane + 64u; k < d; k += 64u) {
+        const uint32_t n = node_at(k);
+        bt.frames[first + d - 1u - k] = (uint16_t)n;
+        all_final = all_final && T.is_final(n);
+      }
+      if (__ballot(!all_final) == 0ull && lane == 0u) sm.can_end = 1u;
+      if (r + 1u == ns && lane == 0u) sm.n_frames = first + d - fb;
+      // the keys: the top node's own list, then one per level that the stack reaches and the cache keeps
+      uint32_t keys[kStackLists];
+      keys[0] = top;
+      uint32_t child = base, key0 = (uint32_t)dc.n_nodes;
 #pragma unroll
       for (uint32_t l = 1; l <= (uint32_t)kCtxLevels; ++l) {
-        uint32_t key = kNoKey;
-        if (more && sm.cidx[tid][l - 1u] != kNoKey && dc.k_base[l - 1u] != nullptr) {
-          const uint32_t kb = dc.k_base[l - 1u][local];
-          if (kb != kNoKey) {
-            local = kb + sm.cidx[tid][l - 1u];
-            key = key0 + local;
-          }
+        const uint32_t c = (uint32_t)__builtin_amdgcn_readlane((int)idx, (int)l - 1);
+        keys[l] = kNoKey;
+        if (child != kNoKey && c != kNoKey) {
+          keys[l] = key0 + child + c;
+          child = l < (uint32_t)kCtxLevels && dc.k_base[l] != nullptr ? dc.k_base[l][child + c] : kNoKey;
+        } else {
+          child = kNoKey;
         }
-        more = key != kNoKey;
-        sm.keys[tid][l] = key;
         key0 += dc.n_k[l - 1u];
       }
-      *reinterpret_cast<uint4*>(h) = make_uint4(top | ((uint32_t)dc.acc_row[top] << 16), d, fb + sm.first[tid], sm.drops[tid]);
-    } else if (tid >= 64u) {
-      // frames, and whether some stack can end the text: every frame of it may end its rule
-      for (uint32_t item = tid - 64u; item < ns * kBatchMaxDepth; item += kAcceptThreads - 64) {
-        const uint32_t r = item / kBatchMaxDepth, k = item % kBatchMaxDepth, ci = sm.slot_of[r];
-        if (k < sm.depth(ci)) {
-          const uint32_t n = sm.frame(ci, k);
-          bt.frames[fb + sm.first[r] + k] = (uint16_t)n;
-          if (!T.is_final(n)) atomicOr(&sm.not_final, 1u << r);
-        }
+      uint32_t* const h = bt.hdrs + (size_t)(sb + r) * hdr_stride;
+      if (lane == 0u) *reinterpret_cast<uint4*>(h) = make_uint4(top | (acc_row << 16), d, first, drops);
+      static_assert(kStackLists == 4, "the offsets of a segment's four lists are one 16-byte store");
+      for (uint32_t sgm = lane; sgm < n_off; sgm += 64u) {
+        uint32_t o[kStackLists];
+#pragma unroll
+        for (uint32_t l = 0; l < kStackLists; ++l) o[l] = keys[l] == kNoKey ? 0u : dc.key_off[(size_t)keys[l] * (uint32_t)bt.n_seg + sgm];
+        *reinterpret_cast<uint4*>(h + stack_hdr_off(sgm, 0u)) = make_uint4(o[0], o[1], o[2], o[3]);
       }
     }
     __syncthreads();
-    can_end = (sm.not_final & ((1u << ns) - 1u)) != ((1u << ns) - 1u) ? 1u : 0u;
+    n_frames = sm.n_frames;
+    can_end = sm.can_end;
     if (sm.bad_context) {  // a frame sits on a node that is no context of its rule: never the case for stacks the walk makes
       if (tid == 0) bt.status[b] = kErrInternal;
       return;
-    }
-    // headers: where the lists' segments start
-    for (uint32_t item = tid; item < ns * kStackLists * n_off; item += kAcceptThreads) {
-      const uint32_t r = item / (kStackLists * n_off), sgm = item / kStackLists % n_off, l = item % kStackLists;
-      const uint32_t key = sm.keys[r][l];
-      bt.hdrs[(size_t)(sb + r) * hdr_stride + stack_hdr_off(sgm, l)] =
-          key == kNoKey ? 0u : dc.key_off[(size_t)key * (uint32_t)bt.n_seg + sgm];
     }
   }
   if (tid == 0) {
@@ -2255,20 +2261,15 @@ __global__ __launch_bounds__(kAcceptThreads) void batch_accept_kernel(DevBatch b
     m.flags = stop ? 3u : can_end;
     m.pad = 0u;
     bt.meta[(size_t)b * bt.H + next] = m;
-    RowDesc r;
-    r.tab = dc.tab;
-    r.acc = dc.acc;
-    r.entries = dc.entries;
+    RowDesc& r = bt.rows[b];  // (its tables and lists stay the same)
     r.stack_begin = sb;
     r.n_stacks = m.n_stacks;
     r.flags = m.flags & 1u;
     r.frame_begin = fb;
     r.n_frames = m.n_frames;
-    r.epoch = bt.rows[b].epoch + 1u;
-    bt.rows[b] = r;
+    r.epoch = epoch + 1u;
     bt.head[b] = next;
-    const int32_t o = bt.older[b] + 1;
-    bt.older[b] = o < bt.H - 1 ? o : bt.H - 1;
+    bt.older[b] = older + 1 < bt.H - 1 ? older + 1 : bt.H - 1;
     bt.status[b] = 0;
   }
 }
