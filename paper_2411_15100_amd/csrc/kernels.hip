@@ -222,11 +222,11 @@ struct ClassifyShared {
 // listed for classify_walks_kernel: 338 K pairs of an 11867-node schema grammar and 151936 tokens, where the first byte
 // alone leaves 1.56 M of the 28 M.
 // Both kernels write whole words of the rank-space bitsets, 64 tokens of one node, which are lines of their own: only those
-// that are not zero (ClassifyArgs::some_acc).  264 us for that grammar (381 with every word written, 451 MB), and 365 us
+// that are not zero (ClassifyArgs::some_acc).  264 us for that grammar (381 with every word written, 451 MB), and 300 us
 // for the walks, where one kernel that walked all pairs that the first byte leaves took 1663 us; JSON (128256 tokens) 37 +
-// 37 us, before 163, where a few waves with the walks of whole strings were the last to finish; 32000 tokens 18 + 30, before
-// 65; a scripting grammar 54 + 175, before 394; the C/SQL-like grammar, whose identifiers are walked to their ends at a
-// hundred nodes, 70 + 1032, before 1283.
+// 34 us, before 163, where a few waves with the walks of whole strings were the last to finish; 32000 tokens 18 + 25, before
+// 65; a scripting grammar 64 + 152, before 394; the C/SQL-like grammar, whose identifiers are walked to their ends at a
+// hundred nodes, 89 + 957, before 1283.
 template <class Tab>
 __device__ __forceinline__ void classify_body(const Tab& T, ClassifyShared& sm, const DevVocab& voc, const ClassifyArgs& a, int32_t n_items_max) {
   // A workgroup owns a run of up to kClassifyItems items of 64 tokens, and kClassifyNodes nodes; lane j of a wave looks at
@@ -793,7 +793,7 @@ __global__ __launch_bounds__(kContextThreads) void exit_positions_kernel(DevTabl
     const uint32_t node = a.base_node[e];
     const TokenRef t = load_token(voc, (int32_t)a.base_ids[e]);
     uint32_t x = 0u;
-    const int res = walk_token<true>(T, t.tk, t.ext, t.len, node, (const uint16_t*)nullptr, 1u, nullptr, T.follow_of(node), 0, &x);
+    const int res = walk_token<true, true>(T, t.tk, t.ext, t.len, node, (const uint16_t*)nullptr, 1u, nullptr, T.follow_of(node), 0, &x);
     a.exits[e] = res == kOverflow ? 0x80000000u : x;
   };
   if (small_sections_staged(tab)) body(LdsTabT<true>(tab, smem));
