@@ -1112,7 +1112,7 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
     args.back = arena.array<uint32_t>(n_slots);
     uint32_t* d_block_sums = arena.array<uint32_t>(slot_blocks(n_slots) * 2);
     auto offsets = [&] {
-      launch_slot_offsets(SlotCounts{d_acc_counts, d_seg_counts, d_counts, N, dv.W, n_seg, n_slots}, reinterpret_cast<unsigned long long*>(d_block_sums),
+      launch_slot_offsets(SlotCounts{d_seg_counts, d_counts, (size_t)N * n_seg, n_slots}, reinterpret_cast<unsigned long long*>(d_block_sums),
                           d_key_off, args.front, args.back, reinterpret_cast<unsigned long long*>(d_found), stream);
       HIP_OK(hipGetLastError());
       HIP_OK(hipMemcpyAsync((void*)h_found, d_found, counts_at, hipMemcpyDeviceToHost, stream));

@@ -165,26 +165,29 @@ constexpr uint32_t kPairNodeBits = 15;  // (XGM_MAX_NODES; the item number takes
 // context-dependent), `z` = the same but c follows the rule in no context (context-dependent by section 3.1
 // alone, rejected everywhere).  One 16-byte load then tells a thread of the classify kernel what its token's
 // first byte means at 32 nodes.
-constexpr int kFirstByteThreads = 256;
+// A wave takes 64 nodes, one in each lane, and 32 byte values.  Bound by the latency of two dependent loads: 3.7 us for JSON's
+// 74 nodes and 5.2 for 11867, where a thread that asked 32 nodes one after the other for a byte took 13 and 29.
+constexpr int kFirstByteThreads = 512;
 __global__ __launch_bounds__(kFirstByteThreads) void first_byte_kernel(DevTables tab, uint32_t n_words, uint4* __restrict__ out) {
-  const uint32_t t = blockIdx.x * kFirstByteThreads + threadIdx.x;
-  if (t >= 256u * n_words) return;
-  const uint32_t c = t / n_words, w = t % n_words;
+  static_assert(kFirstByteThreads / 64 * 32 == 256, "eight waves take all byte values");
+  const uint32_t lane = threadIdx.x & 63u, group = uniform(threadIdx.x >> 6), n = blockIdx.x * 64u + lane;
   const unsigned char* img = reinterpret_cast<const unsigned char*>(tab.image);
-  const uint2* hdr = reinterpret_cast<const uint2*>(img + tab.off_hdr);
-  const uint32_t* first = reinterpret_cast<const uint32_t*>(img + tab.off_first);
-  const uint32_t* follow = reinterpret_cast<const uint32_t*>(img + tab.off_follow);
-  uint4 q = make_uint4(0u, 0u, 0u, 0u);
-  for (uint32_t j = 0; j < 32u; ++j) {
-    const uint32_t n = w * 32u + j;
-    if (n >= (uint32_t)tab.n_nodes) break;
-    if ((first[(size_t)n * 8u + (c >> 5)] >> (c & 31)) & 1u) { q.x |= 1u << j; continue; }
-    const uint2 h = hdr[n];
-    if (!(h.y & 1u)) continue;
-    if ((follow[(h.y >> 16) * 8u + (c >> 5)] >> (c & 31)) & 1u) q.y |= 1u << j;
-    else q.z |= 1u << j;
+  uint32_t first = 0u, follow = 0u;
+  bool final_ = false;
+  if (n < (uint32_t)tab.n_nodes) {
+    first = reinterpret_cast<const uint32_t*>(img + tab.off_first)[(size_t)n * 8u + group];
+    const uint2 h = reinterpret_cast<const uint2*>(img + tab.off_hdr)[n];
+    final_ = h.y & 1u;
+    if (final_) follow = reinterpret_cast<const uint32_t*>(img + tab.off_follow)[(h.y >> 16) * 8u + group];
   }
-  out[t] = q;
+  const uint32_t walks = first, exits = final_ ? ~first & follow : 0u, plain = final_ ? ~first & ~follow : 0u;
+  uint4 q = make_uint4(0u, 0u, 0u, 0u);  // lane j: byte value 32 group + j % 32, nodes of the j / 32-th word
+  for (uint32_t j = 0; j < 32u; ++j) {
+    const unsigned long long x = __ballot((walks >> j) & 1u), y = __ballot((exits >> j) & 1u), z = __ballot((plain >> j) & 1u);
+    if ((lane & 31u) == j) q = lane < 32u ? make_uint4((uint32_t)x, (uint32_t)y, (uint32_t)z, 0u) : make_uint4((uint32_t)(x >> 32), (uint32_t)(y >> 32), (uint32_t)(z >> 32), 0u);
+  }
+  const uint32_t w = blockIdx.x * 2u + (lane >> 5);
+  if (w < n_words) out[(size_t)(group * 32u + (lane & 31u)) * n_words + w] = q;
 }
 
 // The token of byte-sorted rank r.
@@ -506,8 +509,7 @@ __global__ __launch_bounds__(kNodeThreads) void row_stats_kernel(DevVocab voc, R
     a.unc_counts[node] = sums[1];
     if (!kept_as_list(total, voc.W)) a.bitset_nodes[atomicAdd(a.n_bitset_nodes, 1u)] = (uint32_t)node;
   }
-  if (!kept_as_list(total, voc.W)) return;
-  if (acc)
+  if (acc && kept_as_list(total, voc.W))
     for_each_word(voc, a.acc_rank, a.some_acc, node, wave, kNodeThreads / 64, [&](uint32_t item0, u64 x) {
       for_each_token<false>(voc, item0, x, [&](bool has, uint32_t id, uint32_t, uint32_t) { if (has) atomicAdd(&seg[id / (uint32_t)kSegTokens], 1u); });
     });
@@ -516,7 +518,7 @@ __global__ __launch_bounds__(kNodeThreads) void row_stats_kernel(DevVocab voc, R
 }
 
 // The accepted rows of the nodes that keep a bitset, in id space (bit id_of_rank[r] of the output = bit r of the row), and
-// their statistics.  A workgroup builds a row in LDS, of the rarer kind of bit: a row with few set bits starts as zeros
+// their digests.  A workgroup builds a row in LDS, of the rarer kind of bit: a row with few set bits starts as zeros
 // and gets its set bits, one with many as ones and gets its zeros.
 constexpr int kBitsetThreads = 512;
 __global__ __launch_bounds__(kBitsetThreads) void bitset_rows_kernel(DevVocab voc, RankRows a, uint32_t* __restrict__ acc_id,
@@ -524,14 +526,12 @@ __global__ __launch_bounds__(kBitsetThreads) void bitset_rows_kernel(DevVocab vo
   extern __shared__ __align__(16) unsigned char smem[];
   uint32_t* row = reinterpret_cast<uint32_t*>(smem);  // [W]
   __shared__ unsigned long long part[kBitsetThreads / 64];
-  __shared__ uint32_t seg[kMaxSegs];
   const uint32_t n = *a.n_bitset_nodes, n_items = (uint32_t)voc.WR / 2u;
   const uint32_t tail = (voc.V & 31) ? ((1u << (voc.V & 31)) - 1u) : 0xFFFFFFFFu;  // valid bits of the last word
   for (uint32_t k = blockIdx.x; k < n; k += gridDim.x) {
     const size_t node = a.bitset_nodes[k];
     const bool full = a.acc_counts[node] * 2u > (uint32_t)voc.V;
     __syncthreads();
-    if (threadIdx.x < kMaxSegs) seg[threadIdx.x] = 0u;
     for (int32_t w = threadIdx.x; w < voc.W; w += kBitsetThreads) row[w] = !full ? 0u : w == voc.W - 1 ? tail : 0xFFFFFFFFu;
     __syncthreads();
     for (uint32_t item0 = uniform(threadIdx.x >> 6) * 64u; item0 < n_items; item0 += kBitsetThreads) {
@@ -556,14 +556,12 @@ __global__ __launch_bounds__(kBitsetThreads) void bitset_rows_kernel(DevVocab vo
     for (int32_t w = threadIdx.x; w < voc.W; w += kBitsetThreads) {
       const uint32_t x = row[w];
       acc_id[node * voc.W + w] = x;
-      if (x) atomicAdd(&seg[w / kSegWords], (uint32_t)__popc(x));
       h += mix64(((unsigned long long)(uint32_t)w << 32 | x) + 0x9E3779B97F4A7C15ull);
     }
 #pragma unroll
     for (uint32_t d = 32; d > 0; d >>= 1) h += __shfl_down(h, d, 64);
     if ((threadIdx.x & 63u) == 0) part[threadIdx.x >> 6] = h;
     __syncthreads();
-    if ((int32_t)threadIdx.x < voc.n_seg) a.seg_counts[node * voc.n_seg + threadIdx.x] = seg[threadIdx.x];
     if (threadIdx.x == 0) {
       unsigned long long t = 0ull;
       for (int q = 0; q < kBitsetThreads / 64; ++q) t += part[q];
@@ -688,7 +686,7 @@ __global__ __launch_bounds__(kRowThreads) void permute_kernel(DevVocab voc, cons
   for (uint32_t d = 32; d > 0; d >>= 1) h += __shfl_down(h, d, 64);
   if ((threadIdx.x & 63u) == 0) part[threadIdx.x >> 6] = h;
   __syncthreads();
-  if ((int32_t)threadIdx.x < voc.n_seg) seg_counts[node * voc.n_seg + threadIdx.x] = seg[threadIdx.x];
+  if ((int32_t)threadIdx.x < voc.n_seg) seg_counts[node * voc.n_seg + threadIdx.x] = kept_as_list(set_bits[0], voc.W) ? seg[threadIdx.x] : 0u;
   if (threadIdx.x == 0) {
     unsigned long long t = 0ull;
     for (int k = 0; k < kRowThreads / 64; ++k) t += part[k];
@@ -1128,32 +1126,32 @@ __global__ __launch_bounds__(kOpenWriteThreads) void context_level1_write_kernel
 }
 
 // Level `level` >= 2: a fixed grid walks over the records of level - 1, each of which names a chunk of
-// kContextsPerThread contexts; consecutive threads hold consecutive records (neighbouring tokens of one
-// node and context, as a rule).
+// kContextsPerThread contexts.  A wave takes 64 consecutive records (neighbouring tokens of one node and context, as a
+// rule) and two contexts of each, one after the other; neighbouring waves the same records.  Where there are records
+// enough for all waves anyway it takes all eight.  Two launches of the 11867-node schema grammar (151936 tokens) 127 us with
+// eight, 85 with two, 94 with one; JSON (32000) 38, 26, 25; a scripting grammar (128256, 660 K records) 560, 468, 442; the
+// C/SQL-like grammar (1.7 M) 1632, 1775, 1811.
+constexpr uint32_t kManyRecords = 1u << 20;
 template <bool WRITE, class Tab>
 __device__ __forceinline__ void context_deeper_body(const Tab& T, const DevVocab& voc, const ContextListArgs& a, uint32_t level) {
-  const uint32_t n_res = min(a.res_count[level - 2u], a.res_cap);
-  for (uint32_t item = blockIdx.x * kContextThreads + threadIdx.x; item < n_res; item += gridDim.x * kContextThreads) {
+  static_assert(kContextsPerThread == 8, "a record's outcomes are eight 16-bit codes in one uint4");
+  const uint32_t n_res = min(a.res_count[level - 2u], a.res_cap), per = n_res > kManyRecords ? kContextsPerThread : 2u;
+  const uint32_t n_units = (n_res + 63u) / 64u * (kContextsPerThread / per), lane = threadIdx.x & 63u;
+  uint16_t* const keep = WRITE ? nullptr : reinterpret_cast<uint16_t*>(a.deep_outcomes[level - 1u]);
+  for (uint32_t unit = blockIdx.x * (kContextThreads / 64) + uniform(threadIdx.x >> 6); unit < n_units; unit += gridDim.x * (kContextThreads / 64)) {
+    const uint32_t item = unit * per / kContextsPerThread * 64u + lane, q0 = unit * per % kContextsPerThread;
+    if (item >= n_res) continue;
     const uint4 rec = a.res[level - 2u][item];
-    const uint32_t rule = rec.w & 0xFFFFu;
-    const uint32_t cb = a.ctx_off[rule], m = a.ctx_off[rule + 1] - cb;
-    const uint32_t j0 = (rec.w >> 17) * kContextsPerThread;
+    const uint32_t rule = rec.w & 0xFFFFu, cb = a.ctx_off[rule], m = a.ctx_off[rule + 1] - cb, j0 = (rec.w >> 17) * kContextsPerThread;
     const uint32_t id = a.base_ids[rec.x];
     const ContextWork<WRITE, Tab> w{T, voc, a, rec.x, id, load_token(voc, (int32_t)id)};
     const uint32_t kb = a.k_base[level - 1u][rec.y];
-    uint4* keep = WRITE ? nullptr : a.deep_outcomes[level - 1u];
-    static_assert(kContextsPerThread == 8, "a record's outcomes are eight 16-bit codes in one uint4");
-    unsigned long long lo = 0ull, hi = 0ull;  // (the loop is not unrolled: one copy of the walk, not eight)
 #pragma unroll 1
-    for (uint32_t q = 0; q < kContextsPerThread; ++q) {
-      const uint32_t j = j0 + q;
-      if (j >= m) break;
+    for (uint32_t q = q0; q < q0 + per; ++q) {
       uint32_t outcome = 0u;
-      w.step(level, a.ctx_node[cb + j], kb + j, rec.z, (rec.w & 0x10000u) != 0u, keep ? &outcome : nullptr);
-      if (q < 4u) lo |= (unsigned long long)outcome << (q * 16u);
-      else hi |= (unsigned long long)outcome << ((q - 4u) * 16u);
+      if (j0 + q < m) w.step(level, a.ctx_node[cb + j0 + q], kb + j0 + q, rec.z, (rec.w & 0x10000u) != 0u, &outcome);
+      if (keep) keep[(size_t)item * kContextsPerThread + q] = (uint16_t)outcome;
     }
-    if (keep) keep[item] = make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
   }
 }
 template <bool WRITE>
@@ -1187,12 +1185,15 @@ __global__ __launch_bounds__(256) void context_deeper_write_kernel(DevVocab voc,
 
 // The running sum over the slots (see launch_slot_offsets), in two launches: the sum of every block of slots, then the offsets
 // in it (a block adds up the sums of all blocks in front of it by itself: 98 of them for the 11867-node schema grammar).
-// On the host, with the counts copied there and the offsets copied back, this took 350 us of that grammar's build.
+// On the host, with the counts copied there and the offsets copied back, this took 350 us of that grammar's build.  All
+// counts of a thread are fetched at once.
 constexpr int kSlotThreads = 256, kSlotsPerThread = 16, kSlotBlock = kSlotThreads * kSlotsPerThread;
-__device__ __forceinline__ uint32_t slot_count(const SlotCounts& c, size_t k) {
-  if (k >= c.n_slots) return 0u;
-  if (k >= (size_t)c.n_nodes * (uint32_t)c.n_seg) return c.counts[k];
-  return kept_as_list(c.acc_counts[(uint32_t)k / (uint32_t)c.n_seg], c.W) ? c.seg_counts[k] : 0u;
+__device__ __forceinline__ void slot_counts(const SlotCounts& c, uint32_t (&n)[kSlotsPerThread]) {
+#pragma unroll
+  for (int j = 0; j < kSlotsPerThread; ++j) {
+    const size_t k = (size_t)blockIdx.x * kSlotBlock + (uint32_t)(j * kSlotThreads) + threadIdx.x;
+    n[j] = k < c.n_level0 ? c.level0[k] : k < c.n_slots ? c.counts[k] : 0u;
+  }
 }
 // the sum over the workgroup, in every thread (64 bits: a grammar's lists may be too long for 32)
 __device__ __forceinline__ u64 block_sum(u64 v, u64* part) {
@@ -1202,46 +1203,55 @@ __device__ __forceinline__ u64 block_sum(u64 v, u64* part) {
   __syncthreads();
   u64 sum = 0ull;
   for (int k = 0; k < kSlotThreads / 64; ++k) sum += part[k];
-  __syncthreads();
   return sum;
 }
 __global__ __launch_bounds__(kSlotThreads) void slot_sums_kernel(SlotCounts c, u64* __restrict__ block_sums) {
   __shared__ u64 part[kSlotThreads / 64];
+  uint32_t n[kSlotsPerThread];
+  slot_counts(c, n);
   u64 v = 0ull;
-  for (int j = 0; j < kSlotsPerThread; ++j) v += slot_count(c, (size_t)blockIdx.x * kSlotBlock + (uint32_t)(j * kSlotThreads) + threadIdx.x);
+#pragma unroll
+  for (int j = 0; j < kSlotsPerThread; ++j) v += n[j];
   const u64 sum = block_sum(v, part);
   if (threadIdx.x == 0u) block_sums[blockIdx.x] = sum;
 }
 __global__ __launch_bounds__(kSlotThreads) void slot_offsets_kernel(SlotCounts c, const u64* __restrict__ block_sums, uint32_t* __restrict__ key_off,
                                                                     uint32_t* __restrict__ front, uint32_t* __restrict__ back, u64* __restrict__ total) {
-  __shared__ u64 part[kSlotThreads / 64];
+  __shared__ u64 part[kSlotThreads / 64], sums[kSlotsPerThread][kSlotThreads / 64];
+  uint32_t n[kSlotsPerThread];
+  slot_counts(c, n);
   u64 before = 0ull;
   for (uint32_t k = threadIdx.x; k < blockIdx.x; k += kSlotThreads) before += block_sums[k];
-  u64 base = block_sum(before, part);
+  const u64 base = block_sum(before, part);
   const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+  u64 upto[kSlotsPerThread];  // in the wave, of the thread's j-th slot
+#pragma unroll
   for (int j = 0; j < kSlotsPerThread; ++j) {
-    const size_t k = (size_t)blockIdx.x * kSlotBlock + (uint32_t)(j * kSlotThreads) + threadIdx.x;
-    const u64 n = slot_count(c, k);
-    u64 incl = n;
+    upto[j] = n[j];
 #pragma unroll
     for (uint32_t d = 1; d < 64u; d <<= 1) {
-      const u64 v = __shfl_up(incl, d, 64);
-      if (lane >= d) incl += v;
+      const u64 v = __shfl_up(upto[j], d, 64);
+      if (lane >= d) upto[j] += v;
     }
-    if (lane == 63u) part[wave] = incl;
-    __syncthreads();
-    u64 at = base + incl - n;
+    if (lane == 63u) sums[j][wave] = upto[j];
+  }
+  __syncthreads();
+  u64 at = base;
+#pragma unroll
+  for (int j = 0; j < kSlotsPerThread; ++j) {
+    const size_t k = (size_t)blockIdx.x * kSlotBlock + (uint32_t)(j * kSlotThreads) + threadIdx.x;
+    u64 end = at + upto[j];
+#pragma unroll
     for (uint32_t q = 0; q < (uint32_t)kSlotThreads / 64u; ++q) {
-      if (q < wave) at += part[q];
-      base += part[q];
+      if (q < wave) end += sums[j][q];
+      at += sums[j][q];
     }
-    __syncthreads();
     if (k < c.n_slots) {
-      key_off[k] = front[k] = (uint32_t)at;
-      back[k] = (uint32_t)(at + n);
+      key_off[k] = front[k] = (uint32_t)(end - n[j]);
+      back[k] = (uint32_t)end;
       if (k + 1 == c.n_slots) {
-        key_off[k + 1] = (uint32_t)(at + n);
-        *total = at + n;
+        key_off[k + 1] = (uint32_t)end;
+        *total = end;
       }
     }
   }
@@ -2424,8 +2434,7 @@ hipError_t static_scratch(void** out) {
 void launch_first_byte(const DevTables& tab, uint4* first_byte, hipStream_t stream) {
   const uint32_t n_words = first_byte_words(tab.n_nodes);
   if (n_words == 0) return;
-  hipLaunchKernelGGL(first_byte_kernel, dim3((256u * n_words + kFirstByteThreads - 1) / kFirstByteThreads),
-                     dim3(kFirstByteThreads), 0, stream, tab, n_words, first_byte);
+  hipLaunchKernelGGL(first_byte_kernel, dim3((n_words + 1) / 2), dim3(kFirstByteThreads), 0, stream, tab, n_words, first_byte);
 }
 
 void launch_classify(const DevTables& tab, const DevVocab& voc, const ClassifyArgs& args, hipStream_t stream) {

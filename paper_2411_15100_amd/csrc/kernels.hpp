@@ -301,7 +301,7 @@ struct RankRows {
   const uint8_t* some_unc;
   uint32_t* acc_counts;      // [n]
   uint32_t* unc_counts;      // [n]
-  uint32_t* seg_counts;      // [n][n_seg]
+  uint32_t* seg_counts;      // [n][n_seg] of the nodes that list their accepted tokens (others: 0)
   uint32_t* bitset_nodes;    // [n]
   uint32_t* n_bitset_nodes;  // (zero before the launch)
 };
@@ -311,7 +311,7 @@ void launch_base_lists(const DevVocab& voc, const RankRows& rows, int32_t n, con
 // the entries of the level-0 keys (see DevCache)
 void launch_level0_lists(const DevVocab& voc, const RankRows& rows, int32_t n, const uint32_t* key_off, uint32_t* entries, hipStream_t stream);
 // Rank space -> id space for n node rows (two bitsets per node), and - unless the pointers are null - per node the
-// set bits of the first row per segment (seg_counts[n][n_seg]), a digest of the first row and the set bits of both
+// set bits of the first row per segment (seg_counts[n][n_seg]; 0 if there are too many for a list), a digest of the first row and the set bits of both
 // rows (a_counts[n], b_counts[n]).
 void launch_permute(const DevVocab& voc, int32_t n, const uint32_t* a_rank, const uint32_t* b_rank, uint32_t* a_id,
                     uint32_t* b_id, uint32_t* seg_counts, unsigned long long* digest, uint32_t* a_counts, uint32_t* b_counts,
@@ -383,11 +383,9 @@ struct ContextListArgs {
 // of the other keys what the list kernels counted.  *total: all of them (more than 2^32 do not fit key_off).
 // block_sums: slot_blocks(n_slots) words of 64 bits.
 struct SlotCounts {
-  const uint32_t* acc_counts;  // [n_nodes]
-  const uint32_t* seg_counts;  // [n_nodes][n_seg]
-  const uint32_t* counts;      // [n_slots]
-  int32_t n_nodes, W, n_seg;
-  size_t n_slots;
+  const uint32_t* level0;   // [n_level0] the slots of the nodes
+  const uint32_t* counts;   // [n_slots] of the others
+  size_t n_level0, n_slots;
 };
 size_t slot_blocks(size_t n_slots);
 void launch_slot_offsets(const SlotCounts& counts, unsigned long long* block_sums, uint32_t* key_off, uint32_t* front, uint32_t* back,
