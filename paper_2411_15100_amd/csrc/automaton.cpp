@@ -412,6 +412,7 @@ class SequenceTable {
     size_t cap = 64;
     while (cap < expected * 2) cap *= 2;
     slots_.assign(cap, 0);
+    hashed_ = 0;
     pool_.clear();
     off_.assign(1, 0);
   }
@@ -419,7 +420,7 @@ class SequenceTable {
   const int* begin(int id) const { return pool_.data() + off_[id]; }
   const int* end(int id) const { return pool_.data() + off_[id + 1]; }
   int intern(const int* p, size_t n, bool* is_new = nullptr) {
-    if (size() * 2 >= slots_.size()) grow();
+    if (hashed_ * 2 >= slots_.size()) grow();  // (so that at least half of the slots are free)
     size_t at = hash(p, n) & (slots_.size() - 1);
     for (; slots_[at]; at = (at + 1) & (slots_.size() - 1)) {
       const int id = slots_[at] - 1;
@@ -430,10 +431,11 @@ class SequenceTable {
     }
     const int id = append(p, n);
     slots_[at] = id + 1;
+    ++hashed_;
     if (is_new) *is_new = true;
     return id;
   }
-  // a sequence that intern() will never be asked for
+  // a sequence that intern() will never be asked for: it has a number, but no slot
   int append(const int* p, size_t n) {
     const int id = (int)size();
     pool_.insert(pool_.end(), p, p + n);
@@ -451,14 +453,18 @@ class SequenceTable {
     return h;
   }
   void grow() {
-    slots_.assign(slots_.size() * 2, 0);
-    for (int id = 0; id < (int)size(); ++id) {  // (appended ones too: nothing is equal to them)
+    old_.swap(slots_);
+    slots_.assign(old_.size() * 2, 0);
+    for (int slot : old_) {
+      if (!slot) continue;
+      const int id = slot - 1;
       size_t at = hash(begin(id), (size_t)(end(id) - begin(id))) & (slots_.size() - 1);
       while (slots_[at]) at = (at + 1) & (slots_.size() - 1);
-      slots_[at] = id + 1;
+      slots_[at] = slot;
     }
   }
-  std::vector<int> slots_;  // id + 1, or 0
+  std::vector<int> slots_, old_;  // id + 1, or 0
+  size_t hashed_ = 0;             // slots in use
   std::vector<int> pool_;
   std::vector<uint32_t> off_{0};
 };

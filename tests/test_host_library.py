@@ -518,6 +518,270 @@ def test_depth_first_accept_on_random_grammars():
     assert n_grammars > 100 and n_steps > 3000 and n_multi > 100, (n_grammars, n_steps, n_multi)
 
 
+def _compiled(text, seconds=30.0):
+    """The compiled grammar; a compile that does not end fails the test (and is left behind: nothing can stop it)."""
+    out = []
+
+    def work():
+        try:
+            out.append(xgm.Grammar(text, "root"))
+        except Exception as e:
+            out.append(e)
+
+    thread = threading.Thread(target=work, daemon=True)
+    thread.start()
+    thread.join(seconds)
+    assert out, f"the compile of {text[:100]!r}... ({len(text)} characters) does not end"
+    if isinstance(out[0], Exception):
+        raise out[0]
+    return out[0]
+
+
+def _letters(n, k=0):
+    return "".join(chr(ord("a") + (k + 7 * j + j * j // 26) % 26) for j in range(n))
+
+
+# Subset construction looks up sets of one NFA state, all that a literal has, by the state and all others by their hash; so
+# many of the former come before one of the latter here.  Nodes: one in front of each byte of the literal, and `more`.
+@pytest.mark.parametrize("n", [1, 64, 127, 128, 254, 255, 256, 257, 258, 600, 1000, 5000])
+@pytest.mark.parametrize("rest, more, good, bad", [
+    ("[a-z]*", 1, (b"", b"ab"), (b"1",)),                                          # a loop
+    ('ws "}"', 4, (b"}", b"  }"), (b"", b" ")),                                    # a reference that may be skipped
+    ('("ab" "x" | "ac" | "a")', 4, (b"abx", b"ac", b"a"), (b"", b"ab", b"acx")),   # alternatives with a common prefix
+    ('("=" [0-9]+)?', 3, (b"", b"=12"), (b"=", b"1"))])
+def test_literals_of_any_length_compile(n, rest, more, good, bad):
+    lit = _letters(n)
+    text = f'root ::= "{lit}" {rest}\nws ::= " "*'
+    g, og = _compiled(text), oracle.Grammar(text, "root")
+    assert g.num_nodes == n + more
+    data = lit.encode()
+    for tail, ok in [(t, True) for t in good] + [(t, False) for t in bad]:
+        m = xgm.Matcher(grammar=g)
+        rc = m.try_accept_bytes(data + tail)
+        assert (rc == 0) == (og.recognize(data + tail) > 0), tail
+        assert (rc == 0 and m.can_terminate()) == ok == (og.recognize(data + tail) == 2), tail
+    m = xgm.Matcher(grammar=g)
+    if n > 1:
+        assert m.try_accept_bytes(data[:-1]) == 0 and not m.can_terminate()
+    assert m.try_accept_bytes(b"#") == -6
+
+
+@pytest.mark.parametrize("n", [2, 15, 16, 17, 18, 40, 60])
+def test_alternations_of_names_compile(n):
+    names = [_letters(16, 3 * k) + f"{k:02d}" for k in range(n)]
+    text = 'root ::= [a-z]* ":" call\ncall ::= (' + " | ".join(f'"{w}"' for w in names) + ') ws "("\nws ::= " "*'
+    g, og = _compiled(text), oracle.Grammar(text, "root")
+    for data in [f"x:{w}{s}(" for w in names for s in ("", "  ")] + [f":{names[0]}x(", f":{names[-1][:-1]}(", ":("]:
+        m = xgm.Matcher(grammar=g)
+        assert (m.try_accept_bytes(data.encode()) == 0 and m.can_terminate()) == (og.recognize(data.encode()) == 2), data
+
+
+@pytest.mark.parametrize("n", [200, 255, 256, 300, 3000])
+def test_schemas_with_long_names_compile(n):
+    name = _letters(n)
+    text = xgm.schema_to_grammar('{"type": "object", "properties": {"%s": {"type": "string"}, "b": {"enum": ["%s", 1]}}}' % (name, name))
+    g, og = _compiled(text), oracle.Grammar(text, "root")
+    for data in (f'{{"{name}": "x", "b": "{name}"}}', f'{{"{name}":"","b":1}}', f'{{"{name[:-1]}": "x", "b": 1}}', f'{{"{name}": 1, "b": 1}}'):
+        m = xgm.Matcher(grammar=g)
+        assert (m.try_accept_bytes(data.encode()) == 0 and m.can_terminate()) == (og.recognize(data.encode()) == 2), data[-20:]
+
+
+class _ReferenceRules:
+    """Minimal automata of rules from their expressions, the long way: positions of the symbols and which can follow which,
+    sets of them, states that lead nowhere taken out, the others split until nothing changes.  An expression is ("bytes",
+    lo, hi), ("lit", bytes), ("ref", name), ("seq" | "alt", expressions), ("star" | "opt" | "plus", expression); a symbol of
+    an automaton a byte or the name of a rule."""
+
+    def __init__(self, rules):
+        self.rules = rules
+        self.productive = self._least(lambda e, known: self._derives(e, known, True))
+        self.nullable = self._least(lambda e, known: self._derives(e, known, False))
+        self.automata = {r: self._minimal(*self._sets(e)) for r, e in rules.items() if r in self.productive}
+
+    def _least(self, holds):
+        known = set()
+        while True:
+            more = {r for r, e in self.rules.items() if r not in known and holds(e, known)}
+            if not more:
+                return known
+            known |= more
+
+    def _derives(self, e, known, consumes):
+        kind = e[0]
+        if kind in ("bytes", "lit"):
+            return consumes or (kind == "lit" and not e[1])
+        if kind == "ref":
+            return e[1] in known
+        if kind in ("seq", "alt"):
+            return (all if kind == "seq" else any)(self._derives(x, known, consumes) for x in e[1])
+        return kind in ("star", "opt") or self._derives(e[1], known, consumes)
+
+    def _sets(self, e):
+        """(states, start): a state is (can end, {symbol: state})."""
+        symbol, follow = [], []
+
+        def position(s):
+            symbol.append(s)
+            follow.append(set())
+            return len(symbol) - 1
+
+        def parts(e):  # (may be empty, first positions, last positions)
+            kind = e[0]
+            if kind == "bytes":
+                p = position((e[1], e[2]))
+                return False, {p}, {p}
+            if kind == "ref":
+                if e[1] not in self.productive:
+                    return False, set(), set()
+                p = position(e[1])
+                return e[1] in self.nullable, {p}, {p}
+            if kind == "lit":
+                ps = [position((c, c)) for c in e[1]]
+                for p, q in zip(ps, ps[1:]):
+                    follow[p].add(q)
+                return not ps, set(ps[:1]), set(ps[-1:])
+            if kind == "alt":
+                xs = [parts(x) for x in e[1]]
+                return any(x[0] for x in xs), set().union(*(x[1] for x in xs)), set().union(*(x[2] for x in xs))
+            if kind == "seq":
+                empty, first, last = True, set(), set()
+                for x in e[1]:
+                    x_empty, x_first, x_last = parts(x)
+                    for p in last:
+                        follow[p] |= x_first
+                    if empty:
+                        first = first | x_first
+                    last = last | x_last if x_empty else x_last
+                    empty = empty and x_empty
+                return empty, first, last
+            empty, first, last = parts(e[1])
+            if kind != "opt":
+                for p in last:
+                    follow[p] |= first
+            return empty or kind != "plus", first, last
+
+        empty, first, last = parts(e)
+        start = (empty, frozenset(first))
+        states, work = {}, [start]
+        while work:
+            s = work.pop()
+            if s in states:
+                continue
+            states[s] = to = {}
+            by_symbol = {}
+            for p in s[1]:
+                for x in [symbol[p]] if isinstance(symbol[p], str) else range(symbol[p][0], symbol[p][1] + 1):
+                    by_symbol.setdefault(x, []).append(p)
+            for x, ps in by_symbol.items():
+                to[x] = (any(p in last for p in ps), frozenset().union(*(follow[p] for p in ps)))
+                work.append(to[x])
+        return states, start
+
+    @staticmethod
+    def _minimal(states, start):
+        into = {}
+        for s, to in states.items():
+            for t in to.values():
+                into.setdefault(t, []).append(s)
+        alive, work = set(), [s for s in states if s[0]]
+        while work:
+            s = work.pop()
+            if s not in alive:
+                alive.add(s)
+                work += into.get(s, [])
+        block = {s: int(s[0]) for s in alive}
+        while True:
+            signatures = {s: (block[s], frozenset((x, block[t]) for x, t in states[s].items() if t in alive)) for s in alive}
+            numbers = {}
+            new = {s: numbers.setdefault(sig, len(numbers)) for s, sig in signatures.items()}
+            done = len(numbers) == len(set(block.values()))
+            block = new
+            if done:
+                break
+        edges = {block[s]: {x: block[t] for x, t in states[s].items() if t in alive} for s in alive}
+        return edges, block[start], {block[s] for s in alive if s[0]}
+
+    def check(self, g):
+        """Every rule of the compiled grammar has these states: reached by the same symbols, ending the rule alike."""
+        names = [g.rule_name(r) for r in range(g.num_rules)]
+        states = {n: {} for n in names}
+        for node in range(g.num_nodes):
+            name = names[g.node_rule(node)]
+            edges, at, final = self.automata[name]
+            for x in g.node_path(node):
+                at = edges[at][x]
+            assert at not in states[name], (name, node, states[name][at])
+            states[name][at] = node
+            assert g.node_is_final(node) == (at in final), (name, node)
+        for n in names:
+            assert len(states[n]) == len(self.automata[n][0]), n
+
+    def text(self):
+        def show(e):
+            kind = e[0]
+            if kind == "bytes":
+                return f"[{chr(e[1])}-{chr(e[2])}]"
+            if kind == "lit":
+                return '"' + e[1].decode() + '"'
+            if kind == "ref":
+                return e[1]
+            if kind in ("seq", "alt"):
+                return "(" + (" " if kind == "seq" else " | ").join(map(show, e[1])) + ")"
+            return "(" + show(e[1]) + ")" + {"star": "*", "opt": "?", "plus": "+"}[kind]
+        return "\n".join(f"{r} ::= {show(e)}" for r, e in self.rules.items())
+
+
+@pytest.mark.parametrize("loops", [False, True])
+def test_automata_are_the_minimal_ones(loops):
+    """Random rules, with and without loops (those without are minimised from the end, and not at all where no two states
+    have equally long ways to an end), against the reference construction; a literal in ten has hundreds of bytes."""
+    rng = np.random.Generator(np.random.PCG64(77 + loops))
+    n_long = n_merged = n_chain = 0
+    for _ in range(150):
+        n_rules = int(rng.integers(1, 6))
+        names = ["root"] + [f"r{k}" for k in range(1, n_rules)] + ["ws", "dead"]
+        rules = {}
+
+        def literal(longest):
+            n = int(rng.integers(200, longest)) if rng.random() < 0.1 else int(rng.integers(1, 4))
+            return ("lit", bytes(rng.integers(97, 97 + (2 if n < 4 else 26), size=n).astype(np.uint8)))
+
+        def expression(k, depth):
+            x = rng.random()
+            if depth == 0 or x < 0.3:
+                if x < 0.08:
+                    lo = int(rng.integers(97, 101))
+                    return ("bytes", lo, lo + int(rng.integers(0, 3)))
+                if x < 0.25 and k + 1 < len(names):
+                    return ("ref", names[int(rng.integers(k + 1, len(names)))])
+                return literal(1000 if not loops else 400)
+            if x < 0.7:
+                return ("seq", [expression(k, depth - 1) for _ in range(int(rng.integers(2, 5)))])
+            if x < 0.9 or not loops:
+                return ("alt" if x < 0.9 else "opt", [expression(k, depth - 1) for _ in range(int(rng.integers(2, 4)))] if x < 0.9 else expression(k, depth - 1))
+            return (str(rng.choice(["star", "plus", "opt"])), expression(k, depth - 1))
+
+        for k in range(n_rules):
+            rules[names[k]] = ("seq", [expression(k, 3), ("ref", names[k + 1])]) if k + 1 < n_rules else expression(k, 3)
+        rules["ws"] = ("star", ("lit", b" "))
+        rules["dead"] = ("seq", [("lit", b"x"), ("ref", "dead")])
+        want = _ReferenceRules(rules)
+        text = want.text()
+        if "root" not in want.productive:
+            with pytest.raises(xgm.XgmError) as e:
+                xgm.Grammar(text, "root")
+            assert e.value.status == -5
+            continue
+        g = _compiled(text)
+        want.check(g)
+        n_long += len(text) > 256
+        for r in range(g.num_rules):
+            edges = want.automata[g.rule_name(r)][0]
+            n_merged += len(edges) < len(want._sets(rules[g.rule_name(r)])[0])
+            n_chain += len(edges) > 200
+    assert n_long > 20 and n_chain > 20 and n_merged > 20, (n_long, n_chain, n_merged)
+
+
 def test_binding_refuses_what_is_no_number_and_keeps_a_sequence_alive():
     """The calls that csrc/pybinding.cpp marshals take what ctypes and int() take, and no more."""
     v = xgm.Vocab(np.frombuffer(b"123", dtype=np.uint8), np.arange(4, dtype=np.int64), [])
