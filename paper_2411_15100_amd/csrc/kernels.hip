@@ -475,6 +475,13 @@ __device__ __forceinline__ void for_each_token(const DevVocab& voc, uint32_t ite
       if (x[q]) each((bool)((x[q] >> lane) & 1ull), id[q], (uint32_t)__popcll(x[q] & below), (uint32_t)__popcll(x[q]));
   }
 }
+// What the lanes of a wave have written to LDS in front of this is there for all of them behind it (the hardware keeps a wave's
+// LDS operations in order: this is for the compiler).  All lanes of a wave call it together.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 __device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
 #pragma unroll
   for (uint32_t d = 1; d < 64u; d <<= 1) v += __shfl_xor(v, d, 64);
@@ -1083,7 +1090,8 @@ __global__ __launch_bounds__(kContextThreads) void context_level1_kernel(DevTabl
         }
         if (WRITE) continue;
         if (a.outcomes) a.outcomes[(size_t)q * 64u + lane] = (uint16_t)outcome;
-        if (__ballot(outcome != 0u))
+        if (__ballot(outcome != 0u)) {
+          wave_sync();
           for (uint32_t s = lane; s < n_seg; s += 64u) {
             const uint32_t n = mine[s];
             if (n) {
@@ -1091,6 +1099,8 @@ __global__ __launch_bounds__(kContextThreads) void context_level1_kernel(DevTabl
               mine[s] = 0u;
             }
           }
+          wave_sync();
+        }
       }
   };
   if (small_sections_staged(tab)) body(LdsTabT<true>(tab, smem));
@@ -1112,8 +1122,11 @@ __global__ __launch_bounds__(kOpenWriteThreads) void context_level1_write_kernel
     const uint32_t key = a.key0[0] + a.k_base[0][a.base_node[e0]] + i;
     const uint32_t id = code ? a.base_ids[e0 + lane] : 0u, kind = (code & 0xFFu) - 1u;
     const uint32_t at = 2u * (id / (uint32_t)kSegTokens) + (kind == kEntryAccepted ? 0u : 1u);
+    wave_sync();  // (the places of the round before have been handed out)
     for (uint32_t s = lane; s < 2u * n_seg; s += 64u) mine[s] = 0u;
+    wave_sync();
     if (code) atomicAdd(&mine[at], 1u);
+    wave_sync();
     for (uint32_t s = lane; s < 2u * n_seg; s += 64u) {
       const uint32_t n = mine[s];
       if (n) {
@@ -1121,6 +1134,7 @@ __global__ __launch_bounds__(kOpenWriteThreads) void context_level1_write_kernel
         mine[s] = (s & 1u) ? atomicSub(&a.back[slot], n) - n : atomicAdd(&a.front[slot], n);
       }
     }
+    wave_sync();
     if (code) a.entries[atomicAdd(&mine[at], 1u)] = id | ((code >> 8) << kEntryPosShift) | (kind << kEntryKindShift);
   }
 }

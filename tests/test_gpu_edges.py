@@ -523,6 +523,43 @@ def test_contexts_and_pairs_of_all_counts(xgm, wl, m, pairs):
     assert np.array_equal(d_mask.cpu().numpy(), oracle.pack_bitmask(np.stack(want)))
 
 
+# Neighbours in byte-sorted order with ids in different segments: the 64 pairs that a wave of the list kernels takes add to the
+# counters of up to 64 segments, of accepted and of walk entries (with more than 32 segments a lane has several counters), and
+# every wave takes many such groups, one after the other.
+@pytest.mark.parametrize("depth", [0, 1, 2])
+@pytest.mark.parametrize("V", [5000, 9000, 300000])
+def test_lists_over_many_segments(xgm, wl, V, depth):
+    m, seed = 24, V + depth
+    text = 'root ::= item (";" item)*\nws ::= " "+\nitem ::= ' + " | ".join(f'"{rule_word(k)}" ws "{rule_word(5 * k)}" ws' for k in range(m))
+    text += ' | "(" ws root ")"'
+    toks = [bytes([c]) for c in b"();. abcdefghij"] + [b" " * k for k in (2, 3, 17)]
+    for k in range(m):
+        for j in range(40):   # (tokens that end in the second word, behind it, and behind one to three brackets)
+            toks += [b" " + rule_word(5 * k).encode() + b" " * (j % 3) + b")" * (j // 3 % 4) + (b";" + rule_word(j % m).encode()) * (j // 12 % 2) + b" " * (j % 7)]
+        toks += [b" " * (k % 3) + rule_word(5 * k)[:n].encode() for n in range(1, len(rule_word(5 * k)) + 1)]
+    toks += [b" " * k + b";" + rule_word(j).encode() for k in range(8) for j in range(m)] + [b" " * (k % 9) + b")" * (k // 9 + 1) for k in range(90)]
+    toks = list(dict.fromkeys(toks))
+    toks += [b"~%d" % k for k in range(V - 1 - len(toks))]
+    order = np.random.Generator(np.random.PCG64(seed)).permutation(len(toks))
+    toks = [toks[k] for k in order] + [b""]
+    vocab = Vocab(np.frombuffer(b"".join(toks), dtype=np.uint8).copy(), np.cumsum([0] + [len(t) for t in toks]).astype(np.int64),
+                  np.array([len(toks) - 1], dtype=np.int32))
+    assert vocab.size == V
+    cache, og = xgm.Cache(xgm.Grammar(text, "root"), wl.make_xgm_vocab(vocab), depth=depth), oracle.Grammar(text, "root")
+    assert depth == 0 or cache.debug_walk_entries() > 0
+    ms, want = [], []
+    for k in (0, 5, m - 1):
+        for start in (rule_word(k) + " ", rule_word(k) + " " + rule_word(5 * k) + " ", "( ( ( " + rule_word(k) + " " + rule_word(5 * k) + " "):
+            ms.append(xgm.Matcher(cache=cache))
+            ms[-1].accept_bytes(start.encode())
+            om = oracle.EarleyMatcher(og)
+            assert om.advance(start.encode())
+            want.append(om.mask(vocab))
+    d_mask = torch.full((len(ms), xgm.bitmask_words(V)), -1, dtype=torch.int32, device="cuda")
+    xgm.fill_next_token_bitmask(ms, d_mask.data_ptr(), _stream())
+    assert np.array_equal(d_mask.cpu().numpy(), oracle.pack_bitmask(np.stack(want)))
+
+
 # Few walks of a row go to waves, unless a cache of the batch (the markup grammar's) is known to walk to the limits.
 @pytest.mark.parametrize("V", [4096, 32000])
 def test_walks_by_waves_and_by_lanes(xgm, wl, V):
