@@ -6,7 +6,7 @@
 #include <atomic>
 #include <chrono>
 #include <cstring>
-#include <deque>
+#include <memory>
 #include <mutex>
 #include <numeric>
 #include <string>
@@ -111,7 +111,7 @@ T* slab_upload(const std::vector<T>& v) {
 // Temporary device memory of the cache builds: one block that is reused by every build and grows to what
 // the largest build so far needed (allocating and freeing two dozen arrays per build costs more than the
 // kernels of a small grammar take).  Builds are serialised by `mu`.  The same for the pinned host memory that their
-// copies go through, of which at most kPinned bytes are kept.
+// copies go through, of which there are kPinned bytes.
 class TempArena {
  public:
   std::mutex mu;
@@ -132,8 +132,6 @@ class TempArena {
   void reset() {
     for (void* p : extra_) (void)hipFree(p);
     extra_.clear();
-    for (void* p : pinned_extra_) (void)hipHostFree(p);
-    pinned_extra_.clear();
     pinned_used_ = 0;
     host_keep_.clear();
     if (wanted_ > cap_) {
@@ -148,27 +146,24 @@ class TempArena {
   }
   template <class T>
   T* array(size_t n) { return static_cast<T*>(alloc(std::max<size_t>(n, 1) * sizeof(T))); }
-  // pinned host memory, until reset()
-  char* pinned(size_t bytes) {
+  // Host memory that copies go through, until reset(): pinned, or pageable where there is no room left (to free pinned
+  // memory the host waits for everything that the device does, on all streams).
+  char* staging(size_t bytes) {
     bytes = std::max<size_t>((bytes + 255) & ~(size_t)255, 256);
-    if (!pinned_ && bytes <= kPinned) hip_check(hipHostMalloc(&pinned_, kPinned), "hipHostMalloc");
-    if (pinned_ && pinned_used_ + bytes <= kPinned) {
-      char* p = (char*)pinned_ + pinned_used_;
-      pinned_used_ += bytes;
-      return p;
-    }
-    void* p = nullptr;
-    hip_check(hipHostMalloc(&p, bytes), "hipHostMalloc");
-    pinned_extra_.push_back(p);
-    return (char*)p;
+    if (bytes > kPinned - pinned_used_) return keep(bytes);
+    if (!pinned_) hip_check(hipHostMalloc(&pinned_, kPinned), "hipHostMalloc");
+    char* p = (char*)pinned_ + pinned_used_;
+    pinned_used_ += bytes;
+    return p;
   }
   // (the host bytes are kept until reset(), so that the copy may run whenever the stream gets to it)
   template <class T>
   T* upload(const std::vector<T>& v, hipStream_t stream) {
     T* p = array<T>(v.size());
     if (!v.empty()) {
-      host_keep_.emplace_back((const char*)v.data(), (const char*)v.data() + v.size() * sizeof(T));
-      hip_check(hipMemcpyAsync(p, host_keep_.back().data(), v.size() * sizeof(T), hipMemcpyHostToDevice, stream), "hipMemcpyAsync");
+      char* const h = keep(v.size() * sizeof(T));
+      std::memcpy(h, v.data(), v.size() * sizeof(T));
+      hip_check(hipMemcpyAsync(p, h, v.size() * sizeof(T), hipMemcpyHostToDevice, stream), "hipMemcpyAsync");
     }
     return p;
   }
@@ -180,16 +175,20 @@ class TempArena {
   static constexpr size_t kPinned = (size_t)8 << 20;
   void* pinned_ = nullptr;
   size_t pinned_used_ = 0;
-  std::vector<void*> pinned_extra_;
-  std::deque<std::vector<char>> host_keep_;
+  std::vector<std::unique_ptr<char[]>> host_keep_;
+  char* keep(size_t bytes) {
+    host_keep_.push_back(std::unique_ptr<char[]>(new char[bytes]));
+    return host_keep_.back().get();
+  }
 };
 TempArena& temp_arena() {
   static TempArena a;
   return a;
 }
 
-// Host arrays that go to the device in one copy, through pinned memory (an array copied by itself from pageable memory
-// keeps the host for 12 us, however small it is, and a build has some twenty of them).  They are read by send().
+// Host arrays that go to the device in one copy, through pinned memory if there is room (an array copied by itself from
+// pageable memory keeps the host for 12 us, however small it is, and a build has some twenty of them).  They are read by
+// send().
 class Parts {
  public:
   size_t add(const void* src, size_t bytes, size_t align = 256) {
@@ -202,7 +201,7 @@ class Parts {
   size_t add(const std::vector<T>& v) { return add(v.data(), v.size() * sizeof(T)); }
   size_t bytes() const { return bytes_; }
   void send(void* dst, TempArena& arena, hipStream_t stream) const {
-    char* const h = arena.pinned(bytes_);
+    char* const h = arena.staging(bytes_);
     for (const Part& p : parts_)
       if (p.bytes) std::memcpy(h + p.at, p.src, p.bytes);
     if (bytes_) hip_check(hipMemcpyAsync(dst, h, bytes_, hipMemcpyHostToDevice, stream), "hipMemcpyAsync");
@@ -789,7 +788,7 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
     uint32_t* d_n_pairs = d_plain_count + N;
     uint32_t* d_n_bitset_nodes = d_n_pairs + 1;
     OverflowLog* log = reinterpret_cast<OverflowLog*>(d_stats + log_at);
-    const char* const h_stats = arena.pinned(stat_bytes);
+    const char* const h_stats = arena.staging(stat_bytes);
     HIP_OK(hipMemsetAsync(d_plain_count, 0, stat_bytes - plain_at, stream));
     {
       std::lock_guard<std::mutex> lock(ctx().mu);
@@ -1065,7 +1064,7 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
     const size_t open_at = 8, made_at = 16, equal_at = made_at + 16, counts_at = (equal_at + (size_t)N * 4 + 15) / 16 * 16;
     static_assert((kCtxLevels + 1) * 4 <= 16, "the counters of the list kernels");
     char* const d_found = static_cast<char*>(arena.alloc(counts_at + n_slots * 4));
-    const char* const h_found = arena.pinned(counts_at);
+    const char* const h_found = arena.staging(counts_at);
     uint32_t* d_equal = reinterpret_cast<uint32_t*>(d_found + equal_at);
     uint32_t* d_counts = reinterpret_cast<uint32_t*>(d_found + counts_at);
     args.n_open = reinterpret_cast<uint32_t*>(d_found + open_at);

@@ -630,6 +630,40 @@ def test_fills_are_forgotten_only_when_they_are_done(xgm, wl, form, rows):
     assert np.array_equal(d_mask.cpu().numpy(), np.tile(oracle.pack_bitmask(want), (rows, 1)))
 
 
+# A build does not wait for what other streams do (once its temporary memory is there), also where its tables take more than
+# the pinned memory that the builds share: a rule used in n places of a rule that is used in n places has n * n contexts two
+# frames down, 9 MB of keys for 1500.
+@pytest.mark.parametrize("n", [100, 1500])
+def test_builds_do_not_wait_for_other_streams(xgm, wl, n):
+    text = "root ::= " + " ".join(f'w "{k:05d}"' for k in range(n)) + "\nw ::= " + " ".join(f'"{k:05d}" v' for k in range(n)) + "\nv ::= [a-z]+"
+    vocab = si.make_vocab("bpe", 4096, 0)
+    xv, g = wl.make_xgm_vocab(vocab), xgm.Grammar(text, "root")
+    big = torch.empty(1 << 28, dtype=torch.int32, device="cuda")   # 1 GiB: 0.15 ms to fill
+    waited = []
+    for _ in range(6):
+        # (a stream that shares its hardware queue with the other one waits for that; not all of them do)
+        own, other = torch.cuda.Stream(), torch.cuda.Stream()
+        for _ in range(2):
+            cache = xgm.Cache(g, xv, int(own.cuda_stream))
+        torch.cuda.synchronize()
+        with torch.cuda.stream(other):
+            for k in range(600):
+                big.fill_(k)
+            after = torch.cuda.Event()
+            after.record()
+        cache = xgm.Cache(g, xv, int(own.cuda_stream))
+        waited.append(after.query())
+        torch.cuda.synchronize()
+    assert not all(waited)
+    start = b"00000abc00001de" + b"".join(b"%05dx" % k for k in range(2, n)) + b"00000" + b"00000y"
+    m, om = xgm.Matcher(cache=cache), oracle.EarleyMatcher(oracle.Grammar(text, "root"))
+    m.accept_bytes(start)
+    assert om.advance(start)
+    d_mask = torch.full((1, xgm.bitmask_words(4096)), -1, dtype=torch.int32, device="cuda")
+    xgm.fill_next_token_bitmask([m], d_mask.data_ptr(), _stream())
+    assert np.array_equal(d_mask.cpu().numpy()[0], oracle.pack_bitmask(om.mask(vocab)))
+
+
 # Fills on more streams than the library remembers launches of (4), in turn: those of the others are staged; after a thousand
 # fills on one stream the others' places are taken over.
 def test_fills_on_many_streams(xgm, wl):
