@@ -252,7 +252,10 @@ struct xgm_cache {
   std::vector<void*> dev_ptrs;
   // host copies of what packing a stack header needs (see DevCache)
   std::vector<uint16_t> acc_row_host;  // [n_nodes]
+  std::vector<uint32_t> level0_host;   // [n_nodes + 1] where the accepted tokens of the nodes that list them lie in `entries`
   std::vector<uint32_t> k_base_host[kCtxLevels];  // [n_nodes] (kNoKey for a node without context-dependent tokens), [n_k[0]], ...
+  std::mutex key_off_mu;
+  std::vector<uint32_t> key_off_host;  // [n_keys * n_seg + 1], or empty (see xgm_debug_matcher_fill_work)
   int levels = 0;                      // levels of per-context lists kept (<= kCtxLevels)
   std::vector<uint32_t> unc_count;     // [n_nodes] context-dependent tokens
   int32_t n_acc_rows = 0;
@@ -937,10 +940,10 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
     // ---- accepted tokens: a node with few of them keeps a list (its level-0 key), the others a bitset row;
     // every distinct row is kept once (rows with equal digests are compared with the first of them)
     std::vector<char> as_list((size_t)N, 0);
-    uint64_t n_level0 = 0;
+    c->level0_host.assign((size_t)N + 1, 0u);  // (the level-0 keys are the first, and the others of them have no entries)
     for (int32_t n = 0; n < N; ++n) {
       as_list[n] = kept_as_list(acc_counts[n], dv.W);
-      if (as_list[n]) n_level0 += acc_counts[n];
+      c->level0_host[n + 1] = c->level0_host[n] + (as_list[n] ? acc_counts[n] : 0u);
     }
     std::vector<int32_t> rep((size_t)N);
     {
@@ -1194,7 +1197,7 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
     c->stats[1] = (int64_t)n_k[0];
     c->stats[2] = (int64_t)(n_keys - (uint64_t)N - n_k[0]);
     c->stats[3] = (int64_t)total;
-    c->stats[4] = (int64_t)n_level0;
+    c->stats[4] = (int64_t)c->level0_host[N];
     c->stats[5] = (int64_t)n_base;
     c->stats[6] = (int64_t)n_items;
     c->stats[7] = (int64_t)c->n_acc_rows;
@@ -1253,9 +1256,7 @@ int xgm_cache_copy_node_bits(const xgm_cache* c, int32_t node, int32_t* h_acc, i
       HIP_OK(hipMemcpy(h_acc, c->host.acc + (size_t)c->acc_row_host[node] * dv.W, (size_t)dv.W * 4, hipMemcpyDeviceToHost));
     } else {  // the node keeps its accepted tokens as a list (its level-0 key)
       std::memset(h_acc, 0, (size_t)dv.W * 4);
-      uint32_t j0 = 0u, j1 = 0u;
-      HIP_OK(hipMemcpy(&j0, c->host.key_off + (size_t)node * dv.n_seg, 4, hipMemcpyDeviceToHost));
-      HIP_OK(hipMemcpy(&j1, c->host.key_off + (size_t)(node + 1) * dv.n_seg, 4, hipMemcpyDeviceToHost));
+      const uint32_t j0 = c->level0_host[node], j1 = c->level0_host[node + 1];
       std::vector<uint32_t> list(j1 - j0);
       if (j1 > j0) HIP_OK(hipMemcpy(list.data(), c->host.entries + j0, (size_t)(j1 - j0) * 4, hipMemcpyDeviceToHost));
       for (uint32_t e : list) {
@@ -1629,23 +1630,30 @@ static int fill_impl(xgm_matcher* const* ms, int32_t B, int32_t* d_bitmask, void
   API_END
 }
 
+// where the entries of every list begin, on the host (copied by a cache's first call)
+static const std::vector<uint32_t>& key_offsets(xgm_cache& c) {
+  std::lock_guard<std::mutex> lock(c.key_off_mu);
+  if (c.key_off_host.empty()) {
+    std::vector<uint32_t> off((size_t)c.stats[0] * (size_t)c.v->dv.n_seg + 1);
+    HIP_OK(hipMemcpy(off.data(), c.host.key_off, off.size() * 4, hipMemcpyDeviceToHost));
+    c.key_off_host.swap(off);
+  }
+  return c.key_off_host;
+}
 int xgm_debug_matcher_fill_work(const xgm_matcher* m, int64_t* h_out4) {
   API_BEGIN
   if (!m || !m->c || !h_out4) return fail(XGM_ERR_BAD_ARG, "matcher_fill_work: null argument or a matcher without a cache");
   for (int k = 0; k < 4; ++k) h_out4[k] = 0;
   if (m->terminated) return XGM_OK;
   const size_t n_seg = (size_t)m->v->dv.n_seg;
+  const std::vector<uint32_t>& key_off = key_offsets(*m->c);
   uint32_t h[kStackKeysWords];
   for (const Stack& s : m->stacks) {
     pack_stack_keys(m->g->A, *m->c, s, 0u, h);
     if ((h[kStackHdrTop] >> 16) != kNoAccRow) ++h_out4[0];
     for (uint32_t l = 0; l < kStackLists; ++l) {
       const uint32_t key = h[kStackHdrWords + l];
-      uint32_t j0 = 0u, j1 = 0u;
-      if (key == kNoKey) continue;
-      HIP_OK(hipMemcpy(&j0, m->c->host.key_off + key * n_seg, 4, hipMemcpyDeviceToHost));
-      HIP_OK(hipMemcpy(&j1, m->c->host.key_off + (key + 1) * n_seg, 4, hipMemcpyDeviceToHost));
-      h_out4[1 + std::min<uint32_t>(l, 2u)] += j1 - j0;
+      if (key != kNoKey) h_out4[1 + std::min<uint32_t>(l, 2u)] += key_off[(key + 1) * n_seg] - key_off[key * n_seg];
     }
   }
   return XGM_OK;

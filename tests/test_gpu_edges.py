@@ -3,6 +3,7 @@ level, a tile or a segment begins, ends or is just full.  Expected masks come
 from the CPU oracle."""
 
 import itertools
+import time
 
 import numpy as np
 import pytest
@@ -558,6 +559,31 @@ def test_lists_over_many_segments(xgm, wl, V, depth):
     d_mask = torch.full((len(ms), xgm.bitmask_words(V)), -1, dtype=torch.int32, device="cuda")
     xgm.fill_next_token_bitmask(ms, d_mask.data_ptr(), _stream())
     assert np.array_equal(d_mask.cpu().numpy(), oracle.pack_bitmask(np.stack(want)))
+
+
+# What a cache tells about a node is one copy, whether the node lists its accepted tokens or keeps a bitset; what it tells about
+# a matcher's state takes the device only once.
+def test_a_cache_is_read_with_few_copies(xgm, wl):
+    vocab = si.make_vocab("bpe", 32000, 0)
+    cache = xgm.Cache(xgm.Grammar(si.JSON_GRAMMAR, "root"), wl.make_xgm_vocab(vocab))
+
+    def median(call):
+        times = []
+        for _ in range(101):
+            t0 = time.perf_counter()
+            call()
+            times.append(time.perf_counter() - t0)
+        return sorted(times)[50]
+
+    accepted = [int(oracle.unpack_bitmask(cache.copy_node_bits(n, with_uncertain=False)[0], vocab.size).sum()) for n in range(cache.num_nodes)]
+    listed = [n for n, k in enumerate(accepted) if k * 2 <= xgm.bitmask_words(vocab.size)]
+    assert 0 < len(listed) < cache.num_nodes and max(accepted[n] for n in listed) > 0
+    nodes = max(listed, key=lambda n: accepted[n]), max(range(cache.num_nodes), key=lambda n: accepted[n])
+    of_list, of_bitset = (median(lambda: cache.copy_node_bits(n, with_uncertain=False)) for n in nodes)
+    assert of_list < 2 * of_bitset
+    m = xgm.Matcher(cache=cache)
+    m.accept_bytes(b'{"a": [1, "x')
+    assert median(m.debug_fill_work) < of_bitset
 
 
 # Few walks of a row go to waves, unless a cache of the batch (the markup grammar's) is known to walk to the limits.
