@@ -456,19 +456,24 @@ def test_classes_of_tokens_that_share_prefixes(xgm, wl, run, words, nodes):
 
 
 # A build keeps only the words of its rank-space rows that are not zero, unless it keeps the context-dependent bitsets too or
-# goes through the nodes in batches: the same caches from all three, and the same masks; vocabularies that end anywhere in an
-# item of 64 tokens, in 64 items and in 64 times 64 of them.
-@pytest.mark.parametrize("V", [37, 64, 65, 511, 4095, 4097, 8193, 262145])
+# goes through the nodes in batches (of 32 here, the last one smaller): the same caches from all three, and the oracle's masks;
+# vocabularies that end anywhere in an item of 64 tokens, in 64 items and in 64 times 64 of them, and the largest one.
+@pytest.mark.parametrize("V", [37, 64, 65, 511, 4095, 4097, 8193, 262145, 589824])
 @pytest.mark.parametrize("family", ["json", "words"])
 def test_builds_of_all_kinds_give_the_same_cache(xgm, wl, family, V):
-    text = si.JSON_GRAMMAR if family == "json" else 'root ::= ([a-z] [a-z]* | [0-9]+ | " ")* "." | "(" root ")" tail\ntail ::= ("," root)*'
+    text, nodes = si.JSON_GRAMMAR, 74
+    if family == "words":
+        n, nodes = 18, 101
+        text = 'root ::= ([a-z] [a-z]* | [0-9]+ | " " | "-" word)* "." | "(" root ")" tail\ntail ::= ("," root)*\nword ::= '
+        text += " | ".join(f"w{k}" for k in range(n)) + "".join(f'\nw{k} ::= "{rule_word(7 * k)}" " "* [0-9]' for k in range(n))
     chars = bytes(range(33, 127)) if V > 50000 else b'{}[]:,"0123456789.E+- ()abcdefgxyz\\'
     toks = [bytes(t) for n in (1, 2, 3) for t in itertools.islice(itertools.product(chars, repeat=n), V)]
     toks = (toks[:V - 1] if V < 50000 else toks[:V - 1] + [b"%d" % k for k in range(10 ** 6, 10 ** 6 + max(0, V - 1 - len(toks)))]) + [b""]
     vocab = Vocab(np.frombuffer(b"".join(toks), dtype=np.uint8).copy(), np.cumsum([0] + [len(t) for t in toks]).astype(np.int64),
                   np.array([len(toks) - 1], dtype=np.int32))
     assert vocab.size == V and len(set(toks)) == V
-    g, xv = xgm.Grammar(text, "root"), wl.make_xgm_vocab(vocab)
+    g, og, xv = xgm.Grammar(text, "root"), oracle.Grammar(text, "root"), wl.make_xgm_vocab(vocab)
+    assert g.num_nodes == nodes and nodes > 64 and nodes % 32
     caches = [xgm.Cache(g, xv), xgm.Cache(g, xv, keep_plain=True)]
     xgm.debug_set_build_batch_nodes(32)
     try:
@@ -482,17 +487,24 @@ def test_builds_of_all_kinds_give_the_same_cache(xgm, wl, family, V):
             assert c.num_uncertain(node) == caches[0].num_uncertain(node)
             assert c.num_uncertain_plain(node) == caches[0].num_uncertain_plain(node)
     assert caches[0].stats == caches[1].stats == caches[2].stats
-    masks = []
-    for c in caches:
+    starts = [b"", b"[", b'{"a', b'{"a":[1', b"[[[-2.", b'["b",']
+    if family == "words":
+        starts = [b"", b"a", b"(12", b"((b ", b"(c.)", b"(c.),d", b"(a -", b"-h", b"((-aaa  ", b"(-aaa 1-haa"]
+    want = []
+    for start in starts:
+        om = oracle.EarleyMatcher(og)
+        assert om.advance(start)
+        want.append(om.mask(vocab))
+    want = oracle.pack_bitmask(np.stack(want))
+    for kind, c in enumerate(caches):
         ms = []
-        for start in ([b"", b"[", b'{"a', b'{"a":[1', b"[[[-2.", b'["b",'] if family == "json" else [b"", b"a", b"(12", b"((b ", b"(c.)", b"(c.),d"]):
+        for start in starts:
             ms.append(xgm.Matcher(cache=c))
             if start:
                 ms[-1].accept_bytes(start)
         d_mask = torch.full((len(ms), xgm.bitmask_words(V)), -1, dtype=torch.int32, device="cuda")
         xgm.fill_next_token_bitmask(ms, d_mask.data_ptr(), _stream())
-        masks.append(d_mask.cpu().numpy())
-    assert np.array_equal(masks[0], masks[1]) and np.array_equal(masks[0], masks[2])
+        assert np.array_equal(d_mask.cpu().numpy(), want), kind
 
 
 # The list kernels take the pairs of a node 64 at a time and the contexts of its rule 64 and 256 at a time: a rule in m places,
