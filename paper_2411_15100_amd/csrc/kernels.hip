@@ -2523,18 +2523,10 @@ void launch_context_lists(const DevTables& tab, const DevVocab& voc, const Conte
   const DevTables st = staged_for(tab, kContextLdsBudget);
   const dim3 g2(1024);
   if (write && args.outcomes) {
-    // Level 1 from the kept outcomes; its records for level 2 are still there from the counting pass, and so
-    // are the deeper levels' records if their outcomes were kept too (levels that walk again make the records
-    // of the next level again: those counts start at zero).
+    // from the kept outcomes: the records of all levels are still there from the counting pass
     hipLaunchKernelGGL(context_level1_write_kernel, dim3(2048), dim3(kOpenWriteThreads), 0, stream, voc, args);
-    bool deep = true;  // all deeper levels from kept outcomes, or all of them by walking again
     for (uint32_t level = 2; level <= (uint32_t)kCtxLevels && args.k_base[level - 1] != nullptr; ++level)
-      deep = deep && args.deep_outcomes[level - 1] != nullptr;
-    if (!deep) (void)hipMemsetAsync(args.res_count + 1, 0, 4 * (kCtxLevels - 1), stream);
-    for (uint32_t level = 2; level <= (uint32_t)kCtxLevels && args.k_base[level - 1] != nullptr; ++level) {
-      if (deep) hipLaunchKernelGGL(context_deeper_write_kernel, g2, dim3(256), 0, stream, voc, args, level);
-      else hipLaunchKernelGGL(context_deeper_kernel<true>, g2, dim3(kContextThreads), st.stage_bytes, stream, st, voc, args, level);
-    }
+      hipLaunchKernelGGL(context_deeper_write_kernel, g2, dim3(256), 0, stream, voc, args, level);
     return;
   }
   // the tiles whose contexts fit the list, if all of them have to be listed, at a time

@@ -374,8 +374,8 @@ struct ContextListArgs {
   // (kind + 1) | pos << 8.
   uint16_t* outcomes;
   // The same for the deeper levels: deep_outcomes[l][r] holds the outcomes (8 x 16 bits, coded as above) of
-  // record r of res[l - 1], that is of level l + 1, for the contexts of the record's chunk; null: the writing
-  // pass of that level walks again.  Used together with `outcomes` only.
+  // record r of res[l - 1], that is of level l + 1, for the contexts of the record's chunk.  There for every level that
+  // is kept if `outcomes` is, null otherwise.
   uint4* deep_outcomes[kCtxLevels];
 };
 // Where the entries of every slot (key, segment) begin: the running sum of the counts, in key_off (n_slots + 1 words) and
