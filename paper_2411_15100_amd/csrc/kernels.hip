@@ -210,6 +210,13 @@ __device__ __forceinline__ RankedToken load_ranked(const DevVocab& voc, int32_t 
   return t;
 }
 
+// How many bytes two tokens have in common in front of the first that differs, of the 15 that their words hold (behind the end
+// of a token these are 0).
+__device__ __forceinline__ int same_bytes(const uint4 a, const uint4 b) {
+  const uint32_t d0 = a.x ^ b.x, d1 = a.y ^ b.y, d2 = a.z ^ b.z, d3 = (a.w ^ b.w) | 0xFF000000u;
+  return (d0 ? __ffs((int)d0) - 1 : d1 ? __ffs((int)d1) + 31 : d2 ? __ffs((int)d2) + 63 : __ffs((int)d3) + 95) / 8;
+}
+
 // What a workgroup of the classify kernel keeps beside the tables.
 struct ClassifyShared {
   uint32_t next_item, first_pair;
@@ -267,12 +274,10 @@ __device__ __forceinline__ void classify_body(const Tab& T, ClassifyShared& sm, 
       if (__popcll(run) >= kPrefixTokens && (needs & (needs - 1ull)) && !too_long) {
         const int last = 63 - __clzll((long long)run);
         auto of = [&](uint32_t v, int l) { return (uint32_t)__builtin_amdgcn_readlane((int)v, l); };
-        const uint4 pre = make_uint4(of(t.tk.x, first), of(t.tk.y, first), of(t.tk.z, first), of(t.tk.w, first));
+        auto token = [&](int l) { return make_uint4(of(t.tk.x, l), of(t.tk.y, l), of(t.tk.z, l), of(t.tk.w, l)); };
+        const uint4 pre = token(first);
         const int shortest = (int)min(of((uint32_t)t.len, first), of((uint32_t)t.len, last));
-        const uint32_t d0 = pre.x ^ of(t.tk.x, last), d1 = pre.y ^ of(t.tk.y, last), d2 = pre.z ^ of(t.tk.z, last);
-        const uint32_t d3 = (pre.w ^ of(t.tk.w, last)) | 0xFF000000u;
-        const int same = (d0 ? __ffs((int)d0) - 1 : d1 ? __ffs((int)d1) + 31 : d2 ? __ffs((int)d2) + 63 : __ffs((int)d3) + 95) / 8;
-        const int n = min(same, shortest);
+        const int n = min(same_bytes(pre, token(last)), shortest);
         if (n >= 2 && walk) {
           const int res = walk_token<true>(T, pre, voc.bytes, n, own_node, (const uint16_t*)nullptr, 1u, nullptr, T.follow_of(own_node));
           if (res == kUncertain) keep_u |= run;
@@ -985,11 +990,7 @@ __global__ __launch_bounds__(kContextThreads) void context_open_kernel(DevTables
           const uint4 pre = make_uint4(of(t.tk.x), of(t.tk.y), of(t.tk.z), of(t.tk.w));
           // what the tokens of the run have in common with the first of them
           uint32_t same = 15u;
-          if ((run >> lane) & 1ull) {
-            const uint32_t d0 = t.tk.x ^ pre.x, d1 = t.tk.y ^ pre.y, d2 = t.tk.z ^ pre.z, d3 = (t.tk.w ^ pre.w) | 0xFF000000u;
-            same = (uint32_t)(d0 ? __ffs((int)d0) - 1 : d1 ? __ffs((int)d1) + 31 : d2 ? __ffs((int)d2) + 63 : __ffs((int)d3) + 95) / 8u;
-            same = min(same, (uint32_t)t.len);
-          }
+          if ((run >> lane) & 1ull) same = min((uint32_t)same_bytes(t.tk, pre), (uint32_t)t.len);
 #pragma unroll
           for (uint32_t d = 1; d < 64u; d <<= 1) same = min(same, (uint32_t)__shfl_xor((int)same, d, 64));
           same = uniform(same);
