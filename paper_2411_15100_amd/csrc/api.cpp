@@ -1919,8 +1919,8 @@ PackedState pack_state(const xgm_batch& bt, int32_t row, int32_t slot, const xgm
   p.row.flags = p.meta.flags & 1u;
   return p;
 }
-// `epoch`: the row's count of state changes after this write.  The stack headers are written out on the device:
-// launch_batch_headers() has to follow.
+// `epoch`: the row's count of state changes after this write.  The stack headers are written out on the device, and the
+// slot becomes the row's current one there: launch_batch_headers() has to follow.
 void write_state(const xgm_batch& bt, int32_t row, int32_t slot, PackedState p, uint32_t epoch) {
   const size_t hdr_words = stack_hdr_stride(bt.dev.n_seg);
   const size_t at = (size_t)row * bt.H + slot;
@@ -1976,11 +1976,8 @@ int xgm_batch_create(xgm_matcher* const* ms, int32_t B, int32_t history, void* h
     d.status = keep(dev_alloc<int32_t>(B));
     d.log = keep(new_log());
     HIP_OK(hipMemset(d.meta, 0, slots * sizeof(SlotMeta)));
-    HIP_OK(hipMemset(d.head, 0, (size_t)B * 4));
-    HIP_OK(hipMemset(d.older, 0, (size_t)B * 4));
-    HIP_OK(hipMemset(d.status, 0, (size_t)B * 4));
     for (int32_t b = 0; b < B; ++b) write_state(*bt, b, 0, pack_state(*bt, b, 0, *ms[b]), 0u);
-    launch_batch_headers(d, 0, B, 0, stream);
+    launch_batch_headers(d, 0, B, 0, 0, stream);
     HIP_OK(hipGetLastError());
     HIP_OK(hipStreamSynchronize(stream));
     std::lock_guard<std::mutex> lock(ctx().mu);
@@ -2079,14 +2076,9 @@ int xgm_batch_set_row(xgm_batch* bt, int32_t row, const xgm_matcher* m, void* hi
   HIP_OK(hipMemcpy(&cur, bt->dev.rows + row, sizeof(RowDesc), hipMemcpyDeviceToHost));
   const int32_t next = (head + 1) % bt->H;
   write_state(*bt, row, next, pack_state(*bt, row, next, *m), cur.epoch + 1u);
-  launch_batch_headers(bt->dev, row, 1, next, stream);
+  launch_batch_headers(bt->dev, row, 1, next, std::min(older + 1, bt->H - 1), stream);
   HIP_OK(hipGetLastError());
   HIP_OK(hipStreamSynchronize(stream));
-  older = std::min(older + 1, bt->H - 1);
-  const int32_t ok = XGM_OK;
-  HIP_OK(hipMemcpy(bt->dev.head + row, &next, 4, hipMemcpyHostToDevice));
-  HIP_OK(hipMemcpy(bt->dev.older + row, &older, 4, hipMemcpyHostToDevice));
-  HIP_OK(hipMemcpy(bt->dev.status + row, &ok, 4, hipMemcpyHostToDevice));
   return XGM_OK;
   API_END
 }

@@ -1412,10 +1412,17 @@ __global__ __launch_bounds__(kUploadThreads) void upload_stacks_kernel(const uin
   }
 }
 
-// The same in place: the stacks of the states in one slot of some rows of a batch, a workgroup per (stack, row).
-__global__ __launch_bounds__(64) void batch_headers_kernel(DevBatch bt, int32_t row0, int32_t slot) {
+// The same in place: the stacks of the states in one slot of some rows of a batch, a workgroup per (stack, row).  The rows'
+// scalars are written here too: three copies from the host cost 35 us (a state into a row: 149 us with them, 114 without).
+__global__ __launch_bounds__(64) void batch_headers_kernel(DevBatch bt, int32_t row0, int32_t slot, int32_t older) {
   __shared__ uint32_t keys[kStackKeysWords];
-  const size_t at = (size_t)(row0 + (int32_t)blockIdx.y) * bt.H + slot;
+  const int32_t b = row0 + (int32_t)blockIdx.y;
+  const size_t at = (size_t)b * bt.H + slot;
+  if (blockIdx.x == 0u && threadIdx.x == 0u) {
+    bt.head[b] = slot;
+    bt.older[b] = older;
+    bt.status[b] = 0;
+  }
   if (blockIdx.x >= bt.meta[at].n_stacks) return;
   const uint32_t stride = stack_hdr_stride(bt.n_seg), n_seg = (uint32_t)bt.n_seg;
   uint32_t* const h = bt.hdrs + (at * kBatchMaxStacks + blockIdx.x) * stride;
@@ -2567,9 +2574,9 @@ void launch_upload_stacks(const void* src, void* dst, size_t plain_bytes, const 
                      reinterpret_cast<const uint4*>(src_stacks), n_stacks, (uint32_t)n_seg, reinterpret_cast<uint32_t*>(dst_hdrs));
 }
 
-void launch_batch_headers(const DevBatch& bt, int32_t row0, int32_t n, int32_t slot, hipStream_t stream) {
+void launch_batch_headers(const DevBatch& bt, int32_t row0, int32_t n, int32_t slot, int32_t older, hipStream_t stream) {
   static_assert(kStackKeysWords <= stack_hdr_stride(1), "the key words of a stack lie where its header belongs");
-  hipLaunchKernelGGL(batch_headers_kernel, dim3(kBatchMaxStacks, n), dim3(64), 0, stream, bt, row0, slot);
+  hipLaunchKernelGGL(batch_headers_kernel, dim3(kBatchMaxStacks, n), dim3(64), 0, stream, bt, row0, slot, older);
 }
 
 // Walks take long, and few rows of a batch have many: where the segments alone do not fill the chip four workgroups share

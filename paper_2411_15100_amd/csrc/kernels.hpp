@@ -406,7 +406,8 @@ void launch_upload_stacks(const void* src, void* dst, size_t plain_bytes, const 
                           int32_t n_seg, void* dst_hdrs, const void* src_frames, void* dst_frames, size_t frames_bytes,
                           hipStream_t stream);
 // The same in place for the states in slot `slot` of rows [row0, row0 + n): where a header belongs lie kStackKeysWords words.
-void launch_batch_headers(const DevBatch& bt, int32_t row0, int32_t n, int32_t slot, hipStream_t stream);
+// These are the rows' current states from then on, with `older` ones behind them.
+void launch_batch_headers(const DevBatch& bt, int32_t row0, int32_t n, int32_t slot, int32_t older, hipStream_t stream);
 // (b) batched mask fill: one workgroup per (segment, row)
 // walks: what the walks of the batch's caches need.
 // step_counter: null on the hot path; otherwise the counting instantiation is launched.

@@ -598,6 +598,23 @@ def test_a_cache_is_read_with_few_copies(xgm, wl):
     assert median(m.debug_fill_work) < of_bitset
 
 
+# Putting a state into a row is seven small copies and a launch, taking it out is four copies: at most 2.8 times as long (2.4
+# measured; 3.1 with three more copies for the row's scalars, 2.5 with those and without a launch).
+def test_a_state_goes_into_a_row_with_few_copies(xgm, wl):
+    cache = xgm.Cache(xgm.Grammar(si.JSON_GRAMMAR, "root"), wl.make_xgm_vocab(si.make_vocab("bpe", 151936, 0)))
+    m = xgm.Matcher(cache=cache)
+    m.accept_bytes(b'{"a": [1, {"b": "x')
+    batch = xgm.DeviceBatch([m] * 8, history=4, stream=_stream())
+    times = {batch.set_row: [], batch.get_row: []}
+    for _ in range(200):
+        for call, ts in times.items():
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            call(5, m, _stream())
+            ts.append(time.perf_counter() - t0)
+    assert min(times[batch.set_row]) < 2.8 * min(times[batch.get_row])
+
+
 # Few walks of a row go to waves, unless a cache of the batch (the markup grammar's) is known to walk to the limits.
 @pytest.mark.parametrize("V", [4096, 32000])
 def test_walks_by_waves_and_by_lanes(xgm, wl, V):
