@@ -368,9 +368,9 @@ def main():
         lds_rate = xgm.debug_lds_lookup_rate(stream)
         cache_build = {"lds_dependent_lookups_per_s": lds_rate,
                        "headline": "pairs_per_s_whole_build: positions x tokens per second of the whole xgm_cache_build call "
-                                   "(classification, rank -> id permutation, bitset rows and lists, the per-call-site lists of "
-                                   "section 3.2 three frames deep), best of 3; classification_stage = the part of the call up to the point where "
-                                   "the section 3.1 classes of every node are known (classify kernel, permutation, row statistics, one "
+                                   "(classification, bitset rows and lists, the per-call-site lists of section 3.2 three frames "
+                                   "deep), best of 3; classification_stage = the part of the call up to the point where the section "
+                                   "3.1 classes of every node are known (classify kernels, row statistics, bitset rows, one "
                                    "synchronisation)",
                        "note": "steps_per_s = pairs_per_s x the mean automaton steps per pair of a seeded sample; a "
                                "step is 3 to 5 dependent table lookups (header, follow set, class, shape, target); "

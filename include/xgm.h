@@ -31,7 +31,7 @@
  *    bits at positions >= V are 0.
  *  - The library needs a gfx950 device for everything except vocabulary and
  *    grammar handling and the matcher's host state; there is no CPU path for
- *    the three kernels.
+ *    the kernels.
  */
 #ifndef XGM_H
 #define XGM_H
@@ -204,7 +204,7 @@ int xgm_cache_copy_node_plain(const xgm_cache* c, int32_t node, int32_t* h_plain
  * bounds and were classified exactly on the host instead (0 for every
  * workload shipped with this repository). */
 int64_t xgm_cache_host_classified(const xgm_cache* c);
-/* Seconds the GPU spent in the classification kernel during the build, and
+/* Seconds the GPU spent in the classification kernels during the build, and
  * the number of (node, token) pairs it classified. */
 double xgm_cache_build_kernel_seconds(const xgm_cache* c);
 /* Seconds the whole xgm_cache_build call took on the host clock (all kernels,
@@ -212,14 +212,18 @@ double xgm_cache_build_kernel_seconds(const xgm_cache* c);
  * on the first build that uses it). */
 double xgm_cache_build_seconds(const xgm_cache* c);
 /* The part of those seconds that the classification of section 3.1 took: from the start of the call until
- * every node's accepted and context-dependent tokens lie in id-space bitsets on the device and their
- * per-node statistics on the host (first-byte bitsets, classification kernel, rank -> id permutation with
- * the row statistics, one synchronisation).  The rest of the call resolves the context-dependent tokens
- * per call site (section 3.2) and lays out the lists. */
+ * the class of every (node, token) is known on the device, the per-node statistics are on the host, and the
+ * nodes that accept too many tokens for a list have their bitsets in id space (first-byte bitsets,
+ * classification kernels, row statistics, bitset rows, one synchronisation; a build that keeps the
+ * context-dependent bitsets, or goes through its nodes in batches, has both bitsets of every node in id
+ * space by then).  The rest of the call makes the lists of the other nodes, resolves the context-dependent
+ * tokens per call site (section 3.2) and lays out their lists. */
 double xgm_cache_build_classify_seconds(const xgm_cache* c);
 /* Test knob: the following builds classify their nodes in batches of `nodes` (rounded down to a multiple of
- * 32, at least 32) instead of all at once; 0 restores the default (as many nodes as 1 GiB of rank-space rows
- * holds: every grammar of this repository in one batch).  The caches built are the same. */
+ * 32, at least 32) instead of all at once, and resolve their context-dependent tokens in as many parts as they can be
+ * cut into; 0 restores the default (as many nodes as 1 GiB of rank-space rows holds, and parts of 2^23 (64 pairs,
+ * context): every grammar of this repository in one batch and one part).  The caches built are the same; the builds
+ * take much longer. */
 void xgm_debug_set_build_batch_nodes(int32_t nodes);
 /* Section 3.1 (storage of the cache): number of distinct accepted bitsets kept (nodes with few accepted
  * tokens keep a list instead and are not counted), and the bytes of device memory the cache holds
@@ -229,7 +233,8 @@ int64_t xgm_cache_device_bytes(const xgm_cache* c);
 /* Sizes of the cache, into h_out8 (host, 8 values): [0] list keys in all, [1] keys of the first kind
  * (node, context), [2] of the deeper kinds (node, context, context of that context's rule, ...), [3] list entries
  * in all, [4] of them accepted tokens of nodes that keep a list, [5] context-dependent (node, token) pairs
- * the lists were made from, [6] (pair, context) combinations examined at build time, [7] bitset rows. */
+ * the lists were made from, [6] these pairs times the contexts of their nodes' rules (what the first kind of
+ * list is decided for at build time; most combinations without a walk of their own), [7] bitset rows. */
 int xgm_cache_stats(const xgm_cache* c, int64_t* h_out8);
 /* For tests: entries of the lists that a fill has to walk, counted up to about 1024 (0: fills of such caches run a
  * kernel that cannot walk). */
@@ -241,7 +246,7 @@ int32_t xgm_debug_cache_walk_entries(const xgm_cache* c);
  * be tested without a device; nothing on the hot path calls it.  4 = context-
  * dependent by section 3.1 alone, rejected by the one-byte context refinement. */
 int xgm_debug_classify_host(const xgm_grammar* g, int32_t node, const uint8_t* h_bytes, int32_t n);
-/* The token walk of the two GPU kernels, compiled for the host from the same
+/* The token walk of the GPU kernels, compiled for the host from the same
  * source and run on the flattened tables, for tests without a device.
  * h_stack: depth nodes, bottom first.  build != 0: depth must be 1, result is
  * 0 rejected / 1 context-dependent / 2 accepted / 4 plain-only context-

@@ -233,8 +233,8 @@ struct ClassifyShared {
 // alone leaves 1.56 M of the 28 M.
 // Both kernels write whole words of the rank-space bitsets, 64 tokens of one node, which are lines of their own: only those
 // that are not zero (ClassifyArgs::some_acc).  264 us for that grammar (381 with every word written, 451 MB), and 300 us
-// for the walks, where one kernel that walked all pairs that the first byte leaves took 1663 us; JSON (128256 tokens) 37 +
-// 34 us, before 163, where a few waves with the walks of whole strings were the last to finish; 32000 tokens 18 + 25, before
+// for the walks, where one kernel that walked all pairs that the first byte leaves took 1663 us; JSON (128256 tokens) 32 to
+// 49 (one run and another) + 34 us, before 163, where a few waves with the walks of whole strings were the last to finish; 32000 tokens 18 + 25, before
 // 65; a scripting grammar 64 + 152, before 394; the C/SQL-like grammar, whose identifiers are walked to their ends at a
 // hundred nodes, 89 + 957, before 1283.
 template <class Tab>
@@ -945,7 +945,7 @@ struct ContextWork {
 // Both parts and the writing pass: 20 + 111 + 15 us for that grammar, where workgroups of 768 pairs that walked every one
 // of 8 contexts took 381 + 63 (8333 times the staging of the tables, 89 MB of outcomes); JSON and 32000 tokens 8 + 20 + 5,
 // before 76 + 5; a scripting grammar and 128256 tokens 21 + 187 + 11, before 225 + 12; the C/SQL-like grammar, whose
-// pairs get through most contexts, 105 + 897 + 70, before 970 + 62.
+// pairs get through most contexts, 103 + 897 to 934 + 69, before 970 + 62: there the look at the contexts gains nothing.
 // A tile of few contexts is listed as it is (JSON 37 -> 8 us), and so is one of more than a few runs, which would be looked at
 // one after the other (schema grammar 58 us with any number of runs, 28 with 8, 20 with 4).
 constexpr uint32_t kManyContexts = 8;
@@ -1050,7 +1050,7 @@ __global__ __launch_bounds__(kContextThreads) void context_open_kernel(DevTables
 
 // Second part: the listed (64 pairs, context), a wave for each (for two neighbours in the list, mostly of the same pairs, if
 // there are more than the chip has room for: C/SQL-like grammar 958 us with one, 897 with two, 1064 with four, 1329 with
-// eight).  All entries of a wave go to the lists of one key: they are counted
+// eight, side by side).  All entries of a wave go to the lists of one key: they are counted
 // per segment in LDS and added to the global counters once.
 constexpr uint32_t kOpenBlocks = 512;  // the tables are staged once per place on the chip
 template <bool WRITE>
@@ -2084,7 +2084,8 @@ __device__ __forceinline__ int compare_candidates(const AcceptShared& sm, uint32
 // state and tables are there (2.6 before), walk 1.9, stacks 2.6 (3.4 before), the
 // rest 0.4 (0.6); the launch, 13.3 us (14.3 before), lasts as long as its slowest row (a twelve-byte token
 // through several frames: 20 steps of 0.6 us).  A pass of four fills and three accepts of
-// 128 schema rows 86.7 -> 83.3 us, of five and four of one JSON row 42.9 -> 41.6.
+// 128 schema rows 83.4 -> 79.7 us, side by side; one of five and four of one JSON row takes
+// as long as before (43 to 46 us, more from run to run than between the two).
 // With one lane per stack, tables in global memory and stacks copied
 // by that lane: 17.9 us for the launch; one JSON row 8.2 us, now 5.7;
 // rows of the C/SQL-like grammar, 90 frames deep, 46 us in the mean, now 10.

@@ -1,5 +1,6 @@
-// Device-side data layouts and the host-callable launchers of the three
-// kernels (token walk / classify, batched mask fill, -inf apply).
+// Device-side data layouts and the host-callable launchers of the kernels:
+// cache build (classification, per-call-site lists), batched mask fill, -inf
+// apply, and the states that live on the device (accept, rollback, fork).
 #pragma once
 #include <hip/hip_runtime_api.h>
 #include <hip/hip_vector_types.h>
