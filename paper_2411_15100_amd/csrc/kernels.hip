@@ -233,8 +233,8 @@ struct ClassifyShared {
 // alone leaves 1.56 M of the 28 M.
 // Both kernels write whole words of the rank-space bitsets, 64 tokens of one node, which are lines of their own: only those
 // that are not zero (ClassifyArgs::some_acc).  264 us for that grammar (381 with every word written, 451 MB), and 300 us
-// for the walks, where one kernel that walked all pairs that the first byte leaves took 1663 us; JSON (128256 tokens) 32 to
-// 49 (one run and another) + 34 us, before 163, where a few waves with the walks of whole strings were the last to finish; 32000 tokens 18 + 25, before
+// for the walks, where one kernel that walked all pairs that the first byte leaves took 1663 us; JSON (128256 tokens) 31 to
+// 49 (from run to run) + 34 us, before 163, where a few waves with the walks of whole strings were the last to finish; 32000 tokens 18 + 25, before
 // 65; a scripting grammar 64 + 152, before 394; the C/SQL-like grammar, whose identifiers are walked to their ends at a
 // hundred nodes, 89 + 957, before 1283.
 template <class Tab>
@@ -945,7 +945,7 @@ struct ContextWork {
 // Both parts and the writing pass: 20 + 111 + 15 us for that grammar, where workgroups of 768 pairs that walked every one
 // of 8 contexts took 381 + 63 (8333 times the staging of the tables, 89 MB of outcomes); JSON and 32000 tokens 8 + 20 + 5,
 // before 76 + 5; a scripting grammar and 128256 tokens 21 + 187 + 11, before 225 + 12; the C/SQL-like grammar, whose
-// pairs get through most contexts, 103 + 897 to 934 + 69, before 970 + 62: there the look at the contexts gains nothing.
+// pairs get through most contexts, 105 + 900 to 960 (from run to run) + 69, before 970 + 62: there the look at the contexts gains nothing.
 // A tile of few contexts is listed as it is (JSON 37 -> 8 us), and so is one of more than a few runs, which would be looked at
 // one after the other (schema grammar 58 us with any number of runs, 28 with 8, 20 with 4).
 constexpr uint32_t kManyContexts = 8;
