@@ -1455,157 +1455,189 @@ struct UniformFrames {
   __device__ __forceinline__ uint32_t of_lane(uint32_t k) const { return p[k]; }
 };
 // walk_token (of a live stack) for a wave whose tables (the sections in front of the headers) are in LDS: the same
-// paths in the same order, fewer steps.  A step looks many bytes ahead: lane j at node n on byte i + j (the inside of
-// a string stays where it is), lane 32 + j at node n + j on byte i + j (a literal's nodes are numbered one after the
-// other).  While there is nothing to do but a move along a byte edge, all of a run is taken at once, and the move
-// behind it; what the lane in front of which the run ended has read is what the alternatives there are made from.
+// paths in the same order, fewer steps.  The token's bytes lie in the lanes, 32 at a time: lane j and lane 32 + j have the
+// same one.  A step looks at all of them at once, lane j at node n (the inside of a string stays where it is), lane 32 + j at
+// the node that follows n by as many places as the byte does the next one (a literal's nodes are numbered one after the other).
+// A byte at which there is nothing to do but a move along an edge is taken in a loop of its own, and where the move stayed at
+// its node, or went to the next one, so are all bytes behind it of which the lanes have seen the same.
 // Where there is nothing but a return, lane j looks at the frame j below the one returned into, and all frames are
 // returned through that can do nothing else with the byte (an operand in an expression grammar sits a dozen precedence
 // levels deep).
-// The lookup has no branches: to a wave that is alone with its walk a taken branch costs as much as a dozen
-// instructions.  A nine-byte piece of a string takes 1.2 us this way, 6 with a lane's walk byte by byte.
+// Bound by latency: every instruction of a wave that is alone with its walk waits for the one before.  Measured so, in clocks:
+// an arithmetic instruction 4, a branch not taken 6 and taken 20, a comparison whose mask goes through scalar registers back
+// into a select 28, an LDS read 61 (84 with its value in a scalar register).  So the lookup is arithmetic on vectors with
+// three rounds of LDS reads (header, shape and FOLLOW word, target), and one word of it decides whether the step is a move:
+// 400 clocks for a move, where the same lookup made of comparisons and masks, with all runs looked for in every step, took
+// 1106 (a token of 11 bytes in a keyword of the scripting grammar 13236 and 6870, one of 14 bytes through five frames of a
+// schema grammar 34200 and 21900; a pass of 24 rows of the C/SQL-like grammar 30.6 and 25.3 us).
 template <class Note>
 __device__ __forceinline__ int walk_wave(const LdsTabT<true, true>& T, WaveMem& mem, const uint4 tk, const uint8_t* ext, const int len,
                                          const uint32_t start_node, const UniformFrames& live, const uint32_t depth, const Note& note,
                                          const int i0 = 0) {
   if (len > kMaxTokenLen) return kOverflow;
-  const TokenWords tw(tk);
-  const uint32_t lane = threadIdx.x & 63u, ahead = lane & 31u;
-  const uint32_t last_alt = (T.off_hdr - T.off_alts) / 4u - 1u;
+  const uint32_t lane = threadIdx.x & 63u, half = lane & 31u, chained = lane < 32u ? 0u : ~0u;
+  const uint32_t last_alt = (T.off_hdr - T.off_alts) / 4u - 1u, last_target = (T.off_follow - T.off_targets) / 2u - 1u, last_node = T.n_nodes - 1u;
+  const bool all_near = T.n_near >= T.n_nodes;
   uint32_t n = start_node, sp = kLiveBase + depth - 1, f = 1, alt = 0, top = 0, csp = 0, needed = 0;
-  int i = i0;
-  // node `node` on byte `c`, each lane its own: the header's flags, whether c can follow the node's rule, whether there
-  // is a move or calls, and where to
-  struct Found { uint32_t flags, follow, to; bool some; };
-  auto look = [&](uint32_t node, uint32_t c) {
-    Found r;
-    const unsigned long long hdr = node < T.n_near ? *(const XGM_LDS unsigned long long*)(T.lds + T.off_hdr + node * 8u)
-                                                   : *(const XGM_GLOBAL unsigned long long*)(T.img + T.off_hdr + (size_t)node * 8u);
-    const uint32_t hx = (uint32_t)hdr;
-    r.flags = (uint32_t)(hdr >> 32);
-    const uint32_t cl = T.lds[c];
-    r.follow = *(const XGM_LDS uint32_t*)(T.lds + T.off_follow + ((r.flags >> 16) * 8u + (c >> 5)) * 4u) >> (c & 31u);
-    const bool branching = (r.flags & 2u) != 0u;
-    const uint32_t si = T.lds[T.off_shapes + (branching ? (hx & 0xFFFFu) * T.n_cls : 0u) + cl];
-    const uint32_t at = branching && si != 0xFFu ? (hx >> 16) + si : 0u;
-    const uint32_t target = *(const XGM_LDS uint16_t*)(T.lds + T.off_targets + at * 2u);
-    r.some = branching ? si != 0xFFu : c >= (hx & 0xFFu) && c <= ((hx >> 8) & 0xFFu);
-    r.to = branching ? target : hx >> 16;
-    return r;
+  int i = i0, steps = 0;
+  // the lane's byte, and where its class's column of the shapes and its word of a FOLLOW set begin
+  uint32_t byte = 0u, column = 0u, word_of_set = 0u;
+  int window = 0, window_end = i0;  // the bytes in the lanes
+  auto load_window = [&]() {
+    window = i;
+    window_end = min(len, i + 32);
+    const int at = min(i + (int)half, len - 1);
+    byte = token_byte(tk, nullptr, min(at, 14));
+    if (len > 15) {
+      const uint32_t beyond = ext[at];
+      byte = at < 15 ? byte : beyond;
+    }
+    column = T.off_shapes + T.lds[byte];
+    word_of_set = T.off_follow + (byte >> 5) * 4u;
   };
-  for (int steps = 0;; ++steps) {
-    if (steps >= kMaxSteps) return kOverflow;
-    bool back = true;
-    if (i == len) {
-      if constexpr (!Note::kEnumerate) return kAccept;
-      note(n, sp, mem, live);  // then on to the next path
-    } else {
-      const bool mine = (int)ahead < len - i;
-      const uint32_t c = token_byte(tw, ext, mine ? i + (int)ahead : i);
-      const uint32_t node = lane < 32u || !mine ? n : min(n + ahead, T.n_nodes - 1u);
-      const Found at_node = look(node, c);
-      const bool may_return = ((at_node.flags & (ahead == 0u ? f : 1u) & at_node.follow) & 1u) != 0u;
-      const bool moves_on = mine && at_node.some && at_node.to < 0x8000u && !may_return && alt == 0u;
-      const unsigned long long can = __ballot(moves_on), stays = __ballot(moves_on && at_node.to == (lane < 32u ? n : node + 1u));
-      const uint32_t same = (uint32_t)__ffs((int)(~(uint32_t)stays | 0x80000000u)) - 1u;
-      const uint32_t chain = (uint32_t)__ffs((int)(~(uint32_t)(stays >> 32) | 0x80000000u)) - 1u;
-      const uint32_t run = max(same, chain), last = same >= chain ? same : 32u + chain;
-      auto of_last = [&](uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)last); };
-      uint32_t dst = of_last(at_node.to);
-      if (chain > same) n += chain;
-      i += (int)run;
-      steps += (int)run;
-      f = run ? 1u : f;
-      if ((can >> last) & 1ull) {
-        n = dst;
+  // What node `node` does with byte `c`, each lane its own: where to (bits 0..15), kNone = there is neither a move nor a call,
+  // kReturns = the rule may end there and c can follow it.  Vector arithmetic alone: a comparison whose result goes through a
+  // mask in scalar registers costs as much as seven instructions.
+  constexpr uint32_t kNone = 0x10000u, kReturns = 0x20000u;
+  auto look = [&](uint32_t node, uint32_t c, uint32_t col, uint32_t set) {
+    u64 hdr = *(const XGM_LDS u64*)(T.lds + T.off_hdr + (all_near ? node : min(node, T.n_near - 1u)) * 8u);
+    if (!all_near && __ballot(node >= T.n_near)) {  // (all lanes fetch, so that none goes a way of its own)
+      const u64 far = *(const XGM_GLOBAL u64*)(T.img + T.off_hdr + (size_t)node * 8u);
+      hdr = node < T.n_near ? hdr : far;
+    }
+    const uint32_t hx = (uint32_t)hdr, flags = (uint32_t)(hdr >> 32);
+    const uint32_t branching = 0u - ((flags >> 1) & 1u);
+    const uint32_t si = T.lds[col + (__umul24(hx & 0xFFFFu, T.n_cls) & branching)];
+    const uint32_t follow = *(const XGM_LDS uint32_t*)(T.lds + set + (flags >> 16) * 32u) >> (c & 31u);
+    const uint32_t target = *(const XGM_LDS uint16_t*)(T.lds + T.off_targets + min((hx >> 16) + si, last_target) * 2u);
+    const uint32_t outside = ((c - (hx & 0xFFu)) | (((hx >> 8) & 0xFFu) - c)) >> 31, dead = (si + 1u) >> 8;
+    const uint32_t to = (target & branching) | ((hx >> 16) & ~branching), none = (dead & branching) | (outside & ~branching);
+    return to | none << 16 | (flags & follow & 1u) << 17;
+  };
+  auto of = [](uint32_t v, uint32_t l) { return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)l); };
+  for (;;) {    // a path
+    for (;;) {  // its steps
+      uint32_t x, first;
+      for (;;) {
+        if (__builtin_expect(i == window_end, 0)) {
+          if (i == len) break;
+          load_window();
+        }
+        first = (uint32_t)(i - window);
+        const uint32_t node = min(n + ((half - first) & chained), last_node);  // (lanes of bytes that have been taken: any node)
+        const uint32_t found = look(node, byte, column, word_of_set);
+        x = of(found, first);
+        // nothing but a move: on with the next byte
+        if (x >= 0x8000u || alt != 0u) break;
+        ++steps;
         ++i;
         f = 1;
-        continue;
+        const uint32_t d = x - n;
+        n = x;
+        if (d > 1u) continue;
+        // it stayed at its node, or went to the next one: for how many bytes more?
+        const u64 more = __ballot(found == node - chained);
+        const uint32_t run = (uint32_t)__ffs((int)~((uint32_t)(d ? more >> 32 : more) >> first >> 1)) - 1u;
+        const uint32_t taken = min(run, (uint32_t)(window_end - i));
+        i += (int)taken;
+        steps += (int)taken;
+        n += d ? taken : 0u;
       }
-      if (i == len) { --steps; continue; }
-      uint32_t k_some = of_last(at_node.some ? 1u : 0u);
-      uint32_t can_pop = sp == kLiveBase ? 0u : of_last(at_node.flags & at_node.follow) & f & 1u;
-      if (can_pop && !k_some && alt == 0u) {
+      if (steps >= kMaxSteps) return kOverflow;
+      if (i == len) {
+        if constexpr (!Note::kEnumerate) return kAccept;
+        note(n, sp, mem, live);
+        break;  // on to the next path
+      }
+      ++steps;
+      // (what has not consumed a byte since the last push cannot return)
+      uint32_t can_pop = sp != kLiveBase && (x & kReturns) ? f : 0u;
+      if (can_pop && (x & kNone) && alt == 0u) {
         // (frames pushed one after the other lie one after the other, each with the number of the one below)
         const bool pushed = sp < kLiveBase;
-        const uint32_t below = pushed ? sp + 1u : sp - kLiveBase;
-        const uint32_t word = lane >= below ? n : pushed ? mem.arena[sp - lane] : live.of_lane(below - 1u - lane);
-        const Found there = look(word & 0xFFFFu, of_last(c));
-        const bool next = pushed ? (word >> 16) + 1u == sp - lane : lane + 1u < below;  // (frame 0 of the stack is not returned from)
-        const unsigned long long other = ~__ballot(lane < below && next && !there.some && (there.flags & there.follow & 1u));
+        const uint32_t below = pushed ? sp + 1u : sp - kLiveBase, k = min(lane, below - 1u);
+        uint32_t word;
+        if (pushed) word = mem.arena[sp - k];
+        else word = live.of_lane(below - 1u - k);
+        const uint32_t there = look(word & 0xFFFFu, of(byte, first), of(column, first), of(word_of_set, first));
+        const u64 next = pushed ? __ballot((word >> 16) + 1u == sp - lane) : ~0ull;
+        // (frame 0 of the stack is not returned from)
+        const uint32_t last = pushed ? below : below - 1u;
+        const u64 other = ~(__ballot((there & (kNone | kReturns)) == (kNone | kReturns)) & next & (last < 64u ? (1ull << last) - 1ull : ~0ull));
         const uint32_t through = min((uint32_t)__ffsll((long long)other) - 1u, 63u);  // (none: 0xFFFFFFFF)
-        auto of_frame = [&](uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)through); };
-        n = of_frame(word) & 0xFFFFu;
+        const uint32_t frame = of(word, through);
+        n = frame & 0xFFFFu;
         if (pushed && needed <= sp) top = max(sp - through, needed);  // (frames that a pending alternative needs stay)
-        sp = pushed ? of_frame(word) >> 16 : sp - through - 1u;
+        sp = pushed ? frame >> 16 : sp - through - 1u;
         steps += (int)through + 1;
-        dst = of_frame(there.to);
-        k_some = of_frame(there.some ? 1u : 0u);
-        can_pop = sp == kLiveBase ? 0u : of_frame(there.flags & there.follow) & 1u;
+        x = of(there, through);
+        can_pop = sp != kLiveBase && (x & kReturns) ? 1u : 0u;
       }
+      const uint32_t dst = x & 0xFFFFu, k_some = x & kNone ? 0u : 1u;
       const bool pooled = k_some && dst >= 0x8000u;
       // the pool entry: lane j has its word j (a count and the alternatives, or a run of calls)
       const uint32_t base = dst & 0x7FFFu;
-      const uint32_t word = pooled ? *(const XGM_LDS uint32_t*)(T.lds + T.off_alts + min(base + lane, last_alt) * 4u) : 0u;
-      const uint32_t word0 = uniform(word);
+      uint32_t word = 0u, word0 = 0u;
+      if (pooled) {
+        word = *(const XGM_LDS uint32_t*)(T.lds + T.off_alts + min(base + lane, last_alt) * 4u);
+        word0 = uniform(word);
+      }
       const bool calls = (word0 & kRunFlagD) != 0u;
       const uint32_t k = pooled && !calls ? word0 : k_some, total = k + can_pop;
-      if (alt < total) {
-        back = false;
-        if (alt + 1 < total) {
-          if (csp == kChoicePoints) return kOverflow;
-          mem.set_choice(csp++, make_uint2(n | (sp << 16), (uint32_t)i | ((alt + 1) << 8) | (top << 16) | (f << 24)));
-          needed = top;
-        }
-        if (alt < k) {
-          bool consumes;
-          if (calls) {
-            const uint32_t m = run_frames(word0);
-            if (top + m > kArenaFrames) return kOverflow;
-            for (uint32_t j = 0; j < m; ++j) {
-              mem.set_frame(top, ((T.alt(run_frames_at(word0) + (j >> 1)) >> ((j & 1u) * 16u)) & 0xFFFFu) | (sp << 16));
-              sp = top++;
-            }
-            n = (uint32_t)__builtin_amdgcn_readlane((int)word, 1);
-            consumes = (word0 & kRunConsumesD) != 0u;
-          } else {
-            const uint32_t e = !pooled ? (kMoveTagD << 16) | dst : alt < 63u ? (uint32_t)__builtin_amdgcn_readlane((int)word, (int)(1u + alt)) : T.alt(base + 1u + alt);
-            const uint32_t tag = e >> 16;
-            n = e & 0xFFFFu;
-            consumes = tag == kMoveTagD;
-            if (!consumes && tag != kTailTagD) {
-              if (top == kArenaFrames) return kOverflow;
-              mem.set_frame(top, tag | (sp << 16));
-              sp = top++;
-            }
-          }
-          f = consumes ? 1u : 0u;
-          i += consumes ? 1 : 0;
-        } else if (sp < kLiveBase) {   // return into a frame pushed during this walk
-          const uint32_t fr = mem.frame(sp), old = sp;
-          n = fr & 0xFFFFu;
-          sp = fr >> 16;
-          if (needed <= old) top = old;
-        } else {                       // return into a live frame
-          n = live[sp - kLiveBase - 1u];
-          --sp;
-        }
-        alt = 0;
+      if (alt >= total) break;
+      if (alt + 1 < total) {
+        if (csp == kChoicePoints) return kOverflow;
+        mem.set_choice(csp++, make_uint2(n | (sp << 16), (uint32_t)i | ((alt + 1) << 8) | (top << 16) | (f << 24)));
+        needed = top;
       }
+      if (alt < k) {
+        bool consumes;
+        if (calls) {
+          const uint32_t m = run_frames(word0);
+          if (top + m > kArenaFrames) return kOverflow;
+          for (uint32_t j = 0; j < m; ++j) {
+            mem.set_frame(top, ((T.alt(run_frames_at(word0) + (j >> 1)) >> ((j & 1u) * 16u)) & 0xFFFFu) | (sp << 16));
+            sp = top++;
+          }
+          n = of(word, 1u);
+          consumes = (word0 & kRunConsumesD) != 0u;
+        } else {
+          const uint32_t e = !pooled ? (kMoveTagD << 16) | dst : alt < 63u ? of(word, 1u + alt) : T.alt(base + 1u + alt);
+          const uint32_t tag = e >> 16;
+          n = e & 0xFFFFu;
+          consumes = tag == kMoveTagD;
+          if (!consumes && tag != kTailTagD) {
+            if (top == kArenaFrames) return kOverflow;
+            mem.set_frame(top, tag | (sp << 16));
+            sp = top++;
+          }
+        }
+        f = consumes ? 1u : 0u;
+        i += consumes ? 1 : 0;
+      } else if (sp < kLiveBase) {   // return into a frame pushed during this walk
+        const uint32_t fr = mem.frame(sp), old = sp;
+        n = fr & 0xFFFFu;
+        sp = fr >> 16;
+        if (needed <= old) top = old;
+      } else {                       // return into a live frame
+        n = live[sp - kLiveBase - 1u];
+        --sp;
+      }
+      alt = 0;
     }
-    if (back) {  // to the most recent pending alternative
-      if (csp == 0) break;
-      const uint2 ch = mem.choice(--csp);
-      n = ch.x & 0xFFFFu;
-      sp = ch.x >> 16;
-      i = (int)(ch.y & 0xFFu);
-      alt = (ch.y >> 8) & 0xFFu;
-      top = (ch.y >> 16) & 0xFFu;
-      f = (ch.y >> 24) & 1u;
-      needed = csp ? (mem.choice(csp - 1).y >> 16) & 0xFFu : 0u;
-    }
+    // to the most recent pending alternative
+    if (csp == 0) return kReject;
+    const uint2 ch = mem.choice(--csp);
+    n = ch.x & 0xFFFFu;
+    sp = ch.x >> 16;
+    i = (int)(ch.y & 0xFFu);
+    if (i < window) window_end = i;  // (the lanes hold later bytes)
+    alt = (ch.y >> 8) & 0xFFu;
+    top = (ch.y >> 16) & 0xFFu;
+    f = (ch.y >> 24) & 1u;
+    needed = csp ? (mem.choice(csp - 1).y >> 16) & 0xFFu : 0u;
+    ++steps;
   }
-  return kReject;
 }
 constexpr int kFillThreads = 256;
 constexpr int kFillFramesLds = 1024;            // live frames kept in LDS (deeper stacks: global memory)
@@ -2023,6 +2055,9 @@ struct NoteStacks {
   uint32_t stack;
   template <class Mem, class Live>
   __device__ __forceinline__ void operator()(uint32_t n, uint32_t sp, const Mem& mem, const Live& live) const {
+    const uint32_t lane = threadIdx.x & 63u;
+    uint32_t i = 0u;
+    if (lane == 0u) i = atomicAdd(&sm->count, 1u);  // (a stack too many or too deep is the end of the accept anyway)
     while (T->is_dead_end(n)) {
       if (sp < kLiveBase) {
         const uint32_t fr = mem.frame(sp);
@@ -2035,23 +2070,20 @@ struct NoteStacks {
         sp = kLiveBase + d - 1;
       }
     }
-    uint32_t m = 1, h = sp;
-    for (; h < kLiveBase; h = mem.frame(h) >> 16) ++m;
-    const uint32_t d = h - kLiveBase;  // frames kept
-    uint32_t i = kBatchMaxCandidates;
-    if (d + m <= kBatchMaxDepth) {
-      if ((threadIdx.x & 63u) == 0u) i = atomicAdd(&sm->count, 1u);
-      i = uniform(i);
-    }
-    if (i >= kBatchMaxCandidates) { sm->overflow = 1u; return; }
-    sm->from[i] = stack | (d << 8) | (m << 16);
-    uint32_t k = m - 1u;
-    sm->fresh[i][k] = (uint16_t)n;
-    for (h = sp; h < kLiveBase; ) {
+    // lane k: the new frame k + 1 below the top
+    static_assert(kArenaFrames <= 64, "the new frames of a stack fit the lanes");
+    uint32_t m = 1u, h = sp, mine = 0u;
+    for (; h < kLiveBase; ++m) {
       const uint32_t fr = mem.frame(h);
-      sm->fresh[i][--k] = (uint16_t)(fr & 0xFFFFu);
+      mine = lane + 1u == m ? fr & 0xFFFFu : mine;
       h = fr >> 16;
     }
+    const uint32_t d = h - kLiveBase;  // frames kept
+    i = uniform(i);
+    if (d + m > kBatchMaxDepth || i >= kBatchMaxCandidates) { sm->overflow = 1u; return; }
+    sm->from[i] = stack | (d << 8) | (m << 16);
+    sm->fresh[i][m - 1u] = (uint16_t)n;
+    if (lane + 1u < m) sm->fresh[i][m - 2u - lane] = (uint16_t)mine;
   }
 };
 // the order of candidates: element by element from the bottom, the shorter first (the host's order of stacks)
@@ -2082,8 +2114,9 @@ __device__ __forceinline__ int compare_candidates(const AcceptShared& sm, uint32
 // one memory round for the contexts (DevCache::node_ctx_first), one for each level's
 // key and one for the offsets.  In-kernel clocks, mean of 128 schema rows: 2.2 us until
 // state and tables are there (2.6 before), walk 1.9, stacks 2.6 (3.4 before), the
-// rest 0.4 (0.6); the launch, 13.3 us (14.3 before), lasts as long as its slowest row (a twelve-byte token
-// through several frames: 20 steps of 0.6 us).  A pass of four fills and three accepts of
+// rest 0.4 (0.6); the launch, 13.3 us (14.3 before), lasted as long as its slowest row (a twelve-byte token
+// through several frames: 20 steps of 0.6 us; 0.4 since walk_wave takes moves in a loop of their own: a pass of four fills and
+// three accepts 75.6 -> 72.5 us).  A pass of four fills and three accepts of
 // 128 schema rows 83.4 -> 79.7 us, side by side; one of five and four of one JSON row takes
 // as long as before (43 to 46 us, more from run to run than between the two).
 // With one lane per stack, tables in global memory and stacks copied
