@@ -27,6 +27,16 @@ __device__ __forceinline__ void stage_tables(const DevTables& tab, unsigned char
   uint4* dst = reinterpret_cast<uint4*>(smem);
   for (uint32_t k = threadIdx.x; k < tab.stage_bytes / 16; k += nthreads) dst[k] = tab.image[k];
 }
+// The same, fetched straight into LDS: all pieces are in flight at once, and no registers hold them.  staged() must come
+// before the barrier, and before any wave returns.
+__device__ __forceinline__ void stage_tables_async(const DevTables& tab, unsigned char* smem, uint32_t nthreads) {
+  const uint32_t n = tab.stage_bytes / 16u, lane = threadIdx.x & 63u;
+  for (uint32_t k = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x & ~63u)); k < n; k += nthreads)
+    if (k + lane < n)
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(tab.image + k + lane),
+                                       (__attribute__((address_space(3))) void*)(smem + k * 16u), 16, 0, 0);
+}
+__device__ __forceinline__ void staged() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // The table access of the walk (same answers as CompactTab in walk.hpp) on a
 // table image of which bytes [0, lds_end) have been staged by stage_tables().
@@ -486,6 +496,12 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+// A barrier for what is in LDS: __syncthreads() also waits until what the threads have stored to global memory has got there.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 __device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
 #pragma unroll
@@ -2037,6 +2053,7 @@ struct AcceptShared {
   uint32_t common[kBatchMaxStacks][kBatchMaxStacks]; // frames that two of them have in common, from the bottom
   uint32_t slot_of[kBatchMaxStacks];                 // the new stacks in order
   uint32_t mem[kAcceptThreads / 64][kWaveMemWords];
+  uint32_t cache[sizeof(DevCache) / 4];              // the row's DevCache
   uint32_t count, overflow, duplicates, can_end, bad_context, n_frames;
   __device__ __forceinline__ uint32_t kept(uint32_t i) const { return (from[i] >> 8) & 0xFFu; }
   __device__ __forceinline__ uint32_t depth(uint32_t i) const { return kept(i) + (from[i] >> 16); }
@@ -2112,13 +2129,16 @@ __device__ __forceinline__ int compare_candidates(const AcceptShared& sm, uint32
 // as long), and a wave works out a new stack by itself, its frames and their headers
 // one in each lane: what used to be five barriers with a lookup or two between them is
 // one memory round for the contexts (DevCache::node_ctx_first), one for each level's
-// key and one for the offsets.  In-kernel clocks, mean of 128 schema rows: 2.2 us until
-// state and tables are there (2.6 before), walk 1.9, stacks 2.6 (3.4 before), the
-// rest 0.4 (0.6); the launch, 13.3 us (14.3 before), lasted as long as its slowest row (a twelve-byte token
-// through several frames: 20 steps of 0.6 us; 0.4 since walk_wave takes moves in a loop of their own: a pass of four fills and
-// three accepts 75.6 -> 72.5 us).  A pass of four fills and three accepts of
-// 128 schema rows 83.4 -> 79.7 us, side by side; one of five and four of one JSON row takes
-// as long as before (43 to 46 us, more from run to run than between the two).
+// key and one for the offsets.  A round takes 500 clocks (another kernel wrote the state, so no cache holds it), and the
+// compiler makes one of every load that it cannot move in front of a branch: the state, the tables (fetched straight into
+// LDS) and the row's DevCache are fetched by all threads alike, each list's offsets along with the next list's key, and
+// nothing is stored before the last load has come.  In-kernel clocks, mean of 128 schema rows: 3580 until state and tables
+// are there (4940 with the pieces of the tables one after the other), walk 3700 (4580), stacks 4400 (5910, with a wave's sum
+// for the first stack too and the DevCache's pointers read one by one where they were needed), the rest 360; a JSON row
+// that stays in a string 9280 in all, before 11300.  The launch lasts as long as its slowest row (a twelve-byte token
+// through several frames: 17 000 clocks of walk, 27 000 before walk_wave took moves in a loop of their own).  A pass of four
+// fills and three accepts of 128 schema rows 77.2 -> 66.9 us, one of five and four of 8 rows of the scripting grammar 65.7
+// -> 58.3, of one JSON row 47.3 -> 44.6 (walk_wave's part included).
 // With one lane per stack, tables in global memory and stacks copied
 // by that lane: 17.9 us for the launch; one JSON row 8.2 us, now 5.7;
 // rows of the C/SQL-like grammar, 90 frames deep, 46 us in the mean, now 10.
@@ -2142,17 +2162,18 @@ __global__ __launch_bounds__(kAcceptThreads) void batch_accept_kernel(DevBatch b
   const uint32_t epoch = bt.rows[b].epoch;
   const int32_t older = bt.older[b];
   if (tok < 0) return;  // this row is left alone (its status too)
-  {
-    uint4 h = make_uint4(0u, 0u, 0u, 0u);
-    if (tid < kBatchMaxStacks) h = *reinterpret_cast<const uint4*>(bt.hdrs + (size_t)(at * kBatchMaxStacks + tid) * hdr_stride);
-    const uint32_t* frames = reinterpret_cast<const uint32_t*>(bt.frames + (size_t)at * kBatchRowFrames);
-    const uint32_t two = frames[tid];
-    stage_tables(tab, smem, kAcceptThreads);
-    reinterpret_cast<uint32_t*>(sm.live)[tid] = two;
-    for (uint32_t k = tid + kAcceptThreads; k * 2u < cur.n_frames; k += kAcceptThreads) reinterpret_cast<uint32_t*>(sm.live)[k] = frames[k];
-    static_assert(kStackHdrTop == 0 && kStackHdrDepth == 1 && kStackHdrFrames == 2, "a stack's scalars are one 16-byte load");
-    if (tid < kBatchMaxStacks) sm.stack[tid] = (h.z - at * kBatchRowFrames) | (h.y << 16);
-  }
+  // (every thread fetches, whether there is something for it or not: a load under a condition is waited for at its end)
+  static_assert(kStackHdrTop == 0 && kStackHdrDepth == 1 && kStackHdrFrames == 2, "a stack's scalars lie side by side");
+  static_assert(kAcceptThreads >= sizeof(DevCache) / 4 && sizeof(DevCache) % 8 == 0, "a word of the DevCache for each thread");
+  const uint32_t* const frames = reinterpret_cast<const uint32_t*>(bt.frames + (size_t)at * kBatchRowFrames);
+  const uint32_t* const h = bt.hdrs + (size_t)(at * kBatchMaxStacks + tid % kBatchMaxStacks) * hdr_stride;
+  const uint32_t two = frames[tid], h_depth = h[kStackHdrDepth], h_frames = h[kStackHdrFrames];
+  const uint32_t word = reinterpret_cast<const uint32_t*>(&dc)[min(tid, (uint32_t)(sizeof(DevCache) / 4) - 1u)];
+  stage_tables_async(tab, smem, kAcceptThreads);
+  reinterpret_cast<uint32_t*>(sm.live)[tid] = two;
+  if (tid < sizeof(DevCache) / 4) sm.cache[tid] = word;
+  if (tid < kBatchMaxStacks) sm.stack[tid] = (h_frames - at * kBatchRowFrames) | (h_depth << 16);
+  for (uint32_t k = tid + kAcceptThreads; k * 2u < cur.n_frames; k += kAcceptThreads) reinterpret_cast<uint32_t*>(sm.live)[k] = frames[k];
   if (tid == 0) { sm.count = 0u; sm.overflow = 0u; sm.duplicates = 0u; sm.can_end = 0u; sm.bad_context = 0u; }
   if (tid < kBatchMaxCandidates) sm.less[tid] = 0u;
   int32_t status = 0;
@@ -2166,13 +2187,14 @@ __global__ __launch_bounds__(kAcceptThreads) void batch_accept_kernel(DevBatch b
   }
   int len = (int)(tk.w >> 24);
   if (status == 0 && !stop && len == 0) status = kErrTokenRejected;
+  staged();
   if (status != 0) {
     if (tid == 0) bt.status[b] = status;
     return;
   }
   __syncthreads();
   const uint32_t n_off = (uint32_t)bt.n_seg + 1u;
-  const int32_t next = (head + 1) % bt.H;
+  const int32_t next = head + 1 == bt.H ? 0 : head + 1;
   const uint32_t sb = ((uint32_t)b * bt.H + next) * kBatchMaxStacks;
   const uint32_t fb = ((uint32_t)b * bt.H + next) * kBatchRowFrames;
   uint32_t ns = 0u, n_frames = 0u, can_end = 0u;
@@ -2242,18 +2264,23 @@ __global__ __launch_bounds__(kAcceptThreads) void batch_accept_kernel(DevBatch b
       if (tid == 0) bt.status[b] = kErrTooManyStacks;
       return;
     }
-    if (tid < nc && !((dup >> tid) & 1u)) sm.slot_of[__popc(sm.less[tid] & ~dup)] = tid;
-    __syncthreads();
+    if (nc > 1u) {
+      if (tid < nc && !((dup >> tid) & 1u)) sm.slot_of[__popc(sm.less[tid] & ~dup)] = tid;
+      __syncthreads();
+    }
     // A wave writes out a stack, and works out where its lists lie: which context of its rule the frame above each level
     // sits on (a lane per level), the keys (one after the other), the offsets of their segments (a lane per segment).
     for (uint32_t r = wave; r < ns; r += kAcceptThreads / 64) {
-      const uint32_t ci = uniform(sm.slot_of[r]), d = uniform(sm.depth(ci));
+      const uint32_t ci = nc > 1u ? uniform(sm.slot_of[r]) : 0u, d = uniform(sm.depth(ci));
       // lane k: the frame k below the top (below the 64th: looked up when they are needed)
       const uint32_t mine = lane < d ? sm.frame(ci, d - 1u - lane) : 0u;
       const uint32_t top = uniform(mine);
-      const uint32_t base = dc.k_base[0] != nullptr ? dc.k_base[0][top] : kNoKey, acc_row = dc.acc_row[top];
+      const DevCache& own = *reinterpret_cast<const DevCache*>(sm.cache);  // (its pointers are to global memory: see `fetch`)
+      auto fetch = [](const auto* p, size_t k) { return ((const XGM_GLOBAL std::decay_t<decltype(*p)>*)p)[k]; };
+      uint32_t child = own.k_base[0] != nullptr ? fetch(own.k_base[0], top) : kNoKey;
+      const uint32_t acc_row = fetch(own.acc_row, top);
       const uint32_t flags = T.header(mine).y;
-      const uint32_t first = fb + wave_sum(lane < r ? sm.depth(sm.slot_of[lane]) : 0u);
+      const uint32_t first = fb + (r ? wave_sum(lane < r ? sm.depth(sm.slot_of[lane]) : 0u) : 0u);
       auto node_at = [&](uint32_t k) { return sm.frame(ci, d - 1u - k); };
       const uint32_t drops = stack_drops(d, [&](uint32_t k) {
         const uint32_t y = k < 64u ? (uint32_t)__builtin_amdgcn_readlane((int)flags, (int)k) : T.header(node_at(k)).y;
@@ -2267,16 +2294,49 @@ __global__ __launch_bounds__(kAcceptThreads) void batch_accept_kernel(DevBatch b
         if (from > 64u) above = T.header(node_at(from - 1u)).y;
         if (from > 63u) below = node_at(from);
         const uint32_t rule = above >> 16;
-        const uint2 of = dc.node_ctx_first[below];
-        if ((of.x >> 16) == rule) idx = of.x & 0xFFFFu;
-        else if (of.y != kNoKey)
-          for (uint32_t k = 1u; k <= dc.node_ctx[of.y]; ++k) {
-            const uint32_t x = dc.node_ctx[of.y + k];
+        const u64 both = fetch(reinterpret_cast<const u64*>(own.node_ctx_first), below);
+        const uint32_t of_x = (uint32_t)both, of_y = (uint32_t)(both >> 32);
+        if ((of_x >> 16) == rule) idx = of_x & 0xFFFFu;
+        else if (of_y != kNoKey)
+          for (uint32_t k = 1u; k <= fetch(own.node_ctx, of_y); ++k) {
+            const uint32_t x = fetch(own.node_ctx, of_y + k);
             if ((x >> 16) == rule) idx = x & 0xFFFFu;
           }
         if (idx == kNoKey) sm.bad_context = 1u;
       }
-      // frames, and whether the stack can end the text: every frame of it may end its rule
+      // The keys: the top node's own list, then one per level that the stack reaches and the cache keeps.  Each key's number
+      // is fetched with what the one before says, and where its list lies (a lane per segment) along with the next key's.
+      uint32_t off[kStackLists];
+      off[0] = fetch(own.key_off, (size_t)top * (uint32_t)bt.n_seg + min(lane, n_off - 1u));
+      uint32_t keys[kStackLists], key0 = (uint32_t)own.n_nodes;
+      keys[0] = top;
+#pragma unroll
+      for (uint32_t l = 1; l <= (uint32_t)kCtxLevels; ++l) {
+        const uint32_t c = (uint32_t)__builtin_amdgcn_readlane((int)idx, (int)l - 1);
+        keys[l] = kNoKey;
+        off[l] = 0u;
+        child = uniform(child);
+        if (child != kNoKey && c != kNoKey) {
+          keys[l] = key0 + child + c;
+          off[l] = fetch(own.key_off, (size_t)keys[l] * (uint32_t)bt.n_seg + min(lane, n_off - 1u));
+          child = l < (uint32_t)kCtxLevels && own.k_base[l] != nullptr ? fetch(own.k_base[l], child + c) : kNoKey;
+        } else {
+          child = kNoKey;
+        }
+        key0 += own.n_k[l - 1u];
+      }
+      uint32_t* const h = bt.hdrs + (size_t)(sb + r) * hdr_stride;
+      if (lane == 0u) *reinterpret_cast<uint4*>(h) = make_uint4(top | (acc_row << 16), d, first, drops);
+      static_assert(kStackLists == 4, "the offsets of a segment's four lists are one 16-byte store");
+      if (lane < n_off) *reinterpret_cast<uint4*>(h + stack_hdr_off(lane, 0u)) = make_uint4(off[0], off[1], off[2], off[3]);
+      for (uint32_t sgm = lane + 64u; sgm < n_off; sgm += 64u) {
+        uint32_t o[kStackLists];
+#pragma unroll
+        for (uint32_t l = 0; l < kStackLists; ++l) o[l] = keys[l] == kNoKey ? 0u : fetch(own.key_off, (size_t)keys[l] * (uint32_t)bt.n_seg + sgm);
+        *reinterpret_cast<uint4*>(h + stack_hdr_off(sgm, 0u)) = make_uint4(o[0], o[1], o[2], o[3]);
+      }
+      // frames, and whether the stack can end the text: every frame of it may end its rule (behind what had to be
+      // fetched: a wait for a load is one for the stores in front of it)
       bool all_final = lane >= d || (flags & 1u) != 0u;
       if (lane < d) bt.frames[first + d - 1u - lane] = (uint16_t)mine;
       for (uint32_t k = lane + 64u; k < d; k += 64u) {
@@ -2286,33 +2346,8 @@ __global__ __launch_bounds__(kAcceptThreads) void batch_accept_kernel(DevBatch b
       }
       if (__ballot(!all_final) == 0ull && lane == 0u) sm.can_end = 1u;
       if (r + 1u == ns && lane == 0u) sm.n_frames = first + d - fb;
-      // the keys: the top node's own list, then one per level that the stack reaches and the cache keeps
-      uint32_t keys[kStackLists];
-      keys[0] = top;
-      uint32_t child = base, key0 = (uint32_t)dc.n_nodes;
-#pragma unroll
-      for (uint32_t l = 1; l <= (uint32_t)kCtxLevels; ++l) {
-        const uint32_t c = (uint32_t)__builtin_amdgcn_readlane((int)idx, (int)l - 1);
-        keys[l] = kNoKey;
-        if (child != kNoKey && c != kNoKey) {
-          keys[l] = key0 + child + c;
-          child = l < (uint32_t)kCtxLevels && dc.k_base[l] != nullptr ? dc.k_base[l][child + c] : kNoKey;
-        } else {
-          child = kNoKey;
-        }
-        key0 += dc.n_k[l - 1u];
-      }
-      uint32_t* const h = bt.hdrs + (size_t)(sb + r) * hdr_stride;
-      if (lane == 0u) *reinterpret_cast<uint4*>(h) = make_uint4(top | (acc_row << 16), d, first, drops);
-      static_assert(kStackLists == 4, "the offsets of a segment's four lists are one 16-byte store");
-      for (uint32_t sgm = lane; sgm < n_off; sgm += 64u) {
-        uint32_t o[kStackLists];
-#pragma unroll
-        for (uint32_t l = 0; l < kStackLists; ++l) o[l] = keys[l] == kNoKey ? 0u : dc.key_off[(size_t)keys[l] * (uint32_t)bt.n_seg + sgm];
-        *reinterpret_cast<uint4*>(h + stack_hdr_off(sgm, 0u)) = make_uint4(o[0], o[1], o[2], o[3]);
-      }
     }
-    __syncthreads();
+    lds_barrier();
     n_frames = sm.n_frames;
     can_end = sm.can_end;
     if (sm.bad_context) {  // a frame sits on a node that is no context of its rule: never the case for stacks the walk makes
