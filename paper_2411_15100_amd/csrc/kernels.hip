@@ -1655,7 +1655,12 @@ __device__ __forceinline__ int walk_wave(const LdsTabT<true, true>& T, WaveMem& 
     ++steps;
   }
 }
-constexpr int kFillThreads = 256;
+// Threads of a workgroup; where four share a segment (PARTS) it is for the walks, and twice the waves take them at the same
+// time (the tables in LDS leave room for as many such workgroups as of the others).  A workgroup of a row of the C/SQL-like
+// grammar has up to 15 walks of up to 40 000 clocks.  24 such rows, V = 128256, fill and apply, us with 256 threads and with
+// 512 (tables fetched straight into LDS too): 25.3 and 19.9, another draw of states 36.0 and 28.4; five fills and four accepts of 8
+// rows of the scripting grammar 100 and 89.
+constexpr int fill_threads(bool parts) { return parts ? 512 : 256; }
 constexpr int kFillFramesLds = 1024;            // live frames kept in LDS (deeper stacks: global memory)
 
 // One workgroup of 4 waves serves one request and one segment of 8192 token
@@ -1690,7 +1695,7 @@ constexpr int kFillFramesLds = 1024;            // live frames kept in LDS (deep
 // went from 13.7 to 8.7 us, one that walks 500 steps from 53 to 36, and to 31 with a
 // wave for each entry of a short queue; a row of the scripting grammar that walks 50
 // steps from 7.8 to 4.8.
-template <bool WALKS>
+template <bool WALKS, int THREADS>
 struct FillShared {
   uint32_t words[kSegWords];
 };
@@ -1703,21 +1708,21 @@ __device__ __forceinline__ uint32_t queue_entry(uint32_t e, uint32_t stack, uint
 __device__ __forceinline__ uint32_t list_entry(uint32_t q, uint32_t seg_id0) {
   return ((q & 0x1FFFu) + seg_id0) | ((q >> 13) & 0xFFu) << kEntryPosShift | ((q >> 21) & 7u) << kEntryKindShift;
 }
-// Up to this many entries go to a wave each (walk_wave): six one after the other cost what a lane's longest walk does in
+// Up to so many entries for each wave of the workgroup go to the waves (walk_wave): six one after the other cost what a lane's longest walk does in
 // a grammar of deep walks (C/SQL-like: 23 -> 17 us for a row with a walk of 79 steps; with up to 64 a row of 4358 steps
 // took 137 us instead of 55, with up to 256 as long).  None go to waves in a batch with a cache whose build had walks over
 // the limits: such a fill waits for walks of thousands of steps, of which a wave takes longer than a lane each (what a
-// wave looks ahead for is not there) and only four at a time.  Markup grammar, fills of 3 rows x 128256 and of 8 x 151936
+// wave looks ahead for is not there) and only a few at a time.  Markup grammar, fills of 3 rows x 128256 and of 8 x 151936
 // by waves 4.75 and 4.86 ms, by lanes 3.97 and 4.0.
-constexpr uint32_t kWaveWalks = 24;
+constexpr uint32_t kWaveWalks = 6;  // entries per wave
 constexpr uint32_t kPartShift = 2;  // workgroups that share a segment, as a power of two (PARTS)
-template <>
-struct FillShared<true> {
+template <int THREADS>
+struct FillShared<true, THREADS> {
   uint32_t words[kSegWords];
   uint16_t live[kFillFramesLds];
   uint32_t queue[kWalkQueue];
   uint32_t n_queued;                  // counts on beyond the queue's room
-  uint32_t mem[kFillThreads / 64][kWaveMemWords];
+  uint32_t mem[THREADS / 64][kWaveMemWords];
 };
 
 // What the walks need to know about a row, wherever its state came from.
@@ -1746,15 +1751,15 @@ __device__ __forceinline__ bool walk_start(const WalkRow& row, uint32_t stack, u
   return w.depth > w.drop;
 }
 
-// Decides walk entries, thread t the entries t, t + kFillThreads, ... of the queue (list null; neighbours in it go to
+// Decides walk entries, thread t the entries t, t + THREADS, ... of the queue (list null; neighbours in it go to
 // different waves) or of a list of stack `list_stack` (all threads call this).
-template <bool COUNT, bool KEEP_UNDECIDED, bool INLINE, class Tab>
-__device__ __forceinline__ void fill_walks(const Tab& T, FillShared<true>& sm, const WalkRow& row, const int32_t b, const int32_t id0,
+template <bool COUNT, bool KEEP_UNDECIDED, bool INLINE, int THREADS, class Tab>
+__device__ __forceinline__ void fill_walks(const Tab& T, FillShared<true, THREADS>& sm, const WalkRow& row, const int32_t b, const int32_t id0,
                                            const uint32_t n_ids, const XGM_GLOBAL uint32_t* list, const uint32_t list_stack, const uint32_t n,
                                            const DevVocab& voc, OverflowLog* log, uint32_t seq, unsigned long long& my_steps) {
   const bool frames_in_lds = row.n_frames <= kFillFramesLds;
 #pragma unroll 1
-  for (uint32_t q = list ? threadIdx.x : (threadIdx.x & 63u) * (kFillThreads / 64) + (threadIdx.x >> 6); q < n; q += kFillThreads) {
+  for (uint32_t q = list ? threadIdx.x : (threadIdx.x & 63u) * (THREADS / 64) + (threadIdx.x >> 6); q < n; q += THREADS) {
     uint32_t e, stack = list_stack;
     if (list) {
       e = list[q];
@@ -1783,13 +1788,13 @@ __device__ __forceinline__ void fill_walks(const Tab& T, FillShared<true>& sm, c
   }
 }
 // The same for a short queue, a wave per entry (tables and frames are in LDS).
-template <bool KEEP_UNDECIDED, bool INLINE>
-__device__ __forceinline__ void fill_walks_by_wave(const LdsTabT<true, true>& T, FillShared<true>& sm, const WalkRow& row, const int32_t b,
+template <bool KEEP_UNDECIDED, bool INLINE, int THREADS>
+__device__ __forceinline__ void fill_walks_by_wave(const LdsTabT<true, true>& T, FillShared<true, THREADS>& sm, const WalkRow& row, const int32_t b,
                                                    const int32_t id0, const uint32_t n, const DevVocab& voc, OverflowLog* log, uint32_t seq) {
   const uint32_t wave = uniform(threadIdx.x >> 6);
   WaveMem mem{(XGM_LDS uint32_t*)sm.mem[wave], (XGM_LDS uint32_t*)sm.mem[wave] + kArenaFrames};
 #pragma unroll 1
-  for (uint32_t q = wave; q < n; q += kFillThreads / 64) {
+  for (uint32_t q = wave; q < n; q += THREADS / 64) {
     const uint32_t entry = uniform(sm.queue[q]), e = list_entry(entry, (uint32_t)id0 & ~(kSegTokens - 1u)), stack = entry >> 24;
     const uint32_t id = e & kEntryIdMask, pos = (e >> kEntryPosShift) & 0xFFu;
     const uint32_t rel = id - (uint32_t)id0;
@@ -1823,13 +1828,14 @@ struct FusedApply {
 // INLINE != 0: the states came with the launch (InlineStates, the first argument: read where the arguments lie);
 // rows, stack_hdrs_ and frames_ are then not used.
 template <bool COUNT, int APPLY, uint32_t INLINE, bool WALKS, bool PARTS = false>
-__global__ __launch_bounds__(kFillThreads, WALKS ? 4 : 8) void fill_kernel(const InlineStates<INLINE> states_, const RowDesc* __restrict__ rows,
+__global__ __launch_bounds__(fill_threads(PARTS), WALKS ? (PARTS ? 8 : 4) : 8) void fill_kernel(const InlineStates<INLINE> states_, const RowDesc* __restrict__ rows,
                                                             const uint32_t* __restrict__ stack_hdrs_,
                                                             const uint16_t* __restrict__ frames_, DevVocab voc,
                                                             uint32_t* __restrict__ out, OverflowLog* log, uint32_t seq,
                                                             unsigned long long* step_counter, FusedApply fa, uint32_t wave_walks) {
   extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ FillShared<WALKS> sm;
+  constexpr int kThreads = fill_threads(PARTS);
+  __shared__ FillShared<WALKS, kThreads> sm;
   const XGM_GLOBAL uint32_t* stack_hdrs = (const XGM_GLOBAL uint32_t*)stack_hdrs_;
   const uint32_t tid = threadIdx.x;
   const int32_t b = (int32_t)blockIdx.y, seg = (int32_t)blockIdx.x;
@@ -1840,7 +1846,7 @@ __global__ __launch_bounds__(kFillThreads, WALKS ? 4 : 8) void fill_kernel(const
   const int32_t id0 = w_begin * 32;
   const uint32_t n_ids = (uint32_t)part_words * 32u;
   // LDS is cleared before anything is fetched (a barrier waits for what its threads have in flight)
-  for (int32_t w = tid; w < kSegWords; w += kFillThreads) sm.words[w] = 0u;
+  for (int32_t w = tid; w < kSegWords; w += kThreads) sm.words[w] = 0u;
   if constexpr (WALKS)
     if (tid == 0) sm.n_queued = 0u;
   __syncthreads();
@@ -1867,7 +1873,7 @@ __global__ __launch_bounds__(kFillThreads, WALKS ? 4 : 8) void fill_kernel(const
     entries = (const XGM_GLOBAL uint32_t*)rd.entries;
   }
   const uint32_t hdr_stride = stack_hdr_stride(voc.n_seg);
-  // may the request end here?  then its stop tokens are allowed (the first kFillThreads of them are fetched now)
+  // may the request end here?  then its stop tokens are allowed (the first kThreads of them are fetched now)
   const bool may_end = flags & 1u;
   const int32_t my_stop = may_end && (int32_t)tid < voc.n_stop ? voc.stop_ids[tid] : -1;
   auto take = [&](uint32_t e, uint32_t stack) {
@@ -1910,8 +1916,8 @@ __global__ __launch_bounds__(kFillThreads, WALKS ? 4 : 8) void fill_kernel(const
   };
   // 1 + 2. Two stacks at a time: their headers (the same words for every thread), then, in one go, this
   // thread's words of their bitset rows (Algorithm 1: the union over the parallel stacks) and the first
-  // kFillThreads entries of their lists (most lists are shorter than that); then what is left of the lists.
-  constexpr int kWordsPerThread = kSegWords / kFillThreads;
+  // kThreads entries of their lists (most lists are shorter than that); then what is left of the lists.
+  constexpr int kWordsPerThread = std::max(1, kSegWords / kThreads);
   for (uint32_t s0 = 0; s0 < n_stacks; s0 += 2u) {
     uint32_t acc_row[2];
     uint2 lst[2][kStackLists];
@@ -1928,7 +1934,7 @@ __global__ __launch_bounds__(kFillThreads, WALKS ? 4 : 8) void fill_kernel(const
     for (uint32_t q = 0; q < 2u; ++q) {
 #pragma unroll
       for (int k = 0; k < kWordsPerThread; ++k) {
-        const int32_t w = (int32_t)tid + k * kFillThreads;
+        const int32_t w = (int32_t)tid + k * kThreads;
         aw[q][k] = acc_row[q] != kNoAccRow && w < n_words ? acc[(size_t)acc_row[q] * voc.W + w_begin + w] : 0u;
       }
 #pragma unroll
@@ -1945,19 +1951,19 @@ __global__ __launch_bounds__(kFillThreads, WALKS ? 4 : 8) void fill_kernel(const
     for (uint32_t q = 0; q < 2u; ++q) {
 #pragma unroll
       for (int k = 0; k < kWordsPerThread; ++k)
-        if (aw[q][k]) atomicOr(&sm.words[tid + k * kFillThreads], aw[q][k]);
+        if (aw[q][k]) atomicOr(&sm.words[tid + k * kThreads], aw[q][k]);
 #pragma unroll
       for (uint32_t l = 0; l < kStackLists; ++l) {
         if (lst[q][l].x < lst[q][l].y) {
           if (have[q][l]) take(first[q][l], s0 + q);
-          if (lst[q][l].y - lst[q][l].x > (uint32_t)kFillThreads)
-            for (uint32_t j = lst[q][l].x + kFillThreads + tid; j < lst[q][l].y; j += kFillThreads) take(entries[j], s0 + q);
+          if (lst[q][l].y - lst[q][l].x > (uint32_t)kThreads)
+            for (uint32_t j = lst[q][l].x + kThreads + tid; j < lst[q][l].y; j += kThreads) take(entries[j], s0 + q);
         }
       }
     }
   }
   if (may_end)
-    for (int32_t k = tid; k < voc.n_stop; k += kFillThreads) {
+    for (int32_t k = tid; k < voc.n_stop; k += kThreads) {
       const int32_t rel = (k == (int32_t)tid ? my_stop : voc.stop_ids[k]) - id0;
       if (rel >= 0 && rel < n_words * 32) atomicOr(&sm.words[rel >> 5], 1u << (rel & 31));
     }
@@ -1986,18 +1992,19 @@ __global__ __launch_bounds__(kFillThreads, WALKS ? 4 : 8) void fill_kernel(const
         row.epoch = rows[b].epoch;
       }
       unsigned long long my_steps = 0;
-      stage_tables(tab, smem, kFillThreads);
+      stage_tables_async(tab, smem, kThreads);
       if (row.n_frames <= kFillFramesLds) {
 #pragma unroll 1
-        for (uint32_t k = tid; k < row.n_frames; k += kFillThreads) sm.live[k] = row.frames[row.frame0 + k];
+        for (uint32_t k = tid; k < row.n_frames; k += kThreads) sm.live[k] = row.frames[row.frame0 + k];
       }
+      staged();
       __syncthreads();
       // the queue, or, if it overflowed, list after list
       const uint32_t n_queued = sm.n_queued;
       const bool again = n_queued > kWalkQueue;
       // (the waves' walk lies right behind: where the lanes' comes in between, a launch of few rows takes 0.2 us longer)
       if (!COUNT && __builtin_expect(n_queued <= wave_walks && small_sections_staged(tab) && row.n_frames <= kFillFramesLds, 1))
-        fill_walks_by_wave<APPLY != 0, INLINE != 0>(LdsTabT<true, true>(tab, smem), sm, row, b, id0, n_queued, voc, log, seq);
+        fill_walks_by_wave<APPLY != 0, INLINE != 0, kThreads>(LdsTabT<true, true>(tab, smem), sm, row, b, id0, n_queued, voc, log, seq);
       else
 #pragma unroll 1
       for (uint32_t k = 0; k < (again ? n_stacks * kStackLists : 1u); ++k) {
@@ -2010,21 +2017,21 @@ __global__ __launch_bounds__(kFillThreads, WALKS ? 4 : 8) void fill_kernel(const
         }
         const XGM_GLOBAL uint32_t* from = again ? entries + list.x : nullptr;
         if (small_sections_staged(tab))
-          fill_walks<COUNT, APPLY != 0, INLINE != 0>(LdsTabT<true>(tab, smem), sm, row, b, id0, n_ids, from, k / kStackLists, list.y - list.x, voc, log, seq, my_steps);
+          fill_walks<COUNT, APPLY != 0, INLINE != 0, kThreads>(LdsTabT<true>(tab, smem), sm, row, b, id0, n_ids, from, k / kStackLists, list.y - list.x, voc, log, seq, my_steps);
         else
-          fill_walks<COUNT, APPLY != 0, INLINE != 0>(LdsTab(tab, smem), sm, row, b, id0, n_ids, from, k / kStackLists, list.y - list.x, voc, log, seq, my_steps);
+          fill_walks<COUNT, APPLY != 0, INLINE != 0, kThreads>(LdsTab(tab, smem), sm, row, b, id0, n_ids, from, k / kStackLists, list.y - list.x, voc, log, seq, my_steps);
       }
       __syncthreads();
       if (COUNT && my_steps) atomicAdd(step_counter, my_steps);
     }
   }
   // 4. the words, and the logits of the segment; the last segment also takes the columns beyond the vocabulary
-  for (int32_t w = tid; w < n_words; w += kFillThreads) out[(size_t)b * voc.W + w_begin + w] = sm.words[w];
+  for (int32_t w = tid; w < n_words; w += kThreads) out[(size_t)b * voc.W + w_begin + w] = sm.words[w];
   if constexpr (APPLY != 0) {
     const bool last = seg + 1 == voc.n_seg && (!PARTS || blockIdx.z + 1u == 1u << kPartShift);
     const int32_t e_end = last ? fa.V_logits : min(id0 + (int32_t)n_ids, fa.V_logits), lane = (int32_t)(tid & 63u);
     unsigned char* const logits = fa.logits + (size_t)b * fa.row_stride * APPLY;
-    for (int32_t e0 = id0 + (int32_t)uniform(tid >> 6) * kApplyWaveElems; e0 < e_end; e0 += kSegTokens) {
+    for (int32_t e0 = id0 + (int32_t)uniform(tid >> 6) * kApplyWaveElems; e0 < e_end; e0 += kThreads / 64 * kApplyWaveElems) {
       const int32_t e = e0 + lane * 32;  // (words beyond the vocabulary's are zero, and so are the bits of its last one)
       uint32_t allowed = e < id0 + (int32_t)n_ids ? sm.words[(e - id0) >> 5] : 0u;
       if (e + 32 > e_end) allowed |= e < e_end ? ~0u << (e_end - e) : ~0u;
@@ -2665,12 +2672,12 @@ static void launch_fill_of(const InlineStates<INLINE>& st, const RowDesc* rows, 
   const bool parts = walks.entries >= kManyWalks && grid.x * grid.y <= kFillWalkSlots;
   if (parts) grid.z = 1u << kPartShift;
   auto kernel = walks.entries == 0u ? fill_kernel<false, APPLY, INLINE, false> : parts ? fill_kernel<COUNT, APPLY, INLINE, true, true> : fill_kernel<COUNT, APPLY, INLINE, true>;
-  const uint32_t wave_walks = walks.long_walks ? 0u : kWaveWalks;
+  const uint32_t wave_walks = walks.long_walks ? 0u : (uint32_t)fill_threads(parts) / 64u * kWaveWalks;
   if (done)
-    hipExtLaunchKernelGGL(kernel, grid, dim3(kFillThreads), walks.table_bytes, stream, nullptr, done, 0, st, rows, stack_hdrs, frames, voc, out, log,
+    hipExtLaunchKernelGGL(kernel, grid, dim3(fill_threads(parts)), walks.table_bytes, stream, nullptr, done, 0, st, rows, stack_hdrs, frames, voc, out, log,
                           seq, step_counter, fa, wave_walks);
   else
-    hipLaunchKernelGGL(kernel, grid, dim3(kFillThreads), walks.table_bytes, stream, st, rows, stack_hdrs, frames, voc, out, log, seq, step_counter, fa,
+    hipLaunchKernelGGL(kernel, grid, dim3(fill_threads(parts)), walks.table_bytes, stream, st, rows, stack_hdrs, frames, voc, out, log, seq, step_counter, fa,
                        wave_walks);
 }
 void launch_fill(const RowDesc* rows, const uint32_t* stack_hdrs, const uint16_t* frames, int32_t B, const DevVocab& voc, const FillWalks& walks,
