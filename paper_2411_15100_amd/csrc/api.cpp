@@ -156,6 +156,13 @@ class TempArena {
     pinned_used_ += bytes;
     return p;
   }
+  bool is_pinned(const void* p) const { return pinned_ && (const char*)p >= (const char*)pinned_ && (const char*)p < (const char*)pinned_ + kPinned; }
+  // `bytes` bytes between the device and what staging() gave out: with the next launch of `moves`, or, to or from pageable
+  // memory, by a copy of its own.  (Both sides are the beginnings of blocks of whole 256 bytes.)
+  void move(Moves& moves, void* dst, const void* src, size_t bytes, hipMemcpyKind kind, hipStream_t stream) {
+    if (is_pinned(kind == hipMemcpyHostToDevice ? src : dst)) moves.add(dst, src, bytes);
+    else if (bytes) hip_check(hipMemcpyAsync(dst, src, bytes, kind, stream), "hipMemcpyAsync");
+  }
   // (the host bytes are kept until reset(), so that the copy may run whenever the stream gets to it)
   template <class T>
   T* upload(const std::vector<T>& v, hipStream_t stream) {
@@ -186,7 +193,7 @@ TempArena& temp_arena() {
   return a;
 }
 
-// Host arrays that go to the device in one copy, through pinned memory if there is room (an array copied by itself from
+// Host arrays that go to the device in one piece, through pinned memory if there is room (an array copied by itself from
 // pageable memory keeps the host for 12 us, however small it is, and a build has some twenty of them).  They are read by
 // send().
 class Parts {
@@ -200,11 +207,11 @@ class Parts {
   template <class T>
   size_t add(const std::vector<T>& v) { return add(v.data(), v.size() * sizeof(T)); }
   size_t bytes() const { return bytes_; }
-  void send(void* dst, TempArena& arena, hipStream_t stream) const {
+  void send(void* dst, TempArena& arena, Moves& moves, hipStream_t stream) const {
     char* const h = arena.staging(bytes_);
     for (const Part& p : parts_)
       if (p.bytes) std::memcpy(h + p.at, p.src, p.bytes);
-    if (bytes_) hip_check(hipMemcpyAsync(dst, h, bytes_, hipMemcpyHostToDevice, stream), "hipMemcpyAsync");
+    arena.move(moves, dst, h, bytes_, hipMemcpyHostToDevice, stream);
   }
 
  private:
@@ -739,6 +746,8 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
     static_assert(sizeof(NodeHdr) == sizeof(uint2), "header layout");
     DevTables tab{};
     size_t image_bytes = 0;
+    Moves moves;  // what goes along with the next launch of them
+    auto flush = [&] { launch_moves(moves, stream); moves = Moves(); };
     {
       Parts img;
       if (A.cls.size() != 256 || A.follow.size() != A.rule_names.size())
@@ -760,7 +769,7 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
       c->host.tab = staged_for(tab, kFillLdsBudget);
       img.add(&c->host.tab, sizeof(DevTables), 16);
       c->host.dev_tab = reinterpret_cast<const DevTables*>(d_img + image_bytes);
-      img.send(d_img, arena, stream);
+      img.send(d_img, arena, moves, stream);
     }
 
     const int32_t n_seg = dv.n_seg;
@@ -791,8 +800,10 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
     uint32_t* d_n_pairs = d_plain_count + N;
     uint32_t* d_n_bitset_nodes = d_n_pairs + 1;
     OverflowLog* log = reinterpret_cast<OverflowLog*>(d_stats + log_at);
-    const char* const h_stats = arena.staging(stat_bytes);
-    HIP_OK(hipMemsetAsync(d_plain_count, 0, stat_bytes - plain_at, stream));
+    char* const h_stats = arena.staging(stat_bytes);
+    static_assert(sizeof(OverflowLog) >= 16, "(what is cleared behind its first words)");
+    moves.add(d_plain_count, nullptr, stat_bytes - plain_at);
+    flush();
     {
       std::lock_guard<std::mutex> lock(ctx().mu);
       (void)overflow_log();
@@ -871,7 +882,10 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
       permute(node0, nb);
     }
     HIP_OK(hipGetLastError());
-    auto copy_stats = [&] { HIP_OK(hipMemcpyAsync((void*)h_stats, d_stats, stat_bytes, hipMemcpyDeviceToHost, stream)); };
+    auto copy_stats = [&] {
+      arena.move(moves, h_stats, d_stats, stat_bytes, hipMemcpyDeviceToHost, stream);
+      flush();
+    };
     copy_stats();
 
     // ---- while these kernels run: the contexts of the rules, and the same relation by node (what the accept kernel looks
@@ -1044,7 +1058,7 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
       for (int l = 0; l < c->levels; ++l) at_k[l] = kept.add(c->k_base_host[l]);
       const size_t at_off = kept.add(ctx_off), at_ctx = kept.add(ctx_node), at_nfirst = kept.add(node_ctx_first), at_nctx = kept.add(node_ctx);
       char* const k = keep(slab_alloc<char>(kept.bytes()));
-      kept.send(k, arena, stream);
+      kept.send(k, arena, moves, stream);
       for (int l = 0; l < c->levels; ++l) d_k_base[l] = reinterpret_cast<const uint32_t*>(k + at_k[l]);
       c->host.ctx_off = args.ctx_off = reinterpret_cast<const uint32_t*>(k + at_off);
       c->host.ctx_node = args.ctx_node = reinterpret_cast<const uint16_t*>(k + at_ctx);
@@ -1053,7 +1067,7 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
       const size_t at_rep = temp.add(rep), at_first = temp.add(first), at_tiles = temp.add(tiles), at_rule = temp.add(rule_info),
                    at_forced = temp.add(forced_node);
       char* const t = arena.array<char>(temp.bytes());
-      temp.send(t, arena, stream);
+      temp.send(t, arena, moves, stream);
       d_rep = reinterpret_cast<const int32_t*>(t + at_rep);
       d_first = reinterpret_cast<const uint32_t*>(t + at_first);
       args.tiles = reinterpret_cast<const uint4*>(t + at_tiles);
@@ -1067,12 +1081,13 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
     const size_t open_at = 8, made_at = 16, equal_at = made_at + 16, counts_at = (equal_at + (size_t)N * 4 + 15) / 16 * 16;
     static_assert((kCtxLevels + 1) * 4 <= 16, "the counters of the list kernels");
     char* const d_found = static_cast<char*>(arena.alloc(counts_at + n_slots * 4));
-    const char* const h_found = arena.staging(counts_at);
+    char* const h_found = arena.staging(counts_at);
     uint32_t* d_equal = reinterpret_cast<uint32_t*>(d_found + equal_at);
     uint32_t* d_counts = reinterpret_cast<uint32_t*>(d_found + counts_at);
     args.n_open = reinterpret_cast<uint32_t*>(d_found + open_at);
     args.res_count = reinterpret_cast<uint32_t*>(d_found + made_at);
-    HIP_OK(hipMemsetAsync(d_found, 0, counts_at + n_slots * 4, stream));
+    moves.add(d_found, nullptr, counts_at + n_slots * 4);
+    flush();
     launch_rows_equal(acc_id, N, dv.W, d_rep, d_equal, stream);
     uint32_t* d_base_ids = arena.array<uint32_t>((size_t)n_base);
     uint16_t* d_base_node = arena.array<uint16_t>((size_t)n_base);
@@ -1117,7 +1132,8 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
       launch_slot_offsets(SlotCounts{d_seg_counts, d_counts, (size_t)N * n_seg, n_slots}, reinterpret_cast<unsigned long long*>(d_block_sums),
                           d_key_off, args.front, args.back, reinterpret_cast<unsigned long long*>(d_found), stream);
       HIP_OK(hipGetLastError());
-      HIP_OK(hipMemcpyAsync((void*)h_found, d_found, counts_at, hipMemcpyDeviceToHost, stream));
+      arena.move(moves, h_found, d_found, counts_at, hipMemcpyDeviceToHost, stream);
+      flush();
       HIP_OK(hipStreamSynchronize(stream));
     };
     launch_exit_positions(tab, dv, args, stream);
@@ -1161,7 +1177,8 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
       Parts rows;
       const size_t at_row = rows.add(c->acc_row_host), at_unique = rows.add(unique);
       char* const r = keep(slab_alloc<char>(rows.bytes()));
-      rows.send(r, arena, stream);
+      rows.send(r, arena, moves, stream);
+      flush();
       d_acc_row = reinterpret_cast<uint16_t*>(r + at_row);
       launch_gather_rows(acc_id, dv.W, reinterpret_cast<const int32_t*>(r + at_unique), c->n_acc_rows, acc_rows, stream);
       c->device_bytes += (int64_t)unique.size() * dv.W * 4 + (int64_t)N * 2;

@@ -255,6 +255,17 @@ constexpr size_t kStaticScratchBytes = (size_t)1 << 20;
 hipError_t static_scratch(void** out);
 
 // ---- launchers (all asynchronous on `stream`)
+// Copies and fills with zeros in one launch: device memory and pinned host memory, on 16 bytes, whole pieces of 16 bytes (both
+// sides have room for the last one).
+struct Moves {
+  static constexpr int kMost = 3;
+  struct Move { uint4* dst; const uint4* src; uint32_t n; } move[kMost] = {};  // src null: zeros
+  int count = 0;
+  void add(void* dst, const void* src, size_t bytes) {
+    if (bytes) move[count++] = {static_cast<uint4*>(dst), static_cast<const uint4*>(src), (uint32_t)((bytes + 15) / 16)};
+  }
+};
+void launch_moves(const Moves& moves, hipStream_t stream);
 // (a) classify tokens [all ranks] x nodes [node0, node0 + n_nodes) into rank-space bitsets
 struct ClassifyArgs {
   int32_t node0, n_nodes;
