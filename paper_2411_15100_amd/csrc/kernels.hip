@@ -92,33 +92,23 @@ struct LdsTabT {
       h = *(const XGM_LDS unsigned long long*)(lds + off_hdr + n * 8u);
       return make_uint2(uniform((uint32_t)h), uniform((uint32_t)(h >> 32)));
     }
-    if (n < n_near) h = *(const XGM_LDS unsigned long long*)(lds + off_hdr + n * 8u);
+    if (!XGM_ANY(n >= n_near)) h = *(const XGM_LDS unsigned long long*)(lds + off_hdr + n * 8u);
+    else if (n < n_near) h = *(const XGM_LDS unsigned long long*)(lds + off_hdr + n * 8u);
     else h = *(const XGM_GLOBAL unsigned long long*)(img + off_hdr + (size_t)n * 8u);
     return make_uint2((uint32_t)h, (uint32_t)(h >> 32));
   }
-  __device__ __forceinline__ void lookup(uint32_t n, uint32_t c, uint32_t& k, uint32_t& single, uint32_t& base_out,
-                                         uint32_t& run, bool& pooled, uint32_t& fin, uint32_t& rule) const {
+  __device__ __forceinline__ Looked look(uint32_t n, uint32_t c) const {
     const uint2 h = header(n);
-    k = 0; single = 0; base_out = 0; run = 0; pooled = false;
-    fin = h.y & 1u;
-    rule = h.y >> 16;
-    if (h.y & 2u) {
+    const bool branching = (h.y & 2u) != 0u;
+    Looked r{h.x >> 16, c < (h.x & 0xFFu) || c > ((h.x >> 8) & 0xFFu), h.y & 1u, h.y >> 16};
+    if (XGM_ANY(branching)) {
       const uint32_t cl = rd8(c, cls_lds);
-      const uint32_t si = rd8(off_shapes + (h.x & 0xFFFFu) * n_cls + cl, shapes_lds);
-      if (si != 0xFFu) {
-        const uint32_t a = rd16(off_targets + ((h.x >> 16) + si) * 2u, targets_lds);
-        if (a < 0x8000u) { k = 1; single = (0xFFFFu << 16) | a; }
-        else {
-          base_out = a & 0x7FFFu;
-          k = alt(base_out);
-          pooled = true;
-          if (k & kRunFlagD) { run = k; k = 1; }
-        }
-      }
-    } else {
-      const uint32_t lo = h.x & 0xFFu, hi = (h.x >> 8) & 0xFFu;
-      if (c >= lo && c <= hi) { k = 1; single = (0xFFFFu << 16) | (h.x >> 16); }
+      const uint32_t si = rd8(off_shapes + (branching ? (h.x & 0xFFFFu) * n_cls : 0u) + cl, shapes_lds);
+      const uint32_t a = rd16(off_targets + (branching && si != 0xFFu ? (h.x >> 16) + si : 0u) * 2u, targets_lds);
+      r.to = branching ? a : r.to;
+      r.none = branching ? si == 0xFFu : r.none;
     }
+    return r;
   }
   __device__ __forceinline__ uint32_t alt(uint32_t idx) const { return rd32(off_alts + idx * 4u, alts_lds); }
   __device__ __forceinline__ bool is_final(uint32_t n) const { return header(n).y & 1u; }

@@ -25,35 +25,35 @@ XGM_HD uint32_t run_frames(uint32_t word) { return (word >> 16) & 0x3Fu; }
 XGM_HD uint32_t run_frames_at(uint32_t word) { return word & 0x7FFFu; }
 constexpr uint32_t kLiveBase = 0x8000;  // stack handles >= this refer to the request's live frames
 
-// Table access for the walk: at node n on byte c, how many move / call
-// alternatives are there (k), which (a single packed one, or k entries in the
-// alternatives pool from `base`; a run of calls counts as one and has its first
-// word in `run`), may the rule end at n (fin), and n's rule (for `follows`: can
-// c come right after an instance of it at all).
+// Whether any lane of the wave that gets here has it so (on the host: whether it is so).  What stands behind such a test costs a
+// wave of which no lane needs it one scalar branch, where a test of every lane by itself turns lanes off and on again.
+// (classify_walks_kernel, 11867-node schema grammar x 151936: 301 us with lookups that every lane branched through by itself,
+// 284 so; JSON x 32000 24.9 and 23.7; exit_positions_kernel 18.4 and 17.9, context_level1_kernel 111 and 109.)
+#if defined(__HIP_DEVICE_COMPILE__)
+#define XGM_ANY(condition) (__builtin_amdgcn_ballot_w64(condition) != 0ull)
+#else
+#define XGM_ANY(condition) (condition)
+#endif
+
+// Table access for the walk: what node n does with byte c: `to` = the node that a byte edge leads to, or (kAltFlagD) where in
+// the alternatives pool the moves and calls are, `none` = neither; may the rule end at n (fin), and n's rule (for `follows`:
+// can c come right after an instance of it at all).
+struct Looked {
+  uint32_t to;
+  bool none;
+  uint32_t fin, rule;
+};
 struct CompactTab {
   TabView v;
-  XGM_HD void lookup(uint32_t n, uint32_t c, uint32_t& k, uint32_t& single, uint32_t& base, uint32_t& run, bool& pooled,
-                     uint32_t& fin, uint32_t& rule) const {
+  XGM_HD Looked look(uint32_t n, uint32_t c) const {
     const uint2 h = (n < (uint32_t)v.n_near) ? v.hdr_near[n] : v.hdr_far[n];
-    k = 0; single = 0; base = 0; run = 0; pooled = false;
-    fin = h.y & 1u;
-    rule = h.y >> 16;
+    Looked r{h.x >> 16, c < (h.x & 0xFFu) || c > ((h.x >> 8) & 0xFFu), h.y & 1u, h.y >> 16};
     if (h.y & 2u) {
       const uint32_t si = v.shapes[(h.x & 0xFFFFu) * v.n_cls + v.cls[c]];
-      if (si != 0xFFu) {
-        const uint32_t a = v.targets[(h.x >> 16) + si];
-        if (a < 0x8000u) { k = 1; single = (0xFFFFu << 16) | a; }
-        else {
-          base = a & 0x7FFFu;
-          k = v.alts[base];
-          pooled = true;
-          if (k & kRunFlagD) { run = k; k = 1; }
-        }
-      }
-    } else {
-      const uint32_t lo = h.x & 0xFFu, hi = (h.x >> 8) & 0xFFu;
-      if (c >= lo && c <= hi) { k = 1; single = (0xFFFFu << 16) | (h.x >> 16); }
+      r.none = si == 0xFFu;
+      r.to = r.none ? 0u : v.targets[(h.x >> 16) + si];
     }
+    return r;
   }
   XGM_HD uint32_t alt(uint32_t idx) const { return v.alts[idx]; }
   XGM_HD bool is_final(uint32_t n) const { return ((n < (uint32_t)v.n_near) ? v.hdr_near[n] : v.hdr_far[n]).y & 1u; }
@@ -70,7 +70,7 @@ struct TokenWords {
   XGM_HD explicit TokenWords(const uint4& tk) : w0(tk.x), w1(tk.y), w2(tk.z), w3(tk.w) {}
 };
 XGM_HD uint32_t token_byte(const TokenWords& t, const uint8_t* ext, int i) {
-  if (i < 15) {
+  if (!XGM_ANY(i >= 15) || i < 15) {
     // bit masks instead of selects: a select between loaded values invites the
     // compiler to index a copy in scratch memory
     const uint32_t m4 = 0u - (((uint32_t)i >> 2) & 1u), m8 = 0u - (((uint32_t)i >> 3) & 1u);
@@ -161,43 +161,51 @@ XGM_HD int walk_token_in(Mem& mem, const Tab& T, const uint4 tk, const uint8_t* 
     if (i == len) {
       at_end(n, sp, mem, live);      // then on to the next path
     } else {
-      uint32_t k, single, base, run, fin, rule;
-      bool pooled;
-      T.lookup(n, c, k, single, base, run, pooled, fin, rule);
-      uint32_t can_pop = fin & f;
-      if (sp == kLiveBase) {
-        // The bottom frame may end here (nothing is known below it): noted at once instead of kept as a
-        // pending alternative, so that a run through a rule that may end after every byte (the inside of
-        // a string, a number) leaves nothing to come back to.  (BUILD = false: the end of the root rule.)
-        if (BUILD && can_pop) {
-          const uint32_t fo = T.follows(follow, c);
-          left_frame |= 1u | (fo << 1);
-          if (exits_out && fo) *exits_out |= 1u << (i < 31 ? i : 31);
-        }
-        can_pop = 0u;
-      }
-      // A return in front of a byte that can never follow the rule leads nowhere, or - if all frames below may end their
-      // rules as well - out of the bottom frame in front of a byte that follows it in no context.
-      if (can_pop && !T.follows(rule, c)) {
-        can_pop = 0u;
-        if (BUILD && !PRUNE) {
-          if (sp != looked_at) {
-            uint32_t h = sp;
-            for (down = 1; h < kLiveBase && T.is_final(mem.frame(h) & 0xFFFFu); ++down) h = mem.frame(h) >> 16;
-            if (h >= kLiveBase) left_frame |= 1u;
-            looked_at = sp;
+      const Looked at = T.look(n, c);
+      const uint32_t rule = at.rule;
+      uint32_t can_pop = at.fin & f;
+      if (XGM_ANY(can_pop)) {
+        if (sp == kLiveBase) {
+          // The bottom frame may end here (nothing is known below it): noted at once instead of kept as a
+          // pending alternative, so that a run through a rule that may end after every byte (the inside of
+          // a string, a number) leaves nothing to come back to.  (BUILD = false: the end of the root rule.)
+          if (BUILD && can_pop) {
+            const uint32_t fo = T.follows(follow, c);
+            left_frame |= 1u | (fo << 1);
+            if (exits_out && fo) *exits_out |= 1u << (i < 31 ? i : 31);
           }
-          steps += down;
+          can_pop = 0u;
+        }
+        // A return in front of a byte that can never follow the rule leads nowhere, or - if all frames below may end their
+        // rules as well - out of the bottom frame in front of a byte that follows it in no context.
+        if (can_pop && !T.follows(rule, c)) {
+          can_pop = 0u;
+          if (BUILD && !PRUNE) {
+            if (sp != looked_at) {
+              uint32_t h = sp;
+              for (down = 1; h < kLiveBase && T.is_final(mem.frame(h) & 0xFFFFu); ++down) h = mem.frame(h) >> 16;
+              if (h >= kLiveBase) left_frame |= 1u;
+              looked_at = sp;
+            }
+            steps += down;
+          }
         }
       }
-      const uint32_t total = k + can_pop;
       // nothing but a move along a byte edge (most steps inside a string, a number, a name): taken at once
-      if (alt == 0u && total == 1u && k == 1u && !pooled) {
-        n = single & 0xFFFFu;
+      if (alt == 0u && !can_pop && !at.none && at.to < kAltFlagD) {
+        n = at.to;
         f = 1;
         if (++i < len) c = token_byte(tw, ext, i);
         continue;
       }
+      const bool pooled = !at.none && at.to >= kAltFlagD;
+      const uint32_t base = at.to & ~kAltFlagD;
+      uint32_t k = at.none ? 0u : 1u, run = 0u;  // (a run of calls counts as one)
+      if (pooled) {
+        k = T.alt(base);
+        if (k & kRunFlagD) { run = k; k = 1; }
+      }
+      const uint32_t total = k + can_pop;
       if (alt < total) {
         if (alt + 1 < total) {
           if (csp == kChoicePoints) return kOverflow;
@@ -218,7 +226,7 @@ XGM_HD int walk_token_in(Mem& mem, const Tab& T, const uint4 tk, const uint8_t* 
             f = 0;
             consumes = (run & kRunConsumesD) != 0u;
           } else {
-            const uint32_t e = pooled ? T.alt(base + 1 + alt) : single;
+            const uint32_t e = pooled ? T.alt(base + 1 + alt) : (kMoveTagD << 16) | at.to;
             const uint32_t tag = e >> 16;
             n = e & 0xFFFFu;
             f = 0;
