@@ -586,6 +586,50 @@ def test_schemas_with_long_names_compile(n):
         assert (m.try_accept_bytes(data.encode()) == 0 and m.can_terminate()) == (og.recognize(data.encode()) == 2), data[-20:]
 
 
+# Some 102 states and 101 nodes a literal: around 4000 nodes and 8000 states (from where other threads of the compile make what
+# is not in the tables, and take rules in turn), and far beyond.
+@pytest.mark.parametrize("n", [20, 37, 38, 76, 80, 300])
+def test_grammars_of_many_rules_compile_alike_in_several_threads(n):
+    lits = [_letters(97, 5 * k) + f"{k:03d}" for k in range(n)]
+    text = si.JSON_GRAMMAR + "\ntop ::= root | " + " | ".join(f'"~" f{k}' for k in range(n)) + "\n"
+    text += "\n".join(f'f{k} ::= "{lit}" ("," root)?' for k, lit in enumerate(lits))
+    og, made = oracle.Grammar(text, "top"), [None] * 4
+
+    def compile_one(k):
+        made[k] = xgm.Grammar(text, "top")
+
+    threads = [threading.Thread(target=compile_one, args=(k,)) for k in range(len(made))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+
+    def described(g):
+        return [(g.rule_name(g.node_rule(k)), tuple(g.node_path(k))) for k in range(g.num_nodes)]
+
+    assert made[0].num_nodes > 100 * n and all(described(g) == described(made[0]) for g in made[1:])
+    for g in made:
+        for data in [f"~{lit}{tail}".encode() for lit in (lits[0], lits[n // 2], lits[-1]) for tail in ("", ', {"a": [1e3]}', ",", "x")] + [b"[1, null]", b"~"]:
+            m = xgm.Matcher(grammar=g)
+            assert (m.try_accept_bytes(data) == 0 and m.can_terminate()) == (og.recognize(data) == 2), data
+    # what may follow a rule, and in which contexts: classes of tokens that leave it
+    vocab = TinyVocab([b'"', b'a"', b'", ', b'"}', b'"]', b"1}", b"1]", b"},", b"]", b"9", b" ", lits[0][-2:].encode() + b",", b'"~'])
+    g = made[-1]
+    nodes = [k for k in range(g.num_nodes) if not g.rule_name(g.node_rule(k)).startswith("f") or len(g.node_path(k)) > 99]
+    for node in nodes[:: max(1, len(nodes) // 60)]:
+        want = og.classify(g.rule_name(g.node_rule(node)), g.node_path(node), vocab)
+        assert [g.debug_classify_host(node, t) for t in vocab.toks] == list(want)
+
+
+@pytest.mark.parametrize("extra, status", [("f0 ::= f0 \"x\" | \"y\"", -4), ("f0 ::= " + " ".join(f'"{"x" * 200}{k}"' for k in range(200)), -9)])
+def test_large_grammars_are_refused_as_small_ones_are(extra, status):
+    text = "root ::= " + " | ".join(f"f{k}" for k in range(101)) + "\n" + extra + "\n"
+    text += "\n".join(f'f{k} ::= "{_letters(100, k)}{k}"' for k in range(1, 101))
+    with pytest.raises(xgm.XgmError) as e:
+        xgm.Grammar(text, "root")
+    assert e.value.status == status
+
+
 class _ReferenceRules:
     """Minimal automata of rules from their expressions, the long way: positions of the symbols and which can follow which,
     sets of them, states that lead nowhere taken out, the others split until nothing changes.  An expression is ("bytes",
