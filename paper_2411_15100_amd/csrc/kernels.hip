@@ -1564,6 +1564,7 @@ __device__ __forceinline__ int walk_wave(const LdsTabT<true, true>& T, WaveMem& 
       if (i == len) {
         if constexpr (!Note::kEnumerate) return kAccept;
         note(n, sp, mem, live);
+        ++steps;
         break;  // on to the next path
       }
       ++steps;
@@ -1653,7 +1654,6 @@ __device__ __forceinline__ int walk_wave(const LdsTabT<true, true>& T, WaveMem& 
     top = (ch.y >> 16) & 0xFFu;
     f = (ch.y >> 24) & 1u;
     needed = csp ? (mem.choice(csp - 1).y >> 16) & 0xFFu : 0u;
-    ++steps;
   }
 }
 // Threads of a workgroup; where four share a segment (PARTS) it is for the walks, and twice the waves take them at the same

@@ -310,6 +310,80 @@ def test_device_limits_are_reported_and_the_host_takes_over(xgm, wl):
         xgm.DeviceBatch([xgm.Matcher(grammar=xgm.Grammar(nest, "root"), vocab=xv)], history=1, stream=_stream())
 
 
+@pytest.mark.parametrize("length", [1, 2, 14, 15, 16, 17, 30, 31, 32, 33, 34, 47, 48, 63, 64, 65, 66, 96, 97, 128, 200, 253, 254])
+def test_device_accepts_tokens_of_any_length(xgm, wl, length):
+    """A wave looks at the bytes of a token 32 at a time, and takes what stays at a node or goes to the next one at once: a
+    literal, a loop, alternatives that have to be gone back to (all the way, or where the next 32 bytes begin), and frames
+    that are entered and returned from, with the first bytes already taken (`before`) or not."""
+    letters = "".join(chr(97 + (7 * k + k // 26) % 26) for k in range(300))
+    grammar = f'root ::= "<" (p | q | r | t) | n\np ::= "{letters}" "P"\nq ::= [a-z]+ "Q"\nr ::= "{letters[:28]}" s [a-z]* "R"\ns ::= [a-z]? [a-z]?\n'
+    grammar += 't ::= u "T" | v "!"\nu ::= [a-y] [a-z]* "."? \nv ::= [a-z] u?\nn ::= "(" m ")"\nm ::= n | [a-z]* | "1"'
+    host, og = xgm.Grammar(grammar, "root"), oracle.Grammar(grammar, "root")
+    n = min(length, 50)
+    cases = [(b"<" + letters[:k].encode(), letters[k : k + length - len(end)].encode() + end)
+             for k in (0, 1, 20, 33) for end in (b"", b"Q", b"R", b"!", b"T", b".", b"P", b"#") if length > len(end) or end == b""]
+    cases += [(b"", b"<" + letters[: length - 1].encode()), (b"", b"(" * n), (b"(", b"(" * n), (b"(" * 60 + letters[:9].encode(), b")" * n),
+              (b"(" * 50, letters[: max(1, length - n)].encode() + b")" * min(n, length - 1)), (b"(" * 3, (b"(" * n + b"1" + b")" * length)[:length]),
+              (b"(" * 9, letters[:length].encode()), (b"(" * 9 + b"a", b")" * 10), (b"(" * 9 + b"a", b")" * 9)]
+    cases = [(before, token) for before, token in cases if xgm.Matcher(grammar=host).try_accept_bytes(before) == 0]
+    toks = [token for _, token in cases] + [b"a", b")", b""]
+    offsets = np.concatenate([[0], np.cumsum([len(t) for t in toks])]).astype(np.int64)
+    cache = xgm.Cache(host, xgm.Vocab(np.frombuffer(b"".join(toks), dtype=np.uint8).copy(), offsets, np.array([len(toks) - 1], dtype=np.int32)))
+    ms = [xgm.Matcher(cache=cache) for _ in cases]
+    for m, (before, _) in zip(ms, cases):
+        if before:
+            m.accept_bytes(before)
+    batch = xgm.DeviceBatch(ms, history=2, stream=_stream())
+    batch.accept_tokens(_dev(range(len(cases))).data_ptr(), _stream())
+    status, back, taken = batch.status(_stream()), xgm.Matcher(cache=cache), 0
+    for b, (before, token) in enumerate(cases):
+        want = og.recognize(before + token) > 0
+        assert (status[b] == 0) == want and (want or status[b] == -6), (before, token, status[b])
+        if want:
+            ms[b].accept_token(b)
+        taken += want
+        batch.get_row(b, back, _stream())
+        assert _stacks(back) == _stacks(ms[b]), (before, token)
+    assert taken >= 8 and taken < len(cases)
+
+
+@pytest.mark.parametrize("ways, length", [(2, 8), (2, 9), (3, 6), (5, 4), (8, 3), (10, 3), (11, 3), (30, 2), (40, 2)])
+def test_device_accepts_tokens_of_nearly_as_many_steps_as_it_may_take(xgm, wl, ways, length):
+    """A token of which all but one of `ways` ** length paths end in front of its last byte.  A way is two steps (into its rule,
+    and over a byte), the call of `s` in front of the ways one, and the end of a path one, with the return to what is left to
+    try; the path that is left has a few more.  The device takes 4096."""
+    token = b"x" * length + b"!"
+    toks = [token, b"x", b"!", b"a", b"b", b""]
+    steps = 2 * sum(ways ** k for k in range(1, length + 1)) + sum(ways ** k for k in range(length)) + ways ** length
+    accepted = steps < 4096
+    assert not 4064 < steps < 4096
+
+    class V_:
+        data = np.frombuffer(b"".join(toks), dtype=np.uint8).copy()
+        offsets = np.concatenate([[0], np.cumsum([len(t) for t in toks])]).astype(np.int64)
+        stop_ids = np.array([5], dtype=np.int32)
+        size = len(toks)
+
+    names = [f"w{k}" for k in range(ways)]
+    grammar = "root ::= s | \"x\"+ \"!\" \"a\"\ns ::= " + " | ".join(names) + "\n"
+    grammar += "\n".join(f'{w} ::= "x" s? "{chr(98 + k)}"' for k, w in enumerate(names))
+    cache = xgm.Cache(xgm.Grammar(grammar, "root"), xgm.Vocab(V_.data, V_.offsets, V_.stop_ids))
+    m, om = xgm.Matcher(cache=cache), oracle.EarleyMatcher(oracle.Grammar(grammar, "root"))
+    batch = xgm.DeviceBatch([m], history=2, stream=_stream())
+    batch.accept_tokens(_dev([0]).data_ptr(), _stream())
+    assert (batch.status(_stream())[0] == 0) == accepted
+    if accepted:
+        m.accept_token(0)
+        assert om.advance(token)
+    back = xgm.Matcher(cache=cache)
+    batch.get_row(0, back, _stream())
+    assert _stacks(back) == _stacks(m)
+    d = torch.zeros((1, 1), dtype=torch.int32, device="cuda")
+    batch.fill_next_token_bitmask(d.data_ptr(), _stream())
+    batch.fill_overflow_fixup(_stream())
+    assert np.array_equal(d.cpu().numpy()[0], oracle.pack_bitmask(om.mask(V_)))
+
+
 def test_batch_fill_walks_over_the_limits_are_fixed_up(xgm, wl):
     """A token that pushes more than 64 frames: the fill records it, the fixup
     decides it on the host from the state read back from the device; accepting
