@@ -232,11 +232,13 @@ struct ClassifyShared {
 // listed for classify_walks_kernel: 338 K pairs of an 11867-node schema grammar and 151936 tokens, where the first byte
 // alone leaves 1.56 M of the 28 M.
 // Both kernels write whole words of the rank-space bitsets, 64 tokens of one node, which are lines of their own: only those
-// that are not zero (ClassifyArgs::some_acc).  264 us for that grammar (381 with every word written, 451 MB), and 300 us
+// that are not zero (ClassifyArgs::some_acc).  258 us for that grammar (381 with every word written, 451 MB), and 277 us
 // for the walks, where one kernel that walked all pairs that the first byte leaves took 1663 us; JSON (128256 tokens) 31 to
-// 49 (from run to run) + 34 us, before 163, where a few waves with the walks of whole strings were the last to finish; 32000 tokens 18 + 25, before
+// 49 (from run to run) + 34 us, before 163, where a few waves with the walks of whole strings were the last to finish; 32000 tokens 18 + 24, before
 // 65; a scripting grammar 64 + 152, before 394; the C/SQL-like grammar, whose identifiers are walked to their ends at a
-// hundred nodes, 89 + 957, before 1283.
+// hundred nodes, 80 + 940, before 1283.  (Tables fetched straight into LDS as the accept kernel does, and the next item's tokens
+// ahead of this one's walk: 258 and 262 us instead of 258, JSON 19.3 and 19.3 instead of 18: the waves wait for each other's
+// instructions, not for memory.)
 template <class Tab>
 __device__ __forceinline__ void classify_body(const Tab& T, ClassifyShared& sm, const DevVocab& voc, const ClassifyArgs& a, int32_t n_items_max) {
   // A workgroup owns a run of up to kClassifyItems items of 64 tokens, and kClassifyNodes nodes; lane j of a wave looks at
