@@ -747,7 +747,8 @@ int xgm_cache_build_ex(xgm_grammar* g, xgm_vocab* v, void* hip_stream, uint32_t 
     DevTables tab{};
     size_t image_bytes = 0;
     Moves moves;  // what goes along with the next launch of them
-    auto flush = [&] { launch_moves(moves, stream); moves = Moves(); };
+    // (checked at once, as a copy of the runtime's is: what the host reads or the next kernels count up would be left from before)
+    auto flush = [&] { HIP_OK(launch_moves(moves, stream)); moves = Moves(); };
     {
       Parts img;
       if (A.cls.size() != 256 || A.follow.size() != A.rule_names.size())

@@ -2532,11 +2532,12 @@ hipError_t static_scratch(void** out) {
 }
 
 // ------------------------------------------------------------------ launchers
-void launch_moves(const Moves& moves, hipStream_t stream) {
+hipError_t launch_moves(const Moves& moves, hipStream_t stream) {
   uint32_t most = 0u;
   for (int k = 0; k < moves.count; ++k) most = std::max(most, moves.move[k].n);
-  if (most == 0u) return;
+  if (most == 0u) return hipSuccess;
   hipLaunchKernelGGL(moves_kernel, dim3(std::min((most + kMoveThreads - 1) / kMoveThreads, 1024u)), dim3(kMoveThreads), 0, stream, moves);
+  return hipGetLastError();
 }
 void launch_first_byte(const DevTables& tab, uint4* first_byte, hipStream_t stream) {
   const uint32_t n_words = first_byte_words(tab.n_nodes);

@@ -265,7 +265,7 @@ struct Moves {
     if (bytes) move[count++] = {static_cast<uint4*>(dst), static_cast<const uint4*>(src), (uint32_t)((bytes + 15) / 16)};
   }
 };
-void launch_moves(const Moves& moves, hipStream_t stream);
+hipError_t launch_moves(const Moves& moves, hipStream_t stream);  // (or what a launch in front of it failed with)
 // (a) classify tokens [all ranks] x nodes [node0, node0 + n_nodes) into rank-space bitsets
 struct ClassifyArgs {
   int32_t node0, n_nodes;
