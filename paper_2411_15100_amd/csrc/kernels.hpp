@@ -6,6 +6,7 @@
 #include <hip/hip_vector_types.h>
 
 #include <cstdint>
+#include <stdexcept>
 
 namespace xgm {
 
@@ -262,7 +263,9 @@ struct Moves {
   struct Move { uint4* dst; const uint4* src; uint32_t n; } move[kMost] = {};  // src null: zeros
   int count = 0;
   void add(void* dst, const void* src, size_t bytes) {
-    if (bytes) move[count++] = {static_cast<uint4*>(dst), static_cast<const uint4*>(src), (uint32_t)((bytes + 15) / 16)};
+    if (bytes == 0) return;
+    if (count == kMost) throw std::length_error("Moves: more than one launch takes");
+    move[count++] = {static_cast<uint4*>(dst), static_cast<const uint4*>(src), (uint32_t)((bytes + 15) / 16)};
   }
 };
 hipError_t launch_moves(const Moves& moves, hipStream_t stream);  // (or what a launch in front of it failed with)

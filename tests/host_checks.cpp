@@ -9,6 +9,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <stdexcept>
 #include <string>
 
 #include "../include/xgm.h"
@@ -124,6 +125,26 @@ void moves_that_fail() {
   }
   check(build(-1) == XGM_OK, "a build after those that failed");
 }
+// There is room for kMost of them, and one too many is an error, not a write beyond the room.
+void moves_that_are_too_many() {
+  struct { xgm::Moves moves; unsigned char behind[64]; } m;
+  std::memset(m.behind, 0xAB, sizeof(m.behind));
+  alignas(16) static char memory[64];
+  for (int k = 0; k < xgm::Moves::kMost; ++k) m.moves.add(memory, memory + 16 * k, 16);
+  m.moves.add(memory, nullptr, 0);  // (nothing to do)
+  check(m.moves.count == xgm::Moves::kMost, "as many as there is room for");
+  for (int k = 0; k < xgm::Moves::kMost; ++k) check((char*)m.moves.move[k].src == memory + 16 * k && m.moves.move[k].n == 1, "a move as it was given");
+  bool refused = false;
+  try {
+    m.moves.add(memory, memory + 48, 16);
+  } catch (const std::length_error&) {
+    refused = true;
+  }
+  check(refused && m.moves.count == xgm::Moves::kMost, "one too many is refused");
+  bool untouched = true;
+  for (unsigned char c : m.behind) untouched = untouched && c == 0xAB;
+  check(untouched, "nothing is written beyond the room");
+}
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -131,6 +152,7 @@ int main(int argc, char** argv) {
   library = argc > 2 ? dlopen(argv[1], RTLD_NOW | RTLD_GLOBAL) : nullptr;
   if (!library) { std::fprintf(stderr, "%s\n", dlerror()); return 2; }
   if (what == "moves") moves_that_fail();
+  else if (what == "too_many_moves") moves_that_are_too_many();
   else { std::fprintf(stderr, "no check of this name: %s\n", what.c_str()); return 2; }
   std::printf("%s: %d failures\n", what.c_str(), failures);
   return failures ? 1 : 0;

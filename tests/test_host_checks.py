@@ -28,3 +28,7 @@ def host_checks(tmp_path_factory):
 
 def test_a_build_ends_where_a_copy_cannot_be_launched(host_checks):
     host_checks("moves")
+
+
+def test_copies_that_are_too_many_for_a_launch_are_refused(host_checks):
+    host_checks("too_many_moves")
