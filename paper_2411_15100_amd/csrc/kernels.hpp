@@ -66,16 +66,17 @@ constexpr int32_t kContextLdsBudget = 68 * 1024;  // the list kernels keep 8 KB 
 constexpr int32_t kFillLdsBudget = 31 * 1024;     // of the fill kernel that walks, at most (four workgroups per compute unit then)
 constexpr int32_t kAcceptLdsBudget = 64 * 1024;   // (a row is one workgroup: there is room for one or two per compute unit)
 // The staging split for a kernel that has `budget` bytes of LDS for the tables:
-// as many whole sections as fit, then as many headers as fit.
+// as many whole sections as fit, then as many headers as fit.  The last section counts only with room for a header behind
+// it: the walk of a wave reads the staged headers before it knows whether a lane needs one.
 #if defined(__HIPCC__) || defined(__HIP__)
 __host__ __device__
 #endif
 inline DevTables staged_for(DevTables t, int32_t budget) {
-  const uint32_t ends[5] = {256u, t.off_targets, t.off_follow, t.off_alts, t.off_hdr};  // section ends in image order
+  const uint32_t ends[4] = {256u, t.off_targets, t.off_follow, t.off_alts};  // section ends in image order
   t.lds_end = t.stage_bytes = t.n_near = 0;
   for (uint32_t e : ends)
     if (e <= (uint32_t)budget) t.lds_end = e;
-  if (t.lds_end == t.off_hdr) {
+  if (t.off_hdr + 8u <= (uint32_t)budget) {
     const uint32_t k = ((uint32_t)budget - t.off_hdr) / 8;
     t.n_near = k < (uint32_t)t.n_nodes ? k : (uint32_t)t.n_nodes;
     t.lds_end = t.off_hdr + t.n_near * 8;

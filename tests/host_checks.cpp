@@ -22,6 +22,7 @@ std::map<const void*, std::string>& kernel_names() {
 }
 int n_launches = 0, n_moves = 0, fail_at = -1;  // fail_at: which launch of moves_kernel fails (-1: none)
 int launches_when_it_failed = -1;
+xgm::DevTables tables{};  // of the last build
 hipError_t last_error = hipSuccess;
 struct { dim3 grid, block; size_t shared; hipStream_t stream; } pushed;
 }  // namespace
@@ -38,6 +39,7 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* shared, hi
 }
 hipError_t hipLaunchKernel(const void* f, dim3, dim3, void** args, size_t, hipStream_t) {
   ++n_launches;
+  if (kernel_names()[f].find("first_byte_kernel") != std::string::npos) tables = *static_cast<const xgm::DevTables*>(args[0]);
   if (kernel_names()[f].find("moves_kernel") == std::string::npos) return hipSuccess;
   if (n_moves++ == fail_at) {
     launches_when_it_failed = n_launches;
@@ -145,6 +147,38 @@ void moves_that_are_too_many() {
   for (unsigned char c : m.behind) untouched = untouched && c == 0xAB;
   check(untouched, "nothing is written beyond the room");
 }
+// Where the sections in front of the headers count as staged, a header is staged too: walk_wave reads the first of them
+// whether a lane needs one or not.
+void staging_of_tables() {
+  for (int32_t budget : {xgm::kFillLdsBudget, xgm::kAcceptLdsBudget, xgm::kContextLdsBudget, xgm::kClassifyLdsBudget})
+    for (int32_t off_hdr = budget - 64; off_hdr <= budget + 64; off_hdr += 16)
+      for (int32_t n_nodes : {1, 2, 3, 5, 9, 1000}) {
+        xgm::DevTables t{};
+        t.off_shapes = 256; t.off_targets = 1024; t.off_follow = 2048; t.off_alts = 4096;
+        t.off_hdr = (uint32_t)off_hdr;
+        t.n_nodes = n_nodes;
+        const xgm::DevTables s = xgm::staged_for(t, budget);
+        const std::string what = "tables of " + std::to_string(off_hdr) + " bytes and " + std::to_string(n_nodes) + " headers in " + std::to_string(budget);
+        check(s.stage_bytes <= (uint32_t)budget && s.stage_bytes >= s.lds_end && s.stage_bytes - s.lds_end < 16, what + ": bytes");
+        check(s.n_near <= (uint32_t)n_nodes, what + ": headers");
+        if (s.lds_end >= t.off_hdr) check(s.n_near >= 1 && s.lds_end == t.off_hdr + s.n_near * 8, what + ": sections without a header");
+        else check(off_hdr + 8 > budget && s.lds_end == t.off_alts && s.n_near == 0, what + ": a section less than there is room for");
+      }
+}
+// Where the headers of a grammar's tables begin (the grammar's text from stdin, its root rule "root").
+void headers_begin() {
+  std::string text;
+  for (int c; (c = std::getchar()) != EOF;) text += (char)c;
+  xgm_grammar* g = nullptr;
+  xgm_vocab* v = nullptr;
+  xgm_cache* cache = nullptr;
+  const uint8_t bytes[] = "a";
+  const int64_t offsets[] = {0, 1, 1};
+  const int32_t stop = 1;
+  check(XGM(xgm_grammar_compile)(text.data(), text.size(), "root", &g) == XGM_OK && XGM(xgm_vocab_create)(bytes, offsets, 2, &stop, 1, &v) == XGM_OK &&
+        XGM(xgm_cache_build)(g, v, nullptr, &cache) == XGM_OK, XGM(xgm_last_error)());
+  std::printf("%u\n", tables.off_hdr);
+}
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -152,6 +186,8 @@ int main(int argc, char** argv) {
   library = argc > 2 ? dlopen(argv[1], RTLD_NOW | RTLD_GLOBAL) : nullptr;
   if (!library) { std::fprintf(stderr, "%s\n", dlerror()); return 2; }
   if (what == "moves") moves_that_fail();
+  else if (what == "staging") staging_of_tables();
+  else if (what == "headers") headers_begin();
   else if (what == "too_many_moves") moves_that_are_too_many();
   else { std::fprintf(stderr, "no check of this name: %s\n", what.c_str()); return 2; }
   std::printf("%s: %d failures\n", what.c_str(), failures);

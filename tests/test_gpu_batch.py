@@ -10,6 +10,7 @@ import pytest
 
 import oracle
 import synth_inputs as si
+from test_host_checks import EXACT, nested_grammar
 
 pytestmark = pytest.mark.gpu
 
@@ -382,6 +383,48 @@ def test_device_accepts_tokens_of_nearly_as_many_steps_as_it_may_take(xgm, wl, w
     batch.fill_next_token_bitmask(d.data_ptr(), _stream())
     batch.fill_overflow_fixup(_stream())
     assert np.array_equal(d.cpu().numpy()[0], oracle.pack_bitmask(om.mask(V_)))
+
+
+@pytest.mark.parametrize("room", EXACT)
+@pytest.mark.parametrize("more", [-1, 0, 1])
+def test_tables_as_large_as_the_room_for_them(xgm, room, more):
+    """Tables of which the sections in front of the headers fill the room in LDS exactly (more = 0: nothing is left for a
+    header), leave room for a few headers, or do not fit."""
+    rules, digits = EXACT[room]
+    text = nested_grammar(rules + more, digits)
+    toks = [b"(", b")", b"))", b")))", b"))))", b")))))))", b"((((", b"a", b"xyz", b"ab))))", b"1)))))", b"(1)", b"<", b"a" * 9, b"aab", b"=", b"e", b"]", b""]
+
+    class V_:
+        data = np.frombuffer(b"".join(toks), dtype=np.uint8).copy()
+        offsets = np.concatenate([[0], np.cumsum([len(t) for t in toks])]).astype(np.int64)
+        stop_ids = np.array([len(toks) - 1], dtype=np.int32)
+        size = len(toks)
+
+    cache, og = xgm.Cache(xgm.Grammar(text, "root"), xgm.Vocab(V_.data, V_.offsets, V_.stop_ids)), oracle.Grammar(text, "root")
+    texts = [b"", b"(", b"(((((ab", b"((((((((1", b"(((((((((", b"((((())", b"<aaa", b"(" * 40 + b"q", b"=e" if digits == 0 else b"=e("]
+    ms, oms = [xgm.Matcher(cache=cache) for _ in texts], [oracle.EarleyMatcher(og) for _ in texts]
+    for m, om, t in zip(ms, oms, texts):
+        m.accept_bytes(t)
+        assert om.advance(t)
+    batch, scratch = xgm.DeviceBatch(ms, history=8, stream=_stream()), xgm.Matcher(cache=cache)
+    d = torch.zeros((len(texts), 1), dtype=torch.int32, device="cuda")
+    for step in range(6):
+        d.fill_(-1)
+        batch.fill_next_token_bitmask(d.data_ptr(), _stream())
+        want = np.stack([om.mask(V_) for om in oms])
+        assert np.array_equal(d.cpu().numpy(), oracle.pack_bitmask(want)), step
+        ids = []
+        for b, w in enumerate(want):  # the longest token that is allowed, the second longest, ...
+            allowed = sorted((k for k in range(V_.size - 1) if w[k]), key=lambda k: -len(toks[k]))
+            ids.append(allowed[(step + b) % len(allowed)] if allowed else -1)
+        batch.accept_tokens(_dev(ids).data_ptr(), _stream())
+        assert not batch.status(_stream()).any()
+        for b, k in enumerate(ids):
+            if k >= 0:
+                ms[b].accept_token(k)
+                assert oms[b].advance(toks[k])
+            batch.get_row(b, scratch, _stream())
+            assert _stacks(scratch) == _stacks(ms[b]), (step, b)
 
 
 def test_batch_fill_walks_over_the_limits_are_fixed_up(xgm, wl):

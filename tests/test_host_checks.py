@@ -19,9 +19,10 @@ def host_checks(tmp_path_factory):
     subprocess.run([os.environ.get("CXX", "g++"), "-O1", "-std=c++17", "-Wall", "-rdynamic", "-pthread", "-D__HIP_PLATFORM_AMD__", "-isystem", include,
                     os.path.join(HERE, "host_checks.cpp"), "-o", out, "-ldl"], check=True)
 
-    def run(what):
-        done = subprocess.run([out, lib_build.LIB, what], capture_output=True, text=True, timeout=120)
+    def run(what, text=""):
+        done = subprocess.run([out, lib_build.LIB, what], input=text, capture_output=True, text=True, timeout=120)
         assert done.returncode == 0, done.stdout + done.stderr
+        return done.stdout
 
     return run
 
@@ -32,3 +33,23 @@ def test_a_build_ends_where_a_copy_cannot_be_launched(host_checks):
 
 def test_copies_that_are_too_many_for_a_launch_are_refused(host_checks):
     host_checks("too_many_moves")
+
+
+def nested_grammar(rules, digits=0):
+    """Nested brackets, next to a chain of rules that does nothing but make the tables larger: 42 bytes a rule."""
+    text = 'root ::= n | "<" c0 | "=" e\nn ::= "(" m ")"\nm ::= n | [a-z]* | "1"\ne ::= "e"' + " ([0-9] | n)" * digits + "\n"
+    return text + "".join(f'c{k} ::= "a" c{k + 1}\n' for k in range(rules)) + f'c{rules} ::= "z"\n'
+
+
+# (rules, digits) of which the tables in front of the headers are exactly as large as the room that a fill (31 KB) or an
+# accept (64 KB) has for tables
+EXACT = {31 * 1024: (743, 0), 64 * 1024: (1547, 1)}
+
+
+def test_tables_that_count_as_staged_have_a_header_staged(host_checks):
+    host_checks("staging")
+
+
+@pytest.mark.parametrize("room", EXACT)
+def test_grammars_whose_tables_fill_the_room_exactly(host_checks, room):
+    assert int(host_checks("headers", nested_grammar(*EXACT[room])).split()[0]) == room
