@@ -2063,7 +2063,7 @@ struct AcceptShared {
   uint32_t common[kBatchMaxStacks][kBatchMaxStacks]; // frames that two of them have in common, from the bottom
   uint32_t slot_of[kBatchMaxStacks];                 // the new stacks in order
   uint32_t mem[kAcceptThreads / 64][kWaveMemWords];
-  uint32_t cache[sizeof(DevCache) / 4];              // the row's DevCache
+  alignas(DevCache) uint32_t cache[sizeof(DevCache) / 4];  // the row's DevCache
   uint32_t count, overflow, duplicates, can_end, bad_context, n_frames;
   __device__ __forceinline__ uint32_t kept(uint32_t i) const { return (from[i] >> 8) & 0xFFu; }
   __device__ __forceinline__ uint32_t depth(uint32_t i) const { return kept(i) + (from[i] >> 16); }
@@ -2175,6 +2175,7 @@ __global__ __launch_bounds__(kAcceptThreads) void batch_accept_kernel(DevBatch b
   // (every thread fetches, whether there is something for it or not: a load under a condition is waited for at its end)
   static_assert(kStackHdrTop == 0 && kStackHdrDepth == 1 && kStackHdrFrames == 2, "a stack's scalars lie side by side");
   static_assert(kAcceptThreads >= sizeof(DevCache) / 4 && sizeof(DevCache) % 8 == 0, "a word of the DevCache for each thread");
+  static_assert(alignof(AcceptShared) >= alignof(DevCache) && offsetof(AcceptShared, cache) % alignof(DevCache) == 0, "its pointers are read from there");
   const uint32_t* const frames = reinterpret_cast<const uint32_t*>(bt.frames + (size_t)at * kBatchRowFrames);
   const uint32_t* const h = bt.hdrs + (size_t)(at * kBatchMaxStacks + tid % kBatchMaxStacks) * hdr_stride;
   const uint32_t two = frames[tid], h_depth = h[kStackHdrDepth], h_frames = h[kStackHdrFrames];
