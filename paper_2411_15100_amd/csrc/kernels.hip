@@ -1815,7 +1815,13 @@ __device__ __forceinline__ void fill_walks_by_wave(const LdsTabT<true, true>& T,
   }
 }
 
-// The second launch bound keeps the kernel within the registers that eight (four) workgroups per compute unit leave.
+// The second launch bound (waves per SIMD): the kernel without walks keeps within the registers that eight workgroups per
+// compute unit leave.  With walks the scalar registers are what counts: up to seven waves have 106 of them, eight have 78, for
+// which the compiler moved 52 to 109 of them to lanes of vector registers and back (17 to 38 with 106), in walks that wait for
+// every instruction.  Where four workgroups of 512 threads share a segment that is three of them per compute unit instead of four,
+// and still faster.  Mask and bf16 logits in one launch, V = 128256, us with a bound of eight and of six, three draws of
+// states each: 24 rows of the C/SQL-like grammar 23.6, 32.6, 13.8 and 22.5, 32.4, 12.8; 64 rows 31.9, 41.0, 56.6 and 32.4, 40.6,
+// 55.7; 16 rows of the scripting grammar (two draws) 12.5, 30 and 10.5, 24.4; 200 C/SQL-like rows x 32000 53.5 and 49.1.
 // APPLY = 0: the mask only.  APPLY = 2 / 4 (bytes per logit): the workgroup
 // also writes -inf into the logits of its (row, segment) straight from its
 // LDS words (section 2.1), which saves a launch and the re-read of the mask.
@@ -1831,7 +1837,7 @@ struct FusedApply {
 // INLINE != 0: the states came with the launch (InlineStates, the first argument: read where the arguments lie);
 // rows, stack_hdrs_ and frames_ are then not used.
 template <bool COUNT, int APPLY, uint32_t INLINE, bool WALKS, bool PARTS = false>
-__global__ __launch_bounds__(fill_threads(PARTS), WALKS ? (PARTS ? 8 : 4) : 8) void fill_kernel(const InlineStates<INLINE> states_, const RowDesc* __restrict__ rows,
+__global__ __launch_bounds__(fill_threads(PARTS), WALKS ? (PARTS ? 6 : 4) : 8) void fill_kernel(const InlineStates<INLINE> states_, const RowDesc* __restrict__ rows,
                                                             const uint32_t* __restrict__ stack_hdrs_,
                                                             const uint16_t* __restrict__ frames_, DevVocab voc,
                                                             uint32_t* __restrict__ out, OverflowLog* log, uint32_t seq,

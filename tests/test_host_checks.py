@@ -1,7 +1,10 @@
 """Checks of the native library on the host, by a program that stands in for the HIP runtime (host_checks.cpp)."""
 
 import os
+import re
+import struct
 import subprocess
+import tempfile
 
 import pytest
 
@@ -53,3 +56,28 @@ def test_tables_that_count_as_staged_have_a_header_staged(host_checks):
 @pytest.mark.parametrize("room", EXACT)
 def test_grammars_whose_tables_fill_the_room_exactly(host_checks, room):
     assert int(host_checks("headers", nested_grammar(*EXACT[room])).split()[0]) == room
+
+
+def test_kernels_keep_their_registers():
+    """No kernel keeps vector registers in memory; the fills that walk move a few dozen scalar registers to lanes of vector
+    registers and back (up to 38 today), not a hundred: their walks wait for every instruction."""
+    readelf = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin", "llvm-readelf")
+    if not os.path.exists(readelf):
+        pytest.skip("no llvm-readelf")
+    data = open(lib_build.LIB, "rb").read()
+    bundle = data.index(b"__CLANG_OFFLOAD_BUNDLE__")
+    at, code = bundle + 32, b""
+    for _ in range(struct.unpack_from("<Q", data, bundle + 24)[0]):
+        offset, size, length = struct.unpack_from("<QQQ", data, at)
+        if data[at + 24 : at + 24 + length].endswith(b"gfx950"):
+            code = data[bundle + offset : bundle + offset + size]
+        at += 24 + length
+    with tempfile.NamedTemporaryFile(suffix=".co") as f:
+        f.write(code)
+        f.flush()
+        notes = subprocess.run([readelf, "--notes", f.name], capture_output=True, text=True, check=True).stdout
+    kernels = re.findall(r"\.name: +(\S+).*?\.sgpr_spill_count: (\d+).*?\.vgpr_spill_count: (\d+)", notes, re.S)
+    fills = [int(sgpr) for name, sgpr, _ in kernels if "11fill_kernel" in name]
+    assert len(kernels) > 50 and len(fills) > 20
+    assert all(int(vgpr) == 0 for _, _, vgpr in kernels)
+    assert max(fills) <= 48
