@@ -1658,12 +1658,10 @@ __device__ __forceinline__ int walk_wave(const LdsTabT<true, true>& T, WaveMem& 
     needed = csp ? (mem.choice(csp - 1).y >> 16) & 0xFFu : 0u;
   }
 }
-// Threads of a workgroup; where four share a segment (PARTS) it is for the walks, and twice the waves take them at the same
-// time (the tables in LDS leave room for as many such workgroups as of the others).  A workgroup of a row of the C/SQL-like
-// grammar has up to 15 walks of up to 40 000 clocks.  24 such rows, V = 128256, fill and apply, us with 256 threads and with
-// 512 (tables fetched straight into LDS too): 25.3 and 19.9, another draw of states 36.0 and 28.4; five fills and four accepts of 8
-// rows of the scripting grammar 100 and 89.
-constexpr int fill_threads(bool parts) { return parts ? 512 : 256; }
+// Threads of a workgroup that has a segment to itself.  Where four share one (PARTS: their threads) it is for the walks: see
+// part_threads().
+constexpr int kFillThreads = 256;
+constexpr int fill_threads(int parts) { return parts ? parts : kFillThreads; }
 constexpr int kFillFramesLds = 1024;            // live frames kept in LDS (deeper stacks: global memory)
 
 // One workgroup of 4 waves serves one request and one segment of 8192 token
@@ -1836,8 +1834,8 @@ struct FusedApply {
 
 // INLINE != 0: the states came with the launch (InlineStates, the first argument: read where the arguments lie);
 // rows, stack_hdrs_ and frames_ are then not used.
-template <bool COUNT, int APPLY, uint32_t INLINE, bool WALKS, bool PARTS = false>
-__global__ __launch_bounds__(fill_threads(PARTS), WALKS ? (PARTS ? 6 : 4) : 8) void fill_kernel(const InlineStates<INLINE> states_, const RowDesc* __restrict__ rows,
+template <bool COUNT, int APPLY, uint32_t INLINE, bool WALKS, int PARTS = 0>
+__global__ __launch_bounds__(fill_threads(PARTS), WALKS ? (PARTS > kFillThreads ? 6 : 4) : 8) void fill_kernel(const InlineStates<INLINE> states_, const RowDesc* __restrict__ rows,
                                                             const uint32_t* __restrict__ stack_hdrs_,
                                                             const uint16_t* __restrict__ frames_, DevVocab voc,
                                                             uint32_t* __restrict__ out, OverflowLog* log, uint32_t seq,
@@ -2680,21 +2678,43 @@ void launch_batch_headers(const DevBatch& bt, int32_t row0, int32_t n, int32_t s
 // ever walk does not run four workgroups per compute unit for it: one launch of 128 JSON rows x 151936, mask and bf16
 // logits, 10.83 us with 31 KB for all of them, 9.84 so; 127 schema rows and one JSON row, or one of the scripting
 // grammar, 9.3 and 8.46 (8.25 without that row); batches of rows that walk a lot take as long either way.
-constexpr uint32_t kFillWalkSlots = 4 * 256;  // workgroups that the chip has room for if each has 31 KB of tables
+constexpr uint32_t kFillWalkSlots = 4 * 256;  // workgroups of 256 threads that the chip has room for if each has 31 KB of tables
+// Threads of the workgroups that share segments.  With 512 twice the waves take the walks of a part, up to 15 of up to 40 000
+// clocks in a row of the C/SQL-like grammar; three such workgroups fit a compute unit (scalar registers: 24 of 28 waves),
+// whatever its tables.  Of those with 256 threads seven fit if the tables are small: where there are many times more workgroups
+// than the chip holds, that counts for more.  Mask and bf16 logits in one launch, V = 128256, us with 256 and with 512 threads,
+// two or three draws of states.  Tables of 10 KB (scripting grammar), by rows: 8: 7.0, 25.6 and 7.0, 21.0; 16: 11.0, 28.3 and
+// 10.4, 24.3; 32: 28.7, 28.6 and 26.2, 26.5; 40 (2560 workgroups): 29.0, 28.7 and 29.2, 28.2; 44: 29.6, 31.7 and 29.9, 33.4;
+// 64: 35.3, 33.9, 33.2 and 42.7, 40.3, 38.2; 128 rows x 64000: 35.6, 34.5 and 40.5, 37.2.  Tables of 26 KB (C/SQL-like: four
+// workgroups of 256 threads, 16 waves): 24: 24 to 32, 38, 12.1 and 22.5, 32.5, 12.9; 40: 36.8, 55.7 and 33.2, 48.4; 64: 28.8
+// to 36.7, 41.1, 59.7 and 32.3, 40.6, 55.6; 128 x 64000: 60.0, 61.8 and 56.4, 57.9; 200 x 32000: 56.6 and 49.5.
+constexpr uint32_t kManyPartBlocks = 10 * 256;
+static int part_threads(uint32_t blocks, uint32_t table_bytes) {
+  constexpr uint32_t kLds = 160 * 1024;  // of a compute unit
+  static_assert(3 * (sizeof(FillShared<true, 512>) + kFillLdsBudget) <= kLds, "three workgroups of 512 threads per compute unit");
+  static_assert(4 * (sizeof(FillShared<true, kFillThreads>) + kFillLdsBudget) <= kLds, "four of 256");
+  const uint32_t fit = std::min<uint32_t>(7u, kLds / (uint32_t)(sizeof(FillShared<true, kFillThreads>) + table_bytes));
+  return blocks > kManyPartBlocks && fit * kFillThreads > 3u * 512u ? kFillThreads : 512;
+}
 template <bool COUNT, int APPLY, uint32_t INLINE>
 static void launch_fill_of(const InlineStates<INLINE>& st, const RowDesc* rows, const uint32_t* stack_hdrs, const uint16_t* frames, int32_t B,
                            const DevVocab& voc, const FillWalks& walks, uint32_t* out, OverflowLog* log, uint32_t seq, unsigned long long* step_counter,
                            hipStream_t stream, const FusedApply& fa, hipEvent_t done = nullptr) {
   dim3 grid(voc.n_seg, B);
-  const bool parts = walks.entries >= kManyWalks && grid.x * grid.y <= kFillWalkSlots;
-  if (parts) grid.z = 1u << kPartShift;
-  auto kernel = walks.entries == 0u ? fill_kernel<false, APPLY, INLINE, false> : parts ? fill_kernel<COUNT, APPLY, INLINE, true, true> : fill_kernel<COUNT, APPLY, INLINE, true>;
-  const uint32_t wave_walks = walks.long_walks ? 0u : (uint32_t)fill_threads(parts) / 64u * kWaveWalks;
+  const bool shared = walks.entries >= kManyWalks && grid.x * grid.y <= kFillWalkSlots;
+  const int parts = shared ? part_threads(grid.x * grid.y << kPartShift, walks.table_bytes) : 0;
+  if (shared) grid.z = 1u << kPartShift;
+  auto kernel = walks.entries == 0u  ? fill_kernel<false, APPLY, INLINE, false>
+                : parts == 0         ? fill_kernel<COUNT, APPLY, INLINE, true>
+                : parts == 512       ? fill_kernel<COUNT, APPLY, INLINE, true, 512>
+                                     : fill_kernel<COUNT, APPLY, INLINE, true, kFillThreads>;
+  const dim3 threads(fill_threads(parts));
+  const uint32_t wave_walks = walks.long_walks ? 0u : threads.x / 64u * kWaveWalks;
   if (done)
-    hipExtLaunchKernelGGL(kernel, grid, dim3(fill_threads(parts)), walks.table_bytes, stream, nullptr, done, 0, st, rows, stack_hdrs, frames, voc, out, log,
+    hipExtLaunchKernelGGL(kernel, grid, threads, walks.table_bytes, stream, nullptr, done, 0, st, rows, stack_hdrs, frames, voc, out, log,
                           seq, step_counter, fa, wave_walks);
   else
-    hipLaunchKernelGGL(kernel, grid, dim3(fill_threads(parts)), walks.table_bytes, stream, st, rows, stack_hdrs, frames, voc, out, log, seq, step_counter, fa,
+    hipLaunchKernelGGL(kernel, grid, threads, walks.table_bytes, stream, st, rows, stack_hdrs, frames, voc, out, log, seq, step_counter, fa,
                        wave_walks);
 }
 void launch_fill(const RowDesc* rows, const uint32_t* stack_hdrs, const uint16_t* frames, int32_t B, const DevVocab& voc, const FillWalks& walks,

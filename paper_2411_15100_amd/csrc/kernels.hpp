@@ -63,7 +63,7 @@ struct TabView {
 // LDS budgets (bytes of dynamic shared memory) for the staged tables
 constexpr int32_t kClassifyLdsBudget = 76 * 1024;
 constexpr int32_t kContextLdsBudget = 68 * 1024;  // the list kernels keep 8 KB of counters beside the tables
-constexpr int32_t kFillLdsBudget = 31 * 1024;     // of the fill kernel that walks, at most (four workgroups per compute unit then)
+constexpr int32_t kFillLdsBudget = 31 * 1024;     // of the fill kernel that walks, at most (four workgroups of 256 threads per compute unit then, three of 512)
 constexpr int32_t kAcceptLdsBudget = 64 * 1024;   // (a row is one workgroup: there is room for one or two per compute unit)
 // The staging split for a kernel that has `budget` bytes of LDS for the tables:
 // as many whole sections as fit, then as many headers as fit.  The last section counts only with room for a header behind

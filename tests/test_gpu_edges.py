@@ -160,6 +160,49 @@ def test_walk_entries(xgm, wl, V):
     assert xgm.overflow_total() == before
 
 
+# Four workgroups share a segment, of 512 threads or, where there are more than 2560 of them and the tables are small
+# (scripting grammar, not the C/SQL-like one), of 256; more than 1024 segments are not shared.
+@pytest.mark.parametrize("script_only", [True, False])
+@pytest.mark.parametrize("rows", [160, 161, 256, 257])
+def test_walk_entries_of_large_batches(xgm, wl, rows, script_only):
+    vocab = si.make_vocab("bpe", 30000, 7)
+    xv = wl.make_xgm_vocab(vocab)
+    states = [(0, b"x=1"), (0, b"if v==1:x=(1"), (0, b"while x:v[1"), (0, b"x=\"a"), (0, b"def v(x):return v[1]+1"), (0, b"")]
+    if not script_only:
+        states += [(1, b"int x"), (1, b""), (1, b"int x;")]
+    texts = [si.PYDSL_GRAMMAR, si.CSQL_GRAMMAR]
+    caches, ogs = [xgm.Cache(xgm.Grammar(t, "root"), xv) for t in texts], [oracle.Grammar(t, "root") for t in texts]
+    ms, oms = [], []
+    for k, t in states:
+        m, om = xgm.Matcher(cache=caches[k]), oracle.EarleyMatcher(ogs[k])
+        if t:
+            if m.try_accept_bytes(t) != 0:
+                continue
+            assert om.advance(t)
+        ms.append(m)
+        oms.append(om)
+    assert len(ms) >= len(states) - 1
+    want = np.stack([om.mask(vocab) for om in oms])
+    which = [(5 * b + b // 7) % len(ms) for b in range(rows)]
+    bits, allowed = oracle.pack_bitmask(want)[which], torch.from_numpy(np.pad(want, ((0, 0), (0, 16))))[which]
+    before = xgm.overflow_total()
+    resident = xgm.DeviceBatch([ms[k] for k in which], history=0, stream=_stream())
+    d_mask = torch.full((rows, xgm.bitmask_words(vocab.size)), -1, dtype=torch.int32, device="cuda")
+    resident.fill_next_token_bitmask(d_mask.data_ptr(), _stream())
+    assert np.array_equal(d_mask.cpu().numpy(), bits), "resident states"
+    d_mask.fill_(-1)
+    xgm.fill_next_token_bitmask([ms[k] for k in which], d_mask.data_ptr(), _stream())
+    assert np.array_equal(d_mask.cpu().numpy(), bits), "host-side states"
+    for dt, code in ((torch.bfloat16, xgm.DTYPE_BF16), (torch.float32, xgm.DTYPE_F32)):
+        logits = torch.randn((rows, 30016), device="cuda").to(dt)
+        was = logits.cpu()
+        d_mask.fill_(-1)
+        resident.fill_and_apply(d_mask.data_ptr(), logits.data_ptr(), code, 30016, 30016, stream=_stream())
+        assert np.array_equal(d_mask.cpu().numpy(), bits), "one launch"
+        assert torch.equal(logits.cpu(), torch.where(allowed, was, torch.full_like(was, float("-inf")))), dt
+    assert xgm.overflow_total() == before
+
+
 # Logits rows that begin anywhere: groups of 16 bytes in front of the row, behind it, and where the mask's words or a
 # workgroup's 8192 elements end; rows narrower and wider than the mask.
 @pytest.mark.parametrize("dtype_name", ["f32", "bf16"])
