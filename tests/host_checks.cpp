@@ -5,12 +5,19 @@
 #include <dlfcn.h>
 #include <hip/hip_runtime_api.h>
 
+#include <pthread.h>
+#include <sched.h>
+
+#include <algorithm>
+#include <atomic>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <map>
 #include <stdexcept>
 #include <string>
+#include <thread>
+#include <vector>
 
 #include "../include/xgm.h"
 #include "../paper_2411_15100_amd/csrc/kernels.hpp"
@@ -26,6 +33,26 @@ xgm::DevTables tables{};  // of the last build
 hipError_t last_error = hipSuccess;
 struct { dim3 grid, block; size_t shared; hipStream_t stream; } pushed;
 }  // namespace
+
+// Threads that the library starts pass through here: how many, and how many at the same time.
+std::atomic<int> started{0}, alive{0}, most{0};
+thread_local bool own = false;  // this thread starts threads of the checks
+struct Start { void* (*run)(void*); void* arg; };
+static void* counted(void* p) {
+  const Start s = *static_cast<Start*>(p);
+  delete static_cast<Start*>(p);
+  ++started;
+  const int now = ++alive;
+  for (int m = most; now > m && !most.compare_exchange_weak(m, now);) {}
+  void* const r = s.run(s.arg);
+  --alive;
+  return r;
+}
+extern "C" int pthread_create(pthread_t* t, const pthread_attr_t* a, void* (*run)(void*), void* arg) noexcept {
+  using Create = int(pthread_t*, const pthread_attr_t*, void* (*)(void*), void*);
+  static Create* const create = reinterpret_cast<Create*>(dlsym(RTLD_NEXT, "pthread_create"));
+  return own ? create(t, a, run, arg) : create(t, a, counted, new Start{run, arg});
+}
 
 extern "C" {
 void** __hipRegisterFatBinary(const void*) { static void* handle; return &handle; }
@@ -165,10 +192,14 @@ void staging_of_tables() {
         else check(off_hdr + 8 > budget && s.lds_end == t.off_alts && s.n_near == 0, what + ": a section less than there is room for");
       }
 }
-// Where the headers of a grammar's tables begin (the grammar's text from stdin, its root rule "root").
-void headers_begin() {
+std::string input() {
   std::string text;
   for (int c; (c = std::getchar()) != EOF;) text += (char)c;
+  return text;
+}
+// Where the headers of a grammar's tables begin (the grammar's text from stdin, its root rule "root").
+void headers_begin() {
+  const std::string text = input();
   xgm_grammar* g = nullptr;
   xgm_vocab* v = nullptr;
   xgm_cache* cache = nullptr;
@@ -179,6 +210,32 @@ void headers_begin() {
         XGM(xgm_cache_build)(g, v, nullptr, &cache) == XGM_OK, XGM(xgm_last_error)());
   std::printf("%u\n", tables.off_hdr);
 }
+// Compiles of a grammar in `callers` threads, confined to `cpus` CPUs: how many threads the compiles started, and how many
+// there were at the same time.
+void compile_threads(int cpus, int callers) {
+  const std::string text = input();
+  cpu_set_t all, some;
+  CPU_ZERO(&some);
+  check(sched_getaffinity(0, sizeof(all), &all) == 0, "sched_getaffinity");
+  for (int k = 0, n = 0; k < CPU_SETSIZE && n < cpus; ++k)
+    if (CPU_ISSET(k, &all)) { CPU_SET(k, &some); ++n; }
+  if (CPU_COUNT(&some) < cpus) { std::printf("-1 -1\n"); return; }
+  check(sched_setaffinity(0, sizeof(some), &some) == 0, "sched_setaffinity");
+  auto work = [&] {
+    own = false;
+    for (int k = 0; k < 20; ++k) {
+      xgm_grammar* g = nullptr;
+      if (XGM(xgm_grammar_compile)(text.data(), text.size(), "root", &g) != XGM_OK) std::exit(3);
+      XGM(xgm_grammar_destroy)(g);
+    }
+  };
+  std::vector<std::thread> threads;
+  own = true;
+  for (int k = 1; k < callers; ++k) threads.emplace_back(work);
+  work();
+  for (std::thread& t : threads) t.join();
+  std::printf("%d %d\n", started.load(), most.load());
+}
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -188,6 +245,7 @@ int main(int argc, char** argv) {
   if (what == "moves") moves_that_fail();
   else if (what == "staging") staging_of_tables();
   else if (what == "headers") headers_begin();
+  else if (what == "threads" && argc == 5) compile_threads(std::atoi(argv[3]), std::atoi(argv[4]));
   else if (what == "too_many_moves") moves_that_are_too_many();
   else { std::fprintf(stderr, "no check of this name: %s\n", what.c_str()); return 2; }
   std::printf("%s: %d failures\n", what.c_str(), failures);

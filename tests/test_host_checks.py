@@ -22,8 +22,8 @@ def host_checks(tmp_path_factory):
     subprocess.run([os.environ.get("CXX", "g++"), "-O1", "-std=c++17", "-Wall", "-rdynamic", "-pthread", "-D__HIP_PLATFORM_AMD__", "-isystem", include,
                     os.path.join(HERE, "host_checks.cpp"), "-o", out, "-ldl"], check=True)
 
-    def run(what, text=""):
-        done = subprocess.run([out, lib_build.LIB, what], input=text, capture_output=True, text=True, timeout=120)
+    def run(*what, text=""):
+        done = subprocess.run([out, lib_build.LIB, *map(str, what)], input=text, capture_output=True, text=True, timeout=120)
         assert done.returncode == 0, done.stdout + done.stderr
         return done.stdout
 
@@ -55,7 +55,21 @@ def test_tables_that_count_as_staged_have_a_header_staged(host_checks):
 
 @pytest.mark.parametrize("room", EXACT)
 def test_grammars_whose_tables_fill_the_room_exactly(host_checks, room):
-    assert int(host_checks("headers", nested_grammar(*EXACT[room])).split()[0]) == room
+    assert int(host_checks("headers", text=nested_grammar(*EXACT[room])).split()[0]) == room
+
+
+def many_rules(n):
+    return "root ::= " + " | ".join(f"f{k}" for k in range(n)) + "\n" + "".join(f'f{k} ::= "{chr(97 + k % 26) * 110}{k}"\n' for k in range(n))
+
+
+@pytest.mark.parametrize("cpus, callers, most", [(1, 1, 0), (1, 3, 0), (2, 1, 1), (2, 2, 1), (2, 4, 1), (4, 1, 3), (4, 4, 3)])
+def test_compiles_start_no_more_threads_than_there_are_cpus(host_checks, cpus, callers, most):
+    """Callers and helpers together: a compile that is alone for a moment may start one while others have not begun."""
+    started, at_once = map(int, host_checks("threads", cpus, callers, text=many_rules(200)).split()[:2])
+    if started < 0:
+        pytest.skip("not as many CPUs")
+    assert at_once <= most
+    assert (started > 0) == (most > 0) or callers > 1
 
 
 def test_kernels_keep_their_registers():
