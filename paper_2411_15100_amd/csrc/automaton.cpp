@@ -9,6 +9,7 @@
 #include <exception>
 #include <functional>
 #include <iterator>
+#include <optional>
 #include <string_view>
 #include <system_error>
 #include <thread>
@@ -254,15 +255,18 @@ class Parser {
       if (!(t_[p_].kind == T_IDENT && t_[p_ + 1].kind == T_DEFINE)) parse_fail(t_[p_].pos, "expected 'name ::='");
       int r = rule_index_[lexed_.text_of(t_[p_])];
       p_ += 2;
+      const int before = nfa_.size();
       Frag f = alternatives();
       if (t_[p_].kind == T_RP) parse_fail(t_[p_].pos, "unbalanced ')'");
       start_[r] = f.in;
       accept_[r] = f.out;
+      largest_ = std::max(largest_, nfa_.size() - before);
     }
   }
   std::vector<std::string> names_;
   std::unordered_map<std::string_view, int> rule_index_;
   std::vector<int> start_, accept_;
+  int largest_ = 1;  // states of the largest rule
 
  private:
   const Lexed& lexed_;
@@ -939,14 +943,14 @@ class Helpers {
 };
 
 // The minimal DFA of every productive rule.  Rules do not depend on each other: in a large grammar several threads take them
-// in turn (36 KB schema grammar with 239 rules: 720 of 1660 us by one thread; the compile takes 890 us with three more, and
-// what does not go into the tables made beside them, where one compile follows the other, 1370 instead of 1756 as a part of
-// builds, where the threads' cores have been idle).
+// in turn, as many as the largest rule (of `largest` states) leaves work for.  36 KB schema grammar with 239 rules: 720 of 1660
+// us by one thread; the compile takes 890 us with three more, and what does not go into the tables made beside them, where one
+// compile follows the other, 1370 instead of 1756 as a part of builds, where the threads' cores have been idle.
 constexpr int kManyStates = 8000;  // of the NFA: some 250 us of work
 constexpr int kManyNodes = 4000;    // of the automaton: what is made beside the tables takes some 50 us
 constexpr int kCompileHelpers = 3;
 std::vector<Dfa> determinize(const Nfa& nfa, const std::vector<int>& start, const std::vector<int>& accept, const std::vector<char>& productive,
-                             const std::vector<char>& nullable) {
+                             const std::vector<char>& nullable, int largest) {
   const int R = (int)start.size();
   std::vector<Dfa> dfa(R);
   std::atomic<int> next{0};
@@ -954,12 +958,13 @@ std::vector<Dfa> determinize(const Nfa& nfa, const std::vector<int>& start, cons
   std::exception_ptr failure;
   auto work = [&] {
     try {
-      Determinizer determinizer(nfa, productive, nullable);
+      std::optional<Determinizer> determinizer;  // (as large as the NFA: made when there is a rule for it)
       Minimizer minimizer;
       Dfa d;
-      for (int r; (r = next.fetch_add(1)) < R;) {
+      for (int r; !failed && (r = next.fetch_add(1)) < R;) {
         if (!productive[r]) continue;
-        determinizer.run(start[r], accept[r], d);
+        if (!determinizer) determinizer.emplace(nfa, productive, nullable);
+        determinizer->run(start[r], accept[r], d);
         dfa[r] = minimizer.run(d);
       }
     } catch (...) {
@@ -967,7 +972,7 @@ std::vector<Dfa> determinize(const Nfa& nfa, const std::vector<int>& start, cons
     }
   };
   Helpers helpers;
-  if (nfa.size() >= kManyStates) helpers.start(kCompileHelpers, work);
+  if (nfa.size() >= kManyStates) helpers.start(std::min(kCompileHelpers, nfa.size() / largest - 1), work);
   work();
   helpers.join();
   if (failed) std::rethrow_exception(failure);
@@ -1002,7 +1007,7 @@ Automaton compile_grammar(const std::string& text, const std::string& root) {
   if (!productive[root_rule]) throw Failure(XGM_ERR_UNPRODUCTIVE, "grammar: the root rule derives no string");
   const std::vector<char> nullable = derivable(nfa, parser.start_, parser.accept_, [](const NEdge& e) { return e.kind != 1; });
 
-  const std::vector<Dfa> dfa = determinize(nfa, parser.start_, parser.accept_, productive, nullable);
+  const std::vector<Dfa> dfa = determinize(nfa, parser.start_, parser.accept_, productive, nullable, parser.largest_);
 
   // rules reachable from the root
   std::vector<int> new_index(R, -1), order;

@@ -72,6 +72,18 @@ def test_compiles_start_no_more_threads_than_there_are_cpus(host_checks, cpus, c
     assert (started > 0) == (most > 0) or callers > 1
 
 
+# Rules of so many bytes each: the largest decides how long determinising takes, and helpers are for what is left.
+@pytest.mark.parametrize("sizes, helpers", [([9000], 0), ([9000] + [100] * 4, 0), ([5000] * 2, 1), ([4500, 4500, 2900], 1), ([3000] * 3, 2), ([2500] * 4, 3), ([1000] * 12, 3)])
+def test_compiles_start_as_many_threads_as_there_is_work_for(host_checks, sizes, helpers):
+    text = "root ::= " + " | ".join(f"f{k}" for k in range(len(sizes))) + "\n"
+    text += "".join(f'f{k} ::= "' + "".join(chr(97 + (5 * j + j // 26 + k) % 26) for j in range(n)) + '"\n' for k, n in enumerate(sizes))
+    started, at_once = map(int, host_checks("threads", 4, 1, text=text).split()[:2])
+    if started < 0:
+        pytest.skip("not as many CPUs")
+    assert started == 20 * (helpers + 1)  # (20 compiles; one thread more makes what is not in the tables)
+    assert at_once <= max(helpers, 1)
+
+
 def test_kernels_keep_their_registers():
     """No kernel keeps vector registers in memory; the fills that walk move a few dozen scalar registers to lanes of vector
     registers and back (up to 38 today), not a hundred: their walks wait for every instruction."""
