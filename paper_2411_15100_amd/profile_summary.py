@@ -25,7 +25,7 @@ import sys
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 KERNEL_SOURCES = ["kernels.hip", "kernels.hpp", "walk.hpp"]
 # the kernels of the serving step of bench.py (no cache of its batch has walk entries), by their names in a trace
-STEP_KERNELS = {"one launch": "fill_kernel<false, 2, 0u, false, false>", "fill": "fill_kernel<false, 0, 0u, false, false>",
+STEP_KERNELS = {"one launch": "fill_kernel<false, 2, 0u, false, 0>", "fill": "fill_kernel<false, 0, 0u, false, 0>",
                 "apply": "apply_kernel<2>"}
 COPY_KERNEL = "bfloat16_copy_kernel"         # torch's fp32 -> bf16 copy of one logits buffer
 
