@@ -1488,7 +1488,9 @@ struct UniformFrames {
 // three rounds of LDS reads (header, shape and FOLLOW word, target), and one word of it decides whether the step is a move:
 // 400 clocks for a move, where the same lookup made of comparisons and masks, with all runs looked for in every step, took
 // 1106 (a token of 11 bytes in a keyword of the scripting grammar 13236 and 6870, one of 14 bytes through five frames of a
-// schema grammar 34200 and 21900; a pass of 24 rows of the C/SQL-like grammar 30.6 and 25.3 us).
+// schema grammar 34200 and 21900).  Mask and bf16 logits in one launch with that lookup take 1.00 to 1.23 times as long for 24 rows of
+// the C/SQL-like grammar and 128256 tokens (six draws of states, 1.12 in the mean), 1.01 to 1.17 for 64 (four), 1.01 to 1.14 for 8
+// rows of the scripting grammar and 32000 tokens (six), 1.01 to 1.03 for 32 and 128256 (three).
 template <class Note>
 __device__ __forceinline__ int walk_wave(const LdsTabT<true, true>& T, WaveMem& mem, const uint4 tk, const uint8_t* ext, const int len,
                                          const uint32_t start_node, const UniformFrames& live, const uint32_t depth, const Note& note,
@@ -1999,7 +2001,7 @@ __global__ __launch_bounds__(fill_threads(PARTS), WALKS ? (PARTS > kFillThreads 
         row.epoch = rows[b].epoch;
       }
       unsigned long long my_steps = 0;
-      stage_tables_async(tab, smem, kThreads);
+      stage_tables_async(tab, smem, kThreads);  // (through registers: launches of 8 to 64 rows that walk take 1.01 to 1.04 times as long)
       if (row.n_frames <= kFillFramesLds) {
 #pragma unroll 1
         for (uint32_t k = tid; k < row.n_frames; k += kThreads) sm.live[k] = row.frames[row.frame0 + k];
@@ -2150,9 +2152,11 @@ __device__ __forceinline__ int compare_candidates(const AcceptShared& sm, uint32
 // are there (4940 with the pieces of the tables one after the other), walk 3700 (4580), stacks 4400 (5910, with a wave's sum
 // for the first stack too and the DevCache's pointers read one by one where they were needed), the rest 360; a JSON row
 // that stays in a string 9280 in all, before 11300.  The launch lasts as long as its slowest row (a twelve-byte token
-// through several frames: 17 000 clocks of walk, 27 000 before walk_wave took moves in a loop of their own).  A pass of four
-// fills and three accepts of 128 schema rows 77.2 -> 66.9 us, one of five and four of 8 rows of the scripting grammar 65.7
-// -> 58.3, of one JSON row 47.3 -> 44.6 (walk_wave's part included).
+// through several frames: 17 000 clocks of walk, 27 000 before walk_wave took moves in a loop of their own).  Before all of this
+// (walk_wave's part included) a pass of four fills and three accepts of 128 schema rows took 1.11 to 1.20 times as long, one of
+// five and four of 8 rows of the scripting grammar 1.09 to 1.15, of one JSON row 1.05 to 1.14 (four draws of states each: 62 to
+// 73, 50 to 64 and 44 to 47 us now).  Of that, without the tables straight into LDS 1.00 to 1.02, with the DevCache read where
+// it lies 1.02 to 1.04, with __syncthreads() for the last barrier 0.99 to 1.03: no difference beyond the spread.
 // With one lane per stack, tables in global memory and stacks copied
 // by that lane: 17.9 us for the launch; one JSON row 8.2 us, now 5.7;
 // rows of the C/SQL-like grammar, 90 frames deep, 46 us in the mean, now 10.
