@@ -1667,7 +1667,7 @@ constexpr int fill_threads(int parts) { return parts ? parts : kFillThreads; }
 constexpr int kFillFramesLds = 1024;            // live frames kept in LDS (deeper stacks: global memory)
 
 // One workgroup of 4 waves serves one request and one segment of 8192 token
-// ids = 256 mask words, which it owns in LDS:
+// ids = 256 mask words, which it owns in LDS (PARTS: four workgroups a quarter each):
 //   1. every word = OR of the accepted bitsets of the tops of all stacks that
 //      keep one (Algorithm 1: the result is the union over the parallel
 //      stacks); the stop tokens if the text may end;
@@ -1690,8 +1690,8 @@ constexpr int kFillFramesLds = 1024;            // live frames kept in LDS (deep
 // WALKS = false: no mask cache of the batch has a walk entry (a cache knows:
 // schema grammars have none) and step 3 is left out; the kernel then fits eight
 // workgroups per compute unit (registers, LDS) and needs no scratch memory.
-// WALKS = true: up to seven workgroups per compute unit (scalar registers), as many
-// as have room for the batch's tables in LDS (four at 31 KB).  With one
+// WALKS = true: up to seven workgroups of 256 threads per compute unit (scalar registers),
+// as many as have room for the batch's tables in LDS (four at 31 KB), or three of 512.  With one
 // kernel for both the walk was a function of its own, which spilled in its
 // inner loop and cost 5 us before its first step: the fill of a
 // row that walks a handful of tokens (C/SQL-like grammar, 128256 tokens, one row)
