@@ -9,7 +9,6 @@
 #include <exception>
 #include <functional>
 #include <iterator>
-#include <optional>
 #include <string_view>
 #include <system_error>
 #include <thread>
@@ -958,13 +957,14 @@ std::vector<Dfa> determinize(const Nfa& nfa, const std::vector<int>& start, cons
   std::exception_ptr failure;
   auto work = [&] {
     try {
-      std::optional<Determinizer> determinizer;  // (as large as the NFA: made when there is a rule for it)
+      int r = next.fetch_add(1);
+      if (r >= R) return;  // (the determinizer is as large as the NFA: made when there is a rule for it)
+      Determinizer determinizer(nfa, productive, nullable);
       Minimizer minimizer;
       Dfa d;
-      for (int r; !failed && (r = next.fetch_add(1)) < R;) {
+      for (; r < R && !failed; r = next.fetch_add(1)) {
         if (!productive[r]) continue;
-        if (!determinizer) determinizer.emplace(nfa, productive, nullable);
-        determinizer->run(start[r], accept[r], d);
+        determinizer.run(start[r], accept[r], d);
         dfa[r] = minimizer.run(d);
       }
     } catch (...) {
